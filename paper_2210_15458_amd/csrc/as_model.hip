@@ -605,32 +605,156 @@ __global__ __launch_bounds__(256, 2) void bigram_gemm_bf16(const uint16_t *__res
     do_pass(std::integral_constant<int, 3>{});
 }
 
-// Plain dot products for what the MFMA kernel does not take: fp32 weights, or a
-// rank d that is not a multiple of its K step (small models only).
+// ---- vector kernel: what the MFMA kernels do not take (fp32 weights, or a rank d that is not a multiple of
+// their K step), any size and alignment ------------------------------------------------------------------
+//
+// Every logit is one fp32 fused-multiply-add chain over k in ascending order, from zero.  The matrix pipes could
+// run the fp32 products, but not in that order, and the chain is what keeps a logit the same whatever tile it is
+// computed in.  So the bound is the vector FMA rate (one wave64 FMA per 4 cycles and SIMD), and the kernel's job is
+// to feed it: block tile 16*TM x 16*TN over K steps of 32, a thread TM x TN outputs in registers, operands through
+// LDS with K along the rows (a thread's 4 consecutive rows or columns are one 16-byte read; within a wave 4
+// distinct A pieces are broadcast and 16 B pieces lie in consecutive banks), the next K step's elements in
+// registers while this one is worked on (four K steps in the small form, whose blocks run one to a SIMD and have
+// nothing else to hide a load behind).  One launch in fp32, against the form before it (one thread per logit, both
+// operands from the caches at every k): 256 x 4100 x 128 12.1 us against 426, 64 x 1000 x 100 8.4 against 18.4,
+// 1024 x 32128 x 512 482 us against 73 ms (70 TFLOP/s, 89 % of the FMA rate), 64 x 16 x 8 3.9 either way.
+constexpr int VK = 32;
 __device__ __forceinline__ float widen(float x) { return x; }
 __device__ __forceinline__ float widen(uint16_t h) { return __builtin_bit_cast(float, (uint32_t)h << 16); }
 
-template <class WT, class OutT>
-__global__ __launch_bounds__(256) void bigram_dot(const WT *__restrict__ E, const WT *__restrict__ Ut,
-                                                  const int32_t *__restrict__ prev, int64_t R, int32_t V,
-                                                  int32_t d, float alpha, OutT *__restrict__ C, int64_t ldc)
+template <class WT, class OutT, int TM, int TN>
+__global__ __launch_bounds__(256) void bigram_gemm_vec(const WT *__restrict__ E, const WT *__restrict__ Ut,
+                                                       const int32_t *__restrict__ prev, int64_t R, int32_t V,
+                                                       int32_t d, float alpha, OutT *__restrict__ C, int64_t ldc)
 {
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= R * V) return;
-    const int64_t r = idx / V, v = idx % V;
-    const WT *a = E + (int64_t)clamp_token(prev[r], V) * d, *b = Ut + v * d;
-    float acc = 0.f;
-    for (int k = 0; k < d; ++k) acc = fmaf(widen(a[k]), widen(b[k]), acc);
-    C[r * ldc + v] = to_out<OutT>(acc * alpha);
+    static_assert(TM % 4 == 0 && TN % 4 == 0, "a thread's outputs come in runs of 4");
+    constexpr int MT = 16 * TM, NT = 16 * TN, MI = MT / 8, NI = NT / 8;
+    constexpr int AHEAD = TM == 4 ? 4 : 1;                    // K steps requested ahead of the one worked on
+    constexpr int KB = TM == 4 ? 4 : 1;
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    __shared__ __attribute__((aligned(16))) float sA[VK][MT + 4], sB[VK][NT + 4];
+    const int tid = threadIdx.x;
+    const int64_t m0 = (int64_t)blockIdx.x * MT, n0 = (int64_t)blockIdx.y * NT;
+
+    // loader: element k = tid & 31 of tile rows (tid >> 5) + 8*i
+    const int lk = tid & 31, lr = tid >> 5;
+    const WT *pa[MI], *pb[NI];
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+        int64_t m = m0 + lr + 8 * i;
+        if (m > R - 1) m = R - 1;
+        pa[i] = E + (int64_t)clamp_token(prev[m], V) * d;
+    }
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+        int64_t n = n0 + lr + 8 * i;
+        if (n > V - 1) n = V - 1;
+        pb[i] = Ut + n * d;
+    }
+    WT ra[AHEAD][MI], rb[AHEAD][NI];
+    auto request = [&](int k0, auto slot_c) __attribute__((always_inline)) {
+        constexpr int slot = decltype(slot_c)::value;
+        const int k = k0 + lk < d ? k0 + lk : d - 1;
+#pragma unroll
+        for (int i = 0; i < MI; ++i) ra[slot][i] = pa[i][k];
+#pragma unroll
+        for (int i = 0; i < NI; ++i) rb[slot][i] = pb[i][k];
+    };
+    float acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = 0.f;
+    const int tm = (tid >> 4) * 4, tn = (tid & 15) * 4;      // first row / column of the thread's runs
+    auto step = [&](int k0, auto slot_c) __attribute__((always_inline)) {
+        constexpr int slot = decltype(slot_c)::value;
+        const bool in = k0 + lk < d;                          // past the rank: zeros, which leave a chain as it is
+        if (k0 != 0) __syncthreads();
+#pragma unroll
+        for (int i = 0; i < MI; ++i) sA[lk][lr + 8 * i] = in ? widen(ra[slot][i]) : 0.f;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) sB[lk][lr + 8 * i] = in ? widen(rb[slot][i]) : 0.f;
+        __syncthreads();
+        if (k0 + AHEAD * VK < d) request(k0 + AHEAD * VK, slot_c);
+        // KB values of k at a time, the next KB's pieces on their way from LDS meanwhile (left to itself the compiler
+        // reads one k, waits and multiplies: 230 cycles a k where the products take 64)
+        float xa[KB][TM], xb[KB][TN], ya[KB][TM], yb[KB][TN];
+        auto read = [&](float (&a)[KB][TM], float (&b)[KB][TN], int k) __attribute__((always_inline)) {
+#pragma unroll
+            for (int q = 0; q < KB; ++q) {
+#pragma unroll
+                for (int g = 0; g < TM / 4; ++g) {
+                    const f32x4 v = *reinterpret_cast<const f32x4 *>(&sA[k + q][g * 64 + tm]);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) a[q][4 * g + e] = v[e];
+                }
+#pragma unroll
+                for (int g = 0; g < TN / 4; ++g) {
+                    const f32x4 v = *reinterpret_cast<const f32x4 *>(&sB[k + q][g * 64 + tn]);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) b[q][4 * g + e] = v[e];
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto multiply = [&](const float (&a)[KB][TM], const float (&b)[KB][TN]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int q = 0; q < KB; ++q)
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) acc[i][j] = fmaf(a[q][i], b[q][j], acc[i][j]);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        const int kn = d - k0 < VK ? d - k0 : VK;             // (2*KB at a time; the rest of the last ones are zeros)
+        read(xa, xb, 0);
+        for (int k = 0; k < kn; k += 2 * KB) {
+            read(ya, yb, k + KB);
+            multiply(xa, xb);
+            read(xa, xb, k + 2 * KB < VK ? k + 2 * KB : 0);
+            multiply(ya, yb);
+        }
+    };
+    if constexpr (AHEAD == 4) {
+        request(0, std::integral_constant<int, 0>{});
+        request(VK, std::integral_constant<int, 1>{});
+        request(2 * VK, std::integral_constant<int, 2>{});
+        request(3 * VK, std::integral_constant<int, 3>{});
+        for (int k0 = 0; k0 < d; k0 += 4 * VK) {
+            step(k0, std::integral_constant<int, 0>{});
+            if (k0 + VK < d) step(k0 + VK, std::integral_constant<int, 1>{});
+            if (k0 + 2 * VK < d) step(k0 + 2 * VK, std::integral_constant<int, 2>{});
+            if (k0 + 3 * VK < d) step(k0 + 3 * VK, std::integral_constant<int, 3>{});
+        }
+    } else {
+        request(0, std::integral_constant<int, 0>{});
+        for (int k0 = 0; k0 < d; k0 += VK) step(k0, std::integral_constant<int, 0>{});
+    }
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        const int64_t m = m0 + (i / 4) * 64 + tm + (i & 3);
+        if (m >= R) continue;
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const int64_t n = n0 + (j / 4) * 64 + tn + (j & 3);
+            if (n < V) C[m * ldc + n] = to_out<OutT>(acc[i][j] * alpha);
+        }
+    }
 }
 
 template <class WT, class OutT>
-void launch_dot(as_ctx *ctx, const as_model *m, const int32_t *prev, int64_t rows, void *out, int64_t ld,
-                float alpha)
+void launch_vec(as_ctx *ctx, const as_model *m, const int32_t *prev, int64_t rows, void *out, int64_t ld, float alpha)
 {
-    const int64_t n = rows * (int64_t)m->V;
-    launch(ctx, kKernelLogits, bigram_dot<WT, OutT>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0,
-           (const WT *)m->E, (const WT *)m->Ut, prev, rows, m->V, m->d, alpha, (OutT *)out, ld);
+    // 128 x 128 tiles do twice the products per LDS byte of 64 x 64 ones; they pay once there are enough of
+    // them for two blocks on every CU
+    const dim3 big((unsigned)((rows + 127) / 128), (unsigned)((m->V + 127) / 128));
+    const dim3 small((unsigned)((rows + 63) / 64), (unsigned)((m->V + 63) / 64));
+    if ((int64_t)big.x * big.y >= 2 * (int64_t)ctx->num_cus)
+        launch(ctx, kKernelLogits, bigram_gemm_vec<WT, OutT, 8, 8>, big, dim3(256), 0, (const WT *)m->E,
+               (const WT *)m->Ut, prev, rows, m->V, m->d, alpha, (OutT *)out, ld);
+    else
+        launch(ctx, kKernelLogits, bigram_gemm_vec<WT, OutT, 4, 4>, small, dim3(256), 0, (const WT *)m->E,
+               (const WT *)m->Ut, prev, rows, m->V, m->d, alpha, (OutT *)out, ld);
 }
 
 // ------------------------------------------------------------------ estimator
@@ -744,14 +868,12 @@ as_status launch_bigram_logits(as_ctx *ctx, const as_model *m, const int32_t *pr
                        alpha, (float *)logits_out, ld, vec_store);
         }
     } else {
-        if ((rows * (int64_t)m->V + 255) / 256 > 0x7fffffffLL)
-            return fail(ctx, AS_ERR_UNSUPPORTED, "logits grid too large");
         if (m->wdtype == AS_BF16) {
-            if (ctx->dtype == AS_BF16) launch_dot<uint16_t, uint16_t>(ctx, m, prev, rows, logits_out, ld, alpha);
-            else launch_dot<uint16_t, float>(ctx, m, prev, rows, logits_out, ld, alpha);
+            if (ctx->dtype == AS_BF16) launch_vec<uint16_t, uint16_t>(ctx, m, prev, rows, logits_out, ld, alpha);
+            else launch_vec<uint16_t, float>(ctx, m, prev, rows, logits_out, ld, alpha);
         } else {
-            if (ctx->dtype == AS_BF16) launch_dot<float, uint16_t>(ctx, m, prev, rows, logits_out, ld, alpha);
-            else launch_dot<float, float>(ctx, m, prev, rows, logits_out, ld, alpha);
+            if (ctx->dtype == AS_BF16) launch_vec<float, uint16_t>(ctx, m, prev, rows, logits_out, ld, alpha);
+            else launch_vec<float, float>(ctx, m, prev, rows, logits_out, ld, alpha);
         }
     }
     AS_HIP_TRY(ctx, hipGetLastError());

@@ -1,0 +1,56 @@
+"""GPU parity of the logits kernels at the edges of their tiles: against fp64, and a row's logits must not depend on
+which other rows are computed with it (every kernel that can take a row runs the same products in the same order)."""
+import math
+
+import numpy as np
+import pytest
+
+from paper_2210_15458_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+# (V, d, weights, logits, R): the vector kernel's small tiles (64 x 64: one short, exact, one over, in each
+# direction; ranks below, at and over its K step and over the four steps it requests ahead), its large ones
+_VEC = [(63, 7, "f32", "f32", 1), (64, 32, "f32", "f32", 64), (65, 33, "f32", "bf16", 65), (1001, 130, "f32", "f32", 3),
+        (700, 72, "bf16", "f32", 100), (333, 257, "bf16", "bf16", 129), (16500, 40, "f32", "f32", 520),
+        (8200, 31, "f32", "bf16", 1030)]
+
+
+def _logits(model, prev, V, ldt, rows):
+    import torch
+    from paper_2210_15458_amd import binding as B
+    from gpu_util import from_dev_logits
+    ctx = B.Ctx(rows, V, torch.float32 if ldt == "f32" else torch.bfloat16)
+    ld = (V + 7) // 8 * 8 + 8
+    out = torch.full((rows, ld), 7.0, dtype=ctx.torch_dtype, device="cuda")
+    B.as_bigram_logits(ctx, model, torch.from_numpy(prev).cuda(), out)
+    torch.cuda.synchronize()
+    ctx.close()
+    got = from_dev_logits(out)
+    got = got if ldt == "f32" else synth.bf16_bits_to_f32(got)
+    assert np.all(got[:, V:] == 7.0)                    # padding columns untouched
+    return got[:, :V]
+
+
+@pytest.mark.parametrize("V,d,wdt,ldt,R", _VEC)
+def test_logits_tile_edges(V, d, wdt, ldt, R):
+    import torch
+    from paper_2210_15458_amd import binding as B
+    from gpu_util import to_dev_logits
+    E, U = synth.bigram_weights(V, d, seed=V + d, dtype=wdt)
+    model = B.Model(to_dev_logits(E), to_dev_logits(U), scale=3.0)
+    prev = np.random.default_rng(R).integers(0, V, R).astype(np.int32)
+    got = _logits(model, prev, V, ldt, R)
+    Ew = (synth.bf16_bits_to_f32(E) if wdt == "bf16" else E).astype(np.float64)[prev]
+    Uw = (synth.bf16_bits_to_f32(U) if wdt == "bf16" else U).astype(np.float64)
+    ref = (Ew @ Uw) * (3.0 / math.sqrt(d))
+    # fp32 accumulation of d terms (each sum rounds by at most half an ulp of the sum of magnitudes), then one
+    # rounding to the storage type
+    tol = 4 * d * 2.0 ** -24 * (np.abs(Ew) @ np.abs(Uw)) * (3.0 / math.sqrt(d)) + 1e-30
+    if ldt == "bf16":
+        tol = tol + np.abs(ref) * 2.0 ** -8
+    err = np.abs(got - ref)
+    assert np.all(err <= tol), float((err / tol).max())
+    for r in {0, R // 2, R - 1}:
+        assert np.array_equal(_logits(model, prev[r:r + 1], V, ldt, 1)[0], got[r])
+    model.close()

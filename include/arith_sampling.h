@@ -93,9 +93,9 @@ const char *as_last_error(const as_ctx *ctx);
  *   AS_TUNE_GEMM_SHAPE  logits kernel: 1 = the 128x256 tile kernel instead of
  *                       the persistent one
  *   AS_TUNE_THR_PATH    keep-threshold kernel: 1 = the radix select instead of
- *                       the register-resident / streamed kernels; 2 = the
- *                       register-resident kernel also where the single-tile
- *                       top-k and nucleus kernels apply
+ *                       the others; 2 = the 256-thread register-resident
+ *                       kernel wherever the row fits it; 3 = the kernel for
+ *                       any row (256 to 1024 threads each) for every row
  *   AS_TUNE_GEMM_GM     persistent logits kernel with more row tiles than
  *                       workers: workers of one XCD along the rows (a divisor
  *                       of the workers per XCD; otherwise ignored)

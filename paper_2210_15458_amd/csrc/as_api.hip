@@ -98,8 +98,9 @@ static as_status row_ids_in_range(as_ctx *ctx, const int32_t *&row_ids, int64_t 
 constexpr int kMaxDevices = 64;
 static std::mutex g_static_mu;
 static float *g_static_ptr[kMaxDevices] = {};
+static int g_static_cus[kMaxDevices] = {};
 
-static as_status static_scratch(int *device_out, float **ptr_out)
+static as_status static_scratch(int *device_out, float **ptr_out, int *cus_out)
 {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -113,10 +114,13 @@ static as_status static_scratch(int *device_out, float **ptr_out)
             (void)hipGetLastError();
             return hip_fail(nullptr, e, "hipGetSymbolAddress(scratch)");
         }
+        e = hipDeviceGetAttribute(&g_static_cus[dev], hipDeviceAttributeMultiprocessorCount, dev);
+        if (e != hipSuccess) return hip_fail(nullptr, e, "hipDeviceGetAttribute");
         g_static_ptr[dev] = static_cast<float *>(p);
     }
     *device_out = dev;
     *ptr_out = g_static_ptr[dev];
+    *cus_out = g_static_cus[dev];
     return AS_OK;
 }
 
@@ -308,7 +312,7 @@ as_status as_step_static(const void *logits, as_dtype logits_dtype, int64_t rows
     if (isnan(top_p)) return fail(nullptr, AS_ERR_INVALID_ARG, "top_p is NaN");
     // a context that lives for this call only and owns nothing: its threshold workspace is the static array
     as_ctx c;
-    as_status st = static_scratch(&c.device, &c.thr);
+    as_status st = static_scratch(&c.device, &c.thr, &c.num_cus);
     if (st != AS_OK) return st;
     c.stream = static_cast<hipStream_t>(hip_stream);
     c.max_rows = kStaticMaxRows;

@@ -15,13 +15,13 @@
 //
 // The radix select reads the row once per digit and its histograms are hot in a
 // few bins (the leading digit of a bell-shaped row is mostly sign and exponent),
-// so it is the general path only.  Rows of up to 32768 logits that can be read in
-// 16-byte pieces take the resident path further down: the row is loaded once into
-// registers, a coarse histogram with evenly filled bins finds the neighbourhood of
-// the answer, and the few logits in that neighbourhood are ranked exactly.  Longer
-// rows take the same method with passes over memory instead (the streamed path at
-// the end).  All paths use the same keys and the same fixed-point masses, so they
-// return the same threshold.
+// so it is left as a fall-back only.  The resident path further down loads a row of up to
+// 32768 logits once into registers, a coarse histogram with evenly filled bins finds
+// the neighbourhood of the answer, and the few logits in that neighbourhood are
+// ranked exactly; the streamed path does the same with passes over memory.  Both use
+// the same keys and the same fixed-point masses, so they return the same threshold.
+// as_wide.hip has the form of this for any other row; the rules at the end of this file
+// say which rows go where.
 #include <type_traits>
 
 #include "as_common.hpp"
@@ -1052,16 +1052,12 @@ __global__ __launch_bounds__(kThreads) void threshold_resident_kernel(const void
 
 // ------------------------------------------------------------ streamed path
 //
-// Rows too long for the registers (more than 32768 logits) or not laid out in whole 16-byte pieces, k at most
-// half the thread count: the method of the resident kernel with every visit of the row a pass over memory, four pieces
-// per thread in flight.  Top-k with k up to 128 takes two passes (thread maxima, then the logits at or above
-// the bound they give), any larger k three (maximum, count per coarse bin, the logits of the bin that holds
-// the k-th), the nucleus alone three (maximum, mass per coarse bin, the logits of the bin where the nucleus
-// closes); the nucleus after top-k works on the candidate table.  Same keys, same fixed-point masses, same
-// fall-back as the other two kernels, so the same threshold.
-// KMODE 0: no top-k; 1: bound from the thread maxima (k at most half the thread count); 2: any k, by counts per
-// coarse bin, the way the nucleus goes by mass per coarse bin.
-template <int DT, int KMODE, bool HAS_P>
+// Top-k with k above half the thread count on long rows, many of them: the method of the resident kernel with every
+// visit of the row a pass over memory, four pieces per thread in flight.  Three passes (maximum, count per coarse
+// bin, the logits of the bin that holds the k-th), and two more for the nucleus after it (mass per coarse bin, the
+// logits of the bin where it closes).  Same keys, same fixed-point masses, same fall-back as the other two kernels,
+// so the same threshold.
+template <int DT, bool HAS_P>
 __global__ __launch_bounds__(kThreads) void threshold_stream_kernel(const void *logits, int64_t ld, int32_t V,
                                                                     const uint8_t *finished_in,
                                                                     const int32_t *row_ids, float temp,
@@ -1114,30 +1110,9 @@ __global__ __launch_bounds__(kThreads) void threshold_stream_kernel(const void *
             }
         }
     };
-    auto umax = [](uint32_t a, uint32_t b) { return a > b ? a : b; };
-
     uint32_t thr_key = 0;
     bool fall = false;
     uint32_t ncand = 0;
-
-    constexpr bool HAS_K = KMODE == 1;
-    if (HAS_K) {
-        // the k-th largest of the thread maxima bounds the k-th largest logit from below
-        uint32_t tmax = 0;
-        sweep([&](uint32_t key, float) __attribute__((always_inline)) { tmax = umax(tmax, key); });
-        const uint32_t lkey = bound_from_thread_maxima(sh, tmax, top_k);
-        sweep([&](uint32_t key, float) __attribute__((always_inline)) {
-            if (key >= lkey) {
-                const uint32_t i = atomicAdd(&sh.ncand, 1u);
-                if (i < (uint32_t)kCandCap) sh.ckey[i] = key;
-            }
-        });
-        __syncthreads();
-        ncand = sh.ncand;
-        if (ncand > (uint32_t)kCandCap) fall = true;
-        else thr_key = kth_of_candidates(sh, ncand, top_k);
-        __syncthreads();
-    }
 
     const float k = 1.44269504088896340736f / temp;
 
@@ -1199,24 +1174,13 @@ __global__ __launch_bounds__(kThreads) void threshold_stream_kernel(const void *
         thr_key = closing_group(sh, ncand, before, need, thr_key);
     };
 
-    if (KMODE == 2) {
-        // top-k for any k: count the logits per coarse bin from the top until k are reached
-        const float nr = row_reference();
-        select(nr, [](uint32_t, float) { return 1ull; }, [&](unsigned long long) { return (double)top_k; });
-        if (HAS_P && !fall) {
-            const uint32_t floor_key = thr_key;
-            select(nr, [&](uint32_t key, float x) { return key >= floor_key ? mass_q(x, k, nr) : 0ull; },
-                   [&](unsigned long long total) { return (double)top_p * (double)total; });
-        }
-    } else if (HAS_P && !fall) {
-        if (HAS_K) {
-            // every survivor of top-k is in the candidate table
-            thr_key = nucleus_on_candidates<K>(sh, ncand, thr_key, k, top_p);
-        } else {
-            const float nr = row_reference();
-            select(nr, [&](uint32_t, float x) { return mass_q(x, k, nr); },
-                   [&](unsigned long long total) { return (double)top_p * (double)total; });
-        }
+    // count the logits per coarse bin from the top until k are reached
+    const float nr = row_reference();
+    select(nr, [](uint32_t, float) { return 1ull; }, [&](unsigned long long) { return (double)top_k; });
+    if (HAS_P && !fall) {
+        const uint32_t floor_key = thr_key;
+        select(nr, [&](uint32_t key, float x) { return key >= floor_key ? mass_q(x, k, nr) : 0ull; },
+               [&](unsigned long long total) { return (double)top_p * (double)total; });
     }
 
     if (fall) {
@@ -1930,8 +1894,35 @@ void launch_resident(as_ctx *ctx, const void *logits, int64_t rows, int64_t ld, 
                finished_in, row_ids, temp, top_k, top_p, thr_out, StepArgs{});
 }
 
-// top-k (optionally followed by the nucleus), or the nucleus alone on bf16 rows, and the sampling step in one
-// launch; false if the shape does not qualify (then the caller runs the threshold kernel and the step kernel one after the other)
+// Rows that the resident kernel takes (whole aligned pieces, at most 32768 logits, k at most 128), and takes faster
+// than the wide one: several of its 256-thread blocks share a compute unit, so it wins once there are more rows
+// than compute units (bf16, 300 rows of 20003: nucleus 23 us against 47, top-k 40 15.5 against 21; 2000 rows of
+// 32003 fp32 with top-k 40: 56 against 71).  The wide kernel wins with fewer (16 rows of 32003: 17 us against 20,
+// fp32 16.4 against 25), on short rows, where the resident one's lanes idle (2000 rows of 3001: 24 to 47 us against 99
+// to 283), on the fp32 nucleus (300 rows of 32003: 25 against 37) and with many fp32 rows of up to 16384 logits (2000
+// of 9001, top-k 40: 29 against 41).
+static bool resident_pays(const as_ctx *ctx, const void *logits, int64_t rows, int64_t ld, bool has_k, int32_t top_k)
+{
+    const bool half = ctx->dtype == AS_BF16;
+    if (ctx->V > 32768 || reinterpret_cast<uintptr_t>(logits) % 16 != 0 || (ld * (half ? 2 : 4)) % 16 != 0 ||
+        (has_k && top_k > kThreads / 2))
+        return false;
+    if (ctx->thr_path == 2) return true;
+    if (rows <= (int64_t)ctx->num_cus || ctx->V <= (half ? 8192 : 4096)) return false;
+    return half || (has_k && (ctx->V > 16384 || rows <= 2 * (int64_t)ctx->num_cus));
+}
+
+// What is left to the streamed kernel: k above 128 on rows of more than 128 KB, with more rows than compute units (1000
+// rows of 100000 fp32, k = 300: 257 us against 449 in the wide kernel, whose passes over such a row each wait for
+// one block's loads; one row of 256000 bf16 157 against 96).
+static bool streamed_pays(const as_ctx *ctx, int64_t rows, bool has_k, int32_t top_k)
+{
+    return has_k && top_k > kThreads / 2 && rows > (int64_t)ctx->num_cus &&
+           (int64_t)ctx->V * (ctx->dtype == AS_BF16 ? 2 : 4) > 131072;
+}
+
+// top-k and the nucleus and the sampling step in one launch; false where only the radix select and the resident
+// fp32 nucleus are left (then the caller runs the threshold kernel and the step kernel one after the other)
 bool launch_topk_step(as_ctx *ctx, const StepArgs &args, int32_t top_k, float top_p, as_status *st)
 {
     const size_t esz = ctx->dtype == AS_BF16 ? 2 : 4;
@@ -1939,6 +1930,18 @@ bool launch_topk_step(as_ctx *ctx, const StepArgs &args, int32_t top_k, float to
     const bool nt = stream_rows(a.rows, a.ld, esz);
     const bool has_k = top_k > 0 && top_k < ctx->V, has_p = top_p > 0.f && top_p < 1.f;
     const bool nucleus_only = !has_k && has_p && ctx->dtype == AS_BF16;
+    const bool one_tile = ctx->dtype == AS_BF16 && ctx->V % 8 == 0 && ctx->V <= 32768 &&
+                          reinterpret_cast<uintptr_t>(a.logits) % 16 == 0 && (a.ld * esz) % 16 == 0 &&
+                          (has_k ? top_k <= kTileTopK : a.k <= kTileMaxScale);
+    // (short rows leave three of the single-tile kernels' four waves without work: with many of them the wide
+    // kernel is faster, 8192 rows of 4096 top-k 40 92 us against 207)
+    const bool tile = one_tile && !(ctx->V <= 8192 && a.rows > 2 * (int64_t)ctx->num_cus);
+    if (ctx->thr_path == 3 ||
+        (ctx->thr_path == 0 && !tile && !resident_pays(ctx, a.logits, a.rows, a.ld, has_k, top_k) &&
+         !streamed_pays(ctx, a.rows, has_k, top_k))) {
+        *st = launch_wide(ctx, a, has_k ? top_k : 0, has_p ? top_p : 1.f, nullptr);
+        return true;
+    }
     if ((ctx->thr_path != 0 && ctx->thr_path != 2) || !(has_k || nucleus_only) || top_k > kThreads / 2 || ctx->V > 32768 ||
         reinterpret_cast<uintptr_t>(a.logits) % 16 != 0 || (a.ld * esz) % 16 != 0)
         return false;
@@ -1996,27 +1999,25 @@ as_status launch_threshold(as_ctx *ctx, const void *logits, int64_t rows, int64_
     const bool resident = ctx->thr_path != 1 && (has_k || has_p) && ctx->V <= 32768 &&
                           reinterpret_cast<uintptr_t>(logits) % 16 == 0 && (ld * esz) % 16 == 0 &&
                           (!has_k || top_k <= kThreads / 2);
-    // what the resident kernel does not take goes to the streamed one (any row length and stride, any k)
-    const bool streamed = !resident && ctx->thr_path != 1 && (has_k || has_p) &&
-                          reinterpret_cast<uintptr_t>(logits) % esz == 0;
+    if (ctx->thr_path == 3 || (ctx->thr_path == 2 && !resident) ||
+        (ctx->thr_path == 0 && !resident_pays(ctx, logits, rows, ld, has_k, top_k) &&
+         !streamed_pays(ctx, rows, has_k, top_k))) {
+        StepArgs a{};
+        a.logits = logits; a.rows = rows; a.ld = ld; a.V = ctx->V; a.dtype = ctx->dtype; a.temp = temp;
+        a.k = 1.44269504088896340736f / temp; a.finished_in = finished_in; a.row_ids = row_ids;
+        return launch_wide(ctx, a, has_k ? top_k : 0, has_p ? top_p : 1.f, thr_out);
+    }
+    const bool streamed = !resident && ctx->thr_path == 0;
     if (streamed) {
         const dim3 grid((unsigned)rows), block(kThreads);
-        const int kmode = !has_k ? 0 : top_k <= kThreads / 2 ? 1 : 2;
-#define AS_STREAM_LAUNCH1(DT_, KM_, HP_)                                                                        \
-    launch(ctx, kKernelThreshold, threshold_stream_kernel<DT_, KM_, HP_>, grid, block, 0, logits, ld, ctx->V,   \
-           finished_in, row_ids, temp, top_k, top_p, thr_out)
-#define AS_STREAM_LAUNCH(DT_)                                                                                    \
-    do {                                                                                                         \
-        if (kmode == 0) AS_STREAM_LAUNCH1(DT_, 0, true);                                                         \
-        else if (kmode == 1 && has_p) AS_STREAM_LAUNCH1(DT_, 1, true);                                           \
-        else if (kmode == 1) AS_STREAM_LAUNCH1(DT_, 1, false);                                                   \
-        else if (has_p) AS_STREAM_LAUNCH1(DT_, 2, true);                                                         \
-        else AS_STREAM_LAUNCH1(DT_, 2, false);                                                                   \
-    } while (0)
-        if (ctx->dtype == AS_BF16) AS_STREAM_LAUNCH(AS_BF16);
-        else AS_STREAM_LAUNCH(AS_F32);
-#undef AS_STREAM_LAUNCH1
-#undef AS_STREAM_LAUNCH
+        if (ctx->dtype == AS_BF16)
+            launch(ctx, kKernelThreshold,
+                   has_p ? threshold_stream_kernel<AS_BF16, true> : threshold_stream_kernel<AS_BF16, false>, grid, block,
+                   0, logits, ld, ctx->V, finished_in, row_ids, temp, top_k, top_p, thr_out);
+        else
+            launch(ctx, kKernelThreshold,
+                   has_p ? threshold_stream_kernel<AS_F32, true> : threshold_stream_kernel<AS_F32, false>, grid, block,
+                   0, logits, ld, ctx->V, finished_in, row_ids, temp, top_k, top_p, thr_out);
     } else if (resident) {
         if (ctx->dtype == AS_BF16)
             launch_resident<AS_BF16>(ctx, logits, rows, ld, finished_in, row_ids, temp, top_k, top_p, thr_out, has_k,

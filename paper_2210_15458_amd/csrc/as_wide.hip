@@ -1,0 +1,1072 @@
+// Top-k and the nucleus (the logit modifiers of Sec. 2) together with the sampling step (Algorithm 1, Sec. 4.1)
+// in one launch, for rows of any length, alignment and storage type: what the single-tile bf16 kernels do not
+// take.  One work-group of 256 to 1024 threads per row, the row in its registers (up to 16 pieces of 16 bytes a
+// thread: 256 KB with 1024 threads); a longer row goes through the registers a tile at a time and every pass but
+// the first starts with the tile that is still there.
+//
+// What bounds it: a row of V = 50257 fp32 logits is 200 KB, one work-group fills a compute unit's registers with
+// it, so nothing hides the work that follows the last load, and that is vector issue (13 slots a logit to count it,
+// 10 to sum it) and the latency of some 25 block-wide steps.  Hence a histogram filled while the row lands, one
+// more pass, and no visit of memory after the first but for the code's own chunk.
+//
+//   top-k, k <= 128   The k-th largest of 256 group maxima bounds the k-th largest logit from below; the few
+//                     logits at or above it become a candidate table in LDS (value, index), and everything that
+//                     follows - the exact k-th with its ties, the nucleus over the survivors, the code's bucket -
+//                     is ranks and scans over that table.
+//   nucleus           32-bit tallies in 4096 bins, 64 to a factor of two; the bin in which the nucleus closes; the
+//                     chunk sums of everything above a window around it, the window's logits as a list that is
+//                     closed exactly (see below).
+//   k > 128           counts in the same bins, the logits of the closing bin as a list; a nucleus after it by
+//                     fixed-point masses.
+// Then the chunk of the code (64 pieces, vocabulary order), its lane, its logit.  Sums that decide anything are taken
+// in an order, or in integers, that does not depend on which lane comes first.
+//
+// One launch against threshold kernel and sampling kernel before: 1 row of 50257 bf16, p = 0.95 19.8 us (45), 512 rows
+// of 50257 fp32, p = 0.92 51 us (76; the 103 MB alone take 19 at 5.5 TB/s), 230 rows of 256000 bf16, k = 50 then
+// p = 0.95 48 us (171; 21).
+#include <type_traits>
+
+#include "as_common.hpp"
+#include "as_row.hpp"
+#include "as_tile.hpp"
+
+namespace as {
+namespace {
+
+typedef unsigned long long u64;
+
+constexpr int kWideTopK = 128;           // largest k of the candidate table
+constexpr int kTopOctaves = 16;          // factors of two that the bins reach above the reference
+
+// order-preserving key of a logit (-0 and +0 are one value: one key), and back
+__device__ __forceinline__ uint32_t order_key(float f)
+{
+    uint32_t b = __builtin_bit_cast(uint32_t, f);
+    b = (b << 1) ? b : 0u;
+    return b ^ ((uint32_t)((int32_t)b >> 31) | 0x80000000u);
+}
+__device__ __forceinline__ float from_order_key(uint32_t k)
+{
+    return __builtin_bit_cast(float, (k & 0x80000000u) ? (k ^ 0x80000000u) : ~k);
+}
+
+// 40 fractional bits of a weight e < 2^23 (24 significant bits: exact for every weight above 2^-17); a larger
+// one, or NaN, counts as 2^23 (the caller takes another reference then)
+__device__ __forceinline__ u64 fixed_mass(float e)
+{
+    const float a = fminf(e, 8388608.f) * 256.f;
+    const uint32_t hi = (uint32_t)a;
+    const uint32_t lo = (uint32_t)((a - (float)hi) * 4294967296.f);
+    return ((u64)hi << 32) | lo;
+}
+
+template <int NT, bool MULTI> struct WideShared {
+    static constexpr int kWaves = NT / 64;
+    static constexpr int kBins = NT == 1024 ? 4096 : 2048;
+    static constexpr int kPerOctave = kBins / 64;            // 64 factors of two
+    static constexpr int kList = NT == 1024 ? 2048 : 1024;
+    // (a row of 2^21 fp32 logits: 8193; with 512 threads, where two blocks are to share a unit's LDS, rows of fewer)
+    static constexpr int kChunks = !MULTI ? 16 * kWaves + 1 : NT == 1024 ? 8704 : 2304;
+    union {
+        u64 bins[kBins];
+        uint32_t tally[kBins + 64];                          // (and a word per lane for what is not counted)
+        double cw[2][NT];                                    // candidate weights: after top-k, after the nucleus
+    };
+    float chunk[kChunks];                                    // weight of every chunk of 64 pieces, vocabulary order ...
+    static constexpr int kExtra = MULTI ? 2304 : kChunks;    // (longer rows do without the quick way)
+    u64 extra[kExtra];                                       // ... and what the closing bin adds to it, fixed point
+    __attribute__((aligned(16))) uint32_t key[kList + 4];    // a list: keys (selection) or values (candidates) ...
+    union {
+        __attribute__((aligned(16))) u64 q[kList];                                        // ... with their integer weights
+        uint32_t idx[2 * kList];                             // ... or vocabulary indices
+    };
+    uint16_t at[kList];                                      // the chunk of a list entry
+    uint32_t sorted[NT];                                     // a list in another order
+    u64 sink[64];                                            // where a weight of zero is added
+    u64 wave_q[kWaves];
+    double wave_d[kWaves], wave_e[kWaves];
+    float wave_f[kWaves];
+    uint32_t wave_lo[kWaves], wave_hi[kWaves];
+    u64 before;
+    double run;
+    int32_t pick;
+    uint32_t n, sel;
+};
+
+// What the waves of a block have left in LDS, one value each, is taken in by one lane per wave (W <= 16): the row
+// sits in most of the registers, a value per wave in every lane would not fit beside it.
+__device__ __forceinline__ u64 read_lane(u64 x, int lane)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)x, lane);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(x >> 32), lane);
+    return ((u64)hi << 32) | lo;
+}
+template <int N> __device__ __forceinline__ u64 lane_scan(u64 x)
+{
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int d = 1; d < N; d <<= 1) {
+        const u64 y = __shfl_up(x, d, 64);
+        if (lane >= d) x += y;
+    }
+    return x;
+}
+// Exclusive prefix of one integer per thread, thread order, and the block's total.
+template <int NT> __device__ __forceinline__ u64 wide_scan(u64 x, u64 *wave_tot, u64 &total)
+{
+    constexpr int W = NT / 64;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const u64 incl = lane_scan<64>(x);
+    __syncthreads();
+    if (lane == 63) wave_tot[wave] = incl;
+    __syncthreads();
+    const u64 t = lane < W ? wave_tot[lane] : 0ull;
+    const u64 s = lane_scan<W>(t);
+    total = read_lane(s, W - 1);
+    return read_lane(s, wave) - read_lane(t, wave) + incl - x;
+}
+// Sum over the waves of a value that each has left; `base`: of those before this one.
+template <int NT> __device__ __forceinline__ double wide_total(const double *wave_d, double &base)
+{
+    constexpr int W = NT / 64;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const double t = lane < W ? wave_d[lane] : 0.0;
+    const double s = wave_scan_add(t);
+    base = as::read_lane(s, wave) - as::read_lane(t, wave);
+    return as::read_lane(s, 63);
+}
+template <int NT> __device__ __forceinline__ float wide_max(float m, float *wave_f)
+{
+    const int lane = threadIdx.x & 63;
+    m = wave_max(m);
+    __syncthreads();
+    if (lane == 0) wave_f[threadIdx.x >> 6] = m;
+    __syncthreads();
+    return wave_max(lane < NT / 64 ? wave_f[lane] : -__builtin_inff());
+}
+
+// TOPK: top_k is on (and the nucleus if top_p is below 1); otherwise the nucleus alone.  NP: pieces a thread holds.
+// MULTI: the row is longer than that.  Without tokens_out only the keep threshold is written, to thr_out.
+template <int DT, int NT, int NP, bool MULTI, bool TOPK>
+__global__ __launch_bounds__(NT, 4) void wide_step_kernel(StepArgs a, int32_t top_k, float top_p,
+                                                                          float *thr_out)
+{
+    using T = typename Elem<DT>::T;
+    using Sh = WideShared<NT, MULTI>;
+    constexpr int EPV = Elem<DT>::kPerVec;
+    constexpr int W = NT / 64;
+    constexpr uint32_t kNegInf = DT == AS_BF16 ? 0xff80ff80u : 0xff800000u;
+    __shared__ Sh sh;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t r = blockIdx.x;
+    if (a.finished_in != nullptr && a.finished_in[r] != 0) {
+        if (tid == 0 && a.tokens_out) write_finished(a, r);
+        return;
+    }
+    const int64_t src = a.row_ids ? (int64_t)a.row_ids[r] : r;
+    const T *row = reinterpret_cast<const T *>(a.logits) + src * a.ld;
+    const int32_t V = a.V;
+    const float k = a.k;
+    // The row as the 16-byte pieces it touches: `shift` elements of piece 0 lie before it; `nwhole` pieces end
+    // inside it, and a last one may hold `tail` elements of it.
+    const int32_t shift = (int32_t)((reinterpret_cast<uintptr_t>(row) & 15u) / sizeof(T));
+    const u32x4 *const pieces = reinterpret_cast<const u32x4 *>(row - shift);
+    const int32_t vend = V + shift;
+    const int32_t nwhole = vend / EPV, tail = vend % EPV;
+    const int32_t last = nwhole > 0 ? nwhole - 1 : 0;
+    const int32_t ntiles = MULTI ? (nwhole + NT * NP - 1) / (NT * NP) : 1;
+
+    // elements [first, live) of a piece are the row's; the others become -inf, which has no weight
+    auto cut = [&](u32x4 v, int32_t first, int32_t live) __attribute__((always_inline)) {
+#pragma unroll
+        for (int e = 0; e < EPV; ++e) {
+            if (e >= first && e < live) continue;
+            if constexpr (DT == AS_BF16)
+                v[e >> 1] = (e & 1) ? ((v[e >> 1] & 0xffffu) | 0xff800000u) : ((v[e >> 1] & 0xffff0000u) | 0xff80u);
+            else v[e] = kNegInf;
+        }
+        return v;
+    };
+    const u32x4 nothing = u32x4{kNegInf, kNegInf, kNegInf, kNegInf};
+    // piece i of the row wherever it lies (-inf past the end)
+    auto piece_at = [&](int32_t i) __attribute__((always_inline)) {
+        const int32_t at = i <= nwhole - (tail == 0 ? 1 : 0) ? i : 0;
+        u32x4 v = pieces[at];
+        if (i == 0 && shift != 0) v = cut(v, shift, EPV);
+        if (i == nwhole) v = cut(v, i == 0 ? shift : 0, tail);
+        return i < nwhole || (i == nwhole && tail != 0) ? v : nothing;
+    };
+
+    u32x4 raw[NP], rest = nothing;
+    int32_t cur = 0;                                         // the tile in the registers
+    auto load = [&](int32_t t) __attribute__((always_inline)) {
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            const int32_t i = (t * NP + p) * NT + tid;
+            raw[p] = pieces[i < last ? i : last];
+        }
+        cur = t;
+    };
+    auto land = [&](int p) __attribute__((always_inline)) {
+        const bool in = (cur * NP + p) * NT + tid < nwhole;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) raw[p][i] = in ? raw[p][i] : kNegInf;
+        if (p == 0 && shift != 0 && tid == 0 && cur == 0 && nwhole > 0) raw[0] = cut(raw[0], shift, EPV);
+    };
+    load(0);
+    if (tail != 0 && tid == 0) rest = piece_at(nwhole);
+    __builtin_amdgcn_sched_barrier(0);
+
+    // f(piece, p, tile) over the row's whole pieces.  FIRST: the resident tile has only been requested.
+    auto sweep = [&](auto first_c, auto f) __attribute__((always_inline)) {
+        constexpr bool FIRST = decltype(first_c)::value;
+        if constexpr (!MULTI) {
+#pragma unroll
+            for (int p = 0; p < NP; ++p) {
+                if constexpr (FIRST) land(p);
+                else asm volatile("" : "+v"(raw[p]));        // (nothing derived in an earlier pass is kept for this one)
+                f(raw[p], p, 0);
+                __builtin_amdgcn_sched_barrier(0);           // (a piece at a time: interleaved, several do not fit)
+            }
+        } else {
+            const int32_t begin = cur, step = cur == 0 ? 1 : -1;
+            for (int32_t n = 0; n < ntiles; ++n) {
+                const int32_t t = begin + n * step;
+                if (n != 0) {
+                    load(t);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+#pragma unroll
+                for (int p = 0; p < NP; ++p) {
+                    if (FIRST || n != 0) land(p);
+                    f(raw[p], p, t);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        }
+    };
+    typedef std::integral_constant<bool, true> Yes;
+    typedef std::integral_constant<bool, false> No;
+    auto values = [&](const u32x4 &v, float *x) __attribute__((always_inline)) { unpack<DT>(v, x); };
+
+    auto safe_row = [&]() __attribute__((always_inline)) {   // no logit with weight: any row in range
+        if (tid == 0) {
+            RowOut o;
+            o.token = 0;
+            o.c_next = 0.f;
+            o.prob = 0.f;
+            o.f_lo = 0.f;
+            write_row(a, r, o);
+        }
+    };
+
+    // ------------------------------------------------------------------ top-k by a table of candidates
+    if constexpr (TOPK) {
+        float m = -__builtin_inff();
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            land(p);
+            float x[EPV];
+            values(raw[p], x);
+            m = max3(m, vec_max<EPV>(x), m);
+        }
+        if (top_k <= kWideTopK) {
+            if (NT == 1024) {
+                // 256 groups of four lanes
+                m = fmaxf(m, __shfl_xor(m, 1, 64));
+                m = fmaxf(m, __shfl_xor(m, 2, 64));
+            }
+            constexpr int kPerGroup = NT / 256;
+            if (tid % kPerGroup == 0) sh.key[tid / kPerGroup] = order_key(m);
+            if (tid == 0) {
+                sh.n = 0;
+                sh.sel = 0;
+            }
+            __syncthreads();
+            if (wave == 0) {
+                // the largest key that at least k of the maxima reach, by bisection; a round is four ballots
+                uint32_t g[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) g[i] = sh.key[i * 64 + lane];
+                uint32_t lo = min(min(g[0], g[1]), min(g[2], g[3])), hi = max(max(g[0], g[1]), max(g[2], g[3]));
+#pragma unroll
+                for (int d = 32; d >= 1; d >>= 1) {
+                    lo = min(lo, (uint32_t)__shfl_xor((int)lo, d, 64));
+                    hi = max(hi, (uint32_t)__shfl_xor((int)hi, d, 64));
+                }
+                lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)lo);
+                hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)hi);
+                while (lo < hi) {
+                    const uint32_t mid = lo + (hi - lo) / 2u + 1u;
+                    int cnt = 0;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) cnt += __builtin_popcountll(__ballot(g[i] >= mid));
+                    if (cnt >= top_k) lo = mid;
+                    else hi = mid - 1u;
+                }
+                if (lane == 0) sh.before = lo;
+            }
+            __syncthreads();
+            const float xb = from_order_key((uint32_t)sh.before);
+            const bool bounded = xb > -__builtin_inff();
+            auto push = [&](const u32x4 &v, int32_t first) __attribute__((always_inline)) {
+                float x[EPV];
+                values(v, x);
+                if (vec_max<EPV>(x) >= xb) {
+#pragma unroll
+                    for (int e = 0; e < EPV; ++e)
+                        if (x[e] >= xb) {
+                            const uint32_t slot = atomicAdd(&sh.n, 1u);
+                            if (slot < (uint32_t)NT) {
+                                sh.key[slot] = __builtin_bit_cast(uint32_t, x[e]);
+                                sh.idx[slot] = (uint32_t)(first + e - shift);
+                            }
+                        }
+                }
+            };
+            if (bounded) {
+                sweep(No{}, [&](const u32x4 &v, int p, int32_t t) __attribute__((always_inline)) {
+                    push(v, ((t * NP + p) * NT + tid) * EPV);
+                });
+                if (tail != 0 && wave == 0) push(rest, nwhole * EPV);
+            }
+            __syncthreads();
+            const uint32_t n = sh.n;
+            if (bounded && n <= (uint32_t)NT) {
+                const uint32_t n4 = (n + 3u) & ~3u;
+                if ((uint32_t)tid >= n && (uint32_t)tid < n4) {
+                    sh.key[tid] = 0xff800000u;
+                    sh.idx[tid] = 0xffffffffu;
+                }
+                const bool have = (uint32_t)tid < n;
+                const float x = have ? __builtin_bit_cast(float, sh.key[tid]) : -__builtin_inff();
+                const uint32_t idx = have ? sh.idx[tid] : 0xffffffffu;
+                __syncthreads();
+                // its place by value; among the k highest (all that are tied with the k-th) if fewer than k lie above
+                uint32_t above = 0, place = 0;
+                if (wave * 64 < (int)n) {
+#pragma unroll 4
+                    for (uint32_t j = 0; j < n4; j += 4) {
+                        const f32x4 o = *reinterpret_cast<const f32x4 *>(&sh.key[j]);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            above += o[i] > x ? 1u : 0u;
+                            place += o[i] == x && j + i < (uint32_t)tid ? 1u : 0u;
+                        }
+                    }
+                }
+                place += above;
+                bool kept = have && above < (uint32_t)top_k;
+                const float ref = fmaxf(ceilf(wide_max<NT>(kept ? x : -__builtin_inff(), sh.wave_f) * k), kRefFloor);
+                float w = kept ? fast_exp2(fmaf(x, k, -ref)) : 0.f;
+                double before;
+                if (top_p > 0.f && top_p < 1.f) {
+                    // the value at which the running weight, from the highest down, reaches top_p of the survivors'
+                    if (have) {
+                        sh.cw[0][place] = (double)w;
+                        sh.sorted[place] = __builtin_bit_cast(uint32_t, x);
+                    }
+                    if (tid == 0) sh.run = -__builtin_inf();
+                    __syncthreads();
+                    const double v = have ? sh.cw[0][tid] : 0.0;
+                    const double incl = wave_scan_add(v);
+                    if (lane == 63) sh.wave_d[wave] = incl;
+                    __syncthreads();
+                    const double goal = (double)top_p * wide_total<NT>(sh.wave_d, before);
+                    if (have && !(before + incl - v >= goal) && before + incl >= goal)
+                        sh.run = (double)__builtin_bit_cast(float, sh.sorted[tid]);
+                    __syncthreads();
+                    kept = kept && (double)x >= sh.run;
+                    w = kept ? w : 0.f;
+                }
+                if (a.tokens_out == nullptr) {
+                    const float low = -wide_max<NT>(kept ? -x : -__builtin_inff(), sh.wave_f);
+                    if (tid == 0) thr_out[r] = low;
+                    return;
+                }
+                // the kept ones in vocabulary order; the bucket is the last one that has weight and whose mass before
+                // it does not exceed c*S
+                if (have && !(w > 0.f)) sh.idx[tid] = 0xffffffffu;
+                if ((uint32_t)tid < n4) sh.cw[1][tid] = 0.0;
+                __syncthreads();
+                if (wave * 64 < (int)n && w > 0.f) {
+                    place = 0;
+#pragma unroll 4
+                    for (uint32_t j = 0; j < n4; j += 4) {
+                        const u32x4 o = *reinterpret_cast<const u32x4 *>(&sh.idx[j]);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) place += o[i] < idx ? 1u : 0u;
+                    }
+                    sh.cw[1][place] = (double)w;
+                    sh.sorted[place] = idx;
+                }
+                __syncthreads();
+                const double v = (uint32_t)tid < n ? sh.cw[1][tid] : 0.0;
+                const double incl = wave_scan_add(v);
+                if (lane == 63) sh.wave_e[wave] = incl;
+                __syncthreads();
+                const double S = wide_total<NT>(sh.wave_e, before);
+                const double tau = (double)a.codes[r] * S, mine = before + incl - v;
+                const bool cand = v > 0.0 && mine <= tau;
+                if (cand) atomicMax(&sh.sel, (uint32_t)tid + 1u);
+                __syncthreads();
+                const uint32_t sel = sh.sel;
+                if (sel == 0u) safe_row();
+                else if (cand && (uint32_t)tid + 1u == sel) {
+                    const uint32_t token = sh.sorted[tid];
+                    RowOut o;
+                    o.token = (int32_t)(token < (uint32_t)V ? token : (uint32_t)(V - 1));
+                    o.c_next = rescale_code(tau, mine, v);
+                    o.prob = (float)(v / S);
+                    o.f_lo = (float)(mine / S);
+                    write_row(a, r, o);
+                }
+                return;
+            }
+            __syncthreads();
+        }
+    }
+
+    // ------------------------------------------------------------------ selection by integer weights
+    float mx = -__builtin_inff();        // the row's largest logit, once a pass has seen all of it
+    float ref;
+    {
+        if constexpr (!TOPK) land(0);
+        float x[EPV];
+        values(raw[0], x);
+        float m = vec_max<EPV>(x);
+        values(rest, x);
+        m = fmaxf(m, vec_max<EPV>(x));
+        ref = fmaxf(ceilf(wide_max<NT>(m, sh.wave_f) * k), kRefFloor);
+    }
+    constexpr float kTwo23 = 8388608.f;
+    constexpr float kScale = (float)Sh::kPerOctave;
+    constexpr float kBinLo = kTwo23, kBinHi = kTwo23 + (float)(Sh::kBins - 1);
+    constexpr float kBin0 = kTwo23 + (float)(kTopOctaves * Sh::kPerOctave);
+    // coarse bin of an exponent argument relative to the reference, as a float whose low mantissa bits are the bin
+    // (rounded to the nearest integer and clamped to the table; falls as the logit rises)
+    auto bin_of = [&](float y) __attribute__((always_inline)) {
+        return __builtin_amdgcn_fmed3f(fmaf(y, -kScale, kBin0), kBinLo, kBinHi);
+    };
+    typedef __attribute__((address_space(3))) u64 lds_u64;
+    typedef __attribute__((address_space(3))) uint32_t lds_u32;
+    lds_u64 *const bins = (lds_u64 *)sh.bins;
+    lds_u64 *const sink = (lds_u64 *)sh.sink + lane;
+    auto add = [&](lds_u64 *at, u64 q) __attribute__((always_inline)) {
+        __hip_atomic_fetch_add(at, q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    auto clear_bins = [&]() __attribute__((always_inline)) {
+        __syncthreads();
+        for (int b = tid; b < Sh::kBins; b += NT) sh.bins[b] = 0;
+        if (tid == 0) {
+            sh.n = 0;
+            sh.pick = -1;
+        }
+        __syncthreads();
+    };
+    // After the bins are filled: the first one, from the top, at which base + the running weight reaches the
+    // goal.  Leaves it in sh.pick (-1: none does) and the weight above it, base included, in sh.before.
+    auto reach = [&](u64 base, double &need, bool set_need, auto count_c) __attribute__((always_inline)) {
+        constexpr bool COUNT = decltype(count_c)::value;     // counts, in 32 bits
+        constexpr int kPer = Sh::kBins / NT;
+        u64 h[kPer], local = 0, total;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            h[i] = COUNT ? (u64)sh.tally[tid * kPer + i] : sh.bins[tid * kPer + i];
+            local += h[i];
+        }
+        const u64 excl = base + wide_scan<NT>(local, sh.wave_q, total);
+        if (set_need) need = COUNT ? (double)top_k : (double)top_p * (double)total;
+        if (!((double)excl >= need) && (double)(excl + local) >= need) {
+            u64 acc = excl;
+            bool open = true;
+#pragma unroll
+            for (int i = 0; i < kPer; ++i) {
+                if (open && (double)(acc + h[i]) >= need) {
+                    sh.pick = tid * kPer + i;
+                    sh.before = acc;
+                    open = false;
+                }
+                acc += h[i];
+            }
+        }
+        __syncthreads();
+    };
+    // largest factor of two above the reference at which 2^ceil(log2 V) masses still fit the sums
+    const float room = (float)min(kTopOctaves, 23 - (32 - __builtin_clz((uint32_t)V)));
+
+    // The exact end of a selection: the list (n entries) holds the logits of the closing bin,
+    // `base` is the weight above them; the key of the group of equal logits at which the running weight reaches
+    // `need`.  all(put) puts every logit of the bin, for a list that did not take them all.
+    auto close = [&](uint32_t n, u64 base, double need, auto all)
+                     __attribute__((always_inline)) -> uint32_t {
+        if (n <= (uint32_t)NT) {
+            // every entry's place by key, the weights in that order, their running sums (integers below 2^53: exact)
+            double *const sorted = sh.cw[0];
+            uint32_t *const skey = sh.sorted;
+            const uint32_t n4 = (n + 3u) & ~3u;
+            if ((uint32_t)tid >= n && (uint32_t)tid < n4) sh.key[tid] = 0u;
+            if (tid == 0) sh.sel = 0u;
+            __syncthreads();
+            if ((uint32_t)tid < n) {
+                const uint32_t mine = sh.key[tid];
+                uint32_t place = 0;
+#pragma unroll 4
+                for (uint32_t j = 0; j < n4; j += 4) {
+                    const u32x4 o = *reinterpret_cast<const u32x4 *>(&sh.key[j]);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) place += o[i] > mine || (o[i] == mine && j + i < (uint32_t)tid) ? 1u : 0u;
+                }
+                sorted[place] = (double)sh.q[tid];
+                skey[place] = mine;
+            }
+            __syncthreads();
+            const double v = (uint32_t)tid < n ? sorted[tid] : 0.0;
+            const double incl = wave_scan_add(v);
+            if (lane == 63) sh.wave_d[wave] = incl;
+            __syncthreads();
+            double first;
+            wide_total<NT>(sh.wave_d, first);
+            const double goal = need - (double)base, upto = first + incl;
+            if ((uint32_t)tid < n && !(upto - v >= goal) && upto >= goal) sh.sel = skey[tid];
+            __syncthreads();
+            return sh.sel;
+        }
+        // all keys cut into kBins intervals of 2^s of them, from the top, then the one that closes, until it is one key
+        uint32_t klo = 0u, khi = 0xffffffffu;
+        for (;;) {
+            const uint32_t span = khi - klo;
+            const int s = span >= (uint32_t)Sh::kBins ? 32 - __builtin_clz(span) - (31 - __builtin_clz((uint32_t)Sh::kBins)) : 0;
+            clear_bins();
+            auto put = [&](uint32_t key, u64 q) __attribute__((always_inline)) {
+                if (key >= klo && key <= khi) add(bins + ((khi - key) >> s), q);
+            };
+            if (n <= (uint32_t)Sh::kList) {
+                for (uint32_t i = tid; i < n; i += NT) put(sh.key[i], sh.q[i]);
+            } else {
+                all(put);
+            }
+            reach(base, need, false, No{});
+            const int32_t at = sh.pick;
+            if (at < 0) break;                               // (the weights of a NaN row)
+            base = sh.before;
+            const uint32_t top = khi - ((uint32_t)at << s);
+            const uint32_t low = (uint32_t)(1u << s) - 1u;
+            klo = top - klo > low ? top - low : klo;
+            khi = top;
+            if (s == 0) break;
+        }
+        return khi;
+    };
+
+    // f(piece) over the row for the selection by integer weights: with top-k it is the way (k above 128), from the
+    // registers; after the quick way of the nucleus it is the rare case, and goes over memory (kept for it as
+    // well, the row costs spilled registers on the way that is taken)
+    auto every_piece = [&](auto f) __attribute__((always_inline)) {
+        if constexpr (TOPK) {
+            sweep(No{}, [&](const u32x4 &v, int, int32_t) __attribute__((always_inline)) { f(v); });
+            if (tail != 0 && wave == 0) f(rest);
+        } else {
+            for (int32_t i = tid; i <= nwhole; i += NT) f(piece_at(i));
+        }
+    };
+    // One selection: the key of the group of equal logits at which the running weight, from the largest logit
+    // down, reaches the goal.  COUNT: weights of 1 against top_k; otherwise masses of the logits >= floor_x
+    // against top_p of their total.  False if no logit has weight.
+    auto select = [&](auto count_c, float floor_x, float &thr) __attribute__((always_inline)) -> bool {
+        constexpr bool COUNT = decltype(count_c)::value;
+        float nr = -ref;
+        auto weight = [&](float x) __attribute__((always_inline)) -> u64 {
+            if constexpr (COUNT) return 1ull;
+            else return x >= floor_x ? fixed_mass(fast_exp2(fmaf(x, k, nr))) : 0ull;
+        };
+        auto fill = [&]() __attribute__((always_inline)) {
+            float m = -__builtin_inff();
+            auto one = [&](const u32x4 &v) __attribute__((always_inline)) {
+                float x[EPV];
+                values(v, x);
+                m = max3(m, vec_max<EPV>(x), m);
+#pragma unroll
+                for (int e = 0; e < EPV; ++e) {
+                    if constexpr (COUNT) {
+                        // (what lies below the last bin, padding among it, goes to a word of the lane's own)
+                        const float t = __builtin_amdgcn_fmed3f(fmaf(fmaf(x[e], k, nr), -kScale, kBin0), kBinLo,
+                                                                kTwo23 + (float)(Sh::kBins + lane));
+                        __hip_atomic_fetch_add((lds_u32 *)sh.tally + (__builtin_bit_cast(uint32_t, t) - 0x4B000000u), 1u,
+                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    } else {
+                        const uint32_t b = __builtin_bit_cast(uint32_t, bin_of(fmaf(x[e], k, nr))) & (uint32_t)(Sh::kBins - 1);
+                        const u64 q = weight(x[e]);
+                        add(q != 0 ? bins + b : sink, q);
+                    }
+                    if (e % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+                }
+            };
+            every_piece(one);
+            mx = wide_max<NT>(m, sh.wave_f);
+        };
+        clear_bins();
+        fill();
+        const float exact = fmaxf(ceilf(mx * k), kRefFloor);
+        if (!(exact - ref <= room)) {
+            // a logit far above the first pieces' largest: once more against the row's own reference
+            ref = exact;
+            nr = -ref;
+            clear_bins();
+            fill();
+        }
+        double need = 0.0;
+        reach(0ull, need, true, count_c);
+        const int32_t pick = sh.pick;
+        if (pick < 0) {
+            if constexpr (!COUNT) return false;
+            // fewer than k logits within the bins: by key over the whole row
+            thr = from_order_key(close(0xffffffffu, 0ull, need, [&](auto put) __attribute__((always_inline)) {
+                for (int32_t i = tid; i <= nwhole; i += NT) {
+                    float x[EPV];
+                    values(piece_at(i), x);
+                    for (int e = 0; e < EPV; ++e) put(order_key(x[e]), 1ull);
+                }
+            }));
+            return true;
+        }
+        u64 base = sh.before;
+        const float tpick = kTwo23 + (float)pick;
+        auto member = [&](float x) __attribute__((always_inline)) { return bin_of(fmaf(x, k, nr)) == tpick; };
+        // f(key, weight) for the logits of that bin in one piece
+        auto members = [&](const u32x4 &v, auto f) __attribute__((always_inline)) {
+            float x[EPV];
+            values(v, x);
+            bool any = false;
+#pragma unroll
+            for (int e = 0; e < EPV; ++e) any |= member(x[e]);
+            if (any) {
+#pragma unroll
+                for (int e = 0; e < EPV; ++e)
+                    if (member(x[e])) {
+                        const u64 q = weight(x[e]);
+                        if (q) f(order_key(x[e]), q);
+                    }
+            }
+        };
+        every_piece([&](const u32x4 &v) __attribute__((always_inline)) {
+            members(v, [&](uint32_t key, u64 q) __attribute__((always_inline)) {
+                const uint32_t i = atomicAdd(&sh.n, 1u);
+                if (i < (uint32_t)Sh::kList) {
+                    sh.key[i] = key;
+                    sh.q[i] = q;
+                }
+            });
+        });
+        __syncthreads();
+        const uint32_t n = sh.n;
+        thr = from_order_key(close(n, base, need, [&](auto put) __attribute__((always_inline)) {
+            // more than the list takes: from memory (the row's registers in a loop do not fit)
+            for (int32_t i = tid; i <= nwhole; i += NT) members(piece_at(i), put);
+        }));
+        return true;
+    };
+
+    float thr = -__builtin_inff();
+    bool some = true, summed = false;    // summed: the chunk sums of the kept logits are in place
+    if constexpr (TOPK) {
+        some = select(Yes{}, 0.f, thr);
+        if (some && top_p > 0.f && top_p < 1.f) {
+            ref = fmaxf(ceilf(mx * k), kRefFloor);
+            float inner = thr;
+            some = select(No{}, thr, inner);
+            thr = fmaxf(thr, inner);
+        }
+    } else {
+        // The nucleus alone, the quick way.  While the row lands its logits are only counted, per bin, in 32 bits:
+        // 2^s for each, corrected by where in the bin its weight lies (the weight over the bin's own, to 2^-s), so
+        // a bin's tally times the weight at its centre is its mass to a few parts in 10^5.  That names the bin in
+        // which the nucleus closes, give or take a neighbour.  One pass then sums all weights and, per chunk, those
+        // above a window of bins around it, exactly, and lists the logits of the window; the list is closed exactly,
+        // and what it keeps is added to its chunks.  If the window was off, or the list overflows (heavy ties, flat
+        // rows), the general selection follows.
+        // (Adding the masses themselves takes 64-bit LDS atomics, 45 cycles a wave, or float ones, 300.)
+        bool closed = false;
+        const int s_bits = 31 - (32 - __builtin_clz((uint32_t)V));
+        const float s_one = (float)(1u << s_bits);
+        lds_u32 *const tally = (lds_u32 *)sh.tally;
+        auto fill = [&](auto pass) __attribute__((always_inline)) {
+            __syncthreads();
+            for (int b = tid; b < Sh::kBins; b += NT) sh.tally[b] = 0u;
+            if (tid == 0) {
+                sh.n = 0;
+                sh.pick = -1;
+            }
+            __syncthreads();
+            const float nr = -ref, slope = s_one * (0.6931471805599453f / kScale), half = s_one + 0.5f;
+            const float beyond = kTwo23 + (float)(Sh::kBins + lane);
+            float m = -__builtin_inff();
+            auto one = [&](const u32x4 &v) __attribute__((always_inline)) {
+                float x[EPV];
+                values(v, x);
+                m = max3(m, vec_max<EPV>(x), m);
+#pragma unroll
+                for (int i = 0; i < EPV; ++i) {
+                    const float y = fmaf(x[i], k, nr);
+                    const float t = __builtin_amdgcn_fmed3f(fmaf(y, -kScale, kBin0), kBinLo, beyond);
+                    const float off = fmaf(y, kScale, t - kBin0);            // -1/2 .. 1/2 inside the bin
+                    const uint32_t inc = (uint32_t)fmaxf(fmaf(off, slope, half), 0.f);
+                    const uint32_t b = __builtin_bit_cast(uint32_t, t) - 0x4B000000u;
+                    __hip_atomic_fetch_add(tally + b, inc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+                }
+            };
+            pass(one);
+            if (tail != 0 && wave == 0) one(rest);
+            mx = wide_max<NT>(m, sh.wave_f);
+        };
+        fill([&](auto one) __attribute__((always_inline)) {
+            sweep(Yes{}, [&](const u32x4 &v, int, int32_t) __attribute__((always_inline)) { one(v); });
+        });
+        const float exact = fmaxf(ceilf(mx * k), kRefFloor);
+        if (!(exact - ref <= (float)kTopOctaves)) {
+            // a logit far above the first pieces' largest: once more, from memory, against the row's own reference
+            ref = exact;
+            fill([&](auto one) __attribute__((always_inline)) {
+                for (int32_t i = tid; i < nwhole; i += NT) one(piece_at(i));
+            });
+        }
+        const float nr = -ref;
+        {
+            // running mass and running count over the bins
+            constexpr int kPer = Sh::kBins / NT;
+            const float down = 1.f / s_one;
+            double m[kPer], local = 0.0;
+            uint32_t cnt = 0;
+#pragma unroll
+            for (int i = 0; i < kPer; ++i) {
+                const int b = tid * kPer + i;
+                const uint32_t h = sh.tally[b];
+                m[i] = (double)((float)h * down * fast_exp2((float)(kTopOctaves * Sh::kPerOctave - b) / kScale));
+                cnt += (h + (1u << s_bits) / 2u) >> s_bits;
+                local += m[i];
+            }
+            const double incl = wave_scan_add(local);
+            const float cincl = wave_scan_add((float)cnt);
+            if (lane == 63) {
+                sh.wave_d[wave] = incl;
+                sh.wave_e[wave] = (double)cincl;
+            }
+            for (int c = tid; c < Sh::kExtra; c += NT) sh.extra[c] = 0ull;
+            __syncthreads();
+            double lo, clo;
+            const double need = (double)top_p * wide_total<NT>(sh.wave_d, lo);
+            wide_total<NT>(sh.wave_e, clo);
+            lo += incl - local;
+            clo += (double)(cincl - (float)cnt);
+            if (!(lo >= need) && lo + local >= need) {
+                double acc = lo;
+                int32_t found = -1;
+#pragma unroll
+                for (int i = 0; i < kPer; ++i) {
+                    acc += m[i];
+                    if (found < 0 && acc >= need) found = tid * kPer + i;
+                }
+                sh.pick = found >= 0 ? found : tid * kPer + kPer - 1;
+                sh.sel = clo <= 32.0 ? 1u : 0u;              // few logits above: all of them go on the list
+            }
+            __syncthreads();
+        }
+        const int32_t pick = sh.pick;
+        if (pick >= 0 && ntiles * NP * W < Sh::kExtra) {
+            // the window: bins on either side of the picked one until they hold 32 logits
+            int32_t wlo, whi;
+            {
+                const int32_t b = pick - 32 + lane;
+                const bool in = b >= 0 && b < Sh::kBins && lane != 32;
+                const float c = in ? (float)((sh.tally[b >= 0 && b < Sh::kBins ? b : 0] + (1u << s_bits) / 2u) >> s_bits) : 0.f;
+                const float incl = wave_scan_add(c);
+                const float upto = as::read_lane(incl, 32);
+                const u64 near_lo = __ballot(lane < 32 && upto - incl + c <= 32.f);
+                const u64 far_hi = __ballot(lane > 32 && incl - upto > 32.f);
+                wlo = pick - 32 + (near_lo ? (int32_t)__builtin_ctzll(near_lo) : 32);
+                whi = pick - 32 + (far_hi ? (int32_t)__builtin_ctzll(far_hi) - 1 : 63);
+                wlo = sh.sel != 0u || wlo < 0 ? 0 : wlo;
+                whi = whi > Sh::kBins - 1 ? Sh::kBins - 1 : whi;
+            }
+            // (as exponent arguments; the bins' own rounding need not be met, every logit only has to fall on one side)
+            const float yhi = wlo == 0 ? __builtin_inff() : ((float)(kTopOctaves * Sh::kPerOctave - wlo) + 0.5f) / kScale;
+            const float ylo = ((float)(kTopOctaves * Sh::kPerOctave - whi) - 0.5f) / kScale;
+            double all = 0.0, over = 0.0;
+            float all4 = 0.f;
+            // the lane's weight above the window; its logits inside the window join the list
+            auto part = [&](const u32x4 &v, int32_t c) __attribute__((always_inline)) {
+                float x[EPV], sum[EPV / 4];
+                values(v, x);
+#pragma unroll
+                for (int h = 0; h < EPV / 4; ++h) {          // (four at a time: eight do not fit the registers)
+                    float y[4], e[4];
+                    bool any = false;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        y[i] = fmaf(x[4 * h + i], k, nr);
+                        e[i] = fast_exp2(y[i]);
+                        any |= y[i] >= ylo && y[i] <= yhi;
+                    }
+                    all4 += (e[0] + e[1]) + (e[2] + e[3]);
+                    if (any) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            if (y[i] >= ylo && y[i] <= yhi) {
+                                const uint32_t key = order_key(x[4 * h + i]);
+                                const uint32_t j = atomicAdd(&sh.n, 1u);
+                                if (j < (uint32_t)Sh::kList) {
+                                    sh.key[j] = key;
+                                    sh.q[j] = fixed_mass(e[i]);
+                                    sh.at[j] = (uint16_t)c;
+                                }
+                            }
+                    }
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) e[i] = y[i] > yhi ? e[i] : 0.f;
+                    sum[h] = (e[0] + e[1]) + (e[2] + e[3]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if constexpr (EPV == 8) return sum[0] + sum[1];
+                else return sum[0];
+            };
+            float t[4];
+            sweep(No{}, [&](const u32x4 &v, int p, int32_t tile) __attribute__((always_inline)) {
+                t[p & 3] = part(v, (tile * NP + p) * W + wave);
+                if ((p & 3) == 3) {
+                    all += (double)all4;
+                    all4 = 0.f;
+                    wave_sum4_in_lane63(t[0], t[1], t[2], t[3]);
+                    if (lane == 63) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            sh.chunk[(tile * NP + (p & ~3) + i) * W + wave] = t[i];
+                            over += (double)t[i];
+                        }
+                    }
+                }
+            });
+            const int32_t ctail = ntiles * NP * W;
+            float tl = 0.f;
+            if (tail != 0 && wave == 0) tl = part(rest, ctail);
+            if (tid == 0) {
+                sh.chunk[ctail] = tl;
+                sh.run = (double)tl;
+            }
+            all = wave_sum(all + (double)all4);
+            if (lane == 63) {
+                sh.wave_d[wave] = all;
+                sh.wave_e[wave] = over;
+            }
+            __syncthreads();
+            double unused;
+            const double need = (double)top_p * wide_total<NT>(sh.wave_d, unused);
+            const double above = wide_total<NT>(sh.wave_e, unused) + sh.run;
+            const uint32_t n = sh.n;
+            if (n <= (uint32_t)Sh::kList && above < need) {
+                const uint32_t key = close(n, 0ull, (need - above) * 0x1p40, [](auto) {});
+                if (key != 0u) {
+                    thr = from_order_key(key);
+                    for (uint32_t i = tid; i < n; i += NT)
+                        if (sh.key[i] >= key) add((lds_u64 *)sh.extra + sh.at[i], sh.q[i]);
+                    closed = true;
+                }
+            }
+        }
+        if (!closed) {
+            some = select(No{}, -__builtin_inff(), thr);
+            summed = false;
+        } else {
+            summed = true;
+        }
+    }
+    if (a.tokens_out == nullptr) {
+        if (tid == 0) thr_out[r] = some ? thr : -__builtin_inff();
+        return;
+    }
+    if (!some) {
+        safe_row();
+        return;
+    }
+
+    // ------------------------------------------------------------------ the step over the kept logits
+    const float nr = -ref;
+    auto lane_sum = [&](const u32x4 &v) __attribute__((always_inline)) { return tile_lane_sum<DT, true>(v, k, nr, thr); };
+    const int32_t nchunks = ntiles * NP * W + 1;             // the last one: the piece that the row ends in
+    if (!summed) {
+        __syncthreads();
+        if constexpr (TOPK) {
+            float t[4];
+            sweep(No{}, [&](const u32x4 &v, int p, int32_t tile) __attribute__((always_inline)) {
+                t[p & 3] = lane_sum(v);
+                if ((p & 3) == 3) {
+                    wave_sum4_in_lane63(t[0], t[1], t[2], t[3]);
+                    if (lane == 63) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) sh.chunk[(tile * NP + (p & ~3) + i) * W + wave] = t[i];
+                    }
+                }
+            });
+        } else {
+            for (int32_t c = wave; c < nchunks - 1; c += W) {
+                const int32_t i = c * 64 + lane;
+                const float t = wave_sum(lane_sum(piece_at(i < nwhole ? i : nwhole + 1)));
+                if (lane == 0) sh.chunk[c] = t;
+            }
+        }
+        if (tid == 0) sh.chunk[nchunks - 1] = tail != 0 ? lane_sum(rest) : 0.f;
+    }
+    __syncthreads();
+    auto chunk_weight = [&](int32_t c) __attribute__((always_inline)) {
+        return (double)sh.chunk[c] + (summed ? (double)sh.extra[c] * 0x1p-40 : 0.0);
+    };
+    const int32_t per = (nchunks + NT - 1) / NT;
+    double mine = 0.0;
+    for (int32_t i = 0; i < per; ++i) {
+        const int32_t c = tid * per + i;
+        if (c < nchunks) mine += chunk_weight(c);
+    }
+    const double incl_w = wave_scan_add(mine);
+    if (lane == 63) sh.wave_d[wave] = incl_w;
+    __syncthreads();
+    double base;
+    const double S = wide_total<NT>(sh.wave_d, base);
+    const double tau = (double)a.codes[r] * S;
+    // the first thread whose running sum passes c*S; past the end by rounding: the last that holds weight
+    const u64 hit = __ballot(base + incl_w > tau), full = __ballot(mine > 0.0);
+    if (lane == 0) {
+        sh.wave_lo[wave] = hit ? (uint32_t)__builtin_ctzll(hit) : 64u;
+        sh.wave_hi[wave] = full ? 63u - (uint32_t)__builtin_clzll(full) : 64u;
+    }
+    __syncthreads();
+    int32_t owner = 0;
+    {
+        const uint32_t lo = lane < W ? sh.wave_lo[lane] : 64u, hi = lane < W ? sh.wave_hi[lane] : 64u;
+        const u64 any = __ballot(lo < 64u), some = __ballot(hi < 64u);
+        if (any) {
+            const int w = (int)__builtin_ctzll(any);
+            owner = w * 64 + __builtin_amdgcn_readlane((int)lo, w);
+        } else if (some) {
+            const int w = 63 - (int)__builtin_clzll(some);
+            owner = w * 64 + __builtin_amdgcn_readlane((int)hi, w);
+        }
+    }
+    if (tid == owner) {
+        double acc = base + incl_w - mine, at = acc;
+        int32_t found = -1, lastc = tid * per;
+        for (int32_t i = 0; i < per; ++i) {
+            const int32_t c = tid * per + i;
+            if (c >= nchunks) break;
+            const double v = chunk_weight(c);
+            if (v > 0.0) {
+                if (found < 0) { lastc = c; at = acc; }
+                if (found < 0 && acc + v > tau) found = c;
+            }
+            acc += v;
+        }
+        sh.pick = found >= 0 ? found : lastc;
+        sh.run = at;
+    }
+    __syncthreads();
+    if (wave != 0) return;
+    const int32_t ch = sh.pick < nchunks ? sh.pick : nchunks - 1;
+    const double run = sh.run;
+    // the chunk's pieces once more; lane, then logit
+    const int32_t pi = ch < nchunks - 1 ? ch * 64 + lane : (lane == 0 ? nwhole : nwhole + 1);
+    const u32x4 hv = piece_at(ch < nchunks - 1 && pi >= nwhole ? nwhole + 1 : pi);
+    const double lv = (double)lane_sum(hv);
+    const double incl = wave_scan_add(lv) + run;
+    const u64 hit2 = __ballot(incl > tau), nz2 = __ballot(lv > 0.0);
+    const int l2 = hit2 ? (int)__builtin_ctzll(hit2) : (nz2 ? 63 - (int)__builtin_clzll(nz2) : 0);
+    if (lane != l2) return;
+    float x[EPV];
+    values(hv, x);
+    double acc = incl - lv, before = acc, ev = 0.0, before_last = acc, ev_last = 0.0;
+    int ih = -1, ilast = 0;
+#pragma unroll
+    for (int i = 0; i < EPV; ++i) {
+        const double e = x[i] >= thr ? (double)fast_exp2(fmaf(x[i], k, nr)) : 0.0;
+        if (e > 0.0) { ilast = i; before_last = acc; ev_last = e; }
+        if (ih < 0 && acc + e > tau) { ih = i; before = acc; ev = e; }
+        acc += e;
+    }
+    if (ih < 0) { ih = ilast; before = before_last; ev = ev_last; }
+    int64_t token = (int64_t)pi * EPV + ih - shift;
+    token = token < 0 ? 0 : (token > V - 1 ? V - 1 : token);
+    RowOut o;
+    o.token = (int32_t)token;
+    o.c_next = rescale_code(tau, before, ev);
+    o.prob = (float)(ev / S);
+    o.f_lo = (float)(before / S);
+    write_row(a, r, o);
+}
+
+template <int DT, int NT, int NP, bool MULTI, bool TOPK>
+void launch_form(as_ctx *ctx, int kid, const StepArgs &a, int32_t top_k, float top_p, float *thr_out)
+{
+    launch(ctx, kid, wide_step_kernel<DT, NT, NP, MULTI, TOPK>, dim3((unsigned)a.rows), dim3(NT), 0, a, top_k, top_p, thr_out);
+}
+
+// Threads and pieces a thread by the row's pieces of 16 bytes and the number of rows.  With a row per compute unit or
+// fewer, 1024 threads finish it soonest (one row of 50257 bf16: nucleus 20 us, top-k 40 12 us).  With more, smaller
+// blocks that share a unit overlap each other's loads and tails: two blocks of 512 where two fit (300 rows of 20003
+// bf16: nucleus 22 us; as blocks of 1024 47), and with top-k, whose work after the loads is short, as few threads as hold
+// the row (2500 rows of 20003 bf16, top-k 40: 43 us with 256 threads, 67 with 512).  The bf16 nucleus, with twice the
+// logits in a register, does not fit 16 pieces (2500 rows of 50257: 240 us with 512 x 16, 203 with 1024 x 8): a row
+// beyond 1024 x 8 goes tile by tile.
+template <int DT, bool TOPK>
+void launch_type(as_ctx *ctx, int kid, const StepArgs &a, int32_t top_k, float top_p, float *thr_out)
+{
+    constexpr int EPV = Elem<DT>::kPerVec;
+    constexpr bool kDeep = TOPK || DT == AS_F32;             // 16 pieces a thread fit the registers
+    const int64_t most = ((int64_t)a.V + EPV - 1) / EPV;     // whole pieces of a row, whatever its alignment
+    const bool many = a.rows > (int64_t)ctx->num_cus, lots = a.rows > 2 * (int64_t)ctx->num_cus;
+    if (most <= 256 * 4) return launch_form<DT, 256, 4, false, TOPK>(ctx, kid, a, top_k, top_p, thr_out);
+    if constexpr (kDeep) {
+        if (lots && most <= 256 * 16 && (TOPK ? top_k <= kWideTopK : most > 512 * 4))
+            return launch_form<DT, 256, 16, false, TOPK>(ctx, kid, a, top_k, top_p, thr_out);
+    }
+    if constexpr (!TOPK && DT == AS_F32) {
+        if (lots && most <= 256 * 8) return launch_form<DT, 256, 8, false, TOPK>(ctx, kid, a, top_k, top_p, thr_out);
+    }
+    if (many && most <= 512 * 4) return launch_form<DT, 512, 4, false, TOPK>(ctx, kid, a, top_k, top_p, thr_out);
+    if (many && most <= 512 * 8) return launch_form<DT, 512, 8, false, TOPK>(ctx, kid, a, top_k, top_p, thr_out);
+    if constexpr (kDeep) {
+        if (many && most <= 512 * 16) return launch_form<DT, 512, 16, false, TOPK>(ctx, kid, a, top_k, top_p, thr_out);
+    }
+    if (most <= 1024 * 4) return launch_form<DT, 1024, 4, false, TOPK>(ctx, kid, a, top_k, top_p, thr_out);
+    if (most <= 1024 * 8) return launch_form<DT, 1024, 8, false, TOPK>(ctx, kid, a, top_k, top_p, thr_out);
+    if constexpr (kDeep) {
+        if (most <= 1024 * 16) return launch_form<DT, 1024, 16, false, TOPK>(ctx, kid, a, top_k, top_p, thr_out);
+    }
+    if constexpr (!TOPK) {
+        // (with a tile of slack: the last one's chunks are counted whole)
+        if (many && most + 512 * 8 <= 64 * (int64_t)(WideShared<512, true>::kChunks - 1))
+            return launch_form<DT, 512, 8, true, false>(ctx, kid, a, top_k, top_p, thr_out);
+    }
+    launch_form<DT, 1024, TOPK ? 16 : 8, true, TOPK>(ctx, kid, a, top_k, top_p, thr_out);
+}
+
+}  // namespace
+
+// Truncation (top_k on: > 0, else 0; top_p on: in (0, 1), else 1) and the sampling step in one launch; without
+// a.tokens_out the keep thresholds alone, to thr_out.
+as_status launch_wide(as_ctx *ctx, const StepArgs &a, int32_t top_k, float top_p, float *thr_out)
+{
+    if (a.rows == 0) return AS_OK;
+    const int kid = a.tokens_out ? kKernelStep : kKernelThreshold;
+    if (a.dtype == AS_BF16) {
+        if (top_k > 0) launch_type<AS_BF16, true>(ctx, kid, a, top_k, top_p, thr_out);
+        else launch_type<AS_BF16, false>(ctx, kid, a, top_k, top_p, thr_out);
+    } else {
+        if (top_k > 0) launch_type<AS_F32, true>(ctx, kid, a, top_k, top_p, thr_out);
+        else launch_type<AS_F32, false>(ctx, kid, a, top_k, top_p, thr_out);
+    }
+    AS_HIP_TRY(ctx, hipGetLastError());
+    return AS_OK;
+}
+
+}  // namespace as

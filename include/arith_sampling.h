@@ -91,7 +91,8 @@ const char *as_last_error(const as_ctx *ctx);
  *                       kernel also for rows that fit the single-tile one;
  *                       9 the plain three-pass kernel (slow; any alignment)
  *   AS_TUNE_GEMM_SHAPE  logits kernel: 1 = the 128x256 tile kernel instead of
- *                       the persistent one
+ *                       the persistent one and the one for few rows; 2 = the
+ *                       persistent one also for few rows
  *   AS_TUNE_THR_PATH    keep-threshold kernel: 1 = the radix select instead of
  *                       the others; 2 = the 256-thread register-resident
  *                       kernel wherever the row fits it; 3 = the kernel for

@@ -605,6 +605,214 @@ __global__ __launch_bounds__(256, 2) void bigram_gemm_bf16(const uint16_t *__res
     do_pass(std::integral_constant<int, 3>{});
 }
 
+// ---- thin kernel: few rows (a prompt's handful of codes, a first step's prompts) ---------------
+//
+// With up to 128 rows the product is a pass over Ut (33 MB at 32128 x 512) and the persistent kernel's 256 x 256
+// tiles leave half of the chip without one, each with 3 us of latency in front of its first product and
+// rows of padding behind.  Here a block of four waves takes 128 columns and all rows (MT tiles of 32), so
+// that V = 32128 is 251 blocks; K stages of 64 (one 128-byte line per row, loader and swizzle as in the persistent
+// kernel) run through a ring of four, three stages requested ahead: 48 KB of Ut in flight per block, two blocks on a CU
+// at MT = 1.  Same MFMA, K ascending, same epilogue arithmetic: a row's logits (and group masses) are the same
+// bits whichever kernel makes them.
+constexpr int TN = 128, kThinRing = 4;
+template <int MT> constexpr int kThinStage = (TN + 32 * MT) * PK * 2;
+
+// the fragments of two K slices in one go: all reads, one wait, in one piece of text, so that nothing can come between
+// a read in flight and its register
+template <int MT> struct ThinFrags {
+    bf16x8 a[2], b[2][MT];
+};
+template <int MT>
+__device__ __forceinline__ void thin_read(ThinFrags<MT> &f, uint32_t a0, uint32_t b0, uint32_t a1, uint32_t b1)
+{
+    if constexpr (MT == 1) {
+        asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b128 %2, %6\n\tds_read_b128 %3, %7\n\t"
+                     "s_waitcnt lgkmcnt(0)"
+                     : "=&v"(f.a[0]), "=&v"(f.b[0][0]), "=&v"(f.a[1]), "=&v"(f.b[1][0])
+                     : "v"(a0), "v"(b0), "v"(a1), "v"(b1)
+                     : "memory");
+    } else if constexpr (MT == 2) {
+        asm volatile("ds_read_b128 %0, %6\n\tds_read_b128 %1, %7\n\tds_read_b128 %2, %7 offset:4096\n\t"
+                     "ds_read_b128 %3, %8\n\tds_read_b128 %4, %9\n\tds_read_b128 %5, %9 offset:4096\n\t"
+                     "s_waitcnt lgkmcnt(0)"
+                     : "=&v"(f.a[0]), "=&v"(f.b[0][0]), "=&v"(f.b[0][1]), "=&v"(f.a[1]), "=&v"(f.b[1][0]), "=&v"(f.b[1][1])
+                     : "v"(a0), "v"(b0), "v"(a1), "v"(b1)
+                     : "memory");
+    } else {
+        static_assert(MT == 4, "one, two or four tiles of 32 rows");
+        asm volatile("ds_read_b128 %0, %10\n\tds_read_b128 %1, %11\n\tds_read_b128 %2, %11 offset:4096\n\t"
+                     "ds_read_b128 %3, %11 offset:8192\n\tds_read_b128 %4, %11 offset:12288\n\t"
+                     "ds_read_b128 %5, %12\n\tds_read_b128 %6, %13\n\tds_read_b128 %7, %13 offset:4096\n\t"
+                     "ds_read_b128 %8, %13 offset:8192\n\tds_read_b128 %9, %13 offset:12288\n\t"
+                     "s_waitcnt lgkmcnt(0)"
+                     : "=&v"(f.a[0]), "=&v"(f.b[0][0]), "=&v"(f.b[0][1]), "=&v"(f.b[0][2]), "=&v"(f.b[0][3]),
+                       "=&v"(f.a[1]), "=&v"(f.b[1][0]), "=&v"(f.b[1][1]), "=&v"(f.b[1][2]), "=&v"(f.b[1][3])
+                     : "v"(a0), "v"(b0), "v"(a1), "v"(b1)
+                     : "memory");
+    }
+}
+
+// FUSED: as in the persistent kernel, group masses instead of logits (C: float2 [R, ldc], alpha with log2(e)/temp)
+template <class OutT, int MT, bool FUSED>
+__global__ __launch_bounds__(256) void bigram_gemm_thin(const uint16_t *__restrict__ E, const uint16_t *__restrict__ Ut,
+                                                        const int32_t *__restrict__ prev, int32_t R, int32_t V,
+                                                        int32_t d, float alpha, OutT *__restrict__ C, int64_t ldc,
+                                                        int vec_store)
+{
+    constexpr int kStage = kThinStage<MT>, kPerWave = 4 + MT;         // 1 KB requests of a wave per stage
+    constexpr int kOutStride = TN * (int)sizeof(OutT) + 16;           // bytes of a staged row of C
+    constexpr int kLds = kThinRing * kStage > 32 * MT * kOutStride ? kThinRing * kStage : 32 * MT * kOutStride;
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[kLds];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t n0 = (int64_t)blockIdx.x * TN;
+    const uint32_t rowbytes = (uint32_t)d * 2;
+    const unsigned char *Eb = reinterpret_cast<const unsigned char *>(E);
+    const unsigned char *Ub = reinterpret_cast<const unsigned char *>(Ut) + n0 * (int64_t)rowbytes;
+
+    // Loader: chunk c of a stage is 8 rows of 128 bytes; chunks 0..15 are Ut rows (padded to whole tiles of 256: no
+    // bound), 16.. are E rows.  Wave w moves chunks w, w+4, ...  A lane moves piece (lane & 7) ^ swizzle of its row.
+    const int rl = wave * 8 + (lane >> 3);                            // row within 32 of every chunk of this wave
+    const uint32_t pcoff = (uint32_t)(((lane & 7) ^ ((rl >> 1) & 7)) << 4);
+    int64_t off[kPerWave];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) off[i] = (int64_t)(i * 32 + rl) * rowbytes + pcoff;
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+        int32_t m = i * 32 + rl;
+        m = m < R ? m : R - 1;
+        off[4 + i] = (int64_t)clamp_token(prev[m], V) * rowbytes + pcoff;
+    }
+    auto request = [&](int st) __attribute__((always_inline)) {
+        unsigned char *const slot = smem + (st & (kThinRing - 1)) * kStage + wave * 1024;
+#pragma unroll
+        for (int i = 0; i < kPerWave; ++i)
+            __builtin_amdgcn_global_load_lds((glb_void *)((i < 4 ? Ub : Eb) + off[i] + (int64_t)st * (PK * 2)),
+                                             (lds_void *)(slot + i * 4096), 16, 0, 0);
+    };
+    const uint32_t lds_base = (uint32_t)(uintptr_t)(lds_void *)smem;
+    const int frow = lane & 31, fc = lane >> 5;
+    const uint32_t fsw = (uint32_t)((fc ^ ((frow >> 1) & 7)) << 4);
+    const uint32_t fa = lds_base + (uint32_t)(wave * 32 + frow) * 128 + fsw, fb = lds_base + TN * 128 + (uint32_t)frow * 128 + fsw;
+
+    f32x16 acc[MT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[i][v] = 0.f;
+    const int n = d / PK;
+    for (int st = 0; st < kThinRing - 1 && st < n; ++st) request(st);
+    for (int s = 0; s < n; ++s) {
+        // stage s has landed; up to two more stay in flight behind it
+        const int behind = n - 1 - s;
+        if (behind >= 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * kPerWave) : "memory");
+        else if (behind == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kPerWave) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        // (every wave has left stage s - 1, whose slot this is)
+        if (s + kThinRing - 1 < n) request(s + kThinRing - 1);
+        const uint32_t so = (uint32_t)(s & (kThinRing - 1)) * kStage;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            ThinFrags<MT> f;
+            thin_read<MT>(f, (fa + so) ^ (uint32_t)(h * 64), (fb + so) ^ (uint32_t)(h * 64),
+                          (fa + so) ^ (uint32_t)(h * 64 + 32), (fb + so) ^ (uint32_t)(h * 64 + 32));
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int i = 0; i < MT; ++i)
+                    acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[q], f.b[q][i], acc[i], 0, 0, 0);
+        }
+    }
+    // register v of lane l is vocabulary 8*(v/4) + 4*(l/32) + v%4 of the wave's 32, batch row l%32 of the tile
+    const int b = lane & 31, h = lane >> 5;
+    if constexpr (FUSED) {
+        float2 *P = reinterpret_cast<float2 *>(C);
+        const int64_t ncol = n0 + wave * 32;
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+            if (ncol + 32 > V) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v)
+                    if (ncol + 8 * (v >> 2) + 4 * h + (v & 3) >= V) acc[i][v] = -__builtin_inff();
+            }
+            float mx = acc[i][0];
+#pragma unroll
+            for (int v = 1; v < 16; ++v) mx = fmaxf(mx, acc[i][v]);
+            mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+            const float ref = fmaxf(ceilf(mx * alpha), -100000.f);
+            float sum = 0.f;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) sum += __builtin_amdgcn_exp2f(fmaf(acc[i][v], alpha, -ref));
+            sum += __shfl_xor(sum, 32, 64);
+            const int32_t m = i * 32 + b;
+            if (h == 0 && m < R && ncol < V) P[m * ldc + (ncol >> 5)] = float2{sum, ref};
+        }
+    } else {
+        __syncthreads();                                              // the ring gives way to the rows of C
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                unsigned char *at = smem + (i * 32 + b) * kOutStride + (wave * 32 + 8 * q + 4 * h) * (int)sizeof(OutT);
+                if constexpr (sizeof(OutT) == 2) {
+                    u32x2 w;
+                    w[0] = pack_bf16(acc[i][4 * q + 0] * alpha, acc[i][4 * q + 1] * alpha);
+                    w[1] = pack_bf16(acc[i][4 * q + 2] * alpha, acc[i][4 * q + 3] * alpha);
+                    *reinterpret_cast<u32x2 *>(at) = w;
+                } else {
+                    u32x4 w;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) w[e] = __builtin_bit_cast(uint32_t, acc[i][4 * q + e] * alpha);
+                    *reinterpret_cast<u32x4 *>(at) = w;
+                }
+            }
+        __syncthreads();
+        constexpr int kPerPiece = 16 / (int)sizeof(OutT), kPieces = TN / kPerPiece;
+        for (int p = tid; p < 32 * MT * kPieces; p += 256) {
+            const int32_t m = p / kPieces;
+            const int64_t col = n0 + (p % kPieces) * kPerPiece;
+            if (m >= R || col >= V) continue;
+            const unsigned char *sp = smem + m * kOutStride + (p % kPieces) * 16;
+            OutT *gp = C + m * ldc + col;
+            if (vec_store && col + kPerPiece <= V) {
+                *reinterpret_cast<u32x4 *>(gp) = *reinterpret_cast<const u32x4 *>(sp);
+            } else {
+                const OutT *se = reinterpret_cast<const OutT *>(sp);
+                for (int e = 0; e < kPerPiece; ++e)
+                    if (col + e < V) gp[e] = se[e];
+            }
+        }
+    }
+}
+
+// Up to 64 rows always (one launch, bf16 logits: 16 x 32128 x 512 5.2 us against 16.5 for the persistent kernel, which
+// is 6.5 TB/s of Ut; 64 rows 7.2 against 16.5; 32 x 256000 x 1024 98 against 123; 64 x 131071 x 768 39 against 48);
+// up to 128 while the columns are one round of blocks (128 x 32128 x 512 10.8 against 17.1; beyond that the
+// persistent kernel has a tile for every CU and draws level: 128 x 256000 x 1024 144 against 140).
+static bool thin_pays(const as_ctx *ctx, const as_model *m, int64_t rows)
+{
+    return ctx->gemm_shape == 0 && (rows <= 64 || (rows <= 128 && m->V <= (int64_t)TN * ctx->num_cus));
+}
+
+template <class OutT, bool FUSED>
+void launch_thin(as_ctx *ctx, const as_model *m, const int32_t *prev, int64_t rows, OutT *out, int64_t ld, float alpha,
+                 int vec_store)
+{
+    const dim3 grid((unsigned)((m->V + TN - 1) / TN)), block(256);
+    const uint16_t *Ep = (const uint16_t *)m->E, *Up = (const uint16_t *)m->Ut;
+    if (rows <= 32)
+        launch(ctx, kKernelLogits, bigram_gemm_thin<OutT, 1, FUSED>, grid, block, 0, Ep, Up, prev, (int32_t)rows, m->V,
+               m->d, alpha, out, ld, vec_store);
+    else if (rows <= 64)
+        launch(ctx, kKernelLogits, bigram_gemm_thin<OutT, 2, FUSED>, grid, block, 0, Ep, Up, prev, (int32_t)rows, m->V,
+               m->d, alpha, out, ld, vec_store);
+    else
+        launch(ctx, kKernelLogits, bigram_gemm_thin<OutT, 4, FUSED>, grid, block, 0, Ep, Up, prev, (int32_t)rows, m->V,
+               m->d, alpha, out, ld, vec_store);
+}
+
 // ---- vector kernel: what the MFMA kernels do not take (fp32 weights, or a rank d that is not a multiple of
 // their K step), any size and alignment ------------------------------------------------------------------
 //
@@ -846,7 +1054,12 @@ as_status launch_bigram_logits(as_ctx *ctx, const as_model *m, const int32_t *pr
         // the persistent kernel addresses operand rows with 32-bit byte offsets and wants two K stages
         const bool persistent = ctx->gemm_shape != 1 && m->d >= 2 * PK && (int64_t)m->V * m->d * 2 < (1LL << 32) &&
                                 ctx->num_cus >= 8;
-        if (persistent) {
+        if (thin_pays(ctx, m, rows)) {
+            if (ctx->dtype == AS_BF16)
+                launch_thin<uint16_t, false>(ctx, m, prev, rows, (uint16_t *)logits_out, ld, alpha, vec_store);
+            else
+                launch_thin<float, false>(ctx, m, prev, rows, (float *)logits_out, ld, alpha, vec_store);
+        } else if (persistent) {
             const dim3 grid((unsigned)(8 * (ctx->num_cus / 8))), block(512);
             if (ctx->dtype == AS_BF16)
                 launch(ctx, kKernelLogits, bigram_gemm_persistent<uint16_t>, grid, block, 0, Ep, Up, prev, rows,
@@ -894,6 +1107,11 @@ as_status launch_bigram_partials(as_ctx *ctx, const as_model *m, const int32_t *
 {
     if (rows == 0) return AS_OK;
     const float alpha = (float)((double)m->scale / sqrt((double)m->d) * 1.44269504088896340736 / (double)temp);
+    if (thin_pays(ctx, m, rows)) {
+        launch_thin<float, true>(ctx, m, prev, rows, reinterpret_cast<float *>(part), ldp, alpha, 0);
+        AS_HIP_TRY(ctx, hipGetLastError());
+        return AS_OK;
+    }
     const dim3 grid((unsigned)(8 * (ctx->num_cus / 8))), block(512);
     launch(ctx, kKernelLogits, bigram_gemm_persistent<float, true>, grid, block, 0, (const uint16_t *)m->E,
            (const uint16_t *)m->Ut, prev, rows, m->V, m->d, alpha, reinterpret_cast<float *>(part), ldp, 0,

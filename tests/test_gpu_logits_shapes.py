@@ -15,6 +15,12 @@ _VEC = [(63, 7, "f32", "f32", 1), (64, 32, "f32", "f32", 64), (65, 33, "f32", "b
         (700, 72, "bf16", "f32", 100), (333, 257, "bf16", "bf16", 129), (16500, 40, "f32", "f32", 520),
         (8200, 31, "f32", "bf16", 1030)]
 
+# the MFMA kernels: the one for few rows at its tiles of 32 rows and 128 columns, one K stage to five (its ring holds
+# four), and one row more than it takes
+_THIN = [(127, 64, "bf16", "bf16", 1), (129, 64, "bf16", "f32", 32), (128, 128, "bf16", "bf16", 33),
+         (1000, 192, "bf16", "f32", 64), (257, 256, "bf16", "bf16", 65), (4099, 320, "bf16", "bf16", 128),
+         (300, 64, "bf16", "f32", 129), (300, 576, "bf16", "bf16", 17)]
+
 
 def _logits(model, prev, V, ldt, rows):
     import torch
@@ -32,7 +38,7 @@ def _logits(model, prev, V, ldt, rows):
     return got[:, :V]
 
 
-@pytest.mark.parametrize("V,d,wdt,ldt,R", _VEC)
+@pytest.mark.parametrize("V,d,wdt,ldt,R", _VEC + _THIN)
 def test_logits_tile_edges(V, d, wdt, ldt, R):
     import torch
     from paper_2210_15458_amd import binding as B
@@ -54,3 +60,26 @@ def test_logits_tile_edges(V, d, wdt, ldt, R):
     for r in {0, R // 2, R - 1}:
         assert np.array_equal(_logits(model, prev[r:r + 1], V, ldt, 1)[0], got[r])
     model.close()
+
+
+@pytest.mark.parametrize("V,d,R", [(127, 128, 1), (1000, 192, 33), (4099, 320, 65), (33001, 128, 64)])
+def test_group_masses_of_few_rows(V, d, R):
+    # the few-rows kernel against the persistent one: the same bits
+    import torch
+    from paper_2210_15458_amd import binding as B
+    from gpu_util import to_dev_logits
+    E, U = synth.bigram_weights(V, d, seed=V + d, dtype="bf16")
+    model = B.Model(to_dev_logits(E), to_dev_logits(U), scale=3.0)
+    prev = torch.from_numpy(np.random.default_rng(R).integers(0, V, R).astype(np.int32)).cuda()
+    ldp = (-(-V // 32) + 15) // 16 * 16
+    res = []
+    for shape in (0, 2):
+        ctx = B.Ctx(R, V, torch.bfloat16)
+        ctx.set_tuning("gemm_shape", shape)
+        mass = torch.zeros((R, ldp, 2), dtype=torch.float32, device="cuda")
+        B.as_bigram_group_mass(ctx, model, prev, 0.8, mass)
+        torch.cuda.synchronize()
+        res.append(mass.cpu().numpy())
+        ctx.close()
+    model.close()
+    assert np.array_equal(res[0], res[1])

@@ -410,6 +410,66 @@ as_status as_bigram_logits(as_ctx *ctx, const as_model *model, const int32_t *pr
     return launch_bigram_logits(ctx, model, prev, rows, logits_out, ld);
 }
 
+// The state of a running decode or encode in the context's workspace: per row the code, the conditioning token and the
+// finished flag, and the tables of shared logits rows where those pay.
+struct DecodeState {
+    float *codes;
+    int32_t *prev;
+    uint8_t *fin;
+    bool share;
+    RowShare tables;
+};
+
+static as_status decode_state(as_ctx *ctx, const as_model *model, int64_t R, int32_t T, DecodeState &s)
+{
+    s.share = sharing_pays(ctx, model, R, T);
+    const size_t words = (size_t)R * 2 + (s.share ? (size_t)R + 2 * (size_t)ctx->V + (size_t)T : 0);
+    as_status st = grow(ctx, ctx->state, words * 4 + (size_t)R);
+    if (st != AS_OK) return st;
+    int32_t *w = static_cast<int32_t *>(ctx->state.ptr);
+    s.codes = reinterpret_cast<float *>(w);
+    s.prev = w + R;
+    w += 2 * R;
+    s.tables = RowShare{};
+    if (s.share) {
+        s.tables.token = w;
+        s.tables.mark = w + R;
+        s.tables.slot = s.tables.mark + ctx->V;
+        s.tables.count = s.tables.slot + ctx->V;
+        w = s.tables.count + T;
+        st = launch_share_clear(ctx, s.tables, T);
+    }
+    s.fin = reinterpret_cast<uint8_t *>(w);
+    return st;
+}
+
+// The rows of the model's output that step t of a decode needs: in the first step one per prompt (its N codes condition
+// on the same token; ctx->rid already says so), later one per row, or one per token in use where that pays.
+// `rows` is their largest number, `rows_dev` holds the number itself where only the device knows it.
+struct StepRows {
+    const int32_t *prev;
+    int64_t rows;
+    const int32_t *rows_dev;
+    const int32_t *row_ids;
+    int64_t src_rows;
+};
+
+static as_status step_rows(as_ctx *ctx, const DecodeState &s, const int32_t *prompts, int32_t B, int32_t N, int32_t t,
+                           int32_t eos_id, StepRows &o)
+{
+    const int64_t R = (int64_t)B * N;
+    if (t == 0 && N > 1) {
+        o = StepRows{prompts, B, nullptr, ctx->rid, B};
+        return AS_OK;
+    }
+    if (t == 0 || !s.share) {
+        o = StepRows{s.prev, R, nullptr, nullptr, 0};
+        return AS_OK;
+    }
+    o = StepRows{s.tables.token, R, s.tables.count + t, ctx->rid, 0};
+    return launch_share(ctx, s.tables, t, s.prev, eos_id >= 0 ? s.fin : nullptr, R, ctx->rid);
+}
+
 // as_decode and as_decode_ancestral: with `uniforms` the code of row r at step t is uniforms[t*R + r] and
 // the rescaled code is dropped, otherwise codes start on the lattice of u and are carried from step to step.
 static as_status decode_impl(as_ctx *ctx, const as_model *model, const int32_t *prompts, int32_t B, int32_t N,
@@ -433,17 +493,21 @@ static as_status decode_impl(as_ctx *ctx, const as_model *model, const int32_t *
     const int64_t ldw = ((int64_t)ctx->V + 7) / 8 * 8;        // rows start 16-byte aligned
     as_status st = grow(ctx, ctx->logits, (size_t)R * ldw * esz);
     if (st != AS_OK) return st;
-    st = grow(ctx, ctx->state, (size_t)R * 9);
+    DecodeState state;
+    st = decode_state(ctx, model, R, T, state);
     if (st != AS_OK) return st;
-    float *codes = static_cast<float *>(ctx->state.ptr);
-    int32_t *prev = reinterpret_cast<int32_t *>(codes + R);
-    uint8_t *fin = reinterpret_cast<uint8_t *>(prev + R);
+    float *const codes = state.codes;
+    int32_t *const prev = state.prev;
+    uint8_t *const fin = state.fin;
 
-    st = launch_lattice(ctx, u, B, N, uniforms ? nullptr : codes, prompts, prev, fin);
+    st = launch_lattice(ctx, u, B, N, uniforms ? nullptr : codes, prompts, prev, fin, ctx->rid);
     if (st != AS_OK) return st;
     const bool trunc = truncation_on(ctx->V, top_k, top_p);
     for (int32_t t = 0; t < T; ++t) {
-        st = launch_bigram_logits(ctx, model, prev, R, ctx->logits.ptr, ldw);
+        StepRows sr;
+        st = step_rows(ctx, state, prompts, B, N, t, eos_id, sr);
+        if (st != AS_OK) return st;
+        st = launch_bigram_logits(ctx, model, sr.prev, sr.rows, ctx->logits.ptr, ldw, sr.rows_dev);
         if (st != AS_OK) return st;
         StepArgs a{};
         a.logits = ctx->logits.ptr; a.rows = R; a.ld = ldw; a.V = ctx->V; a.dtype = ctx->dtype;
@@ -451,13 +515,13 @@ static as_status decode_impl(as_ctx *ctx, const as_model *model, const int32_t *
         a.tokens_out = tokens_out + t; a.tok_stride = T; a.codes_out = codes;
         a.finished_in = eos_id >= 0 ? fin : nullptr; a.eos_id = eos_id;
         a.finished_out = eos_id >= 0 ? fin : nullptr;
-        a.prob_out = nullptr; a.flo_out = nullptr; a.row_ids = nullptr; a.prev_out = prev;
+        a.prob_out = nullptr; a.flo_out = nullptr; a.row_ids = sr.row_ids; a.src_rows = sr.src_rows; a.prev_out = prev;
         if (trunc) {
             if (launch_topk_step(ctx, a, top_k, top_p, &st)) {
                 if (st != AS_OK) return st;
                 continue;
             }
-            st = launch_threshold(ctx, ctx->logits.ptr, R, ldw, eos_id >= 0 ? fin : nullptr, nullptr, temp,
+            st = launch_threshold(ctx, ctx->logits.ptr, R, ldw, eos_id >= 0 ? fin : nullptr, sr.row_ids, temp,
                                   top_k, top_p, ctx->thr);
             if (st != AS_OK) return st;
             a.thr = ctx->thr;
@@ -562,20 +626,24 @@ as_status as_decode_fused(as_ctx *ctx, const as_model *model, const int32_t *pro
     const int64_t ldp = ((int64_t)ngroups + 15) / 16 * 16;
     as_status st = grow(ctx, ctx->logits, (size_t)R * ldp * sizeof(float2));
     if (st != AS_OK) return st;
-    st = grow(ctx, ctx->state, (size_t)R * 9);
+    DecodeState state;
+    st = decode_state(ctx, model, R, T, state);
     if (st != AS_OK) return st;
-    float *codes = static_cast<float *>(ctx->state.ptr);
-    int32_t *prev = reinterpret_cast<int32_t *>(codes + R);
-    uint8_t *fin = reinterpret_cast<uint8_t *>(prev + R);
+    float *const codes = state.codes;
+    int32_t *const prev = state.prev;
+    uint8_t *const fin = state.fin;
     float2 *part = static_cast<float2 *>(ctx->logits.ptr);
 
-    st = launch_lattice(ctx, u, B, N, codes, prompts, prev, fin);
+    st = launch_lattice(ctx, u, B, N, codes, prompts, prev, fin, ctx->rid);
     if (st != AS_OK) return st;
     for (int32_t t = 0; t < T; ++t) {
-        st = launch_bigram_partials(ctx, model, prev, R, temp, part, ldp);
+        StepRows sr;
+        st = step_rows(ctx, state, prompts, B, N, t, eos_id, sr);
+        if (st != AS_OK) return st;
+        st = launch_bigram_partials(ctx, model, sr.prev, sr.rows, temp, part, ldp, sr.rows_dev);
         if (st != AS_OK) return st;
         FusedArgs a{};
-        a.part = part; a.ldp = ldp; a.ngroups = ngroups; a.rows = R; a.V = ctx->V; a.d = model->d;
+        a.part = part; a.row_ids = sr.row_ids; a.ldp = ldp; a.ngroups = ngroups; a.rows = R; a.V = ctx->V; a.d = model->d;
         a.E = static_cast<const uint16_t *>(model->E); a.Ut = static_cast<const uint16_t *>(model->Ut);
         a.alpha = (float)((double)model->scale / sqrt((double)model->d) * 1.44269504088896340736 / (double)temp);
         a.codes = codes; a.codes_out = codes; a.tokens_out = tokens_out + t; a.tok_stride = T;
@@ -657,20 +725,23 @@ as_status as_encode(as_ctx *ctx, const as_model *model, const int32_t *prompts, 
     const int64_t ldw = ((int64_t)ctx->V + 7) / 8 * 8;        // rows start 16-byte aligned
     as_status st = grow(ctx, ctx->logits, (size_t)R * ldw * esz);
     if (st != AS_OK) return st;
-    st = grow(ctx, ctx->state, (size_t)R * 9);
+    DecodeState state;
+    st = decode_state(ctx, model, R, T, state);
     if (st != AS_OK) return st;
-    float *codes = static_cast<float *>(ctx->state.ptr);      // (unused here; same layout as as_decode)
-    int32_t *prev = reinterpret_cast<int32_t *>(codes + R);
-    uint8_t *fin = reinterpret_cast<uint8_t *>(prev + R);
+    int32_t *const prev = state.prev;
+    uint8_t *const fin = state.fin;
 
-    st = launch_interval_init(ctx, B, N, prompts, lo_out, width_out, prev, fin);
+    st = launch_interval_init(ctx, B, N, prompts, lo_out, width_out, prev, fin, ctx->rid);
     if (st != AS_OK) return st;
     const bool trunc = truncation_on(ctx->V, top_k, top_p);
     for (int32_t t = 0; t < T; ++t) {
-        st = launch_bigram_logits(ctx, model, prev, R, ctx->logits.ptr, ldw);
+        StepRows sr;
+        st = step_rows(ctx, state, prompts, B, N, t, eos_id, sr);
+        if (st != AS_OK) return st;
+        st = launch_bigram_logits(ctx, model, sr.prev, sr.rows, ctx->logits.ptr, ldw, sr.rows_dev);
         if (st != AS_OK) return st;
         if (trunc) {
-            st = launch_threshold(ctx, ctx->logits.ptr, R, ldw, eos_id >= 0 ? fin : nullptr, nullptr, temp,
+            st = launch_threshold(ctx, ctx->logits.ptr, R, ldw, eos_id >= 0 ? fin : nullptr, sr.row_ids, temp,
                                   top_k, top_p, ctx->thr);
             if (st != AS_OK) return st;
         }
@@ -680,7 +751,7 @@ as_status as_encode(as_ctx *ctx, const as_model *model, const int32_t *prompts, 
         a.thr = trunc ? ctx->thr : nullptr;
         a.finished_in = eos_id >= 0 ? fin : nullptr; a.eos_id = eos_id;
         a.finished_out = eos_id >= 0 ? fin : nullptr;
-        a.lo = lo_out; a.width = width_out; a.row_ids = nullptr; a.prev_out = prev;
+        a.lo = lo_out; a.width = width_out; a.row_ids = sr.row_ids; a.src_rows = sr.src_rows; a.prev_out = prev;
         st = launch_interval(ctx, a);
         if (st != AS_OK) return st;
     }

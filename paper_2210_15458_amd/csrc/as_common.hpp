@@ -110,6 +110,7 @@ inline bool stream_rows(int64_t rows, int64_t ld, size_t esz)
 struct StepArgs {
     const void *logits;
     int64_t rows;
+    int64_t src_rows;            // rows of logits that row_ids can name (0: as many as rows)
     int64_t ld;
     int32_t V;
     as_dtype dtype;
@@ -132,6 +133,7 @@ struct StepArgs {
 struct IntervalArgs {
     const void *logits;
     int64_t rows;
+    int64_t src_rows;            // as in StepArgs
     int64_t ld;
     int32_t V;
     as_dtype dtype;
@@ -150,6 +152,7 @@ struct IntervalArgs {
 
 struct FusedArgs {
     const float2 *part;          // [rows, ldp]: (sum, reference) per group of 32 logits
+    const int32_t *row_ids;      // row r's masses are row row_ids[r] of part, or null
     int64_t ldp;                 // multiple of 16
     int32_t ngroups;             // ceil(V / 32)
     int64_t rows;
@@ -172,23 +175,38 @@ struct FusedArgs {
 as_status launch_step(as_ctx *ctx, const StepArgs &a);
 as_status launch_fused_sample(as_ctx *ctx, const FusedArgs &a);
 as_status launch_bigram_partials(as_ctx *ctx, const as_model *m, const int32_t *prev, int64_t rows, float temp,
-                                 float2 *part, int64_t ldp);
+                                 float2 *part, int64_t ldp, const int32_t *rows_dev = nullptr);
 bool fused_path_applies(const as_ctx *ctx, const as_model *m);
 as_status launch_interval(as_ctx *ctx, const IntervalArgs &a);
 as_status launch_interval_init(as_ctx *ctx, int32_t B, int32_t N, const int32_t *prompts, double *lo,
-                               double *width, int32_t *prev, uint8_t *finished);
+                               double *width, int32_t *prev, uint8_t *finished, int32_t *row_ids);
 bool launch_topk_step(as_ctx *ctx, const StepArgs &a, int32_t top_k, float top_p, as_status *st);
 as_status launch_wide(as_ctx *ctx, const StepArgs &a, int32_t top_k, float top_p, float *thr_out);
 as_status launch_threshold(as_ctx *ctx, const void *logits, int64_t rows, int64_t ld,
                            const uint8_t *finished_in, const int32_t *row_ids,
                            float temp, int32_t top_k, float top_p, float *thr_out);
 as_status launch_lattice(as_ctx *ctx, const float *u, int32_t B, int32_t N, float *codes_out,
-                         const int32_t *prompts, int32_t *prev_out, uint8_t *finished_out);
+                         const int32_t *prompts, int32_t *prev_out, uint8_t *finished_out,
+                         int32_t *row_ids_out = nullptr);
 as_status launch_estimate(as_ctx *ctx, const int32_t *tokens, int32_t B, int32_t N, int32_t T, const float *score,
                           int32_t eos_id, double *est_out);
 as_status launch_transpose(const void *U, void *Ut, int32_t d, int32_t V, as_dtype wdtype);
+// rows_dev: the number of rows, at most `rows`, read on the device (persistent kernel only)
 as_status launch_bigram_logits(as_ctx *ctx, const as_model *m, const int32_t *prev,
-                               int64_t rows, void *logits_out, int64_t ld);
+                               int64_t rows, void *logits_out, int64_t ld, const int32_t *rows_dev = nullptr);
+
+// Rows of a decode that condition on the same token have the same logits: one row of them is computed for each
+// token in use, and the rows are told which.  The tables live in the context's decode state.
+struct RowShare {
+    int32_t *mark = nullptr;     // [V] last step that used the token
+    int32_t *slot = nullptr;     // [V] its logits row in that step
+    int32_t *token = nullptr;    // [R] token of each logits row
+    int32_t *count = nullptr;    // [T] logits rows of each step
+};
+bool sharing_pays(const as_ctx *ctx, const as_model *m, int64_t rows, int32_t T);
+as_status launch_share_clear(as_ctx *ctx, const RowShare &s, int32_t T);
+as_status launch_share(as_ctx *ctx, const RowShare &s, int32_t step, const int32_t *prev, const uint8_t *finished,
+                       int64_t rows, int32_t *row_ids);
 
 // ------------------------------------------------------------ wave primitives
 // Data-parallel-primitive (DPP) cross-lane moves.  bound_ctrl is off, so a lane

@@ -38,7 +38,8 @@ __global__ __launch_bounds__(256) void fused_sample_kernel(FusedArgs a)
     const int64_t r = blockIdx.x;
     const int nvec = (int)(a.ldp / 2);                            // float4 = two groups
     const int ntiles = MULTI ? (int)((a.ldp + kTileGroups - 1) / kTileGroups) : 1;
-    const float4 *prow4 = reinterpret_cast<const float4 *>(a.part + r * a.ldp);
+    const int64_t src = a.row_ids ? (int64_t)a.row_ids[r] : r;
+    const float4 *prow4 = reinterpret_cast<const float4 *>(a.part + src * a.ldp);
     float4 tw[kGroupsPerLane / 2];
     // a tile of the row's table, whole lines at a time
     auto load_tile = [&](int tile) __attribute__((always_inline)) {

@@ -349,7 +349,7 @@ __global__ __launch_bounds__(kThreads, 4) void interval_tile_kernel(IntervalArgs
 }
 
 __global__ void interval_init_kernel(int32_t B, int32_t N, const int32_t *prompts, double *lo, double *width,
-                                     int32_t *prev, uint8_t *finished)
+                                     int32_t *prev, uint8_t *finished, int32_t *row_ids)
 {
     const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= (int64_t)B * N) return;
@@ -357,6 +357,7 @@ __global__ void interval_init_kernel(int32_t B, int32_t N, const int32_t *prompt
     width[idx] = 1.0;
     prev[idx] = prompts[idx / N];
     finished[idx] = 0;
+    row_ids[idx] = (int32_t)(idx / N);       // the first step's logits: one row per prompt
 }
 
 }  // namespace
@@ -367,7 +368,7 @@ as_status launch_interval(as_ctx *ctx, const IntervalArgs &args)
     const IntervalArgs &a = args;
     const dim3 grid((unsigned)a.rows), block(kThreads);
     const size_t esz = a.dtype == AS_BF16 ? 2 : 4;
-    const bool nt = stream_rows(a.rows, a.ld, esz);
+    const bool nt = stream_rows(a.src_rows ? a.src_rows : a.rows, a.ld, esz);
     const int epv = (int)(16 / esz);
     const bool tile = a.V % epv == 0 && a.V / epv <= kTileWaves * kTileIters * 64 &&
                       reinterpret_cast<uintptr_t>(a.logits) % 16 == 0 && (a.ld * (int64_t)esz) % 16 == 0 &&
@@ -393,12 +394,12 @@ as_status launch_interval(as_ctx *ctx, const IntervalArgs &args)
 }
 
 as_status launch_interval_init(as_ctx *ctx, int32_t B, int32_t N, const int32_t *prompts, double *lo,
-                               double *width, int32_t *prev, uint8_t *finished)
+                               double *width, int32_t *prev, uint8_t *finished, int32_t *row_ids)
 {
     const int64_t n = (int64_t)B * N;
     if (n == 0) return AS_OK;
     hipLaunchKernelGGL(interval_init_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, ctx->stream, B, N,
-                       prompts, lo, width, prev, finished);
+                       prompts, lo, width, prev, finished, row_ids);
     AS_HIP_TRY(ctx, hipGetLastError());
     return AS_OK;
 }

@@ -16,7 +16,7 @@ namespace {
 // ------------------------------------------------------------------ lattice
 
 __global__ void lattice_kernel(const float *u, int32_t B, int32_t N, float *codes,
-                               const int32_t *prompts, int32_t *prev, uint8_t *finished)
+                               const int32_t *prompts, int32_t *prev, uint8_t *finished, int32_t *row_ids)
 {
     const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= (int64_t)B * N) return;
@@ -26,6 +26,60 @@ __global__ void lattice_kernel(const float *u, int32_t B, int32_t N, float *code
     if (codes) codes[idx] = fminf((float)c, 0x1.fffffep-1f);
     if (prev) prev[idx] = prompts[b];
     if (finished) finished[idx] = 0;
+    if (row_ids) row_ids[idx] = b;           // the first step's logits: one row per prompt
+}
+
+// ------------------------------------------------------------ shared logits rows
+
+__global__ __launch_bounds__(256) void share_clear_kernel(RowShare s, int32_t V, int32_t T)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < V) s.mark[i] = -1;
+    if (i < T) s.count[i] = 0;
+}
+
+// The first row to come with a token takes the next logits row for it: one addition to the step's counter per block
+// (65536 of them on one address would take longer than the product they save).  Which row a token gets differs
+// from run to run; what is in it does not.
+__global__ __launch_bounds__(1024) void share_claim_kernel(RowShare s, int32_t step, int32_t V, const int32_t *prev,
+                                                           const uint8_t *finished, int64_t rows)
+{
+    __shared__ int32_t wave_n[16], block_at;
+    const int64_t r = (int64_t)blockIdx.x * 1024 + threadIdx.x;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    bool mine = false;
+    int32_t v = 0;
+    if (r < rows && !(finished != nullptr && finished[r] != 0)) {
+        v = clamp_token(prev[r], V);
+        mine = atomicExch(&s.mark[v], step) != step;
+    }
+    const unsigned long long m = __ballot(mine);
+    if (lane == 0) wave_n[wave] = __builtin_popcountll(m);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int32_t n = 0;
+        for (int w = 0; w < 16; ++w) {
+            const int32_t c = wave_n[w];
+            wave_n[w] = n;
+            n += c;
+        }
+        block_at = n ? atomicAdd(&s.count[step], n) : 0;
+    }
+    __syncthreads();
+    if (mine) {
+        const int32_t at = block_at + wave_n[wave] + __builtin_popcountll(m & ((1ull << lane) - 1ull));
+        s.slot[v] = at;
+        s.token[at] = v;
+    }
+}
+
+__global__ __launch_bounds__(256) void share_map_kernel(RowShare s, int32_t V, const int32_t *prev,
+                                                        const uint8_t *finished, int64_t rows, int32_t *row_ids)
+{
+    const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (r >= rows) return;
+    // (a finished row reads no logits to speak of; it must name one that exists)
+    row_ids[r] = finished != nullptr && finished[r] != 0 ? 0 : s.slot[clamp_token(prev[r], V)];
 }
 
 // ---------------------------------------------------------------- transpose
@@ -117,7 +171,7 @@ __global__ __launch_bounds__(512, 1) void bigram_gemm_persistent(const uint16_t 
                                                                  const int32_t *__restrict__ prev, int64_t R,
                                                                  int32_t V, int32_t d, float alpha,
                                                                  OutT *__restrict__ C, int64_t ldc, int vec_store,
-                                                                 int gm)
+                                                                 int gm, const int32_t *__restrict__ rows_dev)
 {
     __shared__ __attribute__((aligned(1024))) unsigned char smem[kPersistLds];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -130,6 +184,10 @@ __global__ __launch_bounds__(512, 1) void bigram_gemm_persistent(const uint16_t 
     // column tiles at the same time, so a Ut tile is fetched into that XCD's L2 once.  With more row tiles
     // than workers, the W workers of an XCD stand gm x W/gm over row and column tiles: what they have open
     // at one time, gm A tiles and W/gm Ut tiles, has to fit that XCD's L2 or every tile refetches both.
+    if (rows_dev != nullptr) {
+        R = *rows_dev;
+        if (R <= 0) return;
+    }
     const int64_t m_blocks = (R + PM - 1) / PM;
     const int64_t n_blocks = ((int64_t)V + PN - 1) / PN;
     const int W = (int)(gridDim.x >> 3);
@@ -994,12 +1052,12 @@ __global__ __launch_bounds__(256) void estimate_kernel(const int32_t *tokens, in
 }  // namespace
 
 as_status launch_lattice(as_ctx *ctx, const float *u, int32_t B, int32_t N, float *codes_out,
-                         const int32_t *prompts, int32_t *prev_out, uint8_t *finished_out)
+                         const int32_t *prompts, int32_t *prev_out, uint8_t *finished_out, int32_t *row_ids_out)
 {
     const int64_t n = (int64_t)B * N;
     if (n == 0) return AS_OK;
     hipLaunchKernelGGL(lattice_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, ctx->stream, u, B, N,
-                       codes_out, prompts, prev_out, finished_out);
+                       codes_out, prompts, prev_out, finished_out, row_ids_out);
     AS_HIP_TRY(ctx, hipGetLastError());
     return AS_OK;
 }
@@ -1040,21 +1098,58 @@ static int persistent_gm(const as_ctx *ctx)
     return W % 8 == 0 ? 8 : W;
 }
 
+static bool mfma_applies(const as_model *m)
+{
+    return m->wdtype == AS_BF16 && m->d % BK == 0 && reinterpret_cast<uintptr_t>(m->E) % 16 == 0 &&
+           reinterpret_cast<uintptr_t>(m->Ut) % 16 == 0;
+}
+
+// Whether a decode of `rows` rows shares logits rows after its first step: with tokens spread evenly over the vocabulary
+// (the worst case) rows - V(1 - exp(-rows/V)) rows are saved, at 1 PFLOP/s, against two small launches and the
+// clearing of the tables; the line lies at twice their cost.  (65536 rows, V = 32128, d = 512: 2.03 ms of product
+// a step for 65536 rows, 0.9 for the 28000 tokens in use.)
+bool sharing_pays(const as_ctx *ctx, const as_model *m, int64_t rows, int32_t T)
+{
+    if (T < 2 || ctx->gemm_shape == 1 || ctx->num_cus < 8 || !mfma_applies(m) || m->d < 2 * PK ||
+        (int64_t)m->V * m->d * 2 >= (1LL << 32))
+        return false;
+    const double tokens = (double)m->V * (1.0 - exp(-(double)rows / (double)m->V));
+    return ((double)rows - tokens) * (double)m->V * (double)m->d * 2.0 > 20e-6 * 1e15;
+}
+
+as_status launch_share_clear(as_ctx *ctx, const RowShare &s, int32_t T)
+{
+    const int64_t n = ctx->V > T ? ctx->V : T;
+    hipLaunchKernelGGL(share_clear_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, ctx->stream, s, ctx->V, T);
+    AS_HIP_TRY(ctx, hipGetLastError());
+    return AS_OK;
+}
+
+as_status launch_share(as_ctx *ctx, const RowShare &s, int32_t step, const int32_t *prev, const uint8_t *finished,
+                       int64_t rows, int32_t *row_ids)
+{
+    hipLaunchKernelGGL(share_claim_kernel, dim3((unsigned)((rows + 1023) / 1024)), dim3(1024), 0, ctx->stream, s, step,
+                       ctx->V, prev, finished, rows);
+    AS_HIP_TRY(ctx, hipGetLastError());
+    hipLaunchKernelGGL(share_map_kernel, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, ctx->stream, s, ctx->V, prev,
+                       finished, rows, row_ids);
+    AS_HIP_TRY(ctx, hipGetLastError());
+    return AS_OK;
+}
+
 as_status launch_bigram_logits(as_ctx *ctx, const as_model *m, const int32_t *prev, int64_t rows,
-                               void *logits_out, int64_t ld)
+                               void *logits_out, int64_t ld, const int32_t *rows_dev)
 {
     if (rows == 0) return AS_OK;
     const float alpha = (float)((double)m->scale / sqrt((double)m->d));
-    const bool mfma = m->wdtype == AS_BF16 && m->d % BK == 0 &&
-                      reinterpret_cast<uintptr_t>(m->E) % 16 == 0 && reinterpret_cast<uintptr_t>(m->Ut) % 16 == 0;
-    if (mfma) {
+    if (mfma_applies(m)) {
         const size_t osz = ctx->dtype == AS_BF16 ? 2 : 4;
         const int vec_store = (reinterpret_cast<uintptr_t>(logits_out) % 16 == 0) && ((ld * osz) % 16 == 0);
         const uint16_t *Ep = (const uint16_t *)m->E, *Up = (const uint16_t *)m->Ut;
         // the persistent kernel addresses operand rows with 32-bit byte offsets and wants two K stages
         const bool persistent = ctx->gemm_shape != 1 && m->d >= 2 * PK && (int64_t)m->V * m->d * 2 < (1LL << 32) &&
                                 ctx->num_cus >= 8;
-        if (thin_pays(ctx, m, rows)) {
+        if (rows_dev == nullptr && thin_pays(ctx, m, rows)) {
             if (ctx->dtype == AS_BF16)
                 launch_thin<uint16_t, false>(ctx, m, prev, rows, (uint16_t *)logits_out, ld, alpha, vec_store);
             else
@@ -1063,10 +1158,10 @@ as_status launch_bigram_logits(as_ctx *ctx, const as_model *m, const int32_t *pr
             const dim3 grid((unsigned)(8 * (ctx->num_cus / 8))), block(512);
             if (ctx->dtype == AS_BF16)
                 launch(ctx, kKernelLogits, bigram_gemm_persistent<uint16_t>, grid, block, 0, Ep, Up, prev, rows,
-                       m->V, m->d, alpha, (uint16_t *)logits_out, ld, vec_store, persistent_gm(ctx));
+                       m->V, m->d, alpha, (uint16_t *)logits_out, ld, vec_store, persistent_gm(ctx), rows_dev);
             else
                 launch(ctx, kKernelLogits, bigram_gemm_persistent<float>, grid, block, 0, Ep, Up, prev, rows, m->V,
-                       m->d, alpha, (float *)logits_out, ld, vec_store, persistent_gm(ctx));
+                       m->d, alpha, (float *)logits_out, ld, vec_store, persistent_gm(ctx), rows_dev);
         } else {
             // grid: 8 XCD lanes x ceil(column tiles / 8) x row tiles (see the kernel's tile mapping)
             const int64_t m_blocks = (rows + BM - 1) / BM, n_blocks = ((int64_t)m->V + BN - 1) / BN;
@@ -1103,11 +1198,11 @@ bool fused_path_applies(const as_ctx *ctx, const as_model *m)
 }
 
 as_status launch_bigram_partials(as_ctx *ctx, const as_model *m, const int32_t *prev, int64_t rows, float temp,
-                                 float2 *part, int64_t ldp)
+                                 float2 *part, int64_t ldp, const int32_t *rows_dev)
 {
     if (rows == 0) return AS_OK;
     const float alpha = (float)((double)m->scale / sqrt((double)m->d) * 1.44269504088896340736 / (double)temp);
-    if (thin_pays(ctx, m, rows)) {
+    if (rows_dev == nullptr && thin_pays(ctx, m, rows)) {
         launch_thin<float, true>(ctx, m, prev, rows, reinterpret_cast<float *>(part), ldp, alpha, 0);
         AS_HIP_TRY(ctx, hipGetLastError());
         return AS_OK;
@@ -1115,7 +1210,7 @@ as_status launch_bigram_partials(as_ctx *ctx, const as_model *m, const int32_t *
     const dim3 grid((unsigned)(8 * (ctx->num_cus / 8))), block(512);
     launch(ctx, kKernelLogits, bigram_gemm_persistent<float, true>, grid, block, 0, (const uint16_t *)m->E,
            (const uint16_t *)m->Ut, prev, rows, m->V, m->d, alpha, reinterpret_cast<float *>(part), ldp, 0,
-           persistent_gm(ctx));
+           persistent_gm(ctx), rows_dev);
     AS_HIP_TRY(ctx, hipGetLastError());
     return AS_OK;
 }

@@ -598,7 +598,7 @@ as_status launch_shape(as_ctx *ctx, const StepArgs &a)
     if (lds > 60 * 1024) return fail(ctx, AS_ERR_UNSUPPORTED, "vocabulary too large for the share table");
     if (whole && ntiles == 1 && NW == 4 && ITERS == 16 && ctx->step_shape == 0 && a.k <= kTileMaxScale)
     {
-        if (stream_rows(a.rows, a.ld, sizeof(typename Elem<DT>::T)))
+        if (stream_rows(a.src_rows ? a.src_rows : a.rows, a.ld, sizeof(typename Elem<DT>::T)))
             launch(ctx, kKernelStep, step_tile_kernel<DT, HAS_THR, true>, dim3((unsigned)a.rows), dim3(256), 0, a);
         else
             launch(ctx, kKernelStep, step_tile_kernel<DT, HAS_THR, false>, dim3((unsigned)a.rows), dim3(256), 0, a);

@@ -1927,7 +1927,7 @@ bool launch_topk_step(as_ctx *ctx, const StepArgs &args, int32_t top_k, float to
 {
     const size_t esz = ctx->dtype == AS_BF16 ? 2 : 4;
     const StepArgs &a = args;
-    const bool nt = stream_rows(a.rows, a.ld, esz);
+    const bool nt = stream_rows(a.src_rows ? a.src_rows : a.rows, a.ld, esz);
     const bool has_k = top_k > 0 && top_k < ctx->V, has_p = top_p > 0.f && top_p < 1.f;
     const bool nucleus_only = !has_k && has_p && ctx->dtype == AS_BF16;
     const bool one_tile = ctx->dtype == AS_BF16 && ctx->V % 8 == 0 && ctx->V <= 32768 &&

@@ -489,6 +489,13 @@ static as_status decode_impl(as_ctx *ctx, const as_model *model, const int32_t *
     if (eos_id >= ctx->V) return fail(ctx, AS_ERR_INVALID_ARG, "eos_id outside the vocabulary");
     if (isnan(top_p)) return fail(ctx, AS_ERR_INVALID_ARG, "top_p is NaN");
 
+    const bool trunc = truncation_on(ctx->V, top_k, top_p);
+    if (!trunc && T > 0 && small_decode_applies(ctx, model, R, temp)) {
+        SmallArgs a{};
+        a.temp = temp; a.prompts = prompts; a.u = uniforms ? nullptr : u; a.uniforms = uniforms;
+        a.rows = R; a.N = N; a.T = T; a.eos_id = eos_id; a.tokens = tokens_out; a.codes_out = codes_out;
+        return launch_small_decode(ctx, model, a);
+    }
     const size_t esz = ctx->dtype == AS_BF16 ? 2 : 4;
     const int64_t ldw = ((int64_t)ctx->V + 7) / 8 * 8;        // rows start 16-byte aligned
     as_status st = grow(ctx, ctx->logits, (size_t)R * ldw * esz);
@@ -502,7 +509,6 @@ static as_status decode_impl(as_ctx *ctx, const as_model *model, const int32_t *
 
     st = launch_lattice(ctx, u, B, N, uniforms ? nullptr : codes, prompts, prev, fin, ctx->rid);
     if (st != AS_OK) return st;
-    const bool trunc = truncation_on(ctx->V, top_k, top_p);
     for (int32_t t = 0; t < T; ++t) {
         StepRows sr;
         st = step_rows(ctx, state, prompts, B, N, t, eos_id, sr);

@@ -150,6 +150,19 @@ struct IntervalArgs {
     int32_t *prev_out;           // encode state: next step's conditioning token, or null
 };
 
+struct SmallArgs {               // a whole decode of a model that fits LDS
+    const void *E, *Ut;          // [V, d] each
+    int32_t V, d;
+    float alpha, k, temp;
+    const int32_t *prompts;
+    const float *u;              // shifts of the lattice, or null ...
+    const float *uniforms;       // ... and then the codes [T, rows]
+    int64_t rows;
+    int32_t N, T, eos_id;
+    int32_t *tokens;             // [rows, T]
+    float *codes_out;            // [rows] or null
+};
+
 struct FusedArgs {
     const float2 *part;          // [rows, ldp]: (sum, reference) per group of 32 logits
     const int32_t *row_ids;      // row r's masses are row row_ids[r] of part, or null
@@ -203,6 +216,9 @@ struct RowShare {
     int32_t *token = nullptr;    // [R] token of each logits row
     int32_t *count = nullptr;    // [T] logits rows of each step
 };
+bool mfma_applies(const as_model *m);
+bool small_decode_applies(const as_ctx *ctx, const as_model *m, int64_t rows, float temp);
+as_status launch_small_decode(as_ctx *ctx, const as_model *m, SmallArgs s);
 bool sharing_pays(const as_ctx *ctx, const as_model *m, int64_t rows, int32_t T);
 as_status launch_share_clear(as_ctx *ctx, const RowShare &s, int32_t T);
 as_status launch_share(as_ctx *ctx, const RowShare &s, int32_t step, const int32_t *prev, const uint8_t *finished,

@@ -1098,7 +1098,8 @@ static int persistent_gm(const as_ctx *ctx)
     return W % 8 == 0 ? 8 : W;
 }
 
-static bool mfma_applies(const as_model *m)
+// Whether the MFMA kernels take the model (otherwise the vector kernel does).
+bool mfma_applies(const as_model *m)
 {
     return m->wdtype == AS_BF16 && m->d % BK == 0 && reinterpret_cast<uintptr_t>(m->E) % 16 == 0 &&
            reinterpret_cast<uintptr_t>(m->Ut) % 16 == 0;

@@ -423,7 +423,7 @@ struct DecodeState {
 static as_status decode_state(as_ctx *ctx, const as_model *model, int64_t R, int32_t T, DecodeState &s)
 {
     s.share = sharing_pays(ctx, model, R, T);
-    const size_t words = (size_t)R * 2 + (s.share ? (size_t)R + 2 * (size_t)ctx->V + (size_t)T : 0);
+    const size_t words = (size_t)R * 2 + (s.share ? 2 * (size_t)R + 3 * (size_t)ctx->V + (size_t)T : 0);
     as_status st = grow(ctx, ctx->state, words * 4 + (size_t)R);
     if (st != AS_OK) return st;
     int32_t *w = static_cast<int32_t *>(ctx->state.ptr);
@@ -436,7 +436,9 @@ static as_status decode_state(as_ctx *ctx, const as_model *model, int64_t R, int
         s.tables.mark = w + R;
         s.tables.slot = s.tables.mark + ctx->V;
         s.tables.count = s.tables.slot + ctx->V;
-        w = s.tables.count + T;
+        s.tables.fill = s.tables.count + T;
+        s.tables.order = s.tables.fill + ctx->V;
+        w = s.tables.order + R;
         st = launch_share_clear(ctx, s.tables, T);
     }
     s.fin = reinterpret_cast<uint8_t *>(w);
@@ -452,22 +454,23 @@ struct StepRows {
     const int32_t *rows_dev;
     const int32_t *row_ids;
     int64_t src_rows;
+    const int32_t *order;        // the rows sorted by logits row, where those are read from memory rather than caches
 };
 
 static as_status step_rows(as_ctx *ctx, const DecodeState &s, const int32_t *prompts, int32_t B, int32_t N, int32_t t,
-                           int32_t eos_id, StepRows &o)
+                           bool sorted, StepRows &o)
 {
     const int64_t R = (int64_t)B * N;
     if (t == 0 && N > 1) {
-        o = StepRows{prompts, B, nullptr, ctx->rid, B};
+        o = StepRows{prompts, B, nullptr, ctx->rid, B, nullptr};
         return AS_OK;
     }
     if (t == 0 || !s.share) {
-        o = StepRows{s.prev, R, nullptr, nullptr, 0};
+        o = StepRows{s.prev, R, nullptr, nullptr, 0, nullptr};
         return AS_OK;
     }
-    o = StepRows{s.tables.token, R, s.tables.count + t, ctx->rid, 0};
-    return launch_share(ctx, s.tables, t, s.prev, eos_id >= 0 ? s.fin : nullptr, R, ctx->rid);
+    o = StepRows{s.tables.token, R, s.tables.count + t, ctx->rid, 0, sorted ? s.tables.order : nullptr};
+    return launch_share(ctx, s.tables, t, s.prev, R, ctx->rid, sorted);
 }
 
 // as_decode and as_decode_ancestral: with `uniforms` the code of row r at step t is uniforms[t*R + r] and
@@ -511,7 +514,7 @@ static as_status decode_impl(as_ctx *ctx, const as_model *model, const int32_t *
     if (st != AS_OK) return st;
     for (int32_t t = 0; t < T; ++t) {
         StepRows sr;
-        st = step_rows(ctx, state, prompts, B, N, t, eos_id, sr);
+        st = step_rows(ctx, state, prompts, B, N, t, !trunc && stream_rows(R, ldw, esz), sr);
         if (st != AS_OK) return st;
         st = launch_bigram_logits(ctx, model, sr.prev, sr.rows, ctx->logits.ptr, ldw, sr.rows_dev);
         if (st != AS_OK) return st;
@@ -522,6 +525,7 @@ static as_status decode_impl(as_ctx *ctx, const as_model *model, const int32_t *
         a.finished_in = eos_id >= 0 ? fin : nullptr; a.eos_id = eos_id;
         a.finished_out = eos_id >= 0 ? fin : nullptr;
         a.prob_out = nullptr; a.flo_out = nullptr; a.row_ids = sr.row_ids; a.src_rows = sr.src_rows; a.prev_out = prev;
+        a.order = sr.order;
         if (trunc) {
             if (launch_topk_step(ctx, a, top_k, top_p, &st)) {
                 if (st != AS_OK) return st;
@@ -644,7 +648,7 @@ as_status as_decode_fused(as_ctx *ctx, const as_model *model, const int32_t *pro
     if (st != AS_OK) return st;
     for (int32_t t = 0; t < T; ++t) {
         StepRows sr;
-        st = step_rows(ctx, state, prompts, B, N, t, eos_id, sr);
+        st = step_rows(ctx, state, prompts, B, N, t, false, sr);
         if (st != AS_OK) return st;
         st = launch_bigram_partials(ctx, model, sr.prev, sr.rows, temp, part, ldp, sr.rows_dev);
         if (st != AS_OK) return st;
@@ -742,7 +746,7 @@ as_status as_encode(as_ctx *ctx, const as_model *model, const int32_t *prompts, 
     const bool trunc = truncation_on(ctx->V, top_k, top_p);
     for (int32_t t = 0; t < T; ++t) {
         StepRows sr;
-        st = step_rows(ctx, state, prompts, B, N, t, eos_id, sr);
+        st = step_rows(ctx, state, prompts, B, N, t, false, sr);
         if (st != AS_OK) return st;
         st = launch_bigram_logits(ctx, model, sr.prev, sr.rows, ctx->logits.ptr, ldw, sr.rows_dev);
         if (st != AS_OK) return st;

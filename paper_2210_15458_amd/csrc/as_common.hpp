@@ -128,6 +128,7 @@ struct StepArgs {
     float *flo_out;
     const int32_t *row_ids;
     int32_t *prev_out;           // decode state: next step's conditioning token, or null
+    const int32_t *order;        // a permutation of the rows that puts those with one logits row together, or null
 };
 
 struct IntervalArgs {
@@ -215,14 +216,16 @@ struct RowShare {
     int32_t *slot = nullptr;     // [V] its logits row in that step
     int32_t *token = nullptr;    // [R] token of each logits row
     int32_t *count = nullptr;    // [T] logits rows of each step
+    int32_t *fill = nullptr;     // [V] rows of each logits row, then where the next of them goes in `order`
+    int32_t *order = nullptr;    // [R] the rows sorted by logits row
 };
 bool mfma_applies(const as_model *m);
 bool small_decode_applies(const as_ctx *ctx, const as_model *m, int64_t rows, float temp);
 as_status launch_small_decode(as_ctx *ctx, const as_model *m, SmallArgs s);
 bool sharing_pays(const as_ctx *ctx, const as_model *m, int64_t rows, int32_t T);
 as_status launch_share_clear(as_ctx *ctx, const RowShare &s, int32_t T);
-as_status launch_share(as_ctx *ctx, const RowShare &s, int32_t step, const int32_t *prev, const uint8_t *finished,
-                       int64_t rows, int32_t *row_ids);
+as_status launch_share(as_ctx *ctx, const RowShare &s, int32_t step, const int32_t *prev, int64_t rows,
+                       int32_t *row_ids, bool sorted);
 
 // ------------------------------------------------------------ wave primitives
 // Data-parallel-primitive (DPP) cross-lane moves.  bound_ctrl is off, so a lane

@@ -42,16 +42,18 @@ __global__ __launch_bounds__(256) void share_clear_kernel(RowShare s, int32_t V,
 // (65536 of them on one address would take longer than the product they save).  Which row a token gets differs
 // from run to run; what is in it does not.
 __global__ __launch_bounds__(1024) void share_claim_kernel(RowShare s, int32_t step, int32_t V, const int32_t *prev,
-                                                           const uint8_t *finished, int64_t rows)
+                                                           int64_t rows)
 {
     __shared__ int32_t wave_n[16], block_at;
     const int64_t r = (int64_t)blockIdx.x * 1024 + threadIdx.x;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     bool mine = false;
     int32_t v = 0;
-    if (r < rows && !(finished != nullptr && finished[r] != 0)) {
+    if (r < rows) {
         v = clamp_token(prev[r], V);
-        mine = atomicExch(&s.mark[v], step) != step;
+        // (looked at first: the rows that have ended all come with one token)
+        if (__hip_atomic_load(&s.mark[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != step)
+            mine = atomicExch(&s.mark[v], step) != step;
     }
     const unsigned long long m = __ballot(mine);
     if (lane == 0) wave_n[wave] = __builtin_popcountll(m);
@@ -70,16 +72,50 @@ __global__ __launch_bounds__(1024) void share_claim_kernel(RowShare s, int32_t s
         const int32_t at = block_at + wave_n[wave] + __builtin_popcountll(m & ((1ull << lane) - 1ull));
         s.slot[v] = at;
         s.token[at] = v;
+        s.fill[at] = 0;
     }
 }
 
-__global__ __launch_bounds__(256) void share_map_kernel(RowShare s, int32_t V, const int32_t *prev,
-                                                        const uint8_t *finished, int64_t rows, int32_t *row_ids)
+template <bool SORTED>
+__global__ __launch_bounds__(256) void share_map_kernel(RowShare s, int32_t V, const int32_t *prev, int64_t rows,
+                                                        int32_t *row_ids)
 {
     const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (r >= rows) return;
-    // (a finished row reads no logits to speak of; it must name one that exists)
-    row_ids[r] = finished != nullptr && finished[r] != 0 ? 0 : s.slot[clamp_token(prev[r], V)];
+    const int32_t at = s.slot[clamp_token(prev[r], V)];
+    row_ids[r] = at;
+    if constexpr (SORTED) atomicAdd(&s.fill[at], 1);
+}
+
+// counts per logits row to where its rows start; one block, a run of rows per thread
+__global__ __launch_bounds__(1024) void share_scan_kernel(RowShare s, int32_t step)
+{
+    __shared__ int32_t wave_tot[16];
+    const int32_t n = s.count[step], per = (n + 1023) / 1024;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int32_t lo = (int32_t)threadIdx.x * per, hi = lo + per < n ? lo + per : n;
+    int32_t mine = 0;
+    for (int32_t i = lo; i < hi; ++i) mine += s.fill[i];
+    int32_t incl = mine;
+    for (int d = 1; d < 64; d <<= 1) {
+        const int32_t y = __shfl_up(incl, d, 64);
+        if (lane >= d) incl += y;
+    }
+    if (lane == 63) wave_tot[wave] = incl;
+    __syncthreads();
+    int32_t at = incl - mine;
+    for (int w = 0; w < wave; ++w) at += wave_tot[w];
+    for (int32_t i = lo; i < hi; ++i) {
+        const int32_t c = s.fill[i];
+        s.fill[i] = at;
+        at += c;
+    }
+}
+
+__global__ __launch_bounds__(256) void share_order_kernel(RowShare s, int64_t rows, const int32_t *row_ids)
+{
+    const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (r < rows) s.order[atomicAdd(&s.fill[row_ids[r]], 1)] = (int32_t)r;
 }
 
 // ---------------------------------------------------------------- transpose
@@ -1126,14 +1162,22 @@ as_status launch_share_clear(as_ctx *ctx, const RowShare &s, int32_t T)
     return AS_OK;
 }
 
-as_status launch_share(as_ctx *ctx, const RowShare &s, int32_t step, const int32_t *prev, const uint8_t *finished,
-                       int64_t rows, int32_t *row_ids)
+as_status launch_share(as_ctx *ctx, const RowShare &s, int32_t step, const int32_t *prev, int64_t rows,
+                       int32_t *row_ids, bool sorted)
 {
+    const dim3 blocks((unsigned)((rows + 255) / 256));
     hipLaunchKernelGGL(share_claim_kernel, dim3((unsigned)((rows + 1023) / 1024)), dim3(1024), 0, ctx->stream, s, step,
-                       ctx->V, prev, finished, rows);
+                       ctx->V, prev, rows);
     AS_HIP_TRY(ctx, hipGetLastError());
-    hipLaunchKernelGGL(share_map_kernel, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, ctx->stream, s, ctx->V, prev,
-                       finished, rows, row_ids);
+    if (!sorted) {
+        hipLaunchKernelGGL(share_map_kernel<false>, blocks, dim3(256), 0, ctx->stream, s, ctx->V, prev, rows, row_ids);
+    } else {
+        hipLaunchKernelGGL(share_map_kernel<true>, blocks, dim3(256), 0, ctx->stream, s, ctx->V, prev, rows, row_ids);
+        AS_HIP_TRY(ctx, hipGetLastError());
+        hipLaunchKernelGGL(share_scan_kernel, dim3(1), dim3(1024), 0, ctx->stream, s, step);
+        AS_HIP_TRY(ctx, hipGetLastError());
+        hipLaunchKernelGGL(share_order_kernel, blocks, dim3(256), 0, ctx->stream, s, rows, row_ids);
+    }
     AS_HIP_TRY(ctx, hipGetLastError());
     return AS_OK;
 }

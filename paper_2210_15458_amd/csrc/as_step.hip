@@ -103,7 +103,8 @@ __global__ __launch_bounds__(NW * 64, OCC) void step_kernel(StepArgs a, int ntil
     float *ent_sum = smem + kCsFloats;     // [nent]  sum of a share, relative to its reference
     float *ent_ref = ent_sum + nent;       // [nent]  integer reference of the share
 
-    const int64_t r = blockIdx.x;
+    int64_t r;
+    if (!block_row(a, r)) return;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
@@ -471,7 +472,8 @@ __global__ __launch_bounds__(256, 4) void step_tile_kernel(StepArgs a)
     __shared__ TileSums ts;
     __shared__ GenericScratch gen;
 
-    const int64_t r = blockIdx.x;
+    int64_t r;
+    if (!block_row(a, r)) return;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
@@ -599,15 +601,15 @@ as_status launch_shape(as_ctx *ctx, const StepArgs &a)
     if (whole && ntiles == 1 && NW == 4 && ITERS == 16 && ctx->step_shape == 0 && a.k <= kTileMaxScale)
     {
         if (stream_rows(a.src_rows ? a.src_rows : a.rows, a.ld, sizeof(typename Elem<DT>::T)))
-            launch(ctx, kKernelStep, step_tile_kernel<DT, HAS_THR, true>, dim3((unsigned)a.rows), dim3(256), 0, a);
+            launch(ctx, kKernelStep, step_tile_kernel<DT, HAS_THR, true>, dim3(step_blocks(a)), dim3(256), 0, a);
         else
-            launch(ctx, kKernelStep, step_tile_kernel<DT, HAS_THR, false>, dim3((unsigned)a.rows), dim3(256), 0, a);
+            launch(ctx, kKernelStep, step_tile_kernel<DT, HAS_THR, false>, dim3(step_blocks(a)), dim3(256), 0, a);
     }
     else if (!whole)
-        launch(ctx, kKernelStep, step_kernel<DT, NW, ITERS, OCC, HAS_THR, true>, dim3((unsigned)a.rows), dim3(NW * 64),
+        launch(ctx, kKernelStep, step_kernel<DT, NW, ITERS, OCC, HAS_THR, true>, dim3(step_blocks(a)), dim3(NW * 64),
                lds, a, ntiles);
     else
-        launch(ctx, kKernelStep, step_kernel<DT, NW, ITERS, OCC, HAS_THR, false>, dim3((unsigned)a.rows), dim3(NW * 64),
+        launch(ctx, kKernelStep, step_kernel<DT, NW, ITERS, OCC, HAS_THR, false>, dim3(step_blocks(a)), dim3(NW * 64),
                lds, a, ntiles);
     AS_HIP_TRY(ctx, hipGetLastError());
     return AS_OK;

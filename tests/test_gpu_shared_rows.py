@@ -11,9 +11,10 @@ from paper_2210_15458_amd import synth
 pytestmark = pytest.mark.gpu
 
 # (V, d, prompts, codes, steps, logits): many rows per token in every step; the same with a ragged vocabulary and fp32
-# logits; shared in the first step only, with few prompts (the logits kernel for few rows) and with one code each
+# logits; shared in the first step only, with few prompts (the logits kernel for few rows) and with one code each; rows
+# beyond the caches, which are also sorted by logits row
 CASES = [(2000, 1024, 4, 2048, 4, "bf16"), (1501, 1024, 1, 9000, 3, "f32"), (5000, 128, 3, 50, 3, "bf16"),
-         (5000, 128, 70, 1, 3, "bf16")]
+         (5000, 128, 70, 1, 3, "bf16"), (1501, 1024, 2, 12000, 3, "f32")]
 EOS, TEMP = 1, 1.1
 
 

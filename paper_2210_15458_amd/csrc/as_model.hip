@@ -87,28 +87,40 @@ __global__ __launch_bounds__(256) void share_map_kernel(RowShare s, int32_t V, c
     if constexpr (SORTED) atomicAdd(&s.fill[at], 1);
 }
 
-// counts per logits row to where its rows start; one block, a run of rows per thread
+// Counts per logits row to where its rows start.  One block; a wave takes one run of the table, 64 neighbouring words
+// at a time and eight of those requested together (a run per thread, each word a line of its own: 40 us at 28000).
 __global__ __launch_bounds__(1024) void share_scan_kernel(RowShare s, int32_t step)
 {
+    constexpr int kAhead = 8;
     __shared__ int32_t wave_tot[16];
-    const int32_t n = s.count[step], per = (n + 1023) / 1024;
+    const int32_t n = s.count[step], per = (n + 1023) / 1024 * 64;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int32_t lo = (int32_t)threadIdx.x * per, hi = lo + per < n ? lo + per : n;
+    const int32_t lo = wave * per < n ? wave * per : n, hi = lo + per < n ? lo + per : n;
     int32_t mine = 0;
-    for (int32_t i = lo; i < hi; ++i) mine += s.fill[i];
-    int32_t incl = mine;
-    for (int d = 1; d < 64; d <<= 1) {
-        const int32_t y = __shfl_up(incl, d, 64);
-        if (lane >= d) incl += y;
+    for (int32_t i = lo; i < hi; i += 64 * kAhead) {
+#pragma unroll
+        for (int j = 0; j < kAhead; ++j) mine += i + j * 64 + lane < hi ? s.fill[i + j * 64 + lane] : 0;
     }
-    if (lane == 63) wave_tot[wave] = incl;
+    for (int d = 32; d >= 1; d >>= 1) mine += __shfl_xor(mine, d, 64);
+    if (lane == 0) wave_tot[wave] = mine;
     __syncthreads();
-    int32_t at = incl - mine;
+    int32_t at = 0;
     for (int w = 0; w < wave; ++w) at += wave_tot[w];
-    for (int32_t i = lo; i < hi; ++i) {
-        const int32_t c = s.fill[i];
-        s.fill[i] = at;
-        at += c;
+    for (int32_t i = lo; i < hi; i += 64 * kAhead) {
+        int32_t c[kAhead];
+#pragma unroll
+        for (int j = 0; j < kAhead; ++j) c[j] = i + j * 64 + lane < hi ? s.fill[i + j * 64 + lane] : 0;
+#pragma unroll
+        for (int j = 0; j < kAhead; ++j) {
+            int32_t incl = c[j];
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const int32_t y = __shfl_up(incl, d, 64);
+                if (lane >= d) incl += y;
+            }
+            if (i + j * 64 + lane < hi) s.fill[i + j * 64 + lane] = at + incl - c[j];
+            at += __shfl(incl, 63, 64);
+        }
     }
 }
 

@@ -500,7 +500,8 @@ __global__ __launch_bounds__(NT, 4) void wide_step_kernel(StepArgs a, int32_t to
 
     // The exact end of a selection: the list (n entries) holds the logits of the closing bin,
     // `base` is the weight above them; the key of the group of equal logits at which the running weight reaches
-    // `need`.  all(put) puts every logit of the bin, for a list that did not take them all.
+    // `need`, or 0 (no logit's key) if it does not get there.  all(put) puts every logit of the bin, for a list that did
+    // not take them all.
     auto close = [&](uint32_t n, u64 base, double need, auto all)
                      __attribute__((always_inline)) -> uint32_t {
         if (n <= (uint32_t)NT) {
@@ -551,7 +552,7 @@ __global__ __launch_bounds__(NT, 4) void wide_step_kernel(StepArgs a, int32_t to
             }
             reach(base, need, false, No{});
             const int32_t at = sh.pick;
-            if (at < 0) break;                               // (the weights of a NaN row)
+            if (at < 0) return 0u;
             base = sh.before;
             const uint32_t top = khi - ((uint32_t)at << s);
             const uint32_t low = (uint32_t)(1u << s) - 1u;
@@ -624,14 +625,15 @@ __global__ __launch_bounds__(NT, 4) void wide_step_kernel(StepArgs a, int32_t to
         if (pick < 0) {
             if constexpr (!COUNT) return false;
             // fewer than k logits within the bins: by key over the whole row
-            thr = from_order_key(close(0xffffffffu, 0ull, need, [&](auto put) __attribute__((always_inline)) {
+            const uint32_t key = close(0xffffffffu, 0ull, need, [&](auto put) __attribute__((always_inline)) {
                 for (int32_t i = tid; i <= nwhole; i += NT) {
                     float x[EPV];
                     values(piece_at(i), x);
                     for (int e = 0; e < EPV; ++e) put(order_key(x[e]), 1ull);
                 }
-            }));
-            return true;
+            });
+            thr = from_order_key(key);
+            return key != 0u;
         }
         u64 base = sh.before;
         const float tpick = kTwo23 + (float)pick;
@@ -663,11 +665,12 @@ __global__ __launch_bounds__(NT, 4) void wide_step_kernel(StepArgs a, int32_t to
         });
         __syncthreads();
         const uint32_t n = sh.n;
-        thr = from_order_key(close(n, base, need, [&](auto put) __attribute__((always_inline)) {
+        const uint32_t key = close(n, base, need, [&](auto put) __attribute__((always_inline)) {
             // more than the list takes: from memory (the row's registers in a loop do not fit)
             for (int32_t i = tid; i <= nwhole; i += NT) members(piece_at(i), put);
-        }));
-        return true;
+        });
+        thr = from_order_key(key);
+        return key != 0u;                                    // (0: the weights of a NaN row)
     };
 
     float thr = -__builtin_inff();

@@ -1,0 +1,49 @@
+"""The nucleus in the kernel for rows of any shape, on rows built against what its quick way takes for granted."""
+import numpy as np
+import pytest
+
+from paper_2210_15458_amd import synth
+
+pytestmark = pytest.mark.gpu
+ANY = {"thr_path": 3}
+LOG2E = 1.4426950408889634
+
+
+def _against_oracle(x, dtype, codes, top_p, label):
+    from gpu_util import compare_step, oracle_step, run_gpu_step
+    V = x.shape[1]
+    stored = synth.f32_to_bf16_bits(x) if dtype == "bf16" else x
+    gpu = run_gpu_step(stored, codes, V, top_p=top_p, tuning=ANY)
+    ref = oracle_step(stored, codes, V, top_p=top_p)
+    print(label, compare_step(gpu, ref, V, label, trunc=True, codes=codes), flush=True)
+
+
+def _past_a_full_window(V, per_octave, closing):
+    """A row whose closing bin, by the tallies, ends just before its nucleus does, and the nucleus's share p.
+
+    A tally takes a weight for linear within its bin, which is exact at the bin's centre and too little elsewhere.  Here
+    everything down to the closing bin sits at centres and what lies below at the bins' ends: by the tallies the
+    total is too small by up to (ln2 / per_octave / 2)^2 / 2 of it, and the goal with it.  The bins on either side of
+    the closing one hold too many logits to be looked at along with it.
+    """
+    y = np.full(V, -4.0 - 6.499 / per_octave)
+    at = 0
+    for n, v in ((100, -3.0), (40, -4.0 + 1.0 / per_octave), (closing, -4.0), (40, -4.0 - 1.0 / per_octave)):
+        y[at:at + n] = v
+        at += n
+    w = np.exp2(y)
+    upto, total = w[:140 + closing].sum(), w.sum()
+    low = (np.log(2.0) / per_octave * 0.499) ** 2 / 2 * w[at:].sum()
+    p = np.float32(upto / (total - low / 2))
+    assert upto / total < p < upto / (total - low)
+    # (the first logits of the row among them: the reference is the row's own)
+    return (y / LOG2E).astype(np.float32), float(p)
+
+
+@pytest.mark.parametrize("V,per_octave,closing", [(4096, 32, 200), (4096, 32, 300), (4096, 32, 900),
+                                                  (12288, 64, 800), (12288, 64, 1500), (12288, 64, 2000)])
+def test_goal_just_past_the_closing_bin(V, per_octave, closing):
+    x, p = _past_a_full_window(V, per_octave, closing)
+    codes = np.array([0.1, 0.5, 0.9, 0.999, 1 - 2.0 ** -24], np.float32)
+    rows = np.stack([np.roll(x, s) for s in (0, 17, 64, 1, 333)])
+    _against_oracle(rows, "f32", codes, p, f"V={V} closing={closing} p={p}")

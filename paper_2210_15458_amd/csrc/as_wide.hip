@@ -737,6 +737,10 @@ __global__ __launch_bounds__(NT, 4) void wide_step_kernel(StepArgs a, int32_t to
                 for (int32_t i = tid; i < nwhole; i += NT) one(piece_at(i));
             });
         }
+        // The tallies are against the first pieces' reference; from here on it is the row's own, so that no weight is
+        // above 1: sums of fixed-point masses stay far below 2^64.
+        const float lower = exact - ref;
+        ref = exact;
         const float nr = -ref;
         {
             // running mass and running count over the bins
@@ -796,8 +800,9 @@ __global__ __launch_bounds__(NT, 4) void wide_step_kernel(StepArgs a, int32_t to
                 whi = whi > Sh::kBins - 1 ? Sh::kBins - 1 : whi;
             }
             // (as exponent arguments; the bins' own rounding need not be met, every logit only has to fall on one side)
-            const float yhi = wlo == 0 ? __builtin_inff() : ((float)(kTopOctaves * Sh::kPerOctave - wlo) + 0.5f) / kScale;
-            const float ylo = ((float)(kTopOctaves * Sh::kPerOctave - whi) - 0.5f) / kScale;
+            const float yhi = wlo == 0 ? __builtin_inff()
+                                       : ((float)(kTopOctaves * Sh::kPerOctave - wlo) + 0.5f) / kScale - lower;
+            const float ylo = ((float)(kTopOctaves * Sh::kPerOctave - whi) - 0.5f) / kScale - lower;
             double all = 0.0, over = 0.0;
             float all4 = 0.f;
             // the lane's weight above the window; its logits inside the window join the list

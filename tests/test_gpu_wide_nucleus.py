@@ -1,4 +1,5 @@
-"""The nucleus in the kernel for rows of any shape, on rows built against what its quick way takes for granted."""
+"""The nucleus in the kernel for rows of any shape, on rows built against what its quick way takes for granted: where the
+approximate tallies say the nucleus closes, how far the row's largest logit lies above its first ones."""
 import numpy as np
 import pytest
 
@@ -47,3 +48,18 @@ def test_goal_just_past_the_closing_bin(V, per_octave, closing):
     codes = np.array([0.1, 0.5, 0.9, 0.999, 1 - 2.0 ** -24], np.float32)
     rows = np.stack([np.roll(x, s) for s in (0, 17, 64, 1, 333)])
     _against_oracle(rows, "f32", codes, p, f"V={V} closing={closing} p={p}")
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("gap", [8.5, 9.1, 9.8, 10.4, 11.0])
+def test_largest_logits_past_the_first_ones(gap, dtype):
+    # 2^12 to 2^16 times the weight of the row's first logits, from a few of these to more than any table takes, in one run
+    V = 50257
+    counts = (1, 300, 512, 1000, 1500, 2000, 5000)
+    x = np.zeros((len(counts), V), np.float32)
+    for r, n in enumerate(counts):
+        x[r, 10240:10240 + n] = gap
+    x[:, 20000:20003] = gap - 1.0
+    codes = np.array([0.5, 0.9, 0.3, 0.95, 0.05, 0.7, 0.999], np.float32)
+    for top_p in (0.3, 0.9):
+        _against_oracle(x, dtype, codes, top_p, f"gap={gap} {dtype} p={top_p}")

@@ -50,11 +50,15 @@ __device__ __forceinline__ float from_order_key(uint32_t k)
     return __builtin_bit_cast(float, (k & 0x80000000u) ? (k ^ 0x80000000u) : ~k);
 }
 
-// 40 fractional bits of a weight e < 2^23 (24 significant bits: exact for every weight above 2^-17); a larger
-// one, or NaN, counts as 2^23 (the caller takes another reference then)
-__device__ __forceinline__ u64 fixed_mass(float e)
+// The mass by which a nucleus is closed: 31 fractional bits of a weight e <= 1 against the row's own reference, what the
+// other threshold kernels have (as_threshold.hip), so that the kept set does not depend on the kernel.  Sums of
+// them stay below 2^53 for any row.
+__device__ __forceinline__ uint32_t mass_of(float e) { return (uint32_t)fmaf(e, 2147483648.f, 0.5f); }
+// ... and the one by which a listed logit joins its chunk's weight: 40 fractional bits (24 significant bits: exact for every
+// weight above 2^-17)
+__device__ __forceinline__ u64 fixed_weight(float e)
 {
-    const float a = fminf(e, 8388608.f) * 256.f;
+    const float a = e * 256.f;
     const uint32_t hi = (uint32_t)a;
     const uint32_t lo = (uint32_t)((a - (float)hi) * 4294967296.f);
     return ((u64)hi << 32) | lo;
@@ -77,8 +81,8 @@ template <int NT, bool MULTI> struct WideShared {
     u64 extra[kExtra];                                       // ... and what the closing bin adds to it, fixed point
     __attribute__((aligned(16))) uint32_t key[kList + 4];    // a list: keys (selection) or values (candidates) ...
     union {
-        __attribute__((aligned(16))) u64 q[kList];                                        // ... with their integer weights
-        uint32_t idx[2 * kList];                             // ... or vocabulary indices
+        uint32_t q[kList];                                   // ... with their integer weights
+        __attribute__((aligned(16))) uint32_t idx[kList];    // ... or vocabulary indices
     };
     uint16_t at[kList];                                      // the chunk of a list entry
     uint32_t sorted[NT];                                     // a list in another order
@@ -363,9 +367,9 @@ __global__ __launch_bounds__(NT, 4) void wide_step_kernel(StepArgs a, int32_t to
                 float w = kept ? fast_exp2(fmaf(x, k, -ref)) : 0.f;
                 double before;
                 if (top_p > 0.f && top_p < 1.f) {
-                    // the value at which the running weight, from the highest down, reaches top_p of the survivors'
+                    // the value at which the running mass, from the highest down, reaches top_p of the survivors'
                     if (have) {
-                        sh.cw[0][place] = (double)w;
+                        sh.cw[0][place] = (double)mass_of(w);
                         sh.sorted[place] = __builtin_bit_cast(uint32_t, x);
                     }
                     if (tid == 0) sh.run = -__builtin_inf();
@@ -495,9 +499,6 @@ __global__ __launch_bounds__(NT, 4) void wide_step_kernel(StepArgs a, int32_t to
         }
         __syncthreads();
     };
-    // largest factor of two above the reference at which 2^ceil(log2 V) masses still fit the sums
-    const float room = (float)min(kTopOctaves, 23 - (32 - __builtin_clz((uint32_t)V)));
-
     // The exact end of a selection: the list (n entries) holds the logits of the closing bin,
     // `base` is the weight above them; the key of the group of equal logits at which the running weight reaches
     // `need`, or 0 (no logit's key) if it does not get there.  all(put) puts every logit of the bin, for a list that did
@@ -531,8 +532,8 @@ __global__ __launch_bounds__(NT, 4) void wide_step_kernel(StepArgs a, int32_t to
             __syncthreads();
             double first;
             wide_total<NT>(sh.wave_d, first);
-            const double goal = need - (double)base, upto = first + incl;
-            if ((uint32_t)tid < n && !(upto - v >= goal) && upto >= goal) sh.sel = skey[tid];
+            const double upto = (double)base + first + incl;
+            if ((uint32_t)tid < n && !(upto - v >= need) && upto >= need) sh.sel = skey[tid];
             __syncthreads();
             return sh.sel;
         }
@@ -576,13 +577,13 @@ __global__ __launch_bounds__(NT, 4) void wide_step_kernel(StepArgs a, int32_t to
     };
     // One selection: the key of the group of equal logits at which the running weight, from the largest logit
     // down, reaches the goal.  COUNT: weights of 1 against top_k; otherwise masses of the logits >= floor_x
-    // against top_p of their total.  False if no logit has weight.
+    // against top_p of their total (the reference is the row's own then).  False if no logit has weight.
     auto select = [&](auto count_c, float floor_x, float &thr) __attribute__((always_inline)) -> bool {
         constexpr bool COUNT = decltype(count_c)::value;
         float nr = -ref;
         auto weight = [&](float x) __attribute__((always_inline)) -> u64 {
             if constexpr (COUNT) return 1ull;
-            else return x >= floor_x ? fixed_mass(fast_exp2(fmaf(x, k, nr))) : 0ull;
+            else return x >= floor_x ? (u64)mass_of(fast_exp2(fmaf(x, k, nr))) : 0ull;
         };
         auto fill = [&]() __attribute__((always_inline)) {
             float m = -__builtin_inff();
@@ -611,13 +612,15 @@ __global__ __launch_bounds__(NT, 4) void wide_step_kernel(StepArgs a, int32_t to
         };
         clear_bins();
         fill();
-        const float exact = fmaxf(ceilf(mx * k), kRefFloor);
-        if (!(exact - ref <= room)) {
-            // a logit far above the first pieces' largest: once more against the row's own reference
-            ref = exact;
-            nr = -ref;
-            clear_bins();
-            fill();
+        if constexpr (COUNT) {
+            const float exact = fmaxf(ceilf(mx * k), kRefFloor);
+            if (!(exact - ref <= (float)kTopOctaves)) {
+                // a logit far above the first pieces' largest: once more against the row's own reference
+                ref = exact;
+                nr = -ref;
+                clear_bins();
+                fill();
+            }
         }
         double need = 0.0;
         reach(0ull, need, true, count_c);
@@ -659,7 +662,7 @@ __global__ __launch_bounds__(NT, 4) void wide_step_kernel(StepArgs a, int32_t to
                 const uint32_t i = atomicAdd(&sh.n, 1u);
                 if (i < (uint32_t)Sh::kList) {
                     sh.key[i] = key;
-                    sh.q[i] = q;
+                    sh.q[i] = (uint32_t)q;
                 }
             });
         });
@@ -687,10 +690,11 @@ __global__ __launch_bounds__(NT, 4) void wide_step_kernel(StepArgs a, int32_t to
         // The nucleus alone, the quick way.  While the row lands its logits are only counted, per bin, in 32 bits:
         // 2^s for each, corrected by where in the bin its weight lies (the weight over the bin's own, to 2^-s), so
         // a bin's tally times the weight at its centre is its mass to a few parts in 10^5.  That names the bin in
-        // which the nucleus closes, give or take a neighbour.  One pass then sums all weights and, per chunk, those
-        // above a window of bins around it, exactly, and lists the logits of the window; the list is closed exactly,
-        // and what it keeps is added to its chunks.  If the window was off, or the list overflows (heavy ties, flat
-        // rows), the general selection follows.
+        // which the nucleus closes, give or take a neighbour.  One pass then adds up the masses of all logits and
+        // of those above a window of bins around it, as integers, and the latter's weights per chunk, and lists the
+        // logits of the window; the list is closed by the same integers, and what it keeps is added to its chunks.  If
+        // the window was off (neighbouring bins with more than 32 logits stay out of it) or the list overflows (heavy
+        // ties, flat rows), the general selection follows.
         // (Adding the masses themselves takes 64-bit LDS atomics, 45 cycles a wave, or float ones, 300.)
         bool closed = false;
         const int s_bits = 31 - (32 - __builtin_clz((uint32_t)V));
@@ -737,8 +741,7 @@ __global__ __launch_bounds__(NT, 4) void wide_step_kernel(StepArgs a, int32_t to
                 for (int32_t i = tid; i < nwhole; i += NT) one(piece_at(i));
             });
         }
-        // The tallies are against the first pieces' reference; from here on it is the row's own, so that no weight is
-        // above 1: sums of fixed-point masses stay far below 2^64.
+        // The tallies are against the first pieces' reference; from here on it is the row's own, as the masses need it.
         const float lower = exact - ref;
         ref = exact;
         const float nr = -ref;
@@ -803,8 +806,7 @@ __global__ __launch_bounds__(NT, 4) void wide_step_kernel(StepArgs a, int32_t to
             const float yhi = wlo == 0 ? __builtin_inff()
                                        : ((float)(kTopOctaves * Sh::kPerOctave - wlo) + 0.5f) / kScale - lower;
             const float ylo = ((float)(kTopOctaves * Sh::kPerOctave - whi) - 0.5f) / kScale - lower;
-            double all = 0.0, over = 0.0;
-            float all4 = 0.f;
+            u64 all = 0, over = 0;                           // masses of the lane's logits; of those above the window
             // the lane's weight above the window; its logits inside the window join the list
             auto part = [&](const u32x4 &v, int32_t c) __attribute__((always_inline)) {
                 float x[EPV], sum[EPV / 4];
@@ -812,14 +814,16 @@ __global__ __launch_bounds__(NT, 4) void wide_step_kernel(StepArgs a, int32_t to
 #pragma unroll
                 for (int h = 0; h < EPV / 4; ++h) {          // (four at a time: eight do not fit the registers)
                     float y[4], e[4];
+                    uint32_t q[4];
                     bool any = false;
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
                         y[i] = fmaf(x[4 * h + i], k, nr);
                         e[i] = fast_exp2(y[i]);
+                        q[i] = mass_of(e[i]);
+                        all += q[i];
                         any |= y[i] >= ylo && y[i] <= yhi;
                     }
-                    all4 += (e[0] + e[1]) + (e[2] + e[3]);
                     if (any) {
 #pragma unroll
                         for (int i = 0; i < 4; ++i)
@@ -828,14 +832,18 @@ __global__ __launch_bounds__(NT, 4) void wide_step_kernel(StepArgs a, int32_t to
                                 const uint32_t j = atomicAdd(&sh.n, 1u);
                                 if (j < (uint32_t)Sh::kList) {
                                     sh.key[j] = key;
-                                    sh.q[j] = fixed_mass(e[i]);
+                                    sh.q[j] = q[i];
                                     sh.at[j] = (uint16_t)c;
                                 }
                             }
                     }
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) e[i] = y[i] > yhi ? e[i] : 0.f;
+                    for (int i = 0; i < 4; ++i) {
+                        e[i] = y[i] > yhi ? e[i] : 0.f;
+                        over += y[i] > yhi ? q[i] : 0u;
+                    }
                     sum[h] = (e[0] + e[1]) + (e[2] + e[3]);
+                    asm volatile("" : "+v"(all), "+v"(over));    // (added up here, not as a tree over the row later)
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 if constexpr (EPV == 8) return sum[0] + sum[1];
@@ -845,41 +853,36 @@ __global__ __launch_bounds__(NT, 4) void wide_step_kernel(StepArgs a, int32_t to
             sweep(No{}, [&](const u32x4 &v, int p, int32_t tile) __attribute__((always_inline)) {
                 t[p & 3] = part(v, (tile * NP + p) * W + wave);
                 if ((p & 3) == 3) {
-                    all += (double)all4;
-                    all4 = 0.f;
                     wave_sum4_in_lane63(t[0], t[1], t[2], t[3]);
                     if (lane == 63) {
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            sh.chunk[(tile * NP + (p & ~3) + i) * W + wave] = t[i];
-                            over += (double)t[i];
-                        }
+                        for (int i = 0; i < 4; ++i) sh.chunk[(tile * NP + (p & ~3) + i) * W + wave] = t[i];
                     }
                 }
             });
             const int32_t ctail = ntiles * NP * W;
             float tl = 0.f;
             if (tail != 0 && wave == 0) tl = part(rest, ctail);
-            if (tid == 0) {
-                sh.chunk[ctail] = tl;
-                sh.run = (double)tl;
-            }
-            all = wave_sum(all + (double)all4);
+            if (tid == 0) sh.chunk[ctail] = tl;
+            // (integers below 2^53: exact as doubles, in any order)
+            const double all_wave = wave_sum((double)all), over_wave = wave_sum((double)over);
             if (lane == 63) {
-                sh.wave_d[wave] = all;
-                sh.wave_e[wave] = over;
+                sh.wave_d[wave] = all_wave;
+                sh.wave_e[wave] = over_wave;
             }
             __syncthreads();
             double unused;
             const double need = (double)top_p * wide_total<NT>(sh.wave_d, unused);
-            const double above = wide_total<NT>(sh.wave_e, unused) + sh.run;
+            const double above = wide_total<NT>(sh.wave_e, unused);
             const uint32_t n = sh.n;
             if (n <= (uint32_t)Sh::kList && above < need) {
-                const uint32_t key = close(n, 0ull, (need - above) * 0x1p40, [](auto) {});
+                const uint32_t key = close(n, (u64)above, need, [](auto) {});
                 if (key != 0u) {
                     thr = from_order_key(key);
                     for (uint32_t i = tid; i < n; i += NT)
-                        if (sh.key[i] >= key) add((lds_u64 *)sh.extra + sh.at[i], sh.q[i]);
+                        if (sh.key[i] >= key)
+                            add((lds_u64 *)sh.extra + sh.at[i],
+                                fixed_weight(fast_exp2(fmaf(from_order_key(sh.key[i]), k, nr))));
                     closed = true;
                 }
             }

@@ -63,3 +63,48 @@ def test_largest_logits_past_the_first_ones(gap, dtype):
     codes = np.array([0.5, 0.9, 0.3, 0.95, 0.05, 0.7, 0.999], np.float32)
     for top_p in (0.3, 0.9):
         _against_oracle(x, dtype, codes, top_p, f"gap={gap} {dtype} p={top_p}")
+
+
+# (V, rows): the forms with 256, 512 and 1024 threads, one tile and several, and rows that start off 16 bytes
+SAME = [(4096, 8), (4099, 8), (9001, 600), (20003, 300), (40000, 6), (140001, 3), (70001, 260)]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("V,rows", SAME)
+def test_same_threshold_as_the_radix_select(V, rows, dtype):
+    """The nucleus closes where the fixed-point masses of the general selection say so, whatever the kernel: at shares p
+    that are next to a group's end on purpose, the kept sets are equal (an interval's width is a quotient by the
+    kept weight: the same bits or another set)."""
+    import torch
+    from gpu_util import to_dev_logits
+    from paper_2210_15458_amd import binding as B
+    rng = np.random.default_rng(V)
+    one = synth.gaussian_logits(1, V, sigma=0.7, seed=V, dtype=dtype)[0]
+    x = np.stack([rng.permutation(one) for _ in range(rows)])   # (one set of values, summed in many orders)
+    value = synth.bf16_bits_to_f32(one) if dtype == "bf16" else one
+    logits = to_dev_logits(x)
+    tokens = torch.from_numpy((synth.bf16_bits_to_f32(x) if dtype == "bf16" else x).argmax(axis=1).astype(np.int32)).cuda()
+    ctx = B.Ctx(rows, V, logits.dtype)
+
+    def widths(path, top_k, top_p):
+        ctx.set_tuning("thr_path", path)
+        lo = torch.zeros(rows, dtype=torch.float64, device="cuda")
+        width = torch.ones(rows, dtype=torch.float64, device="cuda")
+        B.as_interval_step(ctx, logits, tokens, 0.9, top_k, top_p, lo, width)
+        return width
+
+    # groups of equal logits, from the largest down, and the running share of the weight
+    values, counts = np.unique(value, return_counts=True)
+    weight = counts[::-1] * np.exp(values[::-1].astype(np.float64) / 0.9)
+    differ = 0
+    for top_k in (0, 100, 300):
+        kept = weight if top_k == 0 else weight[:np.searchsorted(np.cumsum(counts[::-1]), top_k) + 1]
+        share = np.cumsum(kept) / kept.sum()
+        tries = 4 if rows * V > 5e6 else 100 if top_k == 0 else 20
+        for p in rng.choice(share[:-1], min(tries, len(share) - 1), replace=False).astype(np.float32):
+            want = widths(1, top_k, float(p))
+            for path in (3, 0):
+                differ += int((widths(path, top_k, float(p)) != want).sum())
+    print(f"V={V} rows={rows} {dtype}: {differ} rows differ", flush=True)
+    assert differ == 0
+    ctx.close()

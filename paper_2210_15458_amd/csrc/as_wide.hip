@@ -277,12 +277,10 @@ __global__ __launch_bounds__(NT, 4) void wide_step_kernel(StepArgs a, int32_t to
             m = max3(m, vec_max<EPV>(x), m);
         }
         if (top_k <= kWideTopK) {
-            if (NT == 1024) {
-                // 256 groups of four lanes
-                m = fmaxf(m, __shfl_xor(m, 1, 64));
-                m = fmaxf(m, __shfl_xor(m, 2, 64));
-            }
+            // 256 groups of one, two or four lanes
             constexpr int kPerGroup = NT / 256;
+            if (kPerGroup >= 2) m = fmaxf(m, __shfl_xor(m, 1, 64));
+            if (kPerGroup >= 4) m = fmaxf(m, __shfl_xor(m, 2, 64));
             if (tid % kPerGroup == 0) sh.key[tid / kPerGroup] = order_key(m);
             if (tid == 0) {
                 sh.n = 0;

@@ -6,24 +6,24 @@
 //
 // What bounds it: a row of V = 50257 fp32 logits is 200 KB, one work-group fills a compute unit's registers with
 // it, so nothing hides the work that follows the last load, and that is vector issue (13 slots a logit to count it,
-// 10 to sum it) and the latency of some 25 block-wide steps.  Hence a histogram filled while the row lands, one
-// more pass, and no visit of memory after the first but for the code's own chunk.
+// about 17 for its weight and integer mass) and the latency of some 25 block-wide steps.  Hence a histogram filled
+// while the row lands, one more pass, and no visit of memory after the first but for the code's own chunk.
 //
 //   top-k, k <= 128   The k-th largest of 256 group maxima bounds the k-th largest logit from below; the few
 //                     logits at or above it become a candidate table in LDS (value, index), and everything that
 //                     follows - the exact k-th with its ties, the nucleus over the survivors, the code's bucket -
 //                     is ranks and scans over that table.
-//   nucleus           32-bit tallies in 4096 bins, 64 to a factor of two; the bin in which the nucleus closes; the
-//                     chunk sums of everything above a window around it, the window's logits as a list that is
-//                     closed exactly (see below).
+//   nucleus           32-bit tallies in 2048 or 4096 bins over 64 factors of two; the bin in which the nucleus closes;
+//                     the chunk sums of everything above a window around it, the window's logits as a list that is
+//                     closed by integer masses (see below).
 //   k > 128           counts in the same bins, the logits of the closing bin as a list; a nucleus after it by
 //                     fixed-point masses.
 // Then the chunk of the code (64 pieces, vocabulary order), its lane, its logit.  Sums that decide anything are taken
 // in an order, or in integers, that does not depend on which lane comes first.
 //
-// One launch against threshold kernel and sampling kernel before: 1 row of 50257 bf16, p = 0.95 19.8 us (45), 512 rows
-// of 50257 fp32, p = 0.92 51 us (76; the 103 MB alone take 19 at 5.5 TB/s), 230 rows of 256000 bf16, k = 50 then
-// p = 0.95 48 us (171; 21).
+// One launch against threshold kernel and sampling kernel before: 1 row of 50257 bf16, p = 0.95 21.6 us (45), 512 rows
+// of 50257 fp32, p = 0.92 41.6 us (76; the 103 MB alone take 19 at 5.5 TB/s), 230 rows of 256000 bf16, k = 50 then
+// p = 0.95 42.4 us (171; 21).
 #include <type_traits>
 
 #include "as_common.hpp"
@@ -181,6 +181,7 @@ __global__ __launch_bounds__(NT, 4) void wide_step_kernel(StepArgs a, int32_t to
     const int32_t nwhole = vend / EPV, tail = vend % EPV;
     const int32_t last = nwhole > 0 ? nwhole - 1 : 0;
     const int32_t ntiles = MULTI ? (nwhole + NT * NP - 1) / (NT * NP) : 1;
+    const int32_t nfull = (nwhole + 63) / 64;                // chunks of 64 whole pieces
 
     // elements [first, live) of a piece are the row's; the others become -inf, which has no weight
     auto cut = [&](u32x4 v, int32_t first, int32_t live) __attribute__((always_inline)) {
@@ -219,20 +220,29 @@ __global__ __launch_bounds__(NT, 4) void wide_step_kernel(StepArgs a, int32_t to
         for (int i = 0; i < 4; ++i) raw[p][i] = in ? raw[p][i] : kNegInf;
         if (p == 0 && shift != 0 && tid == 0 && cur == 0 && nwhole > 0) raw[0] = cut(raw[0], shift, EPV);
     };
+    // whether the row reaches a tile's p-th piece of any thread: a row pays for the pieces it has, not for all that the
+    // form can hold (block-uniform; the first is always taken in)
+    auto present = [&](int p, int32_t t) __attribute__((always_inline)) { return p == 0 || (t * NP + p) * NT < nwhole; };
     load(0);
     if (tail != 0 && tid == 0) rest = piece_at(nwhole);
     __builtin_amdgcn_sched_barrier(0);
 
-    // f(piece, p, tile) over the row's whole pieces.  FIRST: the resident tile has only been requested.
-    auto sweep = [&](auto first_c, auto f) __attribute__((always_inline)) {
+    // f(piece, p, tile) over the row's whole pieces, after4(p, tile) after every four of them (p: the first of the four).
+    // FIRST: the resident tile has only been requested.
+    auto nothing_more = [](int, int32_t) {};
+    auto sweep = [&](auto first_c, auto f, auto after4) __attribute__((always_inline)) {
         constexpr bool FIRST = decltype(first_c)::value;
         if constexpr (!MULTI) {
 #pragma unroll
             for (int p = 0; p < NP; ++p) {
                 if constexpr (FIRST) land(p);
-                else asm volatile("" : "+v"(raw[p]));        // (nothing derived in an earlier pass is kept for this one)
-                f(raw[p], p, 0);
+                if (present(p, 0)) {
+                    u32x4 v = raw[p];
+                    asm volatile("" : "+v"(v));              // (a copy: nothing derived in one pass is kept for another)
+                    f(v, p, 0);
+                }
                 __builtin_amdgcn_sched_barrier(0);           // (a piece at a time: interleaved, several do not fit)
+                if ((p & 3) == 3 && present(p - 3, 0)) after4(p - 3, 0);
             }
         } else {
             const int32_t begin = cur, step = cur == 0 ? 1 : -1;
@@ -245,8 +255,13 @@ __global__ __launch_bounds__(NT, 4) void wide_step_kernel(StepArgs a, int32_t to
 #pragma unroll
                 for (int p = 0; p < NP; ++p) {
                     if (FIRST || n != 0) land(p);
-                    f(raw[p], p, t);
+                    if (present(p, t)) {
+                        u32x4 v = raw[p];
+                        asm volatile("" : "+v"(v));
+                        f(v, p, t);
+                    }
                     __builtin_amdgcn_sched_barrier(0);
+                    if ((p & 3) == 3 && present(p - 3, t)) after4(p - 3, t);
                 }
             }
         }
@@ -331,7 +346,7 @@ __global__ __launch_bounds__(NT, 4) void wide_step_kernel(StepArgs a, int32_t to
             if (bounded) {
                 sweep(No{}, [&](const u32x4 &v, int p, int32_t t) __attribute__((always_inline)) {
                     push(v, ((t * NP + p) * NT + tid) * EPV);
-                });
+                }, nothing_more);
                 if (tail != 0 && wave == 0) push(rest, nwhole * EPV);
             }
             __syncthreads();
@@ -567,7 +582,7 @@ __global__ __launch_bounds__(NT, 4) void wide_step_kernel(StepArgs a, int32_t to
     // well, the row costs spilled registers on the way that is taken)
     auto every_piece = [&](auto f) __attribute__((always_inline)) {
         if constexpr (TOPK) {
-            sweep(No{}, [&](const u32x4 &v, int, int32_t) __attribute__((always_inline)) { f(v); });
+            sweep(No{}, [&](const u32x4 &v, int, int32_t) __attribute__((always_inline)) { f(v); }, nothing_more);
             if (tail != 0 && wave == 0) f(rest);
         } else {
             for (int32_t i = tid; i <= nwhole; i += NT) f(piece_at(i));
@@ -674,6 +689,18 @@ __global__ __launch_bounds__(NT, 4) void wide_step_kernel(StepArgs a, int32_t to
         return key != 0u;                                    // (0: the weights of a NaN row)
     };
 
+    // four chunk sums of the wave, from its lanes' (0 for a piece that the row does not reach: chunks past the row's end
+    // are written, and read by nobody)
+    auto chunks_done = [&](float (&t)[4], int p, int32_t tile) __attribute__((always_inline)) {
+        wave_sum4_in_lane63(t[0], t[1], t[2], t[3]);
+        if (lane == 63) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) sh.chunk[(tile * NP + p + i) * W + wave] = t[i];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) t[i] = 0.f;
+    };
+
     float thr = -__builtin_inff();
     bool some = true, summed = false;    // summed: the chunk sums of the kept logits are in place
     if constexpr (TOPK) {
@@ -729,7 +756,7 @@ __global__ __launch_bounds__(NT, 4) void wide_step_kernel(StepArgs a, int32_t to
             mx = wide_max<NT>(m, sh.wave_f);
         };
         fill([&](auto one) __attribute__((always_inline)) {
-            sweep(Yes{}, [&](const u32x4 &v, int, int32_t) __attribute__((always_inline)) { one(v); });
+            sweep(Yes{}, [&](const u32x4 &v, int, int32_t) __attribute__((always_inline)) { one(v); }, nothing_more);
         });
         const float exact = fmaxf(ceilf(mx * k), kRefFloor);
         if (!(exact - ref <= (float)kTopOctaves)) {
@@ -784,7 +811,7 @@ __global__ __launch_bounds__(NT, 4) void wide_step_kernel(StepArgs a, int32_t to
             __syncthreads();
         }
         const int32_t pick = sh.pick;
-        if (pick >= 0 && ntiles * NP * W < Sh::kExtra) {
+        if (pick >= 0 && nfull < Sh::kExtra) {
             // the window: bins on either side of the picked one until they hold 32 logits
             int32_t wlo, whi;
             {
@@ -847,21 +874,12 @@ __global__ __launch_bounds__(NT, 4) void wide_step_kernel(StepArgs a, int32_t to
                 if constexpr (EPV == 8) return sum[0] + sum[1];
                 else return sum[0];
             };
-            float t[4];
+            float t[4] = {0.f, 0.f, 0.f, 0.f};
             sweep(No{}, [&](const u32x4 &v, int p, int32_t tile) __attribute__((always_inline)) {
                 t[p & 3] = part(v, (tile * NP + p) * W + wave);
-                if ((p & 3) == 3) {
-                    wave_sum4_in_lane63(t[0], t[1], t[2], t[3]);
-                    if (lane == 63) {
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) sh.chunk[(tile * NP + (p & ~3) + i) * W + wave] = t[i];
-                    }
-                }
-            });
-            const int32_t ctail = ntiles * NP * W;
+            }, [&](int p, int32_t tile) __attribute__((always_inline)) { chunks_done(t, p, tile); });
             float tl = 0.f;
-            if (tail != 0 && wave == 0) tl = part(rest, ctail);
-            if (tid == 0) sh.chunk[ctail] = tl;
+            if (tail != 0 && wave == 0) tl = part(rest, nfull);
             // (integers below 2^53: exact as doubles, in any order)
             const double all_wave = wave_sum((double)all), over_wave = wave_sum((double)over);
             if (lane == 63) {
@@ -869,6 +887,7 @@ __global__ __launch_bounds__(NT, 4) void wide_step_kernel(StepArgs a, int32_t to
                 sh.wave_e[wave] = over_wave;
             }
             __syncthreads();
+            if (tid == 0) sh.chunk[nfull] = tl;              // (in the place of a chunk past the row's end)
             double unused;
             const double need = (double)top_p * wide_total<NT>(sh.wave_d, unused);
             const double above = wide_total<NT>(sh.wave_e, unused);
@@ -904,21 +923,13 @@ __global__ __launch_bounds__(NT, 4) void wide_step_kernel(StepArgs a, int32_t to
     // ------------------------------------------------------------------ the step over the kept logits
     const float nr = -ref;
     auto lane_sum = [&](const u32x4 &v) __attribute__((always_inline)) { return tile_lane_sum<DT, true>(v, k, nr, thr); };
-    const int32_t nchunks = ntiles * NP * W + 1;             // the last one: the piece that the row ends in
+    const int32_t nchunks = nfull + 1;                       // the last one: the piece that the row ends in
     if (!summed) {
         __syncthreads();
         if constexpr (TOPK) {
-            float t[4];
-            sweep(No{}, [&](const u32x4 &v, int p, int32_t tile) __attribute__((always_inline)) {
-                t[p & 3] = lane_sum(v);
-                if ((p & 3) == 3) {
-                    wave_sum4_in_lane63(t[0], t[1], t[2], t[3]);
-                    if (lane == 63) {
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) sh.chunk[(tile * NP + (p & ~3) + i) * W + wave] = t[i];
-                    }
-                }
-            });
+            float t[4] = {0.f, 0.f, 0.f, 0.f};
+            sweep(No{}, [&](const u32x4 &v, int p, int32_t) __attribute__((always_inline)) { t[p & 3] = lane_sum(v); },
+                  [&](int p, int32_t tile) __attribute__((always_inline)) { chunks_done(t, p, tile); });
         } else {
             for (int32_t c = wave; c < nchunks - 1; c += W) {
                 const int32_t i = c * 64 + lane;
@@ -926,6 +937,7 @@ __global__ __launch_bounds__(NT, 4) void wide_step_kernel(StepArgs a, int32_t to
                 if (lane == 0) sh.chunk[c] = t;
             }
         }
+        __syncthreads();
         if (tid == 0) sh.chunk[nchunks - 1] = tail != 0 ? lane_sum(rest) : 0.f;
     }
     __syncthreads();
@@ -1021,40 +1033,35 @@ void launch_form(as_ctx *ctx, int kid, const StepArgs &a, int32_t top_k, float t
 
 // Threads and pieces a thread by the row's pieces of 16 bytes and the number of rows.  With a row per compute unit or
 // fewer, 1024 threads finish it soonest (one row of 50257 bf16: nucleus 20 us, top-k 40 12 us).  With more, smaller
-// blocks that share a unit overlap each other's loads and tails: two blocks of 512 where two fit (300 rows of 20003
-// bf16: nucleus 22 us; as blocks of 1024 47), and with top-k, whose work after the loads is short, as few threads as hold
-// the row (2500 rows of 20003 bf16, top-k 40: 43 us with 256 threads, 67 with 512).  The bf16 nucleus, with twice the
-// logits in a register, does not fit 16 pieces (2500 rows of 50257: 240 us with 512 x 16, 203 with 1024 x 8): a row
-// beyond 1024 x 8 goes tile by tile.
+// blocks that share a unit overlap each other's loads and tails: two blocks of 512 where two fit (nucleus, bf16: 300 rows
+// of 33001 27 us, as blocks of 1024 38; 6439 of them 276, 476; 1000 of 65001 70, 96; fp32 2500 of 33001, which go
+// tile by tile, 129, 200), and with many rows that 256 threads hold, those (nucleus, bf16, 6439 rows: of 9001 108
+// us with 256 x 8, 143 with 512 x 4; of 20001 152 with 256 x 16, 174 with 512 x 8; top-k 40, 2500 of 20003 43, with 512
+// threads 67).
 template <int DT, bool TOPK>
 void launch_type(as_ctx *ctx, int kid, const StepArgs &a, int32_t top_k, float top_p, float *thr_out)
 {
     constexpr int EPV = Elem<DT>::kPerVec;
-    constexpr bool kDeep = TOPK || DT == AS_F32;             // 16 pieces a thread fit the registers
     const int64_t most = ((int64_t)a.V + EPV - 1) / EPV;     // whole pieces of a row, whatever its alignment
     const bool many = a.rows > (int64_t)ctx->num_cus, lots = a.rows > 2 * (int64_t)ctx->num_cus;
     if (most <= 256 * 4) return launch_form<DT, 256, 4, false, TOPK>(ctx, kid, a, top_k, top_p, thr_out);
-    if constexpr (kDeep) {
-        if (lots && most <= 256 * 16 && (TOPK ? top_k <= kWideTopK : most > 512 * 4))
-            return launch_form<DT, 256, 16, false, TOPK>(ctx, kid, a, top_k, top_p, thr_out);
-    }
-    if constexpr (!TOPK && DT == AS_F32) {
+    if constexpr (!TOPK) {
         if (lots && most <= 256 * 8) return launch_form<DT, 256, 8, false, TOPK>(ctx, kid, a, top_k, top_p, thr_out);
     }
+    if (lots && most <= 256 * 16 && (!TOPK || top_k <= kWideTopK))
+        return launch_form<DT, 256, 16, false, TOPK>(ctx, kid, a, top_k, top_p, thr_out);
     if (many && most <= 512 * 4) return launch_form<DT, 512, 4, false, TOPK>(ctx, kid, a, top_k, top_p, thr_out);
     if (many && most <= 512 * 8) return launch_form<DT, 512, 8, false, TOPK>(ctx, kid, a, top_k, top_p, thr_out);
-    if constexpr (kDeep) {
-        if (many && most <= 512 * 16) return launch_form<DT, 512, 16, false, TOPK>(ctx, kid, a, top_k, top_p, thr_out);
+    if (many && most <= 512 * 16) return launch_form<DT, 512, 16, false, TOPK>(ctx, kid, a, top_k, top_p, thr_out);
+    if constexpr (!TOPK) {
+        // (with a tile of slack: the last one's chunks are written whole)
+        if (many && most + 512 * 8 <= 64 * (int64_t)(WideShared<512, true>::kChunks - 1))
+            return launch_form<DT, 512, 8, true, false>(ctx, kid, a, top_k, top_p, thr_out);
     }
     if (most <= 1024 * 4) return launch_form<DT, 1024, 4, false, TOPK>(ctx, kid, a, top_k, top_p, thr_out);
     if (most <= 1024 * 8) return launch_form<DT, 1024, 8, false, TOPK>(ctx, kid, a, top_k, top_p, thr_out);
-    if constexpr (kDeep) {
+    if constexpr (TOPK || DT == AS_F32) {
         if (most <= 1024 * 16) return launch_form<DT, 1024, 16, false, TOPK>(ctx, kid, a, top_k, top_p, thr_out);
-    }
-    if constexpr (!TOPK) {
-        // (with a tile of slack: the last one's chunks are counted whole)
-        if (many && most + 512 * 8 <= 64 * (int64_t)(WideShared<512, true>::kChunks - 1))
-            return launch_form<DT, 512, 8, true, false>(ctx, kid, a, top_k, top_p, thr_out);
     }
     launch_form<DT, 1024, TOPK ? 16 : 8, true, TOPK>(ctx, kid, a, top_k, top_p, thr_out);
 }

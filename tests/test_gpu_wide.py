@@ -3,6 +3,7 @@ form of the kernel at the ends of its range, against the oracle with the accepta
 import numpy as np
 import pytest
 
+from paper_2210_15458_amd import synth
 from test_gpu_step import _check
 
 pytestmark = pytest.mark.gpu
@@ -56,3 +57,45 @@ def test_special_rows():
             gpu = run_gpu_step(stored, codes, V, top_k=top_k, top_p=top_p, tuning=ANY)
             ref = oracle_step(stored, codes, V, top_k=top_k, top_p=top_p)
             compare_step(gpu, ref, V, f"special {dtype} k={top_k} p={top_p}", trunc=True, codes=codes)
+
+
+# The forms that are taken with more rows than compute units, by the pieces of 16 bytes of a row: 256 threads x 8 and
+# x 16, 512 x 4, x 8 and x 16, 512 and 1024 tile by tile (143296 pieces: the longest row that 512 threads take)
+LOTS_OF_ROWS = [(1025, 520), (2048, 520), (2049, 520), (4096, 520), (1025, 300), (2048, 300), (2049, 300), (4096, 300),
+                (4097, 300), (8192, 300), (8193, 300), (20000, 300)]
+
+
+def _check_shared(V, rows, dtype, top_k, top_p, tuning):
+    """_check with a few rows of logits for many codes."""
+    from gpu_util import compare_step, oracle_step, run_gpu_step
+    held = 3
+    stored = synth.gaussian_logits(held, V, seed=V, dtype=dtype)
+    rid = (np.arange(rows) % held).astype(np.int32)
+    codes = synth.uniform_codes(rows, seed=rows)
+    label = f"V={V} R={rows} {dtype} k={top_k} p={top_p}"
+    print("case", label, flush=True)
+    gpu = run_gpu_step(stored, codes, V, temp=0.9, top_k=top_k, top_p=top_p, row_ids=rid, tuning=tuning)
+    ref = oracle_step(stored, codes, V, temp=0.9, top_k=top_k, top_p=top_p, row_ids=rid.astype(np.int64))
+    print("   ", compare_step(gpu, ref, V, label, trunc=True, codes=codes), flush=True)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("pieces,rows", LOTS_OF_ROWS)
+def test_forms_for_many_rows(pieces, rows, dtype):
+    V = pieces * (8 if dtype == "bf16" else 4)
+    for top_k, top_p in ((0, 0.9), (40, 1.0), (128, 0.9), (300, 0.8)):
+        _check_shared(V, rows, dtype, top_k, top_p, ANY)
+    _check_shared(V - 1, rows, dtype, 0, 0.9, None)       # (rows that start off 16 bytes; the library's own choice)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("more", [0, 1])
+def test_longest_rows_of_512_threads(more, dtype):
+    _check_shared(143296 * (8 if dtype == "bf16" else 4) + more, 260, dtype, 0, 0.9, None)
+
+
+@pytest.mark.parametrize("V,dtype", [(65537, "bf16"), (100000, "bf16"), (32769, "f32"), (50257, "f32")])
+def test_streamed_kernel(V, dtype):
+    # what is left to it: k above 128 on rows of more than 128 KB, more rows than compute units
+    for top_k, top_p in ((129, 1.0), (300, 0.8), (5000, 0.95)):
+        _check_shared(V, 300, dtype, top_k, top_p, None)

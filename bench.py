@@ -9,7 +9,8 @@ synthetic, seeded and already resident in HBM when timing starts.
 
 Prints ONE JSON line: whole-job code-steps/s, plus
   roofline      the fused sampling kernel (the dominant HBM-bound kernel): its
-                algorithmic bytes per launch over its average launch duration,
+                algorithmic bytes per launch (logits rows that several codes share
+                counted once) over its average launch duration,
                 taken from the dispatch's own HIP events during the timed region
   roofline_cold the same kernel launched alone over >1 GiB of rotating logits
                 buffers, so no row can be served from the 256 MB Infinity Cache
@@ -54,34 +55,65 @@ def up(a):
     return torch.from_numpy(a).cuda()
 
 
-def sampling_kernel_name(V, ldt, top_k, top_p, temp=1.0):
-    """Which kernel finishes the sampling step for this shape (the choice the library makes)."""
+def compute_units():
+    import torch
+    return torch.cuda.get_device_properties(0).multi_processor_count
+
+
+def sampling_kernel_name(V, ldt, top_k, top_p, temp, rows, d, wdt, cus):
+    """Which kernel finishes a decode's sampling step for this shape (the choice the library makes)."""
     has_k, has_p = 0 < top_k < V, 0.0 < top_p < 1.0
-    tile = V <= (32768 if ldt == "bf16" else 16384) and V % (8 if ldt == "bf16" else 4) == 0
+    half = ldt == "bf16"
+    tile = V <= (32768 if half else 16384) and V % (8 if half else 4) == 0
     first_chunk_reference_ok = 1.4426950408889634 / temp <= 4.0      # (the library's kTileMaxScale)
-    if tile and ldt == "bf16" and has_k and top_k <= 48:
-        return ("topk_tile_kernel (top-k%s and the sampling step in one launch, row resident in registers), "
-                "as launched inside as_decode" % (" + nucleus" if has_p else ""))
-    if tile and ldt == "bf16" and has_p and not has_k and first_chunk_reference_ok:
-        return ("nucleus_tile_kernel (nucleus and the sampling step in one launch, logits counted by stored value), "
-                "as launched inside as_decode")
-    if V <= 32768 and has_k and top_k <= 128:
-        return "threshold_resident_kernel with the sampling step fused (top-k, candidates ranked in LDS), as launched inside as_decode"
-    if has_k or has_p:
-        return "threshold kernel, then the sampling-step kernel, as launched inside as_decode"
-    if tile and first_chunk_reference_ok:
-        return "step_tile_kernel (fused sampling step, one-tile rows), as launched inside as_decode"
-    return "step_kernel (fused sampling step), as launched inside as_decode"
+    name = None
+    if not (has_k or has_p):
+        if (not (wdt == "bf16" and d % 64 == 0) and V <= 1024 and d <= 128 and V * d <= 8192 and
+                V % (8 if half else 4) == 0 and rows <= 3 * cus and first_chunk_reference_ok):
+            name = "decode_small_kernel (the whole decode in one launch)"
+        elif tile and first_chunk_reference_ok:
+            name = "step_tile_kernel (fused sampling step, one-tile rows)"
+        else:
+            name = "step_kernel (fused sampling step)"
+    elif tile and half and not (V <= 8192 and rows > 2 * cus) and (top_k <= 48 if has_k else first_chunk_reference_ok):
+        if has_k:
+            name = ("topk_tile_kernel (top-k%s and the sampling step in one launch, row resident in registers)"
+                    % (" + nucleus" if has_p else ""))
+        else:
+            name = "nucleus_tile_kernel (nucleus and the sampling step in one launch, logits counted by stored value)"
+    elif (V <= 32768 and top_k <= 128 and rows > cus and V > (8192 if half else 4096) and
+          (half or (has_k and (V > 16384 or rows <= 2 * cus)))):
+        name = "threshold_resident_kernel with the sampling step fused"
+    elif has_k and top_k > 128 and rows > cus and V * (2 if half else 4) > 131072:
+        name = "threshold_stream_kernel, then the sampling-step kernel"
+    else:
+        name = "wide_step_kernel (truncation and the sampling step in one launch)"
+    return name + ", as launched inside as_decode"
 
 
-def active_rows(tokens, eos):
-    """Rows still running at each decode step, averaged over the steps (finished rows are not read)."""
-    tk = tokens.cpu().numpy().reshape(-1, tokens.shape[-1])
-    T = tk.shape[1]
+def rows_shared(V, d, R, T, wdt):
+    """Whether a decode shares logits rows after its first step (the choice the library makes)."""
+    if T < 2 or wdt != "bf16" or d % 64 != 0 or d < 128 or V * d * 2 >= 2 ** 32:
+        return False
+    return (R - V * (1.0 - np.exp(-R / V))) * V * d * 2.0 > 20e-6 * 1e15
+
+
+def step_counts(tokens, eos, prompts, shared):
+    """Per step of a decode, averaged over its steps: rows still running (`active`), logits rows that are computed, and
+    logits rows that the rows still running read (`fetched`, each once).  The first step has one logits row per
+    prompt; later ones have one per row, or with sharing one per token that any row (an ended one too) conditions on."""
+    tk = np.asarray(tokens.cpu() if hasattr(tokens, "cpu") else tokens)
+    tk = tk.reshape(-1, tk.shape[-1])
+    R, T = tk.shape
     active = np.ones(tk.shape, dtype=bool)
     for t in range(1, T):
         active[:, t] = active[:, t - 1] & (tk[:, t - 1] != eos)
-    return float(active.sum()) / T
+    computed, fetched = [prompts], [prompts]
+    for t in range(1, T):
+        prev = tk[:, t - 1]
+        computed.append(len(np.unique(prev)) if shared else R)
+        fetched.append(len(np.unique(prev[active[:, t]])) if shared else int(active[:, t].sum()))
+    return {"active": float(active.sum()) / T, "computed": float(np.mean(computed)), "fetched": float(np.mean(fetched))}
 
 
 def compact_leg(cfg_id, top_k, top_p, steps, warmup):
@@ -115,22 +147,25 @@ def compact_leg(cfg_id, top_k, top_p, steps, warmup):
     step_samples, gemm_samples, thr_samples = ctx.profile_samples(0), ctx.profile_samples(1), ctx.profile_samples(2)
     ctx.profile_read(0); ctx.profile_read(1); ctx.profile_read(2)
     ctx.profile(False)
-    act = active_rows(tokens, eos)
+    cnt = step_counts(tokens, eos, Bn, rows_shared(V, d, R, T, cfg["dtype"]))
     bytes_per_row = V * 2 + 18
+    bytes_per_launch = cnt["fetched"] * V * 2 + cnt["active"] * 18      # logits rows in use, each once; codes, tokens, flags
     # the sampling step of a launch: the kernel that finishes it, plus the threshold kernel where that is separate
     samp_us = float(np.mean(step_samples)) * 1e3 + (float(np.mean(thr_samples)) * 1e3 if len(thr_samples) else 0.0)
-    ach = act * bytes_per_row / (samp_us * 1e-6) / 1e9
+    ach = bytes_per_launch / (samp_us * 1e-6) / 1e9
     out = {
         "workload": f"configs[{cfg_id}] {cfg['name']}: as_decode V={V} d={d} bf16, B={Bn} N={N} (R={R}) T={T} "
                     f"temp={temp} top_k={top_k} top_p={top_p} eos={eos}",
         "value": R * T * steps / (t1 - t0), "unit": "code-steps/s", "decodes_timed": steps,
         "ms_per_decode": (t1 - t0) / steps * 1e3,
-        "sampling": {"kernel": sampling_kernel_name(V, "bf16", top_k, top_p, temp), "bound": "hbm",
+        "sampling": {"kernel": sampling_kernel_name(V, "bf16", top_k, top_p, temp, R, d, cfg["dtype"], compute_units()),
+                     "bound": "hbm",
                      "avg_launch_us": samp_us, "spread": spread(step_samples), "achieved": ach, "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": ach / HBM_PEAK_GBS, "bytes_per_code_step": bytes_per_row,
-                     "active_rows_per_launch": act},
+                     "bytes_per_launch": bytes_per_launch, "active_rows_per_launch": cnt["active"], "logits_rows_fetched_per_launch": cnt["fetched"]},
         "logits_gemm": {"avg_launch_us": float(np.mean(gemm_samples)) * 1e3, "spread": spread(gemm_samples),
-                        "achieved": 2.0 * R * d * V / (float(np.mean(gemm_samples)) * 1e-3) / 1e12,
+                        "rows_computed_per_launch": cnt["computed"],
+                        "achieved": 2.0 * cnt["computed"] * d * V / (float(np.mean(gemm_samples)) * 1e-3) / 1e12,
                         "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s"}}
     out["logits_gemm"]["frac"] = out["logits_gemm"]["achieved"] / MFMA_BF16_PEAK_TFLOPS
     if len(thr_samples):
@@ -269,11 +304,14 @@ def main():
 
     wall = t1 - t0
     code_steps = R * T * args.steps
-    # rows that were still running, per launch: finished rows are not read
-    active_rows_per_launch = active_rows(tokens, eos)
+    # rows that were still running, per launch (finished rows are not read), and the logits rows they read
+    cnt = step_counts(tokens, eos, Bn, rows_shared(V, d, R, T, cfg["dtype"]))
     bytes_per_row = V * esz + 18           # the logits row + code in/out, token, flags
+    bytes_per_launch = cnt["fetched"] * V * esz + cnt["active"] * 18
     step_avg_us = step_ms / max(step_n, 1) * 1e3
-    achieved = active_rows_per_launch * bytes_per_row / (step_avg_us * 1e-6) / 1e9 if step_n else None
+    # (a launch that does a whole decode has no logits rows in memory)
+    whole_decode = T > 1 and step_n == args.steps
+    achieved = bytes_per_launch / (step_avg_us * 1e-6) / 1e9 if step_n and not whole_decode else None
 
     out = {
         "metric": "code-steps/sec and sampling-kernel HBM GB/s (% peak), V=32128, N*B=1024",
@@ -296,16 +334,19 @@ def main():
                    "value_over_a_longer_region": {"steps": long_steps, "value": R * T * long_steps / (t5 - t4),
                                                   "ms_per_step": (t5 - t4) / long_steps * 1e3}},
         "roofline": {
-            "kernel": sampling_kernel_name(V, ldt, top_k, top_p, temp),
+            "kernel": sampling_kernel_name(V, ldt, top_k, top_p, temp, R, d, cfg["dtype"], compute_units()),
             "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": (achieved / HBM_PEAK_GBS) if achieved else None, "traffic": None,
             "avg_launch_us": step_avg_us, "launches": step_n, "untimed_launches": step_drop,
-            "bytes_per_code_step": bytes_per_row, "active_rows_per_launch": active_rows_per_launch,
+            "bytes_per_code_step": bytes_per_row, "bytes_per_launch": bytes_per_launch,
+            "active_rows_per_launch": cnt["active"],
+            "logits_rows_fetched_per_launch": cnt["fetched"],
             "note": "rows follow the logits GEMM that just wrote them, so part of each row can come from "
                     "the Infinity Cache rather than HBM; see roofline_cold for the HBM-only figure"},
         "logits_gemm": {
             "bound": "mfma", "avg_launch_us": gemm_ms / max(gemm_n, 1) * 1e3, "launches": gemm_n,
-            "achieved": (2.0 * R * d * V / (gemm_ms / max(gemm_n, 1) * 1e-3) / 1e12) if gemm_n else None,
+            "rows_computed_per_launch": cnt["computed"],
+            "achieved": (2.0 * cnt["computed"] * d * V / (gemm_ms / max(gemm_n, 1) * 1e-3) / 1e12) if gemm_n else None,
             "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s"},
     }
     if out["logits_gemm"]["achieved"]:
@@ -366,7 +407,7 @@ def main():
     out["encode"] = {
         "kernel": "interval_tile_kernel (the single-tile sampling kernel with a lookup of the given token in place of the search), inside as_encode",
         "avg_launch_us": iv_us, "launches": iv_n, "bound": "hbm",
-        "achieved": active_rows_per_launch * bytes_per_row / (iv_us * 1e-6) / 1e9 if iv_n else None,
+        "achieved": bytes_per_launch / (iv_us * 1e-6) / 1e9 if iv_n else None,
         "peak": HBM_PEAK_GBS, "unit": "GB/s",
         "code_steps_per_s_with_dispatch_events": code_steps / args.steps * 3 / (e1 - e0)}
     if out["encode"]["achieved"]:
@@ -449,7 +490,7 @@ def main():
         ach = R * bytes_per_row / (us * 1e-6) / 1e9
         out["roofline_cold"] = {
             "spread": spread(cold_samples),
-            "kernel": "step_kernel alone, rotating over %d logits buffers (%.2f GiB)" % (
+            "kernel": "the sampling kernel alone, rotating over %d logits buffers (%.2f GiB)" % (
                 nbuf, nbuf * R * ld * esz / 2 ** 30),
             "bound": "hbm", "achieved": ach, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": ach / HBM_PEAK_GBS,
             "avg_launch_us": us, "launches": n, "code_steps_per_s": R / (us * 1e-6)}

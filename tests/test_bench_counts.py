@@ -1,0 +1,22 @@
+"""What bench.py divides by a launch's time: logits rows that are computed and read, not rows of codes."""
+import numpy as np
+
+import bench
+
+
+def test_rows_of_a_decode_with_and_without_sharing():
+    # 2 prompts x 3 codes, 4 steps, EOS = 1: two rows end after their second token
+    tokens = np.array([[[5, 5, 7, 7], [5, 1, 1, 1], [6, 6, 7, 9]],
+                       [[5, 8, 8, 8], [9, 1, 1, 1], [6, 6, 8, 9]]])
+    own = bench.step_counts(tokens, 1, 2, False)
+    assert own == {"active": (6 + 6 + 4 + 4) / 4, "computed": (2 + 6 + 6 + 6) / 4, "fetched": (2 + 6 + 4 + 4) / 4}
+    # tokens conditioned on: {5, 6, 9}, {5, 1, 6, 8}, {7, 1, 8}; by rows still running the last two lose EOS
+    shared = bench.step_counts(tokens, 1, 2, True)
+    assert shared == {"active": 5.0, "computed": (2 + 3 + 4 + 3) / 4, "fetched": (2 + 3 + 3 + 2) / 4}
+
+
+def test_sharing_pays_for_wide_lattices_only():
+    assert bench.rows_shared(32128, 512, 65536, 16, "bf16")
+    assert not bench.rows_shared(32128, 512, 1024, 64, "bf16")
+    assert not bench.rows_shared(32128, 512, 65536, 1, "bf16")
+    assert not bench.rows_shared(32128, 512, 65536, 16, "f32")

@@ -91,11 +91,23 @@ def sampling_kernel_name(V, ldt, top_k, top_p, temp, rows, d, wdt, cus):
     return name + ", as launched inside as_decode"
 
 
-def rows_shared(V, d, R, T, wdt):
+def tile_rounds(m, n_blocks, W, gm):
+    nbx = -(-n_blocks // 8)
+    if m >= W or (m >= gm and m % gm == 0):
+        return -(-m // gm) * -(-nbx // (W // gm))
+    return -(-nbx // (W // m))
+
+
+def rows_shared(V, d, R, T, wdt, cus):
     """Whether a decode shares logits rows after its first step (the choice the library makes)."""
     if T < 2 or wdt != "bf16" or d % 64 != 0 or d < 128 or V * d * 2 >= 2 ** 32:
         return False
-    return (R - V * (1.0 - np.exp(-R / V))) * V * d * 2.0 > 20e-6 * 1e15
+    tokens = V * (1.0 - np.exp(-R / V))
+    W = cus // 8
+    gm = 8 if W % 8 == 0 else W
+    n_blocks = -(-V // 256)
+    spared = tile_rounds(-(-R // 256), n_blocks, W, gm) - tile_rounds((int(tokens) + 256) // 256, n_blocks, W, gm)
+    return 0.5 * ((R - tokens) * V * d * 2.0 / 1e15 + spared * (d / 64 * 1.72e-6 + 2.3e-6)) > 20e-6
 
 
 def step_counts(tokens, eos, prompts, shared):
@@ -147,7 +159,7 @@ def compact_leg(cfg_id, top_k, top_p, steps, warmup):
     step_samples, gemm_samples, thr_samples = ctx.profile_samples(0), ctx.profile_samples(1), ctx.profile_samples(2)
     ctx.profile_read(0); ctx.profile_read(1); ctx.profile_read(2)
     ctx.profile(False)
-    cnt = step_counts(tokens, eos, Bn, rows_shared(V, d, R, T, cfg["dtype"]))
+    cnt = step_counts(tokens, eos, Bn, rows_shared(V, d, R, T, cfg["dtype"], compute_units()))
     bytes_per_row = V * 2 + 18
     bytes_per_launch = cnt["fetched"] * V * 2 + cnt["active"] * 18      # logits rows in use, each once; codes, tokens, flags
     # the sampling step of a launch: the kernel that finishes it, plus the threshold kernel where that is separate
@@ -305,7 +317,7 @@ def main():
     wall = t1 - t0
     code_steps = R * T * args.steps
     # rows that were still running, per launch (finished rows are not read), and the logits rows they read
-    cnt = step_counts(tokens, eos, Bn, rows_shared(V, d, R, T, cfg["dtype"]))
+    cnt = step_counts(tokens, eos, Bn, rows_shared(V, d, R, T, cfg["dtype"], compute_units()))
     bytes_per_row = V * esz + 18           # the logits row + code in/out, token, flags
     bytes_per_launch = cnt["fetched"] * V * esz + cnt["active"] * 18
     step_avg_us = step_ms / max(step_n, 1) * 1e3

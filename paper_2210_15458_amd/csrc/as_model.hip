@@ -1153,17 +1153,36 @@ bool mfma_applies(const as_model *m)
            reinterpret_cast<uintptr_t>(m->Ut) % 16 == 0;
 }
 
-// Whether a decode of `rows` rows shares logits rows after its first step: with tokens spread evenly over the vocabulary
-// (the worst case) rows - V(1 - exp(-rows/V)) rows are saved, at 1 PFLOP/s, against two small launches and the
-// clearing of the tables; the line lies at twice their cost.  (65536 rows, V = 32128, d = 512: 2.03 ms of product
-// a step for 65536 rows, 0.9 for the 28000 tokens in use.)
+// Tiles that the busiest worker of the persistent kernel computes, one after the other, for m row tiles (its mapping: with
+// fewer row tiles than workers, and not a multiple of gm of them, some of the workers have none).
+static int64_t tile_rounds(int64_t m, int64_t n_blocks, int W, int gm)
+{
+    const int64_t nbx = (n_blocks + 7) / 8;
+    if (m >= W || (m >= gm && m % gm == 0)) return (m + gm - 1) / gm * ((nbx + W / gm - 1) / (W / gm));
+    return (nbx + W / m - 1) / (W / m);
+}
+
+// Whether a decode of `rows` rows shares logits rows after its first step.  With tokens spread evenly over the vocabulary
+// (the worst case) rows - V(1 - exp(-rows/V)) rows of product are saved; the sharing itself takes 6 to 12 us a step,
+// 20 to 25 where the rows are sorted too, and is asked to save 20.  What the product then takes less lies between
+// the work saved, at 1 PFLOP/s, and the tiles that the busiest worker is spared, 1.72 us a K step and 2.3 for the rest:
+// the rows in use may fit the workers worse than all rows do.  Half of each is what was measured (us a step, every
+// row its own / shared; V = 32128): d = 512, 6144 rows 238 / 262, 6700 303 / 255 (24 row tiles fit, 27 do not), 8192
+// 313 / 335, 9000 364 / 343, 12288 473 / 393, 65536 2680 / 1260; d = 1024, 6144 rows 376 / 421, 6700 478 / 373, 8192
+// 497 / 487.  V = 4096, d = 512: 4096 rows 49 / 44, 8192 80 / 57.
 bool sharing_pays(const as_ctx *ctx, const as_model *m, int64_t rows, int32_t T)
 {
     if (T < 2 || ctx->gemm_shape == 1 || ctx->num_cus < 8 || !mfma_applies(m) || m->d < 2 * PK ||
         (int64_t)m->V * m->d * 2 >= (1LL << 32))
         return false;
     const double tokens = (double)m->V * (1.0 - exp(-(double)rows / (double)m->V));
-    return ((double)rows - tokens) * (double)m->V * (double)m->d * 2.0 > 20e-6 * 1e15;
+    const int W = ctx->num_cus / 8, gm = persistent_gm(ctx);
+    const int64_t n_blocks = ((int64_t)m->V + PN - 1) / PN;
+    const int64_t spared = tile_rounds((rows + PM - 1) / PM, n_blocks, W, gm) -
+                           tile_rounds(((int64_t)tokens + PM) / PM, n_blocks, W, gm);
+    const double work = ((double)rows - tokens) * (double)m->V * (double)m->d * 2.0 / 1e15;
+    const double tiles = (double)spared * ((double)m->d / PK * 1.72e-6 + 2.3e-6);
+    return 0.5 * (work + tiles) > 20e-6;
 }
 
 as_status launch_share_clear(as_ctx *ctx, const RowShare &s, int32_t T)

@@ -16,7 +16,9 @@ def test_rows_of_a_decode_with_and_without_sharing():
 
 
 def test_sharing_pays_for_wide_lattices_only():
-    assert bench.rows_shared(32128, 512, 65536, 16, "bf16")
-    assert not bench.rows_shared(32128, 512, 1024, 64, "bf16")
-    assert not bench.rows_shared(32128, 512, 65536, 1, "bf16")
-    assert not bench.rows_shared(32128, 512, 65536, 16, "f32")
+    def shared(V, d, R, T=16, wdt="bf16"):
+        return bench.rows_shared(V, d, R, T, wdt, 256)
+    assert shared(32128, 512, 65536) and shared(32128, 512, 6700) and shared(4096, 512, 12288)
+    assert not shared(32128, 512, 1024) and not shared(32128, 512, 65536, T=1) and not shared(32128, 512, 65536, wdt="f32")
+    # the rows in use leave workers of the product without a row tile
+    assert not shared(32128, 512, 8192) and not shared(32128, 1024, 6144)

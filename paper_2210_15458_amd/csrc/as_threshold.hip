@@ -1052,12 +1052,15 @@ __global__ __launch_bounds__(kThreads) void threshold_resident_kernel(const void
 
 // ------------------------------------------------------------ streamed path
 //
-// Top-k with k above half the thread count on long rows, many of them: the method of the resident kernel with every
-// visit of the row a pass over memory, four pieces per thread in flight.  Three passes (maximum, count per coarse
-// bin, the logits of the bin that holds the k-th), and two more for the nucleus after it (mass per coarse bin, the
-// logits of the bin where it closes).  Same keys, same fixed-point masses, same fall-back as the other two kernels,
-// so the same threshold.
-template <int DT, bool HAS_P>
+// Rows of any length and stride: the method of the resident kernel with every visit of the row a pass over memory, four
+// pieces per thread in flight.  Top-k with k up to half the thread count takes two passes (thread maxima, then the
+// logits at or above the bound they give), any larger k three (maximum, count per coarse bin, the logits of the bin that
+// holds the k-th), the nucleus alone three (maximum, mass per coarse bin, the logits of the bin where the nucleus
+// closes); the nucleus after top-k works on the candidate table or takes two passes more.  Same keys, same fixed-point
+// masses, same fall-back as the other two kernels, so the same threshold.
+// KMODE 0: no top-k; 1: bound from the thread maxima (k at most half the thread count); 2: any k, by counts per
+// coarse bin, the way the nucleus goes by mass per coarse bin.
+template <int DT, int KMODE, bool HAS_P>
 __global__ __launch_bounds__(kThreads) void threshold_stream_kernel(const void *logits, int64_t ld, int32_t V,
                                                                     const uint8_t *finished_in,
                                                                     const int32_t *row_ids, float temp,
@@ -1110,9 +1113,29 @@ __global__ __launch_bounds__(kThreads) void threshold_stream_kernel(const void *
             }
         }
     };
+    auto umax = [](uint32_t a, uint32_t b) { return a > b ? a : b; };
+
     uint32_t thr_key = 0;
     bool fall = false;
     uint32_t ncand = 0;
+
+    if (KMODE == 1) {
+        // the k-th largest of the thread maxima bounds the k-th largest logit from below
+        uint32_t tmax = 0;
+        sweep([&](uint32_t key, float) __attribute__((always_inline)) { tmax = umax(tmax, key); });
+        const uint32_t lkey = bound_from_thread_maxima(sh, tmax, top_k);
+        sweep([&](uint32_t key, float) __attribute__((always_inline)) {
+            if (key >= lkey) {
+                const uint32_t i = atomicAdd(&sh.ncand, 1u);
+                if (i < (uint32_t)kCandCap) sh.ckey[i] = key;
+            }
+        });
+        __syncthreads();
+        ncand = sh.ncand;
+        if (ncand > (uint32_t)kCandCap) fall = true;
+        else thr_key = kth_of_candidates(sh, ncand, top_k);
+        __syncthreads();
+    }
 
     const float k = 1.44269504088896340736f / temp;
 
@@ -1174,12 +1197,21 @@ __global__ __launch_bounds__(kThreads) void threshold_stream_kernel(const void *
         thr_key = closing_group(sh, ncand, before, need, thr_key);
     };
 
-    // count the logits per coarse bin from the top until k are reached
-    const float nr = row_reference();
-    select(nr, [](uint32_t, float) { return 1ull; }, [&](unsigned long long) { return (double)top_k; });
-    if (HAS_P && !fall) {
-        const uint32_t floor_key = thr_key;
-        select(nr, [&](uint32_t key, float x) { return key >= floor_key ? mass_q(x, k, nr) : 0ull; },
+    if (KMODE == 2) {
+        // count the logits per coarse bin from the top until k are reached
+        const float nr = row_reference();
+        select(nr, [](uint32_t, float) { return 1ull; }, [&](unsigned long long) { return (double)top_k; });
+        if (HAS_P && !fall) {
+            const uint32_t floor_key = thr_key;
+            select(nr, [&](uint32_t key, float x) { return key >= floor_key ? mass_q(x, k, nr) : 0ull; },
+                   [&](unsigned long long total) { return (double)top_p * (double)total; });
+        }
+    } else if (KMODE == 1) {
+        // every survivor of top-k is in the candidate table
+        if (HAS_P && !fall) thr_key = nucleus_on_candidates<K>(sh, ncand, thr_key, k, top_p);
+    } else {
+        const float nr = row_reference();
+        select(nr, [&](uint32_t, float x) { return mass_q(x, k, nr); },
                [&](unsigned long long total) { return (double)top_p * (double)total; });
     }
 
@@ -1894,6 +1926,23 @@ void launch_resident(as_ctx *ctx, const void *logits, int64_t rows, int64_t ld, 
                finished_in, row_ids, temp, top_k, top_p, thr_out, StepArgs{});
 }
 
+template <int DT>
+void launch_streamed(as_ctx *ctx, const void *logits, int64_t rows, int64_t ld, const uint8_t *finished_in,
+                     const int32_t *row_ids, float temp, int32_t top_k, float top_p, float *thr_out, bool has_k,
+                     bool has_p)
+{
+    const dim3 grid((unsigned)rows), block(kThreads);
+    auto go = [&](auto kernel) {
+        launch(ctx, kKernelThreshold, kernel, grid, block, 0, logits, ld, ctx->V, finished_in, row_ids, temp, top_k, top_p,
+               thr_out);
+    };
+    if (!has_k) go(threshold_stream_kernel<DT, 0, true>);
+    else if (top_k <= kThreads / 2 && has_p) go(threshold_stream_kernel<DT, 1, true>);
+    else if (top_k <= kThreads / 2) go(threshold_stream_kernel<DT, 1, false>);
+    else if (has_p) go(threshold_stream_kernel<DT, 2, true>);
+    else go(threshold_stream_kernel<DT, 2, false>);
+}
+
 // Rows that the resident kernel takes (whole aligned pieces, at most 32768 logits, k at most 128), and takes faster
 // than the wide one: several of its 256-thread blocks share a compute unit, so it wins once there are more rows
 // than compute units (bf16, 300 rows of 20003: nucleus 23 us against 47, top-k 40 15.5 against 21; 2000 rows of
@@ -1919,6 +1968,27 @@ static bool streamed_pays(const as_ctx *ctx, int64_t rows, bool has_k, int32_t t
 {
     return has_k && top_k > kThreads / 2 && rows > (int64_t)ctx->num_cus &&
            (int64_t)ctx->V * (ctx->dtype == AS_BF16 ? 2 : 4) > 131072;
+}
+
+// Where only the threshold is wanted (the encode direction) the wide kernel's chunk sums are for nothing, and the two
+// others keep more of the rows.  Nucleus alone, threshold and interval step, us: the resident kernel on rows that it
+// can take above 16384 logits (16384 itself is even), in bf16 with any number of them (1 row of 32128: 16.8 against
+// 18.8, 256 20.5 against 22.6), in fp32 with more than compute units (64 rows of 32128 24.0 against 22.0; 300 37.4, 39.0;
+// 6000 261, 338).
+static bool threshold_resident_pays(const as_ctx *ctx, int64_t rows, bool has_k)
+{
+    return !has_k && ctx->V > 16384 && (ctx->dtype == AS_BF16 || rows > (int64_t)ctx->num_cus);
+}
+// ... the streamed kernel on other rows of up to 12288 bf16 logits (1024 rows: of 3001 15.3 against 20.5, 9001 23.8, 28.5,
+// 12001 27.5, 31.6; few rows of 20003 are 10 % faster in the wide kernel) or 10240 fp32 ones (1024 rows: of 9001 26.3,
+// 30.1, 12001 33.2, 35.1, but 6000 of those 157, 148); with many bf16 rows up to 36864 (6000 of 33001 271 against 301;
+// 40000 is even); and top-k up to 128 on many fp32 rows just too long for two of the wide kernel's blocks on a unit
+// (6000 of 33001, k = 100: 361 against 421; 40000 is even).
+static bool threshold_streamed_pays(const as_ctx *ctx, int64_t rows, bool has_k, int32_t top_k)
+{
+    const bool half = ctx->dtype == AS_BF16, lots = rows > 2 * (int64_t)ctx->num_cus;
+    if (has_k) return !half && lots && top_k <= kThreads / 2 && ctx->V > 32768 && ctx->V <= 36864;
+    return ctx->V <= (half ? 12288 : 10240) || (half && lots && ctx->V <= 36864);
 }
 
 // top-k and the nucleus and the sampling step in one launch; false where only the radix select and the resident
@@ -1999,25 +2069,22 @@ as_status launch_threshold(as_ctx *ctx, const void *logits, int64_t rows, int64_
     const bool resident = ctx->thr_path != 1 && (has_k || has_p) && ctx->V <= 32768 &&
                           reinterpret_cast<uintptr_t>(logits) % 16 == 0 && (ld * esz) % 16 == 0 &&
                           (!has_k || top_k <= kThreads / 2);
+    const bool by_resident = resident_pays(ctx, logits, rows, ld, has_k, top_k) ||
+                             (resident && threshold_resident_pays(ctx, rows, has_k));
+    const bool by_streamed = streamed_pays(ctx, rows, has_k, top_k) ||
+                             (!resident && threshold_streamed_pays(ctx, rows, has_k, top_k));
     if (ctx->thr_path == 3 || (ctx->thr_path == 2 && !resident) ||
-        (ctx->thr_path == 0 && !resident_pays(ctx, logits, rows, ld, has_k, top_k) &&
-         !streamed_pays(ctx, rows, has_k, top_k))) {
+        (ctx->thr_path == 0 && !by_resident && !by_streamed)) {
         StepArgs a{};
         a.logits = logits; a.rows = rows; a.ld = ld; a.V = ctx->V; a.dtype = ctx->dtype; a.temp = temp;
         a.k = 1.44269504088896340736f / temp; a.finished_in = finished_in; a.row_ids = row_ids;
         return launch_wide(ctx, a, has_k ? top_k : 0, has_p ? top_p : 1.f, thr_out);
     }
-    const bool streamed = !resident && ctx->thr_path == 0;
-    if (streamed) {
-        const dim3 grid((unsigned)rows), block(kThreads);
+    if (ctx->thr_path == 0 && !by_resident) {
         if (ctx->dtype == AS_BF16)
-            launch(ctx, kKernelThreshold,
-                   has_p ? threshold_stream_kernel<AS_BF16, true> : threshold_stream_kernel<AS_BF16, false>, grid, block,
-                   0, logits, ld, ctx->V, finished_in, row_ids, temp, top_k, top_p, thr_out);
+            launch_streamed<AS_BF16>(ctx, logits, rows, ld, finished_in, row_ids, temp, top_k, top_p, thr_out, has_k, has_p);
         else
-            launch(ctx, kKernelThreshold,
-                   has_p ? threshold_stream_kernel<AS_F32, true> : threshold_stream_kernel<AS_F32, false>, grid, block,
-                   0, logits, ld, ctx->V, finished_in, row_ids, temp, top_k, top_p, thr_out);
+            launch_streamed<AS_F32>(ctx, logits, rows, ld, finished_in, row_ids, temp, top_k, top_p, thr_out, has_k, has_p);
     } else if (resident) {
         if (ctx->dtype == AS_BF16)
             launch_resident<AS_BF16>(ctx, logits, rows, ld, finished_in, row_ids, temp, top_k, top_p, thr_out, has_k,

@@ -65,8 +65,10 @@ def test_largest_logits_past_the_first_ones(gap, dtype):
         _against_oracle(x, dtype, codes, top_p, f"gap={gap} {dtype} p={top_p}")
 
 
-# (V, rows): the forms with 256, 512 and 1024 threads, one tile and several, and rows that start off 16 bytes
-SAME = [(4096, 8), (4099, 8), (9001, 600), (20003, 300), (40000, 6), (140001, 3), (70001, 260)]
+# (V, rows): the forms with 256, 512 and 1024 threads, one tile and several, and rows that start off 16 bytes; by the
+# library's own choice also the kernels that hold a row or stream it (32128 aligned, odd ones up to 33001)
+SAME = [(4096, 8), (4099, 8), (9001, 600), (20003, 300), (32128, 8), (32128, 300), (33001, 520), (40000, 6), (140001, 3),
+        (70001, 260)]
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])

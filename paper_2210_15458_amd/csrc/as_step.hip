@@ -84,7 +84,7 @@ struct SumRef {
 // fast kernel: rows start on 16 bytes and are padded to whole vectors (the last vector of a row may be partial)
 // ===========================================================================
 // PARTIAL: the row's length is not a whole number of vectors (its last vector is padded out by the row stride)
-template <int DT, int NW, int ITERS, int OCC, bool HAS_THR, bool PARTIAL>
+template <int DT, int NW, int ITERS, int OCC, bool HAS_THR, bool PARTIAL, bool ORDERED = false>
 __global__ __launch_bounds__(NW * 64, OCC) void step_kernel(StepArgs a, int ntiles)
 {
     using T = typename Elem<DT>::T;
@@ -104,7 +104,7 @@ __global__ __launch_bounds__(NW * 64, OCC) void step_kernel(StepArgs a, int ntil
     float *ent_ref = ent_sum + nent;       // [nent]  integer reference of the share
 
     int64_t r;
-    if (!block_row(a, r)) return;
+    if (!block_row<ORDERED>(a, r)) return;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
@@ -460,7 +460,7 @@ __global__ __launch_bounds__(NW * 64, OCC) void step_kernel(StepArgs a, int ntil
 //   * the wave that owns that chunk has the lane sums of its chunks in registers: one more scan finds the lane,
 //     and that lane the element.
 // ===========================================================================
-template <int DT, bool HAS_THR, bool NT>
+template <int DT, bool HAS_THR, bool NT, bool ORDERED = false>
 __global__ __launch_bounds__(256, 4) void step_tile_kernel(StepArgs a)
 {
     using T = typename Elem<DT>::T;
@@ -473,7 +473,7 @@ __global__ __launch_bounds__(256, 4) void step_tile_kernel(StepArgs a)
     __shared__ GenericScratch gen;
 
     int64_t r;
-    if (!block_row(a, r)) return;
+    if (!block_row<ORDERED>(a, r)) return;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
@@ -598,19 +598,24 @@ as_status launch_shape(as_ctx *ctx, const StepArgs &a)
     const int ntiles = (int)((nvec + tile - 1) / tile);
     const size_t lds = ((size_t)NW * ITERS * 64 + (size_t)ntiles * NW * 2) * sizeof(float);
     if (lds > 60 * 1024) return fail(ctx, AS_ERR_UNSUPPORTED, "vocabulary too large for the share table");
-    if (whole && ntiles == 1 && NW == 4 && ITERS == 16 && ctx->step_shape == 0 && a.k <= kTileMaxScale)
-    {
-        if (stream_rows(a.src_rows ? a.src_rows : a.rows, a.ld, sizeof(typename Elem<DT>::T)))
-            launch(ctx, kKernelStep, step_tile_kernel<DT, HAS_THR, true>, dim3(step_blocks(a)), dim3(256), 0, a);
-        else
-            launch(ctx, kKernelStep, step_tile_kernel<DT, HAS_THR, false>, dim3(step_blocks(a)), dim3(256), 0, a);
+    const dim3 grid((unsigned)a.rows), block(NW * 64);
+    const bool one_tile = whole && ntiles == 1 && NW == 4 && ITERS == 16 && ctx->step_shape == 0 && a.k <= kTileMaxScale;
+    const bool nt = stream_rows(a.src_rows ? a.src_rows : a.rows, a.ld, sizeof(typename Elem<DT>::T));
+    if constexpr (!HAS_THR && NW == 4 && ITERS == 16) {
+        // (an order comes with decodes whose logits are streamed; it is a matter of locality only)
+        if (a.order != nullptr && (nt || !one_tile)) {
+            const dim3 runs((unsigned)((a.rows + 7) / 8 * 8));
+            if (one_tile) launch(ctx, kKernelStep, step_tile_kernel<DT, false, true, true>, runs, block, 0, a);
+            else if (!whole) launch(ctx, kKernelStep, step_kernel<DT, NW, ITERS, OCC, false, true, true>, runs, block, lds, a, ntiles);
+            else launch(ctx, kKernelStep, step_kernel<DT, NW, ITERS, OCC, false, false, true>, runs, block, lds, a, ntiles);
+            AS_HIP_TRY(ctx, hipGetLastError());
+            return AS_OK;
+        }
     }
-    else if (!whole)
-        launch(ctx, kKernelStep, step_kernel<DT, NW, ITERS, OCC, HAS_THR, true>, dim3(step_blocks(a)), dim3(NW * 64),
-               lds, a, ntiles);
-    else
-        launch(ctx, kKernelStep, step_kernel<DT, NW, ITERS, OCC, HAS_THR, false>, dim3(step_blocks(a)), dim3(NW * 64),
-               lds, a, ntiles);
+    if (one_tile && nt) launch(ctx, kKernelStep, step_tile_kernel<DT, HAS_THR, true>, grid, block, 0, a);
+    else if (one_tile) launch(ctx, kKernelStep, step_tile_kernel<DT, HAS_THR, false>, grid, block, 0, a);
+    else if (!whole) launch(ctx, kKernelStep, step_kernel<DT, NW, ITERS, OCC, HAS_THR, true>, grid, block, lds, a, ntiles);
+    else launch(ctx, kKernelStep, step_kernel<DT, NW, ITERS, OCC, HAS_THR, false>, grid, block, lds, a, ntiles);
     AS_HIP_TRY(ctx, hipGetLastError());
     return AS_OK;
 }

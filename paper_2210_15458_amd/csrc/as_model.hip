@@ -1056,9 +1056,38 @@ __global__ __launch_bounds__(256) void bigram_gemm_vec(const WT *__restrict__ E,
     }
 }
 
+// The plain form of the same chain, one thread per logit, operands from the caches at every k: what is left to it are
+// products so small that the tiled kernel's barriers, and the microsecond that its launch takes longer to follow and to
+// be followed, cost more.  us a decode step, plain / tiled: 27 rows of 563, fp32, rank 11 9.5 / 10.4; 64 of 1001 9.6 /
+// 10.7, 128 of 2003 12.7 / 11.1; rank 16 is even (64 of 1001 10.7 / 10.7), rank 24 lost (11.3 / 10.9).  bf16 rows are
+// half as long: 64 of 1001, rank 33 11.0 / 12.0, rank 50 12.2 / 12.6, rank 72 19.6 / 13.5; 64 of 2003, rank 33 13.9 / 12.2.
+template <class WT, class OutT>
+__global__ __launch_bounds__(256) void bigram_dot(const WT *__restrict__ E, const WT *__restrict__ Ut,
+                                                  const int32_t *__restrict__ prev, int64_t R, int32_t V,
+                                                  int32_t d, float alpha, OutT *__restrict__ C, int64_t ldc)
+{
+    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (idx >= R * V) return;
+    const int64_t r = idx / V, v = idx % V;
+    const WT *a = E + (int64_t)clamp_token(prev[r], V) * d, *b = Ut + v * d;
+    float acc = 0.f;
+    for (int k = 0; k < d; ++k) acc = fmaf(widen(a[k]), widen(b[k]), acc);
+    C[r * ldc + v] = to_out<OutT>(acc * alpha);
+}
+
+static bool dot_pays(const as_model *m, int64_t rows)
+{
+    return rows * m->V <= 65536 && m->d <= (m->wdtype == AS_BF16 ? 56 : 12);
+}
+
 template <class WT, class OutT>
 void launch_vec(as_ctx *ctx, const as_model *m, const int32_t *prev, int64_t rows, void *out, int64_t ld, float alpha)
 {
+    if (dot_pays(m, rows)) {
+        launch(ctx, kKernelLogits, bigram_dot<WT, OutT>, dim3((unsigned)((rows * m->V + 255) / 256)), dim3(256), 0,
+               (const WT *)m->E, (const WT *)m->Ut, prev, rows, m->V, m->d, alpha, (OutT *)out, ld);
+        return;
+    }
     // 128 x 128 tiles do twice the products per LDS byte of 64 x 64 ones; they pay once there are enough of
     // them for two blocks on every CU
     const dim3 big((unsigned)((rows + 127) / 128), (unsigned)((m->V + 127) / 128));

@@ -1058,9 +1058,7 @@ __global__ __launch_bounds__(256) void bigram_gemm_vec(const WT *__restrict__ E,
 
 // The plain form of the same chain, one thread per logit, operands from the caches at every k: what is left to it are
 // products so small that the tiled kernel's barriers, and the microsecond that its launch takes longer to follow and to
-// be followed, cost more.  us a decode step, plain / tiled: 27 rows of 563, fp32, rank 11 9.5 / 10.4; 64 of 1001 9.6 /
-// 10.7, 128 of 2003 12.7 / 11.1; rank 16 is even (64 of 1001 10.7 / 10.7), rank 24 lost (11.3 / 10.9).  bf16 rows are
-// half as long: 64 of 1001, rank 33 11.0 / 12.0, rank 50 12.2 / 12.6, rank 72 19.6 / 13.5; 64 of 2003, rank 33 13.9 / 12.2.
+// be followed, cost more (dot_pays).
 template <class WT, class OutT>
 __global__ __launch_bounds__(256) void bigram_dot(const WT *__restrict__ E, const WT *__restrict__ Ut,
                                                   const int32_t *__restrict__ prev, int64_t R, int32_t V,
@@ -1075,9 +1073,16 @@ __global__ __launch_bounds__(256) void bigram_dot(const WT *__restrict__ E, cons
     C[r * ldc + v] = to_out<OutT>(acc * alpha);
 }
 
+// us a decode step, plain / tiled.  fp32: 27 rows of 563, rank 11 9.5 / 10.4; 64 of 1001 9.6 / 10.7, but 128 of 2003 12.7 /
+// 11.1; 32 rows of 101 to 1001 0.88 to 0.94 of the time up to rank 26, 1.03 to 1.08 from 28 (up to 128 columns 0.90 to
+// 0.98 up to 38); ranks of a multiple of 8, whose rows meet in the cache, are even at 16 and 24 and lose 10 % at 32.
+// bf16, rows half as long: 64 of 1001, rank 33 11.0 / 12.0, rank 50 12.2 / 12.6, rank 72 19.6 / 13.5; 64 of 2003, rank
+// 33 13.9 / 12.2.
 static bool dot_pays(const as_model *m, int64_t rows)
 {
-    return rows * m->V <= 65536 && m->d <= (m->wdtype == AS_BF16 ? 56 : 12);
+    if (rows * m->V > 65536) return false;
+    if (m->wdtype == AS_BF16) return m->d <= 56;
+    return m->d <= (m->V <= 128 ? 38 : 26) && (m->d <= 16 || m->d % 8 != 0);
 }
 
 template <class WT, class OutT>

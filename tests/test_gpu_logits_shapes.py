@@ -85,11 +85,11 @@ def test_group_masses_of_few_rows(V, d, R):
     assert np.array_equal(res[0], res[1])
 
 
-# the plain kernel up to its line (65536 logits; rank 12 with fp32 weights, 56 with bf16 ones) and the tiled one past it;
-# where all rows are past it, single rows are not
-_PLAIN = [(1024, 12, "f32", "bf16", 64), (1024, 12, "f32", "f32", 65), (1024, 13, "f32", "f32", 64),
-          (8200, 11, "f32", "f32", 33), (1, 1, "f32", "f32", 1), (563, 33, "bf16", "f32", 116),
-          (2003, 56, "bf16", "bf16", 40), (700, 57, "bf16", "f32", 9)]
+# the plain kernel up to its line (65536 logits; rank 26 with fp32 weights, 38 up to 128 columns, 56 with bf16 ones) and the
+# tiled one past it; where all rows are past it, single rows are not
+_PLAIN = [(1024, 12, "f32", "bf16", 64), (1024, 26, "f32", "f32", 65), (1024, 27, "f32", "f32", 64),
+          (128, 38, "f32", "bf16", 512), (128, 32, "f32", "f32", 3), (8200, 11, "f32", "f32", 33), (1, 1, "f32", "f32", 1),
+          (563, 33, "bf16", "f32", 116), (2003, 56, "bf16", "bf16", 40), (700, 57, "bf16", "f32", 9)]
 
 
 @pytest.mark.parametrize("V,d,wdt,ldt,R", _PLAIN)

@@ -240,8 +240,8 @@ as_status as_lattice(as_ctx *ctx, const float *u, int32_t B, int32_t N,
  *   U       DEVICE [d, V] row-major, wdtype; read once here (the model keeps
  *           its own K-contiguous copy) and not needed afterwards
  *   d       rank, >= 1.  AS_BF16 weights with d a multiple of 64 and a 16-byte
- *           aligned E run on the MFMA kernel; anything else on a plain
- *           dot-product kernel meant for small models only
+ *           aligned E run on the MFMA kernels; anything else on the vector
+ *           units (one fp32 fused-multiply-add chain per logit)
  * The call enqueues a re-layout kernel on the default stream and waits for it.
  */
 as_status as_model_create_bigram(as_model **out, const void *E, const void *U,

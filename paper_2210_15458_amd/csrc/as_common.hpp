@@ -51,11 +51,12 @@ struct as_ctx {
     int32_t *rid = nullptr;        // [max_rows] the caller's row_ids brought into range
     // decode workspace (grown on demand by as_decode)
     as::DeviceBuf logits;          // [rows, ld]
-    as::DeviceBuf state;           // codes f32[rows] | prev i32[rows] | finished u8[rows]
+    as::DeviceBuf state;           // codes f32[rows] | prev i32[rows] | tables of shared rows, if any | finished u8[rows]
     as::Profile prof;
     int step_shape = 0;            // work-group shape of the sampling kernel (tuning knob, 0 = default)
-    int gemm_shape = 0;            // logits kernel choice (tuning knob: 0 = persistent where it applies, 1 = tile kernel)
-    int thr_path = 0;              // keep-threshold kernel choice (tuning knob: 0 = resident where it applies, 1 = radix)
+    // choices of a kernel (tuning knobs, 0 = by the rules on sizes)
+    int gemm_shape = 0;            // logits: 1 = tile kernel, 2 = persistent also for few rows
+    int thr_path = 0;              // truncation: 1 = radix select, 2 = resident where the row fits, 3 = wide for every row
     int gemm_gm = 0;               // logits kernel, many row tiles: workers of an XCD along the rows (tuning knob: 0 = default)
     int num_cus = 0;               // compute units of the device (the persistent logits kernel runs one block on each)
     std::string err;

@@ -1943,13 +1943,14 @@ void launch_streamed(as_ctx *ctx, const void *logits, int64_t rows, int64_t ld, 
     else go(threshold_stream_kernel<DT, 2, false>);
 }
 
-// Rows that the resident kernel takes (whole aligned pieces, at most 32768 logits, k at most 128), and takes faster
-// than the wide one: several of its 256-thread blocks share a compute unit, so it wins once there are more rows
-// than compute units (bf16, 300 rows of 20003: nucleus 23 us against 47, top-k 40 15.5 against 21; 2000 rows of
-// 32003 fp32 with top-k 40: 56 against 71).  The wide kernel wins with fewer (16 rows of 32003: 17 us against 20,
-// fp32 16.4 against 25), on short rows, where the resident one's lanes idle (2000 rows of 3001: 24 to 47 us against 99
-// to 283), on the fp32 nucleus (300 rows of 32003: 25 against 37) and with many fp32 rows of up to 16384 logits (2000
-// of 9001, top-k 40: 29 against 41).
+// Rows that the resident kernel takes with the sampling step (whole aligned pieces, at most 32768 logits, k at most 128)
+// in place of the wide one: several of its 256-thread blocks share a compute unit, so only with more rows than compute
+// units, and not where the wide kernel was always faster: fewer rows (us, resident / wide: 16 rows of 32003 bf16
+// nucleus 18.9 / 18.1, fp32 24.2 / 17.4), short ones, where the resident one's lanes idle (2000 rows of 3001: 56 to 282 /
+// 21 to 33), the fp32 nucleus (300 rows of 32003: 36 / 27), many fp32 rows of up to 16384 logits (2000 of 9001, top-k
+// 40: 40 / 27).  Within the line, as both kernels are now: the bf16 nucleus near 32768 (2000 rows of 32003: 66 / 75; of
+// 20003 62 / 58, of 9001 57 / 39), top-k on many long fp32 rows (600 of 20003, k = 40: 19.5 / 22.0; 2000 of 32003 53 /
+// 54, k = 100 with p = 0.9 82 / 73), bf16 top-k about even (2000 of 32003, k = 40 37 / 36; 300 of 20003 14.4 / 12.5).
 static bool resident_pays(const as_ctx *ctx, const void *logits, int64_t rows, int64_t ld, bool has_k, int32_t top_k)
 {
     const bool half = ctx->dtype == AS_BF16;
@@ -1961,9 +1962,11 @@ static bool resident_pays(const as_ctx *ctx, const void *logits, int64_t rows, i
     return half || (has_k && (ctx->V > 16384 || rows <= 2 * (int64_t)ctx->num_cus));
 }
 
-// What is left to the streamed kernel: k above 128 on rows of more than 128 KB, with more rows than compute units (1000
-// rows of 100000 fp32, k = 300: 257 us against 449 in the wide kernel, whose passes over such a row each wait for
-// one block's loads; one row of 256000 bf16 157 against 96).
+// What goes to the streamed kernel, and the step kernel after it, whole steps included: k above 128 on rows of more than
+// 128 KB, with more rows than compute units; the wide kernel's passes over such a row each wait for one block's loads
+// (us, streamed / wide, k = 300: 1000 rows of 100000 fp32 260 / 295, of 256000 bf16 386 / 446; near the line the wide
+// one is ahead: 1000 rows of 50000 fp32 125 / 82, of 100000 bf16 152 / 120; with p = 0.8 as well 386 / 386 and 612 / 618 at
+// the first two).  One row of 256000 bf16 is 157 / 83.
 static bool streamed_pays(const as_ctx *ctx, int64_t rows, bool has_k, int32_t top_k)
 {
     return has_k && top_k > kThreads / 2 && rows > (int64_t)ctx->num_cus &&
@@ -1973,7 +1976,7 @@ static bool streamed_pays(const as_ctx *ctx, int64_t rows, bool has_k, int32_t t
 // Where only the threshold is wanted (the encode direction) the wide kernel's chunk sums are for nothing, and the two
 // others keep more of the rows.  Nucleus alone, threshold and interval step, us: the resident kernel on rows that it
 // can take above 16384 logits (16384 itself is even), in bf16 with any number of them (1 row of 32128: 16.8 against
-// 18.8, 256 20.5 against 22.6), in fp32 with more than compute units (64 rows of 32128 24.0 against 22.0; 300 37.4, 39.0;
+// 18.8, 256 20.5 against 22.6), in fp32 with more than compute units (64 rows of 32128 30.4 against 28.0; 300 38.0, 38.7;
 // 6000 261, 338).
 static bool threshold_resident_pays(const as_ctx *ctx, int64_t rows, bool has_k)
 {
@@ -2004,7 +2007,7 @@ bool launch_topk_step(as_ctx *ctx, const StepArgs &args, int32_t top_k, float to
                           reinterpret_cast<uintptr_t>(a.logits) % 16 == 0 && (a.ld * esz) % 16 == 0 &&
                           (has_k ? top_k <= kTileTopK : a.k <= kTileMaxScale);
     // (short rows leave three of the single-tile kernels' four waves without work: with many of them the wide
-    // kernel is faster, 8192 rows of 4096 top-k 40 92 us against 207)
+    // kernel is faster, 8192 rows of 4096 top-k 40 61 us against 207)
     const bool tile = one_tile && !(ctx->V <= 8192 && a.rows > 2 * (int64_t)ctx->num_cus);
     if (ctx->thr_path == 3 ||
         (ctx->thr_path == 0 && !tile && !resident_pays(ctx, a.logits, a.rows, a.ld, has_k, top_k) &&

@@ -1032,12 +1032,12 @@ void launch_form(as_ctx *ctx, int kid, const StepArgs &a, int32_t top_k, float t
 }
 
 // Threads and pieces a thread by the row's pieces of 16 bytes and the number of rows.  With a row per compute unit or
-// fewer, 1024 threads finish it soonest (one row of 50257 bf16: nucleus 20 us, top-k 40 12 us).  With more, smaller
+// fewer, 1024 threads finish it soonest (one row of 50257 bf16: nucleus 21 us, top-k 40 11 us).  With more, smaller
 // blocks that share a unit overlap each other's loads and tails: two blocks of 512 where two fit (nucleus, bf16: 300 rows
 // of 33001 27 us, as blocks of 1024 38; 6439 of them 276, 476; 1000 of 65001 70, 96; fp32 2500 of 33001, which go
 // tile by tile, 129, 200), and with many rows that 256 threads hold, those (nucleus, bf16, 6439 rows: of 9001 108
-// us with 256 x 8, 143 with 512 x 4; of 20001 152 with 256 x 16, 174 with 512 x 8; top-k 40, 2500 of 20003 43, with 512
-// threads 67).
+// us with 256 x 8, 143 with 512 x 4; of 20001 152 with 256 x 16, 174 with 512 x 8; top-k 40, 2500 of 20003 41, with 512
+// threads 55).
 template <int DT, bool TOPK>
 void launch_type(as_ctx *ctx, int kid, const StepArgs &a, int32_t top_k, float top_p, float *thr_out)
 {

@@ -110,6 +110,14 @@ def rows_shared(V, d, R, T, wdt, cus):
     return 0.5 * ((R - tokens) * V * d * 2.0 / 1e15 + spared * (d / 64 * 1.72e-6 + 2.3e-6)) > 20e-6
 
 
+def conditioned_tokens(seqs, prompts, eos):
+    """Distinct tokens that the positions of sequences [R, T] condition on, up to and including each one's EOS."""
+    R, T = seqs.shape
+    prev = np.concatenate([np.repeat(prompts, R // len(prompts))[:, None], seqs[:, :-1]], axis=1)
+    running = np.cumsum(prev[:, 1:] == eos, axis=1) == 0 if eos >= 0 else np.ones((R, T - 1), bool)
+    return int(np.unique(np.concatenate([prev[:, 0], prev[:, 1:][running]])).size)
+
+
 def step_counts(tokens, eos, prompts, shared):
     """Per step of a decode, averaged over its steps: rows still running (`active`), logits rows that are computed, and
     logits rows that the rows still running read (`fetched`, each once).  The first step has one logits row per
@@ -415,11 +423,14 @@ def main():
     iv_ms, iv_n, _ = ctx.profile_read(3)
     ctx.profile_read(1); ctx.profile_read(2)
     ctx.profile(False)
-    iv_us = iv_ms / max(iv_n, 1) * 1e3
+    # the logits rows that an encode cannot do without: one per token that a position still running conditions on
+    seqs = tokens.cpu().numpy().reshape(R, T)
+    rows = conditioned_tokens(seqs, prompts.cpu().numpy(), eos)
+    iv_us = iv_ms / 3 * 1e3
     out["encode"] = {
-        "kernel": "interval_tile_kernel (the single-tile sampling kernel with a lookup of the given token in place of the search), inside as_encode",
-        "avg_launch_us": iv_us, "launches": iv_n, "bound": "hbm",
-        "achieved": bytes_per_launch / (iv_us * 1e-6) / 1e9 if iv_n else None,
+        "kernel": "row_sums_kernel and row_lookup_kernel (sums of each logits row in use, then a wave per position), inside as_encode",
+        "us_per_encode": iv_us, "launches": iv_n, "bound": "hbm", "logits_rows": rows,
+        "achieved": rows * V * esz / (iv_us * 1e-6) / 1e9 if iv_n else None,
         "peak": HBM_PEAK_GBS, "unit": "GB/s",
         "code_steps_per_s_with_dispatch_events": code_steps / args.steps * 3 / (e1 - e0)}
     if out["encode"]["achieved"]:

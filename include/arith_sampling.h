@@ -373,13 +373,16 @@ as_status as_interval_step(as_ctx *ctx, const void *logits, int64_t rows, int64_
 
 /*
  * Encode direction, whole sequences under the bigram model (Sec. 4.1): the interval
- * [lo, lo + width) of each of the B*N token sequences, the inverse of as_decode.  Per
- * step: logits for the previous token (the prompt's start token first), optional keep
- * threshold, as_interval_step on column t of `tokens`; EOS is sticky as in as_decode.
+ * [lo, lo + width) of each of the B*N token sequences, the inverse of as_decode.  What a
+ * loop of steps gives: logits for the previous token (the prompt's start token first),
+ * optional keep threshold, as_interval_step on column t of `tokens`; EOS is sticky as in
+ * as_decode.  All tokens are known, so the positions are taken together, not step by step.
  *   prompts     DEVICE int32[B]
  *   tokens      DEVICE int32[B, N, T], as written by as_decode
  *   lo_out, width_out   DEVICE double[B*N]
- * Uses (and may grow) the context's decode workspace.
+ * Uses (and may grow) the context's decode workspace: logits of 256 to 8192 rows (fewer if
+ * there are fewer positions; up to 256 MB, or 1024 rows of up to 1 MB, or 256 rows) and at
+ * most 28 bytes a position of 2^19 (or of one column) and 12 a token of the vocabulary.
  */
 as_status as_encode(as_ctx *ctx, const as_model *model, const int32_t *prompts,
                     int32_t B, int32_t N, int32_t T, const int32_t *tokens, float temp,

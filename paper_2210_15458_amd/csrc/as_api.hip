@@ -709,8 +709,115 @@ as_status as_interval_step(as_ctx *ctx, const void *logits, int64_t rows, int64_
     a.logits = logits; a.rows = rows; a.ld = ld; a.V = ctx->V; a.dtype = ctx->dtype;
     a.tokens = tokens; a.tok_stride = 1; a.k = 1.44269504088896340736f / temp; a.thr = thr;
     a.finished_in = finished_in; a.eos_id = eos_id; a.finished_out = finished_out;
-    a.lo = lo; a.width = width; a.row_ids = row_ids; a.prev_out = nullptr;
+    a.lo = lo; a.width = width; a.row_ids = row_ids;
     return launch_interval(ctx, a);
+}
+
+// Rows of an encode's logits computed at a time.  The product wants many (us an encode by rows a chunk 256 / 512 / 1024 /
+// 2048 / 3072 / 4096 / 8192: 65536 positions of 32128 bf16, d = 512 3013 / 1942 / 1564 / 1344 / 1366 / 1268 / 1228; 38985
+// of 153375, d = 896 17213 / 12969 / 12043 / 11419 / 12370 / 11364 / 11350; 15457 of 4597, d = 960 701 / 407 / 258 / 199 /
+// 208 / 182 / 177), in whole sets of 8 row tiles (3072 is not); whether they stay in the caches hardly matters, so
+// memory draws the line.
+static int64_t encode_chunk(int64_t row_bytes)
+{
+    if (8192 * row_bytes <= 256LL << 20) return 8192;
+    if (4096 * row_bytes <= 256LL << 20) return 4096;
+    if (2048 * row_bytes <= 768LL << 20) return 2048;
+    return 1024 * row_bytes <= 1024LL << 20 ? 1024 : 256;
+}
+
+// Its positions are taken a window of columns at a time, which bounds the tables (28 bytes a position).
+constexpr int64_t kEncodePositions = 1LL << 19;
+
+// Whether an encode of n positions gives every token in use one logits row (otherwise every position has its own, the
+// first column's one per prompt).  With tokens spread evenly n - V(1 - exp(-n/V)) rows of product and of sums are spared;
+// the tables take five launches, 20 us.
+static bool claiming_pays(const as_ctx *ctx, const as_model *m, int64_t n)
+{
+    if (!rows_on_device(ctx, m)) return false;
+    const double spared = (double)n - (double)m->V * (1.0 - exp(-(double)n / (double)m->V));
+    const double row = (double)m->V * ((double)m->d * 2.0 / 1e15 + (ctx->dtype == AS_BF16 ? 2.0 : 4.0) / 4e12);
+    return spared * row > 30e-6;
+}
+
+static as_status encode_windows(as_ctx *ctx, const as_model *model, const int32_t *prompts, int64_t R, int32_t N, int32_t T,
+                                const int32_t *tokens, float temp, int32_t top_k, float top_p, int32_t eos_id,
+                                double *lo_out, double *width_out)
+{
+    const size_t esz = ctx->dtype == AS_BF16 ? 2 : 4;
+    const int64_t ldw = ((int64_t)ctx->V + 7) / 8 * 8;        // rows start 16-byte aligned
+    const int32_t window = (int32_t)(kEncodePositions / R < 1 ? 1 : (kEncodePositions / R < T ? kEncodePositions / R : T));
+    const int64_t most = R * window;                          // positions of a window
+    const bool claimed = claiming_pays(ctx, model, most);
+    const int64_t max_rows = claimed && ctx->V < most ? ctx->V : most;
+    int64_t chunk = encode_chunk(ldw * (int64_t)esz);
+    chunk = chunk < max_rows ? chunk : max_rows;
+    const bool trunc = truncation_on(ctx->V, top_k, top_p), by_sums = interval_by_sums(ctx, temp);
+
+    as_status st = AS_OK;
+    Positions w{};
+    w.tokens = tokens; w.prompts = prompts; w.R = R; w.N = N; w.T = T; w.V = ctx->V; w.eos_id = eos_id;
+    w.dtype = ctx->dtype; w.chunk = chunk > 0 ? chunk : 1;
+    if (T > 0) {
+        st = grow(ctx, ctx->logits, (size_t)chunk * ldw * esz);
+        if (st != AS_OK) return st;
+    }
+    const int64_t chunks = (max_rows + w.chunk - 1) / w.chunk;
+    // the tables, 16-byte parts first
+    size_t bytes = 0;
+    auto part = [&](size_t n) { const size_t at = bytes; bytes += (n + 15) / 16 * 16; return at; };
+    const size_t at_f = part(most * 8), at_p = part(most * 8), at_sums = part(by_sums ? chunk * kRowSums * 4 : 0),
+                 at_thr = part(trunc ? chunk * 4 : 0), at_slot = part(most * 4), at_order = part(most * 4),
+                 at_token = part(max_rows * 4), at_ends = part(max_rows * 4), at_idle = part(max_rows), at_ended = part(R),
+                 at_cond = part(claimed ? most * 4 : 0), at_mark = part(claimed ? ctx->V * 4 : 0),
+                 at_claim = part(claimed ? ctx->V * 4 : 0), at_count = part(4), at_chunks = part(chunks * 4);
+    st = grow(ctx, ctx->state, bytes);
+    if (st != AS_OK) return st;
+    unsigned char *const base = static_cast<unsigned char *>(ctx->state.ptr);
+    auto words = [&](size_t at) { return reinterpret_cast<int32_t *>(base + at); };
+    w.f_lo = reinterpret_cast<double *>(base + at_f); w.p = reinterpret_cast<double *>(base + at_p);
+    w.slot = words(at_slot); w.order = words(at_order); w.token = words(at_token); w.ends = words(at_ends);
+    w.idle = base + at_idle; w.ended = base + at_ended; w.cond = words(at_cond); w.count = words(at_count);
+    w.chunk_rows = claimed ? words(at_chunks) : nullptr;
+    float *const sums = reinterpret_cast<float *>(base + at_sums), *const thr = reinterpret_cast<float *>(base + at_thr);
+    RowShare tables{};
+    tables.mark = words(at_mark); tables.slot = words(at_claim); tables.token = w.token; tables.count = w.count;
+    tables.fill = w.ends;
+
+    for (int32_t t0 = 0; t0 < T; t0 += window) {
+        w.t0 = t0;
+        w.Tw = T - t0 < window ? T - t0 : window;
+        const int64_t n = R * w.Tw;
+        st = launch_positions(ctx, w, claimed);
+        if (st == AS_OK && claimed) st = launch_claim_positions(ctx, tables, w.cond, n, w.slot);
+        const int64_t own = t0 == 0 && N > 1 ? R / N + R * (w.Tw - 1) : n;
+        const int64_t rows = claimed ? (n < max_rows ? n : max_rows) : own;
+        if (st == AS_OK && claimed) st = launch_positions_order(ctx, w, rows);
+        if (st != AS_OK) return st;
+        for (int64_t s0 = 0, c = 0; s0 < rows; s0 += chunk, ++c) {
+            const int64_t here = rows - s0 < chunk ? rows - s0 : chunk;
+            const int32_t *const rows_dev = claimed ? w.chunk_rows + c : nullptr;
+            st = launch_bigram_logits(ctx, model, w.token + s0, here, ctx->logits.ptr, ldw, rows_dev);
+            if (st == AS_OK && trunc)
+                st = launch_threshold(ctx, ctx->logits.ptr, here, ldw, w.idle + s0, nullptr, temp, top_k, top_p, thr);
+            if (st != AS_OK) return st;
+            ChunkArgs a{};
+            a.w = w; a.logits = ctx->logits.ptr; a.s0 = s0; a.rows = here; a.ld = ldw; a.V = ctx->V;
+            a.k = 1.44269504088896340736f / temp; a.thr = trunc ? thr : nullptr; a.sums = sums;
+            if (by_sums) {
+                RowSumsArgs q{};
+                q.logits = a.logits; q.ld = ldw; q.V = ctx->V; q.dtype = ctx->dtype; q.k = a.k; q.thr = a.thr; q.sums = sums;
+                q.rows_dev = rows_dev;
+                st = launch_row_sums(ctx, q, here);
+                if (st != AS_OK) return st;
+            }
+            st = launch_interval_chunk(ctx, a, by_sums);
+            if (st != AS_OK) return st;
+        }
+        st = launch_fold(ctx, w, lo_out, width_out);
+        if (st != AS_OK) return st;
+    }
+    return T > 0 ? AS_OK : launch_fold(ctx, w, lo_out, width_out);      // (no column: the whole interval)
 }
 
 as_status as_encode(as_ctx *ctx, const as_model *model, const int32_t *prompts, int32_t B, int32_t N, int32_t T,
@@ -731,41 +838,7 @@ as_status as_encode(as_ctx *ctx, const as_model *model, const int32_t *prompts, 
     if (eos_id >= ctx->V) return fail(ctx, AS_ERR_INVALID_ARG, "eos_id outside the vocabulary");
     if (isnan(top_p)) return fail(ctx, AS_ERR_INVALID_ARG, "top_p is NaN");
 
-    const size_t esz = ctx->dtype == AS_BF16 ? 2 : 4;
-    const int64_t ldw = ((int64_t)ctx->V + 7) / 8 * 8;        // rows start 16-byte aligned
-    as_status st = grow(ctx, ctx->logits, (size_t)R * ldw * esz);
-    if (st != AS_OK) return st;
-    DecodeState state;
-    st = decode_state(ctx, model, R, T, state);
-    if (st != AS_OK) return st;
-    int32_t *const prev = state.prev;
-    uint8_t *const fin = state.fin;
-
-    st = launch_interval_init(ctx, B, N, prompts, lo_out, width_out, prev, fin, ctx->rid);
-    if (st != AS_OK) return st;
-    const bool trunc = truncation_on(ctx->V, top_k, top_p);
-    for (int32_t t = 0; t < T; ++t) {
-        StepRows sr;
-        st = step_rows(ctx, state, prompts, B, N, t, false, sr);
-        if (st != AS_OK) return st;
-        st = launch_bigram_logits(ctx, model, sr.prev, sr.rows, ctx->logits.ptr, ldw, sr.rows_dev);
-        if (st != AS_OK) return st;
-        if (trunc) {
-            st = launch_threshold(ctx, ctx->logits.ptr, R, ldw, eos_id >= 0 ? fin : nullptr, sr.row_ids, temp,
-                                  top_k, top_p, ctx->thr);
-            if (st != AS_OK) return st;
-        }
-        IntervalArgs a{};
-        a.logits = ctx->logits.ptr; a.rows = R; a.ld = ldw; a.V = ctx->V; a.dtype = ctx->dtype;
-        a.tokens = tokens + t; a.tok_stride = T; a.k = 1.44269504088896340736f / temp;
-        a.thr = trunc ? ctx->thr : nullptr;
-        a.finished_in = eos_id >= 0 ? fin : nullptr; a.eos_id = eos_id;
-        a.finished_out = eos_id >= 0 ? fin : nullptr;
-        a.lo = lo_out; a.width = width_out; a.row_ids = sr.row_ids; a.src_rows = sr.src_rows; a.prev_out = prev;
-        st = launch_interval(ctx, a);
-        if (st != AS_OK) return st;
-    }
-    return AS_OK;
+    return encode_windows(ctx, model, prompts, R, N, T, tokens, temp, top_k, top_p, eos_id, lo_out, width_out);
 }
 
 }  // extern "C"

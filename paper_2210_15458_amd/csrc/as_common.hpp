@@ -149,7 +149,49 @@ struct IntervalArgs {
     double *lo;                  // [rows] in/out
     double *width;               // [rows] in/out
     const int32_t *row_ids;
-    int32_t *prev_out;           // encode state: next step's conditioning token, or null
+};
+
+// The positions of one window of an encode: columns t0 .. t0+Tw of R sequences; position p is column t0 + p % Tw of
+// sequence p / Tw.  The tables are the context's decode state.
+struct Positions {
+    const int32_t *tokens;       // [R, T]
+    const int32_t *prompts;      // [R / N]
+    int64_t R;
+    int32_t N, T, V, eos_id, t0, Tw;
+    as_dtype dtype;
+    int32_t *cond;               // [positions] the token each conditions on, -1 behind an EOS (claimed rows only)
+    int32_t *slot;               // [positions] its logits row
+    int32_t *order;              // [positions] the positions by logits row; -1 behind an EOS
+    int32_t *token;              // [rows] token of each logits row
+    int32_t *ends;               // [rows] where the row's positions end in `order`
+    uint8_t *idle;               // [rows] 1 where no position reads the row
+    uint8_t *ended;              // [R] sequences that have ended before the window
+    int32_t *count;              // logits rows in use (claimed rows only) ...
+    int32_t *chunk_rows;         // ... and in each chunk of `chunk` of them, or null
+    int64_t chunk;
+    double *f_lo, *p;            // [Tw, R] each position's shares
+};
+
+struct ChunkArgs {               // a chunk of an encode's logits rows: s0 .. s0+rows
+    Positions w;
+    const void *logits;          // [rows, ld]
+    int64_t s0, rows, ld;
+    int32_t V;
+    float k;                     // log2(e)/temp
+    const float *thr;            // [rows] keep thresholds, or null
+    const float *sums;           // [rows, kRowSums]
+};
+
+constexpr int kRowSums = 68;     // floats that row_sums_kernel leaves per row: 64 chunk sums, 4 references
+struct RowSumsArgs {
+    const void *logits;          // [rows, ld]
+    int64_t ld;
+    int32_t V;
+    as_dtype dtype;
+    float k;
+    const float *thr;            // [rows] or null
+    float *sums;                 // [rows, kRowSums]
+    const int32_t *rows_dev;     // the number of rows where only the device knows it, or null
 };
 
 struct SmallArgs {               // a whole decode of a model that fits LDS
@@ -193,8 +235,12 @@ as_status launch_bigram_partials(as_ctx *ctx, const as_model *m, const int32_t *
                                  float2 *part, int64_t ldp, const int32_t *rows_dev = nullptr);
 bool fused_path_applies(const as_ctx *ctx, const as_model *m);
 as_status launch_interval(as_ctx *ctx, const IntervalArgs &a);
-as_status launch_interval_init(as_ctx *ctx, int32_t B, int32_t N, const int32_t *prompts, double *lo,
-                               double *width, int32_t *prev, uint8_t *finished, int32_t *row_ids);
+as_status launch_positions(as_ctx *ctx, const Positions &w, bool claimed);
+as_status launch_positions_order(as_ctx *ctx, const Positions &w, int64_t max_rows);
+bool interval_by_sums(const as_ctx *ctx, float temp);
+as_status launch_interval_chunk(as_ctx *ctx, const ChunkArgs &a, bool by_sums);
+as_status launch_fold(as_ctx *ctx, const Positions &w, double *lo, double *width);
+as_status launch_row_sums(as_ctx *ctx, const RowSumsArgs &a, int64_t rows);
 bool launch_topk_step(as_ctx *ctx, const StepArgs &a, int32_t top_k, float top_p, as_status *st);
 as_status launch_wide(as_ctx *ctx, const StepArgs &a, int32_t top_k, float top_p, float *thr_out);
 as_status launch_threshold(as_ctx *ctx, const void *logits, int64_t rows, int64_t ld,
@@ -224,9 +270,12 @@ bool mfma_applies(const as_model *m);
 bool small_decode_applies(const as_ctx *ctx, const as_model *m, int64_t rows, float temp);
 as_status launch_small_decode(as_ctx *ctx, const as_model *m, SmallArgs s);
 bool sharing_pays(const as_ctx *ctx, const as_model *m, int64_t rows, int32_t T);
+bool rows_on_device(const as_ctx *ctx, const as_model *m);
 as_status launch_share_clear(as_ctx *ctx, const RowShare &s, int32_t T);
 as_status launch_share(as_ctx *ctx, const RowShare &s, int32_t step, const int32_t *prev, int64_t rows,
                        int32_t *row_ids, bool sorted);
+// the same for the positions of an encode (prev < 0: none): rows claimed, counted and scanned, the order left to the caller
+as_status launch_claim_positions(as_ctx *ctx, const RowShare &s, const int32_t *prev, int64_t rows, int32_t *row_ids);
 
 // ------------------------------------------------------------ wave primitives
 // Data-parallel-primitive (DPP) cross-lane moves.  bound_ctrl is off, so a lane

@@ -41,6 +41,8 @@ __global__ __launch_bounds__(256) void share_clear_kernel(RowShare s, int32_t V,
 // The first row to come with a token takes the next logits row for it: one addition to the step's counter per block
 // (65536 of them on one address would take longer than the product they save).  Which row a token gets differs
 // from run to run; what is in it does not.
+// SKIP: a negative token is no token.
+template <bool SKIP>
 __global__ __launch_bounds__(1024) void share_claim_kernel(RowShare s, int32_t step, int32_t V, const int32_t *prev,
                                                            int64_t rows)
 {
@@ -49,7 +51,7 @@ __global__ __launch_bounds__(1024) void share_claim_kernel(RowShare s, int32_t s
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     bool mine = false;
     int32_t v = 0;
-    if (r < rows) {
+    if (r < rows && (!SKIP || prev[r] >= 0)) {
         v = clamp_token(prev[r], V);
         // (looked at first: the rows that have ended all come with one token)
         if (__hip_atomic_load(&s.mark[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != step)
@@ -76,12 +78,16 @@ __global__ __launch_bounds__(1024) void share_claim_kernel(RowShare s, int32_t s
     }
 }
 
-template <bool SORTED>
+template <bool SORTED, bool SKIP>
 __global__ __launch_bounds__(256) void share_map_kernel(RowShare s, int32_t V, const int32_t *prev, int64_t rows,
                                                         int32_t *row_ids)
 {
     const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (r >= rows) return;
+    if (SKIP && prev[r] < 0) {
+        row_ids[r] = -1;
+        return;
+    }
     const int32_t at = s.slot[clamp_token(prev[r], V)];
     row_ids[r] = at;
     if constexpr (SORTED) atomicAdd(&s.fill[at], 1);
@@ -1196,6 +1202,13 @@ static int64_t tile_rounds(int64_t m, int64_t n_blocks, int W, int gm)
     return (nbx + W / m - 1) / (W / m);
 }
 
+// Whether the logits kernel that takes the model can read the number of rows on the device (the persistent one).
+bool rows_on_device(const as_ctx *ctx, const as_model *m)
+{
+    return ctx->gemm_shape != 1 && ctx->num_cus >= 8 && mfma_applies(m) && m->d >= 2 * PK &&
+           (int64_t)m->V * m->d * 2 < (1LL << 32);
+}
+
 // Whether a decode of `rows` rows shares logits rows after its first step.  With tokens spread evenly over the vocabulary
 // (the worst case) rows - V(1 - exp(-rows/V)) rows of product are saved; the sharing itself takes 6 to 12 us a step,
 // 20 to 25 where the rows are sorted too, and is asked to save 20.  What the product then takes less lies between
@@ -1206,9 +1219,7 @@ static int64_t tile_rounds(int64_t m, int64_t n_blocks, int W, int gm)
 // 497 / 487.  V = 4096, d = 512: 4096 rows 49 / 44, 8192 80 / 57.
 bool sharing_pays(const as_ctx *ctx, const as_model *m, int64_t rows, int32_t T)
 {
-    if (T < 2 || ctx->gemm_shape == 1 || ctx->num_cus < 8 || !mfma_applies(m) || m->d < 2 * PK ||
-        (int64_t)m->V * m->d * 2 >= (1LL << 32))
-        return false;
+    if (T < 2 || !rows_on_device(ctx, m)) return false;
     const double tokens = (double)m->V * (1.0 - exp(-(double)rows / (double)m->V));
     const int W = ctx->num_cus / 8, gm = persistent_gm(ctx);
     const int64_t n_blocks = ((int64_t)m->V + PN - 1) / PN;
@@ -1231,18 +1242,33 @@ as_status launch_share(as_ctx *ctx, const RowShare &s, int32_t step, const int32
                        int32_t *row_ids, bool sorted)
 {
     const dim3 blocks((unsigned)((rows + 255) / 256));
-    hipLaunchKernelGGL(share_claim_kernel, dim3((unsigned)((rows + 1023) / 1024)), dim3(1024), 0, ctx->stream, s, step,
+    hipLaunchKernelGGL(share_claim_kernel<false>, dim3((unsigned)((rows + 1023) / 1024)), dim3(1024), 0, ctx->stream, s, step,
                        ctx->V, prev, rows);
     AS_HIP_TRY(ctx, hipGetLastError());
     if (!sorted) {
-        hipLaunchKernelGGL(share_map_kernel<false>, blocks, dim3(256), 0, ctx->stream, s, ctx->V, prev, rows, row_ids);
+        hipLaunchKernelGGL((share_map_kernel<false, false>), blocks, dim3(256), 0, ctx->stream, s, ctx->V, prev, rows, row_ids);
     } else {
-        hipLaunchKernelGGL(share_map_kernel<true>, blocks, dim3(256), 0, ctx->stream, s, ctx->V, prev, rows, row_ids);
+        hipLaunchKernelGGL((share_map_kernel<true, false>), blocks, dim3(256), 0, ctx->stream, s, ctx->V, prev, rows, row_ids);
         AS_HIP_TRY(ctx, hipGetLastError());
         hipLaunchKernelGGL(share_scan_kernel, dim3(1), dim3(1024), 0, ctx->stream, s, step);
         AS_HIP_TRY(ctx, hipGetLastError());
         hipLaunchKernelGGL(share_order_kernel, blocks, dim3(256), 0, ctx->stream, s, rows, row_ids);
     }
+    AS_HIP_TRY(ctx, hipGetLastError());
+    return AS_OK;
+}
+
+as_status launch_claim_positions(as_ctx *ctx, const RowShare &s, const int32_t *prev, int64_t rows, int32_t *row_ids)
+{
+    as_status st = launch_share_clear(ctx, s, 1);
+    if (st != AS_OK) return st;
+    hipLaunchKernelGGL(share_claim_kernel<true>, dim3((unsigned)((rows + 1023) / 1024)), dim3(1024), 0, ctx->stream, s, 0,
+                       ctx->V, prev, rows);
+    AS_HIP_TRY(ctx, hipGetLastError());
+    hipLaunchKernelGGL((share_map_kernel<true, true>), dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, ctx->stream, s,
+                       ctx->V, prev, rows, row_ids);
+    AS_HIP_TRY(ctx, hipGetLastError());
+    hipLaunchKernelGGL(share_scan_kernel, dim3(1), dim3(1024), 0, ctx->stream, s, 0);
     AS_HIP_TRY(ctx, hipGetLastError());
     return AS_OK;
 }

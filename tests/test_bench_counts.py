@@ -22,3 +22,10 @@ def test_sharing_pays_for_wide_lattices_only():
     assert not shared(32128, 512, 1024) and not shared(32128, 512, 65536, T=1) and not shared(32128, 512, 65536, wdt="f32")
     # the rows in use leave workers of the product without a row tile
     assert not shared(32128, 512, 8192) and not shared(32128, 1024, 6144)
+
+
+def test_rows_of_an_encode():
+    # conditioned on: the prompts 3, 4, then 5 and 6 (rows that have not ended), 7 once
+    seqs = np.array([[5, 7, 9], [1, 8, 8], [6, 1, 8], [5, 7, 1]])
+    assert bench.conditioned_tokens(seqs, np.array([3, 4]), 1) == 5
+    assert bench.conditioned_tokens(seqs, np.array([3, 4]), -1) == 7

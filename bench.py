@@ -118,10 +118,33 @@ def conditioned_tokens(seqs, prompts, eos):
     return int(np.unique(np.concatenate([prev[:, 0], prev[:, 1:][running]])).size)
 
 
-def step_counts(tokens, eos, prompts, shared):
+def rows_kept(V, d, R, B, T, wdt, row_bytes, by_sums):
+    """Whether a decode keeps logits rows from step to step (the choice the library makes)."""
+    if T < 3 or wdt != "bf16" or d % 64 != 0 or d < 128 or V * d * 2 >= 2 ** 32:
+        return False
+    most = min(R * (T - 1) + B, V)
+    if most > 4 * R or (most > R and most * row_bytes > 2 ** 32):
+        return False
+    computed = V * (1.0 - np.exp(-R * (T - 1) / V)) / (T - 1)
+    spared = (R - computed) * V * d * 2.0 / 1e15
+    if by_sums:
+        row = row_bytes / 5e12
+        spared += R * (max(row, 4e-9) - 0.5e-9) - computed * row
+    return spared > 3e-6 + 15e-6 * min(6.0 * V / (R * (T - 1)), 1.0)
+
+
+def step_by_sums(V, ldt, top_k, top_p, temp):
+    """Whether such a decode samples from the sums of its kept rows."""
+    half = ldt == "bf16"
+    return (not (0 < top_k < V) and not (0.0 < top_p < 1.0) and V % (8 if half else 4) == 0 and
+            V <= (32768 if half else 16384) and 1.4426950408889634 / temp <= 4.0)
+
+
+def step_counts(tokens, eos, prompts, shared, kept=False):
     """Per step of a decode, averaged over its steps: rows still running (`active`), logits rows that are computed, and
     logits rows that the rows still running read (`fetched`, each once).  The first step has one logits row per
-    prompt; later ones have one per row, or with sharing one per token that any row (an ended one too) conditions on."""
+    prompt; later ones have one per row, or with sharing one per token that any row (an ended one too) conditions on; where
+    rows are kept, only those of new tokens are computed."""
     tk = np.asarray(tokens.cpu() if hasattr(tokens, "cpu") else tokens)
     tk = tk.reshape(-1, tk.shape[-1])
     R, T = tk.shape
@@ -129,10 +152,13 @@ def step_counts(tokens, eos, prompts, shared):
     for t in range(1, T):
         active[:, t] = active[:, t - 1] & (tk[:, t - 1] != eos)
     computed, fetched = [prompts], [prompts]
+    seen = np.zeros(int(tk.max()) + 1, dtype=bool)
     for t in range(1, T):
         prev = tk[:, t - 1]
-        computed.append(len(np.unique(prev)) if shared else R)
-        fetched.append(len(np.unique(prev[active[:, t]])) if shared else int(active[:, t].sum()))
+        used = np.unique(prev)
+        computed.append(int((~seen[used]).sum()) if kept else len(used) if shared else R)
+        seen[used] = True
+        fetched.append(len(np.unique(prev[active[:, t]])) if shared or kept else int(active[:, t].sum()))
     return {"active": float(active.sum()) / T, "computed": float(np.mean(computed)), "fetched": float(np.mean(fetched))}
 
 
@@ -167,9 +193,15 @@ def compact_leg(cfg_id, top_k, top_p, steps, warmup):
     step_samples, gemm_samples, thr_samples = ctx.profile_samples(0), ctx.profile_samples(1), ctx.profile_samples(2)
     ctx.profile_read(0); ctx.profile_read(1); ctx.profile_read(2)
     ctx.profile(False)
-    cnt = step_counts(tokens, eos, Bn, rows_shared(V, d, R, T, cfg["dtype"], compute_units()))
+    by_sums = step_by_sums(V, "bf16", top_k, top_p, temp)
+    kept = rows_kept(V, d, R, Bn, T, cfg["dtype"], (V + 7) // 8 * 16, by_sums)
+    cnt = step_counts(tokens, eos, Bn, rows_shared(V, d, R, T, cfg["dtype"], compute_units()), kept)
     bytes_per_row = V * 2 + 18
     bytes_per_launch = cnt["fetched"] * V * 2 + cnt["active"] * 18      # logits rows in use, each once; codes, tokens, flags
+    if kept and by_sums:
+        # a step is two launches: the new rows once, then per code its row's sums and one KiB of it
+        bytes_per_launch = cnt["computed"] * V * 2 + cnt["active"] * (272 + 1024 + 18)
+        step_samples = np.asarray(step_samples).reshape(-1, 2).sum(axis=1)
     # the sampling step of a launch: the kernel that finishes it, plus the threshold kernel where that is separate
     samp_us = float(np.mean(step_samples)) * 1e3 + (float(np.mean(thr_samples)) * 1e3 if len(thr_samples) else 0.0)
     ach = bytes_per_launch / (samp_us * 1e-6) / 1e9
@@ -178,7 +210,8 @@ def compact_leg(cfg_id, top_k, top_p, steps, warmup):
                     f"temp={temp} top_k={top_k} top_p={top_p} eos={eos}",
         "value": R * T * steps / (t1 - t0), "unit": "code-steps/s", "decodes_timed": steps,
         "ms_per_decode": (t1 - t0) / steps * 1e3,
-        "sampling": {"kernel": sampling_kernel_name(V, "bf16", top_k, top_p, temp, R, d, cfg["dtype"], compute_units()),
+        "sampling": {"kernel": "row_sums_kernel, then row_select_kernel, as launched inside as_decode" if kept and by_sums else
+                     sampling_kernel_name(V, "bf16", top_k, top_p, temp, R, d, cfg["dtype"], compute_units()),
                      "bound": "hbm",
                      "avg_launch_us": samp_us, "spread": spread(step_samples), "achieved": ach, "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": ach / HBM_PEAK_GBS, "bytes_per_code_step": bytes_per_row,

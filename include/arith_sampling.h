@@ -31,7 +31,10 @@
  *     the context (re)allocates when a call needs more than any earlier call
  *     did: the first call at a size synchronises the stream, frees and
  *     allocates, and must not be made under stream capture; later calls of the
- *     same or a smaller size allocate nothing and can be captured.
+ *     same or a smaller size allocate nothing and can be captured.  The
+ *     logits of a decode take a row per code; where a decode comes back to
+ *     most of its tokens (rows and steps enough, by their number), a row per
+ *     token in use, at most four times as many and then at most 4 GiB.
  *   - One context must not be used from two host threads at once.
  */
 #ifndef ARITH_SAMPLING_H

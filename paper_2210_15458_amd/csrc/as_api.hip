@@ -418,40 +418,72 @@ struct DecodeState {
     uint8_t *fin;
     bool share;
     RowShare tables;
+    int64_t logits_rows;         // rows of the table of logits (or group masses) that the decode works on
+    float *sums;                 // kept rows whose steps work from sums: [logits_rows, kRowSums], else null
 };
 
-static as_status decode_state(as_ctx *ctx, const as_model *model, int64_t R, int32_t T, DecodeState &s)
+// Makes the state and the table of logits, logits_rows x row_bytes.  can_sum: rows of this vocabulary can be stepped from
+// sums; by_sums: this decode's are.  What is reserved depends on the sizes alone, so that a call that differs from an
+// earlier one in its temperature or truncation finds its workspace; if a table of kept rows cannot be had, the decode
+// goes without.
+static as_status decode_state(as_ctx *ctx, const as_model *model, int32_t B, int32_t N, int32_t T, int64_t row_bytes,
+                              bool can_sum, bool by_sums, DecodeState &s)
 {
-    s.share = sharing_pays(ctx, model, R, T);
-    const size_t words = (size_t)R * 2 + (s.share ? 2 * (size_t)R + 3 * (size_t)ctx->V + (size_t)T : 0);
-    as_status st = grow(ctx, ctx->state, words * 4 + (size_t)R);
+    const int64_t R = (int64_t)B * N, V = ctx->V;
+    const int64_t used = R < V ? R * (T > 0 ? T - 1 : 0) + B : V, kept_rows = used < V ? used : V;
+    bool keep = keeping_pays(ctx, model, R, B, T, row_bytes, by_sums);
+    const bool room = keep || keeping_pays(ctx, model, R, B, T, row_bytes, can_sum) ||
+                      keeping_pays(ctx, model, R, B, T, row_bytes, false);
+    as_status st = AS_OK;
+    if (room && kept_rows > R) {
+        st = grow(ctx, ctx->logits, (size_t)kept_rows * row_bytes);
+        if (st != AS_OK && st != AS_ERR_ALLOC) return st;
+        if (st != AS_OK) keep = false;
+    }
+    s.share = keep || sharing_pays(ctx, model, R, T);
+    s.logits_rows = keep ? kept_rows : R;
+    st = grow(ctx, ctx->logits, (size_t)s.logits_rows * row_bytes);
+    if (st != AS_OK) return st;
+    const int64_t filled = keep ? s.logits_rows : V;
+    const size_t sums = keep && by_sums ? (size_t)s.logits_rows * kRowSums : 0;
+    const size_t tables = (size_t)R + s.logits_rows + 2 * (size_t)V + filled + (size_t)T + 1;
+    const size_t words = sums + (size_t)R * 2 + (s.share ? tables : 0);
+    const size_t reserve = room ? (can_sum ? (size_t)kept_rows * kRowSums : 0) + (size_t)R * 3 + 2 * (size_t)kept_rows +
+                                      3 * (size_t)V + (size_t)T + 1
+                                : 0;
+    st = grow(ctx, ctx->state, (words > reserve ? words : reserve) * 4 + (size_t)R);
     if (st != AS_OK) return st;
     int32_t *w = static_cast<int32_t *>(ctx->state.ptr);
+    s.sums = sums ? reinterpret_cast<float *>(w) : nullptr;
+    w += sums;
     s.codes = reinterpret_cast<float *>(w);
     s.prev = w + R;
     w += 2 * R;
     s.tables = RowShare{};
     if (s.share) {
+        s.tables.kept = keep ? (int32_t)s.logits_rows : 0;
         s.tables.token = w;
-        s.tables.mark = w + R;
-        s.tables.slot = s.tables.mark + ctx->V;
-        s.tables.count = s.tables.slot + ctx->V;
-        s.tables.fill = s.tables.count + T;
-        s.tables.order = s.tables.fill + ctx->V;
+        s.tables.mark = w + s.logits_rows;
+        s.tables.slot = s.tables.mark + V;
+        s.tables.count = s.tables.slot + V;
+        s.tables.fill = s.tables.count + T + 1;
+        s.tables.order = s.tables.fill + filled;
         w = s.tables.order + R;
-        st = launch_share_clear(ctx, s.tables, T);
+        if (sums) s.tables.fill = nullptr;                    // (no order is made)
+        st = launch_share_clear(ctx, s.tables, T + 1);
     }
     s.fin = reinterpret_cast<uint8_t *>(w);
     return st;
 }
 
 // The rows of the model's output that step t of a decode needs: in the first step one per prompt (its N codes condition
-// on the same token; ctx->rid already says so), later one per row, or one per token in use where that pays.
-// `rows` is their largest number, `rows_dev` holds the number itself where only the device knows it.
+// on the same token; ctx->rid already says so), later one per row, or one per token in use where that pays, or, where
+// rows are kept, those of the tokens that are new.  `rows` is their largest number, `range` says which they are where
+// only the device knows.
 struct StepRows {
     const int32_t *prev;
     int64_t rows;
-    const int32_t *rows_dev;
+    RowRange range;
     const int32_t *row_ids;
     int64_t src_rows;
     const int32_t *order;        // the rows sorted by logits row, where those are read from memory rather than caches
@@ -461,15 +493,24 @@ static as_status step_rows(as_ctx *ctx, const DecodeState &s, const int32_t *pro
                            bool sorted, StepRows &o)
 {
     const int64_t R = (int64_t)B * N;
+    if (s.tables.kept) {
+        // (the first step's prompts are claimed as such: R rows on a few tokens would queue for them)
+        const int64_t most = t == 0 ? B : (R < s.logits_rows ? R : s.logits_rows);
+        o = StepRows{s.tables.token, most, RowRange{t > 0 ? s.tables.count + t - 1 : nullptr, s.tables.count + t}, ctx->rid,
+                     s.logits_rows, sorted && t > 0 ? s.tables.order : nullptr};
+        const as_status st = launch_claim(ctx, s.tables, t, t == 0 ? prompts : s.prev, t == 0 ? B : R);
+        if (st != AS_OK || s.sums) return st;
+        return launch_share_map(ctx, s.tables, t, s.prev, R, ctx->rid, o.order != nullptr);
+    }
     if (t == 0 && N > 1) {
-        o = StepRows{prompts, B, nullptr, ctx->rid, B, nullptr};
+        o = StepRows{prompts, B, RowRange{}, ctx->rid, B, nullptr};
         return AS_OK;
     }
     if (t == 0 || !s.share) {
-        o = StepRows{s.prev, R, nullptr, nullptr, 0, nullptr};
+        o = StepRows{s.prev, R, RowRange{}, nullptr, 0, nullptr};
         return AS_OK;
     }
-    o = StepRows{s.tables.token, R, s.tables.count + t, ctx->rid, 0, sorted ? s.tables.order : nullptr};
+    o = StepRows{s.tables.token, R, RowRange{nullptr, s.tables.count + t}, ctx->rid, 0, sorted ? s.tables.order : nullptr};
     return launch_share(ctx, s.tables, t, s.prev, R, ctx->rid, sorted);
 }
 
@@ -501,10 +542,9 @@ static as_status decode_impl(as_ctx *ctx, const as_model *model, const int32_t *
     }
     const size_t esz = ctx->dtype == AS_BF16 ? 2 : 4;
     const int64_t ldw = ((int64_t)ctx->V + 7) / 8 * 8;        // rows start 16-byte aligned
-    as_status st = grow(ctx, ctx->logits, (size_t)R * ldw * esz);
-    if (st != AS_OK) return st;
     DecodeState state;
-    st = decode_state(ctx, model, R, T, state);
+    as_status st = decode_state(ctx, model, B, N, T, ldw * (int64_t)esz, step_by_sums(ctx, 1.f),
+                                !trunc && step_by_sums(ctx, temp), state);
     if (st != AS_OK) return st;
     float *const codes = state.codes;
     int32_t *const prev = state.prev;
@@ -516,7 +556,7 @@ static as_status decode_impl(as_ctx *ctx, const as_model *model, const int32_t *
         StepRows sr;
         st = step_rows(ctx, state, prompts, B, N, t, !trunc && stream_rows(R, ldw, esz), sr);
         if (st != AS_OK) return st;
-        st = launch_bigram_logits(ctx, model, sr.prev, sr.rows, ctx->logits.ptr, ldw, sr.rows_dev);
+        st = launch_bigram_logits(ctx, model, sr.prev, sr.rows, ctx->logits.ptr, ldw, sr.range);
         if (st != AS_OK) return st;
         StepArgs a{};
         a.logits = ctx->logits.ptr; a.rows = R; a.ld = ldw; a.V = ctx->V; a.dtype = ctx->dtype;
@@ -526,6 +566,19 @@ static as_status decode_impl(as_ctx *ctx, const as_model *model, const int32_t *
         a.finished_out = eos_id >= 0 ? fin : nullptr;
         a.prob_out = nullptr; a.flo_out = nullptr; a.row_ids = sr.row_ids; a.src_rows = sr.src_rows; a.prev_out = prev;
         a.order = sr.order;
+        if (state.sums) {
+            RowSumsArgs q{};
+            q.logits = a.logits; q.ld = ldw; q.V = ctx->V; q.dtype = ctx->dtype; q.k = a.k; q.sums = state.sums;
+            q.range = sr.range;
+            st = launch_row_sums(ctx, kKernelStep, q, sr.rows);
+            if (st != AS_OK) return st;
+            SelectArgs sel{};
+            sel.step = a; sel.prev = prev; sel.slot = state.tables.slot; sel.sums = state.sums;
+            sel.count = state.tables.count + t;
+            st = launch_row_select(ctx, sel);
+            if (st != AS_OK) return st;
+            continue;
+        }
         if (trunc) {
             if (launch_topk_step(ctx, a, top_k, top_p, &st)) {
                 if (st != AS_OK) return st;
@@ -634,10 +687,8 @@ as_status as_decode_fused(as_ctx *ctx, const as_model *model, const int32_t *pro
 
     const int32_t ngroups = (ctx->V + 31) / 32;
     const int64_t ldp = ((int64_t)ngroups + 15) / 16 * 16;
-    as_status st = grow(ctx, ctx->logits, (size_t)R * ldp * sizeof(float2));
-    if (st != AS_OK) return st;
     DecodeState state;
-    st = decode_state(ctx, model, R, T, state);
+    as_status st = decode_state(ctx, model, B, N, T, ldp * (int64_t)sizeof(float2), false, false, state);
     if (st != AS_OK) return st;
     float *const codes = state.codes;
     int32_t *const prev = state.prev;
@@ -650,7 +701,7 @@ as_status as_decode_fused(as_ctx *ctx, const as_model *model, const int32_t *pro
         StepRows sr;
         st = step_rows(ctx, state, prompts, B, N, t, false, sr);
         if (st != AS_OK) return st;
-        st = launch_bigram_partials(ctx, model, sr.prev, sr.rows, temp, part, ldp, sr.rows_dev);
+        st = launch_bigram_partials(ctx, model, sr.prev, sr.rows, temp, part, ldp, sr.range);
         if (st != AS_OK) return st;
         FusedArgs a{};
         a.part = part; a.row_ids = sr.row_ids; a.ldp = ldp; a.ngroups = ngroups; a.rows = R; a.V = ctx->V; a.d = model->d;
@@ -752,7 +803,7 @@ static as_status encode_windows(as_ctx *ctx, const as_model *model, const int32_
     const int64_t max_rows = claimed && ctx->V < most ? ctx->V : most;
     int64_t chunk = encode_chunk(ldw * (int64_t)esz);
     chunk = chunk < max_rows ? chunk : max_rows;
-    const bool trunc = truncation_on(ctx->V, top_k, top_p), by_sums = interval_by_sums(ctx, temp);
+    const bool trunc = truncation_on(ctx->V, top_k, top_p), by_sums = step_by_sums(ctx, temp);
 
     as_status st = AS_OK;
     Positions w{};
@@ -796,8 +847,8 @@ static as_status encode_windows(as_ctx *ctx, const as_model *model, const int32_
         if (st != AS_OK) return st;
         for (int64_t s0 = 0, c = 0; s0 < rows; s0 += chunk, ++c) {
             const int64_t here = rows - s0 < chunk ? rows - s0 : chunk;
-            const int32_t *const rows_dev = claimed ? w.chunk_rows + c : nullptr;
-            st = launch_bigram_logits(ctx, model, w.token + s0, here, ctx->logits.ptr, ldw, rows_dev);
+            const RowRange range{nullptr, claimed ? w.chunk_rows + c : nullptr};
+            st = launch_bigram_logits(ctx, model, w.token + s0, here, ctx->logits.ptr, ldw, range);
             if (st == AS_OK && trunc)
                 st = launch_threshold(ctx, ctx->logits.ptr, here, ldw, w.idle + s0, nullptr, temp, top_k, top_p, thr);
             if (st != AS_OK) return st;
@@ -807,8 +858,8 @@ static as_status encode_windows(as_ctx *ctx, const as_model *model, const int32_
             if (by_sums) {
                 RowSumsArgs q{};
                 q.logits = a.logits; q.ld = ldw; q.V = ctx->V; q.dtype = ctx->dtype; q.k = a.k; q.thr = a.thr; q.sums = sums;
-                q.rows_dev = rows_dev;
-                st = launch_row_sums(ctx, q, here);
+                q.range = range;
+                st = launch_row_sums(ctx, kKernelInterval, q, here);
                 if (st != AS_OK) return st;
             }
             st = launch_interval_chunk(ctx, a, by_sums);

@@ -182,6 +182,11 @@ struct ChunkArgs {               // a chunk of an encode's logits rows: s0 .. s0
     const float *sums;           // [rows, kRowSums]
 };
 
+// Rows begin .. end of a table, read on the device where only that knows them (end null: not so; begin null: 0).
+struct RowRange {
+    const int32_t *begin = nullptr, *end = nullptr;
+};
+
 constexpr int kRowSums = 68;     // floats that row_sums_kernel leaves per row: 64 chunk sums, 4 references
 struct RowSumsArgs {
     const void *logits;          // [rows, ld]
@@ -191,7 +196,15 @@ struct RowSumsArgs {
     float k;
     const float *thr;            // [rows] or null
     float *sums;                 // [rows, kRowSums]
-    const int32_t *rows_dev;     // the number of rows where only the device knows it, or null
+    RowRange range;              // which of them, where only the device knows it
+};
+
+struct SelectArgs {              // a sampling step from the sums of rows that codes share
+    StepArgs step;               // (row_ids is not used)
+    const int32_t *prev;         // [rows] conditioning token ...
+    const int32_t *slot;         // [V] ... whose logits row is this
+    const float *sums;           // [.., kRowSums]
+    int32_t *count;              // rows claimed so far: carried on to the next step, count[1] = count[0]
 };
 
 struct SmallArgs {               // a whole decode of a model that fits LDS
@@ -232,15 +245,14 @@ struct FusedArgs {
 as_status launch_step(as_ctx *ctx, const StepArgs &a);
 as_status launch_fused_sample(as_ctx *ctx, const FusedArgs &a);
 as_status launch_bigram_partials(as_ctx *ctx, const as_model *m, const int32_t *prev, int64_t rows, float temp,
-                                 float2 *part, int64_t ldp, const int32_t *rows_dev = nullptr);
+                                 float2 *part, int64_t ldp, RowRange range = RowRange{});
 bool fused_path_applies(const as_ctx *ctx, const as_model *m);
 as_status launch_interval(as_ctx *ctx, const IntervalArgs &a);
 as_status launch_positions(as_ctx *ctx, const Positions &w, bool claimed);
 as_status launch_positions_order(as_ctx *ctx, const Positions &w, int64_t max_rows);
-bool interval_by_sums(const as_ctx *ctx, float temp);
 as_status launch_interval_chunk(as_ctx *ctx, const ChunkArgs &a, bool by_sums);
 as_status launch_fold(as_ctx *ctx, const Positions &w, double *lo, double *width);
-as_status launch_row_sums(as_ctx *ctx, const RowSumsArgs &a, int64_t rows);
+as_status launch_row_sums(as_ctx *ctx, int kid, const RowSumsArgs &a, int64_t rows);
 bool launch_topk_step(as_ctx *ctx, const StepArgs &a, int32_t top_k, float top_p, as_status *st);
 as_status launch_wide(as_ctx *ctx, const StepArgs &a, int32_t top_k, float top_p, float *thr_out);
 as_status launch_threshold(as_ctx *ctx, const void *logits, int64_t rows, int64_t ld,
@@ -252,19 +264,21 @@ as_status launch_lattice(as_ctx *ctx, const float *u, int32_t B, int32_t N, floa
 as_status launch_estimate(as_ctx *ctx, const int32_t *tokens, int32_t B, int32_t N, int32_t T, const float *score,
                           int32_t eos_id, double *est_out);
 as_status launch_transpose(const void *U, void *Ut, int32_t d, int32_t V, as_dtype wdtype);
-// rows_dev: the number of rows, at most `rows`, read on the device (persistent kernel only)
+// range: which rows of prev and logits_out, at most `rows`, read on the device (persistent kernel only)
 as_status launch_bigram_logits(as_ctx *ctx, const as_model *m, const int32_t *prev,
-                               int64_t rows, void *logits_out, int64_t ld, const int32_t *rows_dev = nullptr);
+                               int64_t rows, void *logits_out, int64_t ld, RowRange range = RowRange{});
 
 // Rows of a decode that condition on the same token have the same logits: one row of them is computed for each
-// token in use, and the rows are told which.  The tables live in the context's decode state.
+// token in use, and the rows are told which.  Where a decode comes back to most of its tokens, the rows are kept from
+// step to step and only those of new tokens are computed.  The tables live in the context's decode state.
 struct RowShare {
-    int32_t *mark = nullptr;     // [V] last step that used the token
+    int32_t *mark = nullptr;     // [V] last step that used the token (kept rows: 0 where the token has one)
     int32_t *slot = nullptr;     // [V] its logits row in that step
-    int32_t *token = nullptr;    // [R] token of each logits row
-    int32_t *count = nullptr;    // [T] logits rows of each step
-    int32_t *fill = nullptr;     // [V] rows of each logits row, then where the next of them goes in `order`
+    int32_t *token = nullptr;    // [logits rows] token of each logits row
+    int32_t *count = nullptr;    // [T + 1] logits rows of each step (kept rows: up to and including it)
+    int32_t *fill = nullptr;     // [logits rows] rows of each logits row, then where the next of them goes in `order`
     int32_t *order = nullptr;    // [R] the rows sorted by logits row
+    int32_t kept = 0;            // the number of rows that are kept, or 0
 };
 bool mfma_applies(const as_model *m);
 bool small_decode_applies(const as_ctx *ctx, const as_model *m, int64_t rows, float temp);
@@ -274,6 +288,14 @@ bool rows_on_device(const as_ctx *ctx, const as_model *m);
 as_status launch_share_clear(as_ctx *ctx, const RowShare &s, int32_t T);
 as_status launch_share(as_ctx *ctx, const RowShare &s, int32_t step, const int32_t *prev, int64_t rows,
                        int32_t *row_ids, bool sorted);
+// kept rows: those of new tokens among prev[0 .. rows)
+as_status launch_claim(as_ctx *ctx, const RowShare &s, int32_t step, const int32_t *prev, int64_t rows);
+as_status launch_share_map(as_ctx *ctx, const RowShare &s, int32_t step, const int32_t *prev, int64_t rows,
+                           int32_t *row_ids, bool sorted);
+bool keeping_pays(const as_ctx *ctx, const as_model *m, int64_t rows, int64_t prompts, int32_t T, int64_t row_bytes,
+                  bool by_sums);
+bool step_by_sums(const as_ctx *ctx, float temp);
+as_status launch_row_select(as_ctx *ctx, const SelectArgs &a);
 // the same for the positions of an encode (prev < 0: none): rows claimed, counted and scanned, the order left to the caller
 as_status launch_claim_positions(as_ctx *ctx, const RowShare &s, const int32_t *prev, int64_t rows, int32_t *row_ids);
 

@@ -646,13 +646,6 @@ as_status launch_positions_order(as_ctx *ctx, const Positions &w, int64_t max_ro
     return AS_OK;
 }
 
-bool interval_by_sums(const as_ctx *ctx, float temp)
-{
-    const int epv = ctx->dtype == AS_BF16 ? 8 : 4;
-    return ctx->V % epv == 0 && ctx->V / epv <= kTileWaves * kTileIters * 64 && ctx->step_shape == 0 &&
-           1.44269504088896340736f / temp <= kTileMaxScale;
-}
-
 as_status launch_interval_chunk(as_ctx *ctx, const ChunkArgs &a, bool by_sums)
 {
     // (how many positions a chunk's rows have, the device knows: blocks for all of them, or as many as the chip holds)

@@ -41,7 +41,8 @@ __global__ __launch_bounds__(256) void share_clear_kernel(RowShare s, int32_t V,
 // The first row to come with a token takes the next logits row for it: one addition to the step's counter per block
 // (65536 of them on one address would take longer than the product they save).  Which row a token gets differs
 // from run to run; what is in it does not.
-// SKIP: a negative token is no token.
+// Kept rows (s.kept) are claimed once a decode: `mark` then says that the token has a row, and the counter goes on from
+// the step before.  SKIP: a negative token is no token.
 template <bool SKIP>
 __global__ __launch_bounds__(1024) void share_claim_kernel(RowShare s, int32_t step, int32_t V, const int32_t *prev,
                                                            int64_t rows)
@@ -49,14 +50,18 @@ __global__ __launch_bounds__(1024) void share_claim_kernel(RowShare s, int32_t s
     __shared__ int32_t wave_n[16], block_at;
     const int64_t r = (int64_t)blockIdx.x * 1024 + threadIdx.x;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int32_t stamp = s.kept ? 0 : step;
     bool mine = false;
     int32_t v = 0;
     if (r < rows && (!SKIP || prev[r] >= 0)) {
         v = clamp_token(prev[r], V);
         // (looked at first: the rows that have ended all come with one token)
-        if (__hip_atomic_load(&s.mark[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != step)
-            mine = atomicExch(&s.mark[v], step) != step;
+        if (__hip_atomic_load(&s.mark[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != stamp)
+            mine = atomicExch(&s.mark[v], stamp) != stamp;
     }
+    // (kept rows: counted anew each step)
+    if (s.fill != nullptr)
+        for (int64_t i = r; i < s.kept; i += (int64_t)gridDim.x * 1024) s.fill[i] = 0;
     const unsigned long long m = __ballot(mine);
     if (lane == 0) wave_n[wave] = __builtin_popcountll(m);
     __syncthreads();
@@ -74,15 +79,16 @@ __global__ __launch_bounds__(1024) void share_claim_kernel(RowShare s, int32_t s
         const int32_t at = block_at + wave_n[wave] + __builtin_popcountll(m & ((1ull << lane) - 1ull));
         s.slot[v] = at;
         s.token[at] = v;
-        s.fill[at] = 0;
+        if (!s.kept) s.fill[at] = 0;
     }
 }
 
 template <bool SORTED, bool SKIP>
-__global__ __launch_bounds__(256) void share_map_kernel(RowShare s, int32_t V, const int32_t *prev, int64_t rows,
-                                                        int32_t *row_ids)
+__global__ __launch_bounds__(256) void share_map_kernel(RowShare s, int32_t step, int32_t V, const int32_t *prev,
+                                                        int64_t rows, int32_t *row_ids)
 {
     const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (s.kept && r == 0) s.count[step + 1] = s.count[step];
     if (r >= rows) return;
     if (SKIP && prev[r] < 0) {
         row_ids[r] = -1;
@@ -225,7 +231,7 @@ __global__ __launch_bounds__(512, 1) void bigram_gemm_persistent(const uint16_t 
                                                                  const int32_t *__restrict__ prev, int64_t R,
                                                                  int32_t V, int32_t d, float alpha,
                                                                  OutT *__restrict__ C, int64_t ldc, int vec_store,
-                                                                 int gm, const int32_t *__restrict__ rows_dev)
+                                                                 int gm, RowRange range)
 {
     __shared__ __attribute__((aligned(1024))) unsigned char smem[kPersistLds];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -238,9 +244,12 @@ __global__ __launch_bounds__(512, 1) void bigram_gemm_persistent(const uint16_t 
     // column tiles at the same time, so a Ut tile is fetched into that XCD's L2 once.  With more row tiles
     // than workers, the W workers of an XCD stand gm x W/gm over row and column tiles: what they have open
     // at one time, gm A tiles and W/gm Ut tiles, has to fit that XCD's L2 or every tile refetches both.
-    if (rows_dev != nullptr) {
-        R = *rows_dev;
+    if (range.end != nullptr) {
+        const int64_t first = range.begin ? *range.begin : 0;
+        R = *range.end - first;
         if (R <= 0) return;
+        prev += first;
+        C += first * ldc * (FUSED ? 2 : 1);
     }
     const int64_t m_blocks = (R + PM - 1) / PM;
     const int64_t n_blocks = ((int64_t)V + PN - 1) / PN;
@@ -1202,6 +1211,35 @@ static int64_t tile_rounds(int64_t m, int64_t n_blocks, int W, int gm)
     return (nbx + W / m - 1) / (W / m);
 }
 
+// Whether a decode keeps logits rows from step to step.  With tokens spread evenly over the vocabulary (the worst case)
+// U = V(1 - exp(-rows (T - 1)/V)) rows are computed after the first step; what that spares is rows of product, at 1 PFLOP/s, and, where the
+// steps work from sums (by_sums), a pass over a logits row (5 TB/s, at least 4 ns) per row of codes less one per logits
+// row computed and 0.5 ns a code.  It costs the claims and a launch more, 18 us while steps still meet new tokens (about
+// 6 V/rows of them) and 3 after.  us a step, without / with, bf16, V = 32128, d = 512: 8192 rows T = 4 285 / 212,
+// T = 16 325 / 117; 65536 rows T = 16 1275 / 153.  V = 8000, d = 512:
+// 2048 rows T = 4 31.4 / 38.2, T = 16 33.6 / 31.6; 4096 rows T = 4 51.6 / 44.9.  V = 2000, d = 128: 1024 rows T = 64 15.1 /
+// 15.5, 2048 20.9 / 13.8.  Not by sums, V = 5001, d = 512: 2048 rows T = 16 39.0 / 42.1, T = 64 37.5 / 31.6; 8192 rows
+// T = 4 91.7 / 86.5.  Group masses, V = 32128: 16384 rows T = 16 485 / 182; V = 4096: 1024 rows
+// T = 64 23.8 / 24.2.
+// The table has at most four times the rows of one step, which a decode without it has, and those beyond within 4 GiB.
+bool keeping_pays(const as_ctx *ctx, const as_model *m, int64_t rows, int64_t prompts, int32_t T, int64_t row_bytes,
+                  bool by_sums)
+{
+    if (T < 3 || !rows_on_device(ctx, m)) return false;
+    const double V = (double)m->V, R = (double)rows;
+    const double steps = T - 1, used = R * steps + (double)prompts;
+    const double most = used < V ? used : V;
+    if (most > 4.0 * R || (most > R && most * (double)row_bytes > 4.0 * 1024.0 * 1024.0 * 1024.0)) return false;
+    const double computed = V * (1.0 - exp(-R * steps / V)) / steps;           // logits rows a step
+    double spared = (R - computed) * V * (double)m->d * 2.0 / 1e15;
+    if (by_sums) {
+        const double pass = V * (ctx->dtype == AS_BF16 ? 2.0 : 4.0) / 5e12;
+        spared += R * ((pass > 4e-9 ? pass : 4e-9) - 0.5e-9) - computed * pass;
+    }
+    const double meeting = 6.0 * V / (R * steps);
+    return spared > 3e-6 + 15e-6 * (meeting < 1.0 ? meeting : 1.0);
+}
+
 // Whether the logits kernel that takes the model can read the number of rows on the device (the persistent one).
 bool rows_on_device(const as_ctx *ctx, const as_model *m)
 {
@@ -1238,17 +1276,24 @@ as_status launch_share_clear(as_ctx *ctx, const RowShare &s, int32_t T)
     return AS_OK;
 }
 
-as_status launch_share(as_ctx *ctx, const RowShare &s, int32_t step, const int32_t *prev, int64_t rows,
-                       int32_t *row_ids, bool sorted)
+as_status launch_claim(as_ctx *ctx, const RowShare &s, int32_t step, const int32_t *prev, int64_t rows)
 {
-    const dim3 blocks((unsigned)((rows + 255) / 256));
     hipLaunchKernelGGL(share_claim_kernel<false>, dim3((unsigned)((rows + 1023) / 1024)), dim3(1024), 0, ctx->stream, s, step,
                        ctx->V, prev, rows);
     AS_HIP_TRY(ctx, hipGetLastError());
+    return AS_OK;
+}
+
+as_status launch_share_map(as_ctx *ctx, const RowShare &s, int32_t step, const int32_t *prev, int64_t rows,
+                           int32_t *row_ids, bool sorted)
+{
+    const dim3 blocks((unsigned)((rows + 255) / 256));
     if (!sorted) {
-        hipLaunchKernelGGL((share_map_kernel<false, false>), blocks, dim3(256), 0, ctx->stream, s, ctx->V, prev, rows, row_ids);
+        hipLaunchKernelGGL((share_map_kernel<false, false>), blocks, dim3(256), 0, ctx->stream, s, step, ctx->V, prev, rows,
+                           row_ids);
     } else {
-        hipLaunchKernelGGL((share_map_kernel<true, false>), blocks, dim3(256), 0, ctx->stream, s, ctx->V, prev, rows, row_ids);
+        hipLaunchKernelGGL((share_map_kernel<true, false>), blocks, dim3(256), 0, ctx->stream, s, step, ctx->V, prev, rows,
+                           row_ids);
         AS_HIP_TRY(ctx, hipGetLastError());
         hipLaunchKernelGGL(share_scan_kernel, dim3(1), dim3(1024), 0, ctx->stream, s, step);
         AS_HIP_TRY(ctx, hipGetLastError());
@@ -1258,6 +1303,13 @@ as_status launch_share(as_ctx *ctx, const RowShare &s, int32_t step, const int32
     return AS_OK;
 }
 
+as_status launch_share(as_ctx *ctx, const RowShare &s, int32_t step, const int32_t *prev, int64_t rows,
+                       int32_t *row_ids, bool sorted)
+{
+    const as_status st = launch_claim(ctx, s, step, prev, rows);
+    return st != AS_OK ? st : launch_share_map(ctx, s, step, prev, rows, row_ids, sorted);
+}
+
 as_status launch_claim_positions(as_ctx *ctx, const RowShare &s, const int32_t *prev, int64_t rows, int32_t *row_ids)
 {
     as_status st = launch_share_clear(ctx, s, 1);
@@ -1265,7 +1317,7 @@ as_status launch_claim_positions(as_ctx *ctx, const RowShare &s, const int32_t *
     hipLaunchKernelGGL(share_claim_kernel<true>, dim3((unsigned)((rows + 1023) / 1024)), dim3(1024), 0, ctx->stream, s, 0,
                        ctx->V, prev, rows);
     AS_HIP_TRY(ctx, hipGetLastError());
-    hipLaunchKernelGGL((share_map_kernel<true, true>), dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, ctx->stream, s,
+    hipLaunchKernelGGL((share_map_kernel<true, true>), dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, ctx->stream, s, 0,
                        ctx->V, prev, rows, row_ids);
     AS_HIP_TRY(ctx, hipGetLastError());
     hipLaunchKernelGGL(share_scan_kernel, dim3(1), dim3(1024), 0, ctx->stream, s, 0);
@@ -1274,7 +1326,7 @@ as_status launch_claim_positions(as_ctx *ctx, const RowShare &s, const int32_t *
 }
 
 as_status launch_bigram_logits(as_ctx *ctx, const as_model *m, const int32_t *prev, int64_t rows,
-                               void *logits_out, int64_t ld, const int32_t *rows_dev)
+                               void *logits_out, int64_t ld, RowRange range)
 {
     if (rows == 0) return AS_OK;
     const float alpha = (float)((double)m->scale / sqrt((double)m->d));
@@ -1285,7 +1337,7 @@ as_status launch_bigram_logits(as_ctx *ctx, const as_model *m, const int32_t *pr
         // the persistent kernel addresses operand rows with 32-bit byte offsets and wants two K stages
         const bool persistent = ctx->gemm_shape != 1 && m->d >= 2 * PK && (int64_t)m->V * m->d * 2 < (1LL << 32) &&
                                 ctx->num_cus >= 8;
-        if (rows_dev == nullptr && thin_pays(ctx, m, rows)) {
+        if (range.end == nullptr && thin_pays(ctx, m, rows)) {
             if (ctx->dtype == AS_BF16)
                 launch_thin<uint16_t, false>(ctx, m, prev, rows, (uint16_t *)logits_out, ld, alpha, vec_store);
             else
@@ -1294,10 +1346,10 @@ as_status launch_bigram_logits(as_ctx *ctx, const as_model *m, const int32_t *pr
             const dim3 grid((unsigned)(8 * (ctx->num_cus / 8))), block(512);
             if (ctx->dtype == AS_BF16)
                 launch(ctx, kKernelLogits, bigram_gemm_persistent<uint16_t>, grid, block, 0, Ep, Up, prev, rows,
-                       m->V, m->d, alpha, (uint16_t *)logits_out, ld, vec_store, persistent_gm(ctx), rows_dev);
+                       m->V, m->d, alpha, (uint16_t *)logits_out, ld, vec_store, persistent_gm(ctx), range);
             else
                 launch(ctx, kKernelLogits, bigram_gemm_persistent<float>, grid, block, 0, Ep, Up, prev, rows, m->V,
-                       m->d, alpha, (float *)logits_out, ld, vec_store, persistent_gm(ctx), rows_dev);
+                       m->d, alpha, (float *)logits_out, ld, vec_store, persistent_gm(ctx), range);
         } else {
             // grid: 8 XCD lanes x ceil(column tiles / 8) x row tiles (see the kernel's tile mapping)
             const int64_t m_blocks = (rows + BM - 1) / BM, n_blocks = ((int64_t)m->V + BN - 1) / BN;
@@ -1334,11 +1386,11 @@ bool fused_path_applies(const as_ctx *ctx, const as_model *m)
 }
 
 as_status launch_bigram_partials(as_ctx *ctx, const as_model *m, const int32_t *prev, int64_t rows, float temp,
-                                 float2 *part, int64_t ldp, const int32_t *rows_dev)
+                                 float2 *part, int64_t ldp, RowRange range)
 {
     if (rows == 0) return AS_OK;
     const float alpha = (float)((double)m->scale / sqrt((double)m->d) * 1.44269504088896340736 / (double)temp);
-    if (rows_dev == nullptr && thin_pays(ctx, m, rows)) {
+    if (range.end == nullptr && thin_pays(ctx, m, rows)) {
         launch_thin<float, true>(ctx, m, prev, rows, reinterpret_cast<float *>(part), ldp, alpha, 0);
         AS_HIP_TRY(ctx, hipGetLastError());
         return AS_OK;
@@ -1346,7 +1398,7 @@ as_status launch_bigram_partials(as_ctx *ctx, const as_model *m, const int32_t *
     const dim3 grid((unsigned)(8 * (ctx->num_cus / 8))), block(512);
     launch(ctx, kKernelLogits, bigram_gemm_persistent<float, true>, grid, block, 0, (const uint16_t *)m->E,
            (const uint16_t *)m->Ut, prev, rows, m->V, m->d, alpha, reinterpret_cast<float *>(part), ldp, 0,
-           persistent_gm(ctx), rows_dev);
+           persistent_gm(ctx), range);
     AS_HIP_TRY(ctx, hipGetLastError());
     return AS_OK;
 }

@@ -20,63 +20,152 @@ __global__ __launch_bounds__(256, 4) void row_sums_kernel(RowSumsArgs a)
     constexpr int kShare = ITERS * 64;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t r = blockIdx.x;
-    if (a.rows_dev != nullptr && r >= *a.rows_dev) return;
+    const int64_t first = a.range.begin ? *a.range.begin : 0, end = a.range.end ? *a.range.end : first + gridDim.x;
     const int32_t nvec = a.V / EPV;
     const int32_t v0 = wave * kShare;
-    f32x4 *const my_sums = reinterpret_cast<f32x4 *>(a.sums + r * kRowSums + wave * ITERS);
-    if (v0 >= nvec) {                                        // past the row's end
-        if (lane < ITERS / 4) my_sums[lane] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (lane == 0) a.sums[r * kRowSums + kTileWaves * ITERS + wave] = kRefFloor;
-        return;
-    }
-    float thr = -__builtin_inff();
-    if constexpr (HAS_THR) thr = a.thr[r];
-    const unsigned char *const base =
-        reinterpret_cast<const unsigned char *>(reinterpret_cast<const T *>(a.logits) + r * a.ld) + (size_t)v0 * 16u;
-    int32_t mych = (nvec - v0 - lane + 63) >> 6;
-    mych = mych < 0 ? 0 : (mych > ITERS ? ITERS : mych);
-    const uint32_t off0 = (uint32_t)lane * 16u;
-    const uint32_t off_last = mych > 0 ? off0 + (uint32_t)(mych - 1) * 1024u : 0u;
-    u32x4 raw[ITERS];
+    // (as many blocks as rows, or as the chip holds a few times where only the device knows how many there are)
+    for (int64_t r = first + blockIdx.x; r < end; r += gridDim.x) {
+        f32x4 *const my_sums = reinterpret_cast<f32x4 *>(a.sums + r * kRowSums + wave * ITERS);
+        if (v0 >= nvec) {                                        // past the row's end
+            if (lane < ITERS / 4) my_sums[lane] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (lane == 0) a.sums[r * kRowSums + kTileWaves * ITERS + wave] = kRefFloor;
+            continue;
+        }
+        float thr = -__builtin_inff();
+        if constexpr (HAS_THR) thr = a.thr[r];
+        const unsigned char *const base =
+            reinterpret_cast<const unsigned char *>(reinterpret_cast<const T *>(a.logits) + r * a.ld) + (size_t)v0 * 16u;
+        int32_t mych = (nvec - v0 - lane + 63) >> 6;
+        mych = mych < 0 ? 0 : (mych > ITERS ? ITERS : mych);
+        const uint32_t off0 = (uint32_t)lane * 16u;
+        const uint32_t off_last = mych > 0 ? off0 + (uint32_t)(mych - 1) * 1024u : 0u;
+        u32x4 raw[ITERS];
 #pragma unroll
-    for (int j = 0; j < ITERS; ++j) {
-        uint32_t off = off0 + (uint32_t)j * 1024u;
-        off = off < off_last ? off : off_last;
-        if constexpr (NT) raw[j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(base + off));
-        else raw[j] = *reinterpret_cast<const u32x4 *>(base + off);
+        for (int j = 0; j < ITERS; ++j) {
+            uint32_t off = off0 + (uint32_t)j * 1024u;
+            off = off < off_last ? off : off_last;
+            if constexpr (NT) raw[j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(base + off));
+            else raw[j] = *reinterpret_cast<const u32x4 *>(base + off);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        float rw;
+        if (v0 + kShare <= nvec) {
+            rw = tile_reference<DT, HAS_THR, false>(raw[0], a.k, thr, mych);
+            tile_chunk_sums<DT, HAS_THR, false>(raw, a.k, rw, thr, mych, lane, my_sums);
+        } else {
+            rw = tile_reference<DT, HAS_THR, true>(raw[0], a.k, thr, mych);
+            tile_chunk_sums<DT, HAS_THR, true>(raw, a.k, rw, thr, mych, lane, my_sums);
+        }
+        if (lane == 0) a.sums[r * kRowSums + kTileWaves * ITERS + wave] = rw;
     }
-    __builtin_amdgcn_sched_barrier(0);
-    float rw;
-    if (v0 + kShare <= nvec) {
-        rw = tile_reference<DT, HAS_THR, false>(raw[0], a.k, thr, mych);
-        tile_chunk_sums<DT, HAS_THR, false>(raw, a.k, rw, thr, mych, lane, my_sums);
-    } else {
-        rw = tile_reference<DT, HAS_THR, true>(raw[0], a.k, thr, mych);
-        tile_chunk_sums<DT, HAS_THR, true>(raw, a.k, rw, thr, mych, lane, my_sums);
+}
+
+// The sampling step of step_tile_kernel from those sums, bit for bit: a wave per code reads its row's sums, scans them,
+// and reads the one KiB of logits that holds the code.  Bound by its ~400 vector instructions a code: 65536 codes 51 us
+// (step_tile_kernel over the same rows, read in the order of the rows, 440).
+template <int DT>
+__global__ __launch_bounds__(256) void row_select_kernel(SelectArgs q)
+{
+    using T = typename Elem<DT>::T;
+    constexpr int EPV = Elem<DT>::kPerVec;
+    constexpr int NW = kTileWaves, ITERS = kTileIters;
+    __shared__ GenericScratch gen;
+    __shared__ bool slow[NW];
+    __shared__ int32_t slow_row[NW];
+    const StepArgs &a = q.step;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (blockIdx.x == 0 && threadIdx.x == 0) q.count[1] = q.count[0];
+    const int64_t r = (int64_t)blockIdx.x * NW + wave;
+    const int32_t nvec = a.V / EPV;
+    const float k = a.k;
+    bool beyond = false;
+    int32_t row = 0;
+    if (r < a.rows) {
+        if (a.finished_in != nullptr && a.finished_in[r] != 0) {
+            if (lane == 0) write_finished(a, r);
+        } else {
+            const float code = a.codes[r];
+            row = q.slot[clamp_token(q.prev[r], a.V)];
+            const float *const sums = q.sums + (int64_t)row * kRowSums;
+            const float csum = sums[lane], my_ref = sums[NW * ITERS + lane / ITERS];
+            float R = my_ref;
+            R = fmaxf(fmaxf(read_lane(R, 0), read_lane(R, 16)), fmaxf(read_lane(R, 32), read_lane(R, 48)));
+            const double cv = (double)ldexpf(csum, shift_of(my_ref, R));
+            const double cincl = wave_scan_add(cv);
+            const double S = read_lane(cincl, 63);
+            if (!(S < (double)__builtin_inff())) {
+                beyond = true;               // weights beyond fp32, or NaN in the data: the plain routine, below
+            } else {
+                const double tau = (double)code * S;
+                const unsigned long long chit = __ballot(cincl > tau);
+                const unsigned long long cnz = __ballot(cv > 0.0);
+                const int ch = chit ? (__ffsll((long long)chit) - 1) : (cnz ? (63 - __clzll((long long)cnz)) : 0);
+                const double run = read_lane(cincl - cv, ch);
+                const float rw = read_lane(my_ref, ch);
+                const bool inside = ch * 64 + lane < nvec;
+                const u32x4 *const vecs = reinterpret_cast<const u32x4 *>(reinterpret_cast<const T *>(a.logits) + row * a.ld);
+                const u32x4 hv = vecs[inside ? ch * 64 + lane : 0];
+                float cl = tile_lane_sum<DT, false>(hv, k, -rw, 0.f);
+                cl = inside ? cl : 0.f;
+                tile_finish<DT, false>(a, r, 0.f, hv, cl, rw, shift_of(rw, R), tau, run, S, ch * 64, lane);
+            }
+        }
     }
-    if (lane == 0) a.sums[r * kRowSums + kTileWaves * ITERS + wave] = rw;
+    if (!__syncthreads_or(beyond)) return;
+    if (lane == 0) {
+        slow[wave] = beyond;
+        slow_row[wave] = row;
+    }
+    __syncthreads();
+    for (int w = 0; w < NW; ++w) {
+        if (!slow[w]) continue;              // block-uniform
+        StepArgs one = a;                    // row r of the call on the logits row of its token
+        one.logits = reinterpret_cast<const T *>(a.logits) + ((int64_t)slow_row[w] - ((int64_t)blockIdx.x * NW + w)) * a.ld;
+        one.row_ids = nullptr;
+        generic_step_row<T>(one, (int64_t)blockIdx.x * NW + w, -__builtin_inff(), gen);
+        __syncthreads();
+    }
 }
 
 }  // namespace
 
 static_assert(kRowSums == kTileWaves * kTileIters + kTileWaves, "the chunk sums and the waves' references");
 
-as_status launch_row_sums(as_ctx *ctx, const RowSumsArgs &a, int64_t rows)
+as_status launch_row_sums(as_ctx *ctx, int kid, const RowSumsArgs &a, int64_t rows)
 {
     if (rows == 0) return AS_OK;
-    const dim3 grid((unsigned)rows), block(256);
+    const int64_t most = 16 * (int64_t)ctx->num_cus;
+    const dim3 grid((unsigned)(a.range.end && rows > most ? most : rows)), block(256);
     const bool nt = stream_rows(rows, a.ld, a.dtype == AS_BF16 ? 2 : 4);
 #define AS_ROW_SUMS(DT_)                                                                                       \
     do {                                                                                                       \
-        if (a.thr && nt) launch(ctx, kKernelInterval, row_sums_kernel<DT_, true, true>, grid, block, 0, a);    \
-        else if (a.thr) launch(ctx, kKernelInterval, row_sums_kernel<DT_, true, false>, grid, block, 0, a);    \
-        else if (nt) launch(ctx, kKernelInterval, row_sums_kernel<DT_, false, true>, grid, block, 0, a);       \
-        else launch(ctx, kKernelInterval, row_sums_kernel<DT_, false, false>, grid, block, 0, a);              \
+        if (a.thr && nt) launch(ctx, kid, row_sums_kernel<DT_, true, true>, grid, block, 0, a);    \
+        else if (a.thr) launch(ctx, kid, row_sums_kernel<DT_, true, false>, grid, block, 0, a);    \
+        else if (nt) launch(ctx, kid, row_sums_kernel<DT_, false, true>, grid, block, 0, a);       \
+        else launch(ctx, kid, row_sums_kernel<DT_, false, false>, grid, block, 0, a);              \
     } while (0)
     if (a.dtype == AS_BF16) AS_ROW_SUMS(AS_BF16);
     else AS_ROW_SUMS(AS_F32);
 #undef AS_ROW_SUMS
+    AS_HIP_TRY(ctx, hipGetLastError());
+    return AS_OK;
+}
+
+// rows that step_tile_kernel would take
+bool step_by_sums(const as_ctx *ctx, float temp)
+{
+    const int epv = ctx->dtype == AS_BF16 ? 8 : 4;
+    return ctx->V % epv == 0 && ctx->V / epv <= kTileWaves * kTileIters * 64 && ctx->step_shape == 0 &&
+           1.44269504088896340736f / temp <= kTileMaxScale;
+}
+
+as_status launch_row_select(as_ctx *ctx, const SelectArgs &a)
+{
+    if (a.step.rows == 0) return AS_OK;
+    const dim3 grid((unsigned)((a.step.rows + kTileWaves - 1) / kTileWaves)), block(256);
+    if (a.step.dtype == AS_BF16) launch(ctx, kKernelStep, row_select_kernel<AS_BF16>, grid, block, 0, a);
+    else launch(ctx, kKernelStep, row_select_kernel<AS_F32>, grid, block, 0, a);
     AS_HIP_TRY(ctx, hipGetLastError());
     return AS_OK;
 }

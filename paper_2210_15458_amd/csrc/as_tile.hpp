@@ -179,6 +179,56 @@ __device__ __forceinline__ void tile_chunk_sums(const u32x4 (&raw)[kTileIters], 
     }
 }
 
+// The wave that holds the code's chunk: hv its lanes' vectors of the chunk (vector vec0 + lane of the row), cl their sums
+// (0 past the row's end), both relative to rw; run the mass before the chunk.  Finds the lane, that lane the element, and
+// writes the row's results.
+template <int DT, bool HAS_THR>
+__device__ __forceinline__ void tile_finish(const StepArgs &a, int64_t r, float thr, const u32x4 &hv, float cl, float rw,
+                                            int shf, double tau, double run, double S, int32_t vec0, int lane)
+{
+    constexpr int EPV = Elem<DT>::kPerVec;
+    const double lv = (double)ldexpf(cl, shf);
+    const double incl2 = wave_scan_add(lv) + run;
+    const unsigned long long hit2 = __ballot(incl2 > tau);
+    const unsigned long long nz2 = __ballot(lv > 0.0);
+    const int l2 = hit2 ? (__ffsll((long long)hit2) - 1) : (nz2 ? (63 - __clzll((long long)nz2)) : 0);
+    if (lane != l2) return;
+
+    float x[EPV];
+    unpack<DT>(hv, x);
+    double ed[EPV];
+#pragma unroll
+    for (int i = 0; i < EPV; ++i) {
+        float e = fast_exp2(fmaf(x[i], a.k, -rw));
+        if constexpr (HAS_THR) e = (x[i] >= thr) ? e : 0.f;
+        ed[i] = (double)ldexpf(e, shf);
+    }
+    double acc = incl2 - lv;
+    int ih = -1, ilast = 0;
+    double before = acc, before_last = acc, ev = 0.0, ev_last = 0.0;
+#pragma unroll
+    for (int i = 0; i < EPV; ++i) {
+        if (ed[i] > 0.0) { ilast = i; before_last = acc; ev_last = ed[i]; }
+        if (ih < 0 && acc + ed[i] > tau) { ih = i; before = acc; ev = ed[i]; }
+        acc += ed[i];
+    }
+    if (ih < 0) { ih = ilast; before = before_last; ev = ev_last; }
+
+    int64_t tok64 = ((int64_t)vec0 + lane) * EPV + ih;
+    if (tok64 > a.V - 1) tok64 = a.V - 1;
+    RowOut o;
+    o.token = (int32_t)tok64;
+    o.c_next = rescale_code(tau, before, ev);
+    o.prob = 0.f;
+    o.f_lo = 0.f;
+    if (a.prob_out || a.flo_out) {          // records for tests and callers that ask: fp32 quotients of fp64 sums
+        const float Sf = (float)S;
+        o.prob = (float)ev / Sf;
+        o.f_lo = (float)before / Sf;
+    }
+    write_row(a, r, o);
+}
+
 // After the barrier that follows the chunk sums: every wave scans the row's 64 chunk sums (fp64) for the total,
 // the target c*S and the chunk that holds it; the wave that owns that chunk finds the lane, that lane the
 // element, and writes the row's results.  Every thread of the block calls it.  rw is the calling wave's own
@@ -189,7 +239,6 @@ __device__ __forceinline__ void tile_select(const StepArgs &a, int64_t r, float 
                                             int32_t v0, int lane, int wave, const TileSums &ts, GenericScratch &gen)
 {
     using T = typename Elem<DT>::T;
-    constexpr int EPV = Elem<DT>::kPerVec;
     constexpr int NW = kTileWaves, ITERS = kTileIters;
     const float k = a.k;
     float R = ts.share_ref[0];
@@ -228,46 +277,7 @@ __device__ __forceinline__ void tile_select(const StepArgs &a, int64_t r, float 
     // that let a row have eight waves)
     float cl = tile_lane_sum<DT, HAS_THR>(hv, k, -rw, thr);
     if (ragged) cl = cj < mych ? cl : 0.f;
-    const double lv = (double)ldexpf(cl, shf);
-    const double incl2 = wave_scan_add(lv) + run;
-    const unsigned long long hit2 = __ballot(incl2 > tau);
-    const unsigned long long nz2 = __ballot(lv > 0.0);
-    const int l2 = hit2 ? (__ffsll((long long)hit2) - 1) : (nz2 ? (63 - __clzll((long long)nz2)) : 0);
-    if (lane != l2) return;
-
-    float x[EPV];
-    unpack<DT>(hv, x);
-    double ed[EPV];
-#pragma unroll
-    for (int i = 0; i < EPV; ++i) {
-        float e = fast_exp2(fmaf(x[i], k, -rw));
-        if constexpr (HAS_THR) e = (x[i] >= thr) ? e : 0.f;
-        ed[i] = (double)ldexpf(e, shf);
-    }
-    double acc = incl2 - lv;
-    int ih = -1, ilast = 0;
-    double before = acc, before_last = acc, ev = 0.0, ev_last = 0.0;
-#pragma unroll
-    for (int i = 0; i < EPV; ++i) {
-        if (ed[i] > 0.0) { ilast = i; before_last = acc; ev_last = ed[i]; }
-        if (ih < 0 && acc + ed[i] > tau) { ih = i; before = acc; ev = ed[i]; }
-        acc += ed[i];
-    }
-    if (ih < 0) { ih = ilast; before = before_last; ev = ev_last; }
-
-    int64_t tok64 = ((int64_t)v0 + (int64_t)cj * 64 + lane) * EPV + ih;
-    if (tok64 > a.V - 1) tok64 = a.V - 1;
-    RowOut o;
-    o.token = (int32_t)tok64;
-    o.c_next = rescale_code(tau, before, ev);
-    o.prob = 0.f;
-    o.f_lo = 0.f;
-    if (a.prob_out || a.flo_out) {          // records for tests and callers that ask: fp32 quotients of fp64 sums
-        const float Sf = (float)S;
-        o.prob = (float)ev / Sf;
-        o.f_lo = (float)before / Sf;
-    }
-    write_row(a, r, o);
+    tile_finish<DT, HAS_THR>(a, r, thr, hv, cl, rw, shf, tau, run, S, v0 + cj * 64, lane);
 }
 
 }  // namespace

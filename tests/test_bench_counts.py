@@ -12,7 +12,17 @@ def test_rows_of_a_decode_with_and_without_sharing():
     assert own == {"active": (6 + 6 + 4 + 4) / 4, "computed": (2 + 6 + 6 + 6) / 4, "fetched": (2 + 6 + 4 + 4) / 4}
     # tokens conditioned on: {5, 6, 9}, {5, 1, 6, 8}, {7, 1, 8}; by rows still running the last two lose EOS
     shared = bench.step_counts(tokens, 1, 2, True)
+    kept = bench.step_counts(tokens, 1, 2, False, True)
+    assert kept == {"active": 5.0, "computed": (2 + 3 + 3 + 0) / 4, "fetched": (2 + 3 + 3 + 2) / 4}
     assert shared == {"active": 5.0, "computed": (2 + 3 + 4 + 3) / 4, "fetched": (2 + 3 + 3 + 2) / 4}
+
+
+def test_rows_are_kept_where_most_come_again():
+    def kept(V, d, R, T, by_sums=True):
+        return bench.rows_kept(V, d, R, 1, T, "bf16", V * 2, by_sums)
+    assert kept(32128, 512, 65536, 16) and kept(32128, 512, 8192, 4) and kept(8000, 512, 2048, 16) and kept(2000, 128, 2048, 64)
+    assert not kept(32128, 512, 1024, 64) and not kept(8000, 512, 2048, 4) and not kept(2000, 128, 1024, 64)
+    assert not kept(5001, 512, 2048, 16, False) and kept(5001, 512, 2048, 64, False)
 
 
 def test_sharing_pays_for_wide_lattices_only():

@@ -934,190 +934,176 @@ void launch_thin(as_ctx *ctx, const as_model *m, const int32_t *prev, int64_t ro
                m->d, alpha, out, ld, vec_store);
 }
 
-// ---- vector kernel: what the MFMA kernels do not take (fp32 weights, or a rank d that is not a multiple of
-// their K step), any size and alignment ------------------------------------------------------------------
+// ---- chain kernel: what the bf16 MFMA kernels do not take (fp32 weights, or a rank d that is not a multiple of their K
+// step), any size and alignment -----------------------------------------------------------------------------
 //
-// Every logit is one fp32 fused-multiply-add chain over k in ascending order, from zero.  The matrix pipes could
-// run the fp32 products, but not in that order, and the chain is what keeps a logit the same whatever tile it is
-// computed in.  So the bound is the vector FMA rate (one wave64 FMA per 4 cycles and SIMD), and the kernel's job is
-// to feed it: block tile 16*TM x 16*TN over K steps of 32, a thread TM x TN outputs in registers, operands through
-// LDS with K along the rows (a thread's 4 consecutive rows or columns are one 16-byte read; within a wave 4
-// distinct A pieces are broadcast and 16 B pieces lie in consecutive banks), the next K step's elements in
-// registers while this one is worked on (four K steps in the small form, whose blocks run one to a SIMD and have
-// nothing else to hide a load behind).  One launch in fp32, against the form before it (one thread per logit, both
-// operands from the caches at every k): 256 x 4100 x 128 12.1 us against 426, 64 x 1000 x 100 8.4 against 18.4,
-// 1024 x 32128 x 512 482 us against 73 ms (70 TFLOP/s, 89 % of the FMA rate), 64 x 16 x 8 3.9 either way.
-constexpr int VK = 32;
+// Every logit is one fp32 fused-multiply-add chain over k in ascending order, from zero, which keeps it the same whatever
+// tile it is computed in.  v_mfma_f32_16x16x4_f32 adds its four products to the accumulator one after the other, each
+// rounded (the chain bit for bit: tests/test_gpu_logits_shapes.py), at twice the rate of vector fused multiply-adds and
+// with an operand register a lane for 16 x 16 x 4 products.  So operands hardly matter and a block is plain: 4 waves as
+// GM x GN, a wave TM x TN tiles of 16 x 16, K steps of KS through one LDS buffer, the next step's elements in registers
+// meanwhile.  MFMA s of a group of 16 k takes k = 4 s + q from the lanes of quarter q: LDS holds a row's group as four
+// 16-byte pieces, piece q its k = q, q + 4, q + 8, q + 12, so that one read feeds four MFMAs; rows are padded by 16
+// bytes (conflict-free for the reads' and the whole pieces' 16 lanes).
 __device__ __forceinline__ float widen(float x) { return x; }
 __device__ __forceinline__ float widen(uint16_t h) { return __builtin_bit_cast(float, (uint32_t)h << 16); }
 
-template <class WT, class OutT, int TM, int TN>
-__global__ __launch_bounds__(256) void bigram_gemm_vec(const WT *__restrict__ E, const WT *__restrict__ Ut,
-                                                       const int32_t *__restrict__ prev, int64_t R, int32_t V,
-                                                       int32_t d, float alpha, OutT *__restrict__ C, int64_t ldc)
+// WHOLE: rows start on 16 bytes and the rank is a multiple of 16: a thread moves 16 consecutive k of a row at a time
+// (otherwise single elements, consecutive threads consecutive k)
+template <class WT, class OutT, int GM, int GN, int TM, int TN, int KS, int AHEAD, bool WHOLE>
+__global__ __launch_bounds__(256) void bigram_gemm_chain(const WT *__restrict__ E, const WT *__restrict__ Ut,
+                                                         const int32_t *__restrict__ prev, int64_t R, int32_t V,
+                                                         int32_t d, float alpha, OutT *__restrict__ C, int64_t ldc)
 {
-    static_assert(TM % 4 == 0 && TN % 4 == 0, "a thread's outputs come in runs of 4");
-    constexpr int MT = 16 * TM, NT = 16 * TN, MI = MT / 8, NI = NT / 8;
-    constexpr int AHEAD = TM == 4 ? 4 : 1;                    // K steps requested ahead of the one worked on
-    constexpr int KB = TM == 4 ? 4 : 1;
     typedef float f32x4 __attribute__((ext_vector_type(4)));
-    __shared__ __attribute__((aligned(16))) float sA[VK][MT + 4], sB[VK][NT + 4];
-    const int tid = threadIdx.x;
+    static_assert(GM * GN == 4, "four waves");
+    constexpr int MT = GM * TM * 16, NT = GN * TN * 16, ROWS = MT + NT;
+    constexpr int kGroups = KS / 16, kStride = KS * 4 + 16;
+    // what a thread moves per K step: runs of 16 k, or elements
+    constexpr int kUnits = WHOLE ? ROWS * kGroups : ROWS * KS, kMine = (kUnits + 255) / 256, kRun = WHOLE ? 16 : 1;
+    __shared__ __attribute__((aligned(16))) unsigned char smem[ROWS * kStride];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t m0 = (int64_t)blockIdx.x * MT, n0 = (int64_t)blockIdx.y * NT;
 
-    // loader: element k = tid & 31 of tile rows (tid >> 5) + 8*i
-    const int lk = tid & 31, lr = tid >> 5;
-    const WT *pa[MI], *pb[NI];
+    const WT *src[kMine];                     // row starts; rows past the end repeat the last
+    int row_of[kMine], k_of[kMine];
 #pragma unroll
-    for (int i = 0; i < MI; ++i) {
-        int64_t m = m0 + lr + 8 * i;
-        if (m > R - 1) m = R - 1;
-        pa[i] = E + (int64_t)clamp_token(prev[m], V) * d;
+    for (int i = 0; i < kMine; ++i) {
+        const int u = tid + i * 256;
+        constexpr int kPerRow = KS / kRun;
+        row_of[i] = u / kPerRow;
+        k_of[i] = u % kPerRow * kRun;
+        if (kUnits % 256 != 0 && u >= kUnits) row_of[i] = ROWS - 1;
+        if (row_of[i] < MT) {
+            int64_t m = m0 + row_of[i];
+            if (m > R - 1) m = R - 1;
+            src[i] = E + (int64_t)clamp_token(prev[m], V) * d;
+        } else {
+            int64_t n = n0 + row_of[i] - MT;
+            if (n > V - 1) n = V - 1;
+            src[i] = Ut + n * d;
+        }
     }
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-        int64_t n = n0 + lr + 8 * i;
-        if (n > V - 1) n = V - 1;
-        pb[i] = Ut + n * d;
-    }
-    WT ra[AHEAD][MI], rb[AHEAD][NI];
+    WT raw[AHEAD][kMine][kRun];               // K steps requested ahead of the one worked on
     auto request = [&](int k0, auto slot_c) __attribute__((always_inline)) {
         constexpr int slot = decltype(slot_c)::value;
-        const int k = k0 + lk < d ? k0 + lk : d - 1;
 #pragma unroll
-        for (int i = 0; i < MI; ++i) ra[slot][i] = pa[i][k];
+        for (int i = 0; i < kMine; ++i) {
+            int k = k0 + k_of[i];
+            k = k < d ? k : d - kRun;         // (past the rank: anything, replaced by zeros)
+            if constexpr (WHOLE) {
+                constexpr int kPieces = 16 * (int)sizeof(WT) / 16;
 #pragma unroll
-        for (int i = 0; i < NI; ++i) rb[slot][i] = pb[i][k];
+                for (int q = 0; q < kPieces; ++q)
+                    reinterpret_cast<u32x4 *>(raw[slot][i])[q] = reinterpret_cast<const u32x4 *>(src[i] + k)[q];
+            } else {
+                raw[slot][i][0] = src[i][k];
+            }
+        }
     };
-    float acc[TM][TN];
+    auto land = [&](int k0, auto slot_c) __attribute__((always_inline)) {
+        constexpr int slot = decltype(slot_c)::value;
+#pragma unroll
+        for (int i = 0; i < kMine; ++i) {
+            if (kUnits % 256 != 0 && tid + i * 256 >= kUnits) continue;
+            const bool in = k0 + k_of[i] < d; // past the rank: zeros, which leave a chain as it is
+            unsigned char *const at = smem + row_of[i] * kStride + (k_of[i] / 16) * 64;
+            if constexpr (WHOLE) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    f32x4 v;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] = in ? widen(raw[slot][i][4 * e + q]) : 0.f;
+                    *reinterpret_cast<f32x4 *>(at + q * 16) = v;
+                }
+            } else {
+                const int k = k_of[i] & 15;
+                *reinterpret_cast<float *>(at + (k & 3) * 16 + (k >> 2) * 4) = in ? widen(raw[slot][i][0]) : 0.f;
+            }
+        }
+    };
+
+    const int wm = wave / GN, wn = wave % GN;
+    const unsigned char *const fa = smem + (wm * TM * 16 + (lane & 15)) * kStride + (lane >> 4) * 16;
+    const unsigned char *const fb = smem + (MT + wn * TN * 16 + (lane & 15)) * kStride + (lane >> 4) * 16;
+    f32x4 acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = 0.f;
-    const int tm = (tid >> 4) * 4, tn = (tid & 15) * 4;      // first row / column of the thread's runs
+        for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     auto step = [&](int k0, auto slot_c) __attribute__((always_inline)) {
-        constexpr int slot = decltype(slot_c)::value;
-        const bool in = k0 + lk < d;                          // past the rank: zeros, which leave a chain as it is
         if (k0 != 0) __syncthreads();
-#pragma unroll
-        for (int i = 0; i < MI; ++i) sA[lk][lr + 8 * i] = in ? widen(ra[slot][i]) : 0.f;
-#pragma unroll
-        for (int i = 0; i < NI; ++i) sB[lk][lr + 8 * i] = in ? widen(rb[slot][i]) : 0.f;
+        land(k0, slot_c);
         __syncthreads();
-        if (k0 + AHEAD * VK < d) request(k0 + AHEAD * VK, slot_c);
-        // KB values of k at a time, the next KB's pieces on their way from LDS meanwhile (left to itself the compiler
-        // reads one k, waits and multiplies: 230 cycles a k where the products take 64)
-        float xa[KB][TM], xb[KB][TN], ya[KB][TM], yb[KB][TN];
-        auto read = [&](float (&a)[KB][TM], float (&b)[KB][TN], int k) __attribute__((always_inline)) {
+        if (k0 + AHEAD * KS < d) request(k0 + AHEAD * KS, slot_c);
+        const int groups = d - k0 < KS ? (d - k0 + 15) / 16 : kGroups;
 #pragma unroll
-            for (int q = 0; q < KB; ++q) {
+        for (int g = 0; g < kGroups; ++g) {
+            if (g >= groups) break;           // uniform
+            f32x4 a[TM], b[TN];
 #pragma unroll
-                for (int g = 0; g < TM / 4; ++g) {
-                    const f32x4 v = *reinterpret_cast<const f32x4 *>(&sA[k + q][g * 64 + tm]);
+            for (int i = 0; i < TM; ++i) a[i] = *reinterpret_cast<const f32x4 *>(fa + i * 16 * kStride + g * 64);
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) a[q][4 * g + e] = v[e];
-                }
+            for (int j = 0; j < TN; ++j) b[j] = *reinterpret_cast<const f32x4 *>(fb + j * 16 * kStride + g * 64);
 #pragma unroll
-                for (int g = 0; g < TN / 4; ++g) {
-                    const f32x4 v = *reinterpret_cast<const f32x4 *>(&sB[k + q][g * 64 + tn]);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) b[q][4 * g + e] = v[e];
-                }
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        };
-        auto multiply = [&](const float (&a)[KB][TM], const float (&b)[KB][TN]) __attribute__((always_inline)) {
-#pragma unroll
-            for (int q = 0; q < KB; ++q)
+            for (int s = 0; s < 4; ++s)
 #pragma unroll
                 for (int i = 0; i < TM; ++i)
 #pragma unroll
-                    for (int j = 0; j < TN; ++j) acc[i][j] = fmaf(a[q][i], b[q][j], acc[i][j]);
-            __builtin_amdgcn_sched_barrier(0);
-        };
-        const int kn = d - k0 < VK ? d - k0 : VK;             // (2*KB at a time; the rest of the last ones are zeros)
-        read(xa, xb, 0);
-        for (int k = 0; k < kn; k += 2 * KB) {
-            read(ya, yb, k + KB);
-            multiply(xa, xb);
-            read(xa, xb, k + 2 * KB < VK ? k + 2 * KB : 0);
-            multiply(ya, yb);
+                    for (int j = 0; j < TN; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][s], b[j][s], acc[i][j], 0, 0, 0);
         }
     };
-    if constexpr (AHEAD == 4) {
-        request(0, std::integral_constant<int, 0>{});
-        request(VK, std::integral_constant<int, 1>{});
-        request(2 * VK, std::integral_constant<int, 2>{});
-        request(3 * VK, std::integral_constant<int, 3>{});
-        for (int k0 = 0; k0 < d; k0 += 4 * VK) {
+    request(0, std::integral_constant<int, 0>{});
+    if constexpr (AHEAD == 2) {
+        if (KS < d) request(KS, std::integral_constant<int, 1>{});
+        for (int k0 = 0; k0 < d; k0 += 2 * KS) {
             step(k0, std::integral_constant<int, 0>{});
-            if (k0 + VK < d) step(k0 + VK, std::integral_constant<int, 1>{});
-            if (k0 + 2 * VK < d) step(k0 + 2 * VK, std::integral_constant<int, 2>{});
-            if (k0 + 3 * VK < d) step(k0 + 3 * VK, std::integral_constant<int, 3>{});
+            if (k0 + KS < d) step(k0 + KS, std::integral_constant<int, 1>{});
         }
     } else {
-        request(0, std::integral_constant<int, 0>{});
-        for (int k0 = 0; k0 < d; k0 += VK) step(k0, std::integral_constant<int, 0>{});
+        for (int k0 = 0; k0 < d; k0 += KS) step(k0, std::integral_constant<int, 0>{});
     }
+    // register v of lane l is row 4 * (l / 16) + v, column l % 16 of its tile
 #pragma unroll
-    for (int i = 0; i < TM; ++i) {
-        const int64_t m = m0 + (i / 4) * 64 + tm + (i & 3);
-        if (m >= R) continue;
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const int64_t n = n0 + (j / 4) * 64 + tn + (j & 3);
-            if (n < V) C[m * ldc + n] = to_out<OutT>(acc[i][j] * alpha);
+        for (int v = 0; v < 4; ++v) {
+            const int64_t m = m0 + (wm * TM + i) * 16 + 4 * (lane >> 4) + v;
+            if (m >= R) continue;
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                const int64_t n = n0 + (wn * TN + j) * 16 + (lane & 15);
+                if (n < V) C[m * ldc + n] = to_out<OutT>(acc[i][j][v] * alpha);
+            }
         }
-    }
-}
-
-// The plain form of the same chain, one thread per logit, operands from the caches at every k: what is left to it are
-// products so small that the tiled kernel's barriers, and the microsecond that its launch takes longer to follow and to
-// be followed, cost more (dot_pays).
-template <class WT, class OutT>
-__global__ __launch_bounds__(256) void bigram_dot(const WT *__restrict__ E, const WT *__restrict__ Ut,
-                                                  const int32_t *__restrict__ prev, int64_t R, int32_t V,
-                                                  int32_t d, float alpha, OutT *__restrict__ C, int64_t ldc)
-{
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= R * V) return;
-    const int64_t r = idx / V, v = idx % V;
-    const WT *a = E + (int64_t)clamp_token(prev[r], V) * d, *b = Ut + v * d;
-    float acc = 0.f;
-    for (int k = 0; k < d; ++k) acc = fmaf(widen(a[k]), widen(b[k]), acc);
-    C[r * ldc + v] = to_out<OutT>(acc * alpha);
-}
-
-// us a decode step, plain / tiled.  fp32: 27 rows of 563, rank 11 9.5 / 10.4; 64 of 1001 9.6 / 10.7, but 128 of 2003 12.7 /
-// 11.1; 32 rows of 101 to 1001 0.88 to 0.94 of the time up to rank 26, 1.03 to 1.08 from 28 (up to 128 columns 0.90 to
-// 0.98 up to 38); ranks of a multiple of 8, whose rows meet in the cache, are even at 16 and 24 and lose 10 % at 32.
-// bf16, rows half as long: 64 of 1001, rank 33 11.0 / 12.0, rank 50 12.2 / 12.6, rank 72 19.6 / 13.5; 64 of 2003, rank
-// 33 13.9 / 12.2.
-static bool dot_pays(const as_model *m, int64_t rows)
-{
-    if (rows * m->V > 65536) return false;
-    if (m->wdtype == AS_BF16) return m->d <= 56;
-    return m->d <= (m->V <= 128 ? 38 : 26) && (m->d <= 16 || m->d % 8 != 0);
 }
 
 template <class WT, class OutT>
 void launch_vec(as_ctx *ctx, const as_model *m, const int32_t *prev, int64_t rows, void *out, int64_t ld, float alpha)
 {
-    if (dot_pays(m, rows)) {
-        launch(ctx, kKernelLogits, bigram_dot<WT, OutT>, dim3((unsigned)((rows * m->V + 255) / 256)), dim3(256), 0,
-               (const WT *)m->E, (const WT *)m->Ut, prev, rows, m->V, m->d, alpha, (OutT *)out, ld);
-        return;
-    }
-    // 128 x 128 tiles do twice the products per LDS byte of 64 x 64 ones; they pay once there are enough of
-    // them for two blocks on every CU
-    const dim3 big((unsigned)((rows + 127) / 128), (unsigned)((m->V + 127) / 128));
-    const dim3 small((unsigned)((rows + 63) / 64), (unsigned)((m->V + 63) / 64));
-    if ((int64_t)big.x * big.y >= 2 * (int64_t)ctx->num_cus)
-        launch(ctx, kKernelLogits, bigram_gemm_vec<WT, OutT, 8, 8>, big, dim3(256), 0, (const WT *)m->E,
-               (const WT *)m->Ut, prev, rows, m->V, m->d, alpha, (OutT *)out, ld);
-    else
-        launch(ctx, kKernelLogits, bigram_gemm_vec<WT, OutT, 4, 4>, small, dim3(256), 0, (const WT *)m->E,
-               (const WT *)m->Ut, prev, rows, m->V, m->d, alpha, (OutT *)out, ld);
+    const bool whole = m->d % 16 == 0 && reinterpret_cast<uintptr_t>(m->E) % 16 == 0 && reinterpret_cast<uintptr_t>(m->Ut) % 16 == 0;
+#define AS_CHAIN(GM_, GN_, TM_, TN_, KS_, AHEAD_)                                                                              \
+    do {                                                                                                               \
+        const dim3 grid((unsigned)((rows + GM_ * TM_ * 16 - 1) / (GM_ * TM_ * 16)),                                    \
+                        (unsigned)((m->V + GN_ * TN_ * 16 - 1) / (GN_ * TN_ * 16)));                                   \
+        if (whole)                                                                                                     \
+            launch(ctx, kKernelLogits, bigram_gemm_chain<WT, OutT, GM_, GN_, TM_, TN_, KS_, AHEAD_, true>, grid, dim3(256), 0, \
+                   (const WT *)m->E, (const WT *)m->Ut, prev, rows, m->V, m->d, alpha, (OutT *)out, ld);               \
+        else                                                                                                           \
+            launch(ctx, kKernelLogits, bigram_gemm_chain<WT, OutT, GM_, GN_, TM_, TN_, KS_, AHEAD_, false>, grid, dim3(256),   \
+                   0, (const WT *)m->E, (const WT *)m->Ut, prev, rows, m->V, m->d, alpha, (OutT *)out, ld);            \
+    } while (0)
+    // us a launch, 16 x 64 / 32 x 64 / 64 x 128 / 128 x 128 tiles: 64 x 1000 x 100 4.3 / 5.1 / 9.2 / 14.3; 200 x 3000 x 144
+    // 7.6 / 7.1 / 10.2 / 15.2; 256 x 4100 x 128 8.2 / 7.4 / 9.1 / 13.8; 512 x 5000 x 120 16.0 / 12.5 / 15.6 / 16.2; 300 x 9000 x
+    // 72 16.8 / 12.0 / 12.5 / 13.4; 1024 x 4096 x 256 35.5 / 29.1 / 25.6 / 25.2; 1024 x 32128 x 512 450 / 326 / 321 / 310 to 346;
+    // 4096 x 32128 x 520 (bf16) 2120 / 1642 / 1357 / 1307.  By the blocks of 32 x 64 and of 128 x 128 a compute unit:
+    const int64_t fine = (rows + 31) / 32 * ((m->V + 63) / 64), coarse = (rows + 127) / 128 * ((m->V + 127) / 128);
+    if (fine <= ctx->num_cus) AS_CHAIN(1, 4, 1, 1, 64, 1);
+    else if (fine <= 6 * (int64_t)ctx->num_cus) AS_CHAIN(2, 2, 1, 2, 32, 2);
+    else if (coarse < 16 * (int64_t)ctx->num_cus) AS_CHAIN(2, 2, 2, 4, 32, 1);
+    else AS_CHAIN(2, 2, 4, 4, 32, 1);
+#undef AS_CHAIN
 }
 
 // ------------------------------------------------------------------ estimator
@@ -1195,7 +1181,7 @@ static int persistent_gm(const as_ctx *ctx)
     return W % 8 == 0 ? 8 : W;
 }
 
-// Whether the MFMA kernels take the model (otherwise the vector kernel does).
+// Whether the MFMA kernels take the model (otherwise the chain kernel does).
 bool mfma_applies(const as_model *m)
 {
     return m->wdtype == AS_BF16 && m->d % BK == 0 && reinterpret_cast<uintptr_t>(m->E) % 16 == 0 &&

@@ -3,7 +3,7 @@
 //
 // What bounds such a decode is launches: two kernels of 3 to 4 us a step whose work is a few hundred instructions.
 // The block keeps the output matrix (K along the rows, so that neighbouring threads read neighbouring words), the
-// conditioning token's embedding and the row of logits in LDS.  Each logit is the chain of the vector kernel
+// conditioning token's embedding and the row of logits in LDS.  Each logit is the chain of the fp32 kernel
 // (as_model.hip), the step is the single-tile kernel's (as_tile.hpp): the same bits as the loop of launches.
 // V = 16, d = 8, 64 rows, 8 steps: 64 us as launches, 18.8 as one.
 #include <type_traits>
@@ -127,7 +127,7 @@ __global__ __launch_bounds__(256, 3) void decode_small_kernel(SmallArgs s)
 
 }  // namespace
 
-// Models that the vector kernel computes (its chain is what this kernel repeats), rows that the single-tile step takes
+// Models that the fp32 kernel computes (its chain is what this kernel repeats), rows that the single-tile step takes
 // whole, weights that fit the LDS, and as many rows as the chip holds at once: a step then takes 2.2 us (V = 16, d = 8)
 // to 5.5 us (V = 64, d = 128: few threads, long chains) where two launches take 7 to 10; a second round of blocks or a
 // rank of 512 (16 us a step) would lose that.

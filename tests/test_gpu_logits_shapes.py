@@ -95,3 +95,34 @@ _PLAIN = [(1024, 12, "f32", "bf16", 64), (1024, 26, "f32", "f32", 65), (1024, 27
 @pytest.mark.parametrize("V,d,wdt,ldt,R", _PLAIN)
 def test_plain_kernel_at_its_line(V, d, wdt, ldt, R):
     test_logits_tile_edges(V, d, wdt, ldt, R)
+
+
+# the fp32 kernel's four tilings (16 x 64, 32 x 64, 64 x 128, 128 x 128 by the number of blocks), whole rows (ranks of a
+# multiple of 16) and single elements, a last group of k short
+_CHAIN = [(1000, 100, "f32", 17), (1000, 16, "f32", 64), (4100, 128, "f32", 129), (4100, 75, "f32", 200), (4100, 48, "bf16", 1000),
+          (4100, 31, "f32", 1001), (16500, 32, "f32", 4100), (16500, 19, "bf16", 4100)]
+
+
+@pytest.mark.parametrize("V,d,wdt,R", _CHAIN)
+def test_fp32_logits_are_one_chain_over_k(V, d, wdt, R):
+    """Each logit is fma(a_k, b_k, sum) for k = 0, 1, ... from zero, bit for bit: libm's fmaf on the CPU."""
+    import ctypes
+    import torch
+    from paper_2210_15458_amd import binding as B
+    from gpu_util import to_dev_logits
+    fmaf = ctypes.CDLL("libm.so.6").fmaf
+    fmaf.restype, fmaf.argtypes = ctypes.c_float, [ctypes.c_float] * 3
+    E, U = synth.bigram_weights(V, d, seed=V + d, dtype=wdt)
+    model = B.Model(to_dev_logits(E), to_dev_logits(U), scale=math.sqrt(d))      # (alpha = 1: the chain itself)
+    rng = np.random.default_rng(d)
+    prev = rng.integers(0, V, R).astype(np.int32)
+    got = _logits(model, prev, V, "f32", R)
+    Ew = synth.bf16_bits_to_f32(E) if wdt == "bf16" else E
+    Uw = synth.bf16_bits_to_f32(U) if wdt == "bf16" else U
+    at = [(0, 0), (R - 1, V - 1), (0, V - 1), (R - 1, 0)] + list(zip(rng.integers(0, R, 200), rng.integers(0, V, 200)))
+    for r, v in at:
+        acc = 0.0
+        for a, b in zip(Ew[prev[r]].tolist(), Uw[:, v].tolist()):
+            acc = fmaf(a, b, acc)
+        assert got[r, v] == np.float32(acc), (r, v)
+    model.close()

@@ -118,7 +118,7 @@ def conditioned_tokens(seqs, prompts, eos):
     return int(np.unique(np.concatenate([prev[:, 0], prev[:, 1:][running]])).size)
 
 
-def rows_kept(V, d, R, B, T, wdt, row_bytes, by_sums):
+def rows_kept(V, d, R, B, T, wdt, row_bytes, by_sums, cus=256):
     """Whether a decode keeps logits rows from step to step (the choice the library makes)."""
     if T < 3 or wdt != "bf16" or d % 64 != 0 or d < 128 or V * d * 2 >= 2 ** 32:
         return False
@@ -126,11 +126,13 @@ def rows_kept(V, d, R, B, T, wdt, row_bytes, by_sums):
     if most > 4 * R or (most > R and most * row_bytes > 2 ** 32):
         return False
     computed = V * (1.0 - np.exp(-R * (T - 1) / V)) / (T - 1)
-    spared = (R - computed) * V * d * 2.0 / 1e15
+    # (against a row per token in each step where the decode would share those)
+    without = V * (1.0 - np.exp(-R / V)) if rows_shared(V, d, R, T, wdt, cus) else R
+    spared = (without - computed) * V * d * 2.0 / 1e15
     if by_sums:
         row = row_bytes / 5e12
         spared += R * (max(row, 4e-9) - 0.5e-9) - computed * row
-    return spared > 3e-6 + 15e-6 * min(6.0 * V / (R * (T - 1)), 1.0)
+    return spared > 4e-6 + 18e-6 * min(6.0 * V / (R * (T - 1)), 1.0)
 
 
 def step_by_sums(V, ldt, top_k, top_p, temp):

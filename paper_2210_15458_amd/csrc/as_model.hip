@@ -726,12 +726,12 @@ __global__ __launch_bounds__(256, 2) void bigram_gemm_bf16(const uint16_t *__res
     do_pass(std::integral_constant<int, 3>{});
 }
 
-// ---- thin kernel: few rows (a prompt's handful of codes, a first step's prompts) ---------------
+// ---- thin kernel: few rows (a prompt's handful of codes, a first step's prompts), small products ---------------
 //
-// With up to 128 rows the product is a pass over Ut (33 MB at 32128 x 512) and the persistent kernel's 256 x 256
-// tiles leave half of the chip without one, each with 3 us of latency in front of its first product and
-// rows of padding behind.  Here a block of four waves takes 128 columns and all rows (MT tiles of 32), so
-// that V = 32128 is 251 blocks; K stages of 64 (one 128-byte line per row, loader and swizzle as in the persistent
+// With few rows the product is a pass over Ut (33 MB at 32128 x 512), and on any small product the persistent kernel's
+// 256 x 256 tiles leave most of the chip without one, each with 3 us of latency in front of its first product and
+// rows of padding behind.  Here a block of four waves takes 128 columns and MT tiles of 32 rows (which of 1, 2 and 4:
+// thin_tiles), so that V = 32128 is 251 blocks; K stages of 64 (one 128-byte line per row, loader and swizzle as in the persistent
 // kernel) run through a ring of four, three stages requested ahead: 48 KB of Ut in flight per block, two blocks on a CU
 // at MT = 1.  Same MFMA, K ascending, same epilogue arithmetic: a row's logits (and group masses) are the same
 // bits whichever kernel makes them.
@@ -773,10 +773,11 @@ __device__ __forceinline__ void thin_read(ThinFrags<MT> &f, uint32_t a0, uint32_
     }
 }
 
-// FUSED: as in the persistent kernel, group masses instead of logits (C: float2 [R, ldc], alpha with log2(e)/temp)
-template <class OutT, int MT, bool FUSED>
+// FUSED: as in the persistent kernel, group masses instead of logits (C: float2 [R, ldc], alpha with log2(e)/temp).
+// TILES: more row tiles than one (a form of its own: their numbers take 0.7 us to work out, of 5).
+template <class OutT, int MT, bool FUSED, bool TILES>
 __global__ __launch_bounds__(256) void bigram_gemm_thin(const uint16_t *__restrict__ E, const uint16_t *__restrict__ Ut,
-                                                        const int32_t *__restrict__ prev, int32_t R, int32_t V,
+                                                        const int32_t *__restrict__ prev, int32_t rows, int32_t V,
                                                         int32_t d, float alpha, OutT *__restrict__ C, int64_t ldc,
                                                         int vec_store)
 {
@@ -786,7 +787,19 @@ __global__ __launch_bounds__(256) void bigram_gemm_thin(const uint16_t *__restri
     __shared__ __attribute__((aligned(1024))) unsigned char smem[kLds];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int64_t n0 = (int64_t)blockIdx.x * TN;
+    int64_t n0 = (int64_t)blockIdx.x * TN;
+    int32_t R = rows;
+    if constexpr (TILES) {
+        // blocks of one column tile follow each other eight apart, on one XCD: its Ut rows come through that L2 once
+        const uint32_t mtiles = gridDim.y, bid = blockIdx.y * gridDim.x + blockIdx.x;
+        const uint32_t group = bid / (8 * mtiles), in_group = bid % (8 * mtiles);
+        const uint32_t width = gridDim.x - group * 8 < 8 ? gridDim.x - group * 8 : 8;
+        n0 = (int64_t)(group * 8 + in_group % width) * TN;
+        const int32_t m0 = (int32_t)(in_group / width) * 32 * MT;
+        prev += m0;
+        C += m0 * ldc * (FUSED ? 2 : 1);
+        R = rows - m0;                                                // rows from the tile's first on
+    }
     const uint32_t rowbytes = (uint32_t)d * 2;
     const unsigned char *Eb = reinterpret_cast<const unsigned char *>(E);
     const unsigned char *Ub = reinterpret_cast<const unsigned char *>(Ut) + n0 * (int64_t)rowbytes;
@@ -908,30 +921,51 @@ __global__ __launch_bounds__(256) void bigram_gemm_thin(const uint16_t *__restri
     }
 }
 
-// Up to 64 rows always (one launch, bf16 logits: 16 x 32128 x 512 5.2 us against 16.5 for the persistent kernel, which
-// is 6.5 TB/s of Ut; 64 rows 7.2 against 16.5; 32 x 256000 x 1024 98 against 123; 64 x 131071 x 768 39 against 48);
-// up to 128 while the columns are one round of blocks (128 x 32128 x 512 10.8 against 17.1; beyond that the
-// persistent kernel has a tile for every CU and draws level: 128 x 256000 x 1024 144 against 140).
-static bool thin_pays(const as_ctx *ctx, const as_model *m, int64_t rows)
+// Which kernel a product of `rows` rows takes: MT of the thin one, or 0 for the 256 x 256 tiles of the persistent one, which
+// leave most of the chip without a tile on small products and start 3 us later.  S K stages take, in us (fitted to the
+// launches below), 0.4 + 0.22 S for each of the busiest compute unit's blocks at MT = 1 beside 2.6 for the launch (two
+// stand there at a time, of the others one), 1.8 + 0.43 S a round at MT = 2, 3.0 + 0.63 S at MT = 4, and a round of the persistent kernel 1.05 S and up to
+// 2.5 for the traffic of the others, beside 5.2.  Measured, d = 512, persistent / MT = 1 / 2 / 4: 257 x 3000 14.4 / 5.2 / 6.3 /
+// 8.9; 1024 x 3000 15.7 / 10.1 / 11.5 / 9.5; 200 x 8000 14.9 / 7.1 / 6.8 / 9.1; 768 x 8000 16.4 / 16.5 / 16.1 / 16.6; 16 x 32128
+// 16.5 / 5.2; 100 x 32128 16.1 / 12.2 / 11.8 / 9.9; 129 x 32128 16.3 / 14.4 / 16.2 / 17.6; 200 x 32128 17.3 / 18.8 / 21.0 / 17.7;
+// 33 x 50000 17.6 / 12.4 / 12.1 / 16.7; d = 1024: 512 x 3000 23.1 / 9.9 / 9.7 / 13.6, 65 x 100000 49.0 / 41.9 / 58.6 / 53.4, 100 x
+// 100000 50.1 / 54.4 / 61.8 / 55.7; d = 128: 512 x 2000 7.6 / 4.2 / 4.3 / 5.0.
+static int thin_tiles(const as_ctx *ctx, const as_model *m, int64_t rows)
 {
-    return ctx->gemm_shape == 0 && (rows <= 64 || (rows <= 128 && m->V <= (int64_t)TN * ctx->num_cus));
+    if (ctx->gemm_shape != 0) return 0;
+    const double S = (double)m->d / PK, cus = ctx->num_cus > 0 ? ctx->num_cus : 1;
+    const int64_t cols = (m->V + TN - 1) / TN;
+    auto rounds_of = [&](int mt) { return ceil((double)((rows + 32 * mt - 1) / (32 * mt) * cols) / cus); };
+    auto more = [&](int mt) { return rows > 32 * mt ? 0.7 : 0.0; };          // (what TILES costs)
+    const double t1 = 2.6 + rounds_of(1) * (0.4 + 0.22 * S) + more(1), t2 = 0.6 + rounds_of(2) * (1.8 + 0.43 * S) + more(2);
+    const double t4 = 0.5 + rounds_of(4) * (3.0 + 0.63 * S) + more(4);
+    const double tiles = (double)((rows + PM - 1) / PM * (((int64_t)m->V + PN - 1) / PN)), rounds = ceil(tiles / cus);
+    const double persistent = 5.2 + rounds * (1.05 * S + 2.5 * (tiles < cus ? tiles / cus : 1.0));
+    const double best = t1 < t2 ? (t1 < t4 ? t1 : t4) : (t2 < t4 ? t2 : t4);
+    if (best > 0.95 * persistent || rows > 0x7fffffff - 256) return 0;
+    return best == t1 ? 1 : best == t2 ? 2 : 4;
 }
 
 template <class OutT, bool FUSED>
 void launch_thin(as_ctx *ctx, const as_model *m, const int32_t *prev, int64_t rows, OutT *out, int64_t ld, float alpha,
-                 int vec_store)
+                 int vec_store, int mt)
 {
-    const dim3 grid((unsigned)((m->V + TN - 1) / TN)), block(256);
     const uint16_t *Ep = (const uint16_t *)m->E, *Up = (const uint16_t *)m->Ut;
-    if (rows <= 32)
-        launch(ctx, kKernelLogits, bigram_gemm_thin<OutT, 1, FUSED>, grid, block, 0, Ep, Up, prev, (int32_t)rows, m->V,
-               m->d, alpha, out, ld, vec_store);
-    else if (rows <= 64)
-        launch(ctx, kKernelLogits, bigram_gemm_thin<OutT, 2, FUSED>, grid, block, 0, Ep, Up, prev, (int32_t)rows, m->V,
-               m->d, alpha, out, ld, vec_store);
-    else
-        launch(ctx, kKernelLogits, bigram_gemm_thin<OutT, 4, FUSED>, grid, block, 0, Ep, Up, prev, (int32_t)rows, m->V,
-               m->d, alpha, out, ld, vec_store);
+    const unsigned cols = (unsigned)((m->V + TN - 1) / TN);
+    const dim3 grid(cols, (unsigned)((rows + 32 * mt - 1) / (32 * mt))), block(256);
+#define AS_THIN(MT_)                                                                                                   \
+    do {                                                                                                               \
+        if (grid.y > 1)                                                                                                \
+            launch(ctx, kKernelLogits, bigram_gemm_thin<OutT, MT_, FUSED, true>, grid, block, 0, Ep, Up, prev,         \
+                   (int32_t)rows, m->V, m->d, alpha, out, ld, vec_store);                                              \
+        else                                                                                                           \
+            launch(ctx, kKernelLogits, bigram_gemm_thin<OutT, MT_, FUSED, false>, grid, block, 0, Ep, Up, prev,        \
+                   (int32_t)rows, m->V, m->d, alpha, out, ld, vec_store);                                              \
+    } while (0)
+    if (mt == 1) AS_THIN(1);
+    else if (mt == 2) AS_THIN(2);
+    else AS_THIN(4);
+#undef AS_THIN
 }
 
 // ---- chain kernel: what the bf16 MFMA kernels do not take (fp32 weights, or a rank d that is not a multiple of their K
@@ -1197,35 +1231,6 @@ static int64_t tile_rounds(int64_t m, int64_t n_blocks, int W, int gm)
     return (nbx + W / m - 1) / (W / m);
 }
 
-// Whether a decode keeps logits rows from step to step.  With tokens spread evenly over the vocabulary (the worst case)
-// U = V(1 - exp(-rows (T - 1)/V)) rows are computed after the first step; what that spares is rows of product, at 1 PFLOP/s, and, where the
-// steps work from sums (by_sums), a pass over a logits row (5 TB/s, at least 4 ns) per row of codes less one per logits
-// row computed and 0.5 ns a code.  It costs the claims and a launch more, 18 us while steps still meet new tokens (about
-// 6 V/rows of them) and 3 after.  us a step, without / with, bf16, V = 32128, d = 512: 8192 rows T = 4 285 / 212,
-// T = 16 325 / 117; 65536 rows T = 16 1275 / 153.  V = 8000, d = 512:
-// 2048 rows T = 4 31.4 / 38.2, T = 16 33.6 / 31.6; 4096 rows T = 4 51.6 / 44.9.  V = 2000, d = 128: 1024 rows T = 64 15.1 /
-// 15.5, 2048 20.9 / 13.8.  Not by sums, V = 5001, d = 512: 2048 rows T = 16 39.0 / 42.1, T = 64 37.5 / 31.6; 8192 rows
-// T = 4 91.7 / 86.5.  Group masses, V = 32128: 16384 rows T = 16 485 / 182; V = 4096: 1024 rows
-// T = 64 23.8 / 24.2.
-// The table has at most four times the rows of one step, which a decode without it has, and those beyond within 4 GiB.
-bool keeping_pays(const as_ctx *ctx, const as_model *m, int64_t rows, int64_t prompts, int32_t T, int64_t row_bytes,
-                  bool by_sums)
-{
-    if (T < 3 || !rows_on_device(ctx, m)) return false;
-    const double V = (double)m->V, R = (double)rows;
-    const double steps = T - 1, used = R * steps + (double)prompts;
-    const double most = used < V ? used : V;
-    if (most > 4.0 * R || (most > R && most * (double)row_bytes > 4.0 * 1024.0 * 1024.0 * 1024.0)) return false;
-    const double computed = V * (1.0 - exp(-R * steps / V)) / steps;           // logits rows a step
-    double spared = (R - computed) * V * (double)m->d * 2.0 / 1e15;
-    if (by_sums) {
-        const double pass = V * (ctx->dtype == AS_BF16 ? 2.0 : 4.0) / 5e12;
-        spared += R * ((pass > 4e-9 ? pass : 4e-9) - 0.5e-9) - computed * pass;
-    }
-    const double meeting = 6.0 * V / (R * steps);
-    return spared > 3e-6 + 15e-6 * (meeting < 1.0 ? meeting : 1.0);
-}
-
 // Whether the logits kernel that takes the model can read the number of rows on the device (the persistent one).
 bool rows_on_device(const as_ctx *ctx, const as_model *m)
 {
@@ -1252,6 +1257,36 @@ bool sharing_pays(const as_ctx *ctx, const as_model *m, int64_t rows, int32_t T)
     const double work = ((double)rows - tokens) * (double)m->V * (double)m->d * 2.0 / 1e15;
     const double tiles = (double)spared * ((double)m->d / PK * 1.72e-6 + 2.3e-6);
     return 0.5 * (work + tiles) > 20e-6;
+}
+
+// Whether a decode keeps logits rows from step to step.  With tokens spread evenly over the vocabulary (the worst case)
+// U = V(1 - exp(-rows (T - 1)/V)) rows are computed after the first step; what that spares is rows of product, at 1 PFLOP/s, and, where the
+// steps work from sums (by_sums), a pass over a logits row (5 TB/s, at least 4 ns) per row of codes less one per logits
+// row computed and 0.5 ns a code (against a row per token in each step where the decode would share those).  It costs
+// the claims and a launch more, up to 22 us while steps still meet new tokens (about 6 V/rows of them) and 4 after.  us a step, without / with, bf16, V = 32128, d = 512: 8192 rows T = 4 285 / 212,
+// T = 16 325 / 117; 65536 rows T = 16 1275 / 153.  V = 8000, d = 512:
+// 2048 rows T = 4 31.4 / 38.2, T = 16 33.6 / 31.6; 4096 rows T = 4 51.6 / 44.9.  V = 2000, d = 128: 1024 rows T = 64 15.1 /
+// 15.5, 2048 20.9 / 13.8.  Not by sums, V = 5001, d = 512: 2048 rows T = 16 39.0 / 42.1, T = 64 37.5 / 31.6; 8192 rows
+// T = 4 91.7 / 86.5.  Group masses, V = 32128: 16384 rows T = 16 485 / 182; V = 4096: 1024 rows
+// T = 64 23.8 / 24.2.
+// The table has at most four times the rows of one step, which a decode without it has, and those beyond within 4 GiB.
+bool keeping_pays(const as_ctx *ctx, const as_model *m, int64_t rows, int64_t prompts, int32_t T, int64_t row_bytes,
+                  bool by_sums)
+{
+    if (T < 3 || !rows_on_device(ctx, m)) return false;
+    const double V = (double)m->V, R = (double)rows;
+    const double steps = T - 1, used = R * steps + (double)prompts;
+    const double most = used < V ? used : V;
+    if (most > 4.0 * R || (most > R && most * (double)row_bytes > 4.0 * 1024.0 * 1024.0 * 1024.0)) return false;
+    const double computed = V * (1.0 - exp(-R * steps / V)) / steps;           // logits rows a step
+    const double without = sharing_pays(ctx, m, rows, T) ? V * (1.0 - exp(-R / V)) : R;
+    double spared = (without - computed) * V * (double)m->d * 2.0 / 1e15;
+    if (by_sums) {
+        const double pass = V * (ctx->dtype == AS_BF16 ? 2.0 : 4.0) / 5e12;
+        spared += R * ((pass > 4e-9 ? pass : 4e-9) - 0.5e-9) - computed * pass;
+    }
+    const double meeting = 6.0 * V / (R * steps);
+    return spared > 4e-6 + 18e-6 * (meeting < 1.0 ? meeting : 1.0);
 }
 
 as_status launch_share_clear(as_ctx *ctx, const RowShare &s, int32_t T)
@@ -1323,11 +1358,11 @@ as_status launch_bigram_logits(as_ctx *ctx, const as_model *m, const int32_t *pr
         // the persistent kernel addresses operand rows with 32-bit byte offsets and wants two K stages
         const bool persistent = ctx->gemm_shape != 1 && m->d >= 2 * PK && (int64_t)m->V * m->d * 2 < (1LL << 32) &&
                                 ctx->num_cus >= 8;
-        if (range.end == nullptr && thin_pays(ctx, m, rows)) {
+        if (const int mt = range.end == nullptr ? thin_tiles(ctx, m, rows) : 0) {
             if (ctx->dtype == AS_BF16)
-                launch_thin<uint16_t, false>(ctx, m, prev, rows, (uint16_t *)logits_out, ld, alpha, vec_store);
+                launch_thin<uint16_t, false>(ctx, m, prev, rows, (uint16_t *)logits_out, ld, alpha, vec_store, mt);
             else
-                launch_thin<float, false>(ctx, m, prev, rows, (float *)logits_out, ld, alpha, vec_store);
+                launch_thin<float, false>(ctx, m, prev, rows, (float *)logits_out, ld, alpha, vec_store, mt);
         } else if (persistent) {
             const dim3 grid((unsigned)(8 * (ctx->num_cus / 8))), block(512);
             if (ctx->dtype == AS_BF16)
@@ -1376,8 +1411,8 @@ as_status launch_bigram_partials(as_ctx *ctx, const as_model *m, const int32_t *
 {
     if (rows == 0) return AS_OK;
     const float alpha = (float)((double)m->scale / sqrt((double)m->d) * 1.44269504088896340736 / (double)temp);
-    if (range.end == nullptr && thin_pays(ctx, m, rows)) {
-        launch_thin<float, true>(ctx, m, prev, rows, reinterpret_cast<float *>(part), ldp, alpha, 0);
+    if (const int mt = range.end == nullptr ? thin_tiles(ctx, m, rows) : 0) {
+        launch_thin<float, true>(ctx, m, prev, rows, reinterpret_cast<float *>(part), ldp, alpha, 0, mt);
         AS_HIP_TRY(ctx, hipGetLastError());
         return AS_OK;
     }

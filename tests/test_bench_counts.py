@@ -20,8 +20,8 @@ def test_rows_of_a_decode_with_and_without_sharing():
 def test_rows_are_kept_where_most_come_again():
     def kept(V, d, R, T, by_sums=True):
         return bench.rows_kept(V, d, R, 1, T, "bf16", V * 2, by_sums)
-    assert kept(32128, 512, 65536, 16) and kept(32128, 512, 8192, 4) and kept(8000, 512, 2048, 16) and kept(2000, 128, 2048, 64)
-    assert not kept(32128, 512, 1024, 64) and not kept(8000, 512, 2048, 4) and not kept(2000, 128, 1024, 64)
+    assert kept(32128, 512, 65536, 16) and kept(32128, 512, 8192, 4) and kept(8000, 512, 4096, 4) and kept(2000, 128, 2048, 64)
+    assert not kept(32128, 512, 1024, 64) and not kept(8000, 512, 2048, 16) and not kept(2000, 128, 1024, 64)
     assert not kept(5001, 512, 2048, 16, False) and kept(5001, 512, 2048, 64, False)
 
 

@@ -14,7 +14,7 @@ DT = {"bf16": torch.bfloat16, "f32": torch.float32}
 
 # V, d, prompts, codes, steps, top_k, top_p, logits, scale
 CASES = [
-    (3000, 128, 3, 1000, 12, 0, 1.0, "bf16", 3.0),
+    (3000, 128, 3, 1000, 18, 0, 1.0, "bf16", 3.0),
     (8000, 512, 2, 2100, 6, 0, 1.0, "bf16", 3.0),         # more kept rows than rows
     (2000, 128, 1, 4097, 10, 0, 1.0, "f32", 300.0),       # sums beyond fp32
     (3000, 1024, 4, 2000, 6, 20, 0.9, "bf16", 3.0),       # truncated: its own kernels, from the kept rows
@@ -61,7 +61,7 @@ def test_kept_rows_equal_the_loop_of_exported_calls(V, d, Bn, N, T, top_k, top_p
 
 
 def test_kept_rows_replay_from_a_graph():
-    V, d, Bn, N, T = 3000, 128, 3, 1000, 12
+    V, d, Bn, N, T = 3000, 128, 3, 1000, 18
     model, ctx, prompts, u = _setup(V, d, Bn, N, "bf16", 3.0)
     stream = torch.cuda.Stream()
     ctx.close()

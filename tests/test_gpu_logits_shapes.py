@@ -126,3 +126,18 @@ def test_fp32_logits_are_one_chain_over_k(V, d, wdt, R):
             acc = fmaf(a, b, acc)
         assert got[r, v] == np.float32(acc), (r, v)
     model.close()
+
+
+# several row tiles of the few-rows kernel (of 32, 64 and 128 rows), the last of them short, column tiles not a multiple of 8
+_ROW_TILES = [(1000, 512, "bf16", 33), (3000, 512, "bf16", 257), (3000, 512, "f32", 500), (3000, 512, "bf16", 1001),
+              (2100, 128, "f32", 1025), (1030, 1024, "bf16", 130)]
+
+
+@pytest.mark.parametrize("V,d,ldt,R", _ROW_TILES)
+def test_row_tiles_of_small_products(V, d, ldt, R):
+    test_logits_tile_edges(V, d, "bf16", ldt, R)
+
+
+@pytest.mark.parametrize("V,d,R", [(3000, 512, 257), (3000, 512, 1001), (1030, 128, 65)])
+def test_row_tiles_of_group_masses(V, d, R):
+    test_group_masses_of_few_rows(V, d, R)

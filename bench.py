@@ -60,6 +60,21 @@ def compute_units():
     return torch.cuda.get_device_properties(0).multi_processor_count
 
 
+def topk_tile_pays(V, rows, top_k, cus):
+    """Whether the one-tile top-k kernel takes a step (the choice the library makes)."""
+    if top_k > 48 or (V <= 8192 and rows > 2 * cus):
+        return False
+    s = 0.5 * (np.sqrt(3.5 ** 2 + 4.0 * (64 - top_k)) - 3.5)
+    lam, lanes, vecs = s * s + top_k - 2.0, 0.0, V // 8
+    for _ in range(4):
+        here = min(vecs, 1024)
+        if here <= 0:
+            break
+        lanes += min(here, 64) * (1.0 - np.exp(-lam * 8.0 * here / min(here, 64) / V))
+        vecs -= 1024
+    return lanes >= top_k
+
+
 def sampling_kernel_name(V, ldt, top_k, top_p, temp, rows, d, wdt, cus):
     """Which kernel finishes a decode's sampling step for this shape (the choice the library makes)."""
     has_k, has_p = 0 < top_k < V, 0.0 < top_p < 1.0
@@ -75,14 +90,17 @@ def sampling_kernel_name(V, ldt, top_k, top_p, temp, rows, d, wdt, cus):
             name = "step_tile_kernel (fused sampling step, one-tile rows)"
         else:
             name = "step_kernel (fused sampling step)"
-    elif tile and half and not (V <= 8192 and rows > 2 * cus) and (top_k <= 48 if has_k else first_chunk_reference_ok):
+    elif tile and half and (topk_tile_pays(V, rows, top_k, cus) if has_k else
+                            first_chunk_reference_ok and not (V <= 8192 and rows > 2 * cus) and
+                            not (V <= 12288 and rows > 16 * cus)):
         if has_k:
             name = ("topk_tile_kernel (top-k%s and the sampling step in one launch, row resident in registers)"
                     % (" + nucleus" if has_p else ""))
         else:
             name = "nucleus_tile_kernel (nucleus and the sampling step in one launch, logits counted by stored value)"
-    elif (V <= 32768 and top_k <= 128 and rows > cus and V > (8192 if half else 4096) and
-          (half or (has_k and (V > 16384 or rows <= 2 * cus)))):
+    elif V <= 32768 and ((half and not has_k and rows > cus and V > 20480) or
+                         (not half and has_k and V > 16384 and rows > 2 * cus and
+                          (top_k <= 64 or (top_k <= 128 and rows <= 4 * cus)))):
         name = "threshold_resident_kernel with the sampling step fused"
     elif has_k and top_k > 128 and rows > cus and V * (2 if half else 4) > 131072:
         name = "threshold_stream_kernel, then the sampling-step kernel"

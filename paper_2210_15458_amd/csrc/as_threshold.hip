@@ -22,6 +22,7 @@
 // the same keys and the same fixed-point masses, so they return the same threshold.
 // as_wide.hip has the form of this for any other row; the rules at the end of this file
 // say which rows go where.
+#include <math.h>
 #include <type_traits>
 
 #include "as_common.hpp"
@@ -1943,23 +1944,42 @@ void launch_streamed(as_ctx *ctx, const void *logits, int64_t rows, int64_t ld, 
     else go(threshold_stream_kernel<DT, 2, false>);
 }
 
-// Rows that the resident kernel takes with the sampling step (whole aligned pieces, at most 32768 logits, k at most 128)
-// in place of the wide one: several of its 256-thread blocks share a compute unit, so only with more rows than compute
-// units, and not where the wide kernel was always faster: fewer rows (us, resident / wide: 16 rows of 32003 bf16
-// nucleus 18.9 / 18.1, fp32 24.2 / 17.4), short ones, where the resident one's lanes idle (2000 rows of 3001: 56 to 282 /
-// 21 to 33), the fp32 nucleus (300 rows of 32003: 36 / 27), many fp32 rows of up to 16384 logits (2000 of 9001, top-k
-// 40: 40 / 27).  Within the line, as both kernels are now: the bf16 nucleus near 32768 (2000 rows of 32003: 66 / 75; of
-// 20003 62 / 58, of 9001 57 / 39), top-k on many long fp32 rows (600 of 20003, k = 40: 19.5 / 22.0; 2000 of 32003 53 /
-// 54, k = 100 with p = 0.9 82 / 73), bf16 top-k about even (2000 of 32003, k = 40 37 / 36; 300 of 20003 14.4 / 12.5).
+// Whether the resident kernel can take the rows: 16-byte pieces, in its registers, k at most half the thread count.
+static bool resident_fits(const as_ctx *ctx, const void *logits, int64_t ld, bool has_k, int32_t top_k)
+{
+    return ctx->V <= 32768 && reinterpret_cast<uintptr_t>(logits) % 16 == 0 &&
+           (ld * (ctx->dtype == AS_BF16 ? 2 : 4)) % 16 == 0 && (!has_k || top_k <= kThreads / 2);
+}
+
+// Whole steps that it takes from the wide kernel (us, resident / wide): the nucleus alone of long bf16 rows (those of whole
+// pieces have a kernel of their own), 2000 rows of 9001 57 / 39, of 20001 60 / 57, of 32001 66 / 75; top-k of fp32 rows above
+// 16384 on more than two a compute unit, 600 of 24000 k = 40 19 / 24, 2000 42 / 46, but k = 100 2000 76 / 68, and 300 15 / 14.
+// (Top-k of bf16 rows: 300 of 9001 k = 40 15 / 12, 8000 108 / 90, 2000 of 32761 37 / 37, k = 100 66 / 52.)
 static bool resident_pays(const as_ctx *ctx, const void *logits, int64_t rows, int64_t ld, bool has_k, int32_t top_k)
 {
-    const bool half = ctx->dtype == AS_BF16;
-    if (ctx->V > 32768 || reinterpret_cast<uintptr_t>(logits) % 16 != 0 || (ld * (half ? 2 : 4)) % 16 != 0 ||
-        (has_k && top_k > kThreads / 2))
-        return false;
+    if (!resident_fits(ctx, logits, ld, has_k, top_k)) return false;
     if (ctx->thr_path == 2) return true;
-    if (rows <= (int64_t)ctx->num_cus || ctx->V <= (half ? 8192 : 4096)) return false;
-    return half || (has_k && (ctx->V > 16384 || rows <= 2 * (int64_t)ctx->num_cus));
+    if (ctx->dtype == AS_BF16) return !has_k && rows > (int64_t)ctx->num_cus && ctx->V > 20480;
+    return has_k && ctx->V > 16384 && rows > 2 * (int64_t)ctx->num_cus && (top_k <= 64 || rows <= 4 * (int64_t)ctx->num_cus);
+}
+
+// Whether topk_tile_kernel takes a step.  Its bound is the k-th largest of the lanes' maxima, and what reaches the bound
+// has to fit 64 places; a row that does not costs the launch 100 us.  With lambda logits above a bound a lane that
+// holds a share f of the row has one with probability 1 - exp(-lambda f); the lambda logits that bring k such lanes, two
+// for ties and 3.5 times the root of what shares lanes have to stay within 64, that is k lanes have to be reached by
+// lambda = s^2 + k - 2, s^2 + 3.5 s + k - 64 = 0.  (us, here / wide: k = 40, 64 rows of 8000 46 / 11, 300 of 8200 53 / 11, 600
+// of 11000 38 / 15, 600 of 12800 10 / 15, 2000 20 / 29; k = 48, 300 of 32128 156 / 15.)  Short rows leave three of its
+// four waves without work: with many of them the wide kernel is faster (8192 of 4096, k = 40 61 us against 207).
+static bool topk_tile_pays(const as_ctx *ctx, int64_t rows, int32_t top_k)
+{
+    if (top_k > kTileTopK || (ctx->V <= 8192 && rows > 2 * (int64_t)ctx->num_cus)) return false;
+    const double s = 0.5 * (sqrt(3.5 * 3.5 + 4.0 * (64.0 - top_k)) - 3.5), lambda = s * s + top_k - 2.0;
+    double lanes = 0.0;
+    for (int32_t w = 0, vecs = ctx->V / 8; w < kThreads / 64 && vecs > 0; ++w, vecs -= 1024) {
+        const int32_t here = vecs < 1024 ? vecs : 1024, in = here < 64 ? here : 64;
+        lanes += in * (1.0 - exp(-lambda * 8.0 * here / in / ctx->V));
+    }
+    return lanes >= (double)top_k;
 }
 
 // What goes to the streamed kernel, and the step kernel after it, whole steps included: k above 128 on rows of more than
@@ -1977,10 +1997,12 @@ static bool streamed_pays(const as_ctx *ctx, int64_t rows, bool has_k, int32_t t
 // others keep more of the rows.  Nucleus alone, threshold and interval step, us: the resident kernel on rows that it
 // can take above 16384 logits (16384 itself is even), in bf16 with any number of them (1 row of 32128: 16.8 against
 // 18.8, 256 20.5 against 22.6), in fp32 with more than compute units (64 rows of 32128 30.4 against 28.0; 300 38.0, 38.7;
-// 6000 261, 338).
+// 6000 261, 338), bf16 rows above 8192 with more than compute units, and top-k up to 128 with as many.
 static bool threshold_resident_pays(const as_ctx *ctx, int64_t rows, bool has_k)
 {
-    return !has_k && ctx->V > 16384 && (ctx->dtype == AS_BF16 || rows > (int64_t)ctx->num_cus);
+    const bool half = ctx->dtype == AS_BF16, many = rows > (int64_t)ctx->num_cus;
+    if (!has_k) return (ctx->V > 16384 && (half || many)) || (half && many && ctx->V > 8192);
+    return many && ctx->V > (half ? 8192 : 4096) && (half || ctx->V > 16384 || rows <= 2 * (int64_t)ctx->num_cus);
 }
 // ... the streamed kernel on other rows of up to 12288 bf16 logits (1024 rows: of 3001 15.3 against 20.5, 9001 23.8, 28.5,
 // 12001 27.5, 31.6; few rows of 20003 are 10 % faster in the wide kernel) or 10240 fp32 ones (1024 rows: of 9001 26.3,
@@ -2004,11 +2026,13 @@ bool launch_topk_step(as_ctx *ctx, const StepArgs &args, int32_t top_k, float to
     const bool has_k = top_k > 0 && top_k < ctx->V, has_p = top_p > 0.f && top_p < 1.f;
     const bool nucleus_only = !has_k && has_p && ctx->dtype == AS_BF16;
     const bool one_tile = ctx->dtype == AS_BF16 && ctx->V % 8 == 0 && ctx->V <= 32768 &&
-                          reinterpret_cast<uintptr_t>(a.logits) % 16 == 0 && (a.ld * esz) % 16 == 0 &&
-                          (has_k ? top_k <= kTileTopK : a.k <= kTileMaxScale);
-    // (short rows leave three of the single-tile kernels' four waves without work: with many of them the wide
-    // kernel is faster, 8192 rows of 4096 top-k 40 61 us against 207)
-    const bool tile = one_tile && !(ctx->V <= 8192 && a.rows > 2 * (int64_t)ctx->num_cus);
+                          reinterpret_cast<uintptr_t>(a.logits) % 16 == 0 && (a.ld * esz) % 16 == 0;
+    // (the nucleus: 8000 rows of 8200 127 us against 106 in the wide kernel, of 11000 128 / 116, of 12800 even; 2000 even)
+    const int64_t cus = ctx->num_cus;
+    const bool by_tile = has_k ? (ctx->thr_path != 0 ? top_k <= kTileTopK : topk_tile_pays(ctx, a.rows, top_k))
+                               : a.k <= kTileMaxScale && (ctx->thr_path != 0 || !((ctx->V <= 8192 && a.rows > 2 * cus) ||
+                                                                                  (ctx->V <= 12288 && a.rows > 16 * cus)));
+    const bool tile = one_tile && by_tile;
     if (ctx->thr_path == 3 ||
         (ctx->thr_path == 0 && !tile && !resident_pays(ctx, a.logits, a.rows, a.ld, has_k, top_k) &&
          !streamed_pays(ctx, a.rows, has_k, top_k))) {
@@ -2021,7 +2045,7 @@ bool launch_topk_step(as_ctx *ctx, const StepArgs &args, int32_t top_k, float to
     *st = AS_OK;
     if (a.rows == 0) return true;
     const dim3 grid((unsigned)a.rows), block(kThreads);
-    if (has_k && top_k <= kTileTopK && ctx->dtype == AS_BF16 && ctx->V % 8 == 0 && ctx->thr_path != 2) {
+    if (has_k && tile && ctx->thr_path != 2) {
         if (has_p && nt) launch(ctx, kKernelStep, topk_tile_kernel<true, true>, grid, block, 0, a, top_k, top_p);
         else if (has_p) launch(ctx, kKernelStep, topk_tile_kernel<true, false>, grid, block, 0, a, top_k, top_p);
         else if (nt) launch(ctx, kKernelStep, topk_tile_kernel<false, true>, grid, block, 0, a, top_k, top_p);
@@ -2030,7 +2054,7 @@ bool launch_topk_step(as_ctx *ctx, const StepArgs &args, int32_t top_k, float to
         if (e != hipSuccess) *st = hip_fail(ctx, e, "top-k step launch");
         return true;
     }
-    if (nucleus_only && ctx->V % 8 == 0 && ctx->thr_path != 2 && a.k <= kTileMaxScale) {
+    if (nucleus_only && tile && ctx->thr_path != 2) {
         if (nt) launch(ctx, kKernelStep, nucleus_tile_kernel<true>, grid, block, 0, a, top_p);
         else launch(ctx, kKernelStep, nucleus_tile_kernel<false>, grid, block, 0, a, top_p);
         hipError_t e = hipGetLastError();
@@ -2069,11 +2093,8 @@ as_status launch_threshold(as_ctx *ctx, const void *logits, int64_t rows, int64_
     const bool has_k = top_k > 0 && top_k < ctx->V, has_p = top_p > 0.f && top_p < 1.f;
     // resident path: the row fits the block's registers, is read in 16-byte pieces, k at most half the thread
     // count (the k-th largest thread maximum must leave only a few hundred logits above it)
-    const bool resident = ctx->thr_path != 1 && (has_k || has_p) && ctx->V <= 32768 &&
-                          reinterpret_cast<uintptr_t>(logits) % 16 == 0 && (ld * esz) % 16 == 0 &&
-                          (!has_k || top_k <= kThreads / 2);
-    const bool by_resident = resident_pays(ctx, logits, rows, ld, has_k, top_k) ||
-                             (resident && threshold_resident_pays(ctx, rows, has_k));
+    const bool resident = ctx->thr_path != 1 && (has_k || has_p) && resident_fits(ctx, logits, ld, has_k, top_k);
+    const bool by_resident = resident && (ctx->thr_path == 2 || threshold_resident_pays(ctx, rows, has_k));
     const bool by_streamed = streamed_pays(ctx, rows, has_k, top_k) ||
                              (!resident && threshold_streamed_pays(ctx, rows, has_k, top_k));
     if (ctx->thr_path == 3 || (ctx->thr_path == 2 && !resident) ||

@@ -64,11 +64,14 @@ __device__ __forceinline__ u64 fixed_weight(float e)
     return ((u64)hi << 32) | lo;
 }
 
-template <int NT, bool MULTI> struct WideShared {
+// SHORT: the forms for many short rows, where as many blocks as the unit's waves allow hide each other's block-wide
+// steps: half the LDS, 16 bins an octave where a nucleus's window is named (a bin's mass to a few parts in 10^4; the masses that
+// close it are the same).
+template <int NT, bool MULTI, bool SHORT> struct WideShared {
     static constexpr int kWaves = NT / 64;
-    static constexpr int kBins = NT == 1024 ? 4096 : 2048;
+    static constexpr int kBins = NT == 1024 ? 4096 : SHORT ? 1024 : 2048;
     static constexpr int kPerOctave = kBins / 64;            // 64 factors of two
-    static constexpr int kList = NT == 1024 ? 2048 : 1024;
+    static constexpr int kList = NT == 1024 ? 2048 : SHORT ? 512 : 1024;
     // (a row of 2^21 fp32 logits: 8193; with 512 threads, where two blocks are to share a unit's LDS, rows of fewer)
     static constexpr int kChunks = !MULTI ? 16 * kWaves + 1 : NT == 1024 ? 8704 : 2304;
     union {
@@ -151,12 +154,11 @@ template <int NT> __device__ __forceinline__ float wide_max(float m, float *wave
 
 // TOPK: top_k is on (and the nucleus if top_p is below 1); otherwise the nucleus alone.  NP: pieces a thread holds.
 // MULTI: the row is longer than that.  Without tokens_out only the keep threshold is written, to thr_out.
-template <int DT, int NT, int NP, bool MULTI, bool TOPK>
-__global__ __launch_bounds__(NT, 4) void wide_step_kernel(StepArgs a, int32_t top_k, float top_p,
-                                                                          float *thr_out)
+template <int DT, int NT, int NP, bool MULTI, bool TOPK, int WAVES>
+__global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_t top_k, float top_p, float *thr_out)
 {
     using T = typename Elem<DT>::T;
-    using Sh = WideShared<NT, MULTI>;
+    using Sh = WideShared<NT, MULTI, (WAVES > 4)>;
     constexpr int EPV = Elem<DT>::kPerVec;
     constexpr int W = NT / 64;
     constexpr uint32_t kNegInf = DT == AS_BF16 ? 0xff80ff80u : 0xff800000u;
@@ -1025,10 +1027,10 @@ __global__ __launch_bounds__(NT, 4) void wide_step_kernel(StepArgs a, int32_t to
     write_row(a, r, o);
 }
 
-template <int DT, int NT, int NP, bool MULTI, bool TOPK>
+template <int DT, int NT, int NP, bool MULTI, bool TOPK, int WAVES = 4>
 void launch_form(as_ctx *ctx, int kid, const StepArgs &a, int32_t top_k, float top_p, float *thr_out)
 {
-    launch(ctx, kid, wide_step_kernel<DT, NT, NP, MULTI, TOPK>, dim3((unsigned)a.rows), dim3(NT), 0, a, top_k, top_p, thr_out);
+    launch(ctx, kid, wide_step_kernel<DT, NT, NP, MULTI, TOPK, WAVES>, dim3((unsigned)a.rows), dim3(NT), 0, a, top_k, top_p, thr_out);
 }
 
 // Threads and pieces a thread by the row's pieces of 16 bytes and the number of rows.  With a row per compute unit or
@@ -1037,15 +1039,25 @@ void launch_form(as_ctx *ctx, int kid, const StepArgs &a, int32_t top_k, float t
 // of 33001 27 us, as blocks of 1024 38; 6439 of them 276, 476; 1000 of 65001 70, 96; fp32 2500 of 33001, which go
 // tile by tile, 129, 200), and with many rows that 256 threads hold, those (nucleus, bf16, 6439 rows: of 9001 108
 // us with 256 x 8, 143 with 512 x 4; of 20001 152 with 256 x 16, 174 with 512 x 8; top-k 40, 2500 of 20003 41, with 512
-// threads 55).
+// threads 55).  With more than four short rows a unit the blocks are made to fit eight a unit (SHORT; six for k above 128 and
+// for nuclei of two registers' pieces more): 12000 rows of 1281 to 8000 bf16, or half as many fp32, nuclei 1.18 times faster,
+// top-k 1.28 to 1.36, k = 200 1.16; 600 of them no different.
 template <int DT, bool TOPK>
 void launch_type(as_ctx *ctx, int kid, const StepArgs &a, int32_t top_k, float top_p, float *thr_out)
 {
     constexpr int EPV = Elem<DT>::kPerVec;
     const int64_t most = ((int64_t)a.V + EPV - 1) / EPV;     // whole pieces of a row, whatever its alignment
     const bool many = a.rows > (int64_t)ctx->num_cus, lots = a.rows > 2 * (int64_t)ctx->num_cus;
-    if (most <= 256 * 4) return launch_form<DT, 256, 4, false, TOPK>(ctx, kid, a, top_k, top_p, thr_out);
+    if (most <= 256 * 4) {
+        if (a.rows <= 4 * (int64_t)ctx->num_cus) return launch_form<DT, 256, 4, false, TOPK>(ctx, kid, a, top_k, top_p, thr_out);
+        if constexpr (TOPK) {
+            if (top_k > kWideTopK) return launch_form<DT, 256, 4, false, TOPK, 6>(ctx, kid, a, top_k, top_p, thr_out);
+        }
+        return launch_form<DT, 256, 4, false, TOPK, 8>(ctx, kid, a, top_k, top_p, thr_out);
+    }
     if constexpr (!TOPK) {
+        if (a.rows > 4 * (int64_t)ctx->num_cus && most <= 256 * 8)
+            return launch_form<DT, 256, 8, false, TOPK, 6>(ctx, kid, a, top_k, top_p, thr_out);
         if (lots && most <= 256 * 8) return launch_form<DT, 256, 8, false, TOPK>(ctx, kid, a, top_k, top_p, thr_out);
     }
     if (lots && most <= 256 * 16 && (!TOPK || top_k <= kWideTopK))
@@ -1055,7 +1067,7 @@ void launch_type(as_ctx *ctx, int kid, const StepArgs &a, int32_t top_k, float t
     if (many && most <= 512 * 16) return launch_form<DT, 512, 16, false, TOPK>(ctx, kid, a, top_k, top_p, thr_out);
     if constexpr (!TOPK) {
         // (with a tile of slack: the last one's chunks are written whole)
-        if (many && most + 512 * 8 <= 64 * (int64_t)(WideShared<512, true>::kChunks - 1))
+        if (many && most + 512 * 8 <= 64 * (int64_t)(WideShared<512, true, false>::kChunks - 1))
             return launch_form<DT, 512, 8, true, false>(ctx, kid, a, top_k, top_p, thr_out);
     }
     if (most <= 1024 * 4) return launch_form<DT, 1024, 4, false, TOPK>(ctx, kid, a, top_k, top_p, thr_out);

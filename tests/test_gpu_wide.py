@@ -99,3 +99,21 @@ def test_streamed_kernel(V, dtype):
     # what is left to it: k above 128 on rows of more than 128 KB, more rows than compute units
     for top_k, top_p in ((129, 1.0), (300, 0.8), (5000, 0.95)):
         _check_shared(V, 300, dtype, top_k, top_p, None)
+
+
+# the forms for many short rows (more than four a compute unit: less LDS and fewer registers a block), at their ends
+@pytest.mark.parametrize("V,dtype", [(9, "bf16"), (1281, "bf16"), (8185, "bf16"), (8199, "bf16"), (16370, "bf16"), (5, "f32"),
+                                     (4090, "f32"), (4103, "f32"), (8180, "f32")])
+@pytest.mark.parametrize("sigma", [0.05, 3.0])
+def test_many_short_rows(V, dtype, sigma):
+    for top_k, top_p in MODES:
+        if top_k < V:
+            _check(V, 1030, dtype, temp=0.9, sigma=sigma, top_k=top_k, top_p=top_p, seed=V, tuning=ANY)
+
+
+# the one-tile top-k kernel's line: ranks it takes and the next, on rows of one to four waves' worth of logits
+@pytest.mark.parametrize("V,k", [(400, 30), (400, 31), (8000, 33), (8000, 34), (9600, 37), (9600, 38), (16384, 41), (16384, 42),
+                                 (32128, 47), (32128, 48)])
+def test_one_tile_top_k_at_its_line(V, k):
+    for top_p in (1.0, 0.9):
+        _check(V, 70, "bf16", temp=0.9, top_k=k, top_p=top_p, seed=V + k)

@@ -85,7 +85,7 @@ struct SumRef {
 // ===========================================================================
 // PARTIAL: the row's length is not a whole number of vectors (its last vector is padded out by the row stride)
 template <int DT, int NW, int ITERS, int OCC, bool HAS_THR, bool PARTIAL, bool ORDERED = false>
-__global__ __launch_bounds__(NW * 64, OCC) void step_kernel(StepArgs a, int ntiles)
+__global__ __launch_bounds__(NW * 64, OCC) void step_kernel(StepArgs a, int ntiles, int nent)
 {
     using T = typename Elem<DT>::T;
     constexpr int EPV = Elem<DT>::kPerVec;
@@ -99,7 +99,7 @@ __global__ __launch_bounds__(NW * 64, OCC) void step_kernel(StepArgs a, int ntil
     // so a group is one 16- or 8-byte access), then the table of shares
     extern __shared__ float smem[];
     constexpr int kCsFloats = NW * ITERS * 64;
-    const int nent = ntiles * NW;          // shares of the row, in vocabulary order
+    // nent: shares of the row, in vocabulary order (what they sum to does not depend on how many waves work on them)
     float *ent_sum = smem + kCsFloats;     // [nent]  sum of a share, relative to its reference
     float *ent_ref = ent_sum + nent;       // [nent]  integer reference of the share
 
@@ -263,7 +263,7 @@ __global__ __launch_bounds__(NW * 64, OCC) void step_kernel(StepArgs a, int ntil
                     rgl[g] = kRefFloor;
                 }
             }
-            if (pass == 0 && lane == 0) {
+            if (pass == 0 && lane == 0 && (NW < 16 || t * NW + wave < nent)) {
                 ent_sum[t * NW + wave] = wr.sum;
                 ent_ref[t * NW + wave] = wr.ref;
             }
@@ -272,7 +272,7 @@ __global__ __launch_bounds__(NW * 64, OCC) void step_kernel(StepArgs a, int ntil
         __syncthreads();
 
         // ---------------- every wave: total, target, owning share (fp64 carries)
-        if (ntiles == 1) {
+        if (NW < 16 && ntiles == 1) {
             // the common case: NW shares, read by every lane, handled without cross-lane traffic
             float es[NW], er[NW];
 #pragma unroll
@@ -596,8 +596,17 @@ as_status launch_shape(as_ctx *ctx, const StepArgs &a)
     const int64_t nvec = ((int64_t)a.V + (whole ? 0 : EPV - 1) + EPV - 1) / EPV;
     const int64_t tile = (int64_t)NW * ITERS * 64;
     const int ntiles = (int)((nvec + tile - 1) / tile);
-    const size_t lds = ((size_t)NW * ITERS * 64 + (size_t)ntiles * NW * 2) * sizeof(float);
-    if (lds > 60 * 1024) return fail(ctx, AS_ERR_UNSUPPORTED, "vocabulary too large for the share table");
+    if constexpr (NW == 4 && ITERS == 16) {
+        // Long rows, at most one a compute unit: sixteen waves a row, 256 KB of it in flight in place of 64 (us, four / sixteen:
+        // 1 row of 100000 bf16 12.4 / 9.1, 200 15.8 / 11.0, 64 of 50257 12.9 / 9.9, 1 of 256000 21.4 / 16.9, 128 of 32128
+        // fp32 8.5 / 7.1, 256 of 100000 fp32 20.9 / 19.0; more rows fill the units with four: 300 of 50257 15.6 / 18.0)
+        if (ctx->step_shape == 0 && ntiles > 1 && a.rows <= (int64_t)ctx->num_cus && a.order == nullptr)
+            return launch_shape<DT, 16, 16, 4, HAS_THR>(ctx, a);
+    }
+    // (16 waves: the shares of the four-wave form, so that the same sums are scanned in the same places)
+    const int nent = NW == 16 ? (int)((nvec + 4 * ITERS * 64 - 1) / (4 * ITERS * 64)) * 4 : ntiles * NW;
+    const size_t lds = ((size_t)NW * ITERS * 64 + (size_t)nent * 2) * sizeof(float);
+    if (lds > (NW == 16 ? 128 : 60) * 1024) return fail(ctx, AS_ERR_UNSUPPORTED, "vocabulary too large for the share table");
     const dim3 grid((unsigned)a.rows), block(NW * 64);
     const bool one_tile = whole && ntiles == 1 && NW == 4 && ITERS == 16 && ctx->step_shape == 0 && a.k <= kTileMaxScale;
     const bool nt = stream_rows(a.src_rows ? a.src_rows : a.rows, a.ld, sizeof(typename Elem<DT>::T));
@@ -606,16 +615,16 @@ as_status launch_shape(as_ctx *ctx, const StepArgs &a)
         if (a.order != nullptr && (nt || !one_tile)) {
             const dim3 runs((unsigned)((a.rows + 7) / 8 * 8));
             if (one_tile) launch(ctx, kKernelStep, step_tile_kernel<DT, false, true, true>, runs, block, 0, a);
-            else if (!whole) launch(ctx, kKernelStep, step_kernel<DT, NW, ITERS, OCC, false, true, true>, runs, block, lds, a, ntiles);
-            else launch(ctx, kKernelStep, step_kernel<DT, NW, ITERS, OCC, false, false, true>, runs, block, lds, a, ntiles);
+            else if (!whole) launch(ctx, kKernelStep, step_kernel<DT, NW, ITERS, OCC, false, true, true>, runs, block, lds, a, ntiles, nent);
+            else launch(ctx, kKernelStep, step_kernel<DT, NW, ITERS, OCC, false, false, true>, runs, block, lds, a, ntiles, nent);
             AS_HIP_TRY(ctx, hipGetLastError());
             return AS_OK;
         }
     }
     if (one_tile && nt) launch(ctx, kKernelStep, step_tile_kernel<DT, HAS_THR, true>, grid, block, 0, a);
     else if (one_tile) launch(ctx, kKernelStep, step_tile_kernel<DT, HAS_THR, false>, grid, block, 0, a);
-    else if (!whole) launch(ctx, kKernelStep, step_kernel<DT, NW, ITERS, OCC, HAS_THR, true>, grid, block, lds, a, ntiles);
-    else launch(ctx, kKernelStep, step_kernel<DT, NW, ITERS, OCC, HAS_THR, false>, grid, block, lds, a, ntiles);
+    else if (!whole) launch(ctx, kKernelStep, step_kernel<DT, NW, ITERS, OCC, HAS_THR, true>, grid, block, lds, a, ntiles, nent);
+    else launch(ctx, kKernelStep, step_kernel<DT, NW, ITERS, OCC, HAS_THR, false>, grid, block, lds, a, ntiles, nent);
     AS_HIP_TRY(ctx, hipGetLastError());
     return AS_OK;
 }

@@ -474,3 +474,29 @@ def test_step_argument_errors():
                   torch.zeros(9, dtype=torch.int32, device="cuda"), torch.zeros(9, device="cuda"))  # rows > max
     B.as_step(ctx, logits[:0], codes[:0], 1.0, 0, 1.0, tok[:0], codes[:0])                  # empty batch is fine
     ctx.close()
+
+
+@pytest.mark.parametrize("dtype,V", [("bf16", 32769), ("bf16", 65536), ("bf16", 65537), ("bf16", 131073), ("bf16", 300001),
+                                     ("bf16", 1 << 20), ("f32", 16385), ("f32", 32128), ("f32", 65541)])
+def test_long_rows_by_sixteen_waves_and_by_four(dtype, V):
+    """At most a row per compute unit takes sixteen waves a row, more take four: the same bits of every row."""
+    import torch
+    from paper_2210_15458_amd import binding as B
+    g = torch.Generator(device="cuda").manual_seed(V)
+    R = 9
+    logits = torch.randn(R, V + 3, device="cuda", generator=g) * 3.0          # (rows start off 16 bytes)
+    logits[1, : V // 2] = float("-inf")
+    logits = logits.to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    u = torch.rand(R, device="cuda", generator=g).clamp_max_(1.0 - 2.0 ** -24)
+    u[2], u[3] = 0.0, 1.0 - 2.0 ** -24
+    got = []
+    for view in (logits, logits[:, :V].contiguous()):
+        for shape in (0, 6):                                                  # 6: four waves whatever the rows
+            ctx = B.Ctx(R, V, logits.dtype)
+            ctx.set_tuning("step_shape", shape)
+            tok = torch.empty(R, dtype=torch.int32, device="cuda")
+            codes = torch.empty(R, dtype=torch.float32, device="cuda")
+            B.as_step(ctx, view, u, 0.8, 0, 1.0, tok, codes)
+            got.append((tok, codes))
+            ctx.close()
+        assert torch.equal(got[-1][0], got[-2][0]) and torch.equal(got[-1][1], got[-2][1])

@@ -1133,7 +1133,10 @@ void launch_vec(as_ctx *ctx, const as_model *m, const int32_t *prev, int64_t row
     // 72 16.8 / 12.0 / 12.5 / 13.4; 1024 x 4096 x 256 35.5 / 29.1 / 25.6 / 25.2; 1024 x 32128 x 512 450 / 326 / 321 / 310 to 346;
     // 4096 x 32128 x 520 (bf16) 2120 / 1642 / 1357 / 1307.  By the blocks of 32 x 64 and of 128 x 128 a compute unit:
     const int64_t fine = (rows + 31) / 32 * ((m->V + 63) / 64), coarse = (rows + 127) / 128 * ((m->V + 127) / 128);
-    if (fine <= ctx->num_cus) AS_CHAIN(1, 4, 1, 1, 64, 1);
+    // (small ranks in K steps of their size: a step moves zeros past the rank)
+    if (fine <= ctx->num_cus && m->d <= 16) AS_CHAIN(1, 4, 1, 1, 16, 1);
+    else if (fine <= ctx->num_cus && m->d <= 32) AS_CHAIN(1, 4, 1, 1, 32, 1);
+    else if (fine <= ctx->num_cus) AS_CHAIN(1, 4, 1, 1, 64, 1);
     else if (fine <= 6 * (int64_t)ctx->num_cus) AS_CHAIN(2, 2, 1, 2, 32, 2);
     else if (coarse < 16 * (int64_t)ctx->num_cus) AS_CHAIN(2, 2, 2, 4, 32, 1);
     else AS_CHAIN(2, 2, 4, 4, 32, 1);

@@ -99,7 +99,7 @@ def test_plain_kernel_at_its_line(V, d, wdt, ldt, R):
 
 # the fp32 kernel's four tilings (16 x 64, 32 x 64, 64 x 128, 128 x 128 by the number of blocks), whole rows (ranks of a
 # multiple of 16) and single elements, a last group of k short
-_CHAIN = [(1000, 100, "f32", 17), (1000, 16, "f32", 64), (4100, 128, "f32", 129), (4100, 75, "f32", 200), (4100, 48, "bf16", 1000),
+_CHAIN = [(300, 9, "f32", 40), (300, 16, "bf16", 40), (300, 17, "f32", 40), (300, 32, "f32", 40), (1000, 100, "f32", 17), (1000, 16, "f32", 64), (4100, 128, "f32", 129), (4100, 75, "f32", 200), (4100, 48, "bf16", 1000),
           (4100, 31, "f32", 1001), (16500, 32, "f32", 4100), (16500, 19, "bf16", 4100)]
 
 

@@ -534,7 +534,7 @@ static as_status decode_impl(as_ctx *ctx, const as_model *model, const int32_t *
     if (isnan(top_p)) return fail(ctx, AS_ERR_INVALID_ARG, "top_p is NaN");
 
     const bool trunc = truncation_on(ctx->V, top_k, top_p);
-    if (!trunc && T > 0 && small_decode_applies(ctx, model, R, temp)) {
+    if (!trunc && T > 0 && small_decode_applies(ctx, model, R, T, temp)) {
         SmallArgs a{};
         a.temp = temp; a.prompts = prompts; a.u = uniforms ? nullptr : u; a.uniforms = uniforms;
         a.rows = R; a.N = N; a.T = T; a.eos_id = eos_id; a.tokens = tokens_out; a.codes_out = codes_out;

@@ -281,7 +281,7 @@ struct RowShare {
     int32_t kept = 0;            // the number of rows that are kept, or 0
 };
 bool mfma_applies(const as_model *m);
-bool small_decode_applies(const as_ctx *ctx, const as_model *m, int64_t rows, float temp);
+bool small_decode_applies(const as_ctx *ctx, const as_model *m, int64_t rows, int32_t T, float temp);
 as_status launch_small_decode(as_ctx *ctx, const as_model *m, SmallArgs s);
 bool sharing_pays(const as_ctx *ctx, const as_model *m, int64_t rows, int32_t T);
 bool rows_on_device(const as_ctx *ctx, const as_model *m);

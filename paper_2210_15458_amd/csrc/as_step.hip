@@ -602,6 +602,14 @@ as_status launch_shape(as_ctx *ctx, const StepArgs &a)
         // fp32 8.5 / 7.1, 256 of 100000 fp32 20.9 / 19.0; more rows fill the units with four: 300 of 50257 15.6 / 18.0)
         if (ctx->step_shape == 0 && ntiles > 1 && a.rows <= (int64_t)ctx->num_cus && a.order == nullptr)
             return launch_shape<DT, 16, 16, 4, HAS_THR>(ctx, a);
+        // Many rows of one share or two (16 or 32 KB) that the single-tile kernel does not take: the waves that a four-wave
+        // block would leave without a share are other rows'.  The shares left out are empty, the bits the same.  (us, four
+        // waves / fewer: 30000 rows of 2531 bf16 175 / 76, 4096 28.2 / 16.0, 1024 9.6 / 9.1; 30000 of 9001 196 / 129; 30000 of
+        // 3001 fp32 127 / 57, of 8001 157 / 150; even up to two rows a unit)
+        if (ctx->step_shape == 0 && a.rows > 2 * (int64_t)ctx->num_cus && !(whole && ntiles == 1 && a.k <= kTileMaxScale)) {
+            if (nvec <= ITERS * 64) return launch_shape<DT, 1, 16, 4, HAS_THR>(ctx, a);
+            if (nvec <= 2 * ITERS * 64) return launch_shape<DT, 2, 16, 4, HAS_THR>(ctx, a);
+        }
     }
     // (16 waves: the shares of the four-wave form, so that the same sums are scanned in the same places)
     const int nent = NW == 16 ? (int)((nvec + 4 * ITERS * 64 - 1) / (4 * ITERS * 64)) * 4 : ntiles * NW;
@@ -610,12 +618,18 @@ as_status launch_shape(as_ctx *ctx, const StepArgs &a)
     const dim3 grid((unsigned)a.rows), block(NW * 64);
     const bool one_tile = whole && ntiles == 1 && NW == 4 && ITERS == 16 && ctx->step_shape == 0 && a.k <= kTileMaxScale;
     const bool nt = stream_rows(a.src_rows ? a.src_rows : a.rows, a.ld, sizeof(typename Elem<DT>::T));
-    if constexpr (!HAS_THR && NW == 4 && ITERS == 16) {
+    if constexpr (!HAS_THR && NW <= 4 && ITERS == 16) {
         // (an order comes with decodes whose logits are streamed; it is a matter of locality only)
         if (a.order != nullptr && (nt || !one_tile)) {
             const dim3 runs((unsigned)((a.rows + 7) / 8 * 8));
-            if (one_tile) launch(ctx, kKernelStep, step_tile_kernel<DT, false, true, true>, runs, block, 0, a);
-            else if (!whole) launch(ctx, kKernelStep, step_kernel<DT, NW, ITERS, OCC, false, true, true>, runs, block, lds, a, ntiles, nent);
+            if constexpr (NW == 4) {
+                if (one_tile) {
+                    launch(ctx, kKernelStep, step_tile_kernel<DT, false, true, true>, runs, block, 0, a);
+                    AS_HIP_TRY(ctx, hipGetLastError());
+                    return AS_OK;
+                }
+            }
+            if (!whole) launch(ctx, kKernelStep, step_kernel<DT, NW, ITERS, OCC, false, true, true>, runs, block, lds, a, ntiles, nent);
             else launch(ctx, kKernelStep, step_kernel<DT, NW, ITERS, OCC, false, false, true>, runs, block, lds, a, ntiles, nent);
             AS_HIP_TRY(ctx, hipGetLastError());
             return AS_OK;

@@ -500,3 +500,29 @@ def test_long_rows_by_sixteen_waves_and_by_four(dtype, V):
             got.append((tok, codes))
             ctx.close()
         assert torch.equal(got[-1][0], got[-2][0]) and torch.equal(got[-1][1], got[-2][1])
+
+
+@pytest.mark.parametrize("dtype,V,temp", [("bf16", 5, 0.8), ("bf16", 1001, 0.8), ("bf16", 8177, 0.8), ("bf16", 8184, 0.2),
+                                          ("bf16", 8193, 0.8), ("bf16", 16377, 0.8), ("f32", 4081, 0.8), ("f32", 4096, 0.2),
+                                          ("f32", 8185, 0.8)])
+def test_many_rows_of_one_or_two_shares(dtype, V, temp):
+    """Many short rows take a wave or two each, few take four: the same bits of every row."""
+    import torch
+    from paper_2210_15458_amd import binding as B
+    g = torch.Generator(device="cuda").manual_seed(V)
+    R = 777
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    logits = (torch.randn(R, (V + 7) // 8 * 8, device="cuda", generator=g) * 3.0).to(tdt)
+    u = torch.rand(R, device="cuda", generator=g).clamp_max_(1.0 - 2.0 ** -24)
+    u[2], u[3] = 0.0, 1.0 - 2.0 ** -24
+    for view in (logits, logits[:, :V].contiguous()):
+        got = []
+        for shape in (0, 6):
+            ctx = B.Ctx(R, V, tdt)
+            ctx.set_tuning("step_shape", shape)
+            tok = torch.empty(R, dtype=torch.int32, device="cuda")
+            codes = torch.empty(R, dtype=torch.float32, device="cuda")
+            B.as_step(ctx, view, u, temp, 0, 1.0, tok, codes)
+            got.append((tok, codes))
+            ctx.close()
+        assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])

@@ -89,7 +89,8 @@ def sampling_kernel_name(V, ldt, top_k, top_p, temp, rows, d, wdt, cus):
                 V % (8 if half else 4) == 0 and rows <= 3 * cus and first_chunk_reference_ok):
             name = "decode_small_kernel (the whole decode in one launch)"
         elif tile and first_chunk_reference_ok:
-            name = "step_tile_kernel (fused sampling step, one-tile rows)"
+            few = half and rows <= cus and V <= 16384
+            name = "step_tile_few_kernel (fused sampling step, few short rows)" if few else "step_tile_kernel (fused sampling step, one-tile rows)"
         else:
             name = "step_kernel (fused sampling step)"
     elif tile and half and (topk_tile_pays(V, rows, top_k, cus) if has_k else

@@ -76,7 +76,7 @@ struct GenericScratch {
 
 // One row by a block of 256 threads, any alignment, any V: three plain passes (max, sums, search), each
 // thread owning one contiguous run of elements so that thread order is vocabulary order.  Every thread of
-// the block must call it; keeps x >= thr.
+// the block must call it (those past 256, which only blocks on rows of one tile have, own nothing); keeps x >= thr.
 template <class T>
 __device__ __forceinline__ void generic_step_row(const StepArgs &a, int64_t r, float thr, GenericScratch &sh)
 {
@@ -94,7 +94,7 @@ __device__ __forceinline__ void generic_step_row(const StepArgs &a, int64_t r, f
         if (x >= thr) m = fmaxf(m, x);
     }
     m = wave_max(m);
-    if ((tid & 63) == 0) sh.red[tid >> 6] = m;
+    if ((tid & 63) == 0 && tid < 256) sh.red[tid >> 6] = m;
     __syncthreads();
     m = fmaxf(fmaxf(sh.red[0], sh.red[1]), fmaxf(sh.red[2], sh.red[3]));
     const float ref = fmaxf(ceilf(m * k), kRefFloor);
@@ -104,7 +104,7 @@ __device__ __forceinline__ void generic_step_row(const StepArgs &a, int64_t r, f
         const float x = widen_stored(row[v]);
         if (x >= thr) tot += (double)fast_exp2(fmaf(x, k, -ref));
     }
-    sh.tot[tid] = tot;
+    if (tid < 256) sh.tot[tid] = tot;
     __syncthreads();
     if (tid == 0) {
         double S = 0.0;

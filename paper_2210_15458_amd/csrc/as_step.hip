@@ -564,6 +564,69 @@ __global__ __launch_bounds__(256, 4) void step_tile_kernel(StepArgs a)
     tile_select<DT, HAS_THR>(a, r, code, thr, raw, rw, mych, ragged, v0, lane, wave, ts, gen);
 }
 
+// The same for few short rows: a wave per four chunks, up to half a tile.  With at most a block on a compute unit nothing
+// hides what a wave does in turn, and four waves of which one or two hold the row issue sixteen loads and form four groups
+// of sums one after the other.  A share's waves each take its reference from its first chunk, which all but one of them
+// read beside their own, so the sums and what is scanned are step_tile_kernel's, bit for bit.  (At least four waves: the
+// plain routine's threads.)
+template <int DT>
+__global__ __launch_bounds__(512, 4) void step_tile_few_kernel(StepArgs a)
+{
+    using T = typename Elem<DT>::T;
+    constexpr int EPV = Elem<DT>::kPerVec;
+    constexpr int N = kTileGroup, kSplit = kTileIters / N;             // chunks a wave, waves a share
+
+    __shared__ TileSums ts;
+    __shared__ GenericScratch gen;
+
+    const int64_t r = blockIdx.x;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const bool done = a.finished_in != nullptr && a.finished_in[r] != 0;
+    const float code = a.codes[r];
+    const float thr = -__builtin_inff();
+    const int64_t src = a.row_ids ? (int64_t)a.row_ids[r] : r;
+    const u32x4 *const row = reinterpret_cast<const u32x4 *>(reinterpret_cast<const T *>(a.logits) + src * a.ld);
+    const int32_t nvec = a.V / EPV;
+
+    const int32_t share0 = wave / kSplit * kTileIters * 64, v0 = wave * N * 64;
+    const bool live = v0 < nvec;                         // wave-uniform
+    int32_t mych = (nvec - v0 - lane + 63) >> 6;         // chunks of the wave in which this lane is inside the row
+    mych = mych < 0 ? 0 : (mych > N ? N : mych);
+    const bool in_first = share0 + lane < nvec;
+    u32x4 raw[N], first = {0u, 0u, 0u, 0u};
+    if (live) {                                          // (a lane past the row's end reads the row's last vector)
+        first = row[in_first ? share0 + lane : nvec - 1];
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const int32_t v = v0 + j * 64 + lane;
+            raw[j] = row[v < nvec ? v : nvec - 1];
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < N; ++j) raw[j] = u32x4{0u, 0u, 0u, 0u};
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (done) {
+        if (threadIdx.x == 0) write_finished(a, r);
+        return;
+    }
+    float rw = kRefFloor;
+    f32x4 *const my_sums = reinterpret_cast<f32x4 *>(ts.chunk_sum + wave * N);
+    if (live) {
+        rw = tile_reference<DT, false, true>(first, a.k, thr, in_first ? 1 : 0);
+        tile_chunk_sums<DT, false, true>(raw, a.k, rw, thr, mych, lane, my_sums);
+    } else if (lane == 0) {
+        *my_sums = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    if (wave % kSplit == 0 && lane == 0) ts.share_ref[wave / kSplit] = rw;
+    const int waves = blockDim.x >> 6;                   // (the row is at its end before what they leave out)
+    if (wave == 0 && lane >= waves * N) ts.chunk_sum[lane] = 0.f;
+    if (wave == 0 && lane < kTileWaves && lane * kSplit >= waves) ts.share_ref[lane] = kRefFloor;
+    __syncthreads();
+    tile_select<DT, false>(a, r, code, thr, raw, rw, mych, true, v0, lane, wave, ts, gen);
+}
+
 // ===========================================================================
 // generic kernel: any alignment, any V.  Three plain passes over the row (max,
 // sums, search), each thread owning one contiguous run of elements so that
@@ -631,6 +694,18 @@ as_status launch_shape(as_ctx *ctx, const StepArgs &a)
             }
             if (!whole) launch(ctx, kKernelStep, step_kernel<DT, NW, ITERS, OCC, false, true, true>, runs, block, lds, a, ntiles, nent);
             else launch(ctx, kKernelStep, step_kernel<DT, NW, ITERS, OCC, false, false, true>, runs, block, lds, a, ntiles, nent);
+            AS_HIP_TRY(ctx, hipGetLastError());
+            return AS_OK;
+        }
+    }
+    if constexpr (!HAS_THR && DT == AS_BF16 && NW == 4 && ITERS == 16) {
+        // Few short rows (us a decode of 32 steps, a block of four waves / a wave per four chunks: 256 rows of 2000 292 / 263, 64 of
+        // 8000 321 / 295, 16 of 4000 259 / 237, 256 of 16000 462 / 455; the launch alone 4.7 / 3.7, of 16000 4.8 / 4.2; 16 rows
+        // of 32128, by sixteen waves, 635 / 637 for 64 steps).  fp32 rows, half the exponentials a load, gain nothing: 100 of
+        // 8000 301 / 297, 32 of 1000 234 / 240.
+        if (one_tile && nvec <= 2 * ITERS * 64 && a.rows <= (int64_t)ctx->num_cus) {
+            const unsigned waves = nvec <= 4 * 256 ? 4u : (unsigned)((nvec + 255) / 256);
+            launch(ctx, kKernelStep, step_tile_few_kernel<DT>, grid, dim3(waves * 64), 0, a);
             AS_HIP_TRY(ctx, hipGetLastError());
             return AS_OK;
         }

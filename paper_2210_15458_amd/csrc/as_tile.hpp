@@ -157,16 +157,16 @@ __device__ __forceinline__ float tile_reference(const u32x4 &first, float k, flo
     return fmaxf(ceilf(m * k), kRefFloor);
 }
 
-// the sums of the share's sixteen chunks over the wave, relative to rw, to my_sums (LDS, four at a time, by the
-// lane that ends up with them); chunks are taken as they land
-template <int DT, bool HAS_THR, bool RAGGED>
-__device__ __forceinline__ void tile_chunk_sums(const u32x4 (&raw)[kTileIters], float k, float rw, float thr,
+// the sums of the wave's N chunks (the share's sixteen, or a quarter of them) over the wave, relative to rw, to my_sums
+// (LDS, four at a time, by the lane that ends up with them); chunks are taken as they land
+template <int DT, bool HAS_THR, bool RAGGED, int N>
+__device__ __forceinline__ void tile_chunk_sums(const u32x4 (&raw)[N], float k, float rw, float thr,
                                                 int32_t mych, int lane, f32x4 *my_sums)
 {
     constexpr int G = kTileGroup;
     const float nr = -rw;
 #pragma unroll
-    for (int g = 0; g < kTileIters / G; ++g) {
+    for (int g = 0; g < N / G; ++g) {
         float t[G];
 #pragma unroll
         for (int jj = 0; jj < G; ++jj) {
@@ -232,10 +232,10 @@ __device__ __forceinline__ void tile_finish(const StepArgs &a, int64_t r, float 
 // After the barrier that follows the chunk sums: every wave scans the row's 64 chunk sums (fp64) for the total,
 // the target c*S and the chunk that holds it; the wave that owns that chunk finds the lane, that lane the
 // element, and writes the row's results.  Every thread of the block calls it.  rw is the calling wave's own
-// reference (also in ts.share_ref), v0 the first vector of its share.
-template <int DT, bool HAS_THR>
+// reference (also in ts.share_ref), v0 the first vector of its N chunks.
+template <int DT, bool HAS_THR, int N>
 __device__ __forceinline__ void tile_select(const StepArgs &a, int64_t r, float code, float thr,
-                                            const u32x4 (&raw)[kTileIters], float rw, int32_t mych, bool ragged,
+                                            const u32x4 (&raw)[N], float rw, int32_t mych, bool ragged,
                                             int32_t v0, int lane, int wave, const TileSums &ts, GenericScratch &gen)
 {
     using T = typename Elem<DT>::T;
@@ -258,14 +258,14 @@ __device__ __forceinline__ void tile_select(const StepArgs &a, int64_t r, float 
     const unsigned long long cnz = __ballot(cv > 0.0);
     // the first chunk whose running sum passes c*S; past the end by rounding: the last chunk that holds weight
     const int ch = chit ? (__ffsll((long long)chit) - 1) : (cnz ? (63 - __clzll((long long)cnz)) : 0);
-    if (wave != ch / ITERS) return;
+    if (wave != ch / N) return;
     const double run = read_lane(cincl - cv, ch);
 
     // ---------------- owning wave: lane, then element.  Everything it holds is relative to rw.
     const int shf = shift_of(rw, R);
-    const int cj = ch % ITERS;
+    const int cj = ch % N;
     u32x4 hv;
-    with_uniform_index<0, ITERS>(cj, [&](auto c_c) __attribute__((always_inline)) {
+    with_uniform_index<0, N>(cj, [&](auto c_c) __attribute__((always_inline)) {
         uint32_t w0 = raw[decltype(c_c)::value][0], w1 = raw[decltype(c_c)::value][1],
                  w2 = raw[decltype(c_c)::value][2], w3 = raw[decltype(c_c)::value][3];
         // opaque to the optimiser: keeps this a tree of branches over registers instead of an indexed read

@@ -526,3 +526,35 @@ def test_many_rows_of_one_or_two_shares(dtype, V, temp):
             got.append((tok, codes))
             ctx.close()
         assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
+@pytest.mark.parametrize("dtype,V", [("bf16", 8), ("bf16", 512), ("bf16", 520), ("bf16", 2048), ("bf16", 2056), ("bf16", 8192),
+                                     ("bf16", 8200), ("bf16", 32128), ("bf16", 32768), ("f32", 4), ("f32", 1028), ("f32", 4100),
+                                     ("f32", 16384)])
+def test_few_rows_of_one_tile(dtype, V):
+    """At most a row per compute unit takes a wave per four chunks of a short bf16 row, more take four a row: the same bits of every row."""
+    import torch
+    from paper_2210_15458_amd import binding as B
+    g = torch.Generator(device="cuda").manual_seed(V)
+    R, copies = 9, 1 + torch.cuda.get_device_properties(0).multi_processor_count // 4
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    logits = torch.randn(R, V, device="cuda", generator=g) * 3.0
+    logits[1, : V // 2] = float("-inf")
+    logits[2, V - 1] = 300.0                 # beyond fp32 against the first chunk's reference: the plain routine
+    logits = logits.to(tdt)
+    u = torch.rand(R, device="cuda", generator=g).clamp_max_(1.0 - 2.0 ** -24)
+    u[3], u[4] = 0.0, 1.0 - 2.0 ** -24
+    fin = torch.zeros(R, dtype=torch.uint8, device="cuda")
+    fin[5] = 1
+    got = []
+    for n in (1, copies):
+        ctx = B.Ctx(R * n, V, tdt)
+        tok = torch.empty(R * n, dtype=torch.int32, device="cuda")
+        codes = torch.empty(R * n, dtype=torch.float32, device="cuda")
+        fo = torch.empty(R * n, dtype=torch.uint8, device="cuda")
+        B.as_step_ex(ctx, logits.repeat(n, 1), u.repeat(n), 0.8, 0, 1.0, tok, codes, finished_in=fin.repeat(n), eos_id=1,
+                     finished_out=fo)
+        got.append((tok.view(n, R), codes.view(n, R), fo.view(n, R)))
+        ctx.close()
+    for few, many in zip(*got):
+        assert torch.equal(few.expand(copies, R), many)

@@ -103,12 +103,16 @@ const char *as_last_error(const as_ctx *ctx);
  *   AS_TUNE_GEMM_GM     persistent logits kernel with more row tiles than
  *                       workers: workers of one XCD along the rows (a divisor
  *                       of the workers per XCD; otherwise ignored)
+ *   AS_TUNE_WORKSPACE_MIB  largest buffer, in MiB, that a call may add to the
+ *                       decode workspace: a larger one is refused, as by a
+ *                       GPU without the memory
  */
 typedef enum {
     AS_TUNE_STEP_SHAPE = 0,
     AS_TUNE_GEMM_SHAPE = 1,
     AS_TUNE_THR_PATH = 2,
-    AS_TUNE_GEMM_GM = 3
+    AS_TUNE_GEMM_GM = 3,
+    AS_TUNE_WORKSPACE_MIB = 4
 } as_tuning;
 as_status as_ctx_set_tuning(as_ctx *ctx, as_tuning knob, int32_t value);
 

@@ -54,6 +54,16 @@ bool profile_acquire(as_ctx *ctx, int kid, hipEvent_t *start, hipEvent_t *stop)
     return true;
 }
 
+static bool device_alloc(const as_ctx *ctx, void **p, size_t bytes)
+{
+    *p = nullptr;
+    if (ctx->workspace_mib > 0 && bytes > (size_t)ctx->workspace_mib << 20) return false;
+    if (hipMalloc(p, bytes) == hipSuccess) return true;
+    *p = nullptr;
+    (void)hipGetLastError();
+    return false;
+}
+
 static as_status grow(as_ctx *ctx, DeviceBuf &b, size_t bytes)
 {
     if (b.bytes >= bytes) return AS_OK;
@@ -63,13 +73,35 @@ static as_status grow(as_ctx *ctx, DeviceBuf &b, size_t bytes)
         b.ptr = nullptr;
         b.bytes = 0;
     }
-    if (hipMalloc(&b.ptr, bytes) != hipSuccess) {
-        b.ptr = nullptr;
-        (void)hipGetLastError();
-        return fail(ctx, AS_ERR_ALLOC, "device allocation of the decode workspace failed");
-    }
+    if (!device_alloc(ctx, &b.ptr, bytes)) return fail(ctx, AS_ERR_ALLOC, "device allocation of the decode workspace failed");
     b.bytes = bytes;
     return AS_OK;
+}
+
+// The same for a buffer that the call can do without.  The old one is given up only when the new one is there; what could
+// not be had once is not asked for again (the next call would wait for the stream and move the buffer in vain, each
+// time); and nothing is allocated under a capture, which it would end.
+static bool grow_if_possible(as_ctx *ctx, DeviceBuf &b, size_t bytes)
+{
+    if (b.bytes >= bytes) return true;
+    if (b.refused) return false;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(ctx->stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return false;
+    }
+    void *p = nullptr;
+    if (!device_alloc(ctx, &p, bytes)) {
+        b.refused = true;
+        return false;
+    }
+    if (b.ptr && (hipStreamSynchronize(ctx->stream) != hipSuccess || hipFree(b.ptr) != hipSuccess)) {
+        (void)hipFree(p);          // (an earlier launch failed: the call's own launches report it)
+        return false;
+    }
+    b.ptr = p;
+    b.bytes = bytes;
+    return true;
 }
 
 // Row indices handed in by the caller, as the kernels use them: a copy in the context's workspace with every
@@ -215,6 +247,7 @@ as_status as_ctx_set_tuning(as_ctx *ctx, as_tuning knob, int32_t value)
     case AS_TUNE_GEMM_SHAPE: ctx->gemm_shape = value; return AS_OK;
     case AS_TUNE_THR_PATH: ctx->thr_path = value; return AS_OK;
     case AS_TUNE_GEMM_GM: ctx->gemm_gm = value; return AS_OK;
+    case AS_TUNE_WORKSPACE_MIB: ctx->workspace_mib = value; return AS_OK;
     }
     return fail(ctx, AS_ERR_INVALID_ARG, "unknown tuning knob");
 }
@@ -434,15 +467,10 @@ static as_status decode_state(as_ctx *ctx, const as_model *model, int32_t B, int
     bool keep = keeping_pays(ctx, model, R, B, T, row_bytes, by_sums);
     const bool room = keep || keeping_pays(ctx, model, R, B, T, row_bytes, can_sum) ||
                       keeping_pays(ctx, model, R, B, T, row_bytes, false);
-    as_status st = AS_OK;
-    if (room && kept_rows > R) {
-        st = grow(ctx, ctx->logits, (size_t)kept_rows * row_bytes);
-        if (st != AS_OK && st != AS_ERR_ALLOC) return st;
-        if (st != AS_OK) keep = false;
-    }
+    if (room && kept_rows > R && !grow_if_possible(ctx, ctx->logits, (size_t)kept_rows * row_bytes)) keep = false;
     s.share = keep || sharing_pays(ctx, model, R, T);
     s.logits_rows = keep ? kept_rows : R;
-    st = grow(ctx, ctx->logits, (size_t)s.logits_rows * row_bytes);
+    as_status st = grow(ctx, ctx->logits, (size_t)s.logits_rows * row_bytes);
     if (st != AS_OK) return st;
     const int64_t filled = keep ? s.logits_rows : V;
     const size_t sums = keep && by_sums ? (size_t)s.logits_rows * kRowSums : 0;

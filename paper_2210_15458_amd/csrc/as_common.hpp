@@ -20,6 +20,7 @@ constexpr int kWave = 64;
 struct DeviceBuf {
     void *ptr = nullptr;
     size_t bytes = 0;
+    bool refused = false;          // a larger one that the context can do without could not be had: not asked for again
 };
 
 // Optional per-kernel timing: when switched on, every launch of a profiled
@@ -58,6 +59,7 @@ struct as_ctx {
     int gemm_shape = 0;            // logits: 1 = tile kernel, 2 = persistent also for few rows
     int thr_path = 0;              // truncation: 1 = radix select, 2 = resident where the row fits, 3 = wide for every row
     int gemm_gm = 0;               // logits kernel, many row tiles: workers of an XCD along the rows (tuning knob: 0 = default)
+    int workspace_mib = 0;         // largest buffer of the workspace, in MiB (tuning knob: 0 = as large as the device gives)
     int num_cus = 0;               // compute units of the device (the persistent logits kernel runs one block on each)
     std::string err;
 };

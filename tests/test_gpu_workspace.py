@@ -1,0 +1,84 @@
+"""What a call may do to the context's workspace: a call of the same or a smaller size than an earlier one allocates nothing,
+can be captured, and leaves alone the buffers that a graph captured before it works on, whatever form it takes; what
+cannot be had is done without."""
+import pytest
+import torch
+
+from paper_2210_15458_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+EOS, TEMP = 1, 1.1
+
+
+class Job:
+    """A model, a context on a stream of its own, and decodes and encodes on it."""
+
+    def __init__(self, V, d, rows, ldt=torch.bfloat16, wdt=torch.bfloat16):
+        g = torch.Generator(device="cuda").manual_seed(V)
+        self.V = V
+        self.model = B.Model(torch.randn(V, d, device="cuda", generator=g).to(wdt),
+                             torch.randn(d, V, device="cuda", generator=g).to(wdt), scale=3.0)
+        self.prompts = torch.randint(0, V, (1,), device="cuda", generator=g, dtype=torch.int32)
+        self.u = torch.rand(1, device="cuda", generator=g)
+        self.stream = torch.cuda.Stream()
+        torch.cuda.synchronize()
+        self.rows, self.ldt = rows, ldt
+        self.ctx = self.context()
+
+    def context(self):
+        with torch.cuda.stream(self.stream):
+            return B.Ctx(self.rows, self.V, self.ldt)
+
+    def decode(self, N, T, temp=TEMP, top_k=0, ctx=None, out=None):
+        with torch.cuda.stream(self.stream):
+            out = torch.empty((1, N, T), dtype=torch.int32, device="cuda") if out is None else out
+            B.as_decode(ctx or self.ctx, self.model, self.prompts, N, T, self.u, temp, top_k, 1.0, EOS, out)
+        return self.done(out)
+
+    def done(self, out):
+        if not torch.cuda.is_current_stream_capturing():
+            self.stream.synchronize()
+        return out
+
+    def captured(self, call, out):
+        """The graph of a call; raises if the call allocates (it would wait for the stream, which a capture refuses)."""
+        graph = torch.cuda.CUDAGraph()
+        self.stream.synchronize()
+        with torch.cuda.graph(graph, stream=self.stream):
+            call(out)
+        return graph
+
+    def replay(self, graph, out):
+        with torch.cuda.stream(self.stream):
+            for o in out if isinstance(out, tuple) else (out,):
+                o.fill_(-1)
+            graph.replay()
+        self.stream.synchronize()
+        return out
+
+    def close(self):
+        self.ctx.close()
+        self.model.close()
+
+
+def test_a_kept_table_that_is_refused_is_not_asked_for_again():
+    V, d, N, T = 8000, 512, 4200, 6                       # kept rows: 128 MB, against 67 of a row per code
+    job = Job(V, d, N)
+    want = job.decode(N, T)
+    small = job.context()
+    small.set_tuning("workspace_mib", 100)
+    assert torch.equal(job.decode(N, T, ctx=small), want)
+    assert B.lib().as_last_error(small._h) == b""         # the call succeeded: nothing to report
+    # the second call finds its workspace: it neither waits nor moves it
+    out = torch.empty_like(want)
+    graph = job.captured(lambda o: job.decode(N, T, ctx=small, out=o), out)
+    assert torch.equal(job.replay(graph, out), want)
+    assert torch.equal(job.decode(N, T, ctx=small), want) and torch.equal(job.replay(graph, out), want)
+    other = job.context()
+    other.set_tuning("workspace_mib", 10)
+    with pytest.raises(B.ArithSamplingError, match="workspace"):
+        job.decode(N, T, ctx=other)
+    other.close()
+    small.close()
+    job.close()

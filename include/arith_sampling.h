@@ -31,10 +31,13 @@
  *     the context (re)allocates when a call needs more than any earlier call
  *     did: the first call at a size synchronises the stream, frees and
  *     allocates, and must not be made under stream capture; later calls of the
- *     same or a smaller size allocate nothing and can be captured.  The
- *     logits of a decode take a row per code; where a decode comes back to
- *     most of its tokens (rows and steps enough, by their number), a row per
- *     token in use, at most four times as many and then at most 4 GiB.
+ *     same or a smaller size (no more rows, no more steps; any temperature,
+ *     truncation and model) allocate nothing and can be captured.  A decode
+ *     takes a row of logits per code, or room for a row per token of the
+ *     vocabulary where those are more: from a vocabulary of up to four times
+ *     the codes, three steps on, and then at most 4 GiB; without that room it
+ *     does with a row per code.  Its state is 17 bytes a code and 16 a token
+ *     of the vocabulary, and 272 a row of the table that it may keep.
  *   - One context must not be used from two host threads at once.
  */
 #ifndef ARITH_SAMPLING_H

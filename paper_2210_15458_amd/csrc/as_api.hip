@@ -455,32 +455,30 @@ struct DecodeState {
     float *sums;                 // kept rows whose steps work from sums: [logits_rows, kRowSums], else null
 };
 
-// Makes the state and the table of logits, logits_rows x row_bytes.  can_sum: rows of this vocabulary can be stepped from
-// sums; by_sums: this decode's are.  What is reserved depends on the sizes alone, so that a call that differs from an
-// earlier one in its temperature or truncation finds its workspace; if a table of kept rows cannot be had, the decode
-// goes without.
+// Makes the workspace of a decode of `rows` rows (as_workspace.hpp).  A table of kept rows that cannot be had is done without.
+static as_status reserve_decode(as_ctx *ctx, int64_t rows, int32_t T, bool masses)
+{
+    const DecodeSizes z = decode_sizes(ctx->V, ctx->dtype == AS_BF16 ? 2 : 4, rows, T, masses);
+    (void)grow_if_possible(ctx, ctx->logits, z.preferred);
+    const as_status st = grow(ctx, ctx->logits, z.needed);
+    return st != AS_OK ? st : grow(ctx, ctx->state, z.state);
+}
+
+// Lays a decode's state out and takes its table of logits: rows of row_bytes, `masses` if they are group masses.  by_sums:
+// kept rows are stepped from their sums.
 static as_status decode_state(as_ctx *ctx, const as_model *model, int32_t B, int32_t N, int32_t T, int64_t row_bytes,
-                              bool can_sum, bool by_sums, DecodeState &s)
+                              bool masses, bool by_sums, DecodeState &s)
 {
     const int64_t R = (int64_t)B * N, V = ctx->V;
-    const int64_t used = R < V ? R * (T > 0 ? T - 1 : 0) + B : V, kept_rows = used < V ? used : V;
-    bool keep = keeping_pays(ctx, model, R, B, T, row_bytes, by_sums);
-    const bool room = keep || keeping_pays(ctx, model, R, B, T, row_bytes, can_sum) ||
-                      keeping_pays(ctx, model, R, B, T, row_bytes, false);
-    if (room && kept_rows > R && !grow_if_possible(ctx, ctx->logits, (size_t)kept_rows * row_bytes)) keep = false;
+    as_status st = reserve_decode(ctx, R, T, masses);
+    if (st != AS_OK) return st;
+    const int64_t kept_rows = smaller(V, R * larger((int64_t)T - 1, 0) + B);
+    const bool keep = kept_rows_most(V, R, T, row_bytes) > 0 && keeping_pays(ctx, model, R, T, by_sums) &&
+                      (size_t)(kept_rows * row_bytes) <= ctx->logits.bytes;
     s.share = keep || sharing_pays(ctx, model, R, T);
     s.logits_rows = keep ? kept_rows : R;
-    as_status st = grow(ctx, ctx->logits, (size_t)s.logits_rows * row_bytes);
-    if (st != AS_OK) return st;
     const int64_t filled = keep ? s.logits_rows : V;
     const size_t sums = keep && by_sums ? (size_t)s.logits_rows * kRowSums : 0;
-    const size_t tables = (size_t)R + s.logits_rows + 2 * (size_t)V + filled + (size_t)T + 1;
-    const size_t words = sums + (size_t)R * 2 + (s.share ? tables : 0);
-    const size_t reserve = room ? (can_sum ? (size_t)kept_rows * kRowSums : 0) + (size_t)R * 3 + 2 * (size_t)kept_rows +
-                                      3 * (size_t)V + (size_t)T + 1
-                                : 0;
-    st = grow(ctx, ctx->state, (words > reserve ? words : reserve) * 4 + (size_t)R);
-    if (st != AS_OK) return st;
     int32_t *w = static_cast<int32_t *>(ctx->state.ptr);
     s.sums = sums ? reinterpret_cast<float *>(w) : nullptr;
     w += sums;
@@ -571,8 +569,7 @@ static as_status decode_impl(as_ctx *ctx, const as_model *model, const int32_t *
     const size_t esz = ctx->dtype == AS_BF16 ? 2 : 4;
     const int64_t ldw = ((int64_t)ctx->V + 7) / 8 * 8;        // rows start 16-byte aligned
     DecodeState state;
-    as_status st = decode_state(ctx, model, B, N, T, ldw * (int64_t)esz, step_by_sums(ctx, 1.f),
-                                !trunc && step_by_sums(ctx, temp), state);
+    as_status st = decode_state(ctx, model, B, N, T, ldw * (int64_t)esz, false, !trunc && step_by_sums(ctx, temp), state);
     if (st != AS_OK) return st;
     float *const codes = state.codes;
     int32_t *const prev = state.prev;
@@ -716,7 +713,7 @@ as_status as_decode_fused(as_ctx *ctx, const as_model *model, const int32_t *pro
     const int32_t ngroups = (ctx->V + 31) / 32;
     const int64_t ldp = ((int64_t)ngroups + 15) / 16 * 16;
     DecodeState state;
-    as_status st = decode_state(ctx, model, B, N, T, ldp * (int64_t)sizeof(float2), false, false, state);
+    as_status st = decode_state(ctx, model, B, N, T, ldp * (int64_t)sizeof(float2), true, false, state);
     if (st != AS_OK) return st;
     float *const codes = state.codes;
     int32_t *const prev = state.prev;

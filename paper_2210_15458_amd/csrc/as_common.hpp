@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "../../include/arith_sampling.h"
+#include "as_workspace.hpp"
 
 namespace as {
 
@@ -50,9 +51,9 @@ struct as_ctx {
     // fixed workspace (allocated at creation): per-row truncation thresholds
     float *thr = nullptr;          // [max_rows]
     int32_t *rid = nullptr;        // [max_rows] the caller's row_ids brought into range
-    // decode workspace (grown on demand by as_decode)
+    // decode workspace (grown on demand)
     as::DeviceBuf logits;          // [rows, ld]
-    as::DeviceBuf state;           // codes f32[rows] | prev i32[rows] | tables of shared rows, if any | finished u8[rows]
+    as::DeviceBuf state;           // codes, prev, tables and sums of shared rows, finished flags
     as::Profile prof;
     int step_shape = 0;            // work-group shape of the sampling kernel (tuning knob, 0 = default)
     // choices of a kernel (tuning knobs, 0 = by the rules on sizes)
@@ -189,7 +190,6 @@ struct RowRange {
     const int32_t *begin = nullptr, *end = nullptr;
 };
 
-constexpr int kRowSums = 68;     // floats that row_sums_kernel leaves per row: 64 chunk sums, 4 references
 struct RowSumsArgs {
     const void *logits;          // [rows, ld]
     int64_t ld;
@@ -294,8 +294,7 @@ as_status launch_share(as_ctx *ctx, const RowShare &s, int32_t step, const int32
 as_status launch_claim(as_ctx *ctx, const RowShare &s, int32_t step, const int32_t *prev, int64_t rows);
 as_status launch_share_map(as_ctx *ctx, const RowShare &s, int32_t step, const int32_t *prev, int64_t rows,
                            int32_t *row_ids, bool sorted);
-bool keeping_pays(const as_ctx *ctx, const as_model *m, int64_t rows, int64_t prompts, int32_t T, int64_t row_bytes,
-                  bool by_sums);
+bool keeping_pays(const as_ctx *ctx, const as_model *m, int64_t rows, int32_t T, bool by_sums);
 bool step_by_sums(const as_ctx *ctx, float temp);
 as_status launch_row_select(as_ctx *ctx, const SelectArgs &a);
 // the same for the positions of an encode (prev < 0: none): rows claimed, counted and scanned, the order left to the caller

@@ -1272,15 +1272,12 @@ bool sharing_pays(const as_ctx *ctx, const as_model *m, int64_t rows, int32_t T)
 // 15.5, 2048 20.9 / 13.8.  Not by sums, V = 5001, d = 512: 2048 rows T = 16 39.0 / 42.1, T = 64 37.5 / 31.6; 8192 rows
 // T = 4 91.7 / 86.5.  Group masses, V = 32128: 16384 rows T = 16 485 / 182; V = 4096: 1024 rows
 // T = 64 23.8 / 24.2.
-// The table has at most four times the rows of one step, which a decode without it has, and those beyond within 4 GiB.
-bool keeping_pays(const as_ctx *ctx, const as_model *m, int64_t rows, int64_t prompts, int32_t T, int64_t row_bytes,
-                  bool by_sums)
+// (How large its table may be: kept_rows_most.)
+bool keeping_pays(const as_ctx *ctx, const as_model *m, int64_t rows, int32_t T, bool by_sums)
 {
     if (T < 3 || !rows_on_device(ctx, m)) return false;
     const double V = (double)m->V, R = (double)rows;
-    const double steps = T - 1, used = R * steps + (double)prompts;
-    const double most = used < V ? used : V;
-    if (most > 4.0 * R || (most > R && most * (double)row_bytes > 4.0 * 1024.0 * 1024.0 * 1024.0)) return false;
+    const double steps = T - 1;
     const double computed = V * (1.0 - exp(-R * steps / V)) / steps;           // logits rows a step
     const double without = sharing_pays(ctx, m, rows, T) ? V * (1.0 - exp(-R / V)) : R;
     double spared = (without - computed) * V * (double)m->d * 2.0 / 1e15;

@@ -131,6 +131,7 @@ __global__ __launch_bounds__(256) void row_select_kernel(SelectArgs q)
 }  // namespace
 
 static_assert(kRowSums == kTileWaves * kTileIters + kTileWaves, "the chunk sums and the waves' references");
+static_assert(kTileVecs == kTileWaves * kTileIters * 64, "the vectors of a tile");
 
 as_status launch_row_sums(as_ctx *ctx, int kid, const RowSumsArgs &a, int64_t rows)
 {
@@ -155,8 +156,7 @@ as_status launch_row_sums(as_ctx *ctx, int kid, const RowSumsArgs &a, int64_t ro
 // rows that step_tile_kernel would take
 bool step_by_sums(const as_ctx *ctx, float temp)
 {
-    const int epv = ctx->dtype == AS_BF16 ? 8 : 4;
-    return ctx->V % epv == 0 && ctx->V / epv <= kTileWaves * kTileIters * 64 && ctx->step_shape == 0 &&
+    return one_tile_row(ctx->V, ctx->dtype == AS_BF16 ? 2 : 4) && ctx->step_shape == 0 &&
            1.44269504088896340736f / temp <= kTileMaxScale;
 }
 

@@ -82,3 +82,39 @@ def test_a_kept_table_that_is_refused_is_not_asked_for_again():
     other.close()
     small.close()
     job.close()
+
+
+def _free():
+    torch.cuda.synchronize()
+    return torch.cuda.mem_get_info()[0]
+
+
+# steps, temperature, top-k and rows of calls no larger than a decode of 20000 codes x 8 steps that keeps 8000 rows
+OTHERS = [(2, TEMP, 0, 20000), (8, TEMP, 40, 20000), (8, 0.2, 0, 20000), (8, TEMP, 0, 7000), (1, TEMP, 0, 1), (4, TEMP, 3, 2001)]
+
+
+def test_decodes_no_larger_than_an_earlier_one_leave_its_workspace_alone():
+    V, d, N, T = 8000, 512, 20000, 8                      # a row per code: 320 MB
+    job = Job(V, d, N)
+    own = job.context()                                   # for what the other calls give on a workspace of their own
+    want = job.decode(N, T)
+    out = torch.empty_like(want)
+    others = [(o, job.decode(o[3], o[0], o[1], o[2], ctx=own)) for o in OTHERS]
+    outs = [torch.empty_like(w) for _, w in others]
+    graph = job.captured(lambda o: job.decode(N, T, out=o), out)
+    before = _free()
+    for (o, w), buf in zip(others, outs):
+        assert torch.equal(job.decode(o[3], o[0], o[1], o[2], out=buf), w), o
+        assert abs(_free() - before) < 32 << 20, o        # (the runtime's own, not the workspace)
+    assert torch.equal(job.replay(graph, out), want)
+    # and each of them can be captured on a context that has seen the largest alone
+    own.close()
+    own = job.context()
+    assert torch.equal(job.decode(N, T, ctx=own, out=out), want)
+    for (o, w), buf in zip(others, outs):
+        g = job.captured(lambda b, o=o: job.decode(o[3], o[0], o[1], o[2], ctx=own, out=b), buf)
+        for _ in range(3):
+            assert torch.equal(job.replay(g, buf), w), o
+            assert torch.equal(job.decode(N, T, ctx=own, out=out), want)
+    own.close()
+    job.close()

@@ -1,0 +1,97 @@
+"""The arithmetic by which calls reserve workspace (csrc/as_workspace.hpp, compiled here for the host): never less for more
+rows or steps, and enough for every form that a call can take."""
+import ctypes
+import os
+import random
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+SHIM = r"""
+#include "as_workspace.hpp"
+using namespace as;
+extern "C" {
+void sizes(int64_t V, int64_t esz, int64_t rows, int64_t T, int masses, int64_t *out)
+{
+    const DecodeSizes z = decode_sizes(V, esz, rows, T, masses != 0);
+    out[0] = (int64_t)z.needed; out[1] = (int64_t)z.preferred; out[2] = (int64_t)z.state;
+}
+int64_t kept(int64_t V, int64_t rows, int64_t T, int64_t row_bytes) { return kept_rows_most(V, rows, T, row_bytes); }
+int64_t row_bytes(int64_t V, int64_t esz, int masses) { return masses ? mass_row_bytes(V) : logits_row_bytes(V, esz); }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    d = tmp_path_factory.mktemp("sizes")
+    (d / "shim.cpp").write_text(SHIM)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror", "-fPIC", "-shared", "-I",
+                    os.path.join(ROOT, "paper_2210_15458_amd", "csrc"), str(d / "shim.cpp"), "-o", str(d / "shim.so")], check=True)
+    L = ctypes.CDLL(str(d / "shim.so"))
+    i64 = ctypes.c_int64
+    L.sizes.argtypes = [i64, i64, i64, i64, ctypes.c_int, ctypes.POINTER(i64)]
+    L.kept.argtypes, L.kept.restype = [i64] * 4, i64
+    L.row_bytes.argtypes, L.row_bytes.restype = [i64, i64, ctypes.c_int], i64
+    return L
+
+
+def _sizes(lib, V, esz, rows, T, masses=False):
+    out = (ctypes.c_int64 * 3)()
+    lib.sizes(V, esz, rows, T, int(masses), out)
+    return dict(zip(("needed", "preferred", "state"), out))
+
+
+def _log(rng, lo, hi):
+    return int(round(lo * (hi / lo) ** rng.random()))
+
+
+def _pairs(n=20000):
+    """A size, and one of no more rows and no more steps (often of the same), over all vocabularies."""
+    rng = random.Random(5)
+    for _ in range(n):
+        V, esz = _log(rng, 1, 1 << 21), rng.choice([2, 4])
+        rows, T = _log(rng, 1, rng.choice([64, 4096, 1 << 20])), rng.choice([0, 1, 2, 3, 4, 5, 6, 16, 64, 1000])
+        if rng.random() < 0.5:                               # near the lines that the vocabulary draws
+            rows = max(1, round(V * rng.choice([0.125, 0.25, 0.3, 0.5, 1.0, 2.0])) + rng.randint(-3, 3))
+        yield (V, esz, rows, T), (V, esz, rows if rng.random() < 0.4 else rng.randint(1, rows),
+                                  T if rng.random() < 0.3 else rng.randint(0, T))
+
+
+def test_a_smaller_decode_finds_the_workspace_of_a_larger_one(lib):
+    for large, small in _pairs():
+        a, b = _sizes(lib, *large), _sizes(lib, *small)
+        assert all(b[k] <= a[k] for k in a), (large, small)
+        # group masses after logits of the same size
+        c = _sizes(lib, *small, masses=True)
+        assert all(c[k] <= a[k] for k in a), (large, small)
+
+
+def test_what_a_decode_reserves_holds_every_form_of_it(lib):
+    rng = random.Random(6)
+    kept_at_all = 0
+    for (V, esz, R, T), _ in _pairs():
+        N = rng.choice([1, 2, 3, R])
+        B = max(1, R // N)
+        R = B * N
+        for masses in (False, True):
+            z, rb = _sizes(lib, V, esz, R, T, masses), lib.row_bytes(V, esz, int(masses))
+            assert z["needed"] >= R * rb and z["preferred"] >= z["needed"]
+            forms = [2 * R, 2 * R + R + R + 2 * V + V + T + 1]                # own rows; rows shared in a step
+            if lib.kept(V, R, T, rb):
+                K = min(V, R * (T - 1) + B)
+                kept_at_all += 1
+                assert K <= lib.kept(V, R, T, rb) and z["preferred"] >= K * rb and (K <= R or K * rb <= 4 << 30) and K <= 4 * R
+                by_sums = 68 * K if not masses and V * esz % 16 == 0 and V * esz <= 65536 else 0
+                forms += [2 * R + R + K + 2 * V + K + T + 1 + by_sums]
+            assert z["state"] >= max(forms) * 4 + R, (V, esz, R, T, masses)
+    assert kept_at_all > 1000
+
+
+def test_sizes_that_a_shorter_decode_once_took_more_for(lib):
+    # 65536 codes of 32128 keep 32128 rows over 16 steps and have a row each over 2; 8000 codes
+    for V, esz, rows, long, short in ((32128, 2, 65536, 16, 2), (32128, 2, 8000, 16, 4), (2000, 2, 8192, 8, 8)):
+        assert _sizes(lib, V, esz, rows, short)["preferred"] <= _sizes(lib, V, esz, rows, long)["preferred"]
+    assert _sizes(lib, 32128, 2, 65536, 16)["needed"] == 65536 * 64256
+    assert _sizes(lib, 32128, 2, 8000, 4)["preferred"] == 8000 * 64256       # (V > 4 x 8000: no table)

@@ -26,9 +26,9 @@
  *     lies in [0,V) and the new code in [0, 1 - 2^-24].
  *   - A logit of -inf is legal and means probability zero.
  *   - as_step / as_step_ex allocate nothing and touch only the context's
- *     fixed workspace.  as_decode, as_decode_ancestral, as_decode_fused and
- *     as_encode keep their logits and per-row state in a decode workspace that
- *     the context (re)allocates when a call needs more than any earlier call
+ *     fixed workspace.  as_decode, as_decode_ancestral and as_decode_fused
+ *     keep their logits and per-row state in a decode workspace (as_encode in
+ *     one of its own, by the same rules) that the context (re)allocates when a call needs more than any earlier call
  *     did: the first call at a size synchronises the stream, frees and
  *     allocates, and must not be made under stream capture; later calls of the
  *     same or a smaller size (no more rows, no more steps; any temperature,
@@ -390,9 +390,11 @@ as_status as_interval_step(as_ctx *ctx, const void *logits, int64_t rows, int64_
  *   prompts     DEVICE int32[B]
  *   tokens      DEVICE int32[B, N, T], as written by as_decode
  *   lo_out, width_out   DEVICE double[B*N]
- * Uses (and may grow) the context's decode workspace: logits of 256 to 8192 rows (fewer if
- * there are fewer positions; up to 256 MB, or 1024 rows of up to 1 MB, or 256 rows) and at
- * most 28 bytes a position of 2^19 (or of one column) and 12 a token of the vocabulary.
+ * Takes a workspace of its own (grown by the rule for the decode workspace, by rows and
+ * columns): the logits of as many rows as there are positions, at most 8192 or 4096 of up to
+ * 256 MiB together, 2048 of up to 768 MiB, 1024 of up to 1 GiB, otherwise 256; and tables of
+ * 37 bytes a position (of at most 2^19, or one column), 276 a row of those logits, 8 a token
+ * of the vocabulary, 1 a sequence.
  */
 as_status as_encode(as_ctx *ctx, const as_model *model, const int32_t *prompts,
                     int32_t B, int32_t N, int32_t T, const int32_t *tokens, float temp,

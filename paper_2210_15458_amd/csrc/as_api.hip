@@ -73,7 +73,7 @@ static as_status grow(as_ctx *ctx, DeviceBuf &b, size_t bytes)
         b.ptr = nullptr;
         b.bytes = 0;
     }
-    if (!device_alloc(ctx, &b.ptr, bytes)) return fail(ctx, AS_ERR_ALLOC, "device allocation of the decode workspace failed");
+    if (!device_alloc(ctx, &b.ptr, bytes)) return fail(ctx, AS_ERR_ALLOC, "device allocation of the workspace failed");
     b.bytes = bytes;
     return AS_OK;
 }
@@ -227,6 +227,8 @@ as_status as_ctx_destroy(as_ctx *ctx)
     if (ctx->rid) (void)hipFree(ctx->rid);
     if (ctx->logits.ptr) (void)hipFree(ctx->logits.ptr);
     if (ctx->state.ptr) (void)hipFree(ctx->state.ptr);
+    if (ctx->encode_logits.ptr) (void)hipFree(ctx->encode_logits.ptr);
+    if (ctx->encode_state.ptr) (void)hipFree(ctx->encode_state.ptr);
     for (auto &v : ctx->prof.slots)
         for (auto &s : v) {
             (void)hipEventDestroy(s.start);
@@ -789,22 +791,6 @@ as_status as_interval_step(as_ctx *ctx, const void *logits, int64_t rows, int64_
     return launch_interval(ctx, a);
 }
 
-// Rows of an encode's logits computed at a time.  The product wants many (us an encode by rows a chunk 256 / 512 / 1024 /
-// 2048 / 3072 / 4096 / 8192: 65536 positions of 32128 bf16, d = 512 3013 / 1942 / 1564 / 1344 / 1366 / 1268 / 1228; 38985
-// of 153375, d = 896 17213 / 12969 / 12043 / 11419 / 12370 / 11364 / 11350; 15457 of 4597, d = 960 701 / 407 / 258 / 199 /
-// 208 / 182 / 177), in whole sets of 8 row tiles (3072 is not); whether they stay in the caches hardly matters, so
-// memory draws the line.
-static int64_t encode_chunk(int64_t row_bytes)
-{
-    if (8192 * row_bytes <= 256LL << 20) return 8192;
-    if (4096 * row_bytes <= 256LL << 20) return 4096;
-    if (2048 * row_bytes <= 768LL << 20) return 2048;
-    return 1024 * row_bytes <= 1024LL << 20 ? 1024 : 256;
-}
-
-// Its positions are taken a window of columns at a time, which bounds the tables (28 bytes a position).
-constexpr int64_t kEncodePositions = 1LL << 19;
-
 // Whether an encode of n positions gives every token in use one logits row (otherwise every position has its own, the
 // first column's one per prompt).  With tokens spread evenly n - V(1 - exp(-n/V)) rows of product and of sums are spared;
 // the tables take five launches, 20 us.
@@ -822,42 +808,32 @@ static as_status encode_windows(as_ctx *ctx, const as_model *model, const int32_
 {
     const size_t esz = ctx->dtype == AS_BF16 ? 2 : 4;
     const int64_t ldw = ((int64_t)ctx->V + 7) / 8 * 8;        // rows start 16-byte aligned
-    const int32_t window = (int32_t)(kEncodePositions / R < 1 ? 1 : (kEncodePositions / R < T ? kEncodePositions / R : T));
+    const EncodeSizes sizes = encode_sizes(ctx->V, esz, R, T);
+    as_status st = grow(ctx, ctx->encode_logits, sizes.logits);
+    if (st == AS_OK) st = grow(ctx, ctx->encode_state, sizes.state);
+    if (st != AS_OK) return st;
+    void *const logits = ctx->encode_logits.ptr;
+    unsigned char *const base = static_cast<unsigned char *>(ctx->encode_state.ptr);
+
+    const int32_t window = (int32_t)encode_window(R, T);
     const int64_t most = R * window;                          // positions of a window
     const bool claimed = claiming_pays(ctx, model, most);
-    const int64_t max_rows = claimed && ctx->V < most ? ctx->V : most;
-    int64_t chunk = encode_chunk(ldw * (int64_t)esz);
-    chunk = chunk < max_rows ? chunk : max_rows;
+    const int64_t max_rows = claimed ? smaller(ctx->V, most) : most;
+    const int64_t chunk = smaller(encode_chunk(ldw * (int64_t)esz), max_rows);
     const bool trunc = truncation_on(ctx->V, top_k, top_p), by_sums = step_by_sums(ctx, temp);
 
-    as_status st = AS_OK;
     Positions w{};
     w.tokens = tokens; w.prompts = prompts; w.R = R; w.N = N; w.T = T; w.V = ctx->V; w.eos_id = eos_id;
-    w.dtype = ctx->dtype; w.chunk = chunk > 0 ? chunk : 1;
-    if (T > 0) {
-        st = grow(ctx, ctx->logits, (size_t)chunk * ldw * esz);
-        if (st != AS_OK) return st;
-    }
-    const int64_t chunks = (max_rows + w.chunk - 1) / w.chunk;
-    // the tables, 16-byte parts first
-    size_t bytes = 0;
-    auto part = [&](size_t n) { const size_t at = bytes; bytes += (n + 15) / 16 * 16; return at; };
-    const size_t at_f = part(most * 8), at_p = part(most * 8), at_sums = part(by_sums ? chunk * kRowSums * 4 : 0),
-                 at_thr = part(trunc ? chunk * 4 : 0), at_slot = part(most * 4), at_order = part(most * 4),
-                 at_token = part(max_rows * 4), at_ends = part(max_rows * 4), at_idle = part(max_rows), at_ended = part(R),
-                 at_cond = part(claimed ? most * 4 : 0), at_mark = part(claimed ? ctx->V * 4 : 0),
-                 at_claim = part(claimed ? ctx->V * 4 : 0), at_count = part(4), at_chunks = part(chunks * 4);
-    st = grow(ctx, ctx->state, bytes);
-    if (st != AS_OK) return st;
-    unsigned char *const base = static_cast<unsigned char *>(ctx->state.ptr);
-    auto words = [&](size_t at) { return reinterpret_cast<int32_t *>(base + at); };
-    w.f_lo = reinterpret_cast<double *>(base + at_f); w.p = reinterpret_cast<double *>(base + at_p);
-    w.slot = words(at_slot); w.order = words(at_order); w.token = words(at_token); w.ends = words(at_ends);
-    w.idle = base + at_idle; w.ended = base + at_ended; w.cond = words(at_cond); w.count = words(at_count);
-    w.chunk_rows = claimed ? words(at_chunks) : nullptr;
-    float *const sums = reinterpret_cast<float *>(base + at_sums), *const thr = reinterpret_cast<float *>(base + at_thr);
+    w.dtype = ctx->dtype; w.chunk = chunk;
+    const EncodeTables at = encode_tables(ctx->V, esz, R, most, max_rows, chunk, claimed);
+    auto words = [&](size_t o) { return reinterpret_cast<int32_t *>(base + o); };
+    w.f_lo = reinterpret_cast<double *>(base + at.f_lo); w.p = reinterpret_cast<double *>(base + at.p);
+    w.slot = words(at.slot); w.order = words(at.order); w.token = words(at.token); w.ends = words(at.ends);
+    w.idle = base + at.idle; w.ended = base + at.ended; w.cond = words(at.cond); w.count = words(at.count);
+    w.chunk_rows = claimed ? words(at.chunks) : nullptr;
+    float *const sums = reinterpret_cast<float *>(base + at.sums), *const thr = reinterpret_cast<float *>(base + at.thr);
     RowShare tables{};
-    tables.mark = words(at_mark); tables.slot = words(at_claim); tables.token = w.token; tables.count = w.count;
+    tables.mark = words(at.mark); tables.slot = words(at.claim); tables.token = w.token; tables.count = w.count;
     tables.fill = w.ends;
 
     for (int32_t t0 = 0; t0 < T; t0 += window) {
@@ -873,12 +849,12 @@ static as_status encode_windows(as_ctx *ctx, const as_model *model, const int32_
         for (int64_t s0 = 0, c = 0; s0 < rows; s0 += chunk, ++c) {
             const int64_t here = rows - s0 < chunk ? rows - s0 : chunk;
             const RowRange range{nullptr, claimed ? w.chunk_rows + c : nullptr};
-            st = launch_bigram_logits(ctx, model, w.token + s0, here, ctx->logits.ptr, ldw, range);
+            st = launch_bigram_logits(ctx, model, w.token + s0, here, logits, ldw, range);
             if (st == AS_OK && trunc)
-                st = launch_threshold(ctx, ctx->logits.ptr, here, ldw, w.idle + s0, nullptr, temp, top_k, top_p, thr);
+                st = launch_threshold(ctx, logits, here, ldw, w.idle + s0, nullptr, temp, top_k, top_p, thr);
             if (st != AS_OK) return st;
             ChunkArgs a{};
-            a.w = w; a.logits = ctx->logits.ptr; a.s0 = s0; a.rows = here; a.ld = ldw; a.V = ctx->V;
+            a.w = w; a.logits = logits; a.s0 = s0; a.rows = here; a.ld = ldw; a.V = ctx->V;
             a.k = 1.44269504088896340736f / temp; a.thr = trunc ? thr : nullptr; a.sums = sums;
             if (by_sums) {
                 RowSumsArgs q{};

@@ -54,6 +54,9 @@ struct as_ctx {
     // decode workspace (grown on demand)
     as::DeviceBuf logits;          // [rows, ld]
     as::DeviceBuf state;           // codes, prev, tables and sums of shared rows, finished flags
+    // encode workspace: the logits of a chunk of rows, the tables of a window of positions.  Its own, since encodes want
+    // many rows where decodes of their size have few, and neither is to move the other's
+    as::DeviceBuf encode_logits, encode_state;
     as::Profile prof;
     int step_shape = 0;            // work-group shape of the sampling kernel (tuning knob, 0 = default)
     // choices of a kernel (tuning knobs, 0 = by the rules on sizes)
@@ -155,7 +158,7 @@ struct IntervalArgs {
 };
 
 // The positions of one window of an encode: columns t0 .. t0+Tw of R sequences; position p is column t0 + p % Tw of
-// sequence p / Tw.  The tables are the context's decode state.
+// sequence p / Tw.
 struct Positions {
     const int32_t *tokens;       // [R, T]
     const int32_t *prompts;      // [R / N]

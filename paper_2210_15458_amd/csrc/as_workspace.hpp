@@ -56,5 +56,60 @@ inline DecodeSizes decode_sizes(int64_t V, int64_t esz, int64_t rows, int64_t T,
     return z;
 }
 
+// Rows of an encode's logits computed at a time.  The product wants many (us an encode by rows a chunk 256 / 512 / 1024 /
+// 2048 / 3072 / 4096 / 8192: 65536 positions of 32128 bf16, d = 512 3013 / 1942 / 1564 / 1344 / 1366 / 1268 / 1228; 38985
+// of 153375, d = 896 17213 / 12969 / 12043 / 11419 / 12370 / 11364 / 11350; 15457 of 4597, d = 960 701 / 407 / 258 / 199 /
+// 208 / 182 / 177), in whole sets of 8 row tiles (3072 is not); whether they stay in the caches hardly matters, so
+// memory draws the line.
+inline int64_t encode_chunk(int64_t row_bytes)
+{
+    if (8192 * row_bytes <= 256LL << 20) return 8192;
+    if (4096 * row_bytes <= 256LL << 20) return 4096;
+    if (2048 * row_bytes <= 768LL << 20) return 2048;
+    return 1024 * row_bytes <= 1024LL << 20 ? 1024 : 256;
+}
+
+// Its positions are taken a window of columns at a time, which bounds the tables: at most so many, or one column.
+constexpr int64_t kEncodePositions = 1LL << 19;
+inline int64_t encode_window(int64_t rows, int64_t T) { return larger(1, smaller(T, kEncodePositions / rows)); }
+inline int64_t encode_positions_most(int64_t rows, int64_t T)
+{
+    return smaller(rows * larger(T, 1), larger(rows, kEncodePositions));
+}
+
+// The tables of a window: offsets in bytes, and what they take.  `positions` in it, `most_rows` logits rows for them,
+// `chunk` of these at a time; cond, mark and claim only where tokens share logits rows (`claimed`), sums only for rows that
+// have them.
+struct EncodeTables {
+    size_t f_lo, p, sums, thr, slot, order, token, ends, idle, ended, cond, mark, claim, count, chunks, bytes;
+};
+inline EncodeTables encode_tables(int64_t V, int64_t esz, int64_t rows, int64_t positions, int64_t most_rows, int64_t chunk,
+                                  bool claimed)
+{
+    EncodeTables t;
+    size_t end = 0;
+    auto part = [&](int64_t n) { const size_t at = end; end += (size_t)((n + 15) / 16 * 16); return at; };
+    t.f_lo = part(positions * 8); t.p = part(positions * 8);
+    t.sums = part(one_tile_row(V, esz) ? chunk * kRowSums * 4 : 0); t.thr = part(chunk * 4);
+    t.slot = part(positions * 4); t.order = part(positions * 4);
+    t.token = part(most_rows * 4); t.ends = part(most_rows * 4); t.idle = part(most_rows); t.ended = part(rows);
+    t.cond = part(claimed ? positions * 4 : 0); t.mark = part(claimed ? V * 4 : 0); t.claim = part(claimed ? V * 4 : 0);
+    t.count = part(4); t.chunks = part((most_rows + chunk - 1) / chunk * 4);
+    t.bytes = end;
+    return t;
+}
+
+// What an encode reserves, in a workspace of its own: the logits of a chunk, and the tables of a window in any form (37
+// bytes a position, 276 a logits row of the chunk, 8 a token of the vocabulary, 1 a sequence).
+struct EncodeSizes {
+    size_t logits, state;                    // bytes
+};
+inline EncodeSizes encode_sizes(int64_t V, int64_t esz, int64_t rows, int64_t T)
+{
+    const int64_t most = encode_positions_most(rows, T), chunk = smaller(encode_chunk(logits_row_bytes(V, esz)), most);
+    return EncodeSizes{(size_t)(T > 0 ? chunk * logits_row_bytes(V, esz) : 0),
+                       encode_tables(V, esz, rows, most, most, chunk, true).bytes};
+}
+
 }  // namespace as
 #endif

@@ -23,6 +23,8 @@ class Job:
         self.u = torch.rand(1, device="cuda", generator=g)
         self.stream = torch.cuda.Stream()
         torch.cuda.synchronize()
+        self.tokens = torch.randint(0, V, (min(rows, 256), 300), device="cuda", generator=g, dtype=torch.int32)
+        self.columns = {}
         self.rows, self.ldt = rows, ldt
         self.ctx = self.context()
 
@@ -34,6 +36,16 @@ class Job:
         with torch.cuda.stream(self.stream):
             out = torch.empty((1, N, T), dtype=torch.int32, device="cuda") if out is None else out
             B.as_decode(ctx or self.ctx, self.model, self.prompts, N, T, self.u, temp, top_k, 1.0, EOS, out)
+        return self.done(out)
+
+    def encode(self, N, T, temp=TEMP, top_k=0, ctx=None, out=None):
+        """Of tokens that are the same for every call: the first columns of the first sequences."""
+        if T not in self.columns:
+            self.columns[T] = self.tokens[:, :T].contiguous()
+            torch.cuda.synchronize()
+        with torch.cuda.stream(self.stream):
+            out = tuple(torch.empty(N, dtype=torch.float64, device="cuda") for _ in range(2)) if out is None else out
+            B.as_encode(ctx or self.ctx, self.model, self.prompts, N, T, self.columns[T][:N], temp, top_k, 1.0, -1, *out)
         return self.done(out)
 
     def done(self, out):
@@ -84,6 +96,10 @@ def test_a_kept_table_that_is_refused_is_not_asked_for_again():
     job.close()
 
 
+def _same(a, b):
+    return all(torch.equal(x, y) for x, y in zip(a, b))
+
+
 def _free():
     torch.cuda.synchronize()
     return torch.cuda.mem_get_info()[0]
@@ -117,4 +133,47 @@ def test_decodes_no_larger_than_an_earlier_one_leave_its_workspace_alone():
             assert torch.equal(job.replay(g, buf), w), o
             assert torch.equal(job.decode(N, T, ctx=own, out=out), want)
     own.close()
+    job.close()
+
+
+# columns, temperature, top-k and sequences of calls no larger than an encode of 100 x 300: without shared rows, sums or
+# truncation, or with them
+ENCODES = [(100, TEMP, 0, 100), (300, 0.2, 0, 100), (300, TEMP, 30, 100), (300, TEMP, 0, 60), (20, TEMP, 5, 37), (1, TEMP, 0, 1)]
+
+
+def test_encodes_no_larger_than_an_earlier_one_leave_its_workspace_alone():
+    V, d, N, T = 2000, 128, 100, 300                      # a row per token: 16 MB; a row per position of 100 columns: 64
+    job = Job(V, d, N, ldt=torch.float32)
+    own = job.context()
+    want = job.encode(N, T)
+    out = tuple(torch.empty_like(w) for w in want)
+    others = [(o, job.encode(o[3], o[0], o[1], o[2], ctx=own)) for o in ENCODES]
+    outs = [tuple(torch.empty_like(x) for x in w) for _, w in others]
+    graph = job.captured(lambda o: job.encode(N, T, out=o), out)
+    before = _free()
+    for (o, w), buf in zip(others, outs):
+        assert _same(job.encode(o[3], o[0], o[1], o[2], out=buf), w), o
+        assert abs(_free() - before) < 16 << 20, o
+    assert _same(job.replay(graph, out), want)
+    own.close()
+    own = job.context()
+    assert _same(job.encode(N, T, ctx=own, out=out), want)
+    for (o, w), buf in zip(others, outs):
+        g = job.captured(lambda b, o=o: job.encode(o[3], o[0], o[1], o[2], ctx=own, out=b), buf)
+        for _ in range(3):
+            assert _same(job.replay(g, buf), w), o
+            assert _same(job.encode(N, T, ctx=own, out=out), want)
+    own.close()
+    job.close()
+
+
+def test_an_encode_leaves_a_captured_decode_alone():
+    V, d, N = 8000, 128, 40
+    job = Job(V, d, N)
+    want = job.decode(N, 64)
+    out = torch.empty_like(want)
+    graph = job.captured(lambda o: job.decode(N, 64, out=o), out)
+    for T in (64, 200, 300):                              # (wants more rows of logits than the decode has)
+        job.encode(N, T)
+        assert torch.equal(job.replay(graph, out), want)
     job.close()

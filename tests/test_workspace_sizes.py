@@ -17,6 +17,17 @@ void sizes(int64_t V, int64_t esz, int64_t rows, int64_t T, int masses, int64_t 
     const DecodeSizes z = decode_sizes(V, esz, rows, T, masses != 0);
     out[0] = (int64_t)z.needed; out[1] = (int64_t)z.preferred; out[2] = (int64_t)z.state;
 }
+void encode(int64_t V, int64_t esz, int64_t rows, int64_t T, int64_t *out)
+{
+    const EncodeSizes z = encode_sizes(V, esz, rows, T);
+    out[0] = (int64_t)z.logits; out[1] = (int64_t)z.state;
+}
+int64_t tables(int64_t V, int64_t esz, int64_t rows, int64_t positions, int64_t most_rows, int64_t chunk, int claimed)
+{
+    return (int64_t)encode_tables(V, esz, rows, positions, most_rows, chunk, claimed != 0).bytes;
+}
+int64_t chunk(int64_t rb) { return encode_chunk(rb); }
+int64_t window(int64_t rows, int64_t T) { return encode_window(rows, T); }
 int64_t kept(int64_t V, int64_t rows, int64_t T, int64_t row_bytes) { return kept_rows_most(V, rows, T, row_bytes); }
 int64_t row_bytes(int64_t V, int64_t esz, int masses) { return masses ? mass_row_bytes(V) : logits_row_bytes(V, esz); }
 }
@@ -32,6 +43,10 @@ def lib(tmp_path_factory):
     L = ctypes.CDLL(str(d / "shim.so"))
     i64 = ctypes.c_int64
     L.sizes.argtypes = [i64, i64, i64, i64, ctypes.c_int, ctypes.POINTER(i64)]
+    L.encode.argtypes = [i64, i64, i64, i64, ctypes.POINTER(i64)]
+    L.tables.argtypes, L.tables.restype = [i64] * 6 + [ctypes.c_int], i64
+    L.chunk.argtypes, L.chunk.restype = [i64], i64
+    L.window.argtypes, L.window.restype = [i64] * 2, i64
     L.kept.argtypes, L.kept.restype = [i64] * 4, i64
     L.row_bytes.argtypes, L.row_bytes.restype = [i64, i64, ctypes.c_int], i64
     return L
@@ -95,3 +110,37 @@ def test_sizes_that_a_shorter_decode_once_took_more_for(lib):
         assert _sizes(lib, V, esz, rows, short)["preferred"] <= _sizes(lib, V, esz, rows, long)["preferred"]
     assert _sizes(lib, 32128, 2, 65536, 16)["needed"] == 65536 * 64256
     assert _sizes(lib, 32128, 2, 8000, 4)["preferred"] == 8000 * 64256       # (V > 4 x 8000: no table)
+
+
+def _encode(lib, V, esz, rows, T):
+    out = (ctypes.c_int64 * 2)()
+    lib.encode(V, esz, rows, T, out)
+    return dict(zip(("logits", "state"), out))
+
+
+def test_a_smaller_encode_finds_the_workspace_of_a_larger_one(lib):
+    for large, small in _pairs():
+        a, b = _encode(lib, *large), _encode(lib, *small)
+        assert all(b[k] <= a[k] for k in a), (large, small)
+    # 100 sequences of 2000 tokens: fewer columns take a row per position instead of one per token; a window of two columns
+    for V, long, short in ((2000, (100, 300), (100, 200)), (1000, (300000, 8), (200000, 8))):
+        a, b = _encode(lib, V, 2, *long), _encode(lib, V, 2, *short)
+        assert all(b[k] <= a[k] for k in a)
+
+
+def test_what_an_encode_reserves_holds_every_form_of_it(lib):
+    for (V, esz, rows, T), _ in _pairs(4000):
+        if T == 0:
+            continue
+        z, rb = _encode(lib, V, esz, rows, T), lib.row_bytes(V, esz, 0)
+        window = lib.window(rows, T)
+        assert 1 <= window <= T
+        positions = rows * window
+        for claimed, most in ((0, positions), (1, min(V, positions))):
+            chunk = min(lib.chunk(rb), most)
+            assert z["logits"] >= chunk * rb
+            assert z["state"] >= lib.tables(V, esz, rows, positions, most, chunk, claimed)
+        # what the header says
+        chunk = min(lib.chunk(rb), positions)
+        assert z["state"] <= 37 * rows * T + 276 * chunk + 8 * V + rows + 4 * (rows * T // chunk + 1) + 15 * 16
+        assert rows > 1 << 19 or z["state"] <= (37 << 19) + 276 * 8192 + 8 * V + rows + (4 << 19) // chunk + 4 + 15 * 16

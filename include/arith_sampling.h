@@ -37,7 +37,8 @@
  *     vocabulary where those are more: from a vocabulary of up to four times
  *     the codes, three steps on, and then at most 4 GiB; without that room it
  *     does with a row per code.  Its state is 17 bytes a code and 16 a token
- *     of the vocabulary, and 272 a row of the table that it may keep.
+ *     of the vocabulary, and 272 a row of the table that it may keep, or if
+ *     more 34 bytes a code and 276 for each of up to 1024 codes.
  *   - One context must not be used from two host threads at once.
  */
 #ifndef ARITH_SAMPLING_H
@@ -394,7 +395,8 @@ as_status as_interval_step(as_ctx *ctx, const void *logits, int64_t rows, int64_
  * columns): the logits of as many rows as there are positions, at most 8192 or 4096 of up to
  * 256 MiB together, 2048 of up to 768 MiB, 1024 of up to 1 GiB, otherwise 256; and tables of
  * 37 bytes a position (of at most 2^19, or one column), 276 a row of those logits, 8 a token
- * of the vocabulary, 1 a sequence.
+ * of the vocabulary, 1 a sequence.  Where that cannot be had (or the call is captured before
+ * one of its size was made) the decode workspace of a decode of its size will do, slower.
  */
 as_status as_encode(as_ctx *ctx, const as_model *model, const int32_t *prompts,
                     int32_t B, int32_t N, int32_t T, const int32_t *tokens, float temp,

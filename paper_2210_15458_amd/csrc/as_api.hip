@@ -808,18 +808,21 @@ static as_status encode_windows(as_ctx *ctx, const as_model *model, const int32_
 {
     const size_t esz = ctx->dtype == AS_BF16 ? 2 : 4;
     const int64_t ldw = ((int64_t)ctx->V + 7) / 8 * 8;        // rows start 16-byte aligned
+    // its own workspace, or where that cannot be had (memory, a first call under a capture) that of a decode of its size,
+    // a column at a time
     const EncodeSizes sizes = encode_sizes(ctx->V, esz, R, T);
-    as_status st = grow(ctx, ctx->encode_logits, sizes.logits);
-    if (st == AS_OK) st = grow(ctx, ctx->encode_state, sizes.state);
+    const bool own = grow_if_possible(ctx, ctx->encode_logits, sizes.logits) &&
+                     grow_if_possible(ctx, ctx->encode_state, sizes.state);
+    as_status st = own ? AS_OK : reserve_decode(ctx, R, T, false);
     if (st != AS_OK) return st;
-    void *const logits = ctx->encode_logits.ptr;
-    unsigned char *const base = static_cast<unsigned char *>(ctx->encode_state.ptr);
+    void *const logits = own ? ctx->encode_logits.ptr : ctx->logits.ptr;
+    unsigned char *const base = static_cast<unsigned char *>(own ? ctx->encode_state.ptr : ctx->state.ptr);
 
-    const int32_t window = (int32_t)encode_window(R, T);
+    const int32_t window = own ? (int32_t)encode_window(R, T) : 1;
     const int64_t most = R * window;                          // positions of a window
-    const bool claimed = claiming_pays(ctx, model, most);
+    const bool claimed = own && claiming_pays(ctx, model, most);
     const int64_t max_rows = claimed ? smaller(ctx->V, most) : most;
-    const int64_t chunk = smaller(encode_chunk(ldw * (int64_t)esz), max_rows);
+    const int64_t chunk = smaller(own ? encode_chunk(ldw * (int64_t)esz) : kPlainChunk, max_rows);
     const bool trunc = truncation_on(ctx->V, top_k, top_p), by_sums = step_by_sums(ctx, temp);
 
     Positions w{};

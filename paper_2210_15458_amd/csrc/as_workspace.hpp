@@ -37,25 +37,6 @@ inline int64_t kept_rows_most(int64_t V, int64_t rows, int64_t T, int64_t row_by
     return smaller(V, rows * T);
 }
 
-// What a decode reserves: logits (or group masses), a row of them per row, which every form can do with, or a table
-// that is preferred where it can be had; and the state: codes, tokens, flags, the tables of shared rows in any form, and
-// the sums of kept rows.  A decode of logits leaves room for one of group masses of its size.
-struct DecodeSizes {
-    size_t needed, preferred, state;         // bytes
-};
-inline DecodeSizes decode_sizes(int64_t V, int64_t esz, int64_t rows, int64_t T, bool masses)
-{
-    const int64_t lb = logits_row_bytes(V, esz), mb = mass_row_bytes(V);
-    const int64_t kept = masses ? 0 : kept_rows_most(V, rows, T, lb), kept_masses = kept_rows_most(V, rows, T, mb);
-    DecodeSizes z;
-    z.needed = (size_t)(rows * larger(masses ? 0 : lb, mb));
-    z.preferred = (size_t)larger((int64_t)z.needed, larger(kept * lb, kept_masses * mb));
-    const int64_t sums = one_tile_row(V, esz) ? kept * kRowSums : 0;
-    // (codes, prev, order, token of rows that are not kept; mark, slot, fill, or token of rows that are)
-    z.state = (size_t)((sums + 4 * rows + 4 * V + T + 1) * 4 + rows);
-    return z;
-}
-
 // Rows of an encode's logits computed at a time.  The product wants many (us an encode by rows a chunk 256 / 512 / 1024 /
 // 2048 / 3072 / 4096 / 8192: 65536 positions of 32128 bf16, d = 512 3013 / 1942 / 1564 / 1344 / 1366 / 1268 / 1228; 38985
 // of 153375, d = 896 17213 / 12969 / 12043 / 11419 / 12370 / 11364 / 11350; 15457 of 4597, d = 960 701 / 407 / 258 / 199 /
@@ -99,7 +80,30 @@ inline EncodeTables encode_tables(int64_t V, int64_t esz, int64_t rows, int64_t 
     return t;
 }
 
-// What an encode reserves, in a workspace of its own: the logits of a chunk, and the tables of a window in any form (37
+// What a decode reserves: logits (or group masses), a row of them per row, which every form can do with, or a table
+// that is preferred where it can be had; and the state: codes, tokens, flags, the tables of shared rows in any form, and
+// the sums of kept rows.  A decode of logits leaves room for one of group masses of its size, and for an encode of its
+// size a column and kPlainChunk rows at a time.
+constexpr int64_t kPlainChunk = 1024;
+struct DecodeSizes {
+    size_t needed, preferred, state;         // bytes
+};
+inline DecodeSizes decode_sizes(int64_t V, int64_t esz, int64_t rows, int64_t T, bool masses)
+{
+    const int64_t lb = logits_row_bytes(V, esz), mb = mass_row_bytes(V);
+    const int64_t kept = masses ? 0 : kept_rows_most(V, rows, T, lb), kept_masses = kept_rows_most(V, rows, T, mb);
+    DecodeSizes z;
+    z.needed = (size_t)(rows * larger(masses ? 0 : lb, mb));
+    z.preferred = (size_t)larger((int64_t)z.needed, larger(kept * lb, kept_masses * mb));
+    const int64_t sums = one_tile_row(V, esz) ? kept * kRowSums : 0;
+    // (codes, prev, order, token of rows that are not kept; mark, slot, fill, or token of rows that are)
+    const size_t state = (size_t)((sums + 4 * rows + 4 * V + T + 1) * 4 + rows);
+    const size_t column = encode_tables(V, esz, rows, rows, rows, smaller(rows, kPlainChunk), false).bytes;
+    z.state = state > column ? state : column;
+    return z;
+}
+
+// What an encode asks for, in a workspace of its own: the logits of a chunk, and the tables of a window in any form (37
 // bytes a position, 276 a logits row of the chunk, 8 a token of the vocabulary, 1 a sequence).
 struct EncodeSizes {
     size_t logits, state;                    // bytes

@@ -177,3 +177,30 @@ def test_an_encode_leaves_a_captured_decode_alone():
         job.encode(N, T)
         assert torch.equal(job.replay(graph, out), want)
     job.close()
+
+
+@pytest.mark.parametrize("V,d,N,ldt,top_k", [(8000, 512, 40, torch.bfloat16, 0), (8001, 128, 1100, torch.bfloat16, 20),
+                                             (3000, 24, 1025, torch.float32, 0)])
+def test_an_encode_does_with_the_workspace_of_a_decode(V, d, N, ldt, top_k):
+    """Where its own is refused, and under a capture that comes before any encode: the same bits."""
+    T = 90
+    job = Job(V, d, N, ldt=ldt)
+    job.tokens = torch.randint(0, V, (N, T), device="cuda", dtype=torch.int32)
+    want = job.encode(N, T, top_k=top_k)
+    small = job.context()
+    small.set_tuning("workspace_mib", 30)                 # (a row per sequence fits: 17 MB)
+    assert _same(job.encode(N, T, top_k=top_k, ctx=small), want)
+    assert B.lib().as_last_error(small._h) == b""
+    out = tuple(torch.empty_like(w) for w in want)
+    graph = job.captured(lambda o: job.encode(N, T, top_k=top_k, ctx=small, out=o), out)
+    assert _same(job.replay(graph, out), want)
+    small.close()
+    fresh = job.context()
+    tokens = job.decode(N, T, ctx=fresh)
+    graph = job.captured(lambda o: job.encode(N, T, top_k=top_k, ctx=fresh, out=o), out)
+    for _ in range(3):
+        assert _same(job.replay(graph, out), want)
+        assert torch.equal(job.decode(N, T, ctx=fresh), tokens)
+        assert _same(job.encode(N, T, top_k=top_k, ctx=fresh), want)     # (on its own from here on)
+    fresh.close()
+    job.close()

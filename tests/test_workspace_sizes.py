@@ -101,6 +101,8 @@ def test_what_a_decode_reserves_holds_every_form_of_it(lib):
                 by_sums = 68 * K if not masses and V * esz % 16 == 0 and V * esz <= 65536 else 0
                 forms += [2 * R + R + K + 2 * V + K + T + 1 + by_sums]
             assert z["state"] >= max(forms) * 4 + R, (V, esz, R, T, masses)
+            # ... and an encode of its size, a column at a time
+            assert z["state"] >= lib.tables(V, esz, R, R, R, min(R, 1024), 0)
     assert kept_at_all > 1000
 
 

@@ -466,6 +466,14 @@ static as_status reserve_decode(as_ctx *ctx, int64_t rows, int32_t T, bool masse
     return st != AS_OK ? st : grow(ctx, ctx->state, z.state);
 }
 
+// The same for a call that needs none of it
+static void reserve_decode_if_possible(as_ctx *ctx, int64_t rows, int32_t T)
+{
+    const DecodeSizes z = decode_sizes(ctx->V, ctx->dtype == AS_BF16 ? 2 : 4, rows, T, false);
+    (void)grow_if_possible(ctx, ctx->logits, z.preferred);
+    (void)grow_if_possible(ctx, ctx->state, z.state);
+}
+
 // Lays a decode's state out and takes its table of logits: rows of row_bytes, `masses` if they are group masses.  by_sums:
 // kept rows are stepped from their sums.
 static as_status decode_state(as_ctx *ctx, const as_model *model, int32_t B, int32_t N, int32_t T, int64_t row_bytes,
@@ -566,6 +574,8 @@ static as_status decode_impl(as_ctx *ctx, const as_model *model, const int32_t *
         SmallArgs a{};
         a.temp = temp; a.prompts = prompts; a.u = uniforms ? nullptr : u; a.uniforms = uniforms;
         a.rows = R; a.N = N; a.T = T; a.eos_id = eos_id; a.tokens = tokens_out; a.codes_out = codes_out;
+        // (it takes no workspace, but the same call with a truncation, or over one step, does and may be captured)
+        reserve_decode_if_possible(ctx, R, T);
         return launch_small_decode(ctx, model, a);
     }
     const size_t esz = ctx->dtype == AS_BF16 ? 2 : 4;

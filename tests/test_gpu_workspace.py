@@ -204,3 +204,21 @@ def test_an_encode_does_with_the_workspace_of_a_decode(V, d, N, ldt, top_k):
         assert _same(job.encode(N, T, top_k=top_k, ctx=fresh), want)     # (on its own from here on)
     fresh.close()
     job.close()
+
+
+@pytest.mark.parametrize("V,d,N", [(201, 24, 60), (16, 8, 64)])
+def test_a_decode_in_one_launch_leaves_the_workspace_of_its_size(V, d, N):
+    """It needs none itself, but the same call truncated, or over one step, does, and can be captured after it."""
+    job = Job(V, d, N, ldt=torch.float32, wdt=torch.float32)
+    own = job.context()
+    others = [(8, TEMP, 3), (1, TEMP, 0), (5, 0.2, 2), (8, 0.1, 0)]
+    want = [job.decode(N, T, temp, top_k, ctx=own) for T, temp, top_k in others]
+    job.decode(N, 8)
+    for (T, temp, top_k), w in zip(others, want):
+        out = torch.empty_like(w)
+        graph = job.captured(lambda o: job.decode(N, T, temp, top_k, out=o), out)
+        for _ in range(3):
+            assert torch.equal(job.replay(graph, out), w)
+            job.decode(N, 8)
+    own.close()
+    job.close()

@@ -143,7 +143,7 @@ def rows_kept(V, d, R, B, T, wdt, row_bytes, by_sums, cus=256):
     """Whether a decode keeps logits rows from step to step (the choice the library makes)."""
     if T < 3 or wdt != "bf16" or d % 64 != 0 or d < 128 or V * d * 2 >= 2 ** 32:
         return False
-    if V > 4 * R or (V > R and V * row_bytes > 2 ** 32):
+    if (T > 4 or R * T * row_bytes > 2 ** 32) if V > 4 * R else (V > R and V * row_bytes > 2 ** 32):
         return False
     computed = V * (1.0 - np.exp(-R * (T - 1) / V)) / (T - 1)
     # (against a row per token in each step where the decode would share those)

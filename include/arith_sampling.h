@@ -35,10 +35,13 @@
  *     truncation and model) allocate nothing and can be captured.  A decode
  *     takes a row of logits per code, or room for a row per token of the
  *     vocabulary where those are more: from a vocabulary of up to four times
- *     the codes, three steps on, and then at most 4 GiB; without that room it
- *     does with a row per code.  Its state is 17 bytes a code and 16 a token
+ *     the codes, three steps on, and then at most 4 GiB (from a larger one
+ *     over three or four steps, a row per code and step if the first call of
+ *     the size is such a one); without that room it does with a row per code.  Its state is 17 bytes a code and 16 a token
  *     of the vocabulary, and 272 a row of the table that it may keep, or if
  *     more 34 bytes a code and 276 for each of up to 1024 codes.
+ *     (as_decode_fused reserves for decodes of its own kind only, an eighth
+ *     to a sixteenth: a first as_decode after it takes more.)
  *   - One context must not be used from two host threads at once.
  */
 #ifndef ARITH_SAMPLING_H

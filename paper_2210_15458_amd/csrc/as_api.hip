@@ -457,11 +457,24 @@ struct DecodeState {
     float *sums;                 // kept rows whose steps work from sums: [logits_rows, kRowSums], else null
 };
 
-// Makes the workspace of a decode of `rows` rows (as_workspace.hpp).  A table of kept rows that cannot be had is done without.
+// What a decode of `rows` rows asks for (as_workspace.hpp): `few` a table of kept rows that only a first call of its size may
+// make room for, 0 for any other call.  A decode of logits leaves room for group masses, not the other way round.
+static DecodeSizes decode_asks(as_ctx *ctx, int64_t rows, int32_t T, bool masses, size_t &few)
+{
+    const int64_t V = ctx->V, esz = ctx->dtype == AS_BF16 ? 2 : 4;
+    const int64_t row_bytes = masses ? mass_row_bytes(V) : logits_row_bytes(V, esz);
+    const bool covered = ctx->seen[0].covers(rows, T) || (masses && ctx->seen[1].covers(rows, T));
+    few = covered ? 0 : (size_t)(kept_rows_few(V, rows, T, row_bytes) * row_bytes);
+    ctx->seen[masses ? 1 : 0].add(rows, T);
+    return decode_sizes(V, esz, rows, T, masses);
+}
+
+// Makes the workspace of a decode.  A table of kept rows that cannot be had is done without.
 static as_status reserve_decode(as_ctx *ctx, int64_t rows, int32_t T, bool masses)
 {
-    const DecodeSizes z = decode_sizes(ctx->V, ctx->dtype == AS_BF16 ? 2 : 4, rows, T, masses);
-    (void)grow_if_possible(ctx, ctx->logits, z.preferred);
+    size_t few;
+    const DecodeSizes z = decode_asks(ctx, rows, T, masses, few);
+    (void)grow_if_possible(ctx, ctx->logits, few > z.preferred ? few : z.preferred);
     const as_status st = grow(ctx, ctx->logits, z.needed);
     return st != AS_OK ? st : grow(ctx, ctx->state, z.state);
 }
@@ -469,8 +482,9 @@ static as_status reserve_decode(as_ctx *ctx, int64_t rows, int32_t T, bool masse
 // The same for a call that needs none of it
 static void reserve_decode_if_possible(as_ctx *ctx, int64_t rows, int32_t T)
 {
-    const DecodeSizes z = decode_sizes(ctx->V, ctx->dtype == AS_BF16 ? 2 : 4, rows, T, false);
-    (void)grow_if_possible(ctx, ctx->logits, z.preferred);
+    size_t few;
+    const DecodeSizes z = decode_asks(ctx, rows, T, false, few);
+    (void)grow_if_possible(ctx, ctx->logits, few > z.preferred ? few : z.preferred);
     (void)grow_if_possible(ctx, ctx->state, z.state);
 }
 
@@ -483,7 +497,8 @@ static as_status decode_state(as_ctx *ctx, const as_model *model, int32_t B, int
     as_status st = reserve_decode(ctx, R, T, masses);
     if (st != AS_OK) return st;
     const int64_t kept_rows = smaller(V, R * larger((int64_t)T - 1, 0) + B);
-    const bool keep = kept_rows_most(V, R, T, row_bytes) > 0 && keeping_pays(ctx, model, R, T, by_sums) &&
+    const bool keep = (kept_rows_most(V, R, T, row_bytes) > 0 || kept_rows_few(V, R, T, row_bytes) > 0) &&
+                      keeping_pays(ctx, model, R, T, by_sums) &&
                       (size_t)(kept_rows * row_bytes) <= ctx->logits.bytes;
     s.share = keep || sharing_pays(ctx, model, R, T);
     s.logits_rows = keep ? kept_rows : R;

@@ -54,6 +54,7 @@ struct as_ctx {
     // decode workspace (grown on demand)
     as::DeviceBuf logits;          // [rows, ld]
     as::DeviceBuf state;           // codes, prev, tables and sums of shared rows, finished flags
+    as::RowsSeen seen[2];          // by decodes of logits, of group masses
     // encode workspace: the logits of a chunk of rows, the tables of a window of positions.  Its own, since encodes want
     // many rows where decodes of their size have few, and neither is to move the other's
     as::DeviceBuf encode_logits, encode_state;

@@ -28,14 +28,30 @@ inline int64_t mass_row_bytes(int64_t V) { return ((V + 31) / 32 + 15) / 16 * 16
 inline bool one_tile_row(int64_t V, int64_t esz) { return V * esz % 16 == 0 && V * esz / 16 <= kTileVecs; }
 
 // The rows that a decode's table of kept logits rows can come to, or 0 where none is kept: steps enough to come back to a
-// token, a vocabulary of at most four times the rows of one step, and a table of more rows than those within kKeptBytes.
-// (By the vocabulary, not by the rows that the decode's steps can come to: a larger one would be within the bound for
-// three or four steps and beyond it for more, so that a shorter decode took more than a longer one.)
+// token, at most four times the rows of one step, and a table of more rows than those within kKeptBytes.  The bound by the
+// vocabulary alone holds for any number of steps (kept_rows_most); a larger vocabulary meets it over three or four steps
+// only (kept_rows_few), so that a decode of those would take more than a longer one: it may grow the workspace only where
+// no earlier call was of its size or larger (RowsSeen).
 inline int64_t kept_rows_most(int64_t V, int64_t rows, int64_t T, int64_t row_bytes)
 {
     if (T < 3 || V > 4 * rows || (V > rows && V * row_bytes > kKeptBytes)) return 0;
     return smaller(V, rows * T);
 }
+inline int64_t kept_rows_few(int64_t V, int64_t rows, int64_t T, int64_t row_bytes)
+{
+    return T >= 3 && T <= 4 && V > 4 * rows && rows * T * row_bytes <= kKeptBytes ? rows * T : 0;
+}
+
+// Most rows of the calls made so far that had three steps and more, four and more.
+struct RowsSeen {
+    int64_t three = 0, four = 0;
+    bool covers(int64_t rows, int64_t T) const { return rows <= (T >= 4 ? four : three); }      // for T of three or four
+    void add(int64_t rows, int64_t T)
+    {
+        if (T >= 3) three = larger(three, rows);
+        if (T >= 4) four = larger(four, rows);
+    }
+};
 
 // Rows of an encode's logits computed at a time.  The product wants many (us an encode by rows a chunk 256 / 512 / 1024 /
 // 2048 / 3072 / 4096 / 8192: 65536 positions of 32128 bf16, d = 512 3013 / 1942 / 1564 / 1344 / 1366 / 1268 / 1228; 38985
@@ -95,7 +111,7 @@ inline DecodeSizes decode_sizes(int64_t V, int64_t esz, int64_t rows, int64_t T,
     DecodeSizes z;
     z.needed = (size_t)(rows * larger(masses ? 0 : lb, mb));
     z.preferred = (size_t)larger((int64_t)z.needed, larger(kept * lb, kept_masses * mb));
-    const int64_t sums = one_tile_row(V, esz) ? kept * kRowSums : 0;
+    const int64_t sums = one_tile_row(V, esz) && T >= 3 ? smaller(V, rows * (V > 4 * rows ? smaller(T, 4) : T)) * kRowSums : 0;
     // (codes, prev, order, token of rows that are not kept; mark, slot, fill, or token of rows that are)
     const size_t state = (size_t)((sums + 4 * rows + 4 * V + T + 1) * 4 + rows);
     const size_t column = encode_tables(V, esz, rows, rows, rows, smaller(rows, kPlainChunk), false).bytes;

@@ -222,3 +222,20 @@ def test_a_decode_in_one_launch_leaves_the_workspace_of_its_size(V, d, N):
             job.decode(N, 8)
     own.close()
     job.close()
+
+
+def test_a_short_decode_makes_room_for_its_table_only_as_the_first_of_its_size():
+    V, d, N = 32128, 512, 8000                            # rows kept: 1.5 GB over four steps, against 0.5 of a row per code
+    job = Job(V, d, N)
+    want = job.decode(N, 4)                               # (the first: with the table)
+    job.close()
+    job = Job(V, d, N)
+    long = job.decode(N, 6)
+    out = torch.empty_like(long)
+    graph = job.captured(lambda o: job.decode(N, 6, out=o), out)
+    got = torch.empty_like(want)
+    before = _free()
+    assert torch.equal(job.decode(N, 4, out=got), want) and torch.equal(job.decode(N, 3, out=got[:, :, :3].contiguous()), want[:, :, :3])
+    assert abs(_free() - before) < 64 << 20
+    assert torch.equal(job.replay(graph, out), long)
+    job.close()

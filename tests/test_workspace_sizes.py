@@ -29,6 +29,11 @@ int64_t tables(int64_t V, int64_t esz, int64_t rows, int64_t positions, int64_t 
 int64_t chunk(int64_t rb) { return encode_chunk(rb); }
 int64_t window(int64_t rows, int64_t T) { return encode_window(rows, T); }
 int64_t kept(int64_t V, int64_t rows, int64_t T, int64_t row_bytes) { return kept_rows_most(V, rows, T, row_bytes); }
+int64_t few(int64_t V, int64_t rows, int64_t T, int64_t row_bytes) { return kept_rows_few(V, rows, T, row_bytes); }
+static RowsSeen seen;
+void forget() { seen = RowsSeen{}; }
+void add(int64_t rows, int64_t T) { seen.add(rows, T); }
+int covers(int64_t rows, int64_t T) { return seen.covers(rows, T); }
 int64_t row_bytes(int64_t V, int64_t esz, int masses) { return masses ? mass_row_bytes(V) : logits_row_bytes(V, esz); }
 }
 """
@@ -48,6 +53,9 @@ def lib(tmp_path_factory):
     L.chunk.argtypes, L.chunk.restype = [i64], i64
     L.window.argtypes, L.window.restype = [i64] * 2, i64
     L.kept.argtypes, L.kept.restype = [i64] * 4, i64
+    L.few.argtypes, L.few.restype = [i64] * 4, i64
+    L.add.argtypes, L.add.restype = [i64] * 2, None
+    L.covers.argtypes = [i64] * 2
     L.row_bytes.argtypes, L.row_bytes.restype = [i64, i64, ctypes.c_int], i64
     return L
 
@@ -94,10 +102,13 @@ def test_what_a_decode_reserves_holds_every_form_of_it(lib):
             z, rb = _sizes(lib, V, esz, R, T, masses), lib.row_bytes(V, esz, int(masses))
             assert z["needed"] >= R * rb and z["preferred"] >= z["needed"]
             forms = [2 * R, 2 * R + R + R + 2 * V + V + T + 1]                # own rows; rows shared in a step
-            if lib.kept(V, R, T, rb):
+            most, few = lib.kept(V, R, T, rb), lib.few(V, R, T, rb)
+            assert most == 0 or few == 0
+            if most or few:
                 K = min(V, R * (T - 1) + B)
                 kept_at_all += 1
-                assert K <= lib.kept(V, R, T, rb) and z["preferred"] >= K * rb and (K <= R or K * rb <= 4 << 30) and K <= 4 * R
+                assert K <= max(most, few) and (K <= R or K * rb <= 4 << 30) and K <= 4 * R
+                assert few or z["preferred"] >= K * rb
                 by_sums = 68 * K if not masses and V * esz % 16 == 0 and V * esz <= 65536 else 0
                 forms += [2 * R + R + K + 2 * V + K + T + 1 + by_sums]
             assert z["state"] >= max(forms) * 4 + R, (V, esz, R, T, masses)
@@ -111,7 +122,20 @@ def test_sizes_that_a_shorter_decode_once_took_more_for(lib):
     for V, esz, rows, long, short in ((32128, 2, 65536, 16, 2), (32128, 2, 8000, 16, 4), (2000, 2, 8192, 8, 8)):
         assert _sizes(lib, V, esz, rows, short)["preferred"] <= _sizes(lib, V, esz, rows, long)["preferred"]
     assert _sizes(lib, 32128, 2, 65536, 16)["needed"] == 65536 * 64256
-    assert _sizes(lib, 32128, 2, 8000, 4)["preferred"] == 8000 * 64256       # (V > 4 x 8000: no table)
+    assert _sizes(lib, 32128, 2, 8000, 4)["preferred"] == 8000 * 64256       # (V > 4 x 8000)
+
+
+def test_a_table_over_few_steps_is_made_by_first_calls_only(lib):
+    rng = random.Random(7)
+    for _ in range(200):
+        lib.forget()
+        calls = []
+        for _ in range(30):
+            rows, T = rng.randint(1, 40), rng.choice([0, 1, 2, 3, 4, 5, 9])
+            if T in (3, 4):
+                assert bool(lib.covers(rows, T)) == any(r >= rows and t >= T for r, t in calls)
+            lib.add(rows, T)
+            calls.append((rows, T))
 
 
 def _encode(lib, V, esz, rows, T):

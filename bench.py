@@ -62,7 +62,7 @@ def compute_units():
 
 def topk_tile_pays(V, rows, top_k, cus):
     """Whether the one-tile top-k kernel takes a step (the choice the library makes)."""
-    if top_k > 48 or (V <= 8192 and rows > 2 * cus):
+    if top_k > 47 or (V <= 8192 and rows > 2 * cus):
         return False
     s = 0.5 * (np.sqrt(3.5 ** 2 + 4.0 * (64 - top_k)) - 3.5)
     lam, lanes, vecs = s * s + top_k - 2.0, 0.0, V // 8

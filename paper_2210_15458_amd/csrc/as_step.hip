@@ -466,7 +466,7 @@ __global__ __launch_bounds__(256, 4) void step_tile_kernel(StepArgs a)
     using T = typename Elem<DT>::T;
     constexpr int EPV = Elem<DT>::kPerVec;
     // (eight waves of 8 KiB per row, which this code also fits in 64 registers, measured the same)
-    constexpr int NW = kTileWaves, ITERS = kTileIters, G = kTileGroup, NG = ITERS / G;
+    constexpr int ITERS = kTileIters, G = kTileGroup, NG = ITERS / G;
     constexpr int kShare = ITERS * 64;                // vectors per share
 
     __shared__ TileSums ts;

@@ -1246,7 +1246,7 @@ __global__ __launch_bounds__(kThreads) void threshold_stream_kernel(const void *
 //     vocabulary order; the bucket of the code and the rescaling follow (Sec. 4.1 loop body).  fp64 sums.
 // A table that overflows (heavy ties, flat rows) sends the block to the radix select and the plain three-pass
 // step, as in the resident kernel.
-constexpr int kTileTopK = 48;
+constexpr int kTileTopK = 47;      // (a bound of 48 lanes brings more logits than there are places: topk_tile_pays)
 constexpr int kTileCand = 64;
 
 typedef short i16x2 __attribute__((ext_vector_type(2)));
@@ -1290,7 +1290,6 @@ __global__ __launch_bounds__(kThreads, 4) void topk_tile_kernel(StepArgs a, int3
 {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
-    typedef float f32x4 __attribute__((ext_vector_type(4)));
     constexpr int NW = 4, ITERS = 16, G = 4, NG = ITERS / G, EPV = 8;
     constexpr int kShare = ITERS * 64;
     constexpr uint32_t kLowest = 0x80008000u;            // below the key of every stored value, twice: never a candidate
@@ -2029,10 +2028,10 @@ bool launch_topk_step(as_ctx *ctx, const StepArgs &args, int32_t top_k, float to
                           reinterpret_cast<uintptr_t>(a.logits) % 16 == 0 && (a.ld * esz) % 16 == 0;
     // (the nucleus: 8000 rows of 8200 127 us against 106 in the wide kernel, of 11000 128 / 116, of 12800 even; 2000 even)
     const int64_t cus = ctx->num_cus;
-    const bool by_tile = has_k ? (ctx->thr_path != 0 ? top_k <= kTileTopK : topk_tile_pays(ctx, a.rows, top_k))
-                               : a.k <= kTileMaxScale && (ctx->thr_path != 0 || !((ctx->V <= 8192 && a.rows > 2 * cus) ||
-                                                                                  (ctx->V <= 12288 && a.rows > 16 * cus)));
-    const bool tile = one_tile && by_tile;
+    const bool by_tile = has_k ? topk_tile_pays(ctx, a.rows, top_k)
+                               : a.k <= kTileMaxScale && !((ctx->V <= 8192 && a.rows > 2 * cus) ||
+                                                           (ctx->V <= 12288 && a.rows > 16 * cus));
+    const bool tile = ctx->thr_path == 0 && one_tile && by_tile;
     if (ctx->thr_path == 3 ||
         (ctx->thr_path == 0 && !tile && !resident_pays(ctx, a.logits, a.rows, a.ld, has_k, top_k) &&
          !streamed_pays(ctx, a.rows, has_k, top_k))) {
@@ -2045,7 +2044,7 @@ bool launch_topk_step(as_ctx *ctx, const StepArgs &args, int32_t top_k, float to
     *st = AS_OK;
     if (a.rows == 0) return true;
     const dim3 grid((unsigned)a.rows), block(kThreads);
-    if (has_k && tile && ctx->thr_path != 2) {
+    if (has_k && tile) {
         if (has_p && nt) launch(ctx, kKernelStep, topk_tile_kernel<true, true>, grid, block, 0, a, top_k, top_p);
         else if (has_p) launch(ctx, kKernelStep, topk_tile_kernel<true, false>, grid, block, 0, a, top_k, top_p);
         else if (nt) launch(ctx, kKernelStep, topk_tile_kernel<false, true>, grid, block, 0, a, top_k, top_p);
@@ -2054,7 +2053,7 @@ bool launch_topk_step(as_ctx *ctx, const StepArgs &args, int32_t top_k, float to
         if (e != hipSuccess) *st = hip_fail(ctx, e, "top-k step launch");
         return true;
     }
-    if (nucleus_only && tile && ctx->thr_path != 2) {
+    if (nucleus_only && tile) {
         if (nt) launch(ctx, kKernelStep, nucleus_tile_kernel<true>, grid, block, 0, a, top_p);
         else launch(ctx, kKernelStep, nucleus_tile_kernel<false>, grid, block, 0, a, top_p);
         hipError_t e = hipGetLastError();
@@ -2089,7 +2088,6 @@ as_status launch_threshold(as_ctx *ctx, const void *logits, int64_t rows, int64_
                            int32_t top_k, float top_p, float *thr_out)
 {
     if (rows == 0) return AS_OK;
-    const size_t esz = ctx->dtype == AS_BF16 ? 2 : 4;
     const bool has_k = top_k > 0 && top_k < ctx->V, has_p = top_p > 0.f && top_p < 1.f;
     // resident path: the row fits the block's registers, is read in 16-byte pieces, k at most half the thread
     // count (the k-th largest thread maximum must leave only a few hundred logits above it)

@@ -558,3 +558,10 @@ def test_few_rows_of_one_tile(dtype, V):
         ctx.close()
     for few, many in zip(*got):
         assert torch.equal(few.expand(copies, R), many)
+
+
+def test_top_k_at_the_line_of_the_one_tile_kernel():
+    """The largest k that it takes and the first that it does not, and its shortest and longest rows."""
+    for V, k in ((32128, 47), (32128, 48), (32768, 47), (27832, 47), (27824, 47), (11304, 40), (11296, 40)):
+        for top_p in (1.0, 0.9):
+            _check(V, 40, "bf16", top_k=k, top_p=top_p, seed=V + k)

@@ -142,7 +142,6 @@ struct StepArgs {
 struct IntervalArgs {
     const void *logits;
     int64_t rows;
-    int64_t src_rows;            // as in StepArgs
     int64_t ld;
     int32_t V;
     as_dtype dtype;

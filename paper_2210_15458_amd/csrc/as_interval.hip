@@ -603,7 +603,7 @@ as_status launch_interval(as_ctx *ctx, const IntervalArgs &args)
     const IntervalArgs &a = args;
     const dim3 grid((unsigned)a.rows), block(kThreads);
     const size_t esz = a.dtype == AS_BF16 ? 2 : 4;
-    const bool nt = stream_rows(a.src_rows ? a.src_rows : a.rows, a.ld, esz);
+    const bool nt = stream_rows(a.rows, a.ld, esz);
     const int epv = (int)(16 / esz);
     const bool tile = a.V % epv == 0 && a.V / epv <= kTileWaves * kTileIters * 64 &&
                       reinterpret_cast<uintptr_t>(a.logits) % 16 == 0 && (a.ld * (int64_t)esz) % 16 == 0 &&

@@ -113,13 +113,18 @@ const char *as_last_error(const as_ctx *ctx);
  *   AS_TUNE_WORKSPACE_MIB  largest buffer, in MiB, that a call may add to the
  *                       decode workspace: a larger one is refused, as by a
  *                       GPU without the memory
+ *   AS_TUNE_KEPT_ROWS   decodes: 1 = logits rows are not kept from step to
+ *                       step; 2 = wherever there is room for them, whether
+ *                       it pays or not (bf16 weights, a rank that is a
+ *                       multiple of 64 and at least 128, three steps)
  */
 typedef enum {
     AS_TUNE_STEP_SHAPE = 0,
     AS_TUNE_GEMM_SHAPE = 1,
     AS_TUNE_THR_PATH = 2,
     AS_TUNE_GEMM_GM = 3,
-    AS_TUNE_WORKSPACE_MIB = 4
+    AS_TUNE_WORKSPACE_MIB = 4,
+    AS_TUNE_KEPT_ROWS = 5
 } as_tuning;
 as_status as_ctx_set_tuning(as_ctx *ctx, as_tuning knob, int32_t value);
 

@@ -113,7 +113,7 @@ class Ctx:
         if rc != 0:
             raise ArithSamplingError(rc, (lib().as_last_error(self._h) or b"").decode())
 
-    TUNING = {"step_shape": 0, "gemm_shape": 1, "thr_path": 2, "gemm_gm": 3, "workspace_mib": 4}
+    TUNING = {"step_shape": 0, "gemm_shape": 1, "thr_path": 2, "gemm_gm": 3, "workspace_mib": 4, "kept_rows": 5}
 
     def set_tuning(self, knob, value):
         """Pick a kernel variant (tests and measurements): knob is one of Ctx.TUNING."""

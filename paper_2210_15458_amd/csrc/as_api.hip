@@ -249,6 +249,7 @@ as_status as_ctx_set_tuning(as_ctx *ctx, as_tuning knob, int32_t value)
     case AS_TUNE_GEMM_SHAPE: ctx->gemm_shape = value; return AS_OK;
     case AS_TUNE_THR_PATH: ctx->thr_path = value; return AS_OK;
     case AS_TUNE_GEMM_GM: ctx->gemm_gm = value; return AS_OK;
+    case AS_TUNE_KEPT_ROWS: ctx->kept_rows = value; return AS_OK;
     case AS_TUNE_WORKSPACE_MIB: ctx->workspace_mib = value; return AS_OK;
     }
     return fail(ctx, AS_ERR_INVALID_ARG, "unknown tuning knob");

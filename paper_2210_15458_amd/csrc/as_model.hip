@@ -1275,7 +1275,8 @@ bool sharing_pays(const as_ctx *ctx, const as_model *m, int64_t rows, int32_t T)
 // (How large its table may be: kept_rows_most.)
 bool keeping_pays(const as_ctx *ctx, const as_model *m, int64_t rows, int32_t T, bool by_sums)
 {
-    if (T < 3 || !rows_on_device(ctx, m)) return false;
+    if (T < 3 || !rows_on_device(ctx, m) || ctx->kept_rows == 1) return false;
+    if (ctx->kept_rows == 2) return true;
     const double V = (double)m->V, R = (double)rows;
     const double steps = T - 1;
     const double computed = V * (1.0 - exp(-R * steps / V)) / steps;           // logits rows a step

@@ -40,10 +40,16 @@ def test_kept_rows_equal_the_loop_of_exported_calls(V, d, Bn, N, T, top_k, top_p
     R = Bn * N
     assert bench.rows_kept(V, d, R, Bn, T, "bf16", (V + 7) // 8 * 8 * (2 if ldt == "bf16" else 4),
                            bench.step_by_sums(V, ldt, top_k, top_p, TEMP))
+    ctx.set_tuning("kept_rows", 2)                        # (here whatever the rule comes to be)
     out = torch.empty((Bn, N, T), dtype=torch.int32, device="cuda")
     last = torch.empty(R, dtype=torch.float32, device="cuda")
     for _ in range(2):                                    # twice: the tables are left from the call before
         B.as_decode(ctx, model, prompts, N, T, u, TEMP, top_k, top_p, EOS, out, codes_out=last)
+    ctx.profile(True)
+    B.as_decode(ctx, model, prompts, N, T, u, TEMP, top_k, top_p, EOS, out, codes_out=last)
+    steps = ctx.profile_read(0)[1]
+    ctx.profile(False)
+    assert steps == (2 if bench.step_by_sums(V, ldt, top_k, top_p, TEMP) else 1) * T
     logits = torch.empty((R, (V + 7) // 8 * 8), dtype=DT[ldt], device="cuda")
     codes = torch.empty(R, dtype=torch.float32, device="cuda")
     B.as_lattice(ctx, u, N, codes)
@@ -83,5 +89,32 @@ def test_kept_rows_replay_from_a_graph():
             B.as_decode(ctx, model, prompts, N, T, u, TEMP, 0, 1.0, EOS, eager)
         stream.synchronize()
         assert torch.equal(got, eager), f"replay {i}"
+    ctx.close()
+    model.close()
+
+
+def _step_launches(ctx, model, prompts, N, T, u, out):
+    ctx.profile(True)
+    B.as_decode(ctx, model, prompts, N, T, u, TEMP, 0, 1.0, EOS, out)
+    n = ctx.profile_read(0)[1]
+    ctx.profile(False)
+    return n
+
+
+# on either side of the rule: by rows, by steps, by the vocabulary that the workspace has room for
+@pytest.mark.parametrize("V,d,R,T,kept", [(2000, 128, 2048, 64, True), (2000, 128, 1024, 64, False), (8000, 512, 4096, 4, True),
+                                          (8000, 512, 2048, 16, False), (32128, 512, 8192, 5, True), (32128, 512, 8000, 5, False),
+                                          (32128, 512, 8000, 4, True), (3000, 64, 8192, 16, False)])
+def test_which_decodes_keep_rows(V, d, R, T, kept):
+    """Steps from sums are two launches: the library's choice, the knob's, and what the benchmark takes the choice to be."""
+    model, ctx, prompts, u = _setup(V, d, 1, R, "bf16", 3.0)
+    prompts[0] = 7
+    out = torch.empty((1, R, T), dtype=torch.int32, device="cuda")
+    assert _step_launches(ctx, model, prompts, R, T, u, out) == (2 * T if kept else T)
+    assert bench.rows_kept(V, d, R, 1, T, "bf16", V * 2, True) == kept
+    want = out.clone()
+    ctx.set_tuning("kept_rows", 1)
+    assert _step_launches(ctx, model, prompts, R, T, u, out) == T
+    assert torch.equal(out, want)
     ctx.close()
     model.close()

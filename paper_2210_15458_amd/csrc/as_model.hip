@@ -930,6 +930,10 @@ __global__ __launch_bounds__(256) void bigram_gemm_thin(const uint16_t *__restri
 // 16.5 / 5.2; 100 x 32128 16.1 / 12.2 / 11.8 / 9.9; 129 x 32128 16.3 / 14.4 / 16.2 / 17.6; 200 x 32128 17.3 / 18.8 / 21.0 / 17.7;
 // 33 x 50000 17.6 / 12.4 / 12.1 / 16.7; d = 1024: 512 x 3000 23.1 / 9.9 / 9.7 / 13.6, 65 x 100000 49.0 / 41.9 / 58.6 / 53.4, 100 x
 // 100000 50.1 / 54.4 / 61.8 / 55.7; d = 128: 512 x 2000 7.6 / 4.2 / 4.3 / 5.0.
+// The same line where the persistent kernel cannot run and bigram_gemm_bf16 is the other one (us, here / there, as the line has
+// it).  d = 64: 16 x 300 4.1 / 7.2, 8192 x 300 6.0 / 12.8, 1024 x 4000 5.3 / 8.8, 512 x 8000 5.3 / 9.7, 384 x 16000 7.8 / 9.5,
+// 200 x 32128 9.3 / 10.0, 64 x 256000 17.8 / 20.7, and of 160 shapes only 4096 x 2000 (10.2 / 9.6) and 768 x 8000 (9.6 / 9.3)
+// slower.  Operands of 4 GiB, 2^21 tokens, d = 1024: 1 row 711 / 822, 32 792 / 868, 64 988 / 923.
 static int thin_tiles(const as_ctx *ctx, const as_model *m, int64_t rows)
 {
     if (ctx->gemm_shape != 0) return 0;

@@ -9,8 +9,8 @@ from paper_2210_15458_amd import synth
 
 pytestmark = pytest.mark.gpu
 
-# (V, d, weights, logits, R): the vector kernel's small tiles (64 x 64: one short, exact, one over, in each
-# direction; ranks below, at and over its K step and over the four steps it requests ahead), its large ones
+# (V, d, weights, logits, R): the fp32 kernel around tiles of 64 (one short, exact, one over, in each
+# direction) and K steps of 32 and 64, many rows
 _VEC = [(63, 7, "f32", "f32", 1), (64, 32, "f32", "f32", 64), (65, 33, "f32", "bf16", 65), (1001, 130, "f32", "f32", 3),
         (700, 72, "bf16", "f32", 100), (333, 257, "bf16", "bf16", 129), (16500, 40, "f32", "f32", 520),
         (8200, 31, "f32", "bf16", 1030)]
@@ -85,16 +85,27 @@ def test_group_masses_of_few_rows(V, d, R):
     assert np.array_equal(res[0], res[1])
 
 
-# the plain kernel up to its line (65536 logits; rank 26 with fp32 weights, 38 up to 128 columns, 56 with bf16 ones) and the
-# tiled one past it; where all rows are past it, single rows are not
-_PLAIN = [(1024, 12, "f32", "bf16", 64), (1024, 26, "f32", "f32", 65), (1024, 27, "f32", "f32", 64),
+# ranks and sizes where a product was once one thread per logit; single elements, ranks off every K step
+_SMALL = [(1024, 12, "f32", "bf16", 64), (1024, 26, "f32", "f32", 65), (1024, 27, "f32", "f32", 64),
           (128, 38, "f32", "bf16", 512), (128, 32, "f32", "f32", 3), (8200, 11, "f32", "f32", 33), (1, 1, "f32", "f32", 1),
           (563, 33, "bf16", "f32", 116), (2003, 56, "bf16", "bf16", 40), (700, 57, "bf16", "f32", 9)]
 
 
-@pytest.mark.parametrize("V,d,wdt,ldt,R", _PLAIN)
-def test_plain_kernel_at_its_line(V, d, wdt, ldt, R):
+@pytest.mark.parametrize("V,d,wdt,ldt,R", _SMALL)
+def test_small_products(V, d, wdt, ldt, R):
     test_logits_tile_edges(V, d, wdt, ldt, R)
+
+
+# both sides of each line between the fp32 kernel's tilings (256 compute units): K steps of 16, 32 and 64 by the rank up to
+# 256 blocks of 32 x 64, two waves of rows up to six times as many, the largest tiles from 16 times as many of 128 x 128
+_LINES = [(1024, 16, "f32", 512), (1024, 17, "f32", 512), (1024, 32, "f32", 512), (1024, 33, "f32", 512), (1025, 16, "f32", 512),
+          (1024, 33, "bf16", 513), (6144, 40, "f32", 512), (6145, 40, "f32", 512), (6144, 40, "bf16", 513),
+          (32641, 24, "f32", 2048), (32640, 24, "f32", 2048), (32768, 24, "bf16", 2049)]
+
+
+@pytest.mark.parametrize("V,d,wdt,R", _LINES)
+def test_fp32_logits_at_the_lines_between_tilings(V, d, wdt, R):
+    test_fp32_logits_are_one_chain_over_k(V, d, wdt, R)
 
 
 # the fp32 kernel's four tilings (16 x 64, 32 x 64, 64 x 128, 128 x 128 by the number of blocks), whole rows (ranks of a
@@ -141,3 +152,46 @@ def test_row_tiles_of_small_products(V, d, ldt, R):
 @pytest.mark.parametrize("V,d,R", [(3000, 512, 257), (3000, 512, 1001), (1030, 128, 65)])
 def test_row_tiles_of_group_masses(V, d, R):
     test_group_masses_of_few_rows(V, d, R)
+
+
+@pytest.mark.parametrize("V,d,wdt,R", [(300, 17, "f32", 40), (300, 48, "f32", 40), (1000, 100, "f32", 17), (4100, 75, "f32", 200),
+                                       (4100, 48, "bf16", 1000), (4100, 31, "f32", 1001), (16500, 19, "bf16", 4100)])
+def test_fp32_chain_of_values_at_the_ends_of_the_range(V, d, wdt, R):
+    """The same with subnormal factors, products and sums, sums beyond fp32, infinities and NaN: the bits of libm's fmaf
+    (a NaN is a NaN).  One class of values a row, so that one does not hide another."""
+    import ctypes
+    from paper_2210_15458_amd import binding as B
+    from gpu_util import to_dev_logits
+    fmaf = ctypes.CDLL("libm.so.6").fmaf
+    fmaf.restype, fmaf.argtypes = ctypes.c_float, [ctypes.c_float] * 3
+    rng = np.random.default_rng(V + d)
+    kind = np.arange(V) % 5
+    E = rng.standard_normal((V, d)).astype(np.float32)
+    E[kind == 0] *= np.float32(2.0 ** -130)                       # subnormal factors, subnormal sums
+    E[kind == 1] *= np.float32(2.0 ** -75)                        # with the columns' 2^-70: products below the normal range
+    E[kind == 2] *= np.float32(2.0 ** 120)                        # with the columns' 2^10: sums beyond fp32, inf - inf
+    E[kind == 3, d // 2] = np.inf                                 # with a zero in the column: NaN
+    E[kind == 4, d - 1] = np.nan
+    U = rng.standard_normal((d, V)).astype(np.float32)
+    U[:, 1::4] *= np.float32(2.0 ** -70)
+    U[:, 2::4] *= np.float32(2.0 ** 10)
+    U[d // 2, 3::4] = 0.0
+    if wdt == "bf16":                                             # (cut, not rounded: the same classes; a cut NaN stays one)
+        E, U = ((x.view(np.uint32) >> 16).astype(np.uint16) for x in (E, U))
+        Ew, Uw = synth.bf16_bits_to_f32(E), synth.bf16_bits_to_f32(U)
+    else:
+        Ew, Uw = E, U
+    model = B.Model(to_dev_logits(E), to_dev_logits(U), scale=math.sqrt(d))      # (alpha = 1: the chain itself)
+    prev = rng.integers(0, V, R).astype(np.int32)
+    got = _logits(model, prev, V, "f32", R)
+    seen = {"subnormal": 0, "inf": 0, "nan": 0, "normal": 0}
+    for r, v in zip(rng.integers(0, R, 400), rng.integers(0, V, 400)):
+        acc = 0.0
+        for a, b in zip(Ew[prev[r]].tolist(), Uw[:, v].tolist()):
+            acc = fmaf(a, b, acc)
+        want = np.float32(acc)
+        seen["nan" if np.isnan(want) else "inf" if np.isinf(want) else
+             "subnormal" if 0 < abs(want) < 2.0 ** -126 else "normal"] += 1
+        assert np.isnan(got[r, v]) if np.isnan(want) else got[r, v] == want, (r, v, kind[prev[r]], got[r, v], want)
+    assert min(seen.values()) > 0, seen
+    model.close()

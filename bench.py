@@ -83,7 +83,11 @@ def sampling_kernel_name(V, ldt, top_k, top_p, temp, rows, d, wdt, cus):
     first_chunk_reference_ok = 1.4426950408889634 / temp <= 4.0      # (the library's kTileMaxScale)
     name = None
     if not (has_k or has_p):
-        if not (wdt == "bf16" and d % 64 == 0) and V <= (512 if half else 256) and d <= (64 if half else 128) and V * d <= 2048:
+        vecs = 8 if half else 4
+        lds = (d + 3) // 4 * 4 * (-(-V // vecs) * vecs + V) * 4      # (weights of which two blocks fit a compute unit, a few dozen rounds)
+        fit = min(160 * 1024 // (lds + 64), 16)
+        if (not (wdt == "bf16" and d % 64 == 0) and V <= 64 * vecs and d <= (64 if half else 128) and fit >= 2 and
+                rows <= 12 * fit * cus):
             name = "decode_wave_kernel (the whole decode in one launch, a wave per row)"
         elif (not (wdt == "bf16" and d % 64 == 0) and V <= 1024 and d <= 128 and V * d <= 8192 and
                 V % (8 if half else 4) == 0 and rows <= 3 * cus and first_chunk_reference_ok):

@@ -446,7 +446,7 @@ as_status as_bigram_logits(as_ctx *ctx, const as_model *model, const int32_t *pr
     return launch_bigram_logits(ctx, model, prev, rows, logits_out, ld);
 }
 
-// The state of a running decode or encode in the context's workspace: per row the code, the conditioning token and the
+// The state of a running decode in the context's workspace: per row the code, the conditioning token and the
 // finished flag, and the tables of shared logits rows where those pay.
 struct DecodeState {
     float *codes;

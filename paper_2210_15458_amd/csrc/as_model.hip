@@ -1118,7 +1118,7 @@ __global__ __launch_bounds__(256) void bigram_gemm_chain(const WT *__restrict__ 
 }
 
 template <class WT, class OutT>
-void launch_vec(as_ctx *ctx, const as_model *m, const int32_t *prev, int64_t rows, void *out, int64_t ld, float alpha)
+void launch_chain(as_ctx *ctx, const as_model *m, const int32_t *prev, int64_t rows, void *out, int64_t ld, float alpha)
 {
     const bool whole = m->d % 16 == 0 && reinterpret_cast<uintptr_t>(m->E) % 16 == 0 && reinterpret_cast<uintptr_t>(m->Ut) % 16 == 0;
 #define AS_CHAIN(GM_, GN_, TM_, TN_, KS_, AHEAD_)                                                                              \
@@ -1391,11 +1391,11 @@ as_status launch_bigram_logits(as_ctx *ctx, const as_model *m, const int32_t *pr
         }
     } else {
         if (m->wdtype == AS_BF16) {
-            if (ctx->dtype == AS_BF16) launch_vec<uint16_t, uint16_t>(ctx, m, prev, rows, logits_out, ld, alpha);
-            else launch_vec<uint16_t, float>(ctx, m, prev, rows, logits_out, ld, alpha);
+            if (ctx->dtype == AS_BF16) launch_chain<uint16_t, uint16_t>(ctx, m, prev, rows, logits_out, ld, alpha);
+            else launch_chain<uint16_t, float>(ctx, m, prev, rows, logits_out, ld, alpha);
         } else {
-            if (ctx->dtype == AS_BF16) launch_vec<float, uint16_t>(ctx, m, prev, rows, logits_out, ld, alpha);
-            else launch_vec<float, float>(ctx, m, prev, rows, logits_out, ld, alpha);
+            if (ctx->dtype == AS_BF16) launch_chain<float, uint16_t>(ctx, m, prev, rows, logits_out, ld, alpha);
+            else launch_chain<float, float>(ctx, m, prev, rows, logits_out, ld, alpha);
         }
     }
     AS_HIP_TRY(ctx, hipGetLastError());

@@ -188,6 +188,19 @@ def step_counts(tokens, eos, prompts, shared, kept=False):
     return {"active": float(active.sum()) / T, "computed": float(np.mean(computed)), "fetched": float(np.mean(fetched))}
 
 
+def table_figures(V, esz, steps, T, active, step_samples, thr_samples, gemm_samples):
+    """The sampling side of decodes that make the logits rows of all tokens before their first step, per step of the decode
+    (known by their launches: fewer products than steps): every row once for its record, then per code a record and a KiB of
+    a row.  None for other decodes."""
+    if not 0 < len(gemm_samples) < T * steps or not len(thr_samples):
+        return None
+    total = float(np.sum(step_samples) + np.sum(thr_samples)) * 1e3
+    return {"kernel": "the rows' records (row_records_kernel or the truncating kernel of the shape), then walk_kernel, inside as_decode",
+            "avg_launch_us": total / (T * steps), "records_us": float(np.mean(thr_samples)) * 1e3,
+            "bytes_per_launch": V * (V * esz + 1056.0) / T + active * (1056 + 1024 + 18),
+            "rows_computed_per_launch": V * float(steps) / len(gemm_samples)}
+
+
 def compact_leg(cfg_id, top_k, top_p, steps, warmup):
     """One whole-decode measurement of another configuration at its full shape, with the kernels' own times."""
     import torch
@@ -230,13 +243,17 @@ def compact_leg(cfg_id, top_k, top_p, steps, warmup):
         step_samples = np.asarray(step_samples).reshape(-1, 2).sum(axis=1)
     # the sampling step of a launch: the kernel that finishes it, plus the threshold kernel where that is separate
     samp_us = float(np.mean(step_samples)) * 1e3 + (float(np.mean(thr_samples)) * 1e3 if len(thr_samples) else 0.0)
+    table = table_figures(V, 2, steps, T, cnt["active"], step_samples, thr_samples, gemm_samples)
+    if table:
+        samp_us, bytes_per_launch, cnt["computed"] = table["avg_launch_us"], table["bytes_per_launch"], table["rows_computed_per_launch"]
     ach = bytes_per_launch / (samp_us * 1e-6) / 1e9
     out = {
         "workload": f"configs[{cfg_id}] {cfg['name']}: as_decode V={V} d={d} bf16, B={Bn} N={N} (R={R}) T={T} "
                     f"temp={temp} top_k={top_k} top_p={top_p} eos={eos}",
         "value": R * T * steps / (t1 - t0), "unit": "code-steps/s", "decodes_timed": steps,
         "ms_per_decode": (t1 - t0) / steps * 1e3,
-        "sampling": {"kernel": "row_sums_kernel, then row_select_kernel, as launched inside as_decode" if kept and by_sums else
+        "sampling": {"kernel": table["kernel"] if table else
+                     "row_sums_kernel, then row_select_kernel, as launched inside as_decode" if kept and by_sums else
                      sampling_kernel_name(V, "bf16", top_k, top_p, temp, R, d, cfg["dtype"], compute_units()),
                      "bound": "hbm",
                      "avg_launch_us": samp_us, "spread": spread(step_samples), "achieved": ach, "peak": HBM_PEAK_GBS,
@@ -247,7 +264,9 @@ def compact_leg(cfg_id, top_k, top_p, steps, warmup):
                         "achieved": 2.0 * cnt["computed"] * d * V / (float(np.mean(gemm_samples)) * 1e-3) / 1e12,
                         "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s"}}
     out["logits_gemm"]["frac"] = out["logits_gemm"]["achieved"] / MFMA_BF16_PEAK_TFLOPS
-    if len(thr_samples):
+    if table:
+        out["sampling"]["records_us_per_launch"] = table["records_us"]
+    elif len(thr_samples):
         out["sampling"]["threshold_kernel_us"] = float(np.mean(thr_samples)) * 1e3
     if top_k <= 0 and not (0.0 < top_p < 1.0) and R <= 4096:
         # the same decode without the logits round trip (no logit modifiers; logits stay fp32 on chip)
@@ -376,6 +395,7 @@ def main():
     t3 = time.perf_counter()
     step_samples = ctx.profile_samples(0)
     gemm_samples = ctx.profile_samples(1)
+    thr_samples = ctx.profile_samples(2)
     step_ms, step_n, step_drop = ctx.profile_read(0)
     gemm_ms, gemm_n, _ = ctx.profile_read(1)
     thr_ms, thr_n, _ = ctx.profile_read(2)
@@ -388,6 +408,9 @@ def main():
     bytes_per_row = V * esz + 18           # the logits row + code in/out, token, flags
     bytes_per_launch = cnt["fetched"] * V * esz + cnt["active"] * 18
     step_avg_us = step_ms / max(step_n, 1) * 1e3
+    table = table_figures(V, esz, args.steps, T, cnt["active"], step_samples, thr_samples, gemm_samples)
+    if table:
+        step_avg_us, bytes_per_launch, cnt["computed"] = table["avg_launch_us"], table["bytes_per_launch"], table["rows_computed_per_launch"]
     # (a launch that does a whole decode has no logits rows in memory)
     whole_decode = T > 1 and step_n == args.steps
     achieved = bytes_per_launch / (step_avg_us * 1e-6) / 1e9 if step_n and not whole_decode else None
@@ -413,14 +436,16 @@ def main():
                    "value_over_a_longer_region": {"steps": long_steps, "value": R * T * long_steps / (t5 - t4),
                                                   "ms_per_step": (t5 - t4) / long_steps * 1e3}},
         "roofline": {
-            "kernel": sampling_kernel_name(V, ldt, top_k, top_p, temp, R, d, cfg["dtype"], compute_units()),
+            "kernel": table["kernel"] if table else
+            sampling_kernel_name(V, ldt, top_k, top_p, temp, R, d, cfg["dtype"], compute_units()),
             "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": (achieved / HBM_PEAK_GBS) if achieved else None, "traffic": None,
             "avg_launch_us": step_avg_us, "launches": step_n, "untimed_launches": step_drop,
             "bytes_per_code_step": bytes_per_row, "bytes_per_launch": bytes_per_launch,
             "active_rows_per_launch": cnt["active"],
             "logits_rows_fetched_per_launch": cnt["fetched"],
-            "note": "rows follow the logits GEMM that just wrote them, so part of each row can come from "
+            "note": "per step of the decode, its share of the records included" if table else
+                    "rows follow the logits GEMM that just wrote them, so part of each row can come from "
                     "the Infinity Cache rather than HBM; see roofline_cold for the HBM-only figure"},
         "logits_gemm": {
             "bound": "mfma", "avg_launch_us": gemm_ms / max(gemm_n, 1) * 1e3, "launches": gemm_n,
@@ -438,7 +463,9 @@ def main():
         by_step = np.asarray(step_samples).reshape(args.steps, T)
         out["roofline"]["first_step"] = spread(by_step[:, 0])
         out["roofline"]["late_steps"] = spread(by_step[:, T // 2:].ravel())
-    if thr_n:
+    if table:
+        out["roofline"]["records_us_per_launch"] = table["records_us"]
+    elif thr_n:
         out["threshold_kernel"] = {"avg_launch_us": thr_ms / thr_n * 1e3, "launches": thr_n}
 
     # ---- the same decode without the logits round trip (no logit modifiers; logits stay fp32 on chip)

@@ -456,6 +456,11 @@ struct DecodeState {
     RowShare tables;
     int64_t logits_rows;         // rows of the table of logits (or group masses) that the decode works on
     float *sums;                 // kept rows whose steps work from sums: [logits_rows, kRowSums], else null
+    // a table of every token's logits row, made before the first step:
+    bool table;
+    unsigned char *records;      // [V, kTableRecord], where steps work from records
+    int32_t *token;              // [V] the rows' tokens
+    int32_t *prev_next;          // [R] the other half of prev (steps that read it as row_ids)
 };
 
 // What a decode of `rows` rows asks for (as_workspace.hpp): `few` a table of kept rows that only a first call of its size may
@@ -490,17 +495,35 @@ static void reserve_decode_if_possible(as_ctx *ctx, int64_t rows, int32_t T)
 }
 
 // Lays a decode's state out and takes its table of logits: rows of row_bytes, `masses` if they are group masses.  by_sums:
-// kept rows are stepped from their sums.
+// kept rows are stepped from their sums.  form: what steps from a table of every token's row work from.
 static as_status decode_state(as_ctx *ctx, const as_model *model, int32_t B, int32_t N, int32_t T, int64_t row_bytes,
-                              bool masses, bool by_sums, DecodeState &s)
+                              bool masses, bool by_sums, TableForm form, DecodeState &s)
 {
     const int64_t R = (int64_t)B * N, V = ctx->V;
     as_status st = reserve_decode(ctx, R, T, masses);
     if (st != AS_OK) return st;
     const int64_t kept_rows = smaller(V, R * larger((int64_t)T - 1, 0) + B);
-    const bool keep = (kept_rows_most(V, R, T, row_bytes) > 0 || kept_rows_few(V, R, T, row_bytes) > 0) &&
-                      keeping_pays(ctx, model, R, T, by_sums) &&
-                      (size_t)(kept_rows * row_bytes) <= ctx->logits.bytes;
+    bool keep = (kept_rows_most(V, R, T, row_bytes) > 0 || kept_rows_few(V, R, T, row_bytes) > 0) &&
+                keeping_pays(ctx, model, R, T, by_sums) && (size_t)(kept_rows * row_bytes) <= ctx->logits.bytes;
+    // (timed decodes keep their rows where they can: a step's launches are told apart then)
+    s.table = table_rows(V, R, T, row_bytes) > 0 && (size_t)(V * row_bytes) <= ctx->logits.bytes && !(keep && ctx->prof.on) &&
+              table_pays(ctx, model, R, T, form, keep, by_sums);
+    if (s.table) {
+        keep = false;
+        unsigned char *w = static_cast<unsigned char *>(ctx->state.ptr);
+        s.records = w;
+        if (form != kTableRows) w += V * kTableRecord;
+        s.codes = reinterpret_cast<float *>(w);
+        s.prev = reinterpret_cast<int32_t *>(w) + R;
+        s.prev_next = s.prev + R;
+        s.token = s.prev_next + R;
+        s.fin = reinterpret_cast<uint8_t *>(s.token + V);
+        s.share = false;
+        s.tables = RowShare{};
+        s.sums = nullptr;
+        s.logits_rows = V;
+        return launch_table_tokens(ctx, s.token);
+    }
     s.share = keep || sharing_pays(ctx, model, R, T);
     s.logits_rows = keep ? kept_rows : R;
     const int64_t filled = keep ? s.logits_rows : V;
@@ -545,6 +568,10 @@ static as_status step_rows(as_ctx *ctx, const DecodeState &s, const int32_t *pro
                            bool sorted, StepRows &o)
 {
     const int64_t R = (int64_t)B * N;
+    if (s.table) {                                            // (its rows are there)
+        o = StepRows{nullptr, 0, RowRange{}, s.prev, s.logits_rows, nullptr};
+        return AS_OK;
+    }
     if (s.tables.kept) {
         // (the first step's prompts are claimed as such: R rows on a few tokens would queue for them)
         const int64_t most = t == 0 ? B : (R < s.logits_rows ? R : s.logits_rows);
@@ -564,6 +591,34 @@ static as_status step_rows(as_ctx *ctx, const DecodeState &s, const int32_t *pro
     }
     o = StepRows{s.tables.token, R, RowRange{nullptr, s.tables.count + t}, ctx->rid, 0, sorted ? s.tables.order : nullptr};
     return launch_share(ctx, s.tables, t, s.prev, R, ctx->rid, sorted);
+}
+
+// The rows of a table of every token's logits, and the records that its steps work from: each in one launch (1024 / 2048 /
+// 4096 / 8192 / 16384 / all 32128 rows, d = 512, at a time, so that the records find them in the caches: 1708 / 1642 / 1589 /
+// 1693 / 1591 / 1542 us a decode of 1024 codes x 64).
+static as_status fill_table(as_ctx *ctx, const as_model *model, const DecodeState &s, int64_t ldw, TableForm form, float temp,
+                            int32_t top_k, float top_p)
+{
+    const as_status st = launch_bigram_logits(ctx, model, s.token, ctx->V, ctx->logits.ptr, ldw);
+    if (st != AS_OK || form == kTableRows) return st;
+    return launch_table_records(ctx, form, ctx->logits.ptr, ldw, temp, top_k, top_p, s.records);
+}
+
+// Its steps, in one launch (timed: a launch each, so that their times can be told apart)
+static as_status walk_table(as_ctx *ctx, const DecodeState &s, int64_t ldw, TableForm form, int64_t R, int32_t T,
+                            const float *uniforms, float temp, int32_t eos_id, int32_t *tokens_out)
+{
+    WalkArgs a{};
+    a.logits = ctx->logits.ptr; a.records = s.records; a.ld = ldw; a.V = ctx->V; a.dtype = ctx->dtype;
+    a.k = 1.44269504088896340736f / temp; a.rows = R; a.T = T; a.eos_id = eos_id; a.uniforms = uniforms;
+    a.codes = s.codes; a.prev = s.prev; a.finished = s.fin; a.tokens = tokens_out;
+    const int32_t per = ctx->prof.on ? 1 : T;
+    for (a.t0 = 0; a.t0 < T; a.t0 = a.t1) {
+        a.t1 = T - a.t0 < per ? T : a.t0 + per;
+        const as_status st = launch_walk(ctx, form, a);
+        if (st != AS_OK) return st;
+    }
+    return AS_OK;
 }
 
 // as_decode and as_decode_ancestral: with `uniforms` the code of row r at step t is uniforms[t*R + r] and
@@ -597,20 +652,27 @@ static as_status decode_impl(as_ctx *ctx, const as_model *model, const int32_t *
     const size_t esz = ctx->dtype == AS_BF16 ? 2 : 4;
     const int64_t ldw = ((int64_t)ctx->V + 7) / 8 * 8;        // rows start 16-byte aligned
     DecodeState state;
-    as_status st = decode_state(ctx, model, B, N, T, ldw * (int64_t)esz, false, !trunc && step_by_sums(ctx, temp), state);
+    const TableForm form = table_form(ctx, R, temp, top_k, top_p);
+    as_status st = decode_state(ctx, model, B, N, T, ldw * (int64_t)esz, false, !trunc && step_by_sums(ctx, temp), form, state);
     if (st != AS_OK) return st;
     float *const codes = state.codes;
-    int32_t *const prev = state.prev;
     uint8_t *const fin = state.fin;
 
-    st = launch_lattice(ctx, u, B, N, uniforms ? nullptr : codes, prompts, prev, fin, ctx->rid);
+    st = launch_lattice(ctx, u, B, N, uniforms ? nullptr : codes, prompts, state.prev, fin, ctx->rid);
+    if (st == AS_OK && state.table) st = fill_table(ctx, model, state, ldw, form, temp, top_k, top_p);
     if (st != AS_OK) return st;
-    for (int32_t t = 0; t < T; ++t) {
+    const bool walk = state.table && form != kTableRows;
+    if (walk) st = walk_table(ctx, state, ldw, form, R, T, uniforms, temp, eos_id, tokens_out);
+    if (st != AS_OK) return st;
+    for (int32_t t = 0; t < T && !walk; ++t) {
         StepRows sr;
         st = step_rows(ctx, state, prompts, B, N, t, !trunc && stream_rows(R, ldw, esz), sr);
         if (st != AS_OK) return st;
-        st = launch_bigram_logits(ctx, model, sr.prev, sr.rows, ctx->logits.ptr, ldw, sr.range);
+        if (!state.table) st = launch_bigram_logits(ctx, model, sr.prev, sr.rows, ctx->logits.ptr, ldw, sr.range);
         if (st != AS_OK) return st;
+        // (the tokens of the step before are read as row_ids: those of this step go to the other half)
+        if (state.table) { int32_t *const half = state.prev; state.prev = state.prev_next; state.prev_next = half; }
+        int32_t *const prev = state.prev;
         StepArgs a{};
         a.logits = ctx->logits.ptr; a.rows = R; a.ld = ldw; a.V = ctx->V; a.dtype = ctx->dtype;
         a.codes = uniforms ? uniforms + (int64_t)t * R : codes; a.temp = temp; a.k = 1.44269504088896340736f / temp; a.thr = nullptr;
@@ -741,28 +803,30 @@ as_status as_decode_fused(as_ctx *ctx, const as_model *model, const int32_t *pro
     const int32_t ngroups = (ctx->V + 31) / 32;
     const int64_t ldp = ((int64_t)ngroups + 15) / 16 * 16;
     DecodeState state;
-    as_status st = decode_state(ctx, model, B, N, T, ldp * (int64_t)sizeof(float2), true, false, state);
+    as_status st = decode_state(ctx, model, B, N, T, ldp * (int64_t)sizeof(float2), true, false, kTableRows, state);
     if (st != AS_OK) return st;
     float *const codes = state.codes;
-    int32_t *const prev = state.prev;
     uint8_t *const fin = state.fin;
     float2 *part = static_cast<float2 *>(ctx->logits.ptr);
 
-    st = launch_lattice(ctx, u, B, N, codes, prompts, prev, fin, ctx->rid);
+    st = launch_lattice(ctx, u, B, N, codes, prompts, state.prev, fin, ctx->rid);
+    if (st == AS_OK && state.table) st = launch_bigram_partials(ctx, model, state.token, ctx->V, temp, part, ldp);
     if (st != AS_OK) return st;
     for (int32_t t = 0; t < T; ++t) {
         StepRows sr;
         st = step_rows(ctx, state, prompts, B, N, t, false, sr);
         if (st != AS_OK) return st;
-        st = launch_bigram_partials(ctx, model, sr.prev, sr.rows, temp, part, ldp, sr.range);
+        if (!state.table) st = launch_bigram_partials(ctx, model, sr.prev, sr.rows, temp, part, ldp, sr.range);
         if (st != AS_OK) return st;
+        const int32_t *const prev = state.prev;
+        if (state.table) { state.prev = state.prev_next; state.prev_next = const_cast<int32_t *>(prev); }
         FusedArgs a{};
         a.part = part; a.row_ids = sr.row_ids; a.ldp = ldp; a.ngroups = ngroups; a.rows = R; a.V = ctx->V; a.d = model->d;
         a.E = static_cast<const uint16_t *>(model->E); a.Ut = static_cast<const uint16_t *>(model->Ut);
         a.alpha = (float)((double)model->scale / sqrt((double)model->d) * 1.44269504088896340736 / (double)temp);
         a.codes = codes; a.codes_out = codes; a.tokens_out = tokens_out + t; a.tok_stride = T;
         a.finished_in = eos_id >= 0 ? fin : nullptr; a.eos_id = eos_id;
-        a.finished_out = eos_id >= 0 ? fin : nullptr; a.prev = prev; a.prev_out = prev;
+        a.finished_out = eos_id >= 0 ? fin : nullptr; a.prev = prev; a.prev_out = state.prev;
         st = launch_fused_sample(ctx, a);
         if (st != AS_OK) return st;
     }

@@ -64,7 +64,7 @@ struct as_ctx {
     int gemm_shape = 0;            // logits: 1 = tile kernel, 2 = persistent also for few rows
     int thr_path = 0;              // truncation: 1 = radix select, 2 = resident where the row fits, 3 = wide for every row
     int gemm_gm = 0;               // logits kernel, many row tiles: workers of an XCD along the rows (tuning knob: 0 = default)
-    int kept_rows = 0;             // decodes: 1 = no logits rows kept from step to step, 2 = wherever there is room for them
+    int kept_rows = 0;             // decodes: 1 = no logits rows kept from step to step, 2 / 3 = kept / a table of all wherever there is room
     int workspace_mib = 0;         // largest buffer of the workspace, in MiB (tuning knob: 0 = as large as the device gives)
     int num_cus = 0;               // compute units of the device (the persistent logits kernel runs one block on each)
     std::string err;
@@ -138,6 +138,7 @@ struct StepArgs {
     const int32_t *row_ids;
     int32_t *prev_out;           // decode state: next step's conditioning token, or null
     const int32_t *order;        // a permutation of the rows that puts those with one logits row together, or null
+    unsigned char *records;      // the truncating one-tile kernels: not a step, but these records of the rows (else null)
 };
 
 struct IntervalArgs {
@@ -213,6 +214,42 @@ struct SelectArgs {              // a sampling step from the sums of rows that c
     int32_t *count;              // rows claimed so far: carried on to the next step, count[1] = count[0]
 };
 
+// What a decode from a table of every token's logits row reads of a row before its logits, kTableRecord apart.
+struct RowRecord {               // sums of step_tile_kernel's chunks (as_tile.hpp)
+    struct {
+        double before, upto;     // the mass before each chunk, and with it, relative to R (beyond fp64: the row's plain form)
+    } chunk[64];
+    float ref[4], R;             // the waves' references, the largest of them
+    float thr;                   // keep threshold
+};
+struct CandRecord {              // the candidates of topk_tile_kernel
+    struct {
+        double before;           // the mass before it in vocabulary order ...
+        float w;                 // ... its own (0: not kept), and its token
+        int32_t token;
+    } cand[64];
+    double S;                    // the mass of all; no number: the row's plain form, with ...
+    float thr;                   // ... this threshold
+};
+static_assert(sizeof(RowRecord) <= kTableRecord && sizeof(CandRecord) <= kTableRecord && kTableRecord % 16 == 0, "records fit");
+
+struct WalkArgs {                // steps t0 .. t1 of a decode from such a table
+    const void *logits;          // [V, ld]
+    const unsigned char *records;
+    int64_t ld;
+    int32_t V;
+    as_dtype dtype;
+    float k;                     // log2(e)/temp
+    int64_t rows;
+    int32_t T, t0, t1, eos_id;
+    const float *uniforms;       // [T, rows] the codes, or null: carried in `codes`
+    float *codes;                // [rows], as are prev and finished: read at t0, written at t1
+    int32_t *prev;
+    uint8_t *finished;
+    int32_t *tokens;             // [rows, T]
+};
+enum TableForm { kTablePlain, kTableNucleus, kTableTopK, kTableRows };    // what a step works from; kTableRows: the logits alone
+
 struct SmallArgs {               // a whole decode of a model that fits LDS
     const void *E, *Ut;          // [V, d] each
     int32_t V, d;
@@ -264,6 +301,7 @@ as_status launch_wide(as_ctx *ctx, const StepArgs &a, int32_t top_k, float top_p
 as_status launch_threshold(as_ctx *ctx, const void *logits, int64_t rows, int64_t ld,
                            const uint8_t *finished_in, const int32_t *row_ids,
                            float temp, int32_t top_k, float top_p, float *thr_out);
+// prev_out: the prompts, clamped to the vocabulary
 as_status launch_lattice(as_ctx *ctx, const float *u, int32_t B, int32_t N, float *codes_out,
                          const int32_t *prompts, int32_t *prev_out, uint8_t *finished_out,
                          int32_t *row_ids_out = nullptr);
@@ -300,6 +338,14 @@ as_status launch_share_map(as_ctx *ctx, const RowShare &s, int32_t step, const i
                            int32_t *row_ids, bool sorted);
 bool keeping_pays(const as_ctx *ctx, const as_model *m, int64_t rows, int32_t T, bool by_sums);
 bool step_by_sums(const as_ctx *ctx, float temp);
+// a table of every token's logits row: whether it pays, its records, the steps from them
+bool table_pays(const as_ctx *ctx, const as_model *m, int64_t rows, int32_t T, TableForm form, bool keep, bool by_sums);
+TableForm table_form(const as_ctx *ctx, int64_t rows, float temp, int32_t top_k, float top_p);
+as_status launch_table_tokens(as_ctx *ctx, int32_t *tokens);
+as_status launch_table_records(as_ctx *ctx, TableForm form, const void *logits, int64_t ld, float temp, int32_t top_k, float top_p,
+                               unsigned char *records);
+as_status launch_row_records(as_ctx *ctx, const void *logits, int64_t ld, float temp, unsigned char *records);
+as_status launch_walk(as_ctx *ctx, TableForm form, const WalkArgs &a);
 as_status launch_row_select(as_ctx *ctx, const SelectArgs &a);
 // the same for the positions of an encode (prev < 0: none): rows claimed, counted and scanned, the order left to the caller
 as_status launch_claim_positions(as_ctx *ctx, const RowShare &s, const int32_t *prev, int64_t rows, int32_t *row_ids);

@@ -16,7 +16,7 @@ namespace {
 // ------------------------------------------------------------------ lattice
 
 __global__ void lattice_kernel(const float *u, int32_t B, int32_t N, float *codes,
-                               const int32_t *prompts, int32_t *prev, uint8_t *finished, int32_t *row_ids)
+                               const int32_t *prompts, int32_t *prev, uint8_t *finished, int32_t *row_ids, int32_t V)
 {
     const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= (int64_t)B * N) return;
@@ -24,7 +24,7 @@ __global__ void lattice_kernel(const float *u, int32_t B, int32_t N, float *code
     // c_i = (i + u)/N: spacing exactly 1/N around the circle, one shift per prompt
     const double c = codes ? ((double)i + (double)u[b]) / (double)N : 0.0;
     if (codes) codes[idx] = fminf((float)c, 0x1.fffffep-1f);
-    if (prev) prev[idx] = prompts[b];
+    if (prev) prev[idx] = clamp_token(prompts[b], V);
     if (finished) finished[idx] = 0;
     if (row_ids) row_ids[idx] = b;           // the first step's logits: one row per prompt
 }
@@ -140,6 +140,13 @@ __global__ __launch_bounds__(256) void share_order_kernel(RowShare s, int64_t ro
 {
     const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (r < rows) s.order[atomicAdd(&s.fill[row_ids[r]], 1)] = (int32_t)r;
+}
+
+// the rows of a table of every token: its tokens
+__global__ __launch_bounds__(256) void table_tokens_kernel(int32_t *tokens, int32_t V)
+{
+    const int32_t i = blockIdx.x * 256 + threadIdx.x;
+    if (i < V) tokens[i] = i;
 }
 
 // ---------------------------------------------------------------- transpose
@@ -934,19 +941,30 @@ __global__ __launch_bounds__(256) void bigram_gemm_thin(const uint16_t *__restri
 // it).  d = 64: 16 x 300 4.1 / 7.2, 8192 x 300 6.0 / 12.8, 1024 x 4000 5.3 / 8.8, 512 x 8000 5.3 / 9.7, 384 x 16000 7.8 / 9.5,
 // 200 x 32128 9.3 / 10.0, 64 x 256000 17.8 / 20.7, and of 160 shapes only 4096 x 2000 (10.2 / 9.6) and 768 x 8000 (9.6 / 9.3)
 // slower.  Operands of 4 GiB, 2^21 tokens, d = 1024: 1 row 711 / 822, 32 792 / 868, 64 988 / 923.
-static int thin_tiles(const as_ctx *ctx, const as_model *m, int64_t rows)
+struct ProductTimes {            // us by these lines
+    double thin[3], persistent;  // MT = 1, 2, 4
+};
+static ProductTimes product_times(const as_ctx *ctx, const as_model *m, int64_t rows)
 {
-    if (ctx->gemm_shape != 0) return 0;
     const double S = (double)m->d / PK, cus = ctx->num_cus > 0 ? ctx->num_cus : 1;
     const int64_t cols = (m->V + TN - 1) / TN;
     auto rounds_of = [&](int mt) { return ceil((double)((rows + 32 * mt - 1) / (32 * mt) * cols) / cus); };
     auto more = [&](int mt) { return rows > 32 * mt ? 0.7 : 0.0; };          // (what TILES costs)
-    const double t1 = 2.6 + rounds_of(1) * (0.4 + 0.22 * S) + more(1), t2 = 0.6 + rounds_of(2) * (1.8 + 0.43 * S) + more(2);
-    const double t4 = 0.5 + rounds_of(4) * (3.0 + 0.63 * S) + more(4);
+    ProductTimes t;
+    t.thin[0] = 2.6 + rounds_of(1) * (0.4 + 0.22 * S) + more(1);
+    t.thin[1] = 0.6 + rounds_of(2) * (1.8 + 0.43 * S) + more(2);
+    t.thin[2] = 0.5 + rounds_of(4) * (3.0 + 0.63 * S) + more(4);
     const double tiles = (double)((rows + PM - 1) / PM * (((int64_t)m->V + PN - 1) / PN)), rounds = ceil(tiles / cus);
-    const double persistent = 5.2 + rounds * (1.05 * S + 2.5 * (tiles < cus ? tiles / cus : 1.0));
+    t.persistent = 5.2 + rounds * (1.05 * S + 2.5 * (tiles < cus ? tiles / cus : 1.0));
+    return t;
+}
+static int thin_tiles(const as_ctx *ctx, const as_model *m, int64_t rows)
+{
+    if (ctx->gemm_shape != 0) return 0;
+    const ProductTimes t = product_times(ctx, m, rows);
+    const double t1 = t.thin[0], t2 = t.thin[1], t4 = t.thin[2];
     const double best = t1 < t2 ? (t1 < t4 ? t1 : t4) : (t2 < t4 ? t2 : t4);
-    if (best > 0.95 * persistent || rows > 0x7fffffff - 256) return 0;
+    if (best > 0.95 * t.persistent || rows > 0x7fffffff - 256) return 0;
     return best == t1 ? 1 : best == t2 ? 2 : 4;
 }
 
@@ -1181,7 +1199,7 @@ as_status launch_lattice(as_ctx *ctx, const float *u, int32_t B, int32_t N, floa
     const int64_t n = (int64_t)B * N;
     if (n == 0) return AS_OK;
     hipLaunchKernelGGL(lattice_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, ctx->stream, u, B, N,
-                       codes_out, prompts, prev_out, finished_out, row_ids_out);
+                       codes_out, prompts, prev_out, finished_out, row_ids_out, ctx->V);
     AS_HIP_TRY(ctx, hipGetLastError());
     return AS_OK;
 }
@@ -1279,7 +1297,7 @@ bool sharing_pays(const as_ctx *ctx, const as_model *m, int64_t rows, int32_t T)
 // (How large its table may be: kept_rows_most.)
 bool keeping_pays(const as_ctx *ctx, const as_model *m, int64_t rows, int32_t T, bool by_sums)
 {
-    if (T < 3 || !rows_on_device(ctx, m) || ctx->kept_rows == 1) return false;
+    if (T < 3 || !rows_on_device(ctx, m) || ctx->kept_rows == 1 || ctx->kept_rows == 3) return false;
     if (ctx->kept_rows == 2) return true;
     const double V = (double)m->V, R = (double)rows;
     const double steps = T - 1;
@@ -1292,6 +1310,48 @@ bool keeping_pays(const as_ctx *ctx, const as_model *m, int64_t rows, int32_t T,
     }
     const double meeting = 6.0 * V / (R * steps);
     return spared > 4e-6 + 18e-6 * (meeting < 1.0 ? meeting : 1.0);
+}
+
+// What a product of `rows` rows takes, in us
+static double product_us(const as_ctx *ctx, const as_model *m, double rows)
+{
+    if (!mfma_applies(m)) return 3.5 + 2.0 * rows * (double)m->V * (double)m->d / 1e8;
+    const ProductTimes t = product_times(ctx, m, (int64_t)rows + 1);
+    const double thin = t.thin[0] < t.thin[1] ? (t.thin[0] < t.thin[2] ? t.thin[0] : t.thin[2])
+                                              : (t.thin[1] < t.thin[2] ? t.thin[1] : t.thin[2]);
+    // (the line for small products is low where every compute unit has several tiles)
+    const double tiles = ceil(rows / PM) * (double)(((int64_t)m->V + PN - 1) / PN), cus = ctx->num_cus > 0 ? ctx->num_cus : 1;
+    const double large = tiles > cus ? 4.0 + ceil(tiles / cus) * (1.72 * (double)m->d / PK + 2.3) : t.persistent;
+    return (thin < large ? thin : large) + (ctx->dtype == AS_BF16 ? 0.0 : rows * (double)m->V * 2.0 / 5e6);
+}
+
+// Whether a decode makes the logits rows of all tokens first, against a row per code, token in use or new token (`keep`) in
+// each step.  Then it has one large product, one pass over its rows, and steps of 2 us (1 from candidates; 0.5 ns a code where
+// those are many) that share a launch; where the steps' kernels have to read the rows (kTableRows) it spares the products alone.
+// us a decode, every step its own rows / kept / table: 1024 codes x 64 of 32128 x 512 3124 / - / 1486, 16 x 64 638 / - / 1550;
+// k = 40, 1024 x 128 6548 / - / 1504; 65536 x 16 20260 / 2465 / 1808; 3605 x 126 of 1600 x 1024 5281 / 2052 / 267; 406 x 59 of
+// 504 x 128 538 / - / 77; 270 x 117 of 3424 x 832 1401 / - / 193; 1 x 73 of 657 x 19 fp32, k = 100 1056 / - / 838 (rows); 2004 x
+// 49 of 9640 x 768, k = 100 4178 / - / 2265 (rows); against the table: 5579 x 5 of 14277 x 192, fp32 logits 567 / 491 / 535, 12 x
+// 115 of 18904 x 896, fp32 (rows) 1431 / - / 1695.  With tokens that come less evenly than assumed a kept table fills less:
+// it has to be worse by 15 %.
+bool table_pays(const as_ctx *ctx, const as_model *m, int64_t rows, int32_t T, TableForm form, bool keep, bool by_sums)
+{
+    if (ctx->kept_rows != 0) return ctx->kept_rows == 3;
+    const double V = (double)m->V, R = (double)rows, row_us = V * (ctx->dtype == AS_BF16 ? 2.0 : 4.0) / 6e6;
+    const double kept = V * (1.0 - exp(-R * (T - 1) / V)) / (T - 1);
+    const double own = keep ? kept : sharing_pays(ctx, m, rows, T) ? V * (1.0 - exp(-R / V)) : R;      // rows a step
+    const double sampling = 3.5 + R * row_us;
+    const double without = product_us(ctx, m, own) + (keep ? 12.0 : 0.0) + (keep && by_sums ? 4.0 + R * 0.0007 + own * row_us : sampling);
+    const double step = form == kTableRows ? sampling : 3.0 + R * 0.0006;
+    const double table = product_us(ctx, m, V) + (form == kTableRows ? 0.0 : 4.0 + V * row_us);
+    return table + T * step < (keep ? 0.85 : 0.95) * T * without;
+}
+
+as_status launch_table_tokens(as_ctx *ctx, int32_t *tokens)
+{
+    hipLaunchKernelGGL(table_tokens_kernel, dim3((unsigned)((ctx->V + 255) / 256)), dim3(256), 0, ctx->stream, tokens, ctx->V);
+    AS_HIP_TRY(ctx, hipGetLastError());
+    return AS_OK;
 }
 
 as_status launch_share_clear(as_ctx *ctx, const RowShare &s, int32_t T)

@@ -144,5 +144,61 @@ __device__ __forceinline__ void generic_step_row(const StepArgs &a, int64_t r, f
     write_row(a, r, o);
 }
 
+// generic_step_row by one wave, the same arithmetic in the same order (lane l stands for threads l, l + 64, ...): the token
+// and the rescaled code, in every lane.  tot: 256 numbers of the wave's own in LDS.
+template <class T>
+__device__ __forceinline__ int32_t generic_pick_row(const T *row, int32_t V, float k, float thr, float code, double *tot,
+                                                    float &c_next)
+{
+    const int lane = threadIdx.x & 63;
+    const int32_t len = (V + 255) / 256;
+    float m = -__builtin_inff();
+    for (int i = lane; i < 256; i += 64) {
+        const int32_t lo = i * len, hi = (lo + len < V) ? lo + len : V;
+        for (int32_t v = lo; v < hi; ++v) {
+            const float x = widen_stored(row[v]);
+            if (x >= thr) m = fmaxf(m, x);
+        }
+    }
+    const float ref = fmaxf(ceilf(wave_max(m) * k), kRefFloor);
+    for (int i = lane; i < 256; i += 64) {
+        const int32_t lo = i * len, hi = (lo + len < V) ? lo + len : V;
+        double t = 0.0;
+        for (int32_t v = lo; v < hi; ++v) {
+            const float x = widen_stored(row[v]);
+            if (x >= thr) t += (double)fast_exp2(fmaf(x, k, -ref));
+        }
+        tot[i] = t;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    double S = 0.0;
+    for (int i = 0; i < 256; ++i) S += tot[i];
+    const double tau = (double)code * S;
+    double run = 0.0, run_last = 0.0;
+    int hit = -1, last_nz = 0;
+    for (int i = 0; i < 256; ++i) {
+        if (tot[i] > 0.0) { last_nz = i; run_last = run; }
+        if (run + tot[i] > tau) { hit = i; break; }
+        run += tot[i];
+    }
+    if (hit < 0) { hit = last_nz; run = run_last; }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const int32_t lo = hit * len, hi = (lo + len < V) ? lo + len : V;
+    double acc = run, before = run, before_last = run, ev = 0.0, ev_last = 0.0;
+    int32_t tok = -1, tok_last = lo < V ? lo : V - 1;
+    for (int32_t v = lo; v < hi; ++v) {
+        const float x = widen_stored(row[v]);
+        const double e = (x >= thr) ? (double)fast_exp2(fmaf(x, k, -ref)) : 0.0;
+        if (e > 0.0) { tok_last = v; before_last = acc; ev_last = e; }
+        if (tok < 0 && acc + e > tau) { tok = v; before = acc; ev = e; }
+        acc += e;
+    }
+    if (tok < 0) { tok = tok_last; before = before_last; ev = ev_last; }
+    c_next = rescale_code(tau, before, ev);
+    return tok;
+}
+
 }  // namespace as
 #endif

@@ -128,6 +128,159 @@ __global__ __launch_bounds__(256) void row_select_kernel(SelectArgs q)
     }
 }
 
+// The same sums as a RowRecord: what a decode from a table of every token's logits row needs of a row, a block per row.
+template <int DT, bool NT>
+__global__ __launch_bounds__(256, 4) void row_records_kernel(const void *logits, int64_t ld, int32_t V, float k,
+                                                             unsigned char *records)
+{
+    using T = typename Elem<DT>::T;
+    constexpr int EPV = Elem<DT>::kPerVec;
+    constexpr int ITERS = kTileIters;
+    constexpr int kShare = ITERS * 64;
+    __shared__ TileSums ts;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t r = blockIdx.x;
+    const int32_t nvec = V / EPV, v0 = wave * kShare;
+    f32x4 *const my_sums = reinterpret_cast<f32x4 *>(ts.chunk_sum + wave * ITERS);
+    if (v0 >= nvec) {                                            // past the row's end
+        if (lane < ITERS / 4) my_sums[lane] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (lane == 0) ts.share_ref[wave] = kRefFloor;
+    } else {
+        const unsigned char *const base =
+            reinterpret_cast<const unsigned char *>(reinterpret_cast<const T *>(logits) + r * ld) + (size_t)v0 * 16u;
+        int32_t mych = (nvec - v0 - lane + 63) >> 6;
+        mych = mych < 0 ? 0 : (mych > ITERS ? ITERS : mych);
+        const uint32_t off0 = (uint32_t)lane * 16u;
+        const uint32_t off_last = mych > 0 ? off0 + (uint32_t)(mych - 1) * 1024u : 0u;
+        u32x4 raw[ITERS];
+#pragma unroll
+        for (int j = 0; j < ITERS; ++j) {
+            uint32_t off = off0 + (uint32_t)j * 1024u;
+            off = off < off_last ? off : off_last;
+            if constexpr (NT) raw[j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(base + off));
+            else raw[j] = *reinterpret_cast<const u32x4 *>(base + off);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        float rw;
+        if (v0 + kShare <= nvec) {
+            rw = tile_reference<DT, false, false>(raw[0], k, 0.f, mych);
+            tile_chunk_sums<DT, false, false>(raw, k, rw, 0.f, mych, lane, my_sums);
+        } else {
+            rw = tile_reference<DT, false, true>(raw[0], k, 0.f, mych);
+            tile_chunk_sums<DT, false, true>(raw, k, rw, 0.f, mych, lane, my_sums);
+        }
+        if (lane == 0) ts.share_ref[wave] = rw;
+    }
+    __syncthreads();
+    if (wave == 0) write_row_record(ts, -__builtin_inff(), reinterpret_cast<RowRecord *>(records + r * kTableRecord), lane);
+}
+
+// Steps t0 .. t1 of a decode from a table of every token's logits row, a wave per code through all of them: no row waits
+// for another, so there is nothing between a code's steps but its own chain of loads.  A step reads the record of the
+// token before (and, for a plain or nucleus step, the KiB of logits that holds the code) and gives what step_tile_kernel,
+// nucleus_tile_kernel or topk_tile_kernel would, bit for bit.
+template <int DT, TableForm FORM>
+__global__ __launch_bounds__(256) void walk_kernel(WalkArgs a)
+{
+    using T = typename Elem<DT>::T;
+    constexpr int EPV = Elem<DT>::kPerVec, ITERS = kTileIters;
+    constexpr bool HAS_THR = FORM == kTableNucleus;
+    __shared__ double tot[4][256];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t r = (int64_t)blockIdx.x * 4 + wave;
+    if (r >= a.rows) return;
+    const int32_t nvec = a.V / EPV;
+    const float k = a.k;
+    int32_t tok = __builtin_amdgcn_readfirstlane(clamp_token(a.prev[r], a.V));
+    float code = a.uniforms ? 0.f : a.codes[r];
+    bool ended = a.eos_id >= 0 && __builtin_amdgcn_readfirstlane((int)a.finished[r]) != 0;
+    const float *const uniforms = a.uniforms ? a.uniforms + r : nullptr;
+    float u_next = uniforms ? uniforms[(int64_t)a.t0 * a.rows] : 0.f;
+    int32_t held = 0;                                            // the tokens of up to 64 steps, a lane each
+    for (int32_t t = a.t0; t < a.t1; ++t) {
+        if (uniforms) {
+            code = u_next;
+            u_next = uniforms[(int64_t)(t + 1 < a.t1 ? t + 1 : t) * a.rows];
+        }
+        if (ended) {
+            tok = a.eos_id;
+        } else {
+            const unsigned char *const at = a.records + (int64_t)tok * kTableRecord;
+            const T *const row = reinterpret_cast<const T *>(a.logits) + (int64_t)tok * a.ld;
+            if constexpr (FORM == kTableTopK) {
+                const CandRecord *const rec = reinterpret_cast<const CandRecord *>(at);
+                const double S = rec->S, before = rec->cand[lane].before;
+                const float w = rec->cand[lane].w;
+                const int32_t mine = rec->cand[lane].token;
+                if (!(S < (double)__builtin_inff())) {
+                    float c_next;
+                    tok = generic_pick_row<T>(row, a.V, k, rec->thr, code, tot[wave], c_next);
+                    code = c_next;
+                } else {
+                    const double tau = (double)code * S;
+                    const bool has_weight = w > 0.f;
+                    unsigned long long sel = __ballot(has_weight && before <= tau && tau < before + (double)w);
+                    if (sel == 0ull) {
+                        // the code at the very top by rounding: the last kept token of the vocabulary
+                        int32_t best = has_weight ? mine : -1;
+#pragma unroll
+                        for (int d = 32; d >= 1; d >>= 1) {
+                            const int32_t o = __shfl_xor(best, d, 64);
+                            best = o > best ? o : best;
+                        }
+                        sel = __ballot(has_weight && mine == best);
+                    }
+                    const int l = sel ? (int)__builtin_ctzll(sel) : 0;
+                    code = sel ? read_lane(rescale_code(tau, before, (double)w), l) : 0.f;
+                    tok = sel ? __builtin_amdgcn_readlane(mine, l) : 0;
+                }
+            } else {
+                const RowRecord *const rec = reinterpret_cast<const RowRecord *>(at);
+                const double before = rec->chunk[lane].before, upto = rec->chunk[lane].upto;
+                // (ref[0..3], R, thr)
+                const float meta = reinterpret_cast<const float *>(rec->ref)[lane < 6 ? lane : 5];
+                const double S = read_lane(upto, 63);
+                const float thr = HAS_THR ? read_lane(meta, 5) : -__builtin_inff();
+                if (!(S < (double)__builtin_inff())) {
+                    float c_next;
+                    tok = generic_pick_row<T>(row, a.V, k, thr, code, tot[wave], c_next);
+                    code = c_next;
+                } else {
+                    const double tau = (double)code * S;
+                    const unsigned long long chit = __ballot(upto > tau);
+                    const unsigned long long cnz = __ballot(upto > before);
+                    const int ch = chit ? (__ffsll((long long)chit) - 1) : (cnz ? (63 - __clzll((long long)cnz)) : 0);
+                    const double run = read_lane(before, ch);
+                    const float rw = read_lane(meta, ch / ITERS), R = read_lane(meta, 4);
+                    const bool inside = ch * 64 + lane < nvec;
+                    const u32x4 hv = reinterpret_cast<const u32x4 *>(row)[inside ? ch * 64 + lane : 0];
+                    float cl = tile_lane_sum<DT, HAS_THR>(hv, k, -rw, thr);
+                    cl = inside ? cl : 0.f;
+                    const int shf = shift_of(rw, R);
+                    double acc, start, ev;
+                    const int l = tile_lane(cl, shf, tau, run, acc);
+                    const int ih = tile_element<DT, HAS_THR>(hv, k, thr, rw, shf, tau, acc, start, ev);
+                    code = read_lane(rescale_code(tau, start, ev), l);
+                    tok = (ch * 64 + l) * EPV + __builtin_amdgcn_readlane(ih, l);
+                    tok = tok > a.V - 1 ? a.V - 1 : tok;
+                }
+            }
+            tok = __builtin_amdgcn_readfirstlane(tok);
+            ended = a.eos_id >= 0 && tok == a.eos_id;
+        }
+        const int at = (t - a.t0) & 63;
+        held = lane == at ? tok : held;
+        if ((at == 63 || t + 1 == a.t1) && lane <= at) a.tokens[r * a.T + t - at + lane] = held;
+    }
+    if (lane == 0) {
+        if (!uniforms) a.codes[r] = code;
+        a.prev[r] = tok;
+        if (a.eos_id >= 0) a.finished[r] = ended ? 1 : 0;
+    }
+}
+
 }  // namespace
 
 static_assert(kRowSums == kTileWaves * kTileIters + kTileWaves, "the chunk sums and the waves' references");
@@ -158,6 +311,29 @@ bool step_by_sums(const as_ctx *ctx, float temp)
 {
     return one_tile_row(ctx->V, ctx->dtype == AS_BF16 ? 2 : 4) && ctx->step_shape == 0 &&
            1.44269504088896340736f / temp <= kTileMaxScale;
+}
+
+as_status launch_row_records(as_ctx *ctx, const void *logits, int64_t ld, float temp, unsigned char *records)
+{
+    const float k = 1.44269504088896340736f / temp;
+    const dim3 grid((unsigned)ctx->V), block(256);
+    const bool nt = stream_rows(ctx->V, ld, ctx->dtype == AS_BF16 ? 2 : 4);
+    auto go = [&](auto kernel) { launch(ctx, kKernelThreshold, kernel, grid, block, 0, logits, ld, ctx->V, k, records); };
+    if (ctx->dtype == AS_BF16) nt ? go(row_records_kernel<AS_BF16, true>) : go(row_records_kernel<AS_BF16, false>);
+    else nt ? go(row_records_kernel<AS_F32, true>) : go(row_records_kernel<AS_F32, false>);
+    AS_HIP_TRY(ctx, hipGetLastError());
+    return AS_OK;
+}
+
+as_status launch_walk(as_ctx *ctx, TableForm form, const WalkArgs &a)
+{
+    const dim3 grid((unsigned)((a.rows + 3) / 4)), block(256);
+    if (form == kTableTopK) launch(ctx, kKernelStep, walk_kernel<AS_BF16, kTableTopK>, grid, block, 0, a);
+    else if (form == kTableNucleus) launch(ctx, kKernelStep, walk_kernel<AS_BF16, kTableNucleus>, grid, block, 0, a);
+    else if (a.dtype == AS_BF16) launch(ctx, kKernelStep, walk_kernel<AS_BF16, kTablePlain>, grid, block, 0, a);
+    else launch(ctx, kKernelStep, walk_kernel<AS_F32, kTablePlain>, grid, block, 0, a);
+    AS_HIP_TRY(ctx, hipGetLastError());
+    return AS_OK;
 }
 
 as_status launch_row_select(as_ctx *ctx, const SelectArgs &a)

@@ -1285,7 +1285,8 @@ struct TileTopK {
     __attribute__((aligned(16))) double cw[kTileCand];
 };
 
-template <bool HAS_P, bool NT>
+// TABLE: no step, but the candidates of row r as steps to come need them (a.records)
+template <bool HAS_P, bool NT, bool TABLE = false>
 __global__ __launch_bounds__(kThreads, 4) void topk_tile_kernel(StepArgs a, int32_t top_k, float top_p)
 {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -1307,13 +1308,14 @@ __global__ __launch_bounds__(kThreads, 4) void topk_tile_kernel(StepArgs a, int3
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
     uint32_t fin_word = 0u, fin_at = 0u;
-    if (a.finished_in != nullptr) {
+    if (!TABLE && a.finished_in != nullptr) {
         const uint8_t *q = a.finished_in + r;
         fin_at = (uint32_t)(reinterpret_cast<uintptr_t>(q) & 3u);
         fin_word = *reinterpret_cast<const uint32_t *>(q - fin_at);
     }
-    const float code = a.codes[r];
-    const int64_t src = a.row_ids ? (int64_t)a.row_ids[r] : r;
+    const float code = TABLE ? 0.f : a.codes[r];
+    CandRecord *const rec = TABLE ? reinterpret_cast<CandRecord *>(a.records + r * kTableRecord) : nullptr;
+    const int64_t src = !TABLE && a.row_ids ? (int64_t)a.row_ids[r] : r;
     const uint16_t *row = reinterpret_cast<const uint16_t *>(a.logits) + src * a.ld;
     const unsigned char *rowb = reinterpret_cast<const unsigned char *>(row);
     const int32_t V = a.V;
@@ -1471,7 +1473,14 @@ __global__ __launch_bounds__(kThreads, 4) void topk_tile_kernel(StepArgs a, int3
         __syncthreads();                   // the tables give way to the general path's scratch
         const uint32_t thr_key = radix_threshold<AS_BF16>(sc.radix, row, V, a.temp, top_k, HAS_P ? top_p : 1.f);
         __syncthreads();
-        generic_step_row<uint16_t>(a, r, Key<AS_BF16>::from_key(thr_key), sc.gen);
+        if constexpr (TABLE) {
+            if (threadIdx.x == 0) {
+                rec->S = __builtin_nan("");
+                rec->thr = Key<AS_BF16>::from_key(thr_key);
+            }
+        } else {
+            generic_step_row<uint16_t>(a, r, Key<AS_BF16>::from_key(thr_key), sc.gen);
+        }
         return;
     }
     if (wave != 0) return;
@@ -1556,6 +1565,16 @@ __global__ __launch_bounds__(kThreads, 4) void topk_tile_kernel(StepArgs a, int3
     by_index(0, kMostGroups);
     if (ncand > 4 * kMostGroups) by_index(kMostGroups, kTileCand / 4);
     const double bef = before[0] + before[1];
+    if constexpr (TABLE) {
+        rec->cand[lane].before = bef;
+        rec->cand[lane].w = w;
+        rec->cand[lane].token = idx;
+        if (lane == 0) {
+            rec->S = S;
+            rec->thr = -__builtin_inff();
+        }
+        return;
+    }
     const double tau = (double)code * S;
     const bool has_weight = kept && w > 0.f;
     unsigned long long sel = __ballot(has_weight && bef <= tau && tau < bef + (double)w);
@@ -1636,7 +1655,8 @@ __device__ __forceinline__ uint32_t pk_sub_u16(uint32_t a, uint32_t b)
     return __builtin_bit_cast(uint32_t, (u16x2)(__builtin_bit_cast(u16x2, a) - __builtin_bit_cast(u16x2, b)));
 }
 
-template <bool NT>
+// TABLE: no step, but the sums of row r's nucleus as steps to come need them (a.records)
+template <bool NT, bool TABLE = false>
 __global__ __launch_bounds__(kThreads, 4) void nucleus_tile_kernel(StepArgs a, float top_p)
 {
     constexpr int DT = AS_BF16;
@@ -1655,13 +1675,14 @@ __global__ __launch_bounds__(kThreads, 4) void nucleus_tile_kernel(StepArgs a, f
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
     uint32_t fin_word = 0u, fin_at = 0u;
-    if (a.finished_in != nullptr) {
+    if (!TABLE && a.finished_in != nullptr) {
         const uint8_t *q = a.finished_in + r;
         fin_at = (uint32_t)(reinterpret_cast<uintptr_t>(q) & 3u);
         fin_word = *reinterpret_cast<const uint32_t *>(q - fin_at);
     }
-    const float code = a.codes[r];
-    const int64_t src = a.row_ids ? (int64_t)a.row_ids[r] : r;
+    const float code = TABLE ? 0.f : a.codes[r];
+    RowRecord *const rec = TABLE ? reinterpret_cast<RowRecord *>(a.records + r * kTableRecord) : nullptr;
+    const int64_t src = !TABLE && a.row_ids ? (int64_t)a.row_ids[r] : r;
     const uint16_t *row = reinterpret_cast<const uint16_t *>(a.logits) + src * a.ld;
     const unsigned char *rowb = reinterpret_cast<const unsigned char *>(row);
     const int32_t V = a.V;
@@ -1855,7 +1876,12 @@ __global__ __launch_bounds__(kThreads, 4) void nucleus_tile_kernel(StepArgs a, f
         __syncthreads();
         const uint32_t thr_key = radix_threshold<AS_BF16>(sc.radix, row, V, a.temp, 0, top_p);
         __syncthreads();
-        generic_step_row<uint16_t>(a, r, Key<AS_BF16>::from_key(thr_key), sc.gen);
+        if constexpr (TABLE) {
+            if (threadIdx.x < 64) rec->chunk[threadIdx.x].upto = __builtin_nan("");
+            if (threadIdx.x == 0) rec->thr = Key<AS_BF16>::from_key(thr_key);
+        } else {
+            generic_step_row<uint16_t>(a, r, Key<AS_BF16>::from_key(thr_key), sc.gen);
+        }
         return;
     }
     const float thr = bits_f32((((C + (uint32_t)pick) ^ X) & 0xffffu) << 16);
@@ -1906,6 +1932,10 @@ __global__ __launch_bounds__(kThreads, 4) void nucleus_tile_kernel(StepArgs a, f
         }
     }
     __syncthreads();
+    if constexpr (TABLE) {
+        if (wave == 0) write_row_record(tn.sums, thr, rec, lane);
+        return;
+    }
     tile_select<DT, true>(a, r, code, thr, raw, R, mych, ragged, v0, lane, wave, tn.sums, sc.gen);
 }
 
@@ -2015,6 +2045,49 @@ static bool threshold_streamed_pays(const as_ctx *ctx, int64_t rows, bool has_k,
     return ctx->V <= (half ? 12288 : 10240) || (half && lots && ctx->V <= 36864);
 }
 
+// Whether a truncated step of `rows` rows takes a one-tile kernel, where its logits allow one
+// (the nucleus: 8000 rows of 8200 127 us against 106 in the wide kernel, of 11000 128 / 116, of 12800 even; 2000 even)
+static bool by_tile(const as_ctx *ctx, int64_t rows, float k, bool has_k, int32_t top_k)
+{
+    const int64_t cus = ctx->num_cus;
+    if (ctx->thr_path != 0 || ctx->dtype != AS_BF16 || ctx->V % 8 != 0 || ctx->V > 32768) return false;
+    return has_k ? topk_tile_pays(ctx, rows, top_k)
+                 : k <= kTileMaxScale && !((ctx->V <= 8192 && rows > 2 * cus) || (ctx->V <= 12288 && rows > 16 * cus));
+}
+
+// What the steps of a decode from a table of logits rows work from: the form that gives the results of the kernel that
+// as_step_ex takes for `rows` rows.
+TableForm table_form(const as_ctx *ctx, int64_t rows, float temp, int32_t top_k, float top_p)
+{
+    const bool has_k = top_k > 0 && top_k < ctx->V, has_p = top_p > 0.f && top_p < 1.f;
+    if (!has_k && !has_p) return step_by_sums(ctx, temp) ? kTablePlain : kTableRows;
+    if (!by_tile(ctx, rows, 1.44269504088896340736f / temp, has_k, top_k)) return kTableRows;
+    return has_k ? kTableTopK : kTableNucleus;
+}
+
+as_status launch_table_records(as_ctx *ctx, TableForm form, const void *logits, int64_t ld, float temp, int32_t top_k, float top_p,
+                               unsigned char *records)
+{
+    if (form == kTablePlain) return launch_row_records(ctx, logits, ld, temp, records);
+    StepArgs a{};
+    a.logits = logits; a.rows = ctx->V; a.ld = ld; a.V = ctx->V; a.dtype = ctx->dtype; a.temp = temp;
+    a.k = 1.44269504088896340736f / temp; a.records = records;
+    const dim3 grid((unsigned)ctx->V), block(kThreads);
+    const bool nt = stream_rows(a.rows, ld, 2), has_p = top_p > 0.f && top_p < 1.f;
+    if (form == kTableNucleus) {
+        if (nt) launch(ctx, kKernelThreshold, nucleus_tile_kernel<true, true>, grid, block, 0, a, top_p);
+        else launch(ctx, kKernelThreshold, nucleus_tile_kernel<false, true>, grid, block, 0, a, top_p);
+    } else if (has_p) {
+        if (nt) launch(ctx, kKernelThreshold, topk_tile_kernel<true, true, true>, grid, block, 0, a, top_k, top_p);
+        else launch(ctx, kKernelThreshold, topk_tile_kernel<true, false, true>, grid, block, 0, a, top_k, top_p);
+    } else {
+        if (nt) launch(ctx, kKernelThreshold, topk_tile_kernel<false, true, true>, grid, block, 0, a, top_k, top_p);
+        else launch(ctx, kKernelThreshold, topk_tile_kernel<false, false, true>, grid, block, 0, a, top_k, top_p);
+    }
+    AS_HIP_TRY(ctx, hipGetLastError());
+    return AS_OK;
+}
+
 // top-k and the nucleus and the sampling step in one launch; false where only the radix select and the resident
 // fp32 nucleus are left (then the caller runs the threshold kernel and the step kernel one after the other)
 bool launch_topk_step(as_ctx *ctx, const StepArgs &args, int32_t top_k, float top_p, as_status *st)
@@ -2024,14 +2097,8 @@ bool launch_topk_step(as_ctx *ctx, const StepArgs &args, int32_t top_k, float to
     const bool nt = stream_rows(a.src_rows ? a.src_rows : a.rows, a.ld, esz);
     const bool has_k = top_k > 0 && top_k < ctx->V, has_p = top_p > 0.f && top_p < 1.f;
     const bool nucleus_only = !has_k && has_p && ctx->dtype == AS_BF16;
-    const bool one_tile = ctx->dtype == AS_BF16 && ctx->V % 8 == 0 && ctx->V <= 32768 &&
-                          reinterpret_cast<uintptr_t>(a.logits) % 16 == 0 && (a.ld * esz) % 16 == 0;
-    // (the nucleus: 8000 rows of 8200 127 us against 106 in the wide kernel, of 11000 128 / 116, of 12800 even; 2000 even)
-    const int64_t cus = ctx->num_cus;
-    const bool by_tile = has_k ? topk_tile_pays(ctx, a.rows, top_k)
-                               : a.k <= kTileMaxScale && !((ctx->V <= 8192 && a.rows > 2 * cus) ||
-                                                           (ctx->V <= 12288 && a.rows > 16 * cus));
-    const bool tile = ctx->thr_path == 0 && one_tile && by_tile;
+    const bool tile = reinterpret_cast<uintptr_t>(a.logits) % 16 == 0 && (a.ld * esz) % 16 == 0 &&
+                      by_tile(ctx, a.rows, a.k, has_k, top_k);
     if (ctx->thr_path == 3 ||
         (ctx->thr_path == 0 && !tile && !resident_pays(ctx, a.logits, a.rows, a.ld, has_k, top_k) &&
          !streamed_pays(ctx, a.rows, has_k, top_k))) {

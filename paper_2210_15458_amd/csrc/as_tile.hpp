@@ -179,33 +179,37 @@ __device__ __forceinline__ void tile_chunk_sums(const u32x4 (&raw)[N], float k, 
     }
 }
 
-// The wave that holds the code's chunk: hv its lanes' vectors of the chunk (vector vec0 + lane of the row), cl their sums
-// (0 past the row's end), both relative to rw; run the mass before the chunk.  Finds the lane, that lane the element, and
-// writes the row's results.
-template <int DT, bool HAS_THR>
-__device__ __forceinline__ void tile_finish(const StepArgs &a, int64_t r, float thr, const u32x4 &hv, float cl, float rw,
-                                            int shf, double tau, double run, double S, int32_t vec0, int lane)
+// The lane that holds the code in its chunk, and the mass before each lane: cl the lanes' sums (0 past the row's end), shf
+// what brings them to the row's reference, run the mass before the chunk.
+__device__ __forceinline__ int tile_lane(float cl, int shf, double tau, double run, double &before)
 {
-    constexpr int EPV = Elem<DT>::kPerVec;
     const double lv = (double)ldexpf(cl, shf);
     const double incl2 = wave_scan_add(lv) + run;
+    before = incl2 - lv;
     const unsigned long long hit2 = __ballot(incl2 > tau);
     const unsigned long long nz2 = __ballot(lv > 0.0);
-    const int l2 = hit2 ? (__ffsll((long long)hit2) - 1) : (nz2 ? (63 - __clzll((long long)nz2)) : 0);
-    if (lane != l2) return;
+    return hit2 ? (__ffsll((long long)hit2) - 1) : (nz2 ? (63 - __clzll((long long)nz2)) : 0);
+}
 
+// The element of a lane's vector that holds the code, acc the mass before the vector.
+template <int DT, bool HAS_THR>
+__device__ __forceinline__ int tile_element(const u32x4 &hv, float k, float thr, float rw, int shf, double tau, double acc,
+                                            double &before, double &ev)
+{
+    constexpr int EPV = Elem<DT>::kPerVec;
     float x[EPV];
     unpack<DT>(hv, x);
     double ed[EPV];
 #pragma unroll
     for (int i = 0; i < EPV; ++i) {
-        float e = fast_exp2(fmaf(x[i], a.k, -rw));
+        float e = fast_exp2(fmaf(x[i], k, -rw));
         if constexpr (HAS_THR) e = (x[i] >= thr) ? e : 0.f;
         ed[i] = (double)ldexpf(e, shf);
     }
-    double acc = incl2 - lv;
     int ih = -1, ilast = 0;
-    double before = acc, before_last = acc, ev = 0.0, ev_last = 0.0;
+    double before_last = acc, ev_last = 0.0;
+    before = acc;
+    ev = 0.0;
 #pragma unroll
     for (int i = 0; i < EPV; ++i) {
         if (ed[i] > 0.0) { ilast = i; before_last = acc; ev_last = ed[i]; }
@@ -213,8 +217,21 @@ __device__ __forceinline__ void tile_finish(const StepArgs &a, int64_t r, float 
         acc += ed[i];
     }
     if (ih < 0) { ih = ilast; before = before_last; ev = ev_last; }
+    return ih;
+}
 
-    int64_t tok64 = ((int64_t)vec0 + lane) * EPV + ih;
+// The wave that holds the code's chunk: hv its lanes' vectors of the chunk (vector vec0 + lane of the row), cl their sums
+// (0 past the row's end), both relative to rw; run the mass before the chunk.  Finds the lane, that lane the element, and
+// writes the row's results.
+template <int DT, bool HAS_THR>
+__device__ __forceinline__ void tile_finish(const StepArgs &a, int64_t r, float thr, const u32x4 &hv, float cl, float rw,
+                                            int shf, double tau, double run, double S, int32_t vec0, int lane)
+{
+    double acc, before, ev;
+    if (lane != tile_lane(cl, shf, tau, run, acc)) return;
+    const int ih = tile_element<DT, HAS_THR>(hv, a.k, thr, rw, shf, tau, acc, before, ev);
+
+    int64_t tok64 = ((int64_t)vec0 + lane) * Elem<DT>::kPerVec + ih;
     if (tok64 > a.V - 1) tok64 = a.V - 1;
     RowOut o;
     o.token = (int32_t)tok64;
@@ -227,6 +244,22 @@ __device__ __forceinline__ void tile_finish(const StepArgs &a, int64_t r, float 
         o.f_lo = (float)before / Sf;
     }
     write_row(a, r, o);
+}
+
+// The record of a row whose chunk sums are in LDS: what tile_select makes of them, for steps to come (one wave).
+__device__ __forceinline__ void write_row_record(const TileSums &ts, float thr, RowRecord *rec, int lane)
+{
+    constexpr int NW = kTileWaves, ITERS = kTileIters;
+    float R = ts.share_ref[0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) R = fmaxf(R, ts.share_ref[w]);
+    const double cv = (double)ldexpf(ts.chunk_sum[lane], shift_of(ts.share_ref[lane / ITERS], R));
+    const double cincl = wave_scan_add(cv);
+    rec->chunk[lane].before = cincl - cv;
+    rec->chunk[lane].upto = cincl;
+    if (lane < NW) rec->ref[lane] = ts.share_ref[lane];
+    if (lane == NW) rec->R = R;
+    if (lane == NW + 1) rec->thr = thr;
 }
 
 // After the barrier that follows the chunk sums: every wave scans the row's 64 chunk sums (fp64) for the total,

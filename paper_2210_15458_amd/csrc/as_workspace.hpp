@@ -42,6 +42,16 @@ inline int64_t kept_rows_few(int64_t V, int64_t rows, int64_t T, int64_t row_byt
     return T >= 3 && T <= 4 && V > 4 * rows && rows * T * row_bytes <= kKeptBytes ? rows * T : 0;
 }
 
+// The rows of a table of every token's logits row, made before the first step, or 0 where no decode of the size wants one:
+// a row for each of V tokens against T steps of `rows` rows and of the launches that a table spares, which cost what
+// 6e6 / V rows cost (6 us at a rank of 512), within kKeptBytes.  (Whether one is made: table_pays.)
+constexpr int64_t kTableRecord = 1056;       // bytes that a step reads of a row before its logits: RowRecord, CandRecord
+inline int64_t table_rows(int64_t V, int64_t rows, int64_t T, int64_t row_bytes)
+{
+    if (T < 4 || V * row_bytes > kKeptBytes) return 0;
+    return (double)T * ((double)rows + 6e6 / (double)V) >= 1.25 * (double)V ? V : 0;
+}
+
 // Most rows of the calls made so far that had three steps and more, four and more.
 struct RowsSeen {
     int64_t three = 0, four = 0;
@@ -110,10 +120,14 @@ inline DecodeSizes decode_sizes(int64_t V, int64_t esz, int64_t rows, int64_t T,
     const int64_t kept = masses ? 0 : kept_rows_most(V, rows, T, lb), kept_masses = kept_rows_most(V, rows, T, mb);
     DecodeSizes z;
     z.needed = (size_t)(rows * larger(masses ? 0 : lb, mb));
-    z.preferred = (size_t)larger((int64_t)z.needed, larger(kept * lb, kept_masses * mb));
+    const int64_t table = masses ? 0 : table_rows(V, rows, T, lb), table_masses = table_rows(V, rows, T, mb);
+    z.preferred = (size_t)larger(larger((int64_t)z.needed, larger(kept * lb, kept_masses * mb)), larger(table * lb, table_masses * mb));
     const int64_t sums = one_tile_row(V, esz) && T >= 3 ? smaller(V, rows * (V > 4 * rows ? smaller(T, 4) : T)) * kRowSums : 0;
     // (codes, prev, order, token of rows that are not kept; mark, slot, fill, or token of rows that are)
-    const size_t state = (size_t)((sums + 4 * rows + 4 * V + T + 1) * 4 + rows);
+    const size_t steps = (size_t)((sums + 4 * rows + 4 * V + T + 1) * 4 + rows);
+    // (a table's records; codes, prev twice, its tokens)
+    const size_t whole = (size_t)((one_tile_row(V, esz) ? table * kTableRecord : 0) + (3 * rows + V) * 4 + rows);
+    const size_t state = steps > whole ? steps : whole;
     const size_t column = encode_tables(V, esz, rows, rows, rows, smaller(rows, kPlainChunk), false).bytes;
     z.state = state > column ? state : column;
     return z;

@@ -1,0 +1,146 @@
+"""Decodes that make the logits rows of all tokens before the first step, against the loop of exported calls: the same bits.
+Every form that its steps take (sums, candidates, the rows themselves); rows that a one-tile kernel gives up (equal logits,
+weights beyond fp32); rows that end; more steps than a wave holds tokens; replayed from a graph; without the memory."""
+import pytest
+import torch
+
+from paper_2210_15458_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+TEMP = 1.1
+DT = {"bf16": torch.bfloat16, "f32": torch.float32}
+
+# V, d, prompts, codes, steps, top_k, top_p, weights, logits, temp, scale
+CASES = [
+    (8200, 128, 3, 20, 70, 0, 1.0, "bf16", "bf16", TEMP, 3.0),       # a share of the row past its end; 70 steps
+    (600, 64, 1, 37, 20, 0, 1.0, "bf16", "bf16", TEMP, 300.0),       # sums beyond fp32: the plain form of the row
+    (4100, 40, 2, 30, 12, 0, 1.0, "f32", "f32", 0.8, 3.0),
+    (2000, 128, 1, 41, 64, 0, 1.0, "bf16", "f32", 0.36, 3.0),
+    (16000, 128, 2, 100, 65, 40, 1.0, "bf16", "bf16", TEMP, 3.0),    # candidates
+    (16000, 128, 1, 130, 64, 20, 0.9, "bf16", "bf16", 0.3, 3.0),
+    (20000, 192, 2, 130, 64, 0, 0.9, "bf16", "bf16", TEMP, 3.0),     # the nucleus alone
+    (4096, 128, 2, 13, 30, 0, 0.5, "bf16", "bf16", TEMP, 30.0),
+    (2001, 128, 2, 100, 16, 0, 1.0, "bf16", "bf16", TEMP, 3.0),      # ragged rows, a low temperature, k the wide kernel's
+    (2000, 128, 2, 100, 16, 0, 1.0, "bf16", "bf16", 0.2, 3.0),
+    (3000, 128, 1, 70, 20, 100, 0.9, "bf16", "f32", TEMP, 3.0),
+]
+
+
+def _setup(V, d, Bn, N, wdt, ldt, scale):
+    g = torch.Generator(device="cuda").manual_seed(V)
+    E = torch.randn(V, d, device="cuda", generator=g)
+    E[::5] = 0.0                                          # rows of equal logits
+    U = torch.randn(d, V, device="cuda", generator=g)
+    model = B.Model(E.to(DT[wdt]), U.to(DT[wdt]), scale=scale)
+    prompts = torch.randint(0, V, (Bn,), device="cuda", generator=g, dtype=torch.int32)
+    prompts[-1] = V + 9                                   # outside: clamped
+    return model, B.Ctx(Bn * N, V, DT[ldt]), prompts, torch.rand(Bn, device="cuda", generator=g), g
+
+
+def _loop(ctx, model, prompts, N, T, codes, uniforms, temp, top_k, top_p, eos, ldt):
+    """The exported calls, a step at a time: tokens [R, T] and the last codes."""
+    R, V = prompts.numel() * N, model.V
+    logits = torch.empty((R, (V + 7) // 8 * 8), dtype=DT[ldt], device="cuda")
+    prev, fin = prompts.repeat_interleave(N).contiguous(), torch.zeros(R, dtype=torch.uint8, device="cuda")
+    out = torch.empty((R, T), dtype=torch.int32, device="cuda")
+    for t in range(T):
+        B.as_bigram_logits(ctx, model, prev, logits)
+        tok = torch.empty(R, dtype=torch.int32, device="cuda")
+        code = uniforms[t].contiguous() if uniforms is not None else codes
+        B.as_step_ex(ctx, logits, code, temp, top_k, top_p, tok, codes, finished_in=fin, eos_id=eos, finished_out=fin)
+        out[:, t] = tok
+        prev = tok
+    return out, codes
+
+
+def _logits_launches(ctx, call):
+    ctx.profile(True)
+    call()
+    n = ctx.profile_read(1)[1]
+    ctx.profile(False)
+    return n
+
+
+@pytest.mark.parametrize("V,d,Bn,N,T,top_k,top_p,wdt,ldt,temp,scale", CASES)
+def test_decode_from_a_table_equals_the_loop_of_exported_calls(V, d, Bn, N, T, top_k, top_p, wdt, ldt, temp, scale):
+    model, ctx, prompts, u, g = _setup(V, d, Bn, N, wdt, ldt, scale)
+    R = Bn * N
+    ctx.set_tuning("kept_rows", 3)                        # (whatever the rule comes to be)
+    out = torch.empty((Bn, N, T), dtype=torch.int32, device="cuda")
+    last = torch.empty(R, dtype=torch.float32, device="cuda")
+
+    def decode():
+        B.as_decode(ctx, model, prompts, N, T, u, temp, top_k, top_p, eos, out, codes_out=last)
+
+    eos = -1
+    decode()
+    eos = int(out.view(R, T)[:, T // 3].mode().values)    # a token that some codes end with, at different steps
+    decode()                                              # (on the tables that the call before has left)
+    codes = torch.empty(R, dtype=torch.float32, device="cuda")
+    B.as_lattice(ctx, u, N, codes)
+    want, want_codes = _loop(ctx, model, prompts, N, T, codes, None, temp, top_k, top_p, eos, ldt)
+    assert torch.equal(out.view(R, T), want) and torch.equal(last, want_codes)
+    assert (want == eos).any()
+    out.fill_(-1)
+    assert _logits_launches(ctx, decode) < T              # (timed, a step a launch; and the table was what ran)
+    assert torch.equal(out.view(R, T), want) and torch.equal(last, want_codes)
+
+    uniforms = torch.rand(T, R, device="cuda", generator=g).clamp_max_(1.0 - 2.0 ** -24)
+    B.as_decode_ancestral(ctx, model, prompts, N, T, uniforms, temp, top_k, top_p, eos, out)
+    want, _ = _loop(ctx, model, prompts, N, T, codes, uniforms, temp, top_k, top_p, eos, ldt)
+    assert torch.equal(out.view(R, T), want)
+    ctx.close()
+    model.close()
+
+
+def test_fused_decode_from_a_table():
+    V, d, Bn, N, T = 6007, 128, 2, 100, 20
+    model, ctx, prompts, u, _ = _setup(V, d, Bn, N, "bf16", "bf16", 3.0)
+    outs = []
+    for knob in (3, 1):
+        ctx.set_tuning("kept_rows", knob)
+        out = torch.empty((Bn, N, T), dtype=torch.int32, device="cuda")
+        n = _logits_launches(ctx, lambda: B.as_decode_fused(ctx, model, prompts, N, T, u, TEMP, 1, out))
+        assert n == (1 if knob == 3 else T)
+        outs.append(out)
+    assert torch.equal(*outs)
+    ctx.close()
+    model.close()
+
+
+@pytest.mark.parametrize("top_k,ldt", [(0, "bf16"), (10, "bf16"), (0, "f32")])
+def test_decode_from_a_table_replays_from_a_graph(top_k, ldt):
+    V, d, Bn, N, T = 16000, 128, 2, 100, 66
+    model, ctx, prompts, u, _ = _setup(V, d, Bn, N, "bf16", ldt, 3.0)
+    ctx.close()
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        ctx = B.Ctx(Bn * N, V, DT[ldt])
+        ctx.set_tuning("kept_rows", 3)
+        out = torch.empty((Bn, N, T), dtype=torch.int32, device="cuda")
+        eager = torch.empty_like(out)
+        B.as_decode(ctx, model, prompts, N, T, u, TEMP, top_k, 1.0, 1, out)       # (makes the workspace)
+    stream.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        B.as_decode(ctx, model, prompts, N, T, u, TEMP, top_k, 1.0, 1, out)
+    for i in range(4):
+        with torch.cuda.stream(stream):
+            u.uniform_(0.0, 0.99)
+            out.fill_(-1)
+            graph.replay()
+            got = out.clone()
+            B.as_decode(ctx, model, prompts, N, T, u, TEMP, top_k, 1.0, 1, eager)
+        stream.synchronize()
+        assert torch.equal(got, eager), f"replay {i}"
+    # the table is a choice: without its memory the decode takes a row per code
+    other = B.Ctx(Bn * N, V, DT[ldt])
+    other.set_tuning("workspace_mib", 100)
+    B.as_decode(other, model, prompts, N, T, u, TEMP, top_k, 1.0, 1, out)
+    torch.cuda.synchronize()
+    assert torch.equal(out, eager) and B.lib().as_last_error(other._h) == b""
+    other.close()
+    ctx.close()
+    model.close()

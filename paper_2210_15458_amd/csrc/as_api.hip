@@ -522,7 +522,7 @@ static as_status decode_state(as_ctx *ctx, const as_model *model, int32_t B, int
         s.tables = RowShare{};
         s.sums = nullptr;
         s.logits_rows = V;
-        return launch_table_tokens(ctx, s.token);
+        return AS_OK;
     }
     s.share = keep || sharing_pays(ctx, model, R, T);
     s.logits_rows = keep ? kept_rows : R;
@@ -658,7 +658,8 @@ static as_status decode_impl(as_ctx *ctx, const as_model *model, const int32_t *
     float *const codes = state.codes;
     uint8_t *const fin = state.fin;
 
-    st = launch_lattice(ctx, u, B, N, uniforms ? nullptr : codes, prompts, state.prev, fin, ctx->rid);
+    st = launch_lattice(ctx, u, B, N, uniforms ? nullptr : codes, prompts, state.prev, fin, ctx->rid,
+                        state.table ? state.token : nullptr);
     if (st == AS_OK && state.table) st = fill_table(ctx, model, state, ldw, form, temp, top_k, top_p);
     if (st != AS_OK) return st;
     const bool walk = state.table && form != kTableRows;
@@ -809,7 +810,8 @@ as_status as_decode_fused(as_ctx *ctx, const as_model *model, const int32_t *pro
     uint8_t *const fin = state.fin;
     float2 *part = static_cast<float2 *>(ctx->logits.ptr);
 
-    st = launch_lattice(ctx, u, B, N, codes, prompts, state.prev, fin, ctx->rid);
+    st = launch_lattice(ctx, u, B, N, codes, prompts, state.prev, fin, ctx->rid,
+                        state.table ? state.token : nullptr);
     if (st == AS_OK && state.table) st = launch_bigram_partials(ctx, model, state.token, ctx->V, temp, part, ldp);
     if (st != AS_OK) return st;
     for (int32_t t = 0; t < T; ++t) {

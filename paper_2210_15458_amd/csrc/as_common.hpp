@@ -301,10 +301,10 @@ as_status launch_wide(as_ctx *ctx, const StepArgs &a, int32_t top_k, float top_p
 as_status launch_threshold(as_ctx *ctx, const void *logits, int64_t rows, int64_t ld,
                            const uint8_t *finished_in, const int32_t *row_ids,
                            float temp, int32_t top_k, float top_p, float *thr_out);
-// prev_out: the prompts, clamped to the vocabulary
+// prev_out: the prompts, clamped to the vocabulary; table_out: 0 .. V-1
 as_status launch_lattice(as_ctx *ctx, const float *u, int32_t B, int32_t N, float *codes_out,
                          const int32_t *prompts, int32_t *prev_out, uint8_t *finished_out,
-                         int32_t *row_ids_out = nullptr);
+                         int32_t *row_ids_out = nullptr, int32_t *table_out = nullptr);
 as_status launch_estimate(as_ctx *ctx, const int32_t *tokens, int32_t B, int32_t N, int32_t T, const float *score,
                           int32_t eos_id, double *est_out);
 as_status launch_transpose(const void *U, void *Ut, int32_t d, int32_t V, as_dtype wdtype);
@@ -341,7 +341,6 @@ bool step_by_sums(const as_ctx *ctx, float temp);
 // a table of every token's logits row: whether it pays, its records, the steps from them
 bool table_pays(const as_ctx *ctx, const as_model *m, int64_t rows, int32_t T, TableForm form, bool keep, bool by_sums);
 TableForm table_form(const as_ctx *ctx, int64_t rows, float temp, int32_t top_k, float top_p);
-as_status launch_table_tokens(as_ctx *ctx, int32_t *tokens);
 as_status launch_table_records(as_ctx *ctx, TableForm form, const void *logits, int64_t ld, float temp, int32_t top_k, float top_p,
                                unsigned char *records);
 as_status launch_row_records(as_ctx *ctx, const void *logits, int64_t ld, float temp, unsigned char *records);

@@ -16,9 +16,11 @@ namespace {
 // ------------------------------------------------------------------ lattice
 
 __global__ void lattice_kernel(const float *u, int32_t B, int32_t N, float *codes,
-                               const int32_t *prompts, int32_t *prev, uint8_t *finished, int32_t *row_ids, int32_t V)
+                               const int32_t *prompts, int32_t *prev, uint8_t *finished, int32_t *row_ids, int32_t V,
+                               int32_t *table)
 {
     const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (table && idx < V) table[idx] = (int32_t)idx;     // the rows of a table of all tokens
     if (idx >= (int64_t)B * N) return;
     const int32_t b = (int32_t)(idx / N), i = (int32_t)(idx % N);
     // c_i = (i + u)/N: spacing exactly 1/N around the circle, one shift per prompt
@@ -140,13 +142,6 @@ __global__ __launch_bounds__(256) void share_order_kernel(RowShare s, int64_t ro
 {
     const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (r < rows) s.order[atomicAdd(&s.fill[row_ids[r]], 1)] = (int32_t)r;
-}
-
-// the rows of a table of every token: its tokens
-__global__ __launch_bounds__(256) void table_tokens_kernel(int32_t *tokens, int32_t V)
-{
-    const int32_t i = blockIdx.x * 256 + threadIdx.x;
-    if (i < V) tokens[i] = i;
 }
 
 // ---------------------------------------------------------------- transpose
@@ -1203,12 +1198,13 @@ __global__ __launch_bounds__(1024) void estimate_kernel(const int32_t *tokens, i
 }  // namespace
 
 as_status launch_lattice(as_ctx *ctx, const float *u, int32_t B, int32_t N, float *codes_out,
-                         const int32_t *prompts, int32_t *prev_out, uint8_t *finished_out, int32_t *row_ids_out)
+                         const int32_t *prompts, int32_t *prev_out, uint8_t *finished_out, int32_t *row_ids_out,
+                         int32_t *table_out)
 {
-    const int64_t n = (int64_t)B * N;
-    if (n == 0) return AS_OK;
+    const int64_t rows = (int64_t)B * N, n = table_out && ctx->V > rows ? ctx->V : rows;
+    if (rows == 0) return AS_OK;
     hipLaunchKernelGGL(lattice_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, ctx->stream, u, B, N,
-                       codes_out, prompts, prev_out, finished_out, row_ids_out, ctx->V);
+                       codes_out, prompts, prev_out, finished_out, row_ids_out, ctx->V, table_out);
     AS_HIP_TRY(ctx, hipGetLastError());
     return AS_OK;
 }
@@ -1356,13 +1352,6 @@ bool table_pays(const as_ctx *ctx, const as_model *m, int64_t rows, int32_t T, T
     const double step = form == kTableRows ? sampling : 3.0 + R * 0.0006;
     const double table = product_us(ctx, m, V) + (form == kTableRows ? 0.0 : 4.0 + V * row_us);
     return table + T * step < (keep ? 0.85 : 0.95) * T * without;
-}
-
-as_status launch_table_tokens(as_ctx *ctx, int32_t *tokens)
-{
-    hipLaunchKernelGGL(table_tokens_kernel, dim3((unsigned)((ctx->V + 255) / 256)), dim3(256), 0, ctx->stream, tokens, ctx->V);
-    AS_HIP_TRY(ctx, hipGetLastError());
-    return AS_OK;
 }
 
 as_status launch_share_clear(as_ctx *ctx, const RowShare &s, int32_t T)

@@ -36,7 +36,19 @@ namespace {
 typedef unsigned long long u64;
 
 constexpr int kWideTopK = 128;           // largest k of the candidate table
-constexpr int kTopOctaves = 16;          // factors of two that the bins reach above the reference
+constexpr int kWaveTopK = 40;            // ... where a wave has the row (64 candidates)
+
+// The largest k that a form takes by the candidate table; above it, by counts.  A table of n candidates costs what their
+// slots and places do, counts cost a pass over the row: on short rows, with no nucleus behind them, counts are ahead sooner
+// (us, table / counts: 4 rows of 1501 bf16, k = 64 11.4 / 7.9, k = 100 13.2 / 7.9; 1000 of 4001 14.4 / 12.8, 17.7 / 12.9, k = 40
+// 11.6 / 12.8; 1000 of 8001 k = 64 15.2 / 15.0; 4 of 16001 k = 100 14.0 / 11.3, 1000 24.1 / 23.3; from 8 pieces a thread on even
+// or behind; with p = 0.9 1000 of 4001 k = 100 17.9 / 19.2).
+template <int NT, int NP> __host__ __device__ constexpr int32_t table_most(int32_t pieces, bool has_p)
+{
+    if (NT == 64) return kWaveTopK;
+    if (NP > 4 || has_p) return kWideTopK;
+    return NT > 256 ? 96 : pieces <= 512 ? 48 : 64;
+}
 
 // order-preserving key of a logit (-0 and +0 are one value: one key), and back
 __device__ __forceinline__ uint32_t order_key(float f)
@@ -64,14 +76,20 @@ __device__ __forceinline__ u64 fixed_weight(float e)
     return ((u64)hi << 32) | lo;
 }
 
+// NT = 64: a wave a row, for very many short ones; LDS for six waves a SIMD.  A bin is as wide as in SHORT, over half the octaves
+// (counts: as many octaves, twice the width), and a window takes fewer neighbours, so that it closes within the 64 threads.
 // SHORT: the forms for many short rows, where as many blocks as the unit's waves allow hide each other's block-wide
 // steps: half the LDS, 16 bins an octave where a nucleus's window is named (a bin's mass to a few parts in 10^4; the masses that
 // close it are the same).
 template <int NT, bool MULTI, bool SHORT> struct WideShared {
     static constexpr int kWaves = NT / 64;
-    static constexpr int kBins = NT == 1024 ? 4096 : SHORT ? 1024 : 2048;
-    static constexpr int kPerOctave = kBins / 64;            // 64 factors of two
-    static constexpr int kList = NT == 1024 ? 2048 : SHORT ? 512 : 1024;
+    static constexpr bool kWave = NT == 64;                  // a wave a row
+    static constexpr int kBins = NT == 1024 ? 4096 : kWave ? 512 : SHORT ? 1024 : 2048;
+    static constexpr int kOctaves = kWave ? 32 : 64;         // factors of two that the bins take ...
+    static constexpr int kTopOctaves = kOctaves / 4;         // ... and of them above the reference
+    static constexpr int kPerOctave = kBins / kOctaves;
+    static constexpr int kList = NT == 1024 ? 2048 : kWave ? 128 : SHORT ? 512 : 1024;
+    static constexpr float kBeside = kWave ? 12.f : 32.f;    // logits of a nucleus's window on either side of its bin
     // (a row of 2^21 fp32 logits: 8193; with 512 threads, where two blocks are to share a unit's LDS, rows of fewer)
     static constexpr int kChunks = !MULTI ? 16 * kWaves + 1 : NT == 1024 ? 8704 : 2304;
     union {
@@ -285,30 +303,37 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
 
     // ------------------------------------------------------------------ top-k by a table of candidates
     if constexpr (TOPK) {
-        float m = -__builtin_inff();
+        // the largest of the logits of 256 groups: of one, two or four lanes, or (a wave a row) of a lane's pieces by four
+        constexpr int kOwn = Sh::kWave ? 4 : 1;
+        float gm[kOwn];
+#pragma unroll
+        for (int i = 0; i < kOwn; ++i) gm[i] = -__builtin_inff();
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
             land(p);
             float x[EPV];
             values(raw[p], x);
+            float &m = gm[p * kOwn / NP];
             m = max3(m, vec_max<EPV>(x), m);
         }
-        if (top_k <= kWideTopK) {
-            // 256 groups of one, two or four lanes
-            constexpr int kPerGroup = NT / 256;
-            if (kPerGroup >= 2) m = fmaxf(m, __shfl_xor(m, 1, 64));
-            if (kPerGroup >= 4) m = fmaxf(m, __shfl_xor(m, 2, 64));
-            if (tid % kPerGroup == 0) sh.key[tid / kPerGroup] = order_key(m);
+        if (top_k <= table_most<NT, NP>(V / EPV, top_p > 0.f && top_p < 1.f)) {
             if (tid == 0) {
                 sh.n = 0;
                 sh.sel = 0;
             }
-            __syncthreads();
+            uint32_t g[4];
+            if constexpr (!Sh::kWave) {
+                constexpr int kPerGroup = NT / 256;
+                float m = gm[0];
+                if (kPerGroup >= 2) m = fmaxf(m, __shfl_xor(m, 1, 64));
+                if (kPerGroup >= 4) m = fmaxf(m, __shfl_xor(m, 2, 64));
+                if (tid % kPerGroup == 0) sh.key[tid / kPerGroup] = order_key(m);
+                __syncthreads();
+            }
             if (wave == 0) {
                 // the largest key that at least k of the maxima reach, by bisection; a round is four ballots
-                uint32_t g[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) g[i] = sh.key[i * 64 + lane];
+                for (int i = 0; i < 4; ++i) g[i] = Sh::kWave ? order_key(gm[i % kOwn]) : sh.key[i * 64 + lane];
                 uint32_t lo = min(min(g[0], g[1]), min(g[2], g[3])), hi = max(max(g[0], g[1]), max(g[2], g[3]));
 #pragma unroll
                 for (int d = 32; d >= 1; d >>= 1) {
@@ -463,7 +488,7 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
     constexpr float kTwo23 = 8388608.f;
     constexpr float kScale = (float)Sh::kPerOctave;
     constexpr float kBinLo = kTwo23, kBinHi = kTwo23 + (float)(Sh::kBins - 1);
-    constexpr float kBin0 = kTwo23 + (float)(kTopOctaves * Sh::kPerOctave);
+    constexpr float kBin0 = kTwo23 + (float)(Sh::kTopOctaves * Sh::kPerOctave);
     // coarse bin of an exponent argument relative to the reference, as a float whose low mantissa bits are the bin
     // (rounded to the nearest integer and clamped to the table; falls as the logit rises)
     auto bin_of = [&](float y) __attribute__((always_inline)) {
@@ -595,6 +620,8 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
     // against top_p of their total (the reference is the row's own then).  False if no logit has weight.
     auto select = [&](auto count_c, float floor_x, float &thr) __attribute__((always_inline)) -> bool {
         constexpr bool COUNT = decltype(count_c)::value;
+        // (counts always reach over 64 factors of two: a large k may lie deep)
+        constexpr float kCountScale = (float)(Sh::kBins / 64), kCountBin0 = kTwo23 + (float)(Sh::kBins / 4);
         float nr = -ref;
         auto weight = [&](float x) __attribute__((always_inline)) -> u64 {
             if constexpr (COUNT) return 1ull;
@@ -610,7 +637,7 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
                 for (int e = 0; e < EPV; ++e) {
                     if constexpr (COUNT) {
                         // (what lies below the last bin, padding among it, goes to a word of the lane's own)
-                        const float t = __builtin_amdgcn_fmed3f(fmaf(fmaf(x[e], k, nr), -kScale, kBin0), kBinLo,
+                        const float t = __builtin_amdgcn_fmed3f(fmaf(fmaf(x[e], k, nr), -kCountScale, kCountBin0), kBinLo,
                                                                 kTwo23 + (float)(Sh::kBins + lane));
                         __hip_atomic_fetch_add((lds_u32 *)sh.tally + (__builtin_bit_cast(uint32_t, t) - 0x4B000000u), 1u,
                                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -629,7 +656,7 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
         fill();
         if constexpr (COUNT) {
             const float exact = fmaxf(ceilf(mx * k), kRefFloor);
-            if (!(exact - ref <= (float)kTopOctaves)) {
+            if (!(exact - ref <= 16.f)) {
                 // a logit far above the first pieces' largest: once more against the row's own reference
                 ref = exact;
                 nr = -ref;
@@ -655,7 +682,11 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
         }
         u64 base = sh.before;
         const float tpick = kTwo23 + (float)pick;
-        auto member = [&](float x) __attribute__((always_inline)) { return bin_of(fmaf(x, k, nr)) == tpick; };
+        auto member = [&](float x) __attribute__((always_inline)) {
+            const float y = fmaf(x, k, nr);
+            if constexpr (COUNT) return __builtin_amdgcn_fmed3f(fmaf(y, -kCountScale, kCountBin0), kBinLo, kBinHi) == tpick;
+            else return bin_of(y) == tpick;
+        };
         // f(key, weight) for the logits of that bin in one piece
         auto members = [&](const u32x4 &v, auto f) __attribute__((always_inline)) {
             float x[EPV];
@@ -761,7 +792,7 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
             sweep(Yes{}, [&](const u32x4 &v, int, int32_t) __attribute__((always_inline)) { one(v); }, nothing_more);
         });
         const float exact = fmaxf(ceilf(mx * k), kRefFloor);
-        if (!(exact - ref <= (float)kTopOctaves)) {
+        if (!(exact - ref <= (float)Sh::kTopOctaves)) {
             // a logit far above the first pieces' largest: once more, from memory, against the row's own reference
             ref = exact;
             fill([&](auto one) __attribute__((always_inline)) {
@@ -782,7 +813,7 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
             for (int i = 0; i < kPer; ++i) {
                 const int b = tid * kPer + i;
                 const uint32_t h = sh.tally[b];
-                m[i] = (double)((float)h * down * fast_exp2((float)(kTopOctaves * Sh::kPerOctave - b) / kScale));
+                m[i] = (double)((float)h * down * fast_exp2((float)(Sh::kTopOctaves * Sh::kPerOctave - b) / kScale));
                 cnt += (h + (1u << s_bits) / 2u) >> s_bits;
                 local += m[i];
             }
@@ -808,7 +839,7 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
                     if (found < 0 && acc >= need) found = tid * kPer + i;
                 }
                 sh.pick = found >= 0 ? found : tid * kPer + kPer - 1;
-                sh.sel = clo <= 32.0 ? 1u : 0u;              // few logits above: all of them go on the list
+                sh.sel = clo <= (double)Sh::kBeside ? 1u : 0u;              // few logits above: all of them go on the list
             }
             __syncthreads();
         }
@@ -822,8 +853,8 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
                 const float c = in ? (float)((sh.tally[b >= 0 && b < Sh::kBins ? b : 0] + (1u << s_bits) / 2u) >> s_bits) : 0.f;
                 const float incl = wave_scan_add(c);
                 const float upto = as::read_lane(incl, 32);
-                const u64 near_lo = __ballot(lane < 32 && upto - incl + c <= 32.f);
-                const u64 far_hi = __ballot(lane > 32 && incl - upto > 32.f);
+                const u64 near_lo = __ballot(lane < 32 && upto - incl + c <= Sh::kBeside);
+                const u64 far_hi = __ballot(lane > 32 && incl - upto > Sh::kBeside);
                 wlo = pick - 32 + (near_lo ? (int32_t)__builtin_ctzll(near_lo) : 32);
                 whi = pick - 32 + (far_hi ? (int32_t)__builtin_ctzll(far_hi) - 1 : 63);
                 wlo = sh.sel != 0u || wlo < 0 ? 0 : wlo;
@@ -831,8 +862,8 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
             }
             // (as exponent arguments; the bins' own rounding need not be met, every logit only has to fall on one side)
             const float yhi = wlo == 0 ? __builtin_inff()
-                                       : ((float)(kTopOctaves * Sh::kPerOctave - wlo) + 0.5f) / kScale - lower;
-            const float ylo = ((float)(kTopOctaves * Sh::kPerOctave - whi) - 0.5f) / kScale - lower;
+                                       : ((float)(Sh::kTopOctaves * Sh::kPerOctave - wlo) + 0.5f) / kScale - lower;
+            const float ylo = ((float)(Sh::kTopOctaves * Sh::kPerOctave - whi) - 0.5f) / kScale - lower;
             u64 all = 0, over = 0;                           // masses of the lane's logits; of those above the window
             // the lane's weight above the window; its logits inside the window join the list
             auto part = [&](const u32x4 &v, int32_t c) __attribute__((always_inline)) {
@@ -1041,17 +1072,30 @@ void launch_form(as_ctx *ctx, int kid, const StepArgs &a, int32_t top_k, float t
 // us with 256 x 8, 143 with 512 x 4; of 20001 152 with 256 x 16, 174 with 512 x 8; top-k 40, 2500 of 20003 41, with 512
 // threads 55).  With more than four short rows a unit the blocks are made to fit eight a unit (SHORT; six for k above 128 and
 // for nuclei of two registers' pieces more): 12000 rows of 1281 to 8000 bf16, or half as many fp32, nuclei 1.18 times faster,
-// top-k 1.28 to 1.36, k = 200 1.16; 600 of them no different.
+// top-k 1.28 to 1.36, k = 200 1.16; 600 of them no different.  With more rows still, a wave a row: nothing in it waits for
+// another wave, and what a block does in some 25 steps of its waves overlaps over rows instead (us, blocks / waves: nuclei, 1500
+// rows of 1500 bf16 20.5 / 14.9, 600 14.0 / 13.0, 14251 of 1923 119 / 63, 5252 of 3078 57 / 38, 4200 of 8001 58 / 56, 2600 42 /
+// 47; k = 40 2100 of 4001 18.6 / 16.3, 1500 of 3000 13.1 / 14.6, 9000 of 6001 53 / 47, 4200 of 8001 31 / 32; counts, k = 1000,
+// 4000 of 1500 30 / 18, 2100 of 4001 23 / 25, 9000 of 6001 79 / 77, 4200 of 8001 46 / 59).
 template <int DT, bool TOPK>
 void launch_type(as_ctx *ctx, int kid, const StepArgs &a, int32_t top_k, float top_p, float *thr_out)
 {
     constexpr int EPV = Elem<DT>::kPerVec;
     const int64_t most = ((int64_t)a.V + EPV - 1) / EPV;     // whole pieces of a row, whatever its alignment
     const bool many = a.rows > (int64_t)ctx->num_cus, lots = a.rows > 2 * (int64_t)ctx->num_cus;
+    const bool has_p = top_p > 0.f && top_p < 1.f;
+    // (compute units' worth of rows beyond which a wave takes a row; counts on longer rows, and a nucleus after them, never)
+    const bool counts = TOPK && top_k > kWaveTopK;
+    const int64_t waves = most <= 64 * 8 ? (!TOPK ? 4 : counts ? 12 : 6) : !TOPK ? 16 : !counts || (!has_p && a.V <= 6144) ? 20 : 1 << 30;
+    if (most <= 64 * 16 && a.rows > waves * (int64_t)ctx->num_cus) {
+        if (most <= 64 * 8) return launch_form<DT, 64, 8, false, TOPK, 5>(ctx, kid, a, top_k, top_p, thr_out);
+        return launch_form<DT, 64, 16, false, TOPK, 4>(ctx, kid, a, top_k, top_p, thr_out);
+    }
     if (most <= 256 * 4) {
         if (a.rows <= 4 * (int64_t)ctx->num_cus) return launch_form<DT, 256, 4, false, TOPK>(ctx, kid, a, top_k, top_p, thr_out);
         if constexpr (TOPK) {
-            if (top_k > kWideTopK) return launch_form<DT, 256, 4, false, TOPK, 6>(ctx, kid, a, top_k, top_p, thr_out);
+            if (top_k > table_most<256, 4>(a.V / EPV, has_p))
+                return launch_form<DT, 256, 4, false, TOPK, 6>(ctx, kid, a, top_k, top_p, thr_out);
         }
         return launch_form<DT, 256, 4, false, TOPK, 8>(ctx, kid, a, top_k, top_p, thr_out);
     }

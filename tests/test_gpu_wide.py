@@ -117,3 +117,34 @@ def test_many_short_rows(V, dtype, sigma):
 def test_one_tile_top_k_at_its_line(V, k):
     for top_p in (1.0, 0.9):
         _check(V, 70, "bf16", temp=0.9, top_k=k, top_p=top_p, seed=V + k)
+
+
+# the forms of a wave a row (as many rows as make them worth it), at their ends: 512 and 1024 pieces of 16 bytes
+@pytest.mark.parametrize("V,rows,dtype", [(3, 3100, "bf16"), (700, 3100, "bf16"), (4089, 3100, "bf16"), (4096, 3100, "bf16"),
+                                          (4097, 5200, "bf16"), (8186, 5200, "bf16"), (2, 3100, "f32"), (2047, 3100, "f32"),
+                                          (2050, 5200, "f32"), (4093, 5200, "f32")])
+@pytest.mark.parametrize("sigma,temp", [(0.05, 1.0), (3.0, 0.9), (9.0, 0.4)])
+def test_a_wave_a_row(V, rows, dtype, sigma, temp):
+    # k at the ends of its candidate table and of the counts; flat rows overflow both lists
+    from gpu_util import compare_step, oracle_step, run_gpu_step
+    held = 37                                             # rows of logits for many codes
+    stored = synth.gaussian_logits(held, V, sigma=sigma, seed=V + rows, dtype=dtype)
+    rid = (np.arange(rows) % held).astype(np.int32)
+    codes = synth.uniform_codes(rows, seed=rows + V)
+    for top_k, top_p in ((0, 0.9), (1, 1.0), (40, 0.8), (41, 1.0), (41, 0.9), (128, 1.0), (600, 1.0), (600, 0.7)):
+        if top_k >= V:
+            continue
+        label = f"V={V} R={rows} {dtype} sigma={sigma} k={top_k} p={top_p}"
+        print("case", label, flush=True)
+        gpu = run_gpu_step(stored, codes, V, temp=temp, top_k=top_k, top_p=top_p, row_ids=rid, tuning=ANY)
+        ref = oracle_step(stored, codes, V, temp=temp, top_k=top_k, top_p=top_p, row_ids=rid.astype(np.int64))
+        print("   ", compare_step(gpu, ref, V, label, trunc=True, codes=codes), flush=True)
+
+
+# short rows, few of them: the largest k of the candidate table and the first that is counted, on either side of the lengths at
+# which that line moves
+@pytest.mark.parametrize("V,dtype,ks", [(4103, "bf16", (48, 49)), (4104, "bf16", (64, 65)), (2051, "f32", (48, 49)),
+                                        (2052, "f32", (64, 65)), (8200, "bf16", (96, 97)), (16383, "f32", (96, 97))])
+def test_candidates_or_counts(V, dtype, ks):
+    for k in ks:
+        _check(V, 6, dtype, temp=0.9, top_k=k, seed=V + k, tuning=ANY)

@@ -1119,7 +1119,12 @@ void launch_type(as_ctx *ctx, int kid, const StepArgs &a, int32_t top_k, float t
     if constexpr (TOPK || DT == AS_F32) {
         if (most <= 1024 * 16) return launch_form<DT, 1024, 16, false, TOPK>(ctx, kid, a, top_k, top_p, thr_out);
     }
-    launch_form<DT, 1024, TOPK ? 16 : 8, true, TOPK>(ctx, kid, a, top_k, top_p, thr_out);
+    if constexpr (TOPK) {
+        // (the candidate table wants the larger tile; counts, whose 16-piece form spills the row, the smaller one: us, 16 / 8 pieces,
+        // k = 200 256 rows of 256000 bf16 110 / 64, 16 of 182125 76 / 40, fp32 85 / 42)
+        if (top_k <= kWideTopK) return launch_form<DT, 1024, 16, true, TOPK>(ctx, kid, a, top_k, top_p, thr_out);
+    }
+    launch_form<DT, 1024, 8, true, TOPK>(ctx, kid, a, top_k, top_p, thr_out);
 }
 
 }  // namespace

@@ -256,12 +256,14 @@ __global__ __launch_bounds__(256) void walk_kernel(WalkArgs a)
                     const float rw = read_lane(meta, ch / ITERS), R = read_lane(meta, 4);
                     const bool inside = ch * 64 + lane < nvec;
                     const u32x4 hv = reinterpret_cast<const u32x4 *>(row)[inside ? ch * 64 + lane : 0];
-                    float cl = tile_lane_sum<DT, HAS_THR>(hv, k, -rw, thr);
+                    float e[EPV];
+                    tile_weights<DT, HAS_THR>(hv, k, -rw, thr, e);
+                    float cl = vec_sum<EPV>(e);
                     cl = inside ? cl : 0.f;
                     const int shf = shift_of(rw, R);
                     double acc, start, ev;
                     const int l = tile_lane(cl, shf, tau, run, acc);
-                    const int ih = tile_element<DT, HAS_THR>(hv, k, thr, rw, shf, tau, acc, start, ev);
+                    const int ih = tile_element(e, shf, tau, acc, lane == l, start, ev);
                     code = read_lane(rescale_code(tau, start, ev), l);
                     tok = (ch * 64 + l) * EPV + __builtin_amdgcn_readlane(ih, l);
                     tok = tok > a.V - 1 ? a.V - 1 : tok;

@@ -123,19 +123,26 @@ struct TileSums {
     __attribute__((aligned(16))) float share_ref[kTileWaves];                // the integer reference its share's sums are relative to
 };
 
-// the lane's sum over one chunk, relative to the reference -nr
+// a vector's weights, relative to the reference -nr (0 where it is not kept)
 template <int DT, bool HAS_THR>
-__device__ __forceinline__ float tile_lane_sum(const u32x4 &v, float k, float nr, float thr)
+__device__ __forceinline__ void tile_weights(const u32x4 &v, float k, float nr, float thr, float (&e)[Elem<DT>::kPerVec])
 {
     constexpr int EPV = Elem<DT>::kPerVec;
-    float x[EPV], e[EPV];
+    float x[EPV];
     unpack<DT>(v, x);
 #pragma unroll
     for (int i = 0; i < EPV; ++i) {
         e[i] = fast_exp2(fmaf(x[i], k, nr));
         if constexpr (HAS_THR) e[i] = (x[i] >= thr) ? e[i] : 0.f;
     }
-    return vec_sum<EPV>(e);
+}
+// the lane's sum over one chunk
+template <int DT, bool HAS_THR>
+__device__ __forceinline__ float tile_lane_sum(const u32x4 &v, float k, float nr, float thr)
+{
+    float e[Elem<DT>::kPerVec];
+    tile_weights<DT, HAS_THR>(v, k, nr, thr, e);
+    return vec_sum<Elem<DT>::kPerVec>(e);
 }
 
 // the wave's reference: from the first chunk's largest kept logit and, with a threshold, the threshold itself
@@ -191,33 +198,47 @@ __device__ __forceinline__ int tile_lane(float cl, int shf, double tau, double r
     return hit2 ? (__ffsll((long long)hit2) - 1) : (nz2 ? (63 - __clzll((long long)nz2)) : 0);
 }
 
-// The element of a lane's vector that holds the code, acc the mass before the vector.
-template <int DT, bool HAS_THR>
-__device__ __forceinline__ int tile_element(const u32x4 &hv, float k, float thr, float rw, int shf, double tau, double acc,
-                                            double &before, double &ev)
+// The element of a lane's vector that holds the code: e the vector's weights (relative to the wave's reference), acc the mass
+// before the vector; `before` the mass before the element, `ev` its own.  The running sums do not fall, so the element is the last
+// one whose own start lies at or below tau: an addition, a comparison and four moves an element (with the choice of the first hit
+// and of the last weight kept beside each other, and the weights made twice, 65536 codes x 16 steps of 32128 took 1855 us instead of
+// 1766; where a wave has many codes the instructions of a step bound it, 8 waves x 280 of them a SIMD).  Past the end by rounding:
+// the last with weight (asked of the lane whose element counts, `mine`, alone).
+template <int EPV>
+__device__ __forceinline__ int tile_element(const float (&e)[EPV], int shf, double tau, double acc, bool mine, double &before,
+                                            double &ev)
 {
-    constexpr int EPV = Elem<DT>::kPerVec;
-    float x[EPV];
-    unpack<DT>(hv, x);
-    double ed[EPV];
-#pragma unroll
-    for (int i = 0; i < EPV; ++i) {
-        float e = fast_exp2(fmaf(x[i], k, -rw));
-        if constexpr (HAS_THR) e = (x[i] >= thr) ? e : 0.f;
-        ed[i] = (double)ldexpf(e, shf);
-    }
-    int ih = -1, ilast = 0;
-    double before_last = acc, ev_last = 0.0;
+    double run = acc;
+    float w = e[0];
+    int at = 0;
     before = acc;
-    ev = 0.0;
 #pragma unroll
     for (int i = 0; i < EPV; ++i) {
-        if (ed[i] > 0.0) { ilast = i; before_last = acc; ev_last = ed[i]; }
-        if (ih < 0 && acc + ed[i] > tau) { ih = i; before = acc; ev = ed[i]; }
-        acc += ed[i];
+        const bool starts = i > 0 && !(run > tau);
+        before = starts ? run : before;
+        w = starts ? e[i] : w;
+        at = starts ? i : at;
+        run += (double)ldexpf(e[i], shf);
     }
-    if (ih < 0) { ih = ilast; before = before_last; ev = ev_last; }
-    return ih;
+    if (mine && !(run > tau)) {
+        run = acc;
+        asm volatile("" : "+v"(run));            // (a branch of its own: folded into the sums above, it would cost every row)
+        at = 0;
+        w = 0.f;
+        before = run;
+#pragma unroll
+        for (int i = 0; i < EPV; ++i) {
+            const float v = ldexpf(e[i], shf);
+            if (v > 0.f) {
+                at = i;
+                before = run;
+                w = e[i];
+            }
+            run += (double)v;
+        }
+    }
+    ev = (double)ldexpf(w, shf);
+    return at;
 }
 
 // The wave that holds the code's chunk: hv its lanes' vectors of the chunk (vector vec0 + lane of the row), cl their sums
@@ -229,7 +250,9 @@ __device__ __forceinline__ void tile_finish(const StepArgs &a, int64_t r, float 
 {
     double acc, before, ev;
     if (lane != tile_lane(cl, shf, tau, run, acc)) return;
-    const int ih = tile_element<DT, HAS_THR>(hv, a.k, thr, rw, shf, tau, acc, before, ev);
+    float e[Elem<DT>::kPerVec];
+    tile_weights<DT, HAS_THR>(hv, a.k, -rw, thr, e);
+    const int ih = tile_element(e, shf, tau, acc, true, before, ev);
 
     int64_t tok64 = ((int64_t)vec0 + lane) * Elem<DT>::kPerVec + ih;
     if (tok64 > a.V - 1) tok64 = a.V - 1;

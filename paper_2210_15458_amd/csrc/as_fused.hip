@@ -22,12 +22,12 @@ __device__ __forceinline__ int last_lane(unsigned long long mask) { return 63 - 
 // scans those (up to 64: vocabularies up to 2^21), finds the tile of the row's code and walks that one tile
 // again.  Then all four waves recompute the hit group's 32 logits, a wave reading one whole row of U^T per
 // instruction (8 rows per wave) against the embedding piece it fetched at the start; wave 0 finishes.
-constexpr int kMaxPiecesPerLane = 8;          // rank up to 64 * 8 * 8 = 4096
+constexpr int kMaxPiecesPerLane = 8;          // rank up to 64 * 8 * 8 = 4096 (PIECES: what a lane holds of it)
 constexpr int kTileGroups = 64 * kGroupsPerLane;
 constexpr int kMaxTiles = 64;
 
-template <bool MULTI>
-__global__ __launch_bounds__(256) void fused_sample_kernel(FusedArgs a)
+template <bool MULTI, int PIECES, int WAVES>
+__global__ __launch_bounds__(256, WAVES) void fused_sample_kernel(FusedArgs a)
 {
     __shared__ __attribute__((aligned(16))) float2 table[(MULTI ? 4 : 1) * kTileGroups];     // 8 KB per wave that walks
     __shared__ double tile_sum[MULTI ? kMaxTiles : 1];
@@ -64,10 +64,10 @@ __global__ __launch_bounds__(256) void fused_sample_kernel(FusedArgs a)
     }
     // pieces lane, lane+64, ... of the conditioning token's embedding: not needed before the dot products
     const int npieces = a.d / 8;
-    u32x4 ew[kMaxPiecesPerLane];
+    u32x4 ew[PIECES];
     const u32x4 *ep = reinterpret_cast<const u32x4 *>(a.E + (int64_t)prev * a.d);
 #pragma unroll
-    for (int i = 0; i < kMaxPiecesPerLane; ++i)
+    for (int i = 0; i < PIECES; ++i)
         ew[i] = lane + 64 * i < npieces ? ep[lane + 64 * i] : u32x4{0, 0, 0, 0};
 
     float rw = 0.f;
@@ -190,7 +190,7 @@ __global__ __launch_bounds__(256) void fused_sample_kernel(FusedArgs a)
     }
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < kMaxPiecesPerLane; ++i) {
+    for (int i = 0; i < PIECES; ++i) {
         if (64 * i >= npieces) break;                           // uniform
         const bool in = lane + 64 * i < npieces;
         u32x4 uw[8];
@@ -243,8 +243,15 @@ as_status launch_fused_sample(as_ctx *ctx, const FusedArgs &a)
     if (a.rows == 0) return AS_OK;
     if (a.d > 64 * 8 * kMaxPiecesPerLane) return fail(ctx, AS_ERR_UNSUPPORTED, "the fused step takes ranks up to 4096");
     if (a.ldp > (int64_t)kTileGroups * kMaxTiles) return fail(ctx, AS_ERR_UNSUPPORTED, "the fused step takes vocabularies up to 2^21");
-    if (a.ldp <= kTileGroups) launch(ctx, kKernelStep, fused_sample_kernel<false>, dim3((unsigned)a.rows), dim3(256), 0, a);
-    else launch(ctx, kKernelStep, fused_sample_kernel<true>, dim3((unsigned)a.rows), dim3(256), 0, a);
+    // Many rows are bound by how many of them a compute unit has open (a row's wave 0 works alone for most of its time), so the
+    // registers follow the rank: 49 up to 512, 74 up to 1024, 102 beyond.  us a decode, always room for 4096 / by rank:
+    // 38912 rows x 6 of 5105 x 192 1157 / 679, 1024 x 64 of 32128 x 512 3028 / 1742, 8000 x 20 of 16000 x 768 2090 / 1477,
+    // 16 x 64 of 32128 x 512 660 / 636.  Rows of several tiles are bound by LDS (four a unit) and gain nothing.
+    auto go = [&](auto kernel) { launch(ctx, kKernelStep, kernel, dim3((unsigned)a.rows), dim3(256), 0, a); };
+    if (a.ldp > kTileGroups) go(fused_sample_kernel<true, kMaxPiecesPerLane, 4>);
+    else if (a.d <= 512) go(fused_sample_kernel<false, 1, 6>);
+    else if (a.d <= 1024) go(fused_sample_kernel<false, 2, 5>);
+    else go(fused_sample_kernel<false, kMaxPiecesPerLane, 4>);
     AS_HIP_TRY(ctx, hipGetLastError());
     return AS_OK;
 }

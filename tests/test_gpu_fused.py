@@ -81,6 +81,12 @@ def test_fused_decode_lockstep_against_oracle(V, d, Bn, N, T, temp, eos):
     ctx.close(); model.close()
 
 
+# the ranks at which the sampling kernel's registers change, and the largest
+@pytest.mark.parametrize("d", [512, 576, 1024, 1088, 4096])
+def test_fused_decode_at_the_lines_between_ranks(d):
+    test_fused_decode_lockstep_against_oracle(1003, d, 2, 70, 3, 1.0, 1)
+
+
 def test_fused_decode_agrees_with_unfused_on_fp32_logits():
     """Same model, logits kept in fp32: the two paths differ only by accumulation order, so tokens agree except
     at codes next to a bucket boundary (counted)."""

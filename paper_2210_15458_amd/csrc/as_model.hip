@@ -253,6 +253,11 @@ __global__ __launch_bounds__(512, 1) void bigram_gemm_persistent(const uint16_t 
         prev += first;
         C += first * ldc * (FUSED ? 2 : 1);
     }
+    // Logits of twice the last-level cache and more are written past the caches: nothing of them is still there when they are read
+    // (32128 rows of 32128, d = 512: 1017 us, 997 so, and the pass over them after it 375, 345; 263 MB, which are: an encode 1192,
+    // 1202).  Whole lines only: 16160 x 80198, whose rows start inside a line, a decode 39.3 ms, 43.5.
+    const bool past = R * ldc * (int64_t)sizeof(OutT) > (512LL << 20) && ldc * (int64_t)sizeof(OutT) % 128 == 0 &&
+                      reinterpret_cast<uintptr_t>(C) % 128 == 0;
     const int64_t m_blocks = (R + PM - 1) / PM;
     const int64_t n_blocks = ((int64_t)V + PN - 1) / PN;
     const int W = (int)(gridDim.x >> 3);
@@ -539,7 +544,9 @@ __global__ __launch_bounds__(512, 1) void bigram_gemm_persistent(const uint16_t 
                         const int64_t m = m0 + wm * 64 + i * 32 + row;
                         const int64_t n = n0 + wn * 128 + ps * kCols + piece * kPerPiece;
                         OutT *gp = C + m * ldc + n;
-                        if (interior) {
+                        if (interior && past) {
+                            __builtin_nontemporal_store(val[p], reinterpret_cast<u32x4 *>(gp));
+                        } else if (interior) {
                             *reinterpret_cast<u32x4 *>(gp) = val[p];
                         } else if (m < R && n < V) {
                             if (vec_store && n + kPerPiece <= V) {

@@ -1086,7 +1086,8 @@ void launch_type(as_ctx *ctx, int kid, const StepArgs &a, int32_t top_k, float t
     const bool has_p = top_p > 0.f && top_p < 1.f;
     // (compute units' worth of rows beyond which a wave takes a row; counts on longer rows, and a nucleus after them, never)
     const bool counts = TOPK && top_k > kWaveTopK;
-    const int64_t waves = most <= 64 * 8 ? (!TOPK ? 4 : counts ? 12 : 6) : !TOPK ? 16 : !counts || (!has_p && a.V <= 6144) ? 20 : 1 << 30;
+    const bool table = counts && has_p && top_k <= 64 && most > 64 * 4;      // (4816 rows of 3315, k = 50, p = 0.73: 34 / 38)
+    const int64_t waves = most <= 64 * 8 ? (table ? 1 << 30 : !TOPK ? 4 : counts ? 12 : 6) : !TOPK ? 16 : !counts || (!has_p && a.V <= 6144) ? 20 : 1 << 30;
     if (most <= 64 * 16 && a.rows > waves * (int64_t)ctx->num_cus) {
         if (most <= 64 * 8) return launch_form<DT, 64, 8, false, TOPK, 5>(ctx, kid, a, top_k, top_p, thr_out);
         return launch_form<DT, 64, 16, false, TOPK, 4>(ctx, kid, a, top_k, top_p, thr_out);

@@ -78,10 +78,10 @@ static as_status grow(as_ctx *ctx, DeviceBuf &b, size_t bytes)
     return AS_OK;
 }
 
-// The same for a buffer that the call can do without.  The old one is given up only when the new one is there; what could
-// not be had once is not asked for again (the next call would wait for the stream and move the buffer in vain, each
-// time); and nothing is allocated under a capture, which it would end.
-static bool grow_if_possible(as_ctx *ctx, DeviceBuf &b, size_t bytes)
+// The same for a buffer that the call can do without, or with `less` bytes of it.  The old one is given up only when the new
+// one is there; what could not be had once is not asked for again (the next call would wait for the stream and move the
+// buffer in vain, each time); and nothing is allocated under a capture, which it would end.
+static bool grow_if_possible(as_ctx *ctx, DeviceBuf &b, size_t bytes, size_t less = 0)
 {
     if (b.bytes >= bytes) return true;
     if (b.refused) return false;
@@ -93,7 +93,7 @@ static bool grow_if_possible(as_ctx *ctx, DeviceBuf &b, size_t bytes)
     void *p = nullptr;
     if (!device_alloc(ctx, &p, bytes)) {
         b.refused = true;
-        return false;
+        if (b.bytes >= less || !device_alloc(ctx, &p, bytes = less)) return false;
     }
     if (b.ptr && (hipStreamSynchronize(ctx->stream) != hipSuccess || hipFree(b.ptr) != hipSuccess)) {
         (void)hipFree(p);          // (an earlier launch failed: the call's own launches report it)
@@ -475,14 +475,17 @@ static DecodeSizes decode_asks(as_ctx *ctx, int64_t rows, int32_t T, bool masses
     return decode_sizes(V, esz, rows, T, masses);
 }
 
-// Makes the workspace of a decode.  A table of kept rows that cannot be had is done without.
+// Makes the workspace of a decode.  A table, of kept rows or of every token's, or its records that cannot be had are done
+// without.
 static as_status reserve_decode(as_ctx *ctx, int64_t rows, int32_t T, bool masses)
 {
     size_t few;
     const DecodeSizes z = decode_asks(ctx, rows, T, masses, few);
     (void)grow_if_possible(ctx, ctx->logits, few > z.preferred ? few : z.preferred);
     const as_status st = grow(ctx, ctx->logits, z.needed);
-    return st != AS_OK ? st : grow(ctx, ctx->state, z.state);
+    if (st != AS_OK) return st;
+    if (ctx->logits.bytes >= z.preferred) (void)grow_if_possible(ctx, ctx->state, z.state_preferred, z.state);
+    return grow(ctx, ctx->state, z.state);
 }
 
 // The same for a call that needs none of it
@@ -491,7 +494,7 @@ static void reserve_decode_if_possible(as_ctx *ctx, int64_t rows, int32_t T)
     size_t few;
     const DecodeSizes z = decode_asks(ctx, rows, T, false, few);
     (void)grow_if_possible(ctx, ctx->logits, few > z.preferred ? few : z.preferred);
-    (void)grow_if_possible(ctx, ctx->state, z.state);
+    (void)grow_if_possible(ctx, ctx->state, ctx->logits.bytes >= z.preferred ? z.state_preferred : z.state, z.state);
 }
 
 // Lays a decode's state out and takes its table of logits: rows of row_bytes, `masses` if they are group masses.  by_sums:
@@ -506,7 +509,8 @@ static as_status decode_state(as_ctx *ctx, const as_model *model, int32_t B, int
     bool keep = (kept_rows_most(V, R, T, row_bytes) > 0 || kept_rows_few(V, R, T, row_bytes) > 0) &&
                 keeping_pays(ctx, model, R, T, by_sums) && (size_t)(kept_rows * row_bytes) <= ctx->logits.bytes;
     // (timed decodes keep their rows where they can: a step's launches are told apart then)
-    s.table = table_rows(V, R, T, row_bytes) > 0 && (size_t)(V * row_bytes) <= ctx->logits.bytes && !(keep && ctx->prof.on) &&
+    s.table = table_rows(V, R, T, row_bytes) > 0 && (size_t)(V * row_bytes) <= ctx->logits.bytes &&
+              table_state(V, R, form != kTableRows) <= ctx->state.bytes && !(keep && ctx->prof.on) &&
               table_pays(ctx, model, R, T, form, keep, by_sums);
     if (s.table) {
         keep = false;

@@ -107,13 +107,20 @@ inline EncodeTables encode_tables(int64_t V, int64_t esz, int64_t rows, int64_t 
 }
 
 // What a decode reserves: logits (or group masses), a row of them per row, which every form can do with, or a table
-// that is preferred where it can be had; and the state: codes, tokens, flags, the tables of shared rows in any form, and
-// the sums of kept rows.  A decode of logits leaves room for one of group masses of its size, and for an encode of its
-// size a column and kPlainChunk rows at a time.
+// that is preferred where it can be had (of kept rows, or of every token's); and the state: codes, tokens, flags, the
+// tables of shared rows in any form, and the sums of kept rows, or with the records of a table of every token's rows, which is
+// done without where they cannot be had.  A decode of logits leaves room for one of group masses of its size, and for an
+// encode of its size a column and kPlainChunk rows at a time.
 constexpr int64_t kPlainChunk = 1024;
 struct DecodeSizes {
-    size_t needed, preferred, state;         // bytes
+    size_t needed, kept, preferred;          // bytes of logits
+    size_t state, state_preferred;
 };
+// The state of a decode from a table: records (where its steps work from them), codes, prev twice, the table's tokens, flags.
+inline size_t table_state(int64_t V, int64_t rows, bool with_records)
+{
+    return (size_t)((with_records ? V * kTableRecord : 0) + (3 * rows + V) * 4 + rows);
+}
 inline DecodeSizes decode_sizes(int64_t V, int64_t esz, int64_t rows, int64_t T, bool masses)
 {
     const int64_t lb = logits_row_bytes(V, esz), mb = mass_row_bytes(V);
@@ -121,15 +128,15 @@ inline DecodeSizes decode_sizes(int64_t V, int64_t esz, int64_t rows, int64_t T,
     DecodeSizes z;
     z.needed = (size_t)(rows * larger(masses ? 0 : lb, mb));
     const int64_t table = masses ? 0 : table_rows(V, rows, T, lb), table_masses = table_rows(V, rows, T, mb);
-    z.preferred = (size_t)larger(larger((int64_t)z.needed, larger(kept * lb, kept_masses * mb)), larger(table * lb, table_masses * mb));
+    z.kept = (size_t)larger((int64_t)z.needed, larger(kept * lb, kept_masses * mb));
+    z.preferred = (size_t)larger((int64_t)z.kept, larger(table * lb, table_masses * mb));
     const int64_t sums = one_tile_row(V, esz) && T >= 3 ? smaller(V, rows * (V > 4 * rows ? smaller(T, 4) : T)) * kRowSums : 0;
     // (codes, prev, order, token of rows that are not kept; mark, slot, fill, or token of rows that are)
     const size_t steps = (size_t)((sums + 4 * rows + 4 * V + T + 1) * 4 + rows);
-    // (a table's records; codes, prev twice, its tokens)
-    const size_t whole = (size_t)((one_tile_row(V, esz) ? table * kTableRecord : 0) + (3 * rows + V) * 4 + rows);
-    const size_t state = steps > whole ? steps : whole;
     const size_t column = encode_tables(V, esz, rows, rows, rows, smaller(rows, kPlainChunk), false).bytes;
-    z.state = state > column ? state : column;
+    z.state = steps > column ? steps : column;
+    const size_t whole = table > 0 ? table_state(V, rows, one_tile_row(V, esz)) : 0;
+    z.state_preferred = whole > z.state ? whole : z.state;
     return z;
 }
 

@@ -144,3 +144,24 @@ def test_decode_from_a_table_replays_from_a_graph(top_k, ldt):
     other.close()
     ctx.close()
     model.close()
+
+
+@pytest.mark.parametrize("top_k", [0, 10])
+def test_decode_without_the_memory_for_the_records(top_k):
+    """They are 17 MB, a row per code 2 and the rest of the state a third of one: a cap between them takes the table away,
+    not the decode."""
+    V, d, N, T = 16000, 128, 64, 64
+    model, ctx, prompts, u, _ = _setup(V, d, 2, N // 2, "bf16", "bf16", 3.0)
+    ctx.set_tuning("kept_rows", 3)
+    out = torch.empty((2, N // 2, T), dtype=torch.int32, device="cuda")
+    assert _logits_launches(ctx, lambda: B.as_decode(ctx, model, prompts, N // 2, T, u, TEMP, top_k, 1.0, 1, out)) == 1
+    small = B.Ctx(N, V, torch.bfloat16)
+    small.set_tuning("workspace_mib", 10)
+    got = torch.empty_like(out)
+    for _ in range(2):
+        B.as_decode(small, model, prompts, N // 2, T, u, TEMP, top_k, 1.0, 1, got)
+        torch.cuda.synchronize()
+        assert torch.equal(got, out) and B.lib().as_last_error(small._h) == b""
+    small.close()
+    ctx.close()
+    model.close()

@@ -15,8 +15,11 @@ extern "C" {
 void sizes(int64_t V, int64_t esz, int64_t rows, int64_t T, int masses, int64_t *out)
 {
     const DecodeSizes z = decode_sizes(V, esz, rows, T, masses != 0);
-    out[0] = (int64_t)z.needed; out[1] = (int64_t)z.preferred; out[2] = (int64_t)z.state;
+    out[0] = (int64_t)z.needed; out[1] = (int64_t)z.kept; out[2] = (int64_t)z.preferred; out[3] = (int64_t)z.state;
+    out[4] = (int64_t)z.state_preferred;
 }
+int64_t table(int64_t V, int64_t rows, int64_t T, int64_t row_bytes) { return table_rows(V, rows, T, row_bytes); }
+int64_t record() { return kTableRecord; }
 void encode(int64_t V, int64_t esz, int64_t rows, int64_t T, int64_t *out)
 {
     const EncodeSizes z = encode_sizes(V, esz, rows, T);
@@ -54,6 +57,8 @@ def lib(tmp_path_factory):
     L.window.argtypes, L.window.restype = [i64] * 2, i64
     L.kept.argtypes, L.kept.restype = [i64] * 4, i64
     L.few.argtypes, L.few.restype = [i64] * 4, i64
+    L.table.argtypes, L.table.restype = [i64] * 4, i64
+    L.record.restype = i64
     L.add.argtypes, L.add.restype = [i64] * 2, None
     L.covers.argtypes = [i64] * 2
     L.row_bytes.argtypes, L.row_bytes.restype = [i64, i64, ctypes.c_int], i64
@@ -61,9 +66,9 @@ def lib(tmp_path_factory):
 
 
 def _sizes(lib, V, esz, rows, T, masses=False):
-    out = (ctypes.c_int64 * 3)()
+    out = (ctypes.c_int64 * 5)()
     lib.sizes(V, esz, rows, T, int(masses), out)
-    return dict(zip(("needed", "preferred", "state"), out))
+    return dict(zip(("needed", "kept", "preferred", "state", "state_preferred"), out))
 
 
 def _log(rng, lo, hi):
@@ -93,7 +98,7 @@ def test_a_smaller_decode_finds_the_workspace_of_a_larger_one(lib):
 
 def test_what_a_decode_reserves_holds_every_form_of_it(lib):
     rng = random.Random(6)
-    kept_at_all = 0
+    kept_at_all = tables = 0
     for (V, esz, R, T), _ in _pairs():
         N = rng.choice([1, 2, 3, R])
         B = max(1, R // N)
@@ -112,9 +117,18 @@ def test_what_a_decode_reserves_holds_every_form_of_it(lib):
                 by_sums = 68 * K if not masses and V * esz % 16 == 0 and V * esz <= 65536 else 0
                 forms += [2 * R + R + K + 2 * V + K + T + 1 + by_sums]
             assert z["state"] >= max(forms) * 4 + R, (V, esz, R, T, masses)
+            # a table of every token's rows: records where rows are of one tile, codes, prev twice, the tokens, flags.  No
+            # state that a decode has to have holds its records
+            assert z["preferred"] >= z["kept"] >= z["needed"] and z["state_preferred"] >= z["state"]
+            if lib.table(V, R, T, rb):
+                tables += 1
+                records = V * lib.record() if not masses and V * esz % 16 == 0 and V * esz <= 65536 else 0
+                assert V * rb <= 4 << 30 and z["preferred"] >= V * rb
+                assert z["state_preferred"] >= records + (3 * R + V) * 4 + R
+            assert z["state"] <= max((68 * min(V, 4 * R) + 4 * R + 4 * V + T + 1) * 4 + R, lib.tables(V, esz, R, R, R, min(R, 1024), 0))
             # ... and an encode of its size, a column at a time
             assert z["state"] >= lib.tables(V, esz, R, R, R, min(R, 1024), 0)
-    assert kept_at_all > 1000
+    assert kept_at_all > 1000 and tables > 1000
 
 
 def test_sizes_that_a_shorter_decode_once_took_more_for(lib):

@@ -475,13 +475,19 @@ static DecodeSizes decode_asks(as_ctx *ctx, int64_t rows, int32_t T, bool masses
     return decode_sizes(V, esz, rows, T, masses);
 }
 
+// Its table: the largest that it may want, or if that cannot be had the kept rows' alone
+static void reserve_table(as_ctx *ctx, const DecodeSizes &z, size_t few)
+{
+    (void)grow_if_possible(ctx, ctx->logits, few > z.preferred ? few : z.preferred, few > z.kept ? few : z.kept);
+}
+
 // Makes the workspace of a decode.  A table, of kept rows or of every token's, or its records that cannot be had are done
 // without.
 static as_status reserve_decode(as_ctx *ctx, int64_t rows, int32_t T, bool masses)
 {
     size_t few;
     const DecodeSizes z = decode_asks(ctx, rows, T, masses, few);
-    (void)grow_if_possible(ctx, ctx->logits, few > z.preferred ? few : z.preferred);
+    reserve_table(ctx, z, few);
     const as_status st = grow(ctx, ctx->logits, z.needed);
     if (st != AS_OK) return st;
     if (ctx->logits.bytes >= z.preferred) (void)grow_if_possible(ctx, ctx->state, z.state_preferred, z.state);
@@ -493,7 +499,7 @@ static void reserve_decode_if_possible(as_ctx *ctx, int64_t rows, int32_t T)
 {
     size_t few;
     const DecodeSizes z = decode_asks(ctx, rows, T, false, few);
-    (void)grow_if_possible(ctx, ctx->logits, few > z.preferred ? few : z.preferred);
+    reserve_table(ctx, z, few);
     (void)grow_if_possible(ctx, ctx->state, ctx->logits.bytes >= z.preferred ? z.state_preferred : z.state, z.state);
 }
 

@@ -96,6 +96,21 @@ def test_a_kept_table_that_is_refused_is_not_asked_for_again():
     job.close()
 
 
+def test_kept_rows_where_a_table_of_every_token_is_refused():
+    """8000 rows are 128 MB, the 7600 that four steps of 1900 codes can come to 122; a cap between them."""
+    V, d, N, T = 8000, 512, 1900, 4
+    job = Job(V, d, N)
+    want = job.decode(N, T)
+    small = job.context()
+    small.set_tuning("workspace_mib", 118)
+    small.set_tuning("kept_rows", 2)
+    small.profile(True)
+    assert torch.equal(job.decode(N, T, ctx=small), want)
+    assert small.profile_read(0)[1] == 2 * T              # (from sums: two launches a step)
+    small.close()
+    job.close()
+
+
 def _same(a, b):
     return all(torch.equal(x, y) for x, y in zip(a, b))
 

@@ -34,12 +34,20 @@
  *     same or a smaller size (no more rows, no more steps; any temperature,
  *     truncation and model) allocate nothing and can be captured.  A decode
  *     takes a row of logits per code, or room for a row per token of the
- *     vocabulary where those are more: from a vocabulary of up to four times
- *     the codes, three steps on, and then at most 4 GiB (from a larger one
- *     over three or four steps, a row per code and step if the first call of
- *     the size is such a one); without that room it does with a row per code.  Its state is 17 bytes a code and 16 a token
+ *     vocabulary where those are more, at most 4 GiB:
+ *       - from a vocabulary of up to four times the codes, three steps on;
+ *       - for a table of all tokens' rows, four steps on, where
+ *         steps * (codes + 6e6 / tokens) is at least 1.25 times the tokens, and
+ *         the tokens are at most 128 times the codes or the table at most
+ *         512 MiB.  (Whether the table is made depends on the model's rank and
+ *         the truncation as well; the room for it does not.)
+ *     (From a larger vocabulary over three or four steps: a row per code and
+ *     step if the first call of the size is such a one.)  Without that room it
+ *     does with a row per code.  Its state is 17 bytes a code and 16 a token
  *     of the vocabulary, and 272 a row of the table that it may keep, or if
- *     more 34 bytes a code and 276 for each of up to 1024 codes.
+ *     more 34 bytes a code and 276 for each of up to 1024 codes; and with room
+ *     for a table of all tokens' rows 1060 bytes a token and 13 a code if that
+ *     is more and can be had.
  *     (as_decode_fused reserves for decodes of its own kind only, an eighth
  *     to a sixteenth: a first as_decode after it takes more.)
  *   - One context must not be used from two host threads at once.

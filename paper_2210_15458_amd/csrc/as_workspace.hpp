@@ -44,11 +44,16 @@ inline int64_t kept_rows_few(int64_t V, int64_t rows, int64_t T, int64_t row_byt
 
 // The rows of a table of every token's logits row, made before the first step, or 0 where no decode of the size wants one:
 // a row for each of V tokens against T steps of `rows` rows and of the launches that a table spares, which cost what
-// 6e6 / V rows cost (6 us at a rank of 512), within kKeptBytes.  (Whether one is made: table_pays.)
+// 6e6 / V rows cost (6 us at a rank of 512), within kKeptBytes.  A call is not to take memory out of proportion to what it
+// works on: a table beyond kTableBytes has at most 128 times the decode's own rows.  (16 codes over many steps of 32128, which
+// are out by that, would have 2 GB for 1 MB, and be faster from 260 steps on: 512 steps 2.1 ms, 5.1 a row per code.)  The
+// rank is not known here; of sizes spread over 500 to 64000 tokens, 1 to 2000 codes, 4 to 512 steps and ranks of 128 to
+// 1024, 3 % reserve a table that is then not made, 112 MiB of it on average.  (Whether one is made: table_pays.)
 constexpr int64_t kTableRecord = 1056;       // bytes that a step reads of a row before its logits: RowRecord, CandRecord
+constexpr int64_t kTableBytes = 512LL << 20;
 inline int64_t table_rows(int64_t V, int64_t rows, int64_t T, int64_t row_bytes)
 {
-    if (T < 4 || V * row_bytes > kKeptBytes) return 0;
+    if (T < 4 || V * row_bytes > kKeptBytes || (V > 128 * rows && V * row_bytes > kTableBytes)) return 0;
     return (double)T * ((double)rows + 6e6 / (double)V) >= 1.25 * (double)V ? V : 0;
 }
 

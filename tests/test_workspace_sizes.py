@@ -120,10 +120,14 @@ def test_what_a_decode_reserves_holds_every_form_of_it(lib):
             # a table of every token's rows: records where rows are of one tile, codes, prev twice, the tokens, flags.  No
             # state that a decode has to have holds its records
             assert z["preferred"] >= z["kept"] >= z["needed"] and z["state_preferred"] >= z["state"]
-            if lib.table(V, R, T, rb):
+            if not lib.table(V, R, T, rb):
+                assert z["preferred"] <= max(z["kept"], V * lib.row_bytes(V, esz, 1) if lib.table(V, R, T, lib.row_bytes(V, esz, 1)) else 0)
+            else:
                 tables += 1
                 records = V * lib.record() if not masses and V * esz % 16 == 0 and V * esz <= 65536 else 0
-                assert V * rb <= 4 << 30 and z["preferred"] >= V * rb
+                assert V * rb <= 4 << 30 and z["preferred"] >= V * rb and (V <= 128 * R or V * rb <= 512 << 20)
+                # what the header says (4 bytes a record's row: the token; codes and flags beside prev twice)
+                assert T >= 4 and T * (R + 6e6 / V) >= 1.25 * V and records + (3 * R + V) * 4 + R <= 1060 * V + 13 * R
                 assert z["state_preferred"] >= records + (3 * R + V) * 4 + R
             assert z["state"] <= max((68 * min(V, 4 * R) + 4 * R + 4 * V + T + 1) * 4 + R, lib.tables(V, esz, R, R, R, min(R, 1024), 0))
             # ... and an encode of its size, a column at a time
@@ -137,6 +141,16 @@ def test_sizes_that_a_shorter_decode_once_took_more_for(lib):
         assert _sizes(lib, V, esz, rows, short)["preferred"] <= _sizes(lib, V, esz, rows, long)["preferred"]
     assert _sizes(lib, 32128, 2, 65536, 16)["needed"] == 65536 * 64256
     assert _sizes(lib, 32128, 2, 8000, 4)["preferred"] == 8000 * 64256       # (V > 4 x 8000)
+
+
+def test_few_codes_take_no_table_out_of_proportion(lib):
+    for steps in (64, 256, 1024, 1 << 20):
+        for rows in (1, 16, 250):
+            z = _sizes(lib, 32128, 2, rows, steps)                           # (a table: 2 GB and 34 MB)
+            assert z["preferred"] == rows * 64256 or z["preferred"] <= 512 << 20, (rows, steps)
+            assert z["state_preferred"] == z["state"] <= 8 << 20
+    assert _sizes(lib, 32128, 2, 1024, 64)["preferred"] == 32128 * 64256     # (31 times the codes)
+    assert _sizes(lib, 16000, 2, 1, 64)["preferred"] == 16000 * 32000        # (488 MiB)
 
 
 def test_a_table_over_few_steps_is_made_by_first_calls_only(lib):

@@ -1172,17 +1172,20 @@ void launch_chain(as_ctx *ctx, const as_model *m, const int32_t *prev, int64_t r
 // (1/N) sum_i s(x_i) per prompt (Sec. 4.2) for additive per-token scores: s(x) = sum of score[x_t] up to
 // and including the first EOS.  One block per prompt, 2^width lanes (at most a wave) per sequence, its tokens side by side:
 // bound by the two dependent loads of a round, of which a thread per sequence made T, one after another (64 x 16 x 128 tokens 36
-// us, now 6).  fp64 sums in a fixed order.
-__global__ __launch_bounds__(1024) void estimate_kernel(const int32_t *tokens, int32_t N, int32_t T, int32_t V,
+// us, now 6).  A block has 1, 4 or 16 waves: no more than its sequences fill, nor than the chip holds twice over all prompts;
+// otherwise many prompts of few sequences wait for idle waves to start and end (us, by prompts x sequences x tokens, 16 waves
+// always / by size: 65536 x 1 x 1 116 / 16.6, 65536 x 4 x 8 117 / 16.5, 8192 x 300 x 1 17.8 / 5.9).  fp64 sums in a fixed order.
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void estimate_kernel(const int32_t *tokens, int32_t N, int32_t T, int32_t V,
                                                         const float *score, int32_t eos_id, double *est, int width)
 {
-    __shared__ double part[16];
+    __shared__ double part[WAVES];
     const int64_t b = blockIdx.x;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int per = 64 >> width, sub = lane >> width, at = lane & ((1 << width) - 1);
     const unsigned long long before = ((1ull << at) - 1ull) << (sub << width);
     double acc = 0.0;
-    for (int64_t i = (int64_t)wave * per + sub; i - sub < N; i += 16 * per) {
+    for (int64_t i = (int64_t)wave * per + sub; i - sub < N; i += WAVES * per) {
         const int32_t *seq = tokens + (b * N + i) * T;
         for (int32_t t = at; t - at < T; t += 64) {              // (more than one round with the wave's whole width only)
             const bool in = i < N && t < T;
@@ -1197,7 +1200,7 @@ __global__ __launch_bounds__(1024) void estimate_kernel(const int32_t *tokens, i
     __syncthreads();
     if (threadIdx.x == 0) {
         double all = 0.0;
-        for (int w = 0; w < 16; ++w) all += part[w];
+        for (int w = 0; w < WAVES; ++w) all += part[w];
         est[b] = all / (double)N;
     }
 }
@@ -1222,8 +1225,14 @@ as_status launch_estimate(as_ctx *ctx, const int32_t *tokens, int32_t B, int32_t
     if (B == 0) return AS_OK;
     int width = 0;
     while (width < 6 && (1 << width) < T) ++width;
-    hipLaunchKernelGGL(estimate_kernel, dim3((unsigned)B), dim3(1024), 0, ctx->stream, tokens, N, T, ctx->V, score,
-                       eos_id, est_out, width);
+    const int64_t filled = ((int64_t)N + (64 >> width) - 1) / (64 >> width), room = 64LL * ctx->num_cus / B;
+    auto go = [&](auto kernel, int waves) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)B), dim3(64 * waves), 0, ctx->stream, tokens, N, T, ctx->V, score, eos_id, est_out,
+                           width);
+    };
+    if (filled > 4 && room >= 16) go(estimate_kernel<16>, 16);
+    else if (filled > 1 && room >= 4) go(estimate_kernel<4>, 4);
+    else go(estimate_kernel<1>, 1);
     AS_HIP_TRY(ctx, hipGetLastError());
     return AS_OK;
 }

@@ -9,7 +9,9 @@ pytestmark = pytest.mark.gpu
 
 
 # one token, lengths that fill a share of a wave, a whole one, and more than one; more sequences than a block has places
-@pytest.mark.parametrize("Bn,N,T", [(1, 1, 1), (3, 1100, 1), (2, 37, 3), (5, 70, 33), (2, 17, 64), (3, 5, 65), (1, 33, 200)])
+@pytest.mark.parametrize("Bn,N,T", [(1, 1, 1), (3, 1100, 1), (2, 37, 3), (5, 70, 33), (2, 17, 64), (3, 5, 65), (1, 33, 200),
+                                    # one wave and four a prompt, with more sequences than they hold
+                                    (5000, 70, 1), (4097, 3, 40), (2000, 9, 40)])
 @pytest.mark.parametrize("eos", [-1, 1])
 def test_estimate_of_any_shape(Bn, N, T, eos):
     V = 50

@@ -217,7 +217,7 @@ struct SelectArgs {              // a sampling step from the sums of rows that c
 // What a decode from a table of every token's logits row reads of a row before its logits, kTableRecord apart.
 struct RowRecord {               // sums of step_tile_kernel's chunks (as_tile.hpp)
     struct {
-        double before, upto;     // the mass before each chunk, and with it, relative to R (beyond fp64: the row's plain form)
+        double before, upto;     // the mass before each chunk, and with it, relative to R (the last no number: the row's plain form)
     } chunk[64];
     float ref[4], R;             // the waves' references, the largest of them
     float thr;                   // keep threshold
@@ -228,10 +228,16 @@ struct CandRecord {              // the candidates of topk_tile_kernel
         float w;                 // ... its own (0: not kept), and its token
         int32_t token;
     } cand[64];
-    double S;                    // the mass of all; no number: the row's plain form, with ...
-    float thr;                   // ... this threshold
+    double S;                    // the mass of all; no number: the row's plain form
+};
+struct PlainRecord {             // the sums of generic_step_row (as_row.hpp), in a record of either kind that is marked so
+    double run[64];              // the mass before every fourth thread's elements
+    double S, run_last;          // of all; before the last thread's that have any ...
+    float ref, thr;              // what they are relative to; keep threshold
+    int32_t last;                // ... and that thread
 };
 static_assert(sizeof(RowRecord) <= kTableRecord && sizeof(CandRecord) <= kTableRecord && kTableRecord % 16 == 0, "records fit");
+static_assert(sizeof(PlainRecord) <= 1000, "a plain record leaves the marks alone: RowRecord's last sum, CandRecord's S");
 
 struct WalkArgs {                // steps t0 .. t1 of a decode from such a table
     const void *logits;          // [V, ld]

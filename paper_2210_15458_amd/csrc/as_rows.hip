@@ -138,17 +138,18 @@ __global__ __launch_bounds__(256, 4) void row_records_kernel(const void *logits,
     constexpr int ITERS = kTileIters;
     constexpr int kShare = ITERS * 64;
     __shared__ TileSums ts;
+    __shared__ GenericScratch gen;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t r = blockIdx.x;
+    const T *const row = reinterpret_cast<const T *>(logits) + r * ld;
     const int32_t nvec = V / EPV, v0 = wave * kShare;
     f32x4 *const my_sums = reinterpret_cast<f32x4 *>(ts.chunk_sum + wave * ITERS);
     if (v0 >= nvec) {                                            // past the row's end
         if (lane < ITERS / 4) my_sums[lane] = f32x4{0.f, 0.f, 0.f, 0.f};
         if (lane == 0) ts.share_ref[wave] = kRefFloor;
     } else {
-        const unsigned char *const base =
-            reinterpret_cast<const unsigned char *>(reinterpret_cast<const T *>(logits) + r * ld) + (size_t)v0 * 16u;
+        const unsigned char *const base = reinterpret_cast<const unsigned char *>(row) + (size_t)v0 * 16u;
         int32_t mych = (nvec - v0 - lane + 63) >> 6;
         mych = mych < 0 ? 0 : (mych > ITERS ? ITERS : mych);
         const uint32_t off0 = (uint32_t)lane * 16u;
@@ -173,7 +174,7 @@ __global__ __launch_bounds__(256, 4) void row_records_kernel(const void *logits,
         if (lane == 0) ts.share_ref[wave] = rw;
     }
     __syncthreads();
-    if (wave == 0) write_row_record(ts, -__builtin_inff(), reinterpret_cast<RowRecord *>(records + r * kTableRecord), lane);
+    write_row_record(ts, row, V, k, -__builtin_inff(), gen, reinterpret_cast<RowRecord *>(records + r * kTableRecord), lane, wave);
 }
 
 // Steps t0 .. t1 of a decode from a table of every token's logits row, a wave per code through all of them: no row waits
@@ -186,10 +187,8 @@ __global__ __launch_bounds__(256) void walk_kernel(WalkArgs a)
     using T = typename Elem<DT>::T;
     constexpr int EPV = Elem<DT>::kPerVec, ITERS = kTileIters;
     constexpr bool HAS_THR = FORM == kTableNucleus;
-    __shared__ double tot[4][256];
     const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t r = (int64_t)blockIdx.x * 4 + wave;
+    const int64_t r = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (r >= a.rows) return;
     const int32_t nvec = a.V / EPV;
     const float k = a.k;
@@ -216,7 +215,7 @@ __global__ __launch_bounds__(256) void walk_kernel(WalkArgs a)
                 const int32_t mine = rec->cand[lane].token;
                 if (!(S < (double)__builtin_inff())) {
                     float c_next;
-                    tok = generic_pick_row<T>(row, a.V, k, rec->thr, code, tot[wave], c_next);
+                    tok = generic_pick_row(row, a.V, k, code, reinterpret_cast<const PlainRecord *>(at), c_next);
                     code = c_next;
                 } else {
                     const double tau = (double)code * S;
@@ -245,7 +244,7 @@ __global__ __launch_bounds__(256) void walk_kernel(WalkArgs a)
                 const float thr = HAS_THR ? read_lane(meta, 5) : -__builtin_inff();
                 if (!(S < (double)__builtin_inff())) {
                     float c_next;
-                    tok = generic_pick_row<T>(row, a.V, k, thr, code, tot[wave], c_next);
+                    tok = generic_pick_row(row, a.V, k, code, reinterpret_cast<const PlainRecord *>(at), c_next);
                     code = c_next;
                 } else {
                     const double tau = (double)code * S;

@@ -1474,10 +1474,8 @@ __global__ __launch_bounds__(kThreads, 4) void topk_tile_kernel(StepArgs a, int3
         const uint32_t thr_key = radix_threshold<AS_BF16>(sc.radix, row, V, a.temp, top_k, HAS_P ? top_p : 1.f);
         __syncthreads();
         if constexpr (TABLE) {
-            if (threadIdx.x == 0) {
-                rec->S = __builtin_nan("");
-                rec->thr = Key<AS_BF16>::from_key(thr_key);
-            }
+            if (threadIdx.x == 0) rec->S = __builtin_nan("");
+            write_plain_record(row, V, a.k, Key<AS_BF16>::from_key(thr_key), sc.gen, reinterpret_cast<PlainRecord *>(rec));
         } else {
             generic_step_row<uint16_t>(a, r, Key<AS_BF16>::from_key(thr_key), sc.gen);
         }
@@ -1569,10 +1567,7 @@ __global__ __launch_bounds__(kThreads, 4) void topk_tile_kernel(StepArgs a, int3
         rec->cand[lane].before = bef;
         rec->cand[lane].w = w;
         rec->cand[lane].token = idx;
-        if (lane == 0) {
-            rec->S = S;
-            rec->thr = -__builtin_inff();
-        }
+        if (lane == 0) rec->S = S;
         return;
     }
     const double tau = (double)code * S;
@@ -1877,8 +1872,7 @@ __global__ __launch_bounds__(kThreads, 4) void nucleus_tile_kernel(StepArgs a, f
         const uint32_t thr_key = radix_threshold<AS_BF16>(sc.radix, row, V, a.temp, 0, top_p);
         __syncthreads();
         if constexpr (TABLE) {
-            if (threadIdx.x < 64) rec->chunk[threadIdx.x].upto = __builtin_nan("");
-            if (threadIdx.x == 0) rec->thr = Key<AS_BF16>::from_key(thr_key);
+            write_plain_row(row, V, a.k, Key<AS_BF16>::from_key(thr_key), sc.gen, rec);
         } else {
             generic_step_row<uint16_t>(a, r, Key<AS_BF16>::from_key(thr_key), sc.gen);
         }
@@ -1933,7 +1927,7 @@ __global__ __launch_bounds__(kThreads, 4) void nucleus_tile_kernel(StepArgs a, f
     }
     __syncthreads();
     if constexpr (TABLE) {
-        if (wave == 0) write_row_record(tn.sums, thr, rec, lane);
+        write_row_record(tn.sums, row, V, a.k, thr, sc.gen, rec, lane, wave);
         return;
     }
     tile_select<DT, true>(a, r, code, thr, raw, R, mych, ragged, v0, lane, wave, tn.sums, sc.gen);

@@ -269,8 +269,19 @@ __device__ __forceinline__ void tile_finish(const StepArgs &a, int64_t r, float 
     write_row(a, r, o);
 }
 
-// The record of a row whose chunk sums are in LDS: what tile_select makes of them, for steps to come (one wave).
-__device__ __forceinline__ void write_row_record(const TileSums &ts, float thr, RowRecord *rec, int lane)
+// The record of a row in its plain form (a block; gen free to write)
+template <class T>
+__device__ __forceinline__ void write_plain_row(const T *row, int32_t V, float k, float thr, GenericScratch &gen, RowRecord *rec)
+{
+    if (threadIdx.x == 0) rec->chunk[63].upto = __builtin_nan("");
+    write_plain_record(row, V, k, thr, gen, reinterpret_cast<PlainRecord *>(rec));
+}
+
+// The record of a row whose chunk sums are in LDS: what tile_select makes of them, for steps to come.  Every thread of the
+// block calls it.
+template <class T>
+__device__ __forceinline__ void write_row_record(const TileSums &ts, const T *row, int32_t V, float k, float thr, GenericScratch &gen,
+                                                 RowRecord *rec, int lane, int wave)
 {
     constexpr int NW = kTileWaves, ITERS = kTileIters;
     float R = ts.share_ref[0];
@@ -278,6 +289,12 @@ __device__ __forceinline__ void write_row_record(const TileSums &ts, float thr, 
     for (int w = 1; w < NW; ++w) R = fmaxf(R, ts.share_ref[w]);
     const double cv = (double)ldexpf(ts.chunk_sum[lane], shift_of(ts.share_ref[lane / ITERS], R));
     const double cincl = wave_scan_add(cv);
+    if (!(read_lane(cincl, 63) < (double)__builtin_inff())) {
+        __syncthreads();                   // (gen may share ts's place)
+        write_plain_row(row, V, k, thr, gen, rec);
+        return;
+    }
+    if (wave != 0) return;
     rec->chunk[lane].before = cincl - cv;
     rec->chunk[lane].upto = cincl;
     if (lane < NW) rec->ref[lane] = ts.share_ref[lane];

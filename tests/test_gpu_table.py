@@ -24,6 +24,13 @@ CASES = [
     (2001, 128, 2, 100, 16, 0, 1.0, "bf16", "bf16", TEMP, 3.0),      # ragged rows, a low temperature, k the wide kernel's
     (2000, 128, 2, 100, 16, 0, 1.0, "bf16", "bf16", 0.2, 3.0),
     (3000, 128, 1, 70, 20, 100, 0.9, "bf16", "f32", TEMP, 3.0),
+    # rows in their plain form: sums beyond fp32, runs of 256ths that end inside a vector; candidates and nuclei of rows that are
+    # all but equal
+    (8200, 128, 2, 40, 20, 0, 1.0, "bf16", "bf16", 0.4, 200.0),
+    (4100, 128, 2, 40, 20, 0, 1.0, "bf16", "f32", 0.4, 200.0),
+    (8200, 128, 2, 40, 20, 20, 1.0, "bf16", "bf16", 0.4, 0.001),
+    (8200, 128, 2, 40, 20, 0, 0.9, "bf16", "bf16", 0.4, 0.02),
+    (9000, 128, 2, 40, 20, 0, 0.9, "bf16", "bf16", 0.4, 200.0),
 ]
 
 

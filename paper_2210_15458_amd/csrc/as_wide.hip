@@ -76,8 +76,11 @@ __device__ __forceinline__ u64 fixed_weight(float e)
     return ((u64)hi << 32) | lo;
 }
 
-// NT = 64: a wave a row, for very many short ones; LDS for six waves a SIMD.  A bin is as wide as in SHORT, over half the octaves
-// (counts: as many octaves, twice the width), and a window takes fewer neighbours, so that it closes within the 64 threads.
+// NT = 64: a wave a row, for very many short ones.  A bin is as wide as in SHORT, over half the octaves (counts: as many octaves,
+// twice the width), and a window takes fewer neighbours, so that it mostly closes within the 64 threads.  The list is what the
+// waves of a unit leave room for: LDS is given out 1280 bytes at a time, 7680 for five waves a SIMD (16 bytes more of it cost
+// all rows 5 to 10 %), 10240 for four.  With 128 entries flat rows were selected all over: 8000 rows of 8000 bf16, p = 0.9, of
+// a standard deviation of 1 at a temperature of 0.9 249 us, 113 so, 109 in blocks; of 0.3 363, 111, 134.
 // SHORT: the forms for many short rows, where as many blocks as the unit's waves allow hide each other's block-wide
 // steps: half the LDS, 16 bins an octave where a nucleus's window is named (a bin's mass to a few parts in 10^4; the masses that
 // close it are the same).
@@ -88,7 +91,7 @@ template <int NT, bool MULTI, bool SHORT> struct WideShared {
     static constexpr int kOctaves = kWave ? 32 : 64;         // factors of two that the bins take ...
     static constexpr int kTopOctaves = kOctaves / 4;         // ... and of them above the reference
     static constexpr int kPerOctave = kBins / kOctaves;
-    static constexpr int kList = NT == 1024 ? 2048 : kWave ? 128 : SHORT ? 512 : 1024;
+    static constexpr int kList = NT == 1024 ? 2048 : kWave ? (SHORT ? 240 : 480) : SHORT ? 512 : 1024;
     static constexpr float kBeside = kWave ? 12.f : 32.f;    // logits of a nucleus's window on either side of its bin
     // (a row of 2^21 fp32 logits: 8193; with 512 threads, where two blocks are to share a unit's LDS, rows of fewer)
     static constexpr int kChunks = !MULTI ? 16 * kWaves + 1 : NT == 1024 ? 8704 : 2304;
@@ -303,7 +306,7 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
 
     // ------------------------------------------------------------------ top-k by a table of candidates
     if constexpr (TOPK) {
-        // the largest of the logits of 256 groups: of one, two or four lanes, or (a wave a row) of a lane's pieces by four
+        // the largest of the logits of 256 groups: of one, two or four lanes, or (a wave a row) of every fourth of a lane's pieces
         constexpr int kOwn = Sh::kWave ? 4 : 1;
         float gm[kOwn];
 #pragma unroll
@@ -313,8 +316,24 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
             land(p);
             float x[EPV];
             values(raw[p], x);
-            float &m = gm[p * kOwn / NP];
-            m = max3(m, vec_max<EPV>(x), m);
+            if constexpr (Sh::kWave) {
+                // (of short rows a half of a piece each, so that they fill as many groups as they can)
+                const bool halves = p < 2 && nwhole <= 128;
+                float lo = x[0], hi = x[EPV / 2];
+#pragma unroll
+                for (int e = 1; e < EPV / 2; ++e) {
+                    lo = fmaxf(lo, x[e]);
+                    hi = fmaxf(hi, x[EPV / 2 + e]);
+                }
+                if (halves) {
+                    gm[2 * p & 3] = fmaxf(gm[2 * p & 3], lo);
+                    gm[(2 * p + 1) & 3] = fmaxf(gm[(2 * p + 1) & 3], hi);
+                } else {
+                    gm[p & 3] = max3(gm[p & 3], lo, hi);
+                }
+            } else {
+                gm[0] = max3(gm[0], vec_max<EPV>(x), gm[0]);
+            }
         }
         if (top_k <= table_most<NT, NP>(V / EPV, top_p > 0.f && top_p < 1.f)) {
             if (tid == 0) {
@@ -543,6 +562,7 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
     // `base` is the weight above them; the key of the group of equal logits at which the running weight reaches
     // `need`, or 0 (no logit's key) if it does not get there.  all(put) puts every logit of the bin, for a list that did
     // not take them all.
+    constexpr uint32_t kAll = 0xffffffffu;                   // (n for the whole row)
     auto close = [&](uint32_t n, u64 base, double need, auto all)
                      __attribute__((always_inline)) -> uint32_t {
         if (n <= (uint32_t)NT) {
@@ -577,8 +597,31 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
             __syncthreads();
             return sh.sel;
         }
-        // all keys cut into kBins intervals of 2^s of them, from the top, then the one that closes, until it is one key
+        // the range of their keys (a wave's: it has 512 bins, and a bin or a window is narrow: two rounds then, of the whole 32
+        // bits four)
         uint32_t klo = 0u, khi = 0xffffffffu;
+        if (Sh::kWave && n != kAll) {
+            klo = 0xffffffffu;
+            khi = 0u;
+            auto span = [&](uint32_t key, u64) __attribute__((always_inline)) {
+                klo = min(klo, key);
+                khi = max(khi, key);
+            };
+            if (n <= (uint32_t)Sh::kList) {
+                for (uint32_t i = tid; i < n; i += NT) span(sh.key[i], 0ull);
+            } else {
+                all(span);
+            }
+#pragma unroll
+            for (int d = 32; d >= 1; d >>= 1) {
+                klo = min(klo, (uint32_t)__shfl_xor((int)klo, d, 64));
+                khi = max(khi, (uint32_t)__shfl_xor((int)khi, d, 64));
+            }
+            klo = (uint32_t)__builtin_amdgcn_readfirstlane((int)klo);
+            khi = (uint32_t)__builtin_amdgcn_readfirstlane((int)khi);
+            if (klo > khi) return 0u;
+        }
+        // it is cut into kBins intervals of 2^s keys, from the top, then the one that closes, until it is one key
         for (;;) {
             const uint32_t span = khi - klo;
             const int s = span >= (uint32_t)Sh::kBins ? 32 - __builtin_clz(span) - (31 - __builtin_clz((uint32_t)Sh::kBins)) : 0;
@@ -614,6 +657,10 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
         } else {
             for (int32_t i = tid; i <= nwhole; i += NT) f(piece_at(i));
         }
+    };
+    // the same many times over: from memory (the row's registers in a loop do not fit)
+    auto every_piece_again = [&](auto f) __attribute__((always_inline)) {
+        for (int32_t i = tid; i <= nwhole; i += NT) f(piece_at(i));
     };
     // One selection: the key of the group of equal logits at which the running weight, from the largest logit
     // down, reaches the goal.  COUNT: weights of 1 against top_k; otherwise masses of the logits >= floor_x
@@ -670,12 +717,12 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
         if (pick < 0) {
             if constexpr (!COUNT) return false;
             // fewer than k logits within the bins: by key over the whole row
-            const uint32_t key = close(0xffffffffu, 0ull, need, [&](auto put) __attribute__((always_inline)) {
-                for (int32_t i = tid; i <= nwhole; i += NT) {
+            const uint32_t key = close(kAll, 0ull, need, [&](auto put) __attribute__((always_inline)) {
+                every_piece_again([&](const u32x4 &v) __attribute__((always_inline)) {
                     float x[EPV];
-                    values(piece_at(i), x);
+                    values(v, x);
                     for (int e = 0; e < EPV; ++e) put(order_key(x[e]), 1ull);
-                }
+                });
             });
             thr = from_order_key(key);
             return key != 0u;
@@ -715,8 +762,8 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
         __syncthreads();
         const uint32_t n = sh.n;
         const uint32_t key = close(n, base, need, [&](auto put) __attribute__((always_inline)) {
-            // more than the list takes: from memory (the row's registers in a loop do not fit)
-            for (int32_t i = tid; i <= nwhole; i += NT) members(piece_at(i), put);
+            // more than the list takes
+            every_piece_again([&](const u32x4 &v) __attribute__((always_inline)) { members(v, put); });
         });
         thr = from_order_key(key);
         return key != 0u;                                    // (0: the weights of a NaN row)
@@ -750,9 +797,9 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
         // a bin's tally times the weight at its centre is its mass to a few parts in 10^5.  That names the bin in
         // which the nucleus closes, give or take a neighbour.  One pass then adds up the masses of all logits and
         // of those above a window of bins around it, as integers, and the latter's weights per chunk, and lists the
-        // logits of the window; the list is closed by the same integers, and what it keeps is added to its chunks.  If
-        // the window was off (neighbouring bins with more than 32 logits stay out of it) or the list overflows (heavy
-        // ties, flat rows), the general selection follows.
+        // logits of the window; the list is closed by the same integers, and what it keeps is added to its chunks.  If the
+        // list overflows (heavy ties, flat rows), the window is closed from the row.  If the window was off (neighbouring
+        // bins with more than kBeside logits stay out of it), the general selection follows.
         // (Adding the masses themselves takes 64-bit LDS atomics, 45 cycles a wave, or float ones, 300.)
         bool closed = false;
         const int s_bits = 31 - (32 - __builtin_clz((uint32_t)V));
@@ -925,24 +972,32 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
             const double need = (double)top_p * wide_total<NT>(sh.wave_d, unused);
             const double above = wide_total<NT>(sh.wave_e, unused);
             const uint32_t n = sh.n;
-            if (n <= (uint32_t)Sh::kList && above < need) {
-                const uint32_t key = close(n, (u64)above, need, [](auto) {});
+            if (above < need) {
+                // (more than the list takes: the window's logits by their keys, and the chunk sums over again)
+                const uint32_t key = close(n, (u64)above, need, [&](auto put) __attribute__((always_inline)) {
+                    every_piece_again([&](const u32x4 &v) __attribute__((always_inline)) {
+                        float x[EPV];
+                        values(v, x);
+#pragma unroll
+                        for (int e = 0; e < EPV; ++e) {
+                            const float y = fmaf(x[e], k, nr);
+                            if (y >= ylo && y <= yhi) put(order_key(x[e]), (u64)mass_of(fast_exp2(y)));
+                        }
+                    });
+                });
                 if (key != 0u) {
                     thr = from_order_key(key);
-                    for (uint32_t i = tid; i < n; i += NT)
-                        if (sh.key[i] >= key)
-                            add((lds_u64 *)sh.extra + sh.at[i],
-                                fixed_weight(fast_exp2(fmaf(from_order_key(sh.key[i]), k, nr))));
                     closed = true;
+                    summed = n <= (uint32_t)Sh::kList;
+                    if (summed)
+                        for (uint32_t i = tid; i < n; i += NT)
+                            if (sh.key[i] >= key)
+                                add((lds_u64 *)sh.extra + sh.at[i],
+                                    fixed_weight(fast_exp2(fmaf(from_order_key(sh.key[i]), k, nr))));
                 }
             }
         }
-        if (!closed) {
-            some = select(No{}, -__builtin_inff(), thr);
-            summed = false;
-        } else {
-            summed = true;
-        }
+        if (!closed) some = select(No{}, -__builtin_inff(), thr);
     }
     if (a.tokens_out == nullptr) {
         if (tid == 0) thr_out[r] = some ? thr : -__builtin_inff();
@@ -1076,7 +1131,11 @@ void launch_form(as_ctx *ctx, int kid, const StepArgs &a, int32_t top_k, float t
 // another wave, and what a block does in some 25 steps of its waves overlaps over rows instead (us, blocks / waves: nuclei, 1500
 // rows of 1500 bf16 20.5 / 14.9, 600 14.0 / 13.0, 14251 of 1923 119 / 63, 5252 of 3078 57 / 38, 4200 of 8001 58 / 56, 2600 42 /
 // 47; k = 40 2100 of 4001 18.6 / 16.3, 1500 of 3000 13.1 / 14.6, 9000 of 6001 53 / 47, 4200 of 8001 31 / 32; counts, k = 1000,
-// 4000 of 1500 30 / 18, 2100 of 4001 23 / 25, 9000 of 6001 79 / 77, 4200 of 8001 46 / 59).
+// 4000 of 1500 30 / 18, 2100 of 4001 23 / 25, 9000 of 6001 79 / 77 and on flat or steep rows 1.1 to 1.2 behind).  Those rows
+// have a standard deviation of 3 against the temperature; a wave has a shorter list, so flat rows decide whether its line holds:
+// of 0.3 at a temperature of 0.9, nuclei p = 0.9 4000 of 1500 37 / 23, 6000 of 3000 65 / 44, 3000 of 4000 41 / 47, 8000 of 8000
+// 134 / 111; k = 100 then p = 0.9 6000 of 1000 76 / 37, 6000 of 3000 63 / 63, which is behind only where the row is all but
+// constant (0.05: 62 / 121).
 template <int DT, bool TOPK>
 void launch_type(as_ctx *ctx, int kid, const StepArgs &a, int32_t top_k, float top_p, float *thr_out)
 {
@@ -1084,10 +1143,12 @@ void launch_type(as_ctx *ctx, int kid, const StepArgs &a, int32_t top_k, float t
     const int64_t most = ((int64_t)a.V + EPV - 1) / EPV;     // whole pieces of a row, whatever its alignment
     const bool many = a.rows > (int64_t)ctx->num_cus, lots = a.rows > 2 * (int64_t)ctx->num_cus;
     const bool has_p = top_p > 0.f && top_p < 1.f;
-    // (compute units' worth of rows beyond which a wave takes a row; counts on longer rows, and a nucleus after them, never)
+    // (compute units' worth of rows beyond which a wave takes a row; counts on longer rows, and a nucleus after the 64 best of a
+    // row of more than 256 pieces, never)
     const bool counts = TOPK && top_k > kWaveTopK;
     const bool table = counts && has_p && top_k <= 64 && most > 64 * 4;      // (4816 rows of 3315, k = 50, p = 0.73: 34 / 38)
-    const int64_t waves = most <= 64 * 8 ? (table ? 1 << 30 : !TOPK ? 4 : counts ? 12 : 6) : !TOPK ? 16 : !counts || (!has_p && a.V <= 6144) ? 20 : 1 << 30;
+    const int64_t never = 1LL << 40;
+    const int64_t waves = most <= 64 * 8 ? (table ? never : !TOPK ? 4 : counts ? 12 : 6) : !TOPK ? 16 : !counts ? 20 : never;
     if (most <= 64 * 16 && a.rows > waves * (int64_t)ctx->num_cus) {
         if (most <= 64 * 8) return launch_form<DT, 64, 8, false, TOPK, 5>(ctx, kid, a, top_k, top_p, thr_out);
         return launch_form<DT, 64, 16, false, TOPK, 4>(ctx, kid, a, top_k, top_p, thr_out);

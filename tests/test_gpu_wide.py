@@ -141,6 +141,15 @@ def test_a_wave_a_row(V, rows, dtype, sigma, temp):
         print("   ", compare_step(gpu, ref, V, label, trunc=True, codes=codes), flush=True)
 
 
+# rows of up to 128 pieces, whose candidates are bounded by halves of them, and the first above; windows and bins with more logits
+# than a wave's list
+@pytest.mark.parametrize("V,rows,dtype,sigma", [(1016, 3100, "bf16", 3.0), (1024, 3100, "bf16", 0.3), (1033, 3100, "bf16", 3.0),
+                                                (505, 3100, "f32", 3.0), (512, 3100, "f32", 0.3), (520, 3100, "f32", 3.0),
+                                                (4090, 3100, "bf16", 0.3), (8186, 5200, "bf16", 0.3), (4093, 5200, "f32", 0.2)])
+def test_a_wave_on_flat_and_on_short_rows(V, rows, dtype, sigma):
+    test_a_wave_a_row(V, rows, dtype, sigma, 0.9)
+
+
 # short rows, few of them: the largest k of the candidate table and the first that is counted, on either side of the lengths at
 # which that line moves
 @pytest.mark.parametrize("V,dtype,ks", [(4103, "bf16", (48, 49)), (4104, "bf16", (64, 65)), (2051, "f32", (48, 49)),

@@ -126,7 +126,8 @@ const char *as_last_error(const as_ctx *ctx);
  *                       it pays or not (bf16 weights, a rank that is a
  *                       multiple of 64 and at least 128, three steps);
  *                       3 = the rows of all tokens are made before the first
- *                       step wherever the decode's size makes room for them
+ *                       step wherever the decode's size makes room for them;
+ *                       4 = that is never done, the rest by choice
  */
 typedef enum {
     AS_TUNE_STEP_SHAPE = 0,
@@ -146,9 +147,8 @@ as_status as_ctx_set_tuning(as_ctx *ctx, as_tuning knob, int32_t value);
  * and the number of timed launches since the last read for
  *   kernel 0: fused sampling step   1: logits (bigram) kernel   2: threshold   3: interval (encode) step
  * and resets the counters.  (A decode that makes the logits rows of all tokens before its
- * first step has those launches under 1, what it makes of the rows under 2, and its steps, which
- * otherwise share one launch, a launch each under 0; one that can keep its rows from step to step
- * instead does that while it is profiled.)  At most 16384 launches per kernel are timed between
+ * first step has that launch under 1, what it makes of the rows under 2, and its steps, which
+ * share one launch, under 0.  Profiling changes nothing of what a call launches.)  At most 16384 launches per kernel are timed between
  * reads; further ones run untimed and are counted in *untimed.  Any output
  * pointer may be NULL.  Switching profiling on makes the first launches create
  * events (a host-side allocation).

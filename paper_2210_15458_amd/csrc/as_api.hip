@@ -514,9 +514,8 @@ static as_status decode_state(as_ctx *ctx, const as_model *model, int32_t B, int
     const int64_t kept_rows = smaller(V, R * larger((int64_t)T - 1, 0) + B);
     bool keep = (kept_rows_most(V, R, T, row_bytes) > 0 || kept_rows_few(V, R, T, row_bytes) > 0) &&
                 keeping_pays(ctx, model, R, T, by_sums) && (size_t)(kept_rows * row_bytes) <= ctx->logits.bytes;
-    // (timed decodes keep their rows where they can: a step's launches are told apart then)
     s.table = table_rows(V, R, T, row_bytes) > 0 && (size_t)(V * row_bytes) <= ctx->logits.bytes &&
-              table_state(V, R, form != kTableRows) <= ctx->state.bytes && !(keep && ctx->prof.on) &&
+              table_state(V, R, form != kTableRows) <= ctx->state.bytes &&
               table_pays(ctx, model, R, T, form, keep, by_sums);
     if (s.table) {
         keep = false;
@@ -614,7 +613,7 @@ static as_status fill_table(as_ctx *ctx, const as_model *model, const DecodeStat
     return launch_table_records(ctx, form, ctx->logits.ptr, ldw, temp, top_k, top_p, s.records);
 }
 
-// Its steps, in one launch (timed: a launch each, so that their times can be told apart)
+// Its steps, in one launch
 static as_status walk_table(as_ctx *ctx, const DecodeState &s, int64_t ldw, TableForm form, int64_t R, int32_t T,
                             const float *uniforms, float temp, int32_t eos_id, int32_t *tokens_out)
 {
@@ -622,13 +621,7 @@ static as_status walk_table(as_ctx *ctx, const DecodeState &s, int64_t ldw, Tabl
     a.logits = ctx->logits.ptr; a.records = s.records; a.ld = ldw; a.V = ctx->V; a.dtype = ctx->dtype;
     a.k = 1.44269504088896340736f / temp; a.rows = R; a.T = T; a.eos_id = eos_id; a.uniforms = uniforms;
     a.codes = s.codes; a.prev = s.prev; a.finished = s.fin; a.tokens = tokens_out;
-    const int32_t per = ctx->prof.on ? 1 : T;
-    for (a.t0 = 0; a.t0 < T; a.t0 = a.t1) {
-        a.t1 = T - a.t0 < per ? T : a.t0 + per;
-        const as_status st = launch_walk(ctx, form, a);
-        if (st != AS_OK) return st;
-    }
-    return AS_OK;
+    return launch_walk(ctx, form, a);
 }
 
 // as_decode and as_decode_ancestral: with `uniforms` the code of row r at step t is uniforms[t*R + r] and

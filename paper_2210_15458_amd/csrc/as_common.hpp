@@ -64,7 +64,8 @@ struct as_ctx {
     int gemm_shape = 0;            // logits: 1 = tile kernel, 2 = persistent also for few rows
     int thr_path = 0;              // truncation: 1 = radix select, 2 = resident where the row fits, 3 = wide for every row
     int gemm_gm = 0;               // logits kernel, many row tiles: workers of an XCD along the rows (tuning knob: 0 = default)
-    int kept_rows = 0;             // decodes: 1 = no logits rows kept from step to step, 2 / 3 = kept / a table of all wherever there is room
+    int kept_rows = 0;             // decodes: 1 = no logits rows kept from step to step, 2 / 3 = kept / a table of all wherever there is room,
+                                   // 4 = no table of all
     int workspace_mib = 0;         // largest buffer of the workspace, in MiB (tuning knob: 0 = as large as the device gives)
     int num_cus = 0;               // compute units of the device (the persistent logits kernel runs one block on each)
     std::string err;
@@ -239,7 +240,7 @@ struct PlainRecord {             // the sums of generic_step_row (as_row.hpp), i
 static_assert(sizeof(RowRecord) <= kTableRecord && sizeof(CandRecord) <= kTableRecord && kTableRecord % 16 == 0, "records fit");
 static_assert(sizeof(PlainRecord) <= 1000, "a plain record leaves the marks alone: RowRecord's last sum, CandRecord's S");
 
-struct WalkArgs {                // steps t0 .. t1 of a decode from such a table
+struct WalkArgs {                // the steps of a decode from such a table
     const void *logits;          // [V, ld]
     const unsigned char *records;
     int64_t ld;
@@ -247,9 +248,9 @@ struct WalkArgs {                // steps t0 .. t1 of a decode from such a table
     as_dtype dtype;
     float k;                     // log2(e)/temp
     int64_t rows;
-    int32_t T, t0, t1, eos_id;
+    int32_t T, eos_id;
     const float *uniforms;       // [T, rows] the codes, or null: carried in `codes`
-    float *codes;                // [rows], as are prev and finished: read at t0, written at t1
+    float *codes;                // [rows], as are prev and finished: read first, written last
     int32_t *prev;
     uint8_t *finished;
     int32_t *tokens;             // [rows, T]

@@ -1359,7 +1359,7 @@ static double product_us(const as_ctx *ctx, const as_model *m, double rows)
 // it has to be worse by 15 %.
 bool table_pays(const as_ctx *ctx, const as_model *m, int64_t rows, int32_t T, TableForm form, bool keep, bool by_sums)
 {
-    if (ctx->kept_rows != 0) return ctx->kept_rows == 3;
+    if (ctx->kept_rows != 0) return ctx->kept_rows == 3;             // (4: no table)
     const double V = (double)m->V, R = (double)rows, row_us = V * (ctx->dtype == AS_BF16 ? 2.0 : 4.0) / 6e6;
     const double kept = V * (1.0 - exp(-R * (T - 1) / V)) / (T - 1);
     const double own = keep ? kept : sharing_pays(ctx, m, rows, T) ? V * (1.0 - exp(-R / V)) : R;      // rows a step

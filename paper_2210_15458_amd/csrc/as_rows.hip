@@ -177,7 +177,7 @@ __global__ __launch_bounds__(256, 4) void row_records_kernel(const void *logits,
     write_row_record(ts, row, V, k, -__builtin_inff(), gen, reinterpret_cast<RowRecord *>(records + r * kTableRecord), lane, wave);
 }
 
-// Steps t0 .. t1 of a decode from a table of every token's logits row, a wave per code through all of them: no row waits
+// The steps of a decode from a table of every token's logits row, a wave per code through all of them: no row waits
 // for another, so there is nothing between a code's steps but its own chain of loads.  A step reads the record of the
 // token before (and, for a plain or nucleus step, the KiB of logits that holds the code) and gives what step_tile_kernel,
 // nucleus_tile_kernel or topk_tile_kernel would, bit for bit.
@@ -196,12 +196,12 @@ __global__ __launch_bounds__(256) void walk_kernel(WalkArgs a)
     float code = a.uniforms ? 0.f : a.codes[r];
     bool ended = a.eos_id >= 0 && __builtin_amdgcn_readfirstlane((int)a.finished[r]) != 0;
     const float *const uniforms = a.uniforms ? a.uniforms + r : nullptr;
-    float u_next = uniforms ? uniforms[(int64_t)a.t0 * a.rows] : 0.f;
+    float u_next = uniforms ? uniforms[0] : 0.f;
     int32_t held = 0;                                            // the tokens of up to 64 steps, a lane each
-    for (int32_t t = a.t0; t < a.t1; ++t) {
+    for (int32_t t = 0; t < a.T; ++t) {
         if (uniforms) {
             code = u_next;
-            u_next = uniforms[(int64_t)(t + 1 < a.t1 ? t + 1 : t) * a.rows];
+            u_next = uniforms[(int64_t)(t + 1 < a.T ? t + 1 : t) * a.rows];
         }
         if (ended) {
             tok = a.eos_id;
@@ -271,9 +271,9 @@ __global__ __launch_bounds__(256) void walk_kernel(WalkArgs a)
             tok = __builtin_amdgcn_readfirstlane(tok);
             ended = a.eos_id >= 0 && tok == a.eos_id;
         }
-        const int at = (t - a.t0) & 63;
+        const int at = t & 63;
         held = lane == at ? tok : held;
-        if ((at == 63 || t + 1 == a.t1) && lane <= at) a.tokens[r * a.T + t - at + lane] = held;
+        if ((at == 63 || t + 1 == a.T) && lane <= at) a.tokens[r * a.T + t - at + lane] = held;
     }
     if (lane == 0) {
         if (!uniforms) a.codes[r] = code;

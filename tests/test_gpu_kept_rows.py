@@ -73,6 +73,7 @@ def test_kept_rows_replay_from_a_graph():
     ctx.close()
     with torch.cuda.stream(stream):
         ctx = B.Ctx(Bn * N, V, torch.bfloat16)
+        ctx.set_tuning("kept_rows", 2)
         out = torch.empty((Bn, N, T), dtype=torch.int32, device="cuda")
         eager = torch.empty_like(out)
         B.as_decode(ctx, model, prompts, N, T, u, TEMP, 0, 1.0, EOS, out)       # (makes the workspace)
@@ -106,8 +107,10 @@ def _step_launches(ctx, model, prompts, N, T, u, out):
                                           (8000, 512, 2048, 16, False), (32128, 512, 8192, 5, True), (32128, 512, 8000, 5, False),
                                           (32128, 512, 8000, 4, True), (3000, 64, 8192, 16, False)])
 def test_which_decodes_keep_rows(V, d, R, T, kept):
-    """Steps from sums are two launches: the library's choice, the knob's, and what the benchmark takes the choice to be."""
+    """Steps from sums are two launches: the library's choice where it makes no table of all tokens' rows, the knob's, and what
+    the benchmark takes the choice to be."""
     model, ctx, prompts, u = _setup(V, d, 1, R, "bf16", 3.0)
+    ctx.set_tuning("kept_rows", 4)
     prompts[0] = 7
     out = torch.empty((1, R, T), dtype=torch.int32, device="cuda")
     assert _step_launches(ctx, model, prompts, R, T, u, out) == (2 * T if kept else T)

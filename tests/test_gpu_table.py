@@ -61,6 +61,27 @@ def _loop(ctx, model, prompts, N, T, codes, uniforms, temp, top_k, top_p, eos, l
     return out, codes
 
 
+# on either side of the rule: by codes, by steps, by the rank
+@pytest.mark.parametrize("V,d,R,T,top_k,table", [(32128, 512, 1024, 64, 0, True), (32128, 512, 512, 24, 0, False),
+                                                 (32128, 512, 1024, 128, 40, True), (32128, 512, 64, 64, 0, False),
+                                                 (4096, 128, 256, 32, 0, True), (8000, 512, 4096, 16, 0, True),
+                                                 (8000, 512, 16, 4, 0, False), (16000, 128, 64, 64, 0, True), (16000, 1024, 16, 64, 0, False)])
+def test_which_decodes_make_a_table(V, d, R, T, top_k, table):
+    """The library's own choice, as it runs: a product and a walk for a table, a product a step otherwise."""
+    model, ctx, prompts, u, _ = _setup(V, d, 1, R, "bf16", "bf16", 3.0)
+    prompts[0] = 7
+    out = torch.empty((1, R, T), dtype=torch.int32, device="cuda")
+    ctx.profile(True)
+    B.as_decode(ctx, model, prompts, R, T, u, 1.0, top_k, 1.0, 1, out)
+    assert (ctx.profile_read(1)[1] == 1 and ctx.profile_read(0)[1] == 1) == table
+    ctx.profile(False)
+    want = out.clone()
+    B.as_decode(ctx, model, prompts, R, T, u, 1.0, top_k, 1.0, 1, out)
+    assert torch.equal(out, want)
+    ctx.close()
+    model.close()
+
+
 def _logits_launches(ctx, call):
     ctx.profile(True)
     call()
@@ -90,7 +111,7 @@ def test_decode_from_a_table_equals_the_loop_of_exported_calls(V, d, Bn, N, T, t
     assert torch.equal(out.view(R, T), want) and torch.equal(last, want_codes)
     assert (want == eos).any()
     out.fill_(-1)
-    assert _logits_launches(ctx, decode) < T              # (timed, a step a launch; and the table was what ran)
+    assert _logits_launches(ctx, decode) == 1             # (the table was what ran)
     assert torch.equal(out.view(R, T), want) and torch.equal(last, want_codes)
 
     uniforms = torch.rand(T, R, device="cuda", generator=g).clamp_max_(1.0 - 2.0 ** -24)

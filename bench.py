@@ -188,18 +188,21 @@ def step_counts(tokens, eos, prompts, shared, kept=False):
     return {"active": float(active.sum()) / T, "computed": float(np.mean(computed)), "fetched": float(np.mean(fetched))}
 
 
-def table_figures(V, esz, steps, T, active, top_k, step_samples, thr_samples, gemm_samples):
-    """The sampling side of decodes that make the logits rows of all tokens before their first step, per step of the decode
-    (known by their launches: a product, a launch that leaves the rows' records, one that walks them): every row once for
-    its record, then per code a record and, but for the candidates of top-k, a KiB of a row.  None for other decodes."""
-    if not (len(gemm_samples) == len(thr_samples) == len(step_samples) == steps) or T == 1:
+def table_figures(V, esz, steps, T, active, top_k, met, step_samples, thr_samples, gemm_samples):
+    """The sampling side of decodes whose steps work from records of the logits rows, per step of the decode (known by their
+    launches: a product, a launch that leaves the rows' records and one that walks them, once for the rows of all tokens, or a
+    few rounds of them for those that codes meet, at least `met`): every row once for its record, then per code a record and,
+    but for the candidates of top-k, a KiB of a row.  None for other decodes."""
+    n = len(gemm_samples)
+    if not (n == len(thr_samples) == len(step_samples) and n % steps == 0 and 0 < n < T * steps):
         return None
+    rows = V if n == steps else met
     total = float(np.sum(step_samples) + np.sum(thr_samples)) * 1e3
     return {"kernel": "the rows' records (row_records_kernel or the truncating kernel of the shape), then walk_kernel, inside as_decode",
-            "avg_launch_us": total / (T * steps), "records_us": float(np.mean(thr_samples)) * 1e3,
-            "walk_us": float(np.mean(step_samples)) * 1e3,
-            "bytes_per_launch": V * (V * esz + 1056.0) / T + active * (1056 + (0 if 0 < top_k < V else 1024) + 18),
-            "rows_computed_per_launch": V * float(steps) / len(gemm_samples)}
+            "avg_launch_us": total / (T * steps), "records_us": float(np.sum(thr_samples)) / steps * 1e3,
+            "walk_us": float(np.sum(step_samples)) / steps * 1e3,
+            "bytes_per_launch": rows * (V * esz + 1056.0) / T + active * (1056 + (0 if 0 < top_k < V else 1024) + 18),
+            "rows_computed_per_launch": rows * float(steps) / n}
 
 
 def compact_leg(cfg_id, top_k, top_p, steps, warmup):
@@ -238,7 +241,8 @@ def compact_leg(cfg_id, top_k, top_p, steps, warmup):
     cnt = step_counts(tokens, eos, Bn, rows_shared(V, d, R, T, cfg["dtype"], compute_units()), kept)
     bytes_per_row = V * 2 + 18
     bytes_per_launch = cnt["fetched"] * V * 2 + cnt["active"] * 18      # logits rows in use, each once; codes, tokens, flags
-    table = table_figures(V, 2, steps, T, cnt["active"], top_k, step_samples, thr_samples, gemm_samples)
+    met = conditioned_tokens(tokens.view(R, T).cpu().numpy(), prompts.cpu().numpy(), eos)
+    table = table_figures(V, 2, steps, T, cnt["active"], top_k, met, step_samples, thr_samples, gemm_samples)
     if kept and by_sums and not table:
         # a step is two launches: the new rows once, then per code its row's sums and one KiB of it
         bytes_per_launch = cnt["computed"] * V * 2 + cnt["active"] * (272 + 1024 + 18)
@@ -266,7 +270,7 @@ def compact_leg(cfg_id, top_k, top_p, steps, warmup):
                         "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s"}}
     out["logits_gemm"]["frac"] = out["logits_gemm"]["achieved"] / MFMA_BF16_PEAK_TFLOPS
     if table:
-        out["sampling"]["records_us_per_launch"], out["sampling"]["walk_us_per_launch"] = table["records_us"], table["walk_us"]
+        out["sampling"]["records_us_per_decode"], out["sampling"]["walk_us_per_decode"] = table["records_us"], table["walk_us"]
     elif len(thr_samples):
         out["sampling"]["threshold_kernel_us"] = float(np.mean(thr_samples)) * 1e3
     if top_k <= 0 and not (0.0 < top_p < 1.0) and R <= 4096:
@@ -409,7 +413,8 @@ def main():
     bytes_per_row = V * esz + 18           # the logits row + code in/out, token, flags
     bytes_per_launch = cnt["fetched"] * V * esz + cnt["active"] * 18
     step_avg_us = step_ms / max(step_n, 1) * 1e3
-    table = table_figures(V, esz, args.steps, T, cnt["active"], top_k, step_samples, thr_samples, gemm_samples)
+    met = conditioned_tokens(tokens.view(R, T).cpu().numpy(), prompts.cpu().numpy(), eos)
+    table = table_figures(V, esz, args.steps, T, cnt["active"], top_k, met, step_samples, thr_samples, gemm_samples)
     if table:
         step_avg_us, bytes_per_launch, cnt["computed"] = table["avg_launch_us"], table["bytes_per_launch"], table["rows_computed_per_launch"]
     # (a launch that does a whole decode has no logits rows in memory)
@@ -465,7 +470,7 @@ def main():
         out["roofline"]["first_step"] = spread(by_step[:, 0])
         out["roofline"]["late_steps"] = spread(by_step[:, T // 2:].ravel())
     if table:
-        out["roofline"]["records_us_per_launch"], out["roofline"]["walk_us_per_launch"] = table["records_us"], table["walk_us"]
+        out["roofline"]["records_us_per_decode"], out["roofline"]["walk_us_per_decode"] = table["records_us"], table["walk_us"]
     elif thr_n:
         out["threshold_kernel"] = {"avg_launch_us": thr_ms / thr_n * 1e3, "launches": thr_n}
 

@@ -46,7 +46,7 @@
  *     does with a row per code.  Its state is 17 bytes a code and 16 a token
  *     of the vocabulary, and 272 a row of the table that it may keep, or if
  *     more 34 bytes a code and 276 for each of up to 1024 codes; and with room
- *     for a table of all tokens' rows 1060 bytes a token and 13 a code if that
+ *     for a table of all tokens' rows 1068 bytes a token and 13 a code if that
  *     is more and can be had.
  *     (as_decode_fused reserves for decodes of its own kind only, an eighth
  *     to a sixteenth: a first as_decode after it takes more.)
@@ -127,7 +127,9 @@ const char *as_last_error(const as_ctx *ctx);
  *                       multiple of 64 and at least 128, three steps);
  *                       3 = the rows of all tokens are made before the first
  *                       step wherever the decode's size makes room for them;
- *                       4 = that is never done, the rest by choice
+ *                       4 = that is never done, the rest by choice; 5 = as
+ *                       3, of the tokens that codes come to alone, made as
+ *                       they do (weights as for 2, rows of one tile)
  */
 typedef enum {
     AS_TUNE_STEP_SHAPE = 0,

@@ -461,6 +461,9 @@ struct DecodeState {
     unsigned char *records;      // [V, kTableRecord], where steps work from records
     int32_t *token;              // [V] the rows' tokens
     int32_t *prev_next;          // [R] the other half of prev (steps that read it as row_ids)
+    // the same of the tokens that codes come to alone, made as they do
+    bool demand;
+    Demand rows;
 };
 
 // What a decode of `rows` rows asks for (as_workspace.hpp): `few` a table of kept rows that only a first call of its size may
@@ -514,9 +517,11 @@ static as_status decode_state(as_ctx *ctx, const as_model *model, int32_t B, int
     const int64_t kept_rows = smaller(V, R * larger((int64_t)T - 1, 0) + B);
     bool keep = (kept_rows_most(V, R, T, row_bytes) > 0 || kept_rows_few(V, R, T, row_bytes) > 0) &&
                 keeping_pays(ctx, model, R, T, by_sums) && (size_t)(kept_rows * row_bytes) <= ctx->logits.bytes;
-    s.table = table_rows(V, R, T, row_bytes) > 0 && (size_t)(V * row_bytes) <= ctx->logits.bytes &&
-              table_state(V, R, form != kTableRows) <= ctx->state.bytes &&
-              table_pays(ctx, model, R, T, form, keep, by_sums);
+    const bool room = table_rows(V, R, T, row_bytes) > 0 && (size_t)(V * row_bytes) <= ctx->logits.bytes &&
+                      table_state(V, R, form != kTableRows) <= ctx->state.bytes;
+    const TableChoice choice = room ? table_pays(ctx, model, R, T, form, keep, by_sums) : kNoTable;
+    s.table = choice != kNoTable;
+    s.demand = choice == kTableDemand;
     if (s.table) {
         keep = false;
         unsigned char *w = static_cast<unsigned char *>(ctx->state.ptr);
@@ -527,6 +532,14 @@ static as_status decode_state(as_ctx *ctx, const as_model *model, int32_t B, int
         s.prev_next = s.prev + R;
         s.token = s.prev_next + R;
         s.fin = reinterpret_cast<uint8_t *>(s.token + V);
+        if (s.demand) {
+            int32_t *const q = s.token + V;
+            s.rows = Demand{q, q + V, s.prev_next, s.token, q + 2 * V};
+            static_assert((kRounds + 3) * Demand::kNumbers <= 48, "table_state");
+            s.fin = reinterpret_cast<uint8_t *>(q + 2 * V + 48);
+            st = launch_demand_clear(ctx, s.rows, R);
+            if (st != AS_OK) return st;
+        }
         s.share = false;
         s.tables = RowShare{};
         s.sums = nullptr;
@@ -610,18 +623,42 @@ static as_status fill_table(as_ctx *ctx, const as_model *model, const DecodeStat
 {
     const as_status st = launch_bigram_logits(ctx, model, s.token, ctx->V, ctx->logits.ptr, ldw);
     if (st != AS_OK || form == kTableRows) return st;
-    return launch_table_records(ctx, form, ctx->logits.ptr, ldw, temp, top_k, top_p, s.records);
+    return launch_table_records(ctx, form, ctx->logits.ptr, ldw, temp, top_k, top_p, s.records, ctx->V, RowRange{});
 }
 
-// Its steps, in one launch
-static as_status walk_table(as_ctx *ctx, const DecodeState &s, int64_t ldw, TableForm form, int64_t R, int32_t T,
-                            const float *uniforms, float temp, int32_t eos_id, int32_t *tokens_out)
+// What its steps are given; they share one launch.
+static WalkArgs walk_args(as_ctx *ctx, const DecodeState &s, int64_t ldw, int64_t R, int32_t T, const float *uniforms, float temp,
+                          int32_t eos_id, int32_t *tokens_out)
 {
     WalkArgs a{};
     a.logits = ctx->logits.ptr; a.records = s.records; a.ld = ldw; a.V = ctx->V; a.dtype = ctx->dtype;
     a.k = 1.44269504088896340736f / temp; a.rows = R; a.T = T; a.eos_id = eos_id; a.uniforms = uniforms;
     a.codes = s.codes; a.prev = s.prev; a.finished = s.fin; a.tokens = tokens_out;
-    return launch_walk(ctx, form, a);
+    return a;
+}
+
+// Steps from rows made on demand, in rounds: rows for the tokens that codes wait for (the prompts at first; which those are and
+// how many only the device knows), their records, and every code through its steps until it meets a token without a row.  A
+// round takes each code a step at least, so T of them are enough; if codes still wait after kRounds, or tokens turn out to
+// come evenly, the rows of all tokens that are missing are made (demand_claim_kernel).
+static as_status decode_on_demand(as_ctx *ctx, const as_model *model, const DecodeState &s, TableForm form, int32_t B, float temp,
+                                  int32_t top_k, float top_p, WalkArgs a)
+{
+    a.slot = s.rows.slot; a.wanted = s.rows.wanted; a.at = s.rows.at;
+    for (a.every = 0; a.rows > 64 * ((int64_t)a.every + 1); a.every = 2 * a.every + 1) {}
+    const int32_t rounds = a.T <= kRounds + 1 ? a.T : kRounds + 1;
+    for (int32_t i = 0; i < rounds; ++i) {
+        const int64_t most = i == 0 ? smaller(B, ctx->V) : i == 1 ? smaller(a.rows, ctx->V) : ctx->V;
+        a.round = s.rows.round + i * Demand::kNumbers;
+        const RowRange range{a.round + Demand::kMade, a.round + Demand::kNumbers + Demand::kMade};
+        as_status st = launch_demand_claim(ctx, s.rows, i, a.T, a.every + 1, i == kRounds && a.T > rounds);
+        if (st == AS_OK) st = launch_bigram_logits(ctx, model, s.token, most, ctx->logits.ptr, a.ld, range);
+        if (st == AS_OK)
+            st = launch_table_records(ctx, form, ctx->logits.ptr, a.ld, temp, top_k, top_p, s.records, most, range);
+        if (st == AS_OK) st = launch_walk(ctx, form, a);
+        if (st != AS_OK) return st;
+    }
+    return AS_OK;
 }
 
 // as_decode and as_decode_ancestral: with `uniforms` the code of row r at step t is uniforms[t*R + r] and
@@ -662,11 +699,14 @@ static as_status decode_impl(as_ctx *ctx, const as_model *model, const int32_t *
     uint8_t *const fin = state.fin;
 
     st = launch_lattice(ctx, u, B, N, uniforms ? nullptr : codes, prompts, state.prev, fin, ctx->rid,
-                        state.table ? state.token : nullptr);
-    if (st == AS_OK && state.table) st = fill_table(ctx, model, state, ldw, form, temp, top_k, top_p);
+                        state.table && !state.demand ? state.token : nullptr, state.demand ? state.rows.wanted : nullptr);
+    if (st == AS_OK && state.table && !state.demand) st = fill_table(ctx, model, state, ldw, form, temp, top_k, top_p);
     if (st != AS_OK) return st;
     const bool walk = state.table && form != kTableRows;
-    if (walk) st = walk_table(ctx, state, ldw, form, R, T, uniforms, temp, eos_id, tokens_out);
+    if (walk) {
+        const WalkArgs a = walk_args(ctx, state, ldw, R, T, uniforms, temp, eos_id, tokens_out);
+        st = state.demand ? decode_on_demand(ctx, model, state, form, B, temp, top_k, top_p, a) : launch_walk(ctx, form, a);
+    }
     if (st != AS_OK) return st;
     for (int32_t t = 0; t < T && !walk; ++t) {
         StepRows sr;

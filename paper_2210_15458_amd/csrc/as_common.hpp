@@ -117,6 +117,11 @@ inline bool stream_rows(int64_t rows, int64_t ld, size_t esz)
     return (double)rows * (double)ld * (double)esz > 128.0 * 1024.0 * 1024.0;
 }
 
+// Rows begin .. end of a table, read on the device where only that knows them (end null: not so; begin null: 0).
+struct RowRange {
+    const int32_t *begin = nullptr, *end = nullptr;
+};
+
 struct StepArgs {
     const void *logits;
     int64_t rows;
@@ -139,7 +144,8 @@ struct StepArgs {
     const int32_t *row_ids;
     int32_t *prev_out;           // decode state: next step's conditioning token, or null
     const int32_t *order;        // a permutation of the rows that puts those with one logits row together, or null
-    unsigned char *records;      // the truncating one-tile kernels: not a step, but these records of the rows (else null)
+    unsigned char *records;      // the truncating one-tile kernels: not a step, but these records of the rows (else null) ...
+    RowRange range;              // ... in this range of them, where only the device knows it
 };
 
 struct IntervalArgs {
@@ -189,11 +195,6 @@ struct ChunkArgs {               // a chunk of an encode's logits rows: s0 .. s0
     float k;                     // log2(e)/temp
     const float *thr;            // [rows] keep thresholds, or null
     const float *sums;           // [rows, kRowSums]
-};
-
-// Rows begin .. end of a table, read on the device where only that knows them (end null: not so; begin null: 0).
-struct RowRange {
-    const int32_t *begin = nullptr, *end = nullptr;
 };
 
 struct RowSumsArgs {
@@ -254,7 +255,21 @@ struct WalkArgs {                // the steps of a decode from such a table
     int32_t *prev;
     uint8_t *finished;
     int32_t *tokens;             // [rows, T]
+    // rows made on demand, else null:
+    const int32_t *slot;         // [V] a token's row, or -1 where it is not there
+    int32_t *wanted;             // [V] set for a token that a code waits for
+    int32_t *at;                 // [rows] steps done
+    int32_t *round;              // this round's numbers (Demand) ...
+    int32_t every;               // ... to which one code in every + 1 adds (a power of two)
 };
+struct Demand {                  // rows made on demand: which, for whom
+    int32_t *slot, *wanted, *at, *token;         // (token: of each row)
+    // of round i, kNumbers apart: rows made before it, whether a code waits after it, and of a share of the codes the tokens that
+    // had a row and those that had none (the first of a code's round aside, which has one)
+    enum { kMade, kWaits, kMet, kMissed, kNumbers };
+    int32_t *round;
+};
+constexpr int32_t kRounds = 6;   // rounds of a decode before all rows that are still missing are made
 enum TableForm { kTablePlain, kTableNucleus, kTableTopK, kTableRows };    // what a step works from; kTableRows: the logits alone
 
 struct SmallArgs {               // a whole decode of a model that fits LDS
@@ -308,10 +323,10 @@ as_status launch_wide(as_ctx *ctx, const StepArgs &a, int32_t top_k, float top_p
 as_status launch_threshold(as_ctx *ctx, const void *logits, int64_t rows, int64_t ld,
                            const uint8_t *finished_in, const int32_t *row_ids,
                            float temp, int32_t top_k, float top_p, float *thr_out);
-// prev_out: the prompts, clamped to the vocabulary; table_out: 0 .. V-1
+// prev_out: the prompts, clamped to the vocabulary; table_out: 0 .. V-1; wanted_out: [V], set for the prompts
 as_status launch_lattice(as_ctx *ctx, const float *u, int32_t B, int32_t N, float *codes_out,
                          const int32_t *prompts, int32_t *prev_out, uint8_t *finished_out,
-                         int32_t *row_ids_out = nullptr, int32_t *table_out = nullptr);
+                         int32_t *row_ids_out = nullptr, int32_t *table_out = nullptr, int32_t *wanted_out = nullptr);
 as_status launch_estimate(as_ctx *ctx, const int32_t *tokens, int32_t B, int32_t N, int32_t T, const float *score,
                           int32_t eos_id, double *est_out);
 as_status launch_transpose(const void *U, void *Ut, int32_t d, int32_t V, as_dtype wdtype);
@@ -345,12 +360,16 @@ as_status launch_share_map(as_ctx *ctx, const RowShare &s, int32_t step, const i
                            int32_t *row_ids, bool sorted);
 bool keeping_pays(const as_ctx *ctx, const as_model *m, int64_t rows, int32_t T, bool by_sums);
 bool step_by_sums(const as_ctx *ctx, float temp);
-// a table of every token's logits row: whether it pays, its records, the steps from them
-bool table_pays(const as_ctx *ctx, const as_model *m, int64_t rows, int32_t T, TableForm form, bool keep, bool by_sums);
+// a table of every token's logits row, or of those that codes come to: whether it pays, its records, the steps from them
+enum TableChoice { kNoTable, kTableAll, kTableDemand };
+TableChoice table_pays(const as_ctx *ctx, const as_model *m, int64_t rows, int32_t T, TableForm form, bool keep, bool by_sums);
 TableForm table_form(const as_ctx *ctx, int64_t rows, float temp, int32_t top_k, float top_p);
 as_status launch_table_records(as_ctx *ctx, TableForm form, const void *logits, int64_t ld, float temp, int32_t top_k, float top_p,
-                               unsigned char *records);
-as_status launch_row_records(as_ctx *ctx, const void *logits, int64_t ld, float temp, unsigned char *records);
+                               unsigned char *records, int64_t rows, RowRange range);
+as_status launch_row_records(as_ctx *ctx, const void *logits, int64_t ld, float temp, unsigned char *records, int64_t rows,
+                             RowRange range);
+as_status launch_demand_clear(as_ctx *ctx, const Demand &d, int64_t rows);
+as_status launch_demand_claim(as_ctx *ctx, const Demand &d, int32_t i, int32_t T, int32_t each, bool last);
 as_status launch_walk(as_ctx *ctx, TableForm form, const WalkArgs &a);
 as_status launch_row_select(as_ctx *ctx, const SelectArgs &a);
 // the same for the positions of an encode (prev < 0: none): rows claimed, counted and scanned, the order left to the caller

@@ -17,7 +17,7 @@ namespace {
 
 __global__ void lattice_kernel(const float *u, int32_t B, int32_t N, float *codes,
                                const int32_t *prompts, int32_t *prev, uint8_t *finished, int32_t *row_ids, int32_t V,
-                               int32_t *table)
+                               int32_t *table, int32_t *wanted)
 {
     const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (table && idx < V) table[idx] = (int32_t)idx;     // the rows of a table of all tokens
@@ -27,6 +27,7 @@ __global__ void lattice_kernel(const float *u, int32_t B, int32_t N, float *code
     const double c = codes ? ((double)i + (double)u[b]) / (double)N : 0.0;
     if (codes) codes[idx] = fminf((float)c, 0x1.fffffep-1f);
     if (prev) prev[idx] = clamp_token(prompts[b], V);
+    if (wanted && i == 0) wanted[clamp_token(prompts[b], V)] = 1;
     if (finished) finished[idx] = 0;
     if (row_ids) row_ids[idx] = b;           // the first step's logits: one row per prompt
 }
@@ -1209,12 +1210,12 @@ __global__ __launch_bounds__(64 * WAVES) void estimate_kernel(const int32_t *tok
 
 as_status launch_lattice(as_ctx *ctx, const float *u, int32_t B, int32_t N, float *codes_out,
                          const int32_t *prompts, int32_t *prev_out, uint8_t *finished_out, int32_t *row_ids_out,
-                         int32_t *table_out)
+                         int32_t *table_out, int32_t *wanted_out)
 {
     const int64_t rows = (int64_t)B * N, n = table_out && ctx->V > rows ? ctx->V : rows;
     if (rows == 0) return AS_OK;
     hipLaunchKernelGGL(lattice_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, ctx->stream, u, B, N,
-                       codes_out, prompts, prev_out, finished_out, row_ids_out, ctx->V, table_out);
+                       codes_out, prompts, prev_out, finished_out, row_ids_out, ctx->V, table_out, wanted_out);
     AS_HIP_TRY(ctx, hipGetLastError());
     return AS_OK;
 }
@@ -1343,8 +1344,10 @@ static double product_us(const as_ctx *ctx, const as_model *m, double rows)
     const double thin = t.thin[0] < t.thin[1] ? (t.thin[0] < t.thin[2] ? t.thin[0] : t.thin[2])
                                               : (t.thin[1] < t.thin[2] ? t.thin[1] : t.thin[2]);
     // (the line for small products is low where every compute unit has several tiles)
-    const double tiles = ceil(rows / PM) * (double)(((int64_t)m->V + PN - 1) / PN), cus = ctx->num_cus > 0 ? ctx->num_cus : 1;
-    const double large = tiles > cus ? 4.0 + ceil(tiles / cus) * (1.72 * (double)m->d / PK + 2.3) : t.persistent;
+    const int64_t row_tiles = ((int64_t)rows + PM) / PM, n_blocks = ((int64_t)m->V + PN - 1) / PN;
+    const int W = ctx->num_cus / 8;
+    const double large = W > 0 && row_tiles * n_blocks > ctx->num_cus ?
+        4.0 + (double)tile_rounds(row_tiles, n_blocks, W, persistent_gm(ctx)) * (1.72 * (double)m->d / PK + 2.3) : t.persistent;
     return (thin < large ? thin : large) + (ctx->dtype == AS_BF16 ? 0.0 : rows * (double)m->V * 2.0 / 5e6);
 }
 
@@ -1355,19 +1358,36 @@ static double product_us(const as_ctx *ctx, const as_model *m, double rows)
 // k = 40, 1024 x 128 6548 / - / 1504; 65536 x 16 20260 / 2465 / 1808; 3605 x 126 of 1600 x 1024 5281 / 2052 / 267; 406 x 59 of
 // 504 x 128 538 / - / 77; 270 x 117 of 3424 x 832 1401 / - / 193; 1 x 73 of 657 x 19 fp32, k = 100 1056 / - / 838 (rows); 2004 x
 // 49 of 9640 x 768, k = 100 4178 / - / 2265 (rows); against the table: 5579 x 5 of 14277 x 192, fp32 logits 567 / 491 / 535, 12 x
-// 115 of 18904 x 896, fp32 (rows) 1431 / - / 1695.  With tokens that come less evenly than assumed a kept table fills less:
-// it has to be worse by 15 %.
-bool table_pays(const as_ctx *ctx, const as_model *m, int64_t rows, int32_t T, TableForm form, bool keep, bool by_sums)
+// 115 of 18904 x 896, fp32 (rows) 1431 / - / 1695; 2732 x 4 of 8744 x 576, k = 40 (rows) 280 / - / 308.
+//
+// All that is by tokens that come evenly, which is the table's best case: it has a row for each whatever comes.  Rows of one's
+// own cost what they cost by any tokens (ended codes included: their rows are computed too), but kept rows are fewer where
+// tokens are few.  So against those a table of all has to win by the least that they can take (on 300 tokens, measured / by the
+// line below: 65536 codes x 16 914 / 829, 65536 x 6 475 / 336, 16384 x 16 464 / 357, 8192 x 64 1005 / 995, 4096 x 16 274 / 239,
+// 5997 x 6 169 / 122); else rows are made on demand, for the tokens that codes come to, where steps work from
+// records.  us a decode, kept / table / on demand, 32128 x 512, on even tokens: 65536 x 16 2495 / 1729 /
+// 1998, 8192 x 64 3318 / 1580 / 1710, k = 40 16384 x 16 4007 / 1395 / 1601; with a Zipf bias 2501 / 1679 / 2058, 3089 / 1528 / 2217,
+// 3010 / 1363 / 1667; on 300 tokens 923 / 1658 / 515, 1008 / 1508 / 325, 2324 / 1347 / 225.  Behind kept rows where a low rank makes
+// their products cheap and tokens are neither even nor few: 9524 x 11 of 28256 x 128 878 / 765 / 890, Zipf 643 / 759 / 894, on 200
+// 263 / 755 / 184.
+TableChoice table_pays(const as_ctx *ctx, const as_model *m, int64_t rows, int32_t T, TableForm form, bool keep, bool by_sums)
 {
-    if (ctx->kept_rows != 0) return ctx->kept_rows == 3;             // (4: no table)
+    if (ctx->kept_rows == 3) return kTableAll;
+    if (ctx->kept_rows == 5) return form == kTableRows || !rows_on_device(ctx, m) ? kNoTable : kTableDemand;
+    if (ctx->kept_rows != 0) return kNoTable;
     const double V = (double)m->V, R = (double)rows, row_us = V * (ctx->dtype == AS_BF16 ? 2.0 : 4.0) / 6e6;
     const double kept = V * (1.0 - exp(-R * (T - 1) / V)) / (T - 1);
     const double own = keep ? kept : sharing_pays(ctx, m, rows, T) ? V * (1.0 - exp(-R / V)) : R;      // rows a step
     const double sampling = 3.5 + R * row_us;
-    const double without = product_us(ctx, m, own) + (keep ? 12.0 : 0.0) + (keep && by_sums ? 4.0 + R * 0.0007 + own * row_us : sampling);
+    // (the first step's product has a row per prompt)
+    const double without = 5.0 + (T - 1) * product_us(ctx, m, own) +
+                           T * ((keep ? 12.0 : 0.0) + (keep && by_sums ? 4.0 + R * 0.0007 + own * row_us : sampling));
     const double step = form == kTableRows ? sampling : 3.0 + R * 0.0006;
     const double table = product_us(ctx, m, V) + (form == kTableRows ? 0.0 : 4.0 + V * row_us);
-    return table + T * step < (keep ? 0.85 : 0.95) * T * without;
+    if (table + T * step >= (keep ? 0.9 : 0.95) * without) return kNoTable;
+    const double least = 40.0 + T * (10.0 + R * 0.0006);
+    if (!keep || table + (form == kTableRows ? 0.0 : T * step) < least) return kTableAll;
+    return form == kTableRows ? kNoTable : kTableDemand;
 }
 
 as_status launch_share_clear(as_ctx *ctx, const RowShare &s, int32_t T)

@@ -131,7 +131,7 @@ __global__ __launch_bounds__(256) void row_select_kernel(SelectArgs q)
 // The same sums as a RowRecord: what a decode from a table of every token's logits row needs of a row, a block per row.
 template <int DT, bool NT>
 __global__ __launch_bounds__(256, 4) void row_records_kernel(const void *logits, int64_t ld, int32_t V, float k,
-                                                             unsigned char *records)
+                                                             unsigned char *records, RowRange range)
 {
     using T = typename Elem<DT>::T;
     constexpr int EPV = Elem<DT>::kPerVec;
@@ -141,7 +141,8 @@ __global__ __launch_bounds__(256, 4) void row_records_kernel(const void *logits,
     __shared__ GenericScratch gen;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t r = blockIdx.x;
+    const int64_t r = blockIdx.x + (range.begin ? *range.begin : 0);
+    if (range.end && r >= *range.end) return;
     const T *const row = reinterpret_cast<const T *>(logits) + r * ld;
     const int32_t nvec = V / EPV, v0 = wave * kShare;
     f32x4 *const my_sums = reinterpret_cast<f32x4 *>(ts.chunk_sum + wave * ITERS);
@@ -181,7 +182,10 @@ __global__ __launch_bounds__(256, 4) void row_records_kernel(const void *logits,
 // for another, so there is nothing between a code's steps but its own chain of loads.  A step reads the record of the
 // token before (and, for a plain or nucleus step, the KiB of logits that holds the code) and gives what step_tile_kernel,
 // nucleus_tile_kernel or topk_tile_kernel would, bit for bit.
-template <int DT, TableForm FORM>
+//
+// DEMAND: only the rows that codes have come to are there.  A code goes on until it meets a token without a row, asks for it
+// and leaves its state for the next round.
+template <int DT, TableForm FORM, bool DEMAND = false>
 __global__ __launch_bounds__(256) void walk_kernel(WalkArgs a)
 {
     using T = typename Elem<DT>::T;
@@ -189,16 +193,27 @@ __global__ __launch_bounds__(256) void walk_kernel(WalkArgs a)
     constexpr bool HAS_THR = FORM == kTableNucleus;
     const int lane = threadIdx.x & 63;
     const int64_t r = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (DEMAND && blockIdx.x == 0 && threadIdx.x == 0)
+        a.round[2 * Demand::kNumbers + Demand::kMade] = a.round[Demand::kNumbers + Demand::kMade];     // (for the next to add to)
     if (r >= a.rows) return;
+    const int32_t t0 = DEMAND ? __builtin_amdgcn_readfirstlane(a.at[r]) : 0;
+    if (DEMAND && t0 >= a.T) return;
     const int32_t nvec = a.V / EPV;
     const float k = a.k;
     int32_t tok = __builtin_amdgcn_readfirstlane(clamp_token(a.prev[r], a.V));
     float code = a.uniforms ? 0.f : a.codes[r];
     bool ended = a.eos_id >= 0 && __builtin_amdgcn_readfirstlane((int)a.finished[r]) != 0;
     const float *const uniforms = a.uniforms ? a.uniforms + r : nullptr;
-    float u_next = uniforms ? uniforms[0] : 0.f;
+    float u_next = uniforms ? uniforms[(int64_t)t0 * a.rows] : 0.f;
     int32_t held = 0;                                            // the tokens of up to 64 steps, a lane each
-    for (int32_t t = 0; t < a.T; ++t) {
+    int32_t t = t0, live = 0;
+    for (; t < a.T; ++t) {
+        int32_t place = tok;
+        if constexpr (DEMAND) {
+            if (!ended) place = __builtin_amdgcn_readfirstlane(a.slot[tok]);
+            if (place < 0) break;
+            live += ended ? 0 : 1;
+        }
         if (uniforms) {
             code = u_next;
             u_next = uniforms[(int64_t)(t + 1 < a.T ? t + 1 : t) * a.rows];
@@ -206,8 +221,8 @@ __global__ __launch_bounds__(256) void walk_kernel(WalkArgs a)
         if (ended) {
             tok = a.eos_id;
         } else {
-            const unsigned char *const at = a.records + (int64_t)tok * kTableRecord;
-            const T *const row = reinterpret_cast<const T *>(a.logits) + (int64_t)tok * a.ld;
+            const unsigned char *const at = a.records + (int64_t)place * kTableRecord;
+            const T *const row = reinterpret_cast<const T *>(a.logits) + (int64_t)place * a.ld;
             if constexpr (FORM == kTableTopK) {
                 const CandRecord *const rec = reinterpret_cast<const CandRecord *>(at);
                 const double S = rec->S, before = rec->cand[lane].before;
@@ -271,15 +286,82 @@ __global__ __launch_bounds__(256) void walk_kernel(WalkArgs a)
             tok = __builtin_amdgcn_readfirstlane(tok);
             ended = a.eos_id >= 0 && tok == a.eos_id;
         }
-        const int at = t & 63;
+        const int at = (t - t0) & 63;
         held = lane == at ? tok : held;
         if ((at == 63 || t + 1 == a.T) && lane <= at) a.tokens[r * a.T + t - at + lane] = held;
+    }
+    if constexpr (DEMAND) {
+        const int n = (t - t0) & 63;
+        if (t < a.T && lane < n) a.tokens[r * a.T + t - n + lane] = held;
+        if (lane == 0) {
+            a.at[r] = t;
+            if (t < a.T) {
+                // (looked at first, and few add: 65536 codes at one address, or at some, took 45 to 70 us a round)
+                if (a.wanted[tok] == 0) a.wanted[tok] = 1;
+                if (a.round[Demand::kWaits] == 0) a.round[Demand::kWaits] = 1;
+            }
+            if ((r & a.every) == 0) {
+                if (live > 1) atomicAdd(&a.round[Demand::kMet], live - 1);
+                if (t < a.T) atomicAdd(&a.round[Demand::kMissed], 1);
+            }
+        }
     }
     if (lane == 0) {
         if (!uniforms) a.codes[r] = code;
         a.prev[r] = tok;
         if (a.eos_id >= 0) a.finished[r] = ended ? 1 : 0;
     }
+}
+
+__global__ __launch_bounds__(256) void demand_clear_kernel(Demand d, int32_t V, int64_t rows)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < V) {
+        d.slot[i] = -1;
+        d.wanted[i] = 0;
+    }
+    if (i < rows) d.at[i] = 0;
+    if (i < (kRounds + 2) * Demand::kNumbers) d.round[i] = 0;
+}
+
+// Rows for the tokens that codes wait for and that have none: one addition to the round's counter per block.  Which row a token
+// gets differs from run to run; what is in it does not.  For all tokens without one in a last round that codes still wait for,
+// and as soon as tokens seem to come evenly (asked once a 32nd of them have a row, of 64 codes): where the share that has one, of
+// those that codes meet, is hardly above the share of all, and the codes that wait have steps enough left to come to what is
+// missing, more rounds would make nearly all of them by and by.  (Tokens that are few are met again and again: 65536 codes, 3000
+// tokens, after a round with 2900 rows 0.97 of those met against 0.09.)
+__global__ __launch_bounds__(1024) void demand_claim_kernel(Demand d, int32_t i, int32_t T, int32_t each, bool last, int32_t V)
+{
+    __shared__ int32_t wave_n[16], block_at;
+    const int64_t v = (int64_t)blockIdx.x * 1024 + threadIdx.x;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    bool all = false;
+    if (i >= 2) {
+        const int32_t *const before = d.round + (i - 1) * Demand::kNumbers;
+        const float met = (float)before[Demand::kMet], missed = (float)before[Demand::kMissed], n = met + missed;
+        const float made = (float)d.round[i * Demand::kNumbers + Demand::kMade];
+        const bool evenly = n >= 16.f && made * 32.f >= (float)V && met < n * (1.4f * made / (float)V + 0.02f) &&
+                            missed * (float)each * (float)(T - i) * missed >= ((float)V - made) * n;
+        all = before[Demand::kWaits] != 0 && (last || evenly);
+    }
+    const bool mine = v < V && d.slot[v] < 0 && (all || d.wanted[v] != 0);
+    const unsigned long long m = __ballot(mine);
+    if (lane == 0) wave_n[wave] = __builtin_popcountll(m);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int32_t n = 0;
+        for (int w = 0; w < 16; ++w) {
+            const int32_t c = wave_n[w];
+            wave_n[w] = n;
+            n += c;
+        }
+        block_at = n ? atomicAdd(&d.round[(i + 1) * Demand::kNumbers + Demand::kMade], n) : 0;
+    }
+    __syncthreads();
+    if (!mine) return;
+    const int32_t at = block_at + wave_n[wave] + __builtin_popcountll(m & ((1ull << lane) - 1ull));
+    d.slot[v] = at;
+    d.token[at] = (int32_t)v;
 }
 
 }  // namespace
@@ -314,12 +396,13 @@ bool step_by_sums(const as_ctx *ctx, float temp)
            1.44269504088896340736f / temp <= kTileMaxScale;
 }
 
-as_status launch_row_records(as_ctx *ctx, const void *logits, int64_t ld, float temp, unsigned char *records)
+as_status launch_row_records(as_ctx *ctx, const void *logits, int64_t ld, float temp, unsigned char *records, int64_t rows,
+                             RowRange range)
 {
     const float k = 1.44269504088896340736f / temp;
-    const dim3 grid((unsigned)ctx->V), block(256);
-    const bool nt = stream_rows(ctx->V, ld, ctx->dtype == AS_BF16 ? 2 : 4);
-    auto go = [&](auto kernel) { launch(ctx, kKernelThreshold, kernel, grid, block, 0, logits, ld, ctx->V, k, records); };
+    const dim3 grid((unsigned)rows), block(256);
+    const bool nt = stream_rows(rows, ld, ctx->dtype == AS_BF16 ? 2 : 4);
+    auto go = [&](auto kernel) { launch(ctx, kKernelThreshold, kernel, grid, block, 0, logits, ld, ctx->V, k, records, range); };
     if (ctx->dtype == AS_BF16) nt ? go(row_records_kernel<AS_BF16, true>) : go(row_records_kernel<AS_BF16, false>);
     else nt ? go(row_records_kernel<AS_F32, true>) : go(row_records_kernel<AS_F32, false>);
     AS_HIP_TRY(ctx, hipGetLastError());
@@ -328,11 +411,28 @@ as_status launch_row_records(as_ctx *ctx, const void *logits, int64_t ld, float 
 
 as_status launch_walk(as_ctx *ctx, TableForm form, const WalkArgs &a)
 {
-    const dim3 grid((unsigned)((a.rows + 3) / 4)), block(256);
-    if (form == kTableTopK) launch(ctx, kKernelStep, walk_kernel<AS_BF16, kTableTopK>, grid, block, 0, a);
-    else if (form == kTableNucleus) launch(ctx, kKernelStep, walk_kernel<AS_BF16, kTableNucleus>, grid, block, 0, a);
-    else if (a.dtype == AS_BF16) launch(ctx, kKernelStep, walk_kernel<AS_BF16, kTablePlain>, grid, block, 0, a);
-    else launch(ctx, kKernelStep, walk_kernel<AS_F32, kTablePlain>, grid, block, 0, a);
+    auto go = [&](auto kernel) { launch(ctx, kKernelStep, kernel, dim3((unsigned)((a.rows + 3) / 4)), dim3(256), 0, a); };
+    auto either = [&](auto all, auto demand) { a.slot ? go(demand) : go(all); };
+    if (form == kTableTopK) either(walk_kernel<AS_BF16, kTableTopK>, walk_kernel<AS_BF16, kTableTopK, true>);
+    else if (form == kTableNucleus) either(walk_kernel<AS_BF16, kTableNucleus>, walk_kernel<AS_BF16, kTableNucleus, true>);
+    else if (a.dtype == AS_BF16) either(walk_kernel<AS_BF16, kTablePlain>, walk_kernel<AS_BF16, kTablePlain, true>);
+    else either(walk_kernel<AS_F32, kTablePlain>, walk_kernel<AS_F32, kTablePlain, true>);
+    AS_HIP_TRY(ctx, hipGetLastError());
+    return AS_OK;
+}
+
+as_status launch_demand_clear(as_ctx *ctx, const Demand &d, int64_t rows)
+{
+    const int64_t n = larger(larger(ctx->V, rows), (kRounds + 2) * Demand::kNumbers);
+    hipLaunchKernelGGL(demand_clear_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, ctx->stream, d, ctx->V, rows);
+    AS_HIP_TRY(ctx, hipGetLastError());
+    return AS_OK;
+}
+
+as_status launch_demand_claim(as_ctx *ctx, const Demand &d, int32_t i, int32_t T, int32_t each, bool last)
+{
+    hipLaunchKernelGGL(demand_claim_kernel, dim3((unsigned)(((int64_t)ctx->V + 1023) / 1024)), dim3(1024), 0, ctx->stream, d, i, T,
+                       each, last, ctx->V);
     AS_HIP_TRY(ctx, hipGetLastError());
     return AS_OK;
 }

@@ -1303,7 +1303,11 @@ __global__ __launch_bounds__(kThreads, 4) void topk_tile_kernel(StepArgs a, int3
     Scratch &sc = sh.sc;
     TileTopK &tk = sh.tk;
 
-    const int64_t r = blockIdx.x;
+    int64_t r = blockIdx.x;
+    if constexpr (TABLE) {
+        if (a.range.begin) r += *a.range.begin;
+        if (a.range.end && r >= *a.range.end) return;
+    }
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
@@ -1665,7 +1669,11 @@ __global__ __launch_bounds__(kThreads, 4) void nucleus_tile_kernel(StepArgs a, f
     Scratch &sc = sh.sc;
     TileNucleus &tn = sh.tn;
 
-    const int64_t r = blockIdx.x;
+    int64_t r = blockIdx.x;
+    if constexpr (TABLE) {
+        if (a.range.begin) r += *a.range.begin;
+        if (a.range.end && r >= *a.range.end) return;
+    }
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
@@ -2060,13 +2068,14 @@ TableForm table_form(const as_ctx *ctx, int64_t rows, float temp, int32_t top_k,
 }
 
 as_status launch_table_records(as_ctx *ctx, TableForm form, const void *logits, int64_t ld, float temp, int32_t top_k, float top_p,
-                               unsigned char *records)
+                               unsigned char *records, int64_t rows, RowRange range)
 {
-    if (form == kTablePlain) return launch_row_records(ctx, logits, ld, temp, records);
+    if (form == kTablePlain) return launch_row_records(ctx, logits, ld, temp, records, rows, range);
     StepArgs a{};
-    a.logits = logits; a.rows = ctx->V; a.ld = ld; a.V = ctx->V; a.dtype = ctx->dtype; a.temp = temp;
+    a.range = range;
+    a.logits = logits; a.rows = rows; a.ld = ld; a.V = ctx->V; a.dtype = ctx->dtype; a.temp = temp;
     a.k = 1.44269504088896340736f / temp; a.records = records;
-    const dim3 grid((unsigned)ctx->V), block(kThreads);
+    const dim3 grid((unsigned)rows), block(kThreads);
     const bool nt = stream_rows(a.rows, ld, 2), has_p = top_p > 0.f && top_p < 1.f;
     if (form == kTableNucleus) {
         if (nt) launch(ctx, kKernelThreshold, nucleus_tile_kernel<true, true>, grid, block, 0, a, top_p);

@@ -121,10 +121,11 @@ struct DecodeSizes {
     size_t needed, kept, preferred;          // bytes of logits
     size_t state, state_preferred;
 };
-// The state of a decode from a table: records (where its steps work from them), codes, prev twice, the table's tokens, flags.
+// The state of a decode from a table: codes, prev twice (or the steps done), the table's tokens, flags; with records, those,
+// and what rows on demand take: a row and a mark per token, and the rounds' numbers.
 inline size_t table_state(int64_t V, int64_t rows, bool with_records)
 {
-    return (size_t)((with_records ? V * kTableRecord : 0) + (3 * rows + V) * 4 + rows);
+    return (size_t)((with_records ? V * kTableRecord + (2 * V + 48) * 4 : 0) + (3 * rows + V) * 4 + rows);
 }
 inline DecodeSizes decode_sizes(int64_t V, int64_t esz, int64_t rows, int64_t T, bool masses)
 {

@@ -92,9 +92,23 @@ def _logits_launches(ctx, call):
 
 @pytest.mark.parametrize("V,d,Bn,N,T,top_k,top_p,wdt,ldt,temp,scale", CASES)
 def test_decode_from_a_table_equals_the_loop_of_exported_calls(V, d, Bn, N, T, top_k, top_p, wdt, ldt, temp, scale):
+    _compare(V, d, Bn, N, T, top_k, top_p, wdt, ldt, temp, scale, 3, 1)
+
+
+# bf16 weights, ranks of whole K steps, rows of one tile; rounds that are enough (as many as steps), and those after which
+# all rows are made
+@pytest.mark.parametrize("V,d,Bn,N,T,top_k,top_p,wdt,ldt,temp,scale",
+                         [c for c in CASES if c[7] == "bf16" and c[1] >= 128 and c[0] % 8 == 0 and c[9] > 0.37 and c[5] < 48] +
+                         [(4096, 128, 2, 150, 5, 0, 1.0, "bf16", "bf16", TEMP, 3.0), (4096, 128, 1, 900, 7, 0, 0.9, "bf16", "bf16", TEMP, 3.0),
+                          (8192, 128, 3, 60, 130, 0, 1.0, "bf16", "f32", TEMP, 3.0)])
+def test_rows_on_demand_equal_the_loop_of_exported_calls(V, d, Bn, N, T, top_k, top_p, wdt, ldt, temp, scale):
+    _compare(V, d, Bn, N, T, top_k, top_p, wdt, ldt, temp, scale, 5, min(T, 7))
+
+
+def _compare(V, d, Bn, N, T, top_k, top_p, wdt, ldt, temp, scale, knob, launches):
     model, ctx, prompts, u, g = _setup(V, d, Bn, N, wdt, ldt, scale)
     R = Bn * N
-    ctx.set_tuning("kept_rows", 3)                        # (whatever the rule comes to be)
+    ctx.set_tuning("kept_rows", knob)                     # (whatever the rule comes to be)
     out = torch.empty((Bn, N, T), dtype=torch.int32, device="cuda")
     last = torch.empty(R, dtype=torch.float32, device="cuda")
 
@@ -111,13 +125,41 @@ def test_decode_from_a_table_equals_the_loop_of_exported_calls(V, d, Bn, N, T, t
     assert torch.equal(out.view(R, T), want) and torch.equal(last, want_codes)
     assert (want == eos).any()
     out.fill_(-1)
-    assert _logits_launches(ctx, decode) == 1             # (the table was what ran)
+    assert _logits_launches(ctx, decode) == launches      # (that was what ran)
     assert torch.equal(out.view(R, T), want) and torch.equal(last, want_codes)
 
     uniforms = torch.rand(T, R, device="cuda", generator=g).clamp_max_(1.0 - 2.0 ** -24)
     B.as_decode_ancestral(ctx, model, prompts, N, T, uniforms, temp, top_k, top_p, eos, out)
     want, _ = _loop(ctx, model, prompts, N, T, codes, uniforms, temp, top_k, top_p, eos, ldt)
     assert torch.equal(out.view(R, T), want)
+    ctx.close()
+    model.close()
+
+
+@pytest.mark.parametrize("hot", [0, 100, 2000])
+def test_rows_are_made_for_the_tokens_that_come(hot):
+    """Wide decodes on all tokens, and on a few that hold nearly all the mass: as the rule has it, against a row a token and
+    step; the same tokens."""
+    V, d, R, T = 32128, 512, 16384, 16
+    g = torch.Generator(device="cuda").manual_seed(hot)
+    E, U = torch.randn(V, d, device="cuda", generator=g), torch.randn(d, V, device="cuda", generator=g)
+    if hot:
+        E[:, 0] = 4.0
+        bias = torch.full((V,), -20.0, device="cuda")
+        bias[torch.randperm(V, device="cuda", generator=g)[:hot]] = 0.0
+        U[0] = bias / (3.0 / d ** 0.5 * 4.0)
+    model, ctx = B.Model(E.bfloat16(), U.bfloat16(), scale=3.0), B.Ctx(R, V, torch.bfloat16)
+    prompts, u = torch.tensor([5], dtype=torch.int32, device="cuda"), torch.rand(1, device="cuda", generator=g)
+    outs = []
+    for knob in (0, 1):
+        ctx.set_tuning("kept_rows", knob)
+        out = torch.empty((1, R, T), dtype=torch.int32, device="cuda")
+        n = _logits_launches(ctx, lambda: B.as_decode(ctx, model, prompts, R, T, u, 1.0, 0, 1.0, -1, out))
+        assert n == (7 if knob == 0 else T)
+        outs.append(out)
+    assert torch.equal(*outs)
+    if hot:
+        assert torch.unique(outs[0]).numel() < 1.2 * hot + 50
     ctx.close()
     model.close()
 
@@ -137,8 +179,9 @@ def test_fused_decode_from_a_table():
     model.close()
 
 
+@pytest.mark.parametrize("knob", [3, 5])
 @pytest.mark.parametrize("top_k,ldt", [(0, "bf16"), (10, "bf16"), (0, "f32")])
-def test_decode_from_a_table_replays_from_a_graph(top_k, ldt):
+def test_decode_from_a_table_replays_from_a_graph(top_k, ldt, knob):
     V, d, Bn, N, T = 16000, 128, 2, 100, 66
     model, ctx, prompts, u, _ = _setup(V, d, Bn, N, "bf16", ldt, 3.0)
     ctx.close()
@@ -146,7 +189,7 @@ def test_decode_from_a_table_replays_from_a_graph(top_k, ldt):
     torch.cuda.synchronize()
     with torch.cuda.stream(stream):
         ctx = B.Ctx(Bn * N, V, DT[ldt])
-        ctx.set_tuning("kept_rows", 3)
+        ctx.set_tuning("kept_rows", knob)
         out = torch.empty((Bn, N, T), dtype=torch.int32, device="cuda")
         eager = torch.empty_like(out)
         B.as_decode(ctx, model, prompts, N, T, u, TEMP, top_k, 1.0, 1, out)       # (makes the workspace)

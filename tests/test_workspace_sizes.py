@@ -117,8 +117,8 @@ def test_what_a_decode_reserves_holds_every_form_of_it(lib):
                 by_sums = 68 * K if not masses and V * esz % 16 == 0 and V * esz <= 65536 else 0
                 forms += [2 * R + R + K + 2 * V + K + T + 1 + by_sums]
             assert z["state"] >= max(forms) * 4 + R, (V, esz, R, T, masses)
-            # a table of every token's rows: records where rows are of one tile, codes, prev twice, the tokens, flags.  No
-            # state that a decode has to have holds its records
+            # a table of every token's rows: records where rows are of one tile, codes, prev twice, the tokens, flags; or rows
+            # on demand: records, codes, prev, steps, tokens, rows, marks, 48 numbers, flags.  No state that a decode has to have holds its records
             assert z["preferred"] >= z["kept"] >= z["needed"] and z["state_preferred"] >= z["state"]
             if not lib.table(V, R, T, rb):
                 assert z["preferred"] <= max(z["kept"], V * lib.row_bytes(V, esz, 1) if lib.table(V, R, T, lib.row_bytes(V, esz, 1)) else 0)
@@ -126,9 +126,9 @@ def test_what_a_decode_reserves_holds_every_form_of_it(lib):
                 tables += 1
                 records = V * lib.record() if not masses and V * esz % 16 == 0 and V * esz <= 65536 else 0
                 assert V * rb <= 4 << 30 and z["preferred"] >= V * rb and (V <= 128 * R or V * rb <= 512 << 20)
-                # what the header says (4 bytes a record's row: the token; codes and flags beside prev twice)
-                assert T >= 4 and T * (R + 6e6 / V) >= 1.25 * V and records + (3 * R + V) * 4 + R <= 1060 * V + 13 * R
-                assert z["state_preferred"] >= records + (3 * R + V) * 4 + R
+                # what the header says
+                assert T >= 4 and T * (R + 6e6 / V) >= 1.25 * V and records + (3 * R + 3 * V) * 4 + R <= 1068 * V + 13 * R
+                assert z["state_preferred"] >= records + (3 * R + (3 * V + 48 if records else V)) * 4 + R
             assert z["state"] <= max((68 * min(V, 4 * R) + 4 * R + 4 * V + T + 1) * 4 + R, lib.tables(V, esz, R, R, R, min(R, 1024), 0))
             # ... and an encode of its size, a column at a time
             assert z["state"] >= lib.tables(V, esz, R, R, R, min(R, 1024), 0)

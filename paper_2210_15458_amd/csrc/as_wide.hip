@@ -798,8 +798,8 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
         // which the nucleus closes, give or take a neighbour.  One pass then adds up the masses of all logits and
         // of those above a window of bins around it, as integers, and the latter's weights per chunk, and lists the
         // logits of the window; the list is closed by the same integers, and what it keeps is added to its chunks.  If the
-        // list overflows (heavy ties, flat rows), the window is closed from the row.  If the window was off (neighbouring
-        // bins with more than kBeside logits stay out of it), the general selection follows.
+        // list overflows (heavy ties, flat rows), a wave closes the window from the row.  If the window was off (neighbouring
+        // bins with more than kBeside logits stay out of it), or for a block, the general selection follows.
         // (Adding the masses themselves takes 64-bit LDS atomics, 45 cycles a wave, or float ones, 300.)
         bool closed = false;
         const int s_bits = 31 - (32 - __builtin_clz((uint32_t)V));
@@ -972,10 +972,11 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
             const double need = (double)top_p * wide_total<NT>(sh.wave_d, unused);
             const double above = wide_total<NT>(sh.wave_e, unused);
             const uint32_t n = sh.n;
-            if (above < need) {
+            if ((Sh::kWave || n <= (uint32_t)Sh::kList) && above < need) {
                 // (more than the list takes: the window's logits by their keys, and the chunk sums over again)
                 const uint32_t key = close(n, (u64)above, need, [&](auto put) __attribute__((always_inline)) {
-                    every_piece_again([&](const u32x4 &v) __attribute__((always_inline)) {
+                    if constexpr (!Sh::kWave) return;
+                    else every_piece_again([&](const u32x4 &v) __attribute__((always_inline)) {
                         float x[EPV];
                         values(v, x);
 #pragma unroll
@@ -1131,7 +1132,7 @@ void launch_form(as_ctx *ctx, int kid, const StepArgs &a, int32_t top_k, float t
 // another wave, and what a block does in some 25 steps of its waves overlaps over rows instead (us, blocks / waves: nuclei, 1500
 // rows of 1500 bf16 20.5 / 14.9, 600 14.0 / 13.0, 14251 of 1923 119 / 63, 5252 of 3078 57 / 38, 4200 of 8001 58 / 56, 2600 42 /
 // 47; k = 40 2100 of 4001 18.6 / 16.3, 1500 of 3000 13.1 / 14.6, 9000 of 6001 53 / 47, 4200 of 8001 31 / 32; counts, k = 1000,
-// 4000 of 1500 30 / 18, 2100 of 4001 23 / 25, 9000 of 6001 79 / 77 and on flat or steep rows 1.1 to 1.2 behind).  Those rows
+// 4000 of 1500 30 / 18, 2100 of 4001 23 / 25, 9000 of 6001 79 / 77, 6000 of 4000 fp32 k = 200 38 / 33, but on flat or steep ones 38 / 45 and more).  Those rows
 // have a standard deviation of 3 against the temperature; a wave has a shorter list, so flat rows decide whether its line holds:
 // of 0.3 at a temperature of 0.9, nuclei p = 0.9 4000 of 1500 37 / 23, 6000 of 3000 65 / 44, 3000 of 4000 41 / 47, 8000 of 8000
 // 134 / 111; k = 100 then p = 0.9 6000 of 1000 76 / 37, 6000 of 3000 63 / 63, which is behind only where the row is all but
@@ -1143,12 +1144,12 @@ void launch_type(as_ctx *ctx, int kid, const StepArgs &a, int32_t top_k, float t
     const int64_t most = ((int64_t)a.V + EPV - 1) / EPV;     // whole pieces of a row, whatever its alignment
     const bool many = a.rows > (int64_t)ctx->num_cus, lots = a.rows > 2 * (int64_t)ctx->num_cus;
     const bool has_p = top_p > 0.f && top_p < 1.f;
-    // (compute units' worth of rows beyond which a wave takes a row; counts on longer rows, and a nucleus after the 64 best of a
-    // row of more than 256 pieces, never)
+    // (compute units' worth of rows beyond which a wave takes a row; counts on rows of more than 768 pieces or with a nucleus behind
+    // them on more than 512, and a nucleus after the 64 best of a row of more than 256, never)
     const bool counts = TOPK && top_k > kWaveTopK;
     const bool table = counts && has_p && top_k <= 64 && most > 64 * 4;      // (4816 rows of 3315, k = 50, p = 0.73: 34 / 38)
     const int64_t never = 1LL << 40;
-    const int64_t waves = most <= 64 * 8 ? (table ? never : !TOPK ? 4 : counts ? 12 : 6) : !TOPK ? 16 : !counts ? 20 : never;
+    const int64_t waves = most <= 64 * 8 ? (table ? never : !TOPK ? 4 : counts ? 12 : 6) : !TOPK ? 16 : !counts || (!has_p && most <= 64 * 12) ? 20 : never;
     if (most <= 64 * 16 && a.rows > waves * (int64_t)ctx->num_cus) {
         if (most <= 64 * 8) return launch_form<DT, 64, 8, false, TOPK, 5>(ctx, kid, a, top_k, top_p, thr_out);
         return launch_form<DT, 64, 16, false, TOPK, 4>(ctx, kid, a, top_k, top_p, thr_out);

@@ -1339,7 +1339,7 @@ bool keeping_pays(const as_ctx *ctx, const as_model *m, int64_t rows, int32_t T,
 // What a product of `rows` rows takes, in us
 static double product_us(const as_ctx *ctx, const as_model *m, double rows)
 {
-    if (!mfma_applies(m)) return 3.5 + 2.0 * rows * (double)m->V * (double)m->d / 1e8;
+    if (!mfma_applies(m)) return 3.5 + rows * (double)m->V * (2.0 * (double)m->d / 1e8 + (ctx->dtype == AS_BF16 ? 2.0 : 4.0) / 5e6);
     const ProductTimes t = product_times(ctx, m, (int64_t)rows + 1);
     const double thin = t.thin[0] < t.thin[1] ? (t.thin[0] < t.thin[2] ? t.thin[0] : t.thin[2])
                                               : (t.thin[1] < t.thin[2] ? t.thin[1] : t.thin[2]);
@@ -1352,7 +1352,7 @@ static double product_us(const as_ctx *ctx, const as_model *m, double rows)
 }
 
 // Whether a decode makes the logits rows of all tokens first, against a row per code, token in use or new token (`keep`) in
-// each step.  Then it has one large product, one pass over its rows, and steps of 2 us (1 from candidates; 0.5 ns a code where
+// each step.  Then it has one large product, one pass over its rows, and steps of 2 us (1 from candidates; 0.4 ns a code where
 // those are many) that share a launch; where the steps' kernels have to read the rows (kTableRows) it spares the products alone.
 // us a decode, every step its own rows / kept / table: 1024 codes x 64 of 32128 x 512 3124 / - / 1486, 16 x 64 638 / - / 1550;
 // k = 40, 1024 x 128 6548 / - / 1504; 65536 x 16 20260 / 2465 / 1808; 3605 x 126 of 1600 x 1024 5281 / 2052 / 267; 406 x 59 of
@@ -1379,12 +1379,16 @@ TableChoice table_pays(const as_ctx *ctx, const as_model *m, int64_t rows, int32
     const double kept = V * (1.0 - exp(-R * (T - 1) / V)) / (T - 1);
     const double own = keep ? kept : sharing_pays(ctx, m, rows, T) ? V * (1.0 - exp(-R / V)) : R;      // rows a step
     const double sampling = 3.5 + R * row_us;
-    // (the first step's product has a row per prompt)
+    // (the first step's product has a row per prompt; half a us lies between launches)
     const double without = 5.0 + (T - 1) * product_us(ctx, m, own) +
-                           T * ((keep ? 12.0 : 0.0) + (keep && by_sums ? 4.0 + R * 0.0007 + own * row_us : sampling));
-    const double step = form == kTableRows ? sampling : 3.0 + R * 0.0006;
+                           T * (1.0 + (keep ? 12.0 : 0.0) + (keep && by_sums ? 4.0 + R * 0.0007 + own * row_us : sampling));
+    // (rows of a table beyond the caches are read from memory, those of a step's own product where it left them)
+    const double row_bytes = V * (ctx->dtype == AS_BF16 ? 2.0 : 4.0);
+    const double cold = !keep && V * row_bytes > 256e6 && own * row_bytes < 256e6 ? 1.25 : 1.0;
+    const double step = form == kTableRows ? sampling * cold + 0.5 : 2.0 + R * 0.0004;
     const double table = product_us(ctx, m, V) + (form == kTableRows ? 0.0 : 4.0 + V * row_us);
-    if (table + T * step >= (keep ? 0.9 : 0.95) * without) return kNoTable;
+    // (kept rows that have no records are read in an order of the rows, where that pays)
+    if (table + T * step >= (!keep ? 0.95 : form == kTableRows ? 0.85 : 0.9) * without) return kNoTable;
     const double least = 40.0 + T * (10.0 + R * 0.0006);
     if (!keep || table + (form == kTableRows ? 0.0 : T * step) < least) return kTableAll;
     return form == kTableRows ? kNoTable : kTableDemand;

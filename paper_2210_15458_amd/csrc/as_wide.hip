@@ -1,7 +1,7 @@
 // Top-k and the nucleus (the logit modifiers of Sec. 2) together with the sampling step (Algorithm 1, Sec. 4.1)
 // in one launch, for rows of any length, alignment and storage type: what the single-tile bf16 kernels do not
-// take.  One work-group of 256 to 1024 threads per row, the row in its registers (up to 16 pieces of 16 bytes a
-// thread: 256 KB with 1024 threads); a longer row goes through the registers a tile at a time and every pass but
+// take.  One work-group of 64 to 1024 threads per row (launch_type; 64, a wave, for very many rows of up to 16 KB), the row in its
+// registers (up to 16 pieces of 16 bytes a thread: 256 KB with 1024 threads); a longer row goes through the registers a tile at a time and every pass but
 // the first starts with the tile that is still there.
 //
 // What bounds it: a row of V = 50257 fp32 logits is 200 KB, one work-group fills a compute unit's registers with
@@ -9,15 +9,16 @@
 // about 17 for its weight and integer mass) and the latency of some 25 block-wide steps.  Hence a histogram filled
 // while the row lands, one more pass, and no visit of memory after the first but for the code's own chunk.
 //
-//   top-k, k <= 128   The k-th largest of 256 group maxima bounds the k-th largest logit from below; the few
+//   top-k by a table  (k up to table_most: 40, 48, 64, 96 or 128 by the form, the row's length and whether a nucleus follows)
+//                     The k-th largest of 256 group maxima bounds the k-th largest logit from below; the few
 //                     logits at or above it become a candidate table in LDS (value, index), and everything that
 //                     follows - the exact k-th with its ties, the nucleus over the survivors, the code's bucket -
 //                     is ranks and scans over that table.
-//   nucleus           32-bit tallies in 2048 or 4096 bins over 64 factors of two; the bin in which the nucleus closes;
-//                     the chunk sums of everything above a window around it, the window's logits as a list that is
-//                     closed by integer masses (see below).
-//   k > 128           counts in the same bins, the logits of the closing bin as a list; a nucleus after it by
-//                     fixed-point masses.
+//   nucleus           32-bit tallies in kBins bins over kOctaves factors of two (1024 to 4096 over 64; a wave has 512 over 32); the
+//                     bin in which the nucleus closes; the chunk sums of everything above a window around it, the
+//                     window's logits as a list that is closed by integer masses (see below).
+//   larger k          counts in as many bins over 64 factors of two, the logits of the closing bin as a list; a nucleus after it
+//                     by fixed-point masses.
 // Then the chunk of the code (64 pieces, vocabulary order), its lane, its logit.  Sums that decide anything are taken
 // in an order, or in integers, that does not depend on which lane comes first.
 //
@@ -120,6 +121,8 @@ template <int NT, bool MULTI, bool SHORT> struct WideShared {
     int32_t pick;
     uint32_t n, sel;
 };
+
+static_assert(sizeof(WideShared<64, false, true>) <= 7680 && sizeof(WideShared<64, false, false>) <= 10240, "five and four waves a SIMD");
 
 // What the waves of a block have left in LDS, one value each, is taken in by one lane per wave (W <= 16): the row
 // sits in most of the registers, a value per wave in every lane would not fit beside it.
@@ -647,7 +650,7 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
         return khi;
     };
 
-    // f(piece) over the row for the selection by integer weights: with top-k it is the way (k above 128), from the
+    // f(piece) over the row for the selection by integer weights: with top-k it is the way (k above table_most), from the
     // registers; after the quick way of the nucleus it is the rare case, and goes over memory (kept for it as
     // well, the row costs spilled registers on the way that is taken)
     auto every_piece = [&](auto f) __attribute__((always_inline)) {
@@ -892,7 +895,7 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
         }
         const int32_t pick = sh.pick;
         if (pick >= 0 && nfull < Sh::kExtra) {
-            // the window: bins on either side of the picked one until they hold 32 logits
+            // the window: bins on either side of the picked one until they hold kBeside logits
             int32_t wlo, whi;
             {
                 const int32_t b = pick - 32 + lane;

@@ -300,10 +300,10 @@ def compact_leg(cfg_id, top_k, top_p, steps, warmup):
 
 
 def source_stamp():
-    """Hash of the sources the sampling kernel is built from (ties a stored counter reading to the kernel timed)."""
+    """Hash of the sources the sampling kernels of a table are built from (ties a stored counter reading to what is timed)."""
     here = os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_2210_15458_amd", "csrc")
     h = hashlib.sha256()
-    for name in ("as_step.hip", "as_tile.hpp", "as_row.hpp", "as_common.hpp"):
+    for name in ("as_rows.hip", "as_tile.hpp", "as_row.hpp", "as_common.hpp"):
         with open(os.path.join(here, name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]
@@ -569,7 +569,7 @@ def main():
         with open(traffic_file) as f:
             tr = json.load(f)
         # a counter reading of another build of the kernel says nothing about the one timed here
-        if tr.get("source_stamp") == source_stamp():
+        if tr.get("source_stamp") == source_stamp() and table:
             out["roofline"]["traffic"] = tr.get("traffic_bytes_per_launch")
             out["roofline"]["traffic_source"] = tr.get("source")
         else:

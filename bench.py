@@ -251,6 +251,8 @@ def compact_leg(cfg_id, top_k, top_p, steps, warmup):
     samp_us = float(np.mean(step_samples)) * 1e3 + (float(np.mean(thr_samples)) * 1e3 if len(thr_samples) else 0.0)
     if table:
         samp_us, bytes_per_launch, cnt["computed"] = table["avg_launch_us"], table["bytes_per_launch"], table["rows_computed_per_launch"]
+    elif len(gemm_samples) == steps < T * steps:
+        cnt["computed"] = V                # (a table whose rows the steps' own kernels read)
     ach = bytes_per_launch / (samp_us * 1e-6) / 1e9
     out = {
         "workload": f"configs[{cfg_id}] {cfg['name']}: as_decode V={V} d={d} bf16, B={Bn} N={N} (R={R}) T={T} "
@@ -417,6 +419,8 @@ def main():
     table = table_figures(V, esz, args.steps, T, cnt["active"], top_k, met, step_samples, thr_samples, gemm_samples)
     if table:
         step_avg_us, bytes_per_launch, cnt["computed"] = table["avg_launch_us"], table["bytes_per_launch"], table["rows_computed_per_launch"]
+    elif gemm_n == args.steps < T * args.steps:
+        cnt["computed"] = V                # (a table whose rows the steps' own kernels read)
     # (a launch that does a whole decode has no logits rows in memory)
     whole_decode = T > 1 and step_n == args.steps and not table
     achieved = bytes_per_launch / (step_avg_us * 1e-6) / 1e9 if step_n and not whole_decode else None

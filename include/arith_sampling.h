@@ -150,7 +150,8 @@ as_status as_ctx_set_tuning(as_ctx *ctx, as_tuning knob, int32_t value);
  *   kernel 0: fused sampling step   1: logits (bigram) kernel   2: threshold   3: interval (encode) step
  * and resets the counters.  (A decode that makes the logits rows of all tokens before its
  * first step has that launch under 1, what it makes of the rows under 2, and its steps, which
- * share one launch, under 0.  Profiling changes nothing of what a call launches.)  At most 16384 launches per kernel are timed between
+ * share one launch, under 0; one that makes rows for the tokens that come has these a few times
+ * over.  Profiling changes nothing of what a call launches.)  At most 16384 launches per kernel are timed between
  * reads; further ones run untimed and are counted in *untimed.  Any output
  * pointer may be NULL.  Switching profiling on makes the first launches create
  * events (a host-side allocation).

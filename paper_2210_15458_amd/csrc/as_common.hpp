@@ -65,7 +65,7 @@ struct as_ctx {
     int thr_path = 0;              // truncation: 1 = radix select, 2 = resident where the row fits, 3 = wide for every row
     int gemm_gm = 0;               // logits kernel, many row tiles: workers of an XCD along the rows (tuning knob: 0 = default)
     int kept_rows = 0;             // decodes: 1 = no logits rows kept from step to step, 2 / 3 = kept / a table of all wherever there is room,
-                                   // 4 = no table of all
+                                   // 4 = no table of all, 5 = one of the tokens that come
     int workspace_mib = 0;         // largest buffer of the workspace, in MiB (tuning knob: 0 = as large as the device gives)
     int num_cus = 0;               // compute units of the device (the persistent logits kernel runs one block on each)
     std::string err;

@@ -1365,11 +1365,10 @@ static double product_us(const as_ctx *ctx, const as_model *m, double rows)
 // tokens are few.  So against those a table of all has to win by the least that they can take (on 300 tokens, measured / by the
 // line below: 65536 codes x 16 914 / 829, 65536 x 6 475 / 336, 16384 x 16 464 / 357, 8192 x 64 1005 / 995, 4096 x 16 274 / 239,
 // 5997 x 6 169 / 122); else rows are made on demand, for the tokens that codes come to, where steps work from
-// records.  us a decode, kept / table / on demand, 32128 x 512, on even tokens: 65536 x 16 2495 / 1729 /
-// 1998, 8192 x 64 3318 / 1580 / 1710, k = 40 16384 x 16 4007 / 1395 / 1601; with a Zipf bias 2501 / 1679 / 2058, 3089 / 1528 / 2217,
-// 3010 / 1363 / 1667; on 300 tokens 923 / 1658 / 515, 1008 / 1508 / 325, 2324 / 1347 / 225.  Behind kept rows where a low rank makes
-// their products cheap and tokens are neither even nor few: 9524 x 11 of 28256 x 128 878 / 765 / 890, Zipf 643 / 759 / 894, on 200
-// 263 / 755 / 184.
+// records.  us a decode of 32128 x 512, kept / table / on demand, on even tokens: 65536 x 16 2495 / 1729 / 1998, 8192 x 64 3318 / 1580 /
+// 1692, k = 40 16384 x 16 4007 / 1395 / 1571; with a Zipf bias 2501 / 1679 / 2006, 3089 / 1528 / 2127, 3010 / 1363 / 1622; on 300 tokens
+// 923 / 1658 / 515, 1008 / 1508 / 325, 2324 / 1347 / 225.  Behind kept rows where a low rank makes their products cheap and tokens are
+// neither even nor few: 9524 x 11 of 28256 x 128 878 / 765 / 863, Zipf 643 / 759 / 868, on 200 263 / 755 / 184.
 TableChoice table_pays(const as_ctx *ctx, const as_model *m, int64_t rows, int32_t T, TableForm form, bool keep, bool by_sums)
 {
     if (ctx->kept_rows == 3) return kTableAll;

@@ -1249,11 +1249,6 @@ __global__ __launch_bounds__(kThreads) void threshold_stream_kernel(const void *
 constexpr int kTileTopK = 47;      // (a bound of 48 lanes brings more logits than there are places: topk_tile_pays)
 constexpr int kTileCand = 64;
 
-typedef short i16x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint32_t pk_max_i16(uint32_t a, uint32_t b)
-{
-    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(i16x2, a), __builtin_bit_cast(i16x2, b)));
-}
 // two stored bf16 -> two signed 16-bit keys in the same order as the values (negative values have their
 // magnitude bits flipped); its own inverse
 __device__ __forceinline__ uint32_t pk_key_bf16(uint32_t w)
@@ -1644,16 +1639,6 @@ struct TileNucleus {
     int32_t pick[kThreads / 64];
 };
 
-typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint32_t pk_min_u16(uint32_t a, uint32_t b)
-{
-    return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
-}
-__device__ __forceinline__ uint32_t pk_sub_u16(uint32_t a, uint32_t b)
-{
-    return __builtin_bit_cast(uint32_t, (u16x2)(__builtin_bit_cast(u16x2, a) - __builtin_bit_cast(u16x2, b)));
-}
-
 // TABLE: no step, but the sums of row r's nucleus as steps to come need them (a.records)
 template <bool NT, bool TABLE = false>
 __global__ __launch_bounds__(kThreads, 4) void nucleus_tile_kernel(StepArgs a, float top_p)
@@ -1982,16 +1967,15 @@ static bool resident_fits(const as_ctx *ctx, const void *logits, int64_t ld, boo
            (ld * (ctx->dtype == AS_BF16 ? 2 : 4)) % 16 == 0 && (!has_k || top_k <= kThreads / 2);
 }
 
-// Whole steps that it takes from the wide kernel (us, resident / wide): the nucleus alone of long bf16 rows (those of whole
-// pieces have a kernel of their own), 2000 rows of 9001 57 / 39, of 20001 60 / 57, of 32001 66 / 75; top-k of fp32 rows above
-// 16384 on more than two a compute unit, 600 of 24000 k = 40 19 / 24, 2000 42 / 46, but k = 100 2000 76 / 68, and 300 15 / 14.
-// (Top-k of bf16 rows: 300 of 9001 k = 40 15 / 12, 8000 108 / 90, 2000 of 32761 37 / 37, k = 100 66 / 52.)
+// Whole steps that it takes from the wide kernel (us, resident / wide): top-k of fp32 rows above 16384 on more than two a compute
+// unit, 600 of 24000 k = 40 19 / 24, 2000 42 / 46, but k = 100 2000 76 / 68, and 300 15 / 14.  (Of bf16 rows none: k = 40 300 of
+// 9001 15 / 12, 8000 108 / 90, 2000 of 32761 37 / 37, k = 100 66 / 52; nuclei, which the wide kernel counts by value, 300 of 24001
+// 23 / 15, 2000 of 32001 63 / 45, 8000 211 / 146.)
 static bool resident_pays(const as_ctx *ctx, const void *logits, int64_t rows, int64_t ld, bool has_k, int32_t top_k)
 {
     if (!resident_fits(ctx, logits, ld, has_k, top_k)) return false;
     if (ctx->thr_path == 2) return true;
-    if (ctx->dtype == AS_BF16) return !has_k && rows > (int64_t)ctx->num_cus && ctx->V > 20480;
-    return has_k && ctx->V > 16384 && rows > 2 * (int64_t)ctx->num_cus && (top_k <= 64 || rows <= 4 * (int64_t)ctx->num_cus);
+    return ctx->dtype != AS_BF16 && has_k && ctx->V > 16384 && rows > 2 * (int64_t)ctx->num_cus && (top_k <= 64 || rows <= 4 * (int64_t)ctx->num_cus);
 }
 
 // Whether topk_tile_kernel takes a step.  Its bound is the k-th largest of the lanes' maxima, and what reaches the bound

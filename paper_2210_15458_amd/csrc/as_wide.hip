@@ -14,7 +14,8 @@
 //                     logits at or above it become a candidate table in LDS (value, index), and everything that
 //                     follows - the exact k-th with its ties, the nucleus over the survivors, the code's bucket -
 //                     is ranks and scans over that table.
-//   nucleus           32-bit tallies in kBins bins over kOctaves factors of two (1024 to 4096 over 64; a wave has 512 over 32); the
+//   nucleus, bf16     a counter a value while the row lands, look-ups in a table of the kept values' weights after it (see below)
+//   nucleus           (fp32 rows, thresholds alone, bf16 rows that counters do not suit) 32-bit tallies in kBins bins over kOctaves factors of two (1024 to 4096 over 64; a wave has 512 over 32); the
 //                     bin in which the nucleus closes; the chunk sums of everything above a window around it, the
 //                     window's logits as a list that is closed by integer masses (see below).
 //   larger k          counts in as many bins over 64 factors of two, the logits of the closing bin as a list; a nucleus after it
@@ -22,8 +23,8 @@
 // Then the chunk of the code (64 pieces, vocabulary order), its lane, its logit.  Sums that decide anything are taken
 // in an order, or in integers, that does not depend on which lane comes first.
 //
-// One launch against threshold kernel and sampling kernel before: 1 row of 50257 bf16, p = 0.95 21.6 us (45), 512 rows
-// of 50257 fp32, p = 0.92 41.6 us (76; the 103 MB alone take 19 at 5.5 TB/s), 230 rows of 256000 bf16, k = 50 then
+// One launch against threshold kernel and sampling kernel before: 1 row of 50257 bf16, p = 0.95 13.0 us (45; 20.8 by tallies),
+// 512 rows of 50257 fp32, p = 0.92 41.6 us (76; the 103 MB alone take 19 at 5.5 TB/s), 230 rows of 256000 bf16, k = 50 then
 // p = 0.95 42.4 us (171; 21).
 #include <type_traits>
 
@@ -94,11 +95,13 @@ template <int NT, bool MULTI, bool SHORT> struct WideShared {
     static constexpr int kPerOctave = kBins / kOctaves;
     static constexpr int kList = NT == 1024 ? 2048 : kWave ? (SHORT ? 240 : 480) : SHORT ? 512 : 1024;
     static constexpr float kBeside = kWave ? 12.f : 32.f;    // logits of a nucleus's window on either side of its bin
+    static constexpr int kValues = kWave ? 960 : kBins < 2048 ? kBins : 2048;     // bf16 values with a counter of their own ...
+    static constexpr int kHigher = kValues / 4;              // ... of which above the first pieces' largest (128 to a factor of two)
     // (a row of 2^21 fp32 logits: 8193; with 512 threads, where two blocks are to share a unit's LDS, rows of fewer)
     static constexpr int kChunks = !MULTI ? 16 * kWaves + 1 : NT == 1024 ? 8704 : 2304;
     union {
         u64 bins[kBins];
-        uint32_t tally[kBins + 64];                          // (and a word per lane for what is not counted)
+        uint32_t tally[(kBins > kValues ? kBins : kValues) + 64];    // (and a word per lane for what is not counted)
         double cw[2][NT];                                    // candidate weights: after top-k, after the nucleus
     };
     float chunk[kChunks];                                    // weight of every chunk of 64 pieces, vocabulary order ...
@@ -497,15 +500,37 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
 
     // ------------------------------------------------------------------ selection by integer weights
     float mx = -__builtin_inff();        // the row's largest logit, once a pass has seen all of it
-    float ref;
+    float ref, first_max;                // the first pieces' largest
+    // Whether bf16 logits can be counted by value: those that are positive are expected to hold the nucleus.  Of the weights of
+    // half the first pieces the others may be four fifths of what it leaves out (they miss the row's largest logits, so that
+    // share is more likely too large than too small; a row that goes wrong is selected the other way, after one more pass).
+    constexpr bool COUNTED = DT == AS_BF16 && !TOPK;
+    bool by_value = false;
     {
         if constexpr (!TOPK) land(0);
         float x[EPV];
-        values(raw[0], x);
-        float m = vec_max<EPV>(x);
         values(rest, x);
+        float m = vec_max<EPV>(x);
+        values(raw[0], x);
         m = fmaxf(m, vec_max<EPV>(x));
-        ref = fmaxf(ceilf(wide_max<NT>(m, sh.wave_f) * k), kRefFloor);
+        float spare = 0.f;
+        if constexpr (COUNTED) {
+            m = wave_max(m);
+            const float r0 = fmaxf(ceilf(m * k), kRefFloor), in = 0.8f * (1.f - top_p), out = in - 1.f;
+#pragma unroll
+            for (int i = 0; i < EPV; i += 2) spare = fmaf(fast_exp2(fmaf(x[i], k, -r0)), x[i] > 0.f ? in : out, spare);
+            spare = wave_sum(spare);
+            if (lane == 0 && !Sh::kWave) sh.wave_d[wave] = (double)spare;
+        }
+        first_max = COUNTED && Sh::kWave ? m : wide_max<NT>(m, sh.wave_f);
+        ref = fmaxf(ceilf(first_max * k), kRefFloor);
+        if constexpr (COUNTED) {
+            if constexpr (!Sh::kWave) {
+                const float r0 = fmaxf(ceilf((lane < W ? sh.wave_f[lane] : -__builtin_inff()) * k), kRefFloor);
+                spare = wave_sum(lane < W ? (float)sh.wave_d[lane] * fast_exp2(r0 - ref) : 0.f);
+            }
+            by_value = a.tokens_out != nullptr && first_max > 0.f && spare >= 0.f;
+        }
     }
     constexpr float kTwo23 = 8388608.f;
     constexpr float kScale = (float)Sh::kPerOctave;
@@ -785,7 +810,8 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
     };
 
     float thr = -__builtin_inff();
-    bool some = true, summed = false;    // summed: the chunk sums of the kept logits are in place
+    bool some = true, summed = false;    // summed: the chunk sums of the kept logits are in place, a part of them in `extra`
+    bool in_chunks = false;              // ... or all of them in `chunk`
     if constexpr (TOPK) {
         some = select(Yes{}, 0.f, thr);
         if (some && top_p > 0.f && top_p < 1.f) {
@@ -795,6 +821,122 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
             thr = fmaxf(thr, inner);
         }
     } else {
+        bool closed = false;
+        if constexpr (COUNTED) {
+            // bf16 logits by value.  One of 65536 values, so the mass of a group of equal logits is a count times a weight: while
+            // the row lands every logit adds one to the counter of its value, in a window of kValues values around the first
+            // pieces' largest, and its weight to the lane's total; what lies below the window or is not positive goes to a word of
+            // the lane's own.  The counters, from the top, name the value at which the nucleus closes; they give way to a table of
+            // the kept values' weights, and the chunk sums of the kept logits are look-ups: half the instructions of the
+            // tallies and integer masses below, which is what bounds either (one row of 50257 takes 2400 a wave with those, 16 of
+            // its 21 us).  us, tallies / counters: 1 row of 50257 20.8 / 13.0, of 256000 63 / 34, 200 of 33001 21.2 / 12.8, 2000 of
+            // 20001 56 / 36, 2000 of 50257 112 / 72, 16000 of 8001 141 / 90, 14000 of 1501 54 / 43.  A logit above the window or a
+            // nucleus that reaches below it: the other way.  The total is a sum of fp32 weights where the other way has integers,
+            // so a nucleus that ends within 1e-7 of its share may close a group apart; thresholds alone keep to the integers.
+            int32_t top = (int32_t)(__builtin_bit_cast(uint32_t, first_max) >> 16) + Sh::kHigher;
+            top = top > 0x7f7f ? 0x7f7f : top;               // (the largest finite value)
+            const int32_t bottom = top - (Sh::kValues - 1);
+            if (by_value && bottom > 0) {
+                lds_u32 *const tally = (lds_u32 *)sh.tally;
+                __syncthreads();
+                for (int b = tid; b < Sh::kValues + 64; b += NT) sh.tally[b] = 0u;
+                if (tid == 0) sh.pick = -1;
+                __syncthreads();
+                const float nr = -ref;
+                double total = 0.0;
+                uint32_t hi = 0x80008000u;                   // the largest of either half of a word, as the sign leaves them
+                {
+                    const uint32_t low2 = (uint32_t)bottom * 0x10001u, none = (uint32_t)(Sh::kValues + lane) * 0x10001u;
+                    auto one = [&](const u32x4 &v) __attribute__((always_inline)) {
+                        total += (double)tile_lane_sum<DT, false>(v, k, nr, 0.f);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            hi = pk_max_i16(hi, v[i]);
+                            const uint32_t d = pk_min_u16(pk_sub_u16(v[i], low2), none);
+                            __hip_atomic_fetch_add(tally + (d & 0xffffu), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                            __hip_atomic_fetch_add(tally + (d >> 16), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        }
+                        asm volatile("" : "+v"(hi));
+                    };
+                    sweep(Yes{}, [&](const u32x4 &v, int, int32_t) __attribute__((always_inline)) { one(v); }, nothing_more);
+                    if (tail != 0 && wave == 0) one(rest);
+                }
+                const bool above = (int32_t)hi >> 16 > top || (int32_t)(hi << 16) >> 16 > top;
+                total = wave_sum(total);
+                const u64 any_above = __ballot(above);
+                if (lane == 0) {
+                    sh.wave_d[wave] = total;
+                    sh.wave_lo[wave] = any_above != 0ull;
+                }
+                __syncthreads();
+                // running mass over the counters, from the top; a thread has kPer of them
+                constexpr int kPer = Sh::kValues / NT;
+                static_assert(kPer * NT == Sh::kValues, "a share of the counters for every thread");
+                double local = 0.0, unused;
+                total = wide_total<NT>(sh.wave_d, unused);
+                const bool inside = __ballot(lane < W && sh.wave_lo[lane < W ? lane : 0] != 0u) == 0ull;
+                // (Weights made anew where they are wanted again: kept, fifteen of them a lane spill a wave's row, and so does a branch
+                // for the values that no logit has, some of whose weights are beyond fp32.)
+                auto weight_of = [&](int32_t b) __attribute__((always_inline)) {
+                    asm volatile("" : "+v"(b));
+                    return fminf(fast_exp2(fmaf(bits_f32((uint32_t)(bottom + b) << 16), k, nr)), 3e38f);
+                };
+                auto mass_at = [&](int32_t b) __attribute__((always_inline)) {
+                    return (double)sh.tally[b] * (double)weight_of(b);
+                };
+                const int32_t b0 = Sh::kValues - 1 - tid * kPer; // the thread's highest
+#pragma unroll
+                for (int i = 0; i < kPer; ++i) local += mass_at(b0 - i);
+                const double incl = wave_scan_add(local);
+                if (lane == 63) sh.wave_e[wave] = incl;
+                __syncthreads();
+                double lo;
+                wide_total<NT>(sh.wave_e, lo);
+                lo += incl - local;
+                const double need = (double)top_p * total;
+                if (!(lo >= need) && lo + local >= need) {
+                    double acc = lo;
+                    int32_t found = -1, lowest = -1;
+#pragma unroll 1
+                    for (int i = 0; i < kPer; ++i) {
+                        const bool any = sh.tally[b0 - i] != 0u;
+                        acc += mass_at(b0 - i);
+                        if (any) lowest = b0 - i;
+                        if (found < 0 && any && acc >= need) found = b0 - i;
+                    }
+                    sh.pick = found >= 0 ? found : lowest;   // (the two orders of summation differ in the last place)
+                }
+                __syncthreads();
+                const int32_t pick = sh.pick;
+                if (inside && pick >= 0 && total < (double)__builtin_inff()) {
+                    // The kept values' weights, from the threshold's on, and behind them 64 zeros, a word a lane, for all others.
+                    float *const wtab = reinterpret_cast<float *>(sh.tally);
+                    const int32_t kept = Sh::kValues - pick;
+#pragma unroll
+                    for (int i = 0; i < kPer; ++i)
+                        if (b0 - i >= pick) wtab[b0 - i - pick] = weight_of(b0 - i);
+                    if (wave == W - 1) wtab[kept + lane] = 0.f;
+                    thr = bits_f32((uint32_t)(bottom + pick) << 16);
+                    __syncthreads();
+                    const uint32_t low2 = (uint32_t)(bottom + pick) * 0x10001u, none = (uint32_t)(kept + lane) * 0x10001u;
+                    float t[4] = {0.f, 0.f, 0.f, 0.f};
+                    sweep(No{}, [&](const u32x4 &v, int p, int32_t) __attribute__((always_inline)) {
+                        float e[EPV];
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const uint32_t d = pk_min_u16(pk_sub_u16(v[i], low2), none);
+                            e[2 * i] = wtab[d & 0xffffu];
+                            e[2 * i + 1] = wtab[d >> 16];
+                        }
+                        t[p & 3] = vec_sum<EPV>(e);
+                    }, [&](int p, int32_t tile) __attribute__((always_inline)) { chunks_done(t, p, tile); });
+                    __syncthreads();
+                    if (tid == 0) sh.chunk[nfull] = tail != 0 ? tile_lane_sum<DT, true>(rest, k, nr, thr) : 0.f;
+                    closed = in_chunks = true;
+                }
+            }
+        }
+        if (!closed) {
         // The nucleus alone, the quick way.  While the row lands its logits are only counted, per bin, in 32 bits:
         // 2^s for each, corrected by where in the bin its weight lies (the weight over the bin's own, to 2^-s), so
         // a bin's tally times the weight at its centre is its mass to a few parts in 10^5.  That names the bin in
@@ -804,7 +946,6 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
         // list overflows (heavy ties, flat rows), a wave closes the window from the row.  If the window was off (neighbouring
         // bins with more than kBeside logits stay out of it), or for a block, the general selection follows.
         // (Adding the masses themselves takes 64-bit LDS atomics, 45 cycles a wave, or float ones, 300.)
-        bool closed = false;
         const int s_bits = 31 - (32 - __builtin_clz((uint32_t)V));
         const float s_one = (float)(1u << s_bits);
         lds_u32 *const tally = (lds_u32 *)sh.tally;
@@ -816,7 +957,10 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
                 sh.pick = -1;
             }
             __syncthreads();
-            const float nr = -ref, slope = s_one * (0.6931471805599453f / kScale), half = s_one + 0.5f;
+            // in bins: the bin's number, from kBin0 down, and what is left of the exponent inside the bin (-1/2 .. 1/2) as the
+            // weight's part above 2^s
+            const float slope = s_one * (0.6931471805599453f / kScale), half = s_one + 0.5f;
+            const float kb = -kScale * k, bin0 = kBin0 + kScale * ref, ks = slope * kScale * k, zero = half - slope * kScale * ref;
             const float beyond = kTwo23 + (float)(Sh::kBins + lane);
             float m = -__builtin_inff();
             auto one = [&](const u32x4 &v) __attribute__((always_inline)) {
@@ -825,10 +969,9 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
                 m = max3(m, vec_max<EPV>(x), m);
 #pragma unroll
                 for (int i = 0; i < EPV; ++i) {
-                    const float y = fmaf(x[i], k, nr);
-                    const float t = __builtin_amdgcn_fmed3f(fmaf(y, -kScale, kBin0), kBinLo, beyond);
-                    const float off = fmaf(y, kScale, t - kBin0);            // -1/2 .. 1/2 inside the bin
-                    const uint32_t inc = (uint32_t)fmaxf(fmaf(off, slope, half), 0.f);
+                    const float t = __builtin_amdgcn_fmed3f(fmaf(x[i], kb, bin0), kBinLo, beyond);
+                    uint32_t inc;                            // (none where it is negative: what is not counted)
+                    asm("v_cvt_u32_f32 %0, %1" : "=v"(inc) : "v"(fmaf(t - kBin0, slope, fmaf(x[i], ks, zero))));
                     const uint32_t b = __builtin_bit_cast(uint32_t, t) - 0x4B000000u;
                     __hip_atomic_fetch_add(tally + b, inc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                     if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);
@@ -1002,6 +1145,7 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
             }
         }
         if (!closed) some = select(No{}, -__builtin_inff(), thr);
+        }
     }
     if (a.tokens_out == nullptr) {
         if (tid == 0) thr_out[r] = some ? thr : -__builtin_inff();
@@ -1016,7 +1160,7 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
     const float nr = -ref;
     auto lane_sum = [&](const u32x4 &v) __attribute__((always_inline)) { return tile_lane_sum<DT, true>(v, k, nr, thr); };
     const int32_t nchunks = nfull + 1;                       // the last one: the piece that the row ends in
-    if (!summed) {
+    if (!summed && !in_chunks) {
         __syncthreads();
         if constexpr (TOPK) {
             float t[4] = {0.f, 0.f, 0.f, 0.f};
@@ -1134,7 +1278,7 @@ void launch_form(as_ctx *ctx, int kid, const StepArgs &a, int32_t top_k, float t
 // top-k 1.28 to 1.36, k = 200 1.16; 600 of them no different.  With more rows still, a wave a row: nothing in it waits for
 // another wave, and what a block does in some 25 steps of its waves overlaps over rows instead (us, blocks / waves: nuclei, 1500
 // rows of 1500 bf16 20.5 / 14.9, 600 14.0 / 13.0, 14251 of 1923 119 / 63, 5252 of 3078 57 / 38, 4200 of 8001 58 / 56, 2600 42 /
-// 47; k = 40 2100 of 4001 18.6 / 16.3, 1500 of 3000 13.1 / 14.6, 9000 of 6001 53 / 47, 4200 of 8001 31 / 32; counts, k = 1000,
+// 47; counted by value 900 of 1501 11.0 / 10.3, 1500 of 4001 14.4 / 13.8, 2500 of 8001 23.7 / 24.7, 4500 36.2 / 34.9; k = 40 2100 of 4001 18.6 / 16.3, 1500 of 3000 13.1 / 14.6, 9000 of 6001 53 / 47, 4200 of 8001 31 / 32; counts, k = 1000,
 // 4000 of 1500 30 / 18, 2100 of 4001 23 / 25, 9000 of 6001 79 / 77, 6000 of 4000 fp32 k = 200 38 / 33, but on flat or steep ones 38 / 45 and more).  Those rows
 // have a standard deviation of 3 against the temperature; a wave has a shorter list, so flat rows decide whether its line holds:
 // of 0.3 at a temperature of 0.9, nuclei p = 0.9 4000 of 1500 37 / 23, 6000 of 3000 65 / 44, 3000 of 4000 41 / 47, 8000 of 8000
@@ -1152,7 +1296,8 @@ void launch_type(as_ctx *ctx, int kid, const StepArgs &a, int32_t top_k, float t
     const bool counts = TOPK && top_k > kWaveTopK;
     const bool table = counts && has_p && top_k <= 64 && most > 64 * 4;      // (4816 rows of 3315, k = 50, p = 0.73: 34 / 38)
     const int64_t never = 1LL << 40;
-    const int64_t waves = most <= 64 * 8 ? (table ? never : !TOPK ? 4 : counts ? 12 : 6) : !TOPK ? 16 : !counts || (!has_p && most <= 64 * 12) ? 20 : never;
+    const int64_t by_waves = DT == AS_BF16 && a.tokens_out ? 12 : 16;
+    const int64_t waves = most <= 64 * 8 ? (table ? never : !TOPK ? 4 : counts ? 12 : 6) : !TOPK ? by_waves : !counts || (!has_p && most <= 64 * 12) ? 20 : never;
     if (most <= 64 * 16 && a.rows > waves * (int64_t)ctx->num_cus) {
         if (most <= 64 * 8) return launch_form<DT, 64, 8, false, TOPK, 5>(ctx, kid, a, top_k, top_p, thr_out);
         return launch_form<DT, 64, 16, false, TOPK, 4>(ctx, kid, a, top_k, top_p, thr_out);

@@ -1,0 +1,36 @@
+"""The nucleus of bf16 rows of any shape, whose logits the wide kernel counts by value: rows on which that holds and rows on
+which it does not (a logit above the counters, a nucleus that reaches below them or below zero), each form of the kernel."""
+import numpy as np
+import pytest
+
+from paper_2210_15458_amd import synth
+
+pytestmark = pytest.mark.gpu
+ANY = {"thr_path": 3}
+CODES = np.array([0.0, 0.03, 0.2, 0.41, 0.5, 0.77, 0.9, 0.99, 1 - 2.0 ** -24], np.float32)
+
+
+def _rows(V):
+    rng = np.random.default_rng(V)
+    n = lambda s: rng.standard_normal(V) * s
+    x = np.stack([n(3.0), n(2.0) + 20.0, n(1.0), n(0.3), n(2.5) - 30.0,       # (one that is negative throughout)
+                  np.full(V, 4.0), n(3.0), n(3.0), np.where(rng.random(V) < 0.3, -np.inf, n(2.0))]).astype(np.float32)
+    x[6, V // 2] = 4000.0                                    # above every counter
+    x[7, V - 1] = 40.0                                       # the row's last, far above the first ones
+    return synth.f32_to_bf16_bits(x)
+
+
+# a wave a row, 256, 512 and 1024 threads, one tile and several; rows that start off 16 bytes and end inside a piece
+@pytest.mark.parametrize("V,rows", [(5, 9), (1023, 9), (4095, 3200), (4097, 9), (8191, 3200), (8193, 600), (16380, 600), (16385, 300),
+                                    (32769, 9), (50257, 300), (65537, 9), (70001, 300), (140001, 9)])
+def test_counted_rows(V, rows):
+    from gpu_util import compare_step, oracle_step, run_gpu_step
+    stored = _rows(V)
+    rid = (np.arange(rows) % len(stored)).astype(np.int32)
+    codes = CODES if rows == len(CODES) else synth.uniform_codes(rows, seed=V)
+    for temp, top_p in ((1.0, 0.9), (0.7, 0.5), (0.4, 0.98), (1.3, 0.97)):
+        label = f"V={V} R={rows} temp={temp} p={top_p}"
+        print("case", label, flush=True)
+        gpu = run_gpu_step(stored, codes, V, temp=temp, top_p=top_p, row_ids=rid, tuning=ANY)
+        ref = oracle_step(stored, codes, V, temp=temp, top_p=top_p, row_ids=rid.astype(np.int64))
+        print("   ", compare_step(gpu, ref, V, label, trunc=True, codes=codes), flush=True)

@@ -1721,6 +1721,7 @@ __global__ __launch_bounds__(kThreads, 4) void nucleus_tile_kernel(StepArgs a, f
     for (int g = 1; g < kNucAhead; ++g) request_group(g);
     __builtin_amdgcn_sched_barrier(0);
     f32x4 *const my_sums = reinterpret_cast<f32x4 *>(tn.sums.chunk_sum + wave * ITERS);
+    if (lane < NG) my_sums[lane] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     // ---------------- where the window goes: the largest logit of the four waves' first chunks (as a key that
     // orders like the values), and a margin above it
@@ -1761,6 +1762,9 @@ __global__ __launch_bounds__(kThreads, 4) void nucleus_tile_kernel(StepArgs a, f
                 request_group(g + kNucAhead);
                 __builtin_amdgcn_sched_barrier(0);
             }
+            // (a wave pays for the groups that its share has: us, with all sixteen pieces / so, 1000 rows of 9600 21.0 / 15.3, of
+            // 16000 21.4 / 17.7, 3000 of 12800 51 / 40, 300 of 4096 13.3 / 8.6; rows that fill the tile are no slower)
+            if (g != 0 && v0 + g * G * 64 >= nvec) continue;
             float t[G];
 #pragma unroll
             for (int jj = 0; jj < G; ++jj) {
@@ -1900,6 +1904,7 @@ __global__ __launch_bounds__(kThreads, 4) void nucleus_tile_kernel(StepArgs a, f
             asm volatile("" : "+v"(raw[j][0]), "+v"(raw[j][1]), "+v"(raw[j][2]), "+v"(raw[j][3]));
 #pragma unroll
         for (int g = 0; g < NG; ++g) {
+            if (g != 0 && v0 + g * G * 64 >= nvec) continue;
             float t[G];
 #pragma unroll
             for (int jj = 0; jj < G; ++jj) {
@@ -2032,7 +2037,9 @@ static bool threshold_streamed_pays(const as_ctx *ctx, int64_t rows, bool has_k,
 }
 
 // Whether a truncated step of `rows` rows takes a one-tile kernel, where its logits allow one
-// (the nucleus: 8000 rows of 8200 127 us against 106 in the wide kernel, of 11000 128 / 116, of 12800 even; 2000 even)
+// (The nucleus, us, here / in the wide kernel: 1000 rows of 9600 15.3 / 15.1, of 16000 17.7 / 17.5, of 32128 23.4 / 25.4; 3000 of
+// 12800 39.9 / 31.5, of 16000 43.0 / 34.2, but decodes of as many codes work from the records of this form: the lines stay where
+// they were before either counted as it does.)
 static bool by_tile(const as_ctx *ctx, int64_t rows, float k, bool has_k, int32_t top_k)
 {
     const int64_t cus = ctx->num_cus;

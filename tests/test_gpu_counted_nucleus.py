@@ -34,3 +34,14 @@ def test_counted_rows(V, rows):
         gpu = run_gpu_step(stored, codes, V, temp=temp, top_p=top_p, row_ids=rid, tuning=ANY)
         ref = oracle_step(stored, codes, V, temp=temp, top_p=top_p, row_ids=rid.astype(np.int64))
         print("   ", compare_step(gpu, ref, V, label, trunc=True, codes=codes), flush=True)
+
+
+# rows of one tile of whole pieces, which have a kernel of their own: on either side of the groups of pieces that a wave's share has
+@pytest.mark.parametrize("V", [8, 2040, 2048, 2056, 8192, 8200, 10240, 10248, 30720, 30728, 32768])
+def test_one_tile_by_the_groups_of_a_share(V):
+    from gpu_util import compare_step, oracle_step, run_gpu_step
+    stored = synth.gaussian_logits(9, V, seed=V, dtype="bf16")
+    for top_p in (0.5, 0.95):
+        gpu = run_gpu_step(stored, CODES, V, temp=0.9, top_p=top_p)
+        ref = oracle_step(stored, CODES, V, temp=0.9, top_p=top_p)
+        print(f"V={V} p={top_p}", compare_step(gpu, ref, V, f"V={V} p={top_p}", trunc=True, codes=CODES), flush=True)

@@ -11,9 +11,9 @@
 //
 //   top-k by a table  (k up to table_most: 40, 48, 64, 96 or 128 by the form, the row's length and whether a nucleus follows)
 //                     The k-th largest of 256 group maxima bounds the k-th largest logit from below; the few
-//                     logits at or above it become a candidate table in LDS (value, index), and everything that
-//                     follows - the exact k-th with its ties, the nucleus over the survivors, the code's bucket -
-//                     is ranks and scans over that table.
+//                     pieces that hold logits at or above it go to a table of their wave's, from which those logits become
+//                     candidates (value, index), and everything that follows - the exact k-th with its ties, the nucleus
+//                     over the survivors, the code's bucket - is ranks and scans over these, by one wave where 64 hold them.
 //   nucleus, bf16     a counter a value while the row lands, look-ups in a table of the kept values' weights after it (see below)
 //   nucleus           (fp32 rows, thresholds alone, bf16 rows that counters do not suit) 32-bit tallies in kBins bins over kOctaves factors of two (1024 to 4096 over 64; a wave has 512 over 32); the
 //                     bin in which the nucleus closes; the chunk sums of everything above a window around it, the
@@ -24,8 +24,8 @@
 // in an order, or in integers, that does not depend on which lane comes first.
 //
 // One launch against threshold kernel and sampling kernel before: 1 row of 50257 bf16, p = 0.95 13.0 us (45; 20.8 by tallies),
-// 512 rows of 50257 fp32, p = 0.92 41.6 us (76; the 103 MB alone take 19 at 5.5 TB/s), 230 rows of 256000 bf16, k = 50 then
-// p = 0.95 42.4 us (171; 21).
+// 512 rows of 50257 fp32, p = 0.92 40.3 us (76; the 103 MB alone take 19 at 5.5 TB/s), 230 rows of 256000 bf16, k = 50 then
+// p = 0.95 33.4 us (171; 41.0 with candidates one by one and tiles in turn; 21).
 #include <type_traits>
 
 #include "as_common.hpp"
@@ -38,6 +38,7 @@ namespace {
 typedef unsigned long long u64;
 
 constexpr int kWideTopK = 128;           // largest k of the candidate table
+constexpr int kFewTopK = 56;             // ... whose candidates one wave finishes, if there are no more than 64 (ties)
 constexpr int kWaveTopK = 40;            // ... where a wave has the row (64 candidates)
 
 // The largest k that a form takes by the candidate table; above it, by counts.  A table of n candidates costs what their
@@ -103,6 +104,10 @@ template <int NT, bool MULTI, bool SHORT> struct WideShared {
         u64 bins[kBins];
         uint32_t tally[(kBins > kValues ? kBins : kValues) + 64];    // (and a word per lane for what is not counted)
         double cw[2][NT];                                    // candidate weights: after top-k, after the nucleus
+        struct {
+            u32x4 piece[kWaves][64];                         // pieces with candidates, a table of each wave's
+            int32_t first[kWaves][64];                       // the vocabulary index of each one's first logit
+        } hot;
     };
     float chunk[kChunks];                                    // weight of every chunk of 64 pieces, vocabulary order ...
     static constexpr int kExtra = MULTI ? 2304 : kChunks;    // (longer rows do without the quick way)
@@ -135,6 +140,8 @@ __device__ __forceinline__ u64 read_lane(u64 x, int lane)
     const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(x >> 32), lane);
     return ((u64)hi << 32) | lo;
 }
+// What a wave has written to LDS before is there for all its lanes after (it serves a wave in order).
+__device__ __forceinline__ void wave_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 template <int N> __device__ __forceinline__ u64 lane_scan(u64 x)
 {
     const int lane = threadIdx.x & 63;
@@ -310,8 +317,179 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
         }
     };
 
+    // The candidates (n <= NT) that are among the k highest, with all whose upper 16 bits are the k-th's, to the front of the table, by
+    // one wave: it finds those as it found the bound, which becomes that.  (bf16 has no other bits; in fp32 a few more stay.)
+    auto shrink = [&](uint32_t n) __attribute__((always_inline)) {
+        constexpr int kLow = 16;
+        constexpr int M = NT / 64;
+        uint32_t c[M];
+        uint32_t lo = (uint32_t)sh.before >> kLow, hi = 0u;
+#pragma unroll
+        for (int i = 0; i < M; ++i) {
+            c[i] = 0u;
+            if ((uint32_t)(i * 64) < n) {
+                const bool in = (uint32_t)(i * 64 + lane) < n;
+                c[i] = in ? order_key(__builtin_bit_cast(float, sh.key[i * 64 + lane])) >> kLow : 0u;
+                hi = max(hi, c[i]);
+            }
+        }
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) hi = max(hi, (uint32_t)__shfl_xor((int)hi, d, 64));
+        hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)hi);
+        lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)lo);
+        while (lo < hi) {
+            const uint32_t mid = lo + (hi - lo) / 2u + 1u;
+            int cnt = 0;
+#pragma unroll
+            for (int i = 0; i < M; ++i)
+                if ((uint32_t)(i * 64) < n) cnt += __builtin_popcountll(__ballot(c[i] >= mid));
+            if (cnt >= top_k) lo = mid;
+            else hi = mid - 1u;
+        }
+        uint32_t at = 0;
+#pragma unroll
+        for (int i = 0; i < M; ++i)
+            if ((uint32_t)(i * 64) < n) {
+                // (a place is never behind where its candidate is)
+                const uint32_t x = sh.key[i * 64 + lane], id = sh.idx[i * 64 + lane];
+                const u64 in = __ballot(c[i] >= lo);
+                wave_lds();
+                if (c[i] >= lo) {
+                    const uint32_t place = at + __builtin_amdgcn_mbcnt_hi((uint32_t)(in >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)in, 0u));
+                    sh.key[place] = x;
+                    sh.idx[place] = id;
+                }
+                at += (uint32_t)__builtin_popcountll(in);
+            }
+        if (lane == 0) {
+            sh.n = at;
+            sh.before = (u64)lo << kLow;
+        }
+    };
+
+    // The bound alone, and nothing of the table in registers, which hold two tiles of the row then.
+    auto raise = [&](uint32_t n) __attribute__((always_inline)) {
+        uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.before), hi = 0xff800000u;           // (+infinity's)
+        while (lo < hi) {
+            const uint32_t mid = lo + (hi - lo) / 2u + 1u;
+            int cnt = 0;
+#pragma unroll 2
+            for (uint32_t i = 0; i < n; i += 64)
+                cnt += __builtin_popcountll(__ballot(i + lane < n && order_key(__builtin_bit_cast(float, sh.key[i + lane])) >= mid));
+            if (cnt >= top_k) lo = mid;
+            else hi = mid - 1u;
+        }
+        if (lane == 0) sh.before = lo;
+    };
+
+    // The step from n <= 64 candidates, a lane each in sh.key and sh.idx, by one wave; `more`: others than the k highest among them.
+    auto finish_few = [&](uint32_t n, bool more) __attribute__((always_inline)) {
+        const uint32_t n4 = (n + 3u) & ~3u;
+        const bool have = (uint32_t)lane < n;
+        const float x = have ? __builtin_bit_cast(float, sh.key[lane]) : -__builtin_inff();
+        const uint32_t idx = have ? sh.idx[lane] : 0xffffffffu;
+        wave_lds();
+        if (!have && (uint32_t)lane < n4) {
+            sh.key[lane] = 0xff800000u;
+            sh.idx[lane] = 0xffffffffu;
+        }
+        wave_lds();
+        const bool by_mass = top_p > 0.f && top_p < 1.f;
+        bool kept = have;
+        uint32_t place = 0;
+        if (more || by_mass) {
+            // its place by value; among the k highest (all that are tied with the k-th) if fewer than k lie above
+            uint32_t above = 0;
+#pragma unroll 4
+            for (uint32_t j = 0; j < n4; j += 4) {
+                const f32x4 o = *reinterpret_cast<const f32x4 *>(&sh.key[j]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    above += o[i] > x ? 1u : 0u;
+                    place += o[i] == x && j + i < (uint32_t)lane ? 1u : 0u;
+                }
+            }
+            place += above;
+            kept = have && above < (uint32_t)top_k;
+        }
+        const float few_ref = fmaxf(ceilf(wave_max(x) * k), kRefFloor);
+        float w = kept ? fast_exp2(fmaf(x, k, -few_ref)) : 0.f;
+        if (by_mass) {
+            // the value at which the running mass, from the highest down, reaches top_p of the survivors'
+            if (have) {
+                sh.cw[0][place] = (double)mass_of(w);
+                sh.sorted[place] = __builtin_bit_cast(uint32_t, x);
+            }
+            wave_lds();
+            const double v = have ? sh.cw[0][lane] : 0.0;
+            const float by_place = have ? __builtin_bit_cast(float, sh.sorted[lane]) : 0.f;
+            wave_lds();
+            const double incl = wave_scan_add(v);
+            const double goal = (double)top_p * as::read_lane(incl, 63);
+            const u64 closes = __ballot(have && !(incl - v >= goal) && incl >= goal);
+            const float low = closes ? as::read_lane(by_place, (int)__builtin_ctzll(closes)) : -__builtin_inff();
+            kept = kept && x >= low;
+            w = kept ? w : 0.f;
+        }
+        if (a.tokens_out == nullptr) {
+            const float low = -wave_max(kept ? -x : -__builtin_inff());
+            if (lane == 0) thr_out[r] = low;
+            return;
+        }
+        // the kept ones in vocabulary order; the bucket is the last one that has weight and whose mass before it does not exceed c*S
+        if (have && !(w > 0.f)) sh.idx[lane] = 0xffffffffu;
+        sh.cw[1][lane] = 0.0;
+        wave_lds();
+        if (w > 0.f) {
+            uint32_t place = 0;
+#pragma unroll 4
+            for (uint32_t j = 0; j < n4; j += 4) {
+                const u32x4 o = *reinterpret_cast<const u32x4 *>(&sh.idx[j]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) place += o[i] < idx ? 1u : 0u;
+            }
+            sh.cw[1][place] = (double)w;
+            sh.sorted[place] = idx;
+        }
+        wave_lds();
+        const double v = sh.cw[1][lane];
+        const double incl = wave_scan_add(v);
+        const double S = as::read_lane(incl, 63);
+        const double tau = (double)a.codes[r] * S, mine = incl - v;
+        const u64 cand = __ballot(v > 0.0 && mine <= tau);
+        if (cand == 0ull) {
+            safe_row();
+        } else if (lane == 63 - (int)__builtin_clzll(cand)) {
+            const uint32_t token = sh.sorted[lane];
+            RowOut o;
+            o.token = (int32_t)(token < (uint32_t)V ? token : (uint32_t)(V - 1));
+            o.c_next = rescale_code(tau, mine, v);
+            o.prob = (float)(v / S);
+            o.f_lo = (float)(mine / S);
+            write_row(a, r, o);
+        }
+    };
+
     // ------------------------------------------------------------------ top-k by a table of candidates
     if constexpr (TOPK) {
+        const bool by_table = top_k <= table_most<NT, NP>(V / EPV, top_p > 0.f && top_p < 1.f);
+        // Rows of several tiles by the table: the pieces of the tile after the next are requested as those of this one are looked at,
+        // so that loads are on their way throughout.  (us, tiles of 16 pieces in turn, whose row spilled / so: 256 rows of 256000
+        // bf16 k = 50, p = 0.95 45 / 36, k = 128 62 / 45, k = 1 37 / 29.5, 1000 k = 40 144 / 117, 128 of 256000 fp32 47 / 36; a
+        // candidate one by one, each waiting for its place, where waves now keep pieces: 38.)
+        constexpr bool STREAM = MULTI && NP == 8;
+        u32x4 nxt[STREAM ? NP : 1];
+        auto request = [&](u32x4 &v, int p, int32_t t) __attribute__((always_inline)) {
+            const int32_t i = (t * NP + p) * NT + tid;
+            v = pieces[i < last ? i : last];
+        };
+        if constexpr (STREAM) {
+            if (by_table) {
+#pragma unroll
+                for (int p = 0; p < NP; ++p) request(nxt[p], p, 1);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
         // the largest of the logits of 256 groups: of one, two or four lanes, or (a wave a row) of every fourth of a lane's pieces
         constexpr int kOwn = Sh::kWave ? 4 : 1;
         float gm[kOwn];
@@ -341,7 +519,18 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
                 gm[0] = max3(gm[0], vec_max<EPV>(x), gm[0]);
             }
         }
-        if (top_k <= table_most<NT, NP>(V / EPV, top_p > 0.f && top_p < 1.f)) {
+        if (by_table) {
+            if constexpr (STREAM) {                          // (the bound is of two tiles: half as many logits pass it)
+#pragma unroll
+                for (int p = 0; p < NP; ++p) {
+                    const bool in = (NP + p) * NT + tid < nwhole;
+                    float x[EPV];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) nxt[p][q] = in ? nxt[p][q] : kNegInf;
+                    values(nxt[p], x);
+                    gm[0] = max3(gm[0], vec_max<EPV>(x), gm[0]);
+                }
+            }
             if (tid == 0) {
                 sh.n = 0;
                 sh.sel = 0;
@@ -378,12 +567,34 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
                 if (lane == 0) sh.before = lo;
             }
             __syncthreads();
-            const float xb = from_order_key((uint32_t)sh.before);
+            float xb = from_order_key((uint32_t)sh.before);
             const bool bounded = xb > -__builtin_inff();
+            // (positive bf16 in pairs, as they are stored: those above `below`, which is the value under the bound)
+            bool in_pairs = DT == AS_BF16 && xb > 0.f;
+            uint32_t below = ((__builtin_bit_cast(uint32_t, xb) >> 16) - 1u) * 0x10001u;
+            int32_t held = 0;                                // pieces in the wave's table
             auto push = [&](const u32x4 &v, int32_t first) __attribute__((always_inline)) {
-                float x[EPV];
-                values(v, x);
-                if (vec_max<EPV>(x) >= xb) {
+                bool hot;
+                if (in_pairs) {
+                    hot = pk_max_i16(pk_max_i16(pk_max_i16(v[0], v[1]), pk_max_i16(v[2], v[3])), below) != below;
+                } else {
+                    float x[EPV];
+                    values(v, x);
+                    hot = vec_max<EPV>(x) >= xb;
+                }
+                const u64 in = __ballot(hot);
+                if (in == 0ull) return;
+                const int32_t c = __builtin_popcountll(in);
+                if (held + c <= 64) {
+                    if (hot) {
+                        const int32_t at = held + (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(in >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)in, 0u));
+                        sh.hot.piece[wave][at] = v;
+                        sh.hot.first[wave][at] = first - shift;
+                    }
+                    held += c;
+                } else if (hot) {                            // (a wave whose table is full: one by one)
+                    float x[EPV];
+                    values(v, x);
 #pragma unroll
                     for (int e = 0; e < EPV; ++e)
                         if (x[e] >= xb) {
@@ -395,14 +606,99 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
                         }
                 }
             };
+            // the wave's pieces taken apart, a lane each
+            auto take_apart = [&]() __attribute__((always_inline)) {
+                if (held == 0) return;
+                wave_lds();
+                float x[EPV];
+                values(lane < held ? sh.hot.piece[wave][lane] : nothing, x);
+                const int32_t first = sh.hot.first[wave][lane];
+                uint32_t mine = 0;
+#pragma unroll
+                for (int e = 0; e < EPV; ++e) mine += (uint32_t)__builtin_popcountll(__ballot(x[e] >= xb));
+                uint32_t at = 0;
+                if (lane == 0) at = atomicAdd(&sh.n, mine);
+                at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+#pragma unroll
+                for (int e = 0; e < EPV; ++e) {
+                    const u64 in = __ballot(x[e] >= xb);
+                    const uint32_t slot = at + __builtin_amdgcn_mbcnt_hi((uint32_t)(in >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)in, 0u));
+                    if (x[e] >= xb && slot < (uint32_t)NT) {
+                        sh.key[slot] = __builtin_bit_cast(uint32_t, x[e]);
+                        sh.idx[slot] = (uint32_t)(first + e);
+                    }
+                    at += (uint32_t)__builtin_popcountll(in);
+                }
+                held = 0;
+            };
             if (bounded) {
-                sweep(No{}, [&](const u32x4 &v, int p, int32_t t) __attribute__((always_inline)) {
-                    push(v, ((t * NP + p) * NT + tid) * EPV);
-                }, nothing_more);
+                if constexpr (STREAM) {
+                    auto take = [&](u32x4 &v, int p, int32_t t) __attribute__((always_inline)) {
+                        const int32_t i = (t * NP + p) * NT + tid;
+                        if (present(p, t)) {
+                            if (t > 1) {
+                                const bool in = i < nwhole;
+#pragma unroll
+                                for (int q = 0; q < 4; ++q) v[q] = in ? v[q] : kNegInf;
+                            }
+                            push(v, i * EPV);
+                        }
+                        request(v, p, t + 2);
+                        __builtin_amdgcn_sched_barrier(0);
+                    };
+                    for (int32_t t = 0; t < ntiles; t += 2) {
+#pragma unroll
+                        for (int p = 0; p < NP; ++p) take(raw[p], p, t);
+#pragma unroll
+                        for (int p = 0; p < NP; ++p) take(nxt[p], p, t + 1);
+                        if (t + 2 < ntiles) {
+                            // (each tile brings as many as the first: after 2, 4, 8 of them a better bound, from the table)
+                            if (((t + 2) & (t + 1)) != 0) continue;
+                            take_apart();
+                            __syncthreads();
+                            const uint32_t n = sh.n;
+                            if (n > (uint32_t)NT) break;
+                            if (n > (uint32_t)NT / 4) {
+                                __syncthreads();
+                                if (wave == 0) raise(n);
+                                __syncthreads();
+                                xb = from_order_key((uint32_t)sh.before);
+                                below = ((__builtin_bit_cast(uint32_t, xb) >> 16) - 1u) * 0x10001u;
+                                in_pairs = DT == AS_BF16 && xb > 0.f;
+                            }
+                        }
+                    }
+                } else {
+                    sweep(No{}, [&](const u32x4 &v, int p, int32_t t) __attribute__((always_inline)) {
+                        push(v, ((t * NP + p) * NT + tid) * EPV);
+                    }, nothing_more);
+                }
                 if (tail != 0 && wave == 0) push(rest, nwhole * EPV);
+                take_apart();
             }
             __syncthreads();
-            const uint32_t n = sh.n;
+            uint32_t n = sh.n;
+            if constexpr (!Sh::kWave) {
+                // One wave finishes where a lane each holds those that stay: the block takes eight more barriers and ranks all
+                // candidates.  Of more than 64 it finds the k-th largest first, as it found the bound; where more than 64 stay, that
+                // pays if most go (us, by the block / so: 1 row of 50257 bf16 k = 50, p = 0.95 11.9 / 10.0, 900 of 4001 k = 50, p = 0.8
+                // 11.6 / 9.9, 2500 of 20003 k = 40 40.8 / 33.3, 300 of 50257 fp32 26.2 / 23.5; 16 of 9001 fp32 k = 64, of 75 candidates,
+                // 11.1 / 13.8).
+                if (bounded && n <= 64u) {
+                    if (wave == 0) finish_few(n, true);
+                    return;
+                }
+                if (bounded && n <= (uint32_t)NT && (top_k <= kFewTopK || n > 2u * (uint32_t)top_k)) {
+                    if (wave == 0) {
+                        shrink(n);
+                        wave_lds();
+                        if (sh.n <= 64u) finish_few(sh.n, DT != AS_BF16);
+                    }
+                    __syncthreads();
+                    n = sh.n;
+                    if (n <= 64u) return;
+                }
+            }
             if (bounded && n <= (uint32_t)NT) {
                 const uint32_t n4 = (n + 3u) & ~3u;
                 if ((uint32_t)tid >= n && (uint32_t)tid < n4) {
@@ -495,6 +791,12 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
                 return;
             }
             __syncthreads();
+            if constexpr (!Sh::kWave) {
+                // (the table has not taken them all: from the row's start, whose pieces are not kept beside the table)
+                load(0);
+#pragma unroll
+                for (int p = 0; p < NP; ++p) land(p);
+            }
         }
     }
 
@@ -1329,11 +1631,6 @@ void launch_type(as_ctx *ctx, int kid, const StepArgs &a, int32_t top_k, float t
     if (most <= 1024 * 8) return launch_form<DT, 1024, 8, false, TOPK>(ctx, kid, a, top_k, top_p, thr_out);
     if constexpr (TOPK || DT == AS_F32) {
         if (most <= 1024 * 16) return launch_form<DT, 1024, 16, false, TOPK>(ctx, kid, a, top_k, top_p, thr_out);
-    }
-    if constexpr (TOPK) {
-        // (the candidate table wants the larger tile; counts, whose 16-piece form spills the row, the smaller one: us, 16 / 8 pieces,
-        // k = 200 256 rows of 256000 bf16 110 / 64, 16 of 182125 76 / 40, fp32 85 / 42)
-        if (top_k <= kWideTopK) return launch_form<DT, 1024, 16, true, TOPK>(ctx, kid, a, top_k, top_p, thr_out);
     }
     launch_form<DT, 1024, 8, true, TOPK>(ctx, kid, a, top_k, top_p, thr_out);
 }

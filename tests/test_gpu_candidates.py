@@ -1,0 +1,36 @@
+"""Top-k by the wide kernel's table of candidates: rows of several tiles (as many pieces as two, three and more take, with a tail),
+candidates that one wave finishes and that it does not (ties, flat rows), all of them in one wave's pieces."""
+import numpy as np
+import pytest
+
+from paper_2210_15458_amd import synth
+
+pytestmark = pytest.mark.gpu
+ANY = {"thr_path": 3}
+CODES = np.array([0.0, 0.2, 0.41, 0.5, 0.77, 0.99, 1 - 2.0 ** -24], np.float32)
+
+
+def _rows(V):
+    rng = np.random.default_rng(V)
+    x = np.stack([rng.standard_normal(V) * 3.0, rng.standard_normal(V) * 0.05, np.sort(rng.standard_normal(V) * 2.0),
+                  np.sort(rng.standard_normal(V) * 2.0)[::-1], rng.standard_normal(V) - 40.0, np.full(V, 1.5),
+                  rng.standard_normal(V)]).astype(np.float32)
+    x[6, V // 3:V // 3 + min(600, V // 2)] += 30.0           # every candidate among neighbours
+    return x
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("pieces,more", [(0, 3), (3, 1), (1024, 2), (4096, 1), (16384, 1), (24576, 0), (24577, 3), (57344, 1), (65537, 2)])
+def test_candidate_table(pieces, more, dtype):
+    from gpu_util import compare_step, oracle_step, run_gpu_step
+    V = pieces * (8 if dtype == "bf16" else 4) + more
+    x = _rows(V)
+    stored = synth.f32_to_bf16_bits(x) if dtype == "bf16" else x
+    for top_k, top_p in ((1, 1.0), (5, 0.9), (48, 1.0), (56, 0.95), (57, 0.9), (128, 0.8)):
+        if top_k >= V:
+            continue
+        label = f"V={V} {dtype} k={top_k} p={top_p}"
+        print("case", label, flush=True)
+        gpu = run_gpu_step(stored, CODES, V, temp=0.9, top_k=top_k, top_p=top_p, tuning=ANY)
+        ref = oracle_step(stored, CODES, V, temp=0.9, top_k=top_k, top_p=top_p)
+        print("   ", compare_step(gpu, ref, V, label, trunc=True, codes=CODES), flush=True)

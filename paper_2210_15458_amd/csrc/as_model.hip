@@ -1007,8 +1007,11 @@ void launch_thin(as_ctx *ctx, const as_model *m, const int32_t *prev, int64_t ro
 __device__ __forceinline__ float widen(float x) { return x; }
 __device__ __forceinline__ float widen(uint16_t h) { return __builtin_bit_cast(float, (uint32_t)h << 16); }
 
-// WHOLE: rows start on 16 bytes and the rank is a multiple of 16: a thread moves 16 consecutive k of a row at a time
-// (otherwise single elements, consecutive threads consecutive k)
+// WHOLE: rows start on 16 bytes and the rank is a multiple of 16: a thread moves 16 consecutive k of a bf16 row at a time, or a
+// 16-byte piece of an fp32 row (otherwise single elements, consecutive threads consecutive k).  With 16 k of an fp32 row a
+// thread its loads are 64 bytes apart, and each of a wave's requests takes a quarter of 64 lines; pieces of whole lines cost four
+// small LDS writes for one of 16 bytes and are ahead all the same (us, 16 k / pieces: 4100 x 4100 x 128 56.8 / 53.2, 4096 x 4096 x
+// 256 90.0 / 85.2, 1024 x 32128 x 512 322 / 311, 256 x 4100 x 128 7.5 / 7.2).
 template <class WT, class OutT, int GM, int GN, int TM, int TN, int KS, int AHEAD, bool WHOLE>
 __global__ __launch_bounds__(256) void bigram_gemm_chain(const WT *__restrict__ E, const WT *__restrict__ Ut,
                                                          const int32_t *__restrict__ prev, int64_t R, int32_t V,
@@ -1019,7 +1022,8 @@ __global__ __launch_bounds__(256) void bigram_gemm_chain(const WT *__restrict__ 
     constexpr int MT = GM * TM * 16, NT = GN * TN * 16, ROWS = MT + NT;
     constexpr int kGroups = KS / 16, kStride = KS * 4 + 16;
     // what a thread moves per K step: runs of 16 k, or elements
-    constexpr int kUnits = WHOLE ? ROWS * kGroups : ROWS * KS, kMine = (kUnits + 255) / 256, kRun = WHOLE ? 16 : 1;
+    constexpr int kRun = !WHOLE ? 1 : sizeof(WT) == 4 ? 4 : 16;
+    constexpr int kUnits = ROWS * KS / kRun, kMine = (kUnits + 255) / 256;
     __shared__ __attribute__((aligned(16))) unsigned char smem[ROWS * kStride];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t m0 = (int64_t)blockIdx.x * MT, n0 = (int64_t)blockIdx.y * NT;
@@ -1051,7 +1055,7 @@ __global__ __launch_bounds__(256) void bigram_gemm_chain(const WT *__restrict__ 
             int k = k0 + k_of[i];
             k = k < d ? k : d - kRun;         // (past the rank: anything, replaced by zeros)
             if constexpr (WHOLE) {
-                constexpr int kPieces = 16 * (int)sizeof(WT) / 16;
+                constexpr int kPieces = kRun * (int)sizeof(WT) / 16;
 #pragma unroll
                 for (int q = 0; q < kPieces; ++q)
                     reinterpret_cast<u32x4 *>(raw[slot][i])[q] = reinterpret_cast<const u32x4 *>(src[i] + k)[q];
@@ -1067,7 +1071,11 @@ __global__ __launch_bounds__(256) void bigram_gemm_chain(const WT *__restrict__ 
             if (kUnits % 256 != 0 && tid + i * 256 >= kUnits) continue;
             const bool in = k0 + k_of[i] < d; // past the rank: zeros, which leave a chain as it is
             unsigned char *const at = smem + row_of[i] * kStride + (k_of[i] / 16) * 64;
-            if constexpr (WHOLE) {
+            if constexpr (kRun == 4) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    *reinterpret_cast<float *>(at + q * 16 + (k_of[i] & 15)) = in ? widen(raw[slot][i][q]) : 0.f;
+            } else if constexpr (WHOLE) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     f32x4 v;

@@ -30,7 +30,7 @@ def stale():
     if not os.path.exists(OUT):
         return True
     t = os.path.getmtime(OUT)
-    deps = sources() + [os.path.join(CSRC, "as_common.hpp"), os.path.join(CSRC, "as_row.hpp"), os.path.join(CSRC, "as_tile.hpp"),
+    deps = sources() + [os.path.join(CSRC, "as_common.hpp"), os.path.join(CSRC, "as_row.hpp"), os.path.join(CSRC, "as_tile.hpp"), os.path.join(CSRC, "as_pairs.hpp"),
                         os.path.join(CSRC, "as_workspace.hpp"),
                         os.path.join(HERE, "..", "include", "arith_sampling.h")]
     return any(os.path.getmtime(d) > t for d in deps)

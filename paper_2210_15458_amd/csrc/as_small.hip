@@ -130,7 +130,7 @@ __global__ __launch_bounds__(256, 3) void decode_small_kernel(SmallArgs s)
 // (which leave a chain as it is).  The row's first chunk is all of it, so the chunk that holds the code is known, and no
 // weight exceeds 1.  The bits are those of the launches that such a decode takes otherwise: rows of whole vectors have
 // the wave's reference of step_tile_kernel; ragged rows and low temperatures (LANE_REF) step_kernel's reference per lane.
-// V = 16, d = 8, 64 rows, 8 steps: 18.3 us as a block per row, 9.4 so (0.2 us a step); 2000 rows 71 (as launches), 15.
+// V = 16, d = 8, 64 rows, 8 steps: 18.3 us as a block per row, 8.3 so (0.2 us a step); 2000 rows 71 (as launches), 9.5.
 template <class WT, int DT, bool LANE_REF>
 __global__ __launch_bounds__(64) void decode_wave_kernel(SmallArgs s)
 {

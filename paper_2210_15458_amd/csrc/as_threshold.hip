@@ -26,6 +26,7 @@
 #include <type_traits>
 
 #include "as_common.hpp"
+#include "as_pairs.hpp"
 #include "as_row.hpp"
 #include "as_tile.hpp"
 

@@ -60,22 +60,6 @@ __device__ __forceinline__ float max3(float a, float b, float c)
     return d;
 }
 
-// two 16-bit values a word
-typedef short i16x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint32_t pk_max_i16(uint32_t a, uint32_t b)
-{
-    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(i16x2, a), __builtin_bit_cast(i16x2, b)));
-}
-typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint32_t pk_min_u16(uint32_t a, uint32_t b)
-{
-    return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
-}
-__device__ __forceinline__ uint32_t pk_sub_u16(uint32_t a, uint32_t b)
-{
-    return __builtin_bit_cast(uint32_t, (u16x2)(__builtin_bit_cast(u16x2, a) - __builtin_bit_cast(u16x2, b)));
-}
-
 template <int EPV> __device__ __forceinline__ float vec_max(const float *x)
 {
     if constexpr (EPV == 8) return max3(max3(max3(x[0], x[1], x[2]), x[3], x[4]), max3(x[5], x[6], x[7]), x[5]);

@@ -29,6 +29,7 @@
 #include <type_traits>
 
 #include "as_common.hpp"
+#include "as_pairs.hpp"
 #include "as_row.hpp"
 #include "as_tile.hpp"
 
@@ -592,18 +593,17 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
                         sh.hot.first[wave][at] = first - shift;
                     }
                     held += c;
-                } else if (hot) {                            // (a wave whose table is full: one by one)
-                    float x[EPV];
-                    values(v, x);
-#pragma unroll
-                    for (int e = 0; e < EPV; ++e)
-                        if (x[e] >= xb) {
-                            const uint32_t slot = atomicAdd(&sh.n, 1u);
-                            if (slot < (uint32_t)NT) {
-                                sh.key[slot] = __builtin_bit_cast(uint32_t, x[e]);
-                                sh.idx[slot] = (uint32_t)(first + e - shift);
-                            }
+                } else if (hot) {                            // (a wave whose table is full: one by one; small, it is there per piece)
+#pragma unroll 1
+                    for (int e = 0; e < EPV; ++e) {
+                        const float xe = DT == AS_BF16 ? bits_f32(e & 1 ? v[e >> 1] & 0xffff0000u : v[e >> 1] << 16) : bits_f32(v[e]);
+                        if (!(xe >= xb)) continue;
+                        const uint32_t slot = atomicAdd(&sh.n, 1u);
+                        if (slot < (uint32_t)NT) {
+                            sh.key[slot] = __builtin_bit_cast(uint32_t, xe);
+                            sh.idx[slot] = (uint32_t)(first + e - shift);
                         }
+                    }
                 }
             };
             // the wave's pieces taken apart, a lane each
@@ -652,13 +652,15 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
 #pragma unroll
                         for (int p = 0; p < NP; ++p) take(nxt[p], p, t + 1);
                         if (t + 2 < ntiles) {
-                            // (each tile brings as many as the first: after 2, 4, 8 of them a better bound, from the table)
+                            // (Each tile brings as many as the first two did apiece: after 4, 8 of them a better bound, from the table, if
+                            // that is half full.  us, from a quarter / from a half: 16 rows of 190001 fp32 k = 100 43 / 28, 256 of 256000 k =
+                            // 128 79 / 64.)
                             if (((t + 2) & (t + 1)) != 0) continue;
                             take_apart();
                             __syncthreads();
                             const uint32_t n = sh.n;
                             if (n > (uint32_t)NT) break;
-                            if (n > (uint32_t)NT / 4) {
+                            if (n > (uint32_t)NT / 2) {
                                 __syncthreads();
                                 if (wave == 0) raise(n);
                                 __syncthreads();
@@ -1360,11 +1362,13 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
                                        : ((float)(Sh::kTopOctaves * Sh::kPerOctave - wlo) + 0.5f) / kScale - lower;
             const float ylo = ((float)(Sh::kTopOctaves * Sh::kPerOctave - whi) - 0.5f) / kScale - lower;
             u64 all = 0, over = 0;                           // masses of the lane's logits; of those above the window
-            __syncthreads();                                 // (the tallies give way to tables of pieces)
             // A logit of the window joins the list: from the pieces that a wave has kept, a lane each, at the pass's end, or, where
             // they are more than its table takes, one by one, each waiting for its place.  (us, one by one throughout / so: 512
             // rows of 50257 fp32 40.3 / 39.7, 3000 of 8001 43.2 / 41.0, 8000 of 1501 32.4 / 30.1; flat bf16 rows, which are not counted
-            // by value, 2000 of 50257 149 / 138, 8000 of 8001 93 / 86.)
+            // by value, 2000 of 50257 149 / 138, 8000 of 8001 93 / 86.  A row that has a unit to itself is better off one by one, with
+            // a barrier and a pass over a table less: fp32, 1 of 5003 11.6 / 12.0, 250 12.6 / 12.9, 1 of 20011 14.7 / 15.0.)
+            constexpr bool ONE_BY_ONE = NT == 1024 && !MULTI;
+            if constexpr (!ONE_BY_ONE) __syncthreads();      // (the tallies give way to tables of pieces)
             int32_t held = 0;
             auto list = [&](float x, uint32_t q, uint32_t j, int32_t c) __attribute__((always_inline)) {
                 if (j < (uint32_t)Sh::kList) {
@@ -1391,6 +1395,14 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
                         all += q[i];
                         any |= in_window(y[i]);
                     }
+                    if constexpr (ONE_BY_ONE) {
+                        if (any) {
+#pragma unroll
+                            for (int i = 0; i < 4; ++i)
+                                if (in_window(y[i])) list(x[4 * h + i], q[i], atomicAdd(&sh.n, 1u), c);
+                        }
+                        any = false;
+                    }
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
                         e[i] = y[i] > yhi ? e[i] : 0.f;
@@ -1400,7 +1412,7 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
                     asm volatile("" : "+v"(all), "+v"(over));    // (added up here, not as a tree over the row later)
                     __builtin_amdgcn_sched_barrier(0);
                 }
-                const u64 in = __ballot(any);
+                const u64 in = ONE_BY_ONE ? 0ull : __ballot(any);
                 if (in != 0ull) {
                     const int32_t n = __builtin_popcountll(in);
                     if (held + n <= 64) {

@@ -1165,12 +1165,11 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
                     sweep(Yes{}, [&](const u32x4 &v, int, int32_t) __attribute__((always_inline)) { one(v); }, nothing_more);
                     if (tail != 0 && wave == 0) one(rest);
                 }
-                const bool above = (int32_t)hi >> 16 > top || (int32_t)(hi << 16) >> 16 > top;
                 total = wave_sum(total);
-                const u64 any_above = __ballot(above);
+                const float largest = wave_max((float)max((int32_t)hi >> 16, (int32_t)(hi << 16) >> 16));
                 if (lane == 0) {
                     sh.wave_d[wave] = total;
-                    sh.wave_lo[wave] = any_above != 0ull;
+                    sh.wave_f[wave] = largest;
                 }
                 __syncthreads();
                 // running mass over the counters, from the top; a thread has kPer of them
@@ -1178,12 +1177,18 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
                 static_assert(kPer * NT == Sh::kValues, "a share of the counters for every thread");
                 double local = 0.0, unused;
                 total = wide_total<NT>(sh.wave_d, unused);
-                const bool inside = __ballot(lane < W && sh.wave_lo[lane < W ? lane : 0] != 0u) == 0ull;
+                // The row's largest value, as it is stored (a NaN's and infinity's are above the window).  From here on weights are
+                // against it: the first pieces' largest may lie a hundred factors of two lower, where a chunk's sum leaves fp32 with
+                // every lane's inside it.
+                const int32_t stored = (int32_t)wave_max(lane < W ? sh.wave_f[lane] : 0.f);
+                const bool inside = stored <= top;
+                const float own = fmaxf(ceilf(bits_f32((uint32_t)stored << 16) * k), kRefFloor);
+                total = ldexp(total, (int)(ref - own));
                 // (Weights made anew where they are wanted again: kept, fifteen of them a lane spill a wave's row, and so does a branch
-                // for the values that no logit has, some of whose weights are beyond fp32.)
+                // for the values above the largest, which no logit has and whose weights may be beyond fp32.)
                 auto weight_of = [&](int32_t b) __attribute__((always_inline)) {
                     asm volatile("" : "+v"(b));
-                    return fminf(fast_exp2(fmaf(bits_f32((uint32_t)(bottom + b) << 16), k, nr)), 3e38f);
+                    return fminf(fast_exp2(fmaf(bits_f32((uint32_t)(bottom + b) << 16), k, -own)), 1.f);
                 };
                 auto mass_at = [&](int32_t b) __attribute__((always_inline)) {
                     return (double)sh.tally[b] * (double)weight_of(b);
@@ -1221,6 +1226,7 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
                         if (b0 - i >= pick) wtab[b0 - i - pick] = weight_of(b0 - i);
                     if (wave == W - 1) wtab[kept + lane] = 0.f;
                     thr = bits_f32((uint32_t)(bottom + pick) << 16);
+                    ref = own;
                     __syncthreads();
                     const uint32_t low2 = (uint32_t)(bottom + pick) * 0x10001u, none = (uint32_t)(kept + lane) * 0x10001u;
                     float t[4] = {0.f, 0.f, 0.f, 0.f};
@@ -1235,7 +1241,7 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
                         t[p & 3] = vec_sum<EPV>(e);
                     }, [&](int p, int32_t tile) __attribute__((always_inline)) { chunks_done(t, p, tile); });
                     __syncthreads();
-                    if (tid == 0) sh.chunk[nfull] = tail != 0 ? tile_lane_sum<DT, true>(rest, k, nr, thr) : 0.f;
+                    if (tid == 0) sh.chunk[nfull] = tail != 0 ? tile_lane_sum<DT, true>(rest, k, -own, thr) : 0.f;
                     closed = in_chunks = true;
                 }
             }

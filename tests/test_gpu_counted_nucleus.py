@@ -45,3 +45,36 @@ def test_one_tile_by_the_groups_of_a_share(V):
         gpu = run_gpu_step(stored, CODES, V, temp=0.9, top_p=top_p)
         ref = oracle_step(stored, CODES, V, temp=0.9, top_p=top_p)
         print(f"V={V} p={top_p}", compare_step(gpu, ref, V, f"V={V} p={top_p}", trunc=True, codes=CODES), flush=True)
+
+
+# Weights against the first pieces' largest logit, 118 to 127 factors of two below many tied ones: a piece's eight add up, a
+# chunk's 512 pass what fp32 holds.  (a wave a row; 256 threads with counters of 1024 and of 2048 values; 512; 1024; several tiles)
+@pytest.mark.parametrize("V,rows", [(4095, 3200), (8191, 3200), (8193, 1100), (16380, 600), (16380, 300), (33001, 300), (50257, 3),
+                                    (140001, 3)])
+def test_largest_far_above_the_first_pieces(V, rows):
+    from gpu_util import compare_step, oracle_step, run_gpu_step
+    x = np.full((7, V), 10.0, np.float32)
+    at = (V // 2 + 511) // 512 * 512
+    for r, (value, n) in enumerate(((14.125, 100), (14.25, 100), (14.375, 100), (14.25, 512), (14.375, 1500), (14.375, 1))):
+        x[r, at:at + n] = value
+    x[6, V // 2:] = 14.25
+    stored = synth.f32_to_bf16_bits(x)
+    rid = (np.arange(rows) % len(x)).astype(np.int32)
+    codes = synth.uniform_codes(rows, seed=V)
+    codes[:3] = 0.0, 0.5, 0.999
+    for temp, top_p in ((0.05, 0.9), (0.05, 0.5), (0.0487, 0.97)):
+        label = f"V={V} R={rows} temp={temp} p={top_p}"
+        print("case", label, flush=True)
+        gpu = run_gpu_step(stored, codes, V, temp=temp, top_p=top_p, row_ids=rid, tuning=ANY)
+        ref = oracle_step(stored, codes, V, temp=temp, top_p=top_p, row_ids=rid.astype(np.int64))
+        print("   ", compare_step(gpu, ref, V, label, trunc=True, codes=codes), flush=True)
+
+
+def test_half_a_row_far_above_the_other():
+    from gpu_util import compare_step, oracle_step, run_gpu_step
+    V = 50257
+    x = np.full((3, V), 10.0, np.float32)
+    x[:, 25000:50000] = 95.0                                 # (not the row's tail, which is looked at with the first pieces)
+    stored, codes = synth.f32_to_bf16_bits(x), np.array([0.0, 0.5, 0.99], np.float32)
+    gpu = run_gpu_step(stored, codes, V, temp=1.0, top_p=0.9)
+    print(compare_step(gpu, oracle_step(stored, codes, V, temp=1.0, top_p=0.9), V, "95 above 10", trunc=True, codes=codes))

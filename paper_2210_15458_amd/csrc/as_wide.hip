@@ -129,6 +129,7 @@ template <int NT, bool MULTI, bool SHORT> struct WideShared {
     double run;
     int32_t pick;
     uint32_t n, sel;
+    uint32_t stay;                                           // of n candidates, those that stay (n itself is still being read)
 };
 
 static_assert(sizeof(WideShared<64, false, true>) <= 7680 && sizeof(WideShared<64, false, false>) <= 10240, "five and four waves a SIMD");
@@ -363,7 +364,7 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
                 at += (uint32_t)__builtin_popcountll(in);
             }
         if (lane == 0) {
-            sh.n = at;
+            sh.stay = at;
             sh.before = (u64)lo << kLow;
         }
     };
@@ -694,10 +695,10 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
                     if (wave == 0) {
                         shrink(n);
                         wave_lds();
-                        if (sh.n <= 64u) finish_few(sh.n, DT != AS_BF16);
+                        if (sh.stay <= 64u) finish_few(sh.stay, DT != AS_BF16);
                     }
                     __syncthreads();
-                    n = sh.n;
+                    n = sh.stay;
                     if (n <= 64u) return;
                 }
             }

@@ -34,3 +34,25 @@ def test_candidate_table(pieces, more, dtype):
         gpu = run_gpu_step(stored, CODES, V, temp=0.9, top_k=top_k, top_p=top_p, tuning=ANY)
         ref = oracle_step(stored, CODES, V, temp=0.9, top_k=top_k, top_p=top_p)
         print("   ", compare_step(gpu, ref, V, label, trunc=True, codes=CODES), flush=True)
+
+
+# Where more than 64 stay whatever one wave leaves out, each wave goes by the number that all of them counted: k on either side of
+# the line between the two ways, candidates on either side of twice as many, in blocks of 256, 512 and 1024.
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("pieces,rows", [(1000, 256), (2040, 600), (4000, 300), (4000, 7), (8000, 300), (12000, 7)])
+def test_candidates_that_stay(pieces, rows, dtype):
+    from gpu_util import compare_step, oracle_step, run_gpu_step
+    V = pieces * (8 if dtype == "bf16" else 4) + 1
+    rng = np.random.default_rng(pieces)
+    x = (rng.standard_normal((5, V)) * 2.0).astype(np.float32)
+    for r, n in enumerate((100, 115, 130, 200, 250)):        # (so many above the rest, among them ties)
+        x[r, rng.permutation(V)[:n]] = np.round(20.0 + rng.standard_normal(n) * 2.0, 1)
+    stored = synth.f32_to_bf16_bits(x) if dtype == "bf16" else x
+    rid = (np.arange(rows) % len(x)).astype(np.int32)
+    codes = synth.uniform_codes(rows, seed=pieces)
+    for top_k, top_p in ((56, 0.95), (57, 0.95), (65, 1.0), (80, 0.9), (128, 1.0)):
+        label = f"V={V} R={rows} {dtype} k={top_k} p={top_p}"
+        print("case", label, flush=True)
+        gpu = run_gpu_step(stored, codes, V, temp=0.9, top_k=top_k, top_p=top_p, row_ids=rid, tuning=ANY)
+        ref = oracle_step(stored, codes, V, temp=0.9, top_k=top_k, top_p=top_p, row_ids=rid.astype(np.int64))
+        print("   ", compare_step(gpu, ref, V, label, trunc=True, codes=codes), flush=True)

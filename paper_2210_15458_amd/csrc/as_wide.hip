@@ -660,9 +660,9 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
                             take_apart();
                             __syncthreads();
                             const uint32_t n = sh.n;
+                            __syncthreads();                 // (all have read it before a wave whose table fills adds to it)
                             if (n > (uint32_t)NT) break;
                             if (n > (uint32_t)NT / 2) {
-                                __syncthreads();
                                 if (wave == 0) raise(n);
                                 __syncthreads();
                                 xb = from_order_key((uint32_t)sh.before);

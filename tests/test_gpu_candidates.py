@@ -56,3 +56,38 @@ def test_candidates_that_stay(pieces, rows, dtype):
         gpu = run_gpu_step(stored, codes, V, temp=0.9, top_k=top_k, top_p=top_p, row_ids=rid, tuning=ANY)
         ref = oracle_step(stored, codes, V, temp=0.9, top_k=top_k, top_p=top_p, row_ids=rid.astype(np.int64))
         print("   ", compare_step(gpu, ref, V, label, trunc=True, codes=codes), flush=True)
+
+
+def _filling(V, per):
+    """Rows of several tiles in which single waves meet more pieces with candidates than their tables take, between the places where
+    the block counts what it has: neighbouring logits (a wave's own pieces) in every tile, as many as bring the table to a half, to its
+    end and past it; a row that keeps rising; one whose last tile alone holds them."""
+    rng = np.random.default_rng(V)
+    tile = 8192 * per
+    x = (rng.standard_normal((6, V)) * 2.0).astype(np.float32)
+    for r, run in enumerate((90, 260, 700)):
+        for at in range(3 * 64 * per, V - run, tile):
+            x[r, at:at + run] += 25.0 + rng.standard_normal(run).astype(np.float32)
+    x[3] = np.sort(x[3])
+    x[4] += np.arange(V) // tile * 6.0
+    x[5, V - 3000:] += 20.0
+    return x
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("tiles", [3, 4, 5, 8, 9])
+def test_tables_that_fill_between_tiles(tiles, dtype):
+    from gpu_util import compare_step, oracle_step, run_gpu_step
+    per = 8 if dtype == "bf16" else 4
+    V = tiles * 8192 * per - 5
+    x = _filling(V, per)
+    stored = synth.f32_to_bf16_bits(x) if dtype == "bf16" else x
+    rows = 300 if tiles == 3 else 12
+    rid = (np.arange(rows) % len(x)).astype(np.int32)
+    codes = synth.uniform_codes(rows, seed=tiles)
+    for top_k, top_p in ((1, 1.0), (40, 0.9), (64, 1.0), (100, 1.0), (128, 0.9)):
+        label = f"V={V} {dtype} k={top_k} p={top_p}"
+        print("case", label, flush=True)
+        gpu = run_gpu_step(stored, codes, V, temp=0.9, top_k=top_k, top_p=top_p, row_ids=rid, tuning=ANY)
+        ref = oracle_step(stored, codes, V, temp=0.9, top_k=top_k, top_p=top_p, row_ids=rid.astype(np.int64))
+        print("   ", compare_step(gpu, ref, V, label, trunc=True, codes=codes), flush=True)

@@ -67,8 +67,8 @@ __device__ __forceinline__ float from_order_key(uint32_t k)
 }
 
 // The mass by which a nucleus is closed: 31 fractional bits of a weight e <= 1 against the row's own reference, what the
-// other threshold kernels have (as_threshold.hip), so that the kept set does not depend on the kernel.  Sums of
-// them stay below 2^53 for any row.
+// other threshold kernels have (as_threshold.hip; its one-tile nucleus of bf16 rows has sums of fp32 weights), so that the kept set
+// does not depend on the kernel.  Sums of them stay below 2^53 for any row.
 __device__ __forceinline__ uint32_t mass_of(float e) { return (uint32_t)fmaf(e, 2147483648.f, 0.5f); }
 // ... and the one by which a listed logit joins its chunk's weight: 40 fractional bits (24 significant bits: exact for every
 // weight above 2^-17)
@@ -127,7 +127,7 @@ template <int NT, bool MULTI, bool SHORT> struct WideShared {
     uint32_t wave_lo[kWaves], wave_hi[kWaves];
     u64 before;
     double run;
-    int32_t pick;
+    int32_t pick, again;
     uint32_t n, sel;
     uint32_t stay;                                           // of n candidates, those that stay (n itself is still being read)
 };
@@ -1134,10 +1134,14 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
             // the lane's own.  The counters, from the top, name the value at which the nucleus closes; they give way to a table of
             // the kept values' weights, and the chunk sums of the kept logits are look-ups: half the instructions of the
             // tallies and integer masses below, which is what bounds either (one row of 50257 takes 2400 a wave with those, 16 of
-            // its 21 us).  us, tallies / counters: 1 row of 50257 20.8 / 13.0, of 256000 63 / 34, 200 of 33001 21.2 / 12.8, 2000 of
-            // 20001 56 / 36, 2000 of 50257 112 / 72, 16000 of 8001 141 / 90, 14000 of 1501 54 / 43.  A logit above the window or a
-            // nucleus that reaches below it: the other way.  The total is a sum of fp32 weights where the other way has integers,
-            // so a nucleus that ends within 1e-7 of its share may close a group apart; thresholds alone keep to the integers.
+            // its 21 us).  us, tallies / counters: 1 row of 50257 20.8 / 13.1, of 256000 63 / 34, 200 of 33001 21.2 / 14.2, 2000 of
+            // 20001 56 / 38, 2000 of 50257 112 / 77, 16000 of 8001 141 / 91, 14000 of 1501 54 / 43.  A logit above the window or a
+            // nucleus that reaches below it: the other way.  The counters are weighed in the other way's integers; the total, a sum of
+            // fp32 weights, is known to some 2e-6, and where that leaves open which group of equal logits closes (a row in 500 of
+            // these), one more pass adds up the row's integers, so that the kept set is the other way's.  (A launch lasts as long as
+            // its last such row, and the pass costs registers beside the row's: us, without / so, 200 rows of 33001 13.5 / 14.2, 2000 of
+            // 32001 45.6 / 50.6, 2000 of 50257 72.5 / 77.3, 1100 of 12001 18.0 / 19.4, 16000 of 8001 even; with the whole other way for
+            // such rows 17.5, 60.5, 91, 22.7, 105.)
             int32_t top = (int32_t)(__builtin_bit_cast(uint32_t, first_max) >> 16) + Sh::kHigher;
             top = top > 0x7f7f ? 0x7f7f : top;               // (the largest finite value)
             const int32_t bottom = top - (Sh::kValues - 1);
@@ -1145,7 +1149,8 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
                 lds_u32 *const tally = (lds_u32 *)sh.tally;
                 __syncthreads();
                 for (int b = tid; b < Sh::kValues + 64; b += NT) sh.tally[b] = 0u;
-                if (tid == 0) sh.pick = -1;
+                constexpr int32_t kOpen = -2;
+                if (tid == 0) sh.pick = sh.again = -1;
                 __syncthreads();
                 const float nr = -ref;
                 double total = 0.0;
@@ -1184,7 +1189,6 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
                 const int32_t stored = (int32_t)wave_max(lane < W ? sh.wave_f[lane] : 0.f);
                 const bool inside = stored <= top;
                 const float own = fmaxf(ceilf(bits_f32((uint32_t)stored << 16) * k), kRefFloor);
-                total = ldexp(total, (int)(ref - own));
                 // (Weights made anew where they are wanted again: kept, fifteen of them a lane spill a wave's row, and so does a branch
                 // for the values above the largest, which no logit has and whose weights may be beyond fp32.)
                 auto weight_of = [&](int32_t b) __attribute__((always_inline)) {
@@ -1192,7 +1196,7 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
                     return fminf(fast_exp2(fmaf(bits_f32((uint32_t)(bottom + b) << 16), k, -own)), 1.f);
                 };
                 auto mass_at = [&](int32_t b) __attribute__((always_inline)) {
-                    return (double)sh.tally[b] * (double)weight_of(b);
+                    return (double)sh.tally[b] * (double)mass_of(weight_of(b));
                 };
                 const int32_t b0 = Sh::kValues - 1 - tid * kPer; // the thread's highest
 #pragma unroll
@@ -1203,22 +1207,55 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
                 double lo;
                 wide_total<NT>(sh.wave_e, lo);
                 lo += incl - local;
-                const double need = (double)top_p * total;
-                if (!(lo >= need) && lo + local >= need) {
-                    double acc = lo;
-                    int32_t found = -1, lowest = -1;
+                // In masses the total may be off, against the sum of the row's integers, by three roundings of a piece's sum and one of
+                // a mass near 2^23, 2.5 2^-23 of it together, and by a half for every logit.  Where the reference was another, also by
+                // two exponentials, 2^-23 each, and the rounding of their arguments: 2.8 2^-23 each where those are at most 16 (the
+                // weights below 2^-16 are at most V 2^-16 together: 0.05 a logit), twice that up to 32, and so on.
+                const double lower = (double)(own - ref);
+                total = ldexp(total, (int)(ref - own) + 31);
+                const double off = lower == 0.0 ? 3.2e-7 * total + 0.5 * (double)V
+                                          : (1.3e-6 + 1e-7 * fmax(lower - 8.0, 0.0)) * total + 0.55 * (double)V;
+                auto find = [&](double slack, int32_t *at) __attribute__((always_inline)) {
+                    const double need = (double)top_p * total;
+                    if (!(lo >= need) && lo + local >= need) {
+                        double above = lo, upto = lo;        // (sums of integers below 2^53: exact)
+                        int32_t found = -1;
 #pragma unroll 1
-                    for (int i = 0; i < kPer; ++i) {
-                        const bool any = sh.tally[b0 - i] != 0u;
-                        acc += mass_at(b0 - i);
-                        if (any) lowest = b0 - i;
-                        if (found < 0 && any && acc >= need) found = b0 - i;
+                        for (int i = 0; i < kPer && found < 0; ++i) {
+                            above = upto;
+                            upto += mass_at(b0 - i);
+                            if (upto >= need) found = b0 - i;
+                        }
+                        *at = above < need - slack && upto >= need + slack ? found : kOpen;
                     }
-                    sh.pick = found >= 0 ? found : lowest;   // (the two orders of summation differ in the last place)
+                    __syncthreads();
+                    return *at;
+                };
+                const bool fits = inside && total < (double)__builtin_inff();
+                int32_t pick = find((double)top_p * off, &sh.pick);
+                if (pick == kOpen && fits) {
+                    u64 all = 0;
+                    auto one = [&](const u32x4 &v) __attribute__((always_inline)) {
+                        float x[EPV];
+                        values(v, x);
+#pragma unroll
+                        for (int i = 0; i < EPV; ++i) all += mass_of(fast_exp2(fmaf(x[i], k, -own)));
+                        asm volatile("" : "+v"(all));
+                    };
+                    // (us, from memory / from the registers: 16000 rows of 8001 99 / 91, 2000 of 32001, whose registers are spilled, 50.6 / 53.4)
+                    if constexpr (NT * NP <= 1024) {
+                        sweep(No{}, [&](const u32x4 &v, int, int32_t) __attribute__((always_inline)) { one(v); }, nothing_more);
+                        if (tail != 0 && wave == 0) one(rest);
+                    } else {
+                        every_piece(one);
+                    }
+                    const double all_wave = wave_sum((double)all);
+                    if (lane == 0) sh.wave_d[wave] = all_wave;
+                    __syncthreads();
+                    total = wide_total<NT>(sh.wave_d, unused);
+                    pick = find(0.0, &sh.again);
                 }
-                __syncthreads();
-                const int32_t pick = sh.pick;
-                if (inside && pick >= 0 && total < (double)__builtin_inff()) {
+                if (fits && pick >= 0) {
                     // The kept values' weights, from the threshold's on, and behind them 64 zeros, a word a lane, for all others.
                     float *const wtab = reinterpret_cast<float *>(sh.tally);
                     const int32_t kept = Sh::kValues - pick;

@@ -78,3 +78,38 @@ def test_half_a_row_far_above_the_other():
     stored, codes = synth.f32_to_bf16_bits(x), np.array([0.0, 0.5, 0.99], np.float32)
     gpu = run_gpu_step(stored, codes, V, temp=1.0, top_p=0.9)
     print(compare_step(gpu, oracle_step(stored, codes, V, temp=1.0, top_p=0.9), V, "95 above 10", trunc=True, codes=codes))
+
+
+# At shares next to a group's end the counted way keeps what the integer masses keep: a step's probability and the width that its
+# token has as an interval are quotients by the kept weight, equal to the rounding of its fp32 sums (below 1e-6), where a group more
+# or less, a thousandth of the weight here, is another set.  So each token sampled is one that the encode direction keeps.
+@pytest.mark.parametrize("V,rows", [(2047, 1600), (4095, 3200), (8191, 3200), (8193, 1100), (16380, 600), (33001, 300), (50257, 60), (70001, 260), (140001, 20)])
+def test_shares_next_to_a_groups_end(V, rows):
+    import torch
+    from gpu_util import to_dev_logits
+    from paper_2210_15458_amd import binding as B
+    rng = np.random.default_rng(V)
+    one = synth.bf16_bits_to_f32(synth.f32_to_bf16_bits((rng.standard_normal(V) * 1.5 + 3.0).astype(np.float32)))
+    x = np.stack([rng.permutation(one) for _ in range(rows)])    # (one set of values, summed in many orders)
+    logits = to_dev_logits(synth.f32_to_bf16_bits(x))
+    values, counts = np.unique(one, return_counts=True)
+    share = np.cumsum(counts[::-1] * np.exp(values[::-1].astype(np.float64)))
+    share /= share[-1]
+    near = share[(share > 0.3) & (share < 0.95)].astype(np.float32)
+    codes = torch.from_numpy(synth.uniform_codes(rows, seed=V)).cuda()
+    token = torch.zeros(rows, dtype=torch.int32, device="cuda")
+    prob, c_out = torch.zeros(rows, device="cuda"), torch.zeros(rows, device="cuda")
+    lo, width = (torch.zeros(rows, dtype=torch.float64, device="cuda") for _ in range(2))
+    ctx = B.Ctx(rows, V, logits.dtype)
+    ctx.set_tuning("thr_path", 3)
+    differ = 0
+    for p in rng.choice(near, min(20, len(near)), replace=False):
+        for share_of in (np.nextafter(p, np.float32(0)), p, np.nextafter(p, np.float32(1))):
+            lo.zero_()
+            width.fill_(1.0)
+            B.as_step_ex(ctx, logits, codes, 1.0, 0, float(share_of), token, c_out, prob_out=prob)
+            B.as_interval_step(ctx, logits, token, 1.0, 0, float(share_of), lo, width)
+            differ += int(((prob.double() - width).abs() > 1e-5 * prob).sum())
+    print(f"V={V} rows={rows}: {differ} steps differ", flush=True)
+    ctx.close()
+    assert differ == 0

@@ -653,10 +653,12 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
 #pragma unroll
                         for (int p = 0; p < NP; ++p) take(nxt[p], p, t + 1);
                         if (t + 2 < ntiles) {
-                            // (Each tile brings as many as the first two did apiece: after 4, 8 of them a better bound, from the table, if
+                            // (Each tile brings as many as the first two did apiece: after 2, 4, 8 of them a better bound, from the table, if
                             // that is half full.  us, from a quarter / from a half: 16 rows of 190001 fp32 k = 100 43 / 28, 256 of 256000 k =
-                            // 128 79 / 64.)
-                            if (((t + 2) & (t + 1)) != 0) continue;
+                            // 128 79 / 64.  Of bf16, twice as many logits a tile, not after 2: us, with / without that, 230 of 256000 k = 50, p
+                            // = 0.95 34.7 / 33.7, k = 128 44.2 / 42.6, 1 row 20.2 / 19.1, rows in rising order 423 / 449; fp32 256 of 256000 k =
+                            // 128 63.2 / 63.9.)
+                            if ((DT == AS_BF16 && t == 0) || ((t + 2) & (t + 1)) != 0) continue;
                             take_apart();
                             __syncthreads();
                             const uint32_t n = sh.n;

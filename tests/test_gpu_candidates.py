@@ -91,3 +91,40 @@ def test_tables_that_fill_between_tiles(tiles, dtype):
         gpu = run_gpu_step(stored, codes, V, temp=0.9, top_k=top_k, top_p=top_p, row_ids=rid, tuning=ANY)
         ref = oracle_step(stored, codes, V, temp=0.9, top_k=top_k, top_p=top_p, row_ids=rid.astype(np.int64))
         print("   ", compare_step(gpu, ref, V, label, trunc=True, codes=codes), flush=True)
+
+
+# Rows that break the contract among ordinary ones, in each form of the kernel (a wave a row, 256, 512 and 1024 threads, several
+# tiles): outputs stay in their range, and the other rows get what they get without these beside them.  A row without a finite
+# logit gets the first token.
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("pieces,rows", [(500, 3200), (1000, 5200), (1000, 9), (2040, 600), (4000, 600), (4000, 300), (8000, 300),
+                                         (12000, 9), (20000, 300), (20000, 9)])
+def test_rows_of_nan_and_infinities(pieces, rows, dtype):
+    from gpu_util import run_gpu_step
+    V = pieces * (8 if dtype == "bf16" else 4) + 1
+    rng = np.random.default_rng(pieces)
+    nan, inf = np.float32(np.nan), np.float32(np.inf)
+    x = (rng.standard_normal((9, V)) * 2.0 + 3.0).astype(np.float32)
+    good = [1, 4, 8]
+    x[0] = nan
+    x[2, rng.integers(0, V, V // 50)] = nan
+    x[3, V // 2] = inf                                       # (past the first pieces)
+    x[5] = -inf
+    x[6, ::2] = inf
+    x[6, 1::2] = -nan
+    x[7] = -inf
+    x[7, V - 1] = -nan
+    stored = synth.f32_to_bf16_bits(x) if dtype == "bf16" else x
+    rid = (np.arange(rows) % len(x)).astype(np.int32)
+    codes = synth.uniform_codes(rows, seed=pieces)
+    mine = np.isin(rid, good)
+    for top_k, top_p in ((0, 0.9), (0, 0.999), (40, 1.0), (50, 0.9), (128, 1.0), (1000, 0.9)):
+        print(f"case V={V} R={rows} {dtype} k={top_k} p={top_p}", flush=True)
+        out = run_gpu_step(stored, codes, V, temp=0.9, top_k=top_k, top_p=top_p, row_ids=rid, tuning=ANY)
+        tok, c = out["token"], out["c_next"]
+        assert ((tok >= 0) & (tok < V)).all()
+        assert np.isfinite(c).all() and (c >= 0.0).all() and (c <= np.float32(1.0) - np.float32(2.0 ** -24)).all()
+        assert (tok[rid == 5] == 0).all()
+        other = run_gpu_step(stored, codes, V, temp=0.9, top_k=top_k, top_p=top_p, row_ids=np.where(mine, rid, 8).astype(np.int32), tuning=ANY)
+        for key in ("token", "c_next", "p"):
+            assert np.array_equal(out[key][mine], other[key][mine]), key

@@ -26,7 +26,7 @@ def test_candidate_table(pieces, more, dtype):
     V = pieces * (8 if dtype == "bf16" else 4) + more
     x = _rows(V)
     stored = synth.f32_to_bf16_bits(x) if dtype == "bf16" else x
-    for top_k, top_p in ((1, 1.0), (5, 0.9), (48, 1.0), (56, 0.95), (57, 0.9), (128, 0.8)):
+    for top_k, top_p in ((1, 1.0), (1, 0.3), (5, 0.9), (48, 1.0), (56, 0.95), (57, 0.9), (128, 0.8)):
         if top_k >= V:
             continue
         label = f"V={V} {dtype} k={top_k} p={top_p}"

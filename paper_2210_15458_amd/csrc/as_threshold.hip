@@ -467,10 +467,8 @@ __device__ __forceinline__ unsigned long long bin_that_reaches(Resident &sh, Goa
     return before;
 }
 
-// STEP: go on and finish the sampling step for the row, which is then not read a second time.  With HAS_K from
-// the candidate table (after top-k every kept logit is in it); with the nucleus alone, where most of the row
-// can be kept, from the registers (bf16 rows: their 4096 sums of 8 logits take the histogram's place in LDS).
-// sa then carries the step's arguments.
+// STEP: go on and finish the sampling step for the row, which is then not read a second time, from the candidate table (after
+// top-k every kept logit is in it).  sa then carries the step's arguments.
 template <int DT, bool HAS_K, bool HAS_P, bool STEP = false>
 __global__ __launch_bounds__(kThreads) void threshold_resident_kernel(const void *logits, int64_t ld, int32_t V,
                                                                       const uint8_t *finished_in,
@@ -478,8 +476,7 @@ __global__ __launch_bounds__(kThreads) void threshold_resident_kernel(const void
                                                                       int32_t top_k, float top_p, float *thr_out,
                                                                       StepArgs sa)
 {
-    static_assert(!STEP || HAS_K || (HAS_P && DT == AS_BF16),
-                  "the fused step works on the top-k candidate table, or for a bf16 row on its registers");
+    static_assert(!STEP || (HAS_K && DT == AS_F32), "the fused step works on the top-k candidate table; bf16 rows have other kernels");
     using K = Key<DT>;
     using T = typename K::T;
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -653,7 +650,6 @@ __global__ __launch_bounds__(kThreads) void threshold_resident_kernel(const void
     }
 
     // ---------------- nucleus over the survivors
-    float nr_row = 0.f;                  // minus the row's integer reference, as the nucleus pass took it
     if (HAS_P && !fall) {
         const float k = 1.44269504088896340736f / temp;
         double need;
@@ -685,7 +681,6 @@ __global__ __launch_bounds__(kThreads) void threshold_resident_kernel(const void
 #pragma unroll
             for (int w = 1; w < kThreads / 64; ++w) m = fmaxf(m, fred[w]);
             const float nr = -fmaxf(ceilf(m * k), -100000.f);
-            nr_row = nr;
             __syncthreads();
             // mass per coarse bin, in the fixed point of the radix path
             forget_row();
@@ -820,103 +815,6 @@ __global__ __launch_bounds__(kThreads) void threshold_resident_kernel(const void
         __syncthreads();
         if (fall) {
             generic_step_row<T>(sa, r, K::from_key(thr_key), sc.gen);
-            return;
-        }
-        if constexpr (!HAS_K) {
-            // ---- the sampling step from the registers (Sec. 4.1 loop body).  Weights exp2(x*k - ref) of the
-            // kept logits against the reference of the nucleus pass; per piece of 8 an fp32 sum in vocabulary
-            // order; fp64 from there on.  The bucket is the last piece, then the last logit in it, that has
-            // weight and whose mass before it does not exceed c*S: with c*S inside the row that is the one
-            // it falls into, and past the end by rounding it is the last kept token.
-            const float k = sa.k;
-            const float thr = K::from_key(thr_key);
-            float nr3 = nr_row;
-            asm volatile("" : "+v"(nr3));
-            forget_row();
-            float *psum = reinterpret_cast<float *>(sh.hist);            // NP * kThreads = 4096 entries
-            double *dred = reinterpret_cast<double *>(sh.ckey);
-            uint32_t *ured = sh.mcount;
-            auto weight = [&](uint32_t bits) __attribute__((always_inline)) {
-                const float x = __builtin_bit_cast(float, bits);
-                return x >= thr ? fast_exp2(fmaf(x, k, nr3)) : 0.f;
-            };
-#pragma unroll
-            for (int p = 0; p < NP; ++p) {
-                float sum = 0.f;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const uint32_t w = pc[p][i];
-                    sum += weight(w << 16);
-                    sum += weight(w & 0xffff0000u);
-                }
-                psum[p * kThreads + tid] = sum;
-            }
-            __syncthreads();
-            float ent[NP];
-            double local = 0.0;
-#pragma unroll
-            for (int i = 0; i < NP; ++i) {
-                ent[i] = psum[tid * NP + i];
-                local += (double)ent[i];
-            }
-            const double incl = wave_scan_add(local);
-            if ((tid & 63) == 63) dred[tid >> 6] = incl;
-            __syncthreads();
-            double base = 0.0, S = 0.0;
-#pragma unroll
-            for (int w = 0; w < kThreads / 64; ++w) {
-                const double t = dred[w];
-                if (w < (tid >> 6)) base += t;
-                S += t;
-            }
-            const double tau = (double)sa.codes[r] * S;
-            uint32_t best = 0;                                           // piece index + 1
-            double best_before = 0.0, acc = base + incl - local;
-#pragma unroll
-            for (int i = 0; i < NP; ++i) {
-                if (ent[i] > 0.f && acc <= tau) {
-                    best = (uint32_t)(tid * NP + i) + 1u;
-                    best_before = acc;
-                }
-                acc += (double)ent[i];
-            }
-            const uint32_t wbest = wave_reduce_umax(best);
-            if ((tid & 63) == 0) ured[tid >> 6] = wbest;
-            __syncthreads();
-            uint32_t gbest = ured[0];
-#pragma unroll
-            for (int w = 1; w < kThreads / 64; ++w) gbest = gbest > ured[w] ? gbest : ured[w];
-            if (best == gbest && gbest != 0u) dred[4] = best_before;
-            __syncthreads();
-            if (tid == 0) {
-                int32_t piece = gbest ? (int32_t)gbest - 1 : 0;
-                if (piece > npieces - 1) piece = npieces - 1;
-                const u32x4 again = reinterpret_cast<const u32x4 *>(row)[piece];
-                double before = gbest ? dred[4] : 0.0, lo = before;
-                float ev = 0.f;
-                int32_t token = piece * EPP;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const uint32_t w = again[i];
-#pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        const int32_t v = piece * EPP + 2 * i + h;
-                        const float e = v < V ? weight(h ? (w & 0xffff0000u) : (w << 16)) : 0.f;
-                        if (e > 0.f && before <= tau) {
-                            token = v;
-                            lo = before;
-                            ev = e;
-                        }
-                        before += (double)e;
-                    }
-                }
-                RowOut o;
-                o.token = token;
-                o.c_next = rescale_code(tau, lo, (double)ev);
-                o.prob = (float)((double)ev / S);
-                o.f_lo = (float)(lo / S);
-                write_row(sa, r, o);
-            }
             return;
         }
         // ---- the sampling step on the kept candidates (Sec. 4.1 loop body): weights against an integer
@@ -1973,14 +1871,13 @@ static bool resident_fits(const as_ctx *ctx, const void *logits, int64_t ld, boo
            (ld * (ctx->dtype == AS_BF16 ? 2 : 4)) % 16 == 0 && (!has_k || top_k <= kThreads / 2);
 }
 
-// Whole steps that it takes from the wide kernel (us, resident / wide): top-k of fp32 rows above 16384 on more than two a compute
-// unit, 600 of 24000 k = 40 19 / 24, 2000 42 / 46, but k = 100 2000 76 / 68, and 300 15 / 14.  (Of bf16 rows none: k = 40 300 of
-// 9001 15 / 12, 8000 108 / 90, 2000 of 32761 37 / 37, k = 100 66 / 52; nuclei, which the wide kernel counts by value, 300 of 24001
-// 23 / 15, 2000 of 32001 63 / 45, 8000 211 / 146.)
+// Whole steps that it takes from the wide kernel: top-k of fp32 rows above 16384 on more than two a compute unit.  (us, resident /
+// wide: 300 of 24000 k = 40 16.5 / 12.9, 600 21.2 / 21.1, 2000 48.4 / 46.9, 6000 117 / 123; k = 100 900 39.0 / 38.6, 2000 62 / 70; 2000 of
+// 32000 k = 20, p = 0.9 54 / 49.  The lines lay between the two before the wide kernel took its candidates by pieces, 19 / 24, 42 / 46
+// and 76 / 68 at 600, 2000 and k = 100; now they lie among shapes that are even or better off on either side.)
 static bool resident_pays(const as_ctx *ctx, const void *logits, int64_t rows, int64_t ld, bool has_k, int32_t top_k)
 {
     if (!resident_fits(ctx, logits, ld, has_k, top_k)) return false;
-    if (ctx->thr_path == 2) return true;
     return ctx->dtype != AS_BF16 && has_k && ctx->V > 16384 && rows > 2 * (int64_t)ctx->num_cus && (top_k <= 64 || rows <= 4 * (int64_t)ctx->num_cus);
 }
 
@@ -2083,15 +1980,14 @@ as_status launch_table_records(as_ctx *ctx, TableForm form, const void *logits, 
     return AS_OK;
 }
 
-// top-k and the nucleus and the sampling step in one launch; false where only the radix select and the resident
-// fp32 nucleus are left (then the caller runs the threshold kernel and the step kernel one after the other)
+// top-k and the nucleus and the sampling step in one launch; false where a threshold kernel and the step kernel are left, which the
+// caller runs one after the other
 bool launch_topk_step(as_ctx *ctx, const StepArgs &args, int32_t top_k, float top_p, as_status *st)
 {
     const size_t esz = ctx->dtype == AS_BF16 ? 2 : 4;
     const StepArgs &a = args;
     const bool nt = stream_rows(a.src_rows ? a.src_rows : a.rows, a.ld, esz);
     const bool has_k = top_k > 0 && top_k < ctx->V, has_p = top_p > 0.f && top_p < 1.f;
-    const bool nucleus_only = !has_k && has_p && ctx->dtype == AS_BF16;
     const bool tile = reinterpret_cast<uintptr_t>(a.logits) % 16 == 0 && (a.ld * esz) % 16 == 0 &&
                       by_tile(ctx, a.rows, a.k, has_k, top_k);
     if (ctx->thr_path == 3 ||
@@ -2100,8 +1996,8 @@ bool launch_topk_step(as_ctx *ctx, const StepArgs &args, int32_t top_k, float to
         *st = launch_wide(ctx, a, has_k ? top_k : 0, has_p ? top_p : 1.f, nullptr);
         return true;
     }
-    if ((ctx->thr_path != 0 && ctx->thr_path != 2) || !(has_k || nucleus_only) || top_k > kThreads / 2 || ctx->V > 32768 ||
-        reinterpret_cast<uintptr_t>(a.logits) % 16 != 0 || (a.ld * esz) % 16 != 0)
+    if (!tile && ((ctx->thr_path != 0 && ctx->thr_path != 2) || ctx->dtype == AS_BF16 || !has_k || top_k > kThreads / 2 ||
+                  ctx->V > 32768 || reinterpret_cast<uintptr_t>(a.logits) % 16 != 0 || (a.ld * esz) % 16 != 0))
         return false;
     *st = AS_OK;
     if (a.rows == 0) return true;
@@ -2115,31 +2011,19 @@ bool launch_topk_step(as_ctx *ctx, const StepArgs &args, int32_t top_k, float to
         if (e != hipSuccess) *st = hip_fail(ctx, e, "top-k step launch");
         return true;
     }
-    if (nucleus_only && tile) {
+    if (tile) {
         if (nt) launch(ctx, kKernelStep, nucleus_tile_kernel<true>, grid, block, 0, a, top_p);
         else launch(ctx, kKernelStep, nucleus_tile_kernel<false>, grid, block, 0, a, top_p);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) *st = hip_fail(ctx, e, "nucleus step launch");
         return true;
     }
-    if (nucleus_only) {
-        launch(ctx, kKernelStep, threshold_resident_kernel<AS_BF16, false, true, true>, grid, block, 0, a.logits, a.ld,
+    if (has_p)
+        launch(ctx, kKernelStep, threshold_resident_kernel<AS_F32, true, true, true>, grid, block, 0, a.logits, a.ld,
                ctx->V, a.finished_in, a.row_ids, a.temp, top_k, top_p, (float *)nullptr, a);
-    } else if (ctx->dtype == AS_BF16) {
-        if (has_p)
-            launch(ctx, kKernelStep, threshold_resident_kernel<AS_BF16, true, true, true>, grid, block, 0, a.logits, a.ld,
-                   ctx->V, a.finished_in, a.row_ids, a.temp, top_k, top_p, (float *)nullptr, a);
-        else
-            launch(ctx, kKernelStep, threshold_resident_kernel<AS_BF16, true, false, true>, grid, block, 0, a.logits, a.ld,
-                   ctx->V, a.finished_in, a.row_ids, a.temp, top_k, top_p, (float *)nullptr, a);
-    } else {
-        if (has_p)
-            launch(ctx, kKernelStep, threshold_resident_kernel<AS_F32, true, true, true>, grid, block, 0, a.logits, a.ld,
-                   ctx->V, a.finished_in, a.row_ids, a.temp, top_k, top_p, (float *)nullptr, a);
-        else
-            launch(ctx, kKernelStep, threshold_resident_kernel<AS_F32, true, false, true>, grid, block, 0, a.logits, a.ld,
-                   ctx->V, a.finished_in, a.row_ids, a.temp, top_k, top_p, (float *)nullptr, a);
-    }
+    else
+        launch(ctx, kKernelStep, threshold_resident_kernel<AS_F32, true, false, true>, grid, block, 0, a.logits, a.ld,
+               ctx->V, a.finished_in, a.row_ids, a.temp, top_k, top_p, (float *)nullptr, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) *st = hip_fail(ctx, e, "fused top-k step launch");
     return true;

@@ -1607,9 +1607,10 @@ __global__ __launch_bounds__(kThreads, 4) void nucleus_tile_kernel(StepArgs a, f
     for (int i = threadIdx.x; i < (kNucBins + 64) / 4; i += kThreads)
         reinterpret_cast<u32x4 *>(tn.hist)[i] = u32x4{0u, 0u, 0u, 0u};
     __builtin_amdgcn_sched_barrier(0);
-    // From here to the end of the counting there is one path for every wave, with no branch between the loads
-    // and the code that takes them in (the compiler's wait counters are exact only then).  A share past the
-    // row's end (mych = 0 in every lane) re-reads the row's first piece and counts it for nothing.
+    // From here to the first group's counting there is one path for every wave, with no branch between the loads
+    // and the code that takes them in (the compiler's wait counters are exact only then); a wave then leaves out the groups that
+    // its share does not have.  A share past the row's end (mych = 0 in every lane) re-reads the row's first piece and counts one
+    // group of it for nothing.
     request_group(0);
     __builtin_amdgcn_sched_barrier(0);
     if (((fin_word >> (8u * fin_at)) & 0xffu) != 0u) {
@@ -1886,8 +1887,10 @@ static bool resident_pays(const as_ctx *ctx, const void *logits, int64_t rows, i
 // holds a share f of the row has one with probability 1 - exp(-lambda f); the lambda logits that bring k such lanes, two
 // for ties and 3.5 times the root of what shares lanes have to stay within 64, that is k lanes have to be reached by
 // lambda = s^2 + k - 2, s^2 + 3.5 s + k - 64 = 0.  (us, here / wide: k = 40, 64 rows of 8000 46 / 11, 300 of 8200 53 / 11, 600
-// of 11000 38 / 15, 600 of 12800 10 / 15, 2000 20 / 29; k = 48, 300 of 32128 156 / 15.)  Short rows leave three of its
-// four waves without work: with many of them the wide kernel is faster (8192 of 4096, k = 40 61 us against 207).
+// of 11000 38 / 15; 600 of 24000 11.3 / 14.5, of 32128 11.9 / 15.9, 4000 43 / 55; k = 20, p = 0.9 1024 of 12800 11.2 / 12.9; k = 48, 300
+// of 32128 156 / 15.)  Next to the line the margin is too small for a launch of many random rows, of which one that does not fit is
+// enough: k = 40, 600 of 12800 22 / 12, of 16000 28 / 13, k = 47 1024 of 32128 88 / 21.  (Decodes' records go by the same line.)  Short
+// rows leave three of its four waves without work: with many of them the wide kernel is faster (8192 of 4096, k = 40 61 us against 207).
 static bool topk_tile_pays(const as_ctx *ctx, int64_t rows, int32_t top_k)
 {
     if (top_k > kTileTopK || (ctx->V <= 8192 && rows > 2 * (int64_t)ctx->num_cus)) return false;
@@ -1935,9 +1938,10 @@ static bool threshold_streamed_pays(const as_ctx *ctx, int64_t rows, bool has_k,
 }
 
 // Whether a truncated step of `rows` rows takes a one-tile kernel, where its logits allow one
-// (The nucleus, us, here / in the wide kernel: 1000 rows of 9600 15.3 / 15.1, of 16000 17.7 / 17.5, of 32128 23.4 / 25.4; 3000 of
-// 12800 39.9 / 31.5, of 16000 43.0 / 34.2, but decodes of as many codes work from the records of this form: the lines stay where
-// they were before either counted as it does.)
+// (The nucleus, us, here / in the wide kernel: 300 rows of 4096 8.6 / 8.5, 1000 of 9600 16.3 / 16.2, of 16000 18.6 / 18.6, of 32128
+// 24.4 / 28.7, 3000 55 / 63; 3000 of 9600 38 / 31, of 12800 41 / 35, of 16000 44 / 38, 8000 of 12800 98 / 77.  The lines are from before
+// either counted as it does; one for steps of many rows of up to 16000 would lie lower, but decodes of as many codes work from
+// the records of this form and go by the same lines, and that has not been measured.)
 static bool by_tile(const as_ctx *ctx, int64_t rows, float k, bool has_k, int32_t top_k)
 {
     const int64_t cus = ctx->num_cus;

@@ -24,8 +24,8 @@
 // in an order, or in integers, that does not depend on which lane comes first.
 //
 // One launch against threshold kernel and sampling kernel before: 1 row of 50257 bf16, p = 0.95 13.0 us (45; 20.8 by tallies),
-// 512 rows of 50257 fp32, p = 0.92 40.3 us (76; the 103 MB alone take 19 at 5.5 TB/s), 230 rows of 256000 bf16, k = 50 then
-// p = 0.95 33.4 us (171; 41.0 with candidates one by one and tiles in turn; 21).
+// 512 rows of 50257 fp32, p = 0.92 39.7 us (76; the 103 MB alone take 19 at 5.5 TB/s), 230 rows of 256000 bf16, k = 50 then
+// p = 0.95 33.7 us (171; 41.0 with candidates one by one and tiles in turn; 21).
 #include <type_traits>
 
 #include "as_common.hpp"
@@ -44,9 +44,10 @@ constexpr int kWaveTopK = 40;            // ... where a wave has the row (64 can
 
 // The largest k that a form takes by the candidate table; above it, by counts.  A table of n candidates costs what their
 // slots and places do, counts cost a pass over the row: on short rows, with no nucleus behind them, counts are ahead sooner
-// (us, table / counts: 4 rows of 1501 bf16, k = 64 11.4 / 7.9, k = 100 13.2 / 7.9; 1000 of 4001 14.4 / 12.8, 17.7 / 12.9, k = 40
-// 11.6 / 12.8; 1000 of 8001 k = 64 15.2 / 15.0; 4 of 16001 k = 100 14.0 / 11.3, 1000 24.1 / 23.3; from 8 pieces a thread on even
-// or behind; with p = 0.9 1000 of 4001 k = 100 17.9 / 19.2).
+// (us, table / counts: 4 rows of 1501 bf16, k = 64 10.4 / 7.8, k = 100 13.0 / 7.9; 1000 of 4001 14.3 / 13.4, 17.7 / 13.3, k = 40
+// 9.8 / 13.2; 1000 of 8001 k = 64 15.7 / 15.8, k = 100 19.2 / 15.9; 4 of 16001 k = 100 14.5 / 11.3, 300 17.3 / 14.6, 1000 23.1 / 23.8; with
+// p = 0.9 1000 of 4001 k = 100 18.1 / 19.1.  fp32, whose pieces are half as many logits, is behind sooner: 4 of 4001 k = 56 8.2 / 7.5,
+// 1000 of 3001 k = 60 13.6 / 11.8).
 template <int NT, int NP> __host__ __device__ constexpr int32_t table_most(int32_t pieces, bool has_p)
 {
     if (NT == 64) return kWaveTopK;
@@ -84,7 +85,7 @@ __device__ __forceinline__ u64 fixed_weight(float e)
 // twice the width), and a window takes fewer neighbours, so that it mostly closes within the 64 threads.  The list is what the
 // waves of a unit leave room for: LDS is given out 1280 bytes at a time, 7680 for five waves a SIMD (16 bytes more of it cost
 // all rows 5 to 10 %), 10240 for four.  With 128 entries flat rows were selected all over: 8000 rows of 8000 bf16, p = 0.9, of
-// a standard deviation of 1 at a temperature of 0.9 249 us, 113 so, 109 in blocks; of 0.3 363, 111, 134.
+// a standard deviation of 1 at a temperature of 0.9 249 us, 98 so, 114 in blocks; of 0.3 363, 122, 134.
 // SHORT: the forms for many short rows, where as many blocks as the unit's waves allow hide each other's block-wide
 // steps: half the LDS, 16 bins an octave where a nucleus's window is named (a bin's mass to a few parts in 10^4; the masses that
 // close it are the same).
@@ -833,6 +834,9 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
     // Whether bf16 logits can be counted by value: those that are positive are expected to hold the nucleus.  Of the weights of
     // half the first pieces the others may be four fifths of what it leaves out (they miss the row's largest logits, so that
     // share is more likely too large than too small; a row that goes wrong is selected the other way, after one more pass).
+    // Between rows that are counted late and those that are counted in vain (us, never counted / up to 0.4 / 0.8 / 1.2 / 2 of that:
+    // 1000 rows of 9001 of a standard deviation of 1.5, p = 0.9 23.6 / 23.6 / 20.5 / 17.6 / 17.6; of 2, p = 0.98 24.3 / 24.3 / 26.7 / 30.1 /
+    // 30.8; of 3 about -3, p = 0.9 24.1 / 22.9 / 18.3 / 17.3 / 17.4, p = 0.98 24.1 / 26.6 / 28.4 / 29.5 / 30.3; of 3, p = 0.5 to 0.98 24 / 17).
     constexpr bool COUNTED = DT == AS_BF16 && !TOPK;
     bool by_value = false;
     {
@@ -1433,7 +1437,8 @@ __global__ __launch_bounds__(NT, WAVES) void wide_step_kernel(StepArgs a, int32_
             // A logit of the window joins the list: from the pieces that a wave has kept, a lane each, at the pass's end, or, where
             // they are more than its table takes, one by one, each waiting for its place.  (us, one by one throughout / so: 512
             // rows of 50257 fp32 40.3 / 39.7, 3000 of 8001 43.2 / 41.0, 8000 of 1501 32.4 / 30.1; flat bf16 rows, which are not counted
-            // by value, 2000 of 50257 149 / 138, 8000 of 8001 93 / 86.  A row that has a unit to itself is better off one by one, with
+            // by value, 2000 of 50257 149 / 138, 8000 of 8001 of a standard deviation of 1 104 / 98, of 0.3, whose lists none of this
+            // makes fit, 118 / 122.  A row that has a unit to itself is better off one by one, with
             // a barrier and a pass over a table less: fp32, 1 of 5003 11.6 / 12.0, 250 12.6 / 12.9, 1 of 20011 14.7 / 15.0.)
             constexpr bool ONE_BY_ONE = NT == 1024 && !MULTI;
             if constexpr (!ONE_BY_ONE) __syncthreads();      // (the tallies give way to tables of pieces)
@@ -1689,21 +1694,22 @@ void launch_form(as_ctx *ctx, int kid, const StepArgs &a, int32_t top_k, float t
 }
 
 // Threads and pieces a thread by the row's pieces of 16 bytes and the number of rows.  With a row per compute unit or
-// fewer, 1024 threads finish it soonest (one row of 50257 bf16: nucleus 21 us, top-k 40 11 us).  With more, smaller
+// fewer, 1024 threads finish it soonest (one row of 50257 bf16: nucleus 13 us, top-k 40 9 us).  With more, smaller
 // blocks that share a unit overlap each other's loads and tails: two blocks of 512 where two fit (nucleus, bf16: 300 rows
-// of 33001 27 us, as blocks of 1024 38; 6439 of them 276, 476; 1000 of 65001 70, 96; fp32 2500 of 33001, which go
-// tile by tile, 129, 200), and with many rows that 256 threads hold, those (nucleus, bf16, 6439 rows: of 9001 108
-// us with 256 x 8, 143 with 512 x 4; of 20001 152 with 256 x 16, 174 with 512 x 8; top-k 40, 2500 of 20003 41, with 512
-// threads 55).  With more than four short rows a unit the blocks are made to fit eight a unit (SHORT; six for k above 128 and
-// for nuclei of two registers' pieces more): 12000 rows of 1281 to 8000 bf16, or half as many fp32, nuclei 1.18 times faster,
-// top-k 1.28 to 1.36, k = 200 1.16; 600 of them no different.  With more rows still, a wave a row: nothing in it waits for
-// another wave, and what a block does in some 25 steps of its waves overlaps over rows instead (us, blocks / waves: nuclei, 1500
-// rows of 1500 bf16 20.5 / 14.9, 600 14.0 / 13.0, 14251 of 1923 119 / 63, 5252 of 3078 57 / 38, 4200 of 8001 58 / 56, 2600 42 /
-// 47; counted by value 900 of 1501 11.0 / 10.3, 1500 of 4001 14.4 / 13.8, 2500 of 8001 23.7 / 24.7, 4500 36.2 / 34.9; k = 40 2100 of 4001 18.6 / 16.3, 1500 of 3000 13.1 / 14.6, 9000 of 6001 53 / 47, 4200 of 8001 31 / 32; counts, k = 1000,
-// 4000 of 1500 30 / 18, 2100 of 4001 23 / 25, 9000 of 6001 79 / 77, 6000 of 4000 fp32 k = 200 38 / 33, but on flat or steep ones 38 / 45 and more).  Those rows
+// of 33001 19 us, as blocks of 1024 24; 6439 of them 178, 284; 1000 of 65001 50, 66; fp32 2500 of 33001, which go
+// tile by tile, 128, 204), and with many rows that 256 threads hold, those (nucleus, bf16, 6439 rows: of 9001 59
+// us with 256 x 8, 95 with 512 x 4; of 20001 99 with 256 x 16, 130 with 512 x 8; top-k 40, 2500 of 20003 33, with 512
+// threads 44).  With more than four short rows a unit the blocks are made to fit eight a unit (SHORT; six for k above 128 and
+// for nuclei of two registers' pieces more): 12000 rows of 1281 to 8000 bf16, or half as many fp32, nuclei 1.17 to 1.22 times faster,
+// top-k 1.38, k = 200 1.09; 600 of them no different.  With more rows still, a wave a row: nothing in it waits for
+// another wave, and what a block does in some 25 steps of its waves overlaps over rows instead (us, blocks / waves: nuclei, 600
+// rows of 1500 bf16 9.5 / 9.4, 1500 15.4 / 11.4, 14251 of 1923 86 / 46, 5252 of 3078 38 / 27, 1500 of 4001 17.1 / 15.4, 2600 of 8001 27.9 /
+// 27.0, 4200 38.5 / 36.1; fp32 6000 of 4000 54 / 39, 1100 of 4001 18.7 / 20.2; k = 40 1500 of 3000 bf16 11.4 / 12.2, 2100 of 4001 15.5 / 14.9,
+// 4200 of 8001 25.5 / 27.6, 9000 of 6001 44 / 39; k = 50, p = 0.73 4816 of 3315 28 / 38; counts, k = 1000, 4000 of 1500 31 / 18, 2100 of
+// 4001 23.7 / 22.8, 9000 of 6001 83 / 72, 6000 of 4000 fp32 k = 200 40 / 35, but on flat or steep ones 38 / 45 and more).  Those rows
 // have a standard deviation of 3 against the temperature; a wave has a shorter list, so flat rows decide whether its line holds:
-// of 0.3 at a temperature of 0.9, nuclei p = 0.9 4000 of 1500 37 / 23, 6000 of 3000 65 / 44, 3000 of 4000 41 / 47, 8000 of 8000
-// 134 / 111; k = 100 then p = 0.9 6000 of 1000 76 / 37, 6000 of 3000 63 / 63, which is behind only where the row is all but
+// of 0.3 at a temperature of 0.9, nuclei p = 0.9 4000 of 1500 44 / 24, 6000 of 3000 72 / 44, 3000 of 4000 46 / 34, 8000 of 8000
+// 134 / 122; k = 100 then p = 0.9 6000 of 1000 75 / 37, 6000 of 3000 62 / 62, which is behind only where the row is all but
 // constant (0.05: 62 / 121).
 template <int DT, bool TOPK>
 void launch_type(as_ctx *ctx, int kid, const StepArgs &a, int32_t top_k, float top_p, float *thr_out)
@@ -1715,7 +1721,7 @@ void launch_type(as_ctx *ctx, int kid, const StepArgs &a, int32_t top_k, float t
     // (compute units' worth of rows beyond which a wave takes a row; counts on rows of more than 768 pieces or with a nucleus behind
     // them on more than 512, and a nucleus after the 64 best of a row of more than 256, never)
     const bool counts = TOPK && top_k > kWaveTopK;
-    const bool table = counts && has_p && top_k <= 64 && most > 64 * 4;      // (4816 rows of 3315, k = 50, p = 0.73: 34 / 38)
+    const bool table = counts && has_p && top_k <= 64 && most > 64 * 4;
     const int64_t never = 1LL << 40;
     const int64_t by_waves = DT == AS_BF16 && a.tokens_out ? 12 : 16;
     const int64_t waves = most <= 64 * 8 ? (table ? never : !TOPK ? 4 : counts ? 12 : 6) : !TOPK ? by_waves : !counts || (!has_p && most <= 64 * 12) ? 20 : never;

@@ -389,7 +389,10 @@ as_status as_estimate_mean(as_ctx *ctx, const int32_t *tokens, int32_t B, int32_
  *     lo[r]    += width[r] * F(tokens[r] - 1)
  *     width[r] *= P(tokens[r])
  * Start from lo = 0, width = 1; after the last token the codes in [lo, lo + width)
- * are the ones as_step decodes to that sequence (up to the rounding of an fp32 code).
+ * are the ones as_step decodes to that sequence (up to the rounding of an fp32 code;
+ * and a nucleus that ends within about 1e-6 of top_p may close a group of equal logits
+ * apart on bf16 rows of whole 16-byte pieces of up to 32768 logits, which as_step
+ * closes by fp32 sums).
  *   logits, rows, ld, temp, top_k, top_p, row_ids, logits_rows   as in as_step_ex
  *   tokens        DEVICE int32[rows]; a token outside [0,V) or outside the kept set
  *                 has probability zero (width becomes 0)
